@@ -354,7 +354,7 @@ kvtc_status kvtc_entropy_decode_batch(const kvtc_entropy* e, const kvtc_entropy_
  *   blocks_dev  n_blocks x {start, n} (device): 1 <= n <= 1024, start + n <= ld; a block outside these
  *               limits gets NaN in its row of the result (the list is not visible to the host)
  *   change_dev  [n_blocks][max_bits] fp64 (device, 8-byte aligned); max_bits in 1..8
- * One workgroup per block with fixed summation order: results are reproducible.  No allocation, no
+ * Fixed summation order: results are reproducible.  No allocation, no
  * synchronisation.  The PCA itself (an eigen-decomposition of a p x p matrix) is not part of this library.
  */
 typedef struct { int32_t start; int32_t n; } kvtc_calib_block;
@@ -365,7 +365,7 @@ kvtc_status kvtc_calib_block_errors(const float* coef_dev, int64_t n_tokens, int
  * Calibration: the one pass over the calibration tokens that the PCA needs (paper, Section "Feature
  * decorrelation", eq. 2: the mean and the SVD of the centred calibration matrix C - mu; the right singular
  * vectors are the eigenvectors of the centred second-moment matrix).  Computes, in double precision and
- * with a fixed summation order (token by token),
+ * with a fixed summation order (results are reproducible),
  *     sum_dev[f]      = sum over tokens of x[t][f]
  *     gram_dev[f][g]  = sum over tokens of x[t][f] * x[t][g]          (all p x p entries)
  * from which the caller forms mu = sum / n and the covariance gram / n - mu mu^T and decomposes it on the

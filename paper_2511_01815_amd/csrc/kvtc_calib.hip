@@ -4,12 +4,11 @@
 // PCA coordinates and every quantiser type, the block of calibration coefficients is quantised as the
 // coder would quantise it, and the squared error is compared with dropping the block.)
 //
-// One workgroup per candidate block, so every sum has a fixed order and the table is reproducible.
-// A group of L = 16 or 64 lanes owns a token (L = 16 for blocks of fewer than 64 coordinates): the
-// token's coefficients of the block sit in registers, the group's min and max come from shuffles, and
-// every width is evaluated from the same registers with the coder's own scalar numerics (fp16 shift
-// rounded down, scale rounded up, code by subtract, multiply by the rounded reciprocal, round to
-// even, clamp).  Errors are accumulated in double from exactly representable terms.
+// A workgroup owns a (candidate block, width) pair, so every sum has a fixed order and the table is
+// reproducible.  Four lanes or more own a token: its coefficients sit in registers, min and max come
+// from lane exchanges, and the errors use the coder's own scalar numerics (fp16 shift rounded down,
+// scale rounded up, code by subtract, multiply by the rounded reciprocal, round to even, clamp),
+// accumulated in double from exactly representable terms.
 //
 // Also here: the first and second moments of the calibration tokens (sum of x and sum of x x^T, in
 // double), the one pass over the calibration data that the PCA needs (paper, Section "Feature
@@ -29,107 +28,155 @@ namespace {
 
 constexpr int kCalibMaxBits = 8;
 constexpr int kCalibMaxN = 1024;
-constexpr int kCalibThreads = 256;
+constexpr int kCalibThreads = 1024;   // 16 waves: the pair with the longest block is the tail of the launch
+constexpr int kCalibTok = 4;          // tokens a lane group works on at once
 
-template <int L>
-__device__ __forceinline__ float group_min(float v) {
-#pragma unroll
-    for (int d = L / 2; d > 0; d >>= 1) v = fminf(v, __shfl_xor(v, d, 64));
+// Minimum or maximum over groups of L lanes (4, 16 or 64), in every lane: register exchanges inside a row of 16
+// lanes (quads, then the mirrored half row, then the mirrored row: each partner holds the other half's result),
+// lane swaps through the LDS crossbar beyond.
+template <int CTRL> __device__ __forceinline__ float dpp_f32(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int L, typename F> __device__ __forceinline__ float group_reduce(float v, F f) {
+    v = f(v, dpp_f32<0xB1>(v));          // quad_perm [1,0,3,2]
+    v = f(v, dpp_f32<0x4E>(v));          // quad_perm [2,3,0,1]
+    if constexpr (L >= 16) {
+        v = f(v, dpp_f32<0x141>(v));     // row_half_mirror
+        v = f(v, dpp_f32<0x140>(v));     // row_mirror
+    }
+    if constexpr (L == 64) {
+        v = f(v, __shfl_xor(v, 16, 64));
+        v = f(v, __shfl_xor(v, 32, 64));
+    }
     return v;
 }
-template <int L>
-__device__ __forceinline__ float group_max(float v) {
-#pragma unroll
-    for (int d = L / 2; d > 0; d >>= 1) v = fmaxf(v, __shfl_xor(v, d, 64));
-    return v;
-}
 
-// PER = coordinates per lane (n <= L * PER)
-template <int L, int PER>
-__device__ __forceinline__ void block_errors(const float* coef, int64_t n_tokens, int64_t ld, int start, int n, int max_bits, double* acc /*[kCalibMaxBits + 1]*/) {
-    const int tid = threadIdx.x;
-    const int grp = tid / L, gl = tid % L, n_grp = kCalibThreads / L;
-    for (int64_t t0 = 0; t0 < n_tokens; t0 += n_grp) {          // every lane runs the same trips: the shuffles need whole waves
-        const int64_t t = t0 + grp;
-        const bool live = t < n_tokens;
-        float d[PER];
-        float lo = __builtin_inff(), hi = -__builtin_inff();
+// This thread's part of sum (d - d_hat)^2 - d^2 = d_hat (d_hat - 2 d) over its tokens, at one width.  L lanes own a
+// token, PER coordinates each (n <= L * PER; FULL: n == L * PER).  kCalibTok tokens at a time, so that the header --
+// two directed fp16 roundings and two correctly rounded divides, as many instructions as eight codes -- is worked out
+// once per token by one lane of four and handed round, and not by all lanes that share the token.
+// d_hat = shift + code * scale is exact in double: all its terms are multiples of 2^-24 below 2^26.
+template <int L, int PER, bool FULL>
+__device__ __forceinline__ double block_error(const float* coef, int64_t t_begin, int64_t n_tokens, int64_t ld, int start, int n, int bits) {
+    constexpr int GRP = kCalibThreads / L, STEP = GRP * kCalibTok;
+    const int tid = threadIdx.x, grp = tid / L, gl = tid % L, lane = tid & 63, mine = lane & 3;
+    const float qmax = (float)((1u << bits) - 1u);
+    auto coord = [&](int k) { return (k >> 2) * 4 * L + 4 * gl + (k & 3); };         // four neighbours at a time: 16-byte loads
+    double e = 0.0;
+    for (int64_t s0 = t_begin; s0 < n_tokens; s0 += STEP) {          // every lane runs the same trips
+        const int64_t t0 = s0 + grp * kCalibTok;
+        float d[kCalibTok][PER];
+        float lo = 0.0f, hi = 0.0f;
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int j = gl + k * L;
-            const bool in = live && j < n;
-            d[k] = in ? coef[t * ld + start + j] : 0.0f;
-            if (in) { lo = fminf(lo, d[k]); hi = fmaxf(hi, d[k]); }
+        for (int s = 0; s < kCalibTok; ++s) {
+            const float* row = coef + (t0 + s < n_tokens ? t0 + s : n_tokens - 1) * ld + start;
+            float l = __builtin_inff(), h = -__builtin_inff();
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                const int j = coord(k);
+                const bool in = FULL || j < n;
+                d[s][k] = in ? row[j] : 0.0f;
+                l = fminf(l, in ? d[s][k] : l);
+                h = fmaxf(h, in ? d[s][k] : h);
+            }
+            l = group_reduce<L>(l, [](float a, float b) { return fminf(a, b); });
+            h = group_reduce<L>(h, [](float a, float b) { return fmaxf(a, b); });
+            if (mine == s) { lo = l; hi = h; }
         }
-        lo = group_min<L>(lo);
-        hi = group_max<L>(hi);
-        if (!live) continue;
-        double energy = 0.0;
+        const GroupQ q = group_header(lo, hi, bits);
 #pragma unroll
-        for (int k = 0; k < PER; ++k)
-            if (gl + k * L < n) energy += (double)d[k] * (double)d[k];
-        acc[0] += energy;
+        for (int s = 0; s < kCalibTok; ++s) {
+            const int from = (lane & ~3) | s;
+            const float shift = __shfl(q.shift, from, 64), inv = __shfl(q.inv, from, 64);
+            const double sh = (double)shift, sc = (double)f16_bits_to_f32((uint16_t)__shfl((int)q.scale16, from, 64));
+            const bool live = t0 + s < n_tokens;
 #pragma unroll
-        for (int b = 1; b <= kCalibMaxBits; ++b) {          // (unrolled: the accumulators stay in registers)
-            if (b > max_bits) break;
-            const GroupQ q = group_header(lo, hi, b);
-            const float qmax = (float)((1u << b) - 1u);
-            const double shift = (double)q.shift, scale = (double)f16_bits_to_f32(q.scale16);
-            double e = 0.0;
-#pragma unroll
-            for (int k = 0; k < PER; ++k)
-                if (gl + k * L < n) {
-                    const double dh = shift + (double)code_of(d[k], q.shift, q.inv, qmax) * scale;
-                    const double r = (double)d[k] - dh;
-                    e += r * r;
-                }
-            acc[b] += e;
+            for (int k = 0; k < PER; ++k) {
+                const double dh = __builtin_fma((double)code_of(d[s][k], shift, inv, qmax), sc, sh);
+                const double term = __builtin_fma(-2.0, (double)d[s][k], dh);
+                const bool in = live && (FULL || coord(k) < n);
+                e = __builtin_fma(in ? dh : 0.0, term, e);
+            }
         }
     }
+    return e;
 }
 
-// change[block][b - 1] = sum over tokens and the block's coordinates of (d - d_hat)^2 - d^2
+// Blocks of more than 256 coordinates are cut in two halves of the tokens, whose sums are ADDED to the zeroed result: with
+// two terms on top of zero the order of arrival cannot show, so the table stays reproducible.
+__device__ __forceinline__ bool calib_long_block(const kvtc_calib_block& b) { return b.n > 256; }
+__device__ __forceinline__ bool calib_bad_block(const kvtc_calib_block& b, int64_t ld) {
+    return b.n < 1 || b.n > kCalibMaxN || b.start < 0 || (int64_t)b.start + b.n > ld;
+}
+
+__global__ void __launch_bounds__(256) calib_zero_kernel(double* change, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) change[i] = 0.0;
+}
+
+// change[block][b - 1] = sum over tokens and the block's coordinates of (d - d_hat)^2 - d^2.  Grid: (block, width, part).
+// What bounds it is vector arithmetic (six fp32 and five half-rate fp64 instructions per coefficient and width) and, at the
+// end, the workgroups of the longest blocks: parts 0 and 1 are the halves of the long blocks, ahead of everything else
+// in the grid, part 2 all others.  175 blocks x 8 widths x 2048 tokens (the default set at 1024 features): 4.59 ms with
+// a workgroup of 256 threads per block that evaluated all widths and 16 or 64 lanes per token, 0.386 ms with one of 1024
+// threads per block and width (half of it for the headers), 0.208 ms with 16 coordinates per lane.
 __global__ void __launch_bounds__(kCalibThreads) calib_block_errors_kernel(const float* coef, int64_t n_tokens, int64_t ld, const kvtc_calib_block* blocks,
                                                                           int max_bits, double* change) {
     __shared__ double red[kCalibThreads];
     const kvtc_calib_block blk = blocks[blockIdx.x];
-    const int start = blk.start, n = blk.n;
+    const int start = blk.start, n = blk.n, bits = (int)blockIdx.y + 1, part = (int)blockIdx.z;
+    double* out = change + (size_t)blockIdx.x * max_bits + blockIdx.y;
     // the list lives on the device, out of the host's sight: a block outside a row (or longer than a lane group holds) gets NaN
-    if (n < 1 || n > kCalibMaxN || start < 0 || (int64_t)start + n > ld) {
-        if ((int)threadIdx.x < max_bits) change[(size_t)blockIdx.x * max_bits + threadIdx.x] = __builtin_nan("");
+    if (calib_bad_block(blk, ld)) {
+        if (threadIdx.x == 0 && part == 2) *out = __builtin_nan("");
         return;
     }
-    double acc[kCalibMaxBits + 1];
-#pragma unroll
-    for (int b = 0; b <= kCalibMaxBits; ++b) acc[b] = 0.0;
-    if (n < 64) block_errors<16, 4>(coef, n_tokens, ld, start, n, max_bits, acc);
-    else if (n <= 256) block_errors<64, 4>(coef, n_tokens, ld, start, n, max_bits, acc);
-    else block_errors<64, 16>(coef, n_tokens, ld, start, n, max_bits, acc);
-    // fixed-order reduction over the workgroup, one width at a time
-    double energy = 0.0;
-#pragma unroll
-    for (int b = 0; b <= kCalibMaxBits; ++b) {
-        if (b > max_bits) break;
-        red[threadIdx.x] = acc[b];
+    if (calib_long_block(blk) != (part < 2)) return;
+    double e;
+    if (part < 2) {
+        const int64_t half = (n_tokens + 1) / 2, b = part ? half : 0, m = part ? n_tokens : half;
+        e = n == 1024 ? block_error<64, 16, true>(coef, b, m, ld, start, n, bits) : block_error<64, 16, false>(coef, b, m, ld, start, n, bits);
+    } else if (n <= 16) {
+        e = n == 16 ? block_error<4, 4, true>(coef, 0, n_tokens, ld, start, n, bits) : block_error<4, 4, false>(coef, 0, n_tokens, ld, start, n, bits);
+    } else if (n <= 64) {
+        e = n == 64 ? block_error<4, 16, true>(coef, 0, n_tokens, ld, start, n, bits) : block_error<4, 16, false>(coef, 0, n_tokens, ld, start, n, bits);
+    } else {
+        e = n == 256 ? block_error<16, 16, true>(coef, 0, n_tokens, ld, start, n, bits) : block_error<16, 16, false>(coef, 0, n_tokens, ld, start, n, bits);
+    }
+    // fixed-order reduction over the workgroup
+    red[threadIdx.x] = e;
+    __syncthreads();
+    for (int d = kCalibThreads / 2; d > 0; d >>= 1) {
+        if ((int)threadIdx.x < d) red[threadIdx.x] += red[threadIdx.x + d];
         __syncthreads();
-        for (int d = kCalibThreads / 2; d > 0; d >>= 1) {
-            if ((int)threadIdx.x < d) red[threadIdx.x] += red[threadIdx.x + d];
-            __syncthreads();
-        }
-        if (b == 0) energy = red[0];
-        else if (threadIdx.x == 0) change[(size_t)blockIdx.x * max_bits + (b - 1)] = red[0] - energy;
-        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        if (part < 2) unsafeAtomicAdd(out, red[0]);
+        else *out = red[0];
     }
 }
 
 
 // ---- moments ------------------------------------------------------------------------------------
-constexpr int kGramTile = 64;      // a workgroup owns a 64 x 64 tile of the second-moment matrix, a thread 4 x 4 of it
-constexpr int kGramTokens = 32;    // tokens staged per step
+// The second-moment matrix is symmetric: a workgroup owns a 32 x 32 tile on or above the diagonal and stores it both ways.
+// Its four waves take a quarter of the tokens each and are summed in wave order at the end.  Products on the fp64
+// matrix cores (v_mfma_f64_16x16x4: 16 x 16 features, 4 tokens), 2 x 2 of them per wave: the even and the odd features
+// of each 32-feature strip, so that a lane's operands for both are one dword (bf16) of its token's row and a wave reads
+// 64 contiguous bytes of four tokens.  Operands go straight from memory to registers, kGramAhead groups of four tokens
+// ahead of their use; strips are re-read from L2.  A diagonal tile also sums its own operands: the first moment.
+// Bound by the fp64 matrix rate: 8192 tokens x 1024 features are 8.9 GFLOP = 0.11 ms at 78 TFLOP/s, and 528 tiles on
+// 256 compute units end as three.  Measured: 1.24 ms with vector fp64 from LDS over the whole matrix, plus 2.03 ms for a
+// separate pass of sums; 0.25 ms for both this way.
+constexpr int kGramStrip = 32;
+constexpr int kGramWaves = 4;
+constexpr int kGramAhead = 8;
 
-template <typename XT> __device__ __forceinline__ double load_as_double(const XT* p);
-template <> __device__ __forceinline__ double load_as_double<uint16_t>(const uint16_t* p) { return (double)bits_f32((uint32_t)*p << 16); }
-template <> __device__ __forceinline__ double load_as_double<float>(const float* p) { return (double)*p; }
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+struct GramPair { double even, odd; };
+__device__ __forceinline__ GramPair gram_pair(uint32_t v) { return {(double)bits_f32(v << 16), (double)bits_f32(v & 0xffff0000u)}; }
+__device__ __forceinline__ GramPair gram_pair(float2 v) { return {(double)v.x, (double)v.y}; }
+template <typename XT> struct GramVec { using type = uint32_t; };
+template <> struct GramVec<float> { using type = float2; };
 
 // element offset of feature f inside a token (blocks of 2^blk_log2 features lie blk_jump elements apart; 0 = contiguous)
 __device__ __forceinline__ int64_t feature_offset(int f, int blk_log2, int64_t blk_jump) {
@@ -137,51 +184,89 @@ __device__ __forceinline__ int64_t feature_offset(int f, int blk_log2, int64_t b
 }
 
 template <typename XT>
-__global__ void __launch_bounds__(256) calib_sum_kernel(const XT* x, int64_t n_tokens, int p, int64_t ld, int blk_log2, int64_t blk_jump, double* sum) {
-    const int f = blockIdx.x * 256 + threadIdx.x;
-    if (f >= p) return;
-    const XT* col = x + feature_offset(f, blk_log2, blk_jump);
-    double s = 0.0;
-    for (int64_t t = 0; t < n_tokens; ++t) s += load_as_double<XT>(col + t * ld);       // token order: a fixed sum
-    sum[f] = s;
-}
+__global__ void __launch_bounds__(64 * kGramWaves, 3) calib_gram_kernel(const XT* x, int64_t n_tokens, int p, int64_t ld, int blk_log2, int64_t blk_jump,
+                                                                     double* sum, double* gram) {
+    using V = typename GramVec<XT>::type;
+    __shared__ double red[kGramWaves][18][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, k = lane >> 4;
+    // tile number -> (bi <= bj): column bj of the triangle starts at bj (bj + 1) / 2
+    const int tile = blockIdx.x;
+    int bj = (int)((__builtin_sqrtf(8.0f * (float)tile + 1.0f) - 1.0f) * 0.5f);
+    while ((int64_t)bj * (bj + 1) / 2 > tile) --bj;
+    while ((int64_t)(bj + 1) * (bj + 2) / 2 <= tile) ++bj;
+    const int bi = tile - (int)((int64_t)bj * (bj + 1) / 2);
+    const bool diag = bi == bj;
+    const XT* xa = x + feature_offset(bi * kGramStrip + 2 * l16, blk_log2, blk_jump);
+    const XT* xb = x + feature_offset(bj * kGramStrip + 2 * l16, blk_log2, blk_jump);
+    const int64_t quarter = (n_tokens + 4 * kGramWaves - 1) / (4 * kGramWaves) * 4;          // whole groups of four tokens
+    const int64_t t_begin = wave * quarter, t_end = t_begin + quarter < n_tokens ? t_begin + quarter : n_tokens;
 
-template <typename XT>
-__global__ void __launch_bounds__(256) calib_gram_kernel(const XT* x, int64_t n_tokens, int p, int64_t ld, int blk_log2, int64_t blk_jump, double* gram) {
-    __shared__ double a[kGramTokens][kGramTile], b[kGramTokens][kGramTile];
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-    const int i0 = blockIdx.y * kGramTile, j0 = blockIdx.x * kGramTile;
-    double acc[4][4];
+    f64x4 acc[2][2];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = 0.0;
-    for (int64_t t0 = 0; t0 < n_tokens; t0 += kGramTokens) {
-#pragma unroll
-        for (int k = 0; k < kGramTokens * kGramTile / 256; ++k) {
-            const int e = tid + k * 256, tt = e / kGramTile, ff = e % kGramTile;
-            const int64_t t = t0 + tt;
-            const bool in = t < n_tokens;
-            a[tt][ff] = in ? load_as_double<XT>(x + t * ld + feature_offset(i0 + ff, blk_log2, blk_jump)) : 0.0;
-            b[tt][ff] = in ? load_as_double<XT>(x + t * ld + feature_offset(j0 + ff, blk_log2, blk_jump)) : 0.0;
+        for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    double s_even = 0.0, s_odd = 0.0;
+    V va[kGramAhead], vb[kGramAhead];
+    auto fetch = [&](int64_t t0, int u) {                        // tokens past the end read as zeros
+        const int64_t t = t0 + 4 * u + k;
+        va[u] = V{};
+        vb[u] = V{};
+        if (t < t_end) {
+            va[u] = *reinterpret_cast<const V*>(xa + t * ld);
+            vb[u] = *reinterpret_cast<const V*>(xb + t * ld);
         }
-        __syncthreads();
-#pragma unroll 4
-        for (int tt = 0; tt < kGramTokens; ++tt) {
-            double ra[4], rb[4];
+    };
 #pragma unroll
-            for (int r = 0; r < 4; ++r) { ra[r] = a[tt][ty * 4 + r]; rb[r] = b[tt][tx * 4 + r]; }
+    for (int u = 0; u < kGramAhead; ++u) fetch(t_begin, u);
+    for (int64_t t0 = t_begin; t0 < t_end; t0 += 4 * kGramAhead) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[r][c] = __builtin_fma(ra[r], rb[c], acc[r][c]);
+        for (int u = 0; u < kGramAhead; ++u) {
+            const GramPair a = gram_pair(va[u]), b = gram_pair(vb[u]);
+            fetch(t0 + 4 * kGramAhead, u);
+            acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.even, b.even, acc[0][0], 0, 0, 0);
+            acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.even, b.odd, acc[0][1], 0, 0, 0);
+            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.odd, b.even, acc[1][0], 0, 0, 0);
+            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.odd, b.odd, acc[1][1], 0, 0, 0);
+            if (diag) {
+                s_even += a.even;
+                s_odd += a.odd;
+            }
         }
-        __syncthreads();
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) gram[(size_t)(i0 + ty * 4 + r) * p + (j0 + tx * 4 + c)] = acc[r][c];
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wave][(a * 2 + b) * 4 + r][lane] = acc[a][b][r];
+    red[wave][16][lane] = s_even;
+    red[wave][17][lane] = s_odd;
+    __syncthreads();
+    auto total = [&](int v, int l) {
+        double s = red[0][v][l];
+#pragma unroll
+        for (int w = 1; w < kGramWaves; ++w) s += red[w][v][l];
+        return s;
+    };
+    // wave r stores accumulator register r: rows 4 r + lane / 16 of the 16 x 16 results, columns lane % 16
+    static_assert(kGramWaves == 4, "a wave per accumulator register");
+    const int r = wave;
+    double m[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) m[a][b] = total((a * 2 + b) * 4 + r, lane);
+    const int i = bi * kGramStrip + 2 * (4 * r + k), j = bj * kGramStrip + 2 * l16;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) *reinterpret_cast<double2*>(gram + (size_t)(i + a) * p + j) = make_double2(m[a][0], m[a][1]);
+    if (!diag) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) *reinterpret_cast<double2*>(gram + (size_t)(j + b) * p + i) = make_double2(m[0][b], m[1][b]);
+    } else if (tid < 32) {                                       // lane l16 + 16 k holds the tokens 4 g + k of feature pair l16
+        const int v = 16 + (tid & 1), l = tid >> 1;
+        sum[bi * kGramStrip + tid] = ((total(v, l) + total(v, l + 16)) + total(v, l + 32)) + total(v, l + 48);
+    }
 }
 
 }  // namespace
@@ -190,20 +275,15 @@ namespace kvtc {
 // x: n_tokens tokens of p features (p a multiple of 64) at the given layout; sum [p], gram [p][p]
 hipError_t launch_calib_moments(const void* x, kvtc_dtype dtype, int64_t n_tokens, int p, int64_t ld, int blk_log2, int64_t blk_jump,
                                 double* sum, double* gram, hipStream_t stream) {
-    const dim3 gs((unsigned)((p + 255) / 256)), gg((unsigned)(p / kGramTile), (unsigned)(p / kGramTile));
-    if (dtype == KVTC_BF16) {
-        hipLaunchKernelGGL(calib_sum_kernel<uint16_t>, gs, dim3(256), 0, stream, static_cast<const uint16_t*>(x), n_tokens, p, ld, blk_log2, blk_jump, sum);
-        hipLaunchKernelGGL(calib_gram_kernel<uint16_t>, gg, dim3(256), 0, stream, static_cast<const uint16_t*>(x), n_tokens, p, ld, blk_log2, blk_jump, gram);
-    } else {
-        hipLaunchKernelGGL(calib_sum_kernel<float>, gs, dim3(256), 0, stream, static_cast<const float*>(x), n_tokens, p, ld, blk_log2, blk_jump, sum);
-        hipLaunchKernelGGL(calib_gram_kernel<float>, gg, dim3(256), 0, stream, static_cast<const float*>(x), n_tokens, p, ld, blk_log2, blk_jump, gram);
-    }
+    const unsigned strips = (unsigned)(p / kGramStrip);
+    const dim3 grid(strips * (strips + 1) / 2), threads(64 * kGramWaves);
+    if (dtype == KVTC_BF16)
+        hipLaunchKernelGGL(calib_gram_kernel<uint16_t>, grid, threads, 0, stream, static_cast<const uint16_t*>(x), n_tokens, p, ld, blk_log2, blk_jump, sum, gram);
+    else
+        hipLaunchKernelGGL(calib_gram_kernel<float>, grid, threads, 0, stream, static_cast<const float*>(x), n_tokens, p, ld, blk_log2, blk_jump, sum, gram);
     return hipGetLastError();
 }
 }  // namespace kvtc
-
-namespace {
-}  // namespace
 
 extern "C" {
 
@@ -216,7 +296,9 @@ kvtc_status kvtc_calib_block_errors(const float* coef_dev, int64_t n_tokens, int
     if (ld < 1) return set_error(KVTC_E_ARG, "kvtc_calib_block_errors: ld=%lld", (long long)ld);
     if ((reinterpret_cast<uintptr_t>(coef_dev) & 3u) || (reinterpret_cast<uintptr_t>(change_dev) & 7u) || (reinterpret_cast<uintptr_t>(blocks_dev) & 3u))
         return set_error(KVTC_E_ARG, "kvtc_calib_block_errors: misaligned buffer");
-    hipLaunchKernelGGL(calib_block_errors_kernel, dim3((unsigned)n_blocks), dim3(kCalibThreads), 0, static_cast<hipStream_t>(stream), coef_dev, n_tokens, ld,
+    const int64_t n_out = (int64_t)n_blocks * max_bits;
+    hipLaunchKernelGGL(calib_zero_kernel, dim3((unsigned)(n_out < 262144 ? (n_out + 255) / 256 : 1024)), dim3(256), 0, static_cast<hipStream_t>(stream), change_dev, n_out);
+    hipLaunchKernelGGL(calib_block_errors_kernel, dim3((unsigned)n_blocks, (unsigned)max_bits, 3), dim3(kCalibThreads), 0, static_cast<hipStream_t>(stream), coef_dev, n_tokens, ld,
                        blocks_dev, max_bits, change_dev);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return set_error(KVTC_E_HIP, "kvtc_calib_block_errors: launch failed: %s", hipGetErrorString(err));

@@ -1,0 +1,56 @@
+"""The calibration passes at the edges of what their kernels are built for: block sizes around each lane-group width (16, 64,
+256, 1024 coordinates), token counts around the groups of four and the split of long blocks in two halves, feature counts of
+one, two and several strips; against the oracle's scalar numerics and NumPy in float64."""
+import numpy as np
+import pytest
+import torch
+
+import kvtc_oracle as ko
+import paper_2511_01815_amd as kv
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("n_tok", [1, 3, 4, 5, 63, 66, 129, 1030])
+def test_block_errors_at_every_lane_group_edge(n_tok):
+    rng = np.random.default_rng(n_tok)
+    ld = 1037
+    P = (rng.standard_normal((n_tok, ld)) * np.arange(1, ld + 1) ** -0.6).astype(np.float32)
+    cand = [(s, n) for n in (1, 3, 15, 16, 17, 63, 64, 65, 255, 256, 257, 1000, 1023, 1024) for s in (0, ld - n)]
+    blocks = torch.tensor(cand, dtype=torch.int32, device=DEV)
+    out = torch.full((len(cand), 8), -7.0, dtype=torch.float64, device=DEV)
+    pd = torch.from_numpy(P).to(DEV)
+    for _ in range(2):
+        kv.kvtc_calib_block_errors(pd, n_tok, ld, blocks, len(cand), 8, out)
+        first = out.clone() if _ == 0 else first
+    torch.cuda.synchronize()
+    assert torch.equal(out, first)                       # the same bits again
+    got = out.cpu().numpy()
+    for i, (s, n) in enumerate(cand):
+        d = P[:, s:s + n]
+        energy = float((d.astype(np.float64) ** 2).sum())
+        for b in range(1, 9):
+            sh, sc, codes = ko.quantise_group(d, b)
+            dh = ko.dequantise_group(sh, sc, codes).astype(np.float64)
+            ref = float(((d - dh) ** 2).sum()) - energy
+            # the same terms in another order: n_tok * n sums of double precision, each term within energy's scale
+            assert abs(got[i, b - 1] - ref) <= 1e-12 * (energy + abs(ref)), (n_tok, s, n, b)
+
+
+@pytest.mark.parametrize("n_tok,p", [(1, 64), (3, 64), (4, 128), (17, 192), (130, 64), (515, 320)])
+def test_moments_at_strip_and_token_edges(n_tok, p):
+    rng = np.random.default_rng(n_tok + p)
+    for dtype in (kv.KVTC_BF16, kv.KVTC_F32):
+        X = rng.standard_normal((n_tok, p + 8)).astype(np.float32)
+        xd = torch.from_numpy(X).to(DEV)
+        if dtype == kv.KVTC_BF16:
+            xd = xd.to(torch.bfloat16)
+        x64 = xd.double().cpu().numpy()[:, :p]
+        s = torch.full((p,), -7.0, dtype=torch.float64, device=DEV)
+        g = torch.full((p, p), -7.0, dtype=torch.float64, device=DEV)
+        kv.kvtc_calib_moments(xd, dtype, n_tok, p, kv.layout(p + 8), s, g)
+        torch.cuda.synchronize()
+        # double-precision sums of n_tok terms: n_tok * 2^-53 of the sum of magnitudes at most
+        assert np.all(np.abs(s.cpu().numpy() - x64.sum(0)) <= n_tok * 2.0 ** -52 * np.abs(x64).sum(0))
+        assert np.all(np.abs(g.cpu().numpy() - x64.T @ x64) <= n_tok * 2.0 ** -52 * (np.abs(x64).T @ np.abs(x64)))
