@@ -9,7 +9,9 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvtc.so")
-SOURCES = ["kvtc_api.hip", "kvtc_encode.hip", "kvtc_decode.hip", "kvtc_fp8.hip", "kvtc_rope.hip", "kvtc_probe.hip", "kvtc_entropy.hip", "kvtc_calib.hip"]
+# (source, object, macros): the decode kernels' many widths are compiled in parts, side by side
+SOURCES = [(f"{s}.hip", f"{s}.o", []) for s in ("kvtc_api", "kvtc_encode", "kvtc_fp8", "kvtc_rope", "kvtc_probe", "kvtc_entropy", "kvtc_calib")]
+SOURCES += [("kvtc_decode.hip", f"kvtc_decode_{k}.o", [f"-DKVTC_DECODE_PART={k}"]) for k in range(6)]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
@@ -28,9 +30,10 @@ def build(verbose: bool = False, extra_flags=()) -> str:
     os.makedirs(objdir, exist_ok=True)
     hipcc = _hipcc()
 
-    def compile_one(src: str) -> str:
-        obj = os.path.join(objdir, src.replace(".hip", ".o"))
-        cmd = [hipcc, *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
+    def compile_one(source) -> str:
+        src, obj, macros = source
+        obj = os.path.join(objdir, obj)
+        cmd = [hipcc, *FLAGS, *macros, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
         res = subprocess.run(cmd, capture_output=True, text=True)
         err = "\n".join(l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l)
         if res.returncode != 0:
@@ -39,8 +42,8 @@ def build(verbose: bool = False, extra_flags=()) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        objs = list(ex.map(compile_one, SOURCES))
+    with ThreadPoolExecutor(max_workers=os.cpu_count() or 4) as ex:
+        objs = list(ex.map(compile_one, SOURCES[::-1]))
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:

@@ -602,17 +602,20 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
     a.dec_sum_ld = sum_ld;
     const int slots = cu_count() * plan->h.dec_wgs;
     // A tensor short enough for all its 128-token tiles to run at once takes the variant with one token
-    // tile per wave (same plan data: it depends on the padded width only).
+    // tile per wave (same plan data: it depends on the padded width only).  The workgroups beyond a launch's tiles
+    // share the tiles' features (at most one workgroup per 64 of them).
+    const int64_t spans = plan->h.p / 64;
     const int64_t tiles_short = (n_tokens + kDecShortTile - 1) / kDecShortTile;
     hipError_t e;
     if (plan->h.dec_tt == 2 && tiles_short <= slots) {
         const DecLayout lay = decode_layout(decode_rec_bytes(1, plan->h.rec_dwords), plan->h.dec_ring_lds, plan->h.dec_wgs);
         a.dec_ring_off = lay.ring_off;
         a.dec_short = 1;
-        e = launch_decode(a, dtype, 100 + plan->h.dec_cls, (int)tiles_short, lay.lds_bytes, static_cast<hipStream_t>(stream));
+        const int grid = (int)(tiles_short * spans < slots ? tiles_short * spans : slots);
+        e = launch_decode(a, dtype, 100 + plan->h.dec_cls, grid, lay.lds_bytes, static_cast<hipStream_t>(stream));
     } else {
         const int64_t tiles = (n_tokens + plan->h.dec_tok_wg - 1) / plan->h.dec_tok_wg;
-        const int grid = (int)(tiles < slots ? tiles : slots);
+        const int grid = (int)(tiles * spans < slots ? tiles * spans : slots);
         const DecLayout lay = decode_layout(plan->h.dec_rec_lds, plan->h.dec_ring_lds, plan->h.dec_wgs);
         a.dec_ring_off = lay.ring_off;
         e = launch_decode(a, dtype, plan->h.dec_tt * 100 + plan->h.dec_cls, grid, lay.lds_bytes, static_cast<hipStream_t>(stream));

@@ -113,13 +113,16 @@ __device__ __forceinline__ int issue_records(const KernelArgs& a, const TileRef&
     return n;
 }
 
+// The 32-feature tiles [begin, end) a workgroup sweeps, both even: all of a token's, or a part of them (below).
+struct FeatureSpan { int begin, end; };
+
 // One workgroup tile.  The work area holds the tile's block table and record image, landed and
 // published.  With `prefetch` the ring does not overlap them: the first basis slab is requested
 // before unpacking, and the records of the workgroup's next tile (if any) are requested during
 // the first step of the feature sweep.
 template <int NCT, int TT, typename OT, int ACC>
 __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr, const KernelArgs& a, uint4* work, uint4* ring,
-                                            bool prefetch, bool has_next, const TileRef& next, const PlanDec& Pn) {
+                                            bool prefetch, bool has_next, const TileRef& next, const PlanDec& Pn, FeatureSpan fs) {
     constexpr int TOK_W = 32 * TT;
     constexpr int TOK_WG = 4 * TOK_W;
     constexpr int SLAB_U4 = 2 * NCT * 64;          // one 32-feature tile of V_kept
@@ -130,13 +133,12 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
-    const int p = P.p;
     const int T = tr.n_tokens;
     const int tok_tile0 = tr.tile * TOK_WG;
     const int rd = P.rec_dwords;
     const int n_valid = min(TOK_WG, T - tok_tile0);
     const RecImage im = rec_image(rd, tr.offset + (uint64_t)tok_tile0 * (uint64_t)rd * 4ull);
-    const int n_ft = p / 32;                                   // even: p is a multiple of 64
+    const int ft_begin = fs.begin, n_ft = fs.end;              // 32-feature tiles, both even: p is a multiple of 64
 
     // basis slab of feature tile ft -> ring stage; wave 0 also moves the tile's mu entries
     const uint4* vg = P.v_dec;
@@ -150,7 +152,7 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
                 dma16_async(vsrc + i * kThreads, (uint32_t)tid * 16u, dst + (uint32_t)(i * kThreads + wave * 64) * 16u);
         if (wave == 0 && lane < kMuU4) dma16_async(vsrc + SLAB_U4, (uint32_t)lane * 16u, dst + (uint32_t)SLAB_U4 * 16u);
     };
-    if (prefetch) issue_slab(0, 0);
+    if (prefetch) issue_slab(ft_begin, 0);
 
     // ---- each lane unpacks its blocks from the record image ------------------------------
     // A lane owns one token (l32) and, per 32-coordinate tile, the 16-coordinate block of its half h.
@@ -198,7 +200,7 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
     if (P.code_bits_max <= 8) unpack(std::true_type()); else unpack(std::false_type());
     if (!prefetch) {
         __syncthreads();          // record image is dead; the ring reuses its space
-        issue_slab(0, 0);
+        issue_slab(ft_begin, 0);
     }
     wait_vmem<0>();
     __syncthreads();              // slab 0 is published (and, with prefetch, the record image is dead)
@@ -245,13 +247,13 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
     // operations complete in issue order, so it is enough that no more operations are in flight
     // than this wave issued after that slab's transfers (the next tile's records in the first
     // step, the stores in odd steps).
-    for (int f0 = 0; f0 < n_ft; f0 += 2) {
+    for (int f0 = ft_begin; f0 < n_ft; f0 += 2) {
         f32x16 acc0[TT], acc1[TT];
         issue_slab(f0 + 1, 1);
         int n_rec = 0;
-        if (f0 == 0 && has_next) n_rec = issue_records(a, next, Pn, lds_offset(work));
+        if (f0 == ft_begin && has_next) n_rec = issue_records(a, next, Pn, lds_offset(work));
         tile_step(0, acc0);
-        if (f0 == 0) wait_vmem_dyn(n_rec); else wait_vmem<0>();
+        if (f0 == ft_begin) wait_vmem_dyn(n_rec); else wait_vmem<0>();
         __syncthreads();
 
         const bool more = f0 + 2 < n_ft;
@@ -332,18 +334,18 @@ template <int TT, int CLS> constexpr int dec_wgs_per_cu() { return CLS <= 4 ? 3 
 // The widths built for each class; a plan's tile count is rounded up to the next of them at plan creation.
 template <int CLS, int TT, typename OT, int ACC>
 __device__ __forceinline__ void decode_tile_of_class(const PlanDec& P, const TileRef& tr, const KernelArgs& a, uint4* work, uint4* ring,
-                                                     bool prefetch, bool has_next, const TileRef& next, const PlanDec& Pn) {
-#define KVTC_W(N) case N: decode_tile<N, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn); break;
+                                                     bool prefetch, bool has_next, const TileRef& next, const PlanDec& Pn, FeatureSpan fs) {
+#define KVTC_W(N) case N: decode_tile<N, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn, fs); break;
     if constexpr (CLS == 4) {
-        switch (P.dec_nct) { KVTC_W(2) default: decode_tile<4, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn); break; }
+        switch (P.dec_nct) { KVTC_W(2) default: decode_tile<4, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn, fs); break; }
     } else if constexpr (CLS == 10) {
-        switch (P.dec_nct) { KVTC_W(6) KVTC_W(7) KVTC_W(8) KVTC_W(9) default: decode_tile<10, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn); break; }
+        switch (P.dec_nct) { KVTC_W(6) KVTC_W(7) KVTC_W(8) KVTC_W(9) default: decode_tile<10, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn, fs); break; }
     } else if constexpr (CLS == 18) {
-        switch (P.dec_nct) { KVTC_W(12) KVTC_W(16) KVTC_W(17) default: decode_tile<18, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn); break; }
+        switch (P.dec_nct) { KVTC_W(12) KVTC_W(16) KVTC_W(17) default: decode_tile<18, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn, fs); break; }
     } else if constexpr (CLS == 24) {
-        switch (P.dec_nct) { KVTC_W(20) default: decode_tile<24, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn); break; }
+        switch (P.dec_nct) { KVTC_W(20) default: decode_tile<24, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn, fs); break; }
     } else {
-        decode_tile<32, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn);
+        decode_tile<32, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next, next, Pn, fs);
     }
 #undef KVTC_W
 }
@@ -354,14 +356,28 @@ __global__ void __launch_bounds__(kThreads, (dec_wgs_per_cu<TT, CLS>())) kvtc_de
     uint32_t* tile_start = reinterpret_cast<uint32_t*>(smem);
     uint4* work = smem + kJobTableBytes / 16 + 1;
     const uint32_t total = build_tile_table<false>(a, TT * 100 + CLS, tile_start, reinterpret_cast<uint32_t*>(work));
-    const TileRange mine = my_tiles(total);
+    // Few tiles: every token tile is given to `parts` workgroups, each of which unpacks it again and sweeps its own share
+    // of the features, so that a launch of a few tiles spreads over the chip instead of a lone workgroup walking all
+    // features (48 tokens of 1024 features: 27 us -> 10).  Features are independent of each other: the results are the same bits.
+    const uint32_t parts = total ? gridDim.x / total : 0u;
+    TileRange mine = my_tiles(total);
+    uint32_t part = 0u;
+    if (parts > 1u) {
+        mine = TileRange{blockIdx.x / parts, total, total};       // one tile each
+        part = blockIdx.x % parts;
+    }
     uint32_t tile = mine.first;
     if (tile >= mine.end) return;
+    auto span = [&](const PlanDec& P) {
+        const uint32_t pairs = (uint32_t)P.p / 64u, n = min(max(parts, 1u), pairs);
+        return part < n ? FeatureSpan{(int)(2u * (part * pairs / n)), (int)(2u * ((part + 1u) * pairs / n))} : FeatureSpan{0, 0};
+    };
     const bool prefetch = a.dec_ring_off != 0u;
     uint4* ring = work + a.dec_ring_off / 16u;
     TileRef tr = find_tile(a, tile_start, tile);
     PlanDec P = load_plan_dec(a.plans + tr.plan);
     P.dec_tok_wg = 4 * 32 * TT;              // this variant's tile (the descriptor holds the bulk variant's)
+    if (span(P).end == 0) return;
     issue_records(a, tr, P, lds_offset(work));
     wait_vmem<0>();
     __syncthreads();
@@ -375,7 +391,7 @@ __global__ void __launch_bounds__(kThreads, (dec_wgs_per_cu<TT, CLS>())) kvtc_de
             Pn = load_plan_dec(a.plans + trn.plan);
             Pn.dec_tok_wg = 4 * 32 * TT;
         }
-        decode_tile_of_class<CLS, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next && prefetch, trn, Pn);
+        decode_tile_of_class<CLS, TT, OT, ACC>(P, tr, a, work, ring, prefetch, has_next && prefetch, trn, Pn, span(P));
         if (!has_next) break;
         tile = next;
         tr = trn;
@@ -390,26 +406,47 @@ __global__ void __launch_bounds__(kThreads, (dec_wgs_per_cu<TT, CLS>())) kvtc_de
 
 // (token tiles per wave, class): the bulk kernels, then the same classes with one token tile per wave (128-token
 // workgroup tiles) for single tensors short enough to run all their tiles at once -- a workgroup without a
-// neighbour is bound by its own instruction stream, and this halves it
-#define KVTC_DEC_VARIANTS(X) X(2, 4) X(2, 10) X(2, 18) X(2, 24) X(1, 32) X(1, 4) X(1, 10) X(1, 18) X(1, 24)
+// neighbour is bound by its own instruction stream, and this halves it.
+// The file is compiled once per part, each holding some of the classes: the parts compile side by side.
+#define KVTC_DEC_PART_0(X) X(2, 4) X(1, 4) X(1, 32)
+#define KVTC_DEC_PART_1(X) X(2, 10) X(1, 10)
+#define KVTC_DEC_PART_2(X) X(2, 18)
+#define KVTC_DEC_PART_3(X) X(1, 18)
+#define KVTC_DEC_PART_4(X) X(2, 24)
+#define KVTC_DEC_PART_5(X) X(1, 24)
 
-// key = 100 * TT + CLS
-hipError_t launch_decode(const KernelArgs& a, kvtc_dtype dtype, int key, int grid, size_t lds_bytes, hipStream_t stream) {
-    const void* fn = nullptr;
+#define KVTC_CAT2(A, B) A##B
+#define KVTC_CAT(A, B) KVTC_CAT2(A, B)
+
+// The kernel of a key (100 * TT + CLS) if this part holds it, else null.
+const void* KVTC_CAT(decode_kernel_part_, KVTC_DECODE_PART)(int key, kvtc_dtype dtype, int accumulate) {
     switch (key) {
 #define KVTC_X(TT, CLS)                                                                                        \
     case (TT) * 100 + (CLS):                                                                                   \
         if (dtype == KVTC_BF16)                                                                                \
-            fn = a.dec_accumulate == 2 ? reinterpret_cast<const void*>(&kvtc_decode_kernel<uint16_t, TT, CLS, 2>) \
-                                       : reinterpret_cast<const void*>(&kvtc_decode_kernel<uint16_t, TT, CLS>); \
-        else                                                                                                   \
-            fn = a.dec_accumulate == 1 ? reinterpret_cast<const void*>(&kvtc_decode_kernel<float, TT, CLS, 1>) \
-                                       : reinterpret_cast<const void*>(&kvtc_decode_kernel<float, TT, CLS>);   \
-        break;
-        KVTC_DEC_VARIANTS(KVTC_X)
+            return accumulate == 2 ? reinterpret_cast<const void*>(&kvtc_decode_kernel<uint16_t, TT, CLS, 2>)  \
+                                   : reinterpret_cast<const void*>(&kvtc_decode_kernel<uint16_t, TT, CLS>);    \
+        return accumulate == 1 ? reinterpret_cast<const void*>(&kvtc_decode_kernel<float, TT, CLS, 1>)         \
+                               : reinterpret_cast<const void*>(&kvtc_decode_kernel<float, TT, CLS>);
+        KVTC_CAT(KVTC_DEC_PART_, KVTC_DECODE_PART)(KVTC_X)
 #undef KVTC_X
-        default: return hipErrorInvalidValue;
+        default: return nullptr;
     }
+}
+
+#if KVTC_DECODE_PART == 0
+
+#define KVTC_DEC_PARTS(X) X(0) X(1) X(2) X(3) X(4) X(5)
+#define KVTC_X(P) const void* decode_kernel_part_##P(int key, kvtc_dtype dtype, int accumulate);
+KVTC_DEC_PARTS(KVTC_X)
+#undef KVTC_X
+
+hipError_t launch_decode(const KernelArgs& a, kvtc_dtype dtype, int key, int grid, size_t lds_bytes, hipStream_t stream) {
+    const void* fn = nullptr;
+#define KVTC_X(P) if (!fn) fn = decode_kernel_part_##P(key, dtype, a.dec_accumulate);
+    KVTC_DEC_PARTS(KVTC_X)
+#undef KVTC_X
+    if (!fn) return hipErrorInvalidValue;
     hipError_t e = allow_full_lds(fn);
     if (e != hipSuccess) return e;
     KernelArgs args = a;
@@ -425,5 +462,7 @@ int decode_rec_bytes(int tt, int rec_dwords) {
 }
 int decode_ring_bytes(int nct) { return kDecStages * (2 * nct * 64 + kMuU4) * 16; }
 int decode_stage_u4(int nct) { return 2 * nct * 64 + kMuU4; }
+
+#endif  // KVTC_DECODE_PART == 0
 
 }  // namespace kvtc
