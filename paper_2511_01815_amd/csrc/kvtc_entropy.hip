@@ -3,21 +3,19 @@
 // quantiser's byte array goes through a lossless coder on the GPU; the paper uses a general-purpose
 // DEFLATE, this library a byte-wise entropy coder matched to the records' fixed layout.)
 //
-// Work decomposition: a wavefront owns a chunk of 64 tokens, a lane one token; blockIdx.y is the job
-// (tensor) of a batched call.  The code tables are data (256 code lengths per byte position and table
-// set, from calibration); canonical codes and the decoding tables are derived from them on the host at
+// Work decomposition: a wavefront owns chunks of 64 tokens; blockIdx.y is the job (tensor) of a batched call, so a
+// workgroup's chunks share one table set, which it keeps in LDS.  The code tables are data (256 code lengths per byte
+// position and table set, from calibration); canonical codes and the decoding tables are derived from them on the host at
 // creation.
-//   encode = three launches: (1) every lane sums the code lengths of its record's bytes -> len_bits[]
-//   and the chunk sizes, written into the container's own directory; (2) a workgroup per job turns the
-//   sizes into offsets; (3) every lane writes its code string into the chunk's image in LDS at the bit
-//   offset the lengths before it give (whole dwords OR-ed in), and the wave copies the image out.
-//   decode = one launch: the chunk's bit string is staged in LDS and every lane walks its own string.
-//   The walk depends on nothing but arithmetic: with canonical codes the next 12 bits, read as a
-//   number with the first bit on top, are below limit[L] exactly when the code has at most L bits
-//   (limit[] = 12 wave-uniform numbers per byte position), so a symbol's length is a count of
-//   comparisons, and its rank among the position's symbols follows from one more table entry; the
-//   ranks are turned into byte values afterwards, by gathers that wait for nothing.  Rows are
-//   collected in LDS and copied out whole.
+//   encode = three launches: (1) code lengths -> len_bits[] and the chunk sizes, written into the container's own
+//   directory; (2) a workgroup per job turns the sizes into offsets; (3) the code strings.  In (1) and (3) a chunk is the
+//   flat run of its records' bytes, dealt to the lanes in 16-byte pieces (coalesced loads, no staging, no idle lanes
+//   whatever the record size): a chunk's bit string is the concatenation of its bytes' codes in that very order, so one
+//   prefix sum over the wave places every lane's string.
+//   decode = one launch: a lane walks the string of one token, all lanes at the same byte position.  A code's length is
+//   what a 256-entry table says for the next 8 bits (9 for every longer code) plus a count of comparisons: with canonical
+//   codes the next 12 bits, read as a number with the first bit on top, are below limit[L] exactly when the code has at most
+//   L bits.  Length and bits give the symbol's rank, the rank the symbol; the walk waits for neither.
 // Nothing is allocated: the directory lives in the output buffer.
 #include <hip/hip_runtime.h>
 
@@ -34,53 +32,42 @@ using namespace kvtc;
 
 struct kvtc_entropy {
     int record_bytes, n_tables;
-    void* blob;                 // device: enc[n_tables][R][256] u16, then dec[n_tables][R] DecPos
-    const uint16_t* enc_dev;    // reversed code | length << 12
-    const void* dec_dev;        // per byte position: limits, rank offsets, symbols by rank
+    void* blob;                 // device: the four tables below
+    const uint16_t* enc_dev;    // [n_tables][R][256] reversed code | length << 12
+    const uint8_t* len_dev;     // [n_tables][R][256] length
+    const uint8_t* dec_dev;     // [n_tables][R][kDecRow], staged in LDS by the decoder
+    const uint32_t* lim_dev;    // [n_tables][R][4]
 };
 
 namespace {
 
 constexpr int kMaxLen = 12;
 constexpr int kChunk = 64;
-constexpr int kMaxRecord = 576;       // bytes: a wave's images (chunk string + rows) must fit the LDS
+constexpr int kMaxRecord = 576;       // bytes
 constexpr int kMaxEntropyJobs = 65535;
 
 __host__ __device__ inline uint32_t chunk_image_dwords(int R) { return (uint32_t)(kChunk * R * kMaxLen + 31) / 32u; }   // worst case
-__host__ __device__ inline uint32_t row_stride_dwords(int R) { return (uint32_t)R / 4u + 1u; }
 __host__ __device__ inline uint64_t header_bytes(int64_t n_chunks) { return 4ull * (uint64_t)(n_chunks + 1) + 2ull * kChunk * (uint64_t)n_chunks; }
 
-// LDS of a launch.  The kernel that writes the code strings holds, per wave, the chunk's image (worst case) and its rows;
-// the decoder its rows and, per workgroup, 64 bytes of tables per byte position.  Waves per workgroup: the count (1..4) that
-// lets the most waves share a compute unit's 160 KB -- a wave alone on its SIMD has nothing to hide its latencies behind.
-inline size_t lds_bytes(int R, int waves, bool decode) {
-    const size_t rows = (size_t)kChunk * row_stride_dwords(R) * 4;
-    return decode ? (size_t)waves * rows + (size_t)R * 64 : (size_t)waves * ((size_t)chunk_image_dwords(R) * 4 + rows);
-}
-inline int waves_per_wg(int R, bool decode) {
-    int best = 1;
-    size_t best_cu = 0;
-    for (int n = 1; n <= 4; ++n) {
-        const size_t b = lds_bytes(R, n, decode);
-        if (b > 150u * 1024u) break;
-        size_t wgs = (size_t)kLdsBudget / b;
-        if (wgs * n > 32) wgs = 32 / n;                 // a compute unit holds 32 waves at most
-        if (wgs * n > best_cu) { best_cu = wgs * n; best = n; }
-    }
-    return best;
-}
+// Tables in LDS: the rows of successive byte positions are a dword apart from a multiple of the banks, so that lanes that
+// look up like bytes of different positions do not all meet on one bank.
+constexpr int kLenRow = 256 + 4, kEncRow = 512 + 4;                          // bytes per byte position
+constexpr int kImageDw = 392;         // a wave's part of the bit string: 64 pieces of 16 codes of at most 12 bits, a carried dword, whole 16 bytes
+constexpr int kLdsMost = kLdsBudget - 1024;
+static_assert(kMaxRecord * kLenRow + 16 * kChunk * 4 <= kLdsMost, "the length table of every record size fits");
 
 // Decoding data of one byte position.  Codes are canonical: those of L bits are first[L] .. first[L] + count[L] - 1.
-//   limit[L-1] = (first[L] + count[L]) << (12 - L): the next 12 bits of the string, first bit on top, are below it exactly
-//                when the code has at most L bits (non-decreasing in L; entries 12..15 are never reached)
-//   off[L-1]   = first[L] - (number of symbols with shorter codes): rank of the symbol = (those 12 bits >> (12 - L)) - off
-//   sym[rank]  = byte value, symbols ordered by (length, value)
-struct DecPos {
-    uint16_t limit[16];
-    int16_t off[16];
-    uint8_t sym[256];
-};
-static_assert(sizeof(DecPos) == 320, "layout");
+// In LDS, kDecRow bytes: [256] by the next 8 bits of the string, the code's length, 9 for every code of 9 bits or more (10 .. 12 if none is
+// shorter);
+// [256] symbols by rank, i.e. ordered by (length, value); [16] at L: first[L] - (number of symbols with shorter codes), modulo
+// 256, so that the rank of a code of L bits is its value minus this.  (All lanes look up the same position at a time: rows
+// need no padding.)  Records too long for one table in LDS are decoded in segments of kDecSegment bytes.
+// In scalar registers, four dwords: ((first[L] + count[L]) << (32 - L)) - 1 for L = 9, 10, 11: a string whose next 32 bits, first
+// bit on top, exceed it begins with a code of more than L bits.
+// A wave collects kDecBatch dwords of its 64 rows behind the table, at a pitch of whole 16-byte pieces.
+constexpr int kDecSym = 256, kDecOff = 512, kDecRow = 528;
+constexpr int kDecSegment = 144, kDecBatch = 16, kDecPitch = 20;
+static_assert(kDecSegment % 16 == 0 && kDecSegment * kDecRow + 16 * kChunk * kDecPitch * 4 <= kLdsMost, "a segment's table and 16 waves' rows fit");
 
 struct EntropyArgs {
     const kvtc_entropy_job* jobs;     // device, or nullptr -> `single`
@@ -92,8 +79,11 @@ struct EntropyArgs {
     uint64_t coded_total;
     uint64_t* coded_bytes;            // encode: [n_jobs] container lengths
     const uint16_t* enc;
-    const DecPos* dec;
+    const uint8_t* len;
+    const uint8_t* dec;
+    const uint32_t* lim;
     int32_t R, n_tables;
+    int32_t chunks_per_wave;          // chunks a wave takes one after the other, so that a workgroup's tables serve several
     int64_t max_tokens;               // the launch covers this many tokens per job; a longer job is left alone
 };
 
@@ -106,8 +96,7 @@ struct JobView {
     uint16_t* len_bits;
     uint8_t* payload;          // ... and payload
     uint64_t payload_cap;
-    const uint16_t* enc;
-    const DecPos* dec;
+    size_t table;              // first byte position of the job's table set
 };
 __device__ __forceinline__ JobView job_view(const EntropyArgs& a, int j) {
     const kvtc_entropy_job jb = a.jobs ? a.jobs[j] : a.single;
@@ -125,68 +114,125 @@ __device__ __forceinline__ JobView job_view(const EntropyArgs& a, int j) {
     v.len_bits = reinterpret_cast<uint16_t*>(v.chunk_off + v.n_chunks + 1);
     v.payload = a.coded + jb.coded_off + hdr;
     v.payload_cap = jb.coded_cap - hdr;
-    v.enc = a.enc + (size_t)jb.table * a.R * 256;
-    v.dec = a.dec + (size_t)jb.table * a.R;
+    v.table = (size_t)jb.table * a.R;
     return v;
 }
 
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+// inclusive prefix sum over the 64 lanes, on the vector unit alone
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);      // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
     return v;
 }
-// exclusive prefix sum over the 64 lanes
-__device__ __forceinline__ uint32_t wave_exclusive_scan(uint32_t v) {
-    const int lane = threadIdx.x & 63;
-    uint32_t s = v;
+// LDS written by some lanes of a wave and read by others of the same wave
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+struct __attribute__((packed, aligned(4))) Dwords4 { uint32_t w[4]; };      // 16 bytes on any dword boundary
+struct __attribute__((packed, aligned(4))) Dwords2 { uint32_t w[2]; };
+
+// A wave's walk over a chunk's bytes: in every step the wave takes 64 pieces of four dwords, a lane one piece.
+struct PieceWalk {
+    uint32_t dw, n_dw;          // the piece's first dword in the chunk; dwords of the chunk
+    uint32_t at;                // that dword's place in its record
+    uint32_t per_row, step;     // dwords per record; 256 modulo that
+    __device__ __forceinline__ PieceWalk(int64_t T, int64_t chunk, int R) {
+        const int64_t left = T - chunk * kChunk;
+        per_row = (uint32_t)R / 4u;
+        n_dw = (uint32_t)(left < kChunk ? left : kChunk) * per_row;
+        dw = (threadIdx.x & 63u) * 4u;
+        at = dw % per_row;
+        step = 256u % per_row;
+    }
+    __device__ __forceinline__ void load(const uint32_t* src, uint32_t (&w)[4]) const {
+        if (dw + 4u <= n_dw) {
+            const Dwords4 v = *reinterpret_cast<const Dwords4*>(src + dw);
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = __shfl_up(s, d, 64);
-        if (lane >= d) s += o;
-    }
-    return s - v;
-}
-
-// The chunk's records, global -> this wave's rows in LDS: whole dwords, coalesced; row r at rows[r * rs].
-__device__ __forceinline__ void stage_rows(const JobView& v, int64_t chunk, int R, uint32_t* rows) {
-    const int lane = threadIdx.x & 63;
-    const int64_t t0 = chunk * kChunk;
-    const uint32_t n_rows = (uint32_t)((v.T - t0) < kChunk ? (v.T - t0) : kChunk);
-    const uint32_t per_row = (uint32_t)R / 4u, rs = row_stride_dwords(R);
-    const uint32_t* src = v.rec + t0 * per_row;
-    for (uint32_t i = lane; i < n_rows * per_row; i += 64) {
-        const uint32_t r = i / per_row, c = i - r * per_row;
-        rows[r * rs + c] = src[i];
-    }
-}
-
-// (1) bits of every token's code string -> len_bits[]; bytes of every chunk's bit string -> chunk_off[chunk] (sizes for now)
-__global__ void __launch_bounds__(256) entropy_size_kernel(const EntropyArgs a) {
-    extern __shared__ uint32_t lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int R = a.R;
-    const JobView v = job_view(a, blockIdx.y);
-    const int64_t chunk = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
-    const bool live = v.ok && chunk < v.n_chunks;
-    uint32_t* rows = lds + (size_t)wave * kChunk * row_stride_dwords(R);
-    if (live) stage_rows(v, chunk, R, rows);
-    __syncthreads();
-    if (!live) return;
-    const int64_t t = chunk * kChunk + lane;
-    uint32_t bits = 0;
-    if (t < v.T) {
-        const uint32_t* row = rows + (uint32_t)lane * row_stride_dwords(R);
-#pragma unroll 4
-        for (int d = 0; d < R / 4; ++d) {
-            const uint32_t w = row[d];
-            const uint16_t* e = v.enc + (size_t)(4 * d) * 256;
-            bits += (uint32_t)(e[w & 0xffu] >> 12) + (uint32_t)(e[256 + ((w >> 8) & 0xffu)] >> 12) +
-                    (uint32_t)(e[512 + ((w >> 16) & 0xffu)] >> 12) + (uint32_t)(e[768 + (w >> 24)] >> 12);
+            for (int j = 0; j < 4; ++j) w[j] = v.w[j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[j] = dw + j < n_dw ? src[dw + j] : 0u;
         }
     }
-    v.len_bits[t] = (uint16_t)bits;                        // the directory has 64 entries per chunk: zero beyond the last token
-    const uint32_t total = wave_sum(bits);
-    if (lane == 0) v.chunk_off[chunk] = (total + 31u) / 32u * 4u;
+    __device__ __forceinline__ void next() {
+        dw += 256u;
+        at += step;
+        if (at >= per_row) at -= per_row;
+    }
+};
+
+// the workgroup's tables, global -> LDS: rows of `from` dwords, a dword of padding behind each
+__device__ __forceinline__ void stage_table(const uint32_t* src, int rows, int log2_from, uint32_t* dst) {
+    const int n = rows << log2_from;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i + (i >> log2_from)] = src[i];
+}
+
+// (1) bits of every token's code string -> len_bits[]; bytes of every chunk's bit string -> chunk_off[chunk] (sizes for now).
+// Bound by the table lookups: one LDS gather per byte (looked up in global memory, with a lane per token and the rows staged
+// in LDS, the same 256 MiB took 237 us; now 75).  A token's length is the difference of the running bit count at its last
+// dword and at the token's before it.
+__global__ void __launch_bounds__(1024, 2) entropy_size_kernel(const EntropyArgs a) {
+    extern __shared__ uint32_t lds[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    const int R = a.R;
+    const JobView v = job_view(a, blockIdx.y);
+    const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
+    if (!v.ok || first >= v.n_chunks) return;
+    uint32_t* ends = lds + wave * kChunk;                            // running bit count at the end of every token
+    uint32_t* tab32 = lds + n_waves * kChunk;
+    stage_table(reinterpret_cast<const uint32_t*>(a.len + v.table * 256), R, 6, tab32);
+    const uint8_t* tab = reinterpret_cast<const uint8_t*>(tab32);
+    __syncthreads();
+    for (int c = 0; c < a.chunks_per_wave; ++c) {
+        const int64_t chunk = first + (int64_t)c * n_waves + wave;
+        if (chunk >= v.n_chunks) break;
+        PieceWalk pw(v.T, chunk, R);
+        const uint32_t* src = v.rec + chunk * kChunk * pw.per_row;
+        uint32_t token = pw.dw / pw.per_row;
+        const uint32_t token_step = 256u / pw.per_row;
+        uint32_t run = 0;                                            // bits of the pieces before this step
+        uint32_t w[4];
+        pw.load(src, w);
+        for (uint32_t d0 = 0; d0 < pw.n_dw; d0 += 256u) {
+            const PieceWalk cur = pw;
+            const uint32_t tok0 = token;
+            uint32_t s[4], at = cur.at, tok = tok0, last = 0u, end_tok[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint8_t* e = tab + at * (4 * kLenRow);
+                const uint32_t bits = (uint32_t)e[w[j] & 0xffu] + (uint32_t)e[kLenRow + ((w[j] >> 8) & 0xffu)] +
+                                      (uint32_t)e[2 * kLenRow + ((w[j] >> 16) & 0xffu)] + (uint32_t)e[3 * kLenRow + (w[j] >> 24)];
+                s[j] = cur.dw + j < cur.n_dw ? bits : 0u;
+                ++at;
+                end_tok[j] = at == cur.per_row && cur.dw + j < cur.n_dw ? tok : ~0u;
+                if (at == cur.per_row) { at = 0u; ++tok; }
+                last += s[j];
+            }
+            token += token_step + (pw.at + pw.step >= pw.per_row ? 1u : 0u);
+            pw.next();
+            if (d0 + 256u < pw.n_dw) pw.load(src, w);                // the next step's bytes travel under this step's sums
+            const uint32_t incl = wave_inclusive_scan(last);
+            uint32_t upto = run + incl - last;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                upto += s[j];
+                if (end_tok[j] != ~0u) ends[end_tok[j]] = upto;
+            }
+            run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        }
+        wave_fence();
+        const int64_t t = chunk * kChunk + lane;
+        // the directory has 64 entries per chunk: zero beyond the last token
+        v.len_bits[t] = t < v.T ? (uint16_t)(ends[lane] - (lane > 0 ? ends[lane - 1] : 0u)) : (uint16_t)0;
+        if (lane == 0) v.chunk_off[chunk] = (run + 31u) / 32u * 4u;
+        wave_fence();
+    }
 }
 
 // (2) sizes -> offsets, in place, one workgroup per job; the container's length -> coded_bytes[job] (all ones for a job
@@ -226,159 +272,247 @@ __global__ void __launch_bounds__(256) entropy_scan_kernel(const EntropyArgs a) 
 }
 
 // (3) the code strings.  A chunk whose string would end beyond the job's room is left unwritten (the caller sees the
-// needed size in coded_bytes).
-__global__ void __launch_bounds__(256) entropy_write_kernel(const EntropyArgs a) {
-    extern __shared__ uint32_t lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int R = a.R;
-    const JobView v = job_view(a, blockIdx.y);
-    const int64_t chunk = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
-    const bool live = v.ok && chunk < v.n_chunks;
-    const uint32_t img_dw = chunk_image_dwords(R), rs = row_stride_dwords(R);
-    uint32_t* img = lds + (size_t)wave * (img_dw + kChunk * rs);
-    uint32_t* rows = img + img_dw;
-    uint32_t begin = 0, end = 0;
-    if (live) { begin = v.chunk_off[chunk]; end = v.chunk_off[chunk + 1]; }
-    const bool fits = live && end >= begin && (uint64_t)end <= v.payload_cap && (end - begin) / 4u <= img_dw;
-    const uint32_t n_dw = fits ? (end - begin) / 4u : 0u;
-    for (uint32_t i = lane; i < n_dw; i += 64) img[i] = 0u;
-    if (fits) stage_rows(v, chunk, R, rows);
-    __syncthreads();
-    if (fits) {
-        const int64_t t = chunk * kChunk + lane;
-        const uint32_t my_bits = v.len_bits[t];
-        uint32_t pos = wave_exclusive_scan(my_bits);           // bit offset of this token's string in the chunk
-        if (t < v.T) {
-            const uint32_t* row = rows + (uint32_t)lane * rs;
-            // the string is built pre-shifted by pos % 32, so that whole dwords of the image are OR-ed in
-            uint64_t acc = 0;
-            uint32_t nacc = pos & 31u;
-            uint32_t dw = pos >> 5;
-#pragma unroll 4
-            for (int d = 0; d < R / 4; ++d) {
-                const uint32_t w = row[d];
-                const uint16_t* e = v.enc + (size_t)(4 * d) * 256;
-                uint32_t ent[4];
-#pragma unroll
-                for (int b = 0; b < 4; ++b) ent[b] = e[b * 256 + ((w >> (8 * b)) & 0xffu)];
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    acc |= (uint64_t)(ent[b] & 0xfffu) << nacc;
-                    nacc += ent[b] >> 12;
-                    if (nacc >= 32u) {
-                        if (dw < n_dw) atomicOr(&img[dw], (uint32_t)acc);
-                        ++dw;
-                        acc >>= 32;
-                        nacc -= 32u;
-                    }
-                }
-            }
-            if (nacc != 0u && dw < n_dw) atomicOr(&img[dw], (uint32_t)acc);
-        }
-    }
-    __syncthreads();
-    if (fits) {
-        uint32_t* out = reinterpret_cast<uint32_t*>(v.payload + begin);
-        for (uint32_t i = lane; i < n_dw; i += 64) out[i] = img[i];
-    }
-}
-
-// decode: one wave per chunk.  Every read of the container is clamped to the job's bytes, so a damaged container gives
-// wrong bytes, never a fault.  A lane reads its own bit string straight from the container, one dword ahead of need: the
-// strings of a chunk's tokens follow each other, so the wave's reads fall on a few lines that stay in the L1.  LDS: the waves'
-// output rows, then the job's limits and rank offsets of every byte position (64 bytes each; the workgroup's chunks belong to
-// one job) -- no image of the chunk, which would halve the waves a compute unit can hold.
-__global__ void __launch_bounds__(256) entropy_decode_kernel(const EntropyArgs a) {
+// needed size in coded_bytes).  Per step a wave builds the string of its 64 pieces (1 KiB of records) in LDS, starting at the
+// bits the step before left over, and stores the whole dwords coalesced: 1.5 KiB of LDS per wave, where the image of a whole
+// chunk and its rows took 20 and left a compute unit seven waves.  LDS_TAB: the codes come from the workgroup's copy of the
+// table (records of up to 268 bytes), else from global memory.  Bound by about 16 vector instructions per byte:
+// 256 MiB in 634 us before, 167 now.
+template <bool LDS_TAB>
+__global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
     const int R = a.R;
     const JobView v = job_view(a, blockIdx.y);
-    const int64_t chunk = (int64_t)blockIdx.x * n_waves + wave;
-    const bool live = v.ok && chunk < v.n_chunks;
-    const uint32_t rs = row_stride_dwords(R);
-    uint32_t* rows = lds + (size_t)wave * kChunk * rs;
-    uint32_t* tab = lds + (size_t)n_waves * kChunk * rs;          // [R][16] dwords: limit[16] u16, off[16] i16
-    if (v.ok) {
-        for (int i = threadIdx.x; i < R * 16; i += blockDim.x)
-            tab[i] = reinterpret_cast<const uint32_t*>(v.dec + (i >> 4))[i & 15];
+    const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
+    if (!v.ok || first >= v.n_chunks) return;
+    uint32_t* img = lds + wave * kImageDw;
+    constexpr int kRow = LDS_TAB ? kEncRow / 2 : 256;                // entries from one byte position to the next
+    const uint16_t* tab = a.enc + v.table * 256;
+    if constexpr (LDS_TAB) {
+        uint32_t* tab32 = lds + n_waves * kImageDw;
+        stage_table(reinterpret_cast<const uint32_t*>(tab), R, 7, tab32);
+        tab = reinterpret_cast<const uint16_t*>(tab32);
     }
+    for (int i = lane; i < kImageDw; i += 64) img[i] = 0u;
     __syncthreads();
-    if (live) {
-        uint64_t begin = v.chunk_off[chunk], end = v.chunk_off[chunk + 1];
-        begin = begin < v.payload_cap ? begin : v.payload_cap;
-        end = end < begin ? begin : (end < v.payload_cap ? end : v.payload_cap);
-        const uint32_t n_dw = (uint32_t)((end - begin) / 4u);
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(v.payload + (begin & ~3ull));
-        const int64_t t = chunk * kChunk + lane;
-        const uint32_t pos = wave_exclusive_scan((uint32_t)v.len_bits[t]);
-        if (t < v.T) {
-            uint32_t* my = rows + (uint32_t)lane * rs;
-            auto word = [&](uint32_t i) { return i < n_dw ? src[i] : 0u; };
-            // the next bits of the string in a register; the container is read a dword ahead of need
-            uint32_t idx = (pos >> 5) + 2u;
-            uint64_t buf = (((uint64_t)word(idx - 1u) << 32) | word(idx - 2u)) >> (pos & 31u);
-            uint32_t nbuf = 64u - (pos & 31u);
-            uint32_t ahead = word(idx);
-            // pass A: lengths (the only chain) and ranks
-            for (int d = 0; d < R / 4; ++d) {
-                // the limits of this dword's four positions: wave-uniform LDS reads, fetched before the chain needs them
-                uint4 lim[4][2];
+    for (int c = 0; c < a.chunks_per_wave; ++c) {
+        const int64_t chunk = first + (int64_t)c * n_waves + wave;
+        if (chunk >= v.n_chunks) break;
+        const uint32_t begin = __builtin_amdgcn_readfirstlane(v.chunk_off[chunk]), end = __builtin_amdgcn_readfirstlane(v.chunk_off[chunk + 1]);
+        if (end < begin || (uint64_t)end > v.payload_cap) continue;
+        const uint32_t n_out = (end - begin) / 4u;
+        uint32_t* out = reinterpret_cast<uint32_t*>(v.payload + begin);
+        PieceWalk pw(v.T, chunk, R);
+        const uint32_t* src = v.rec + chunk * kChunk * pw.per_row;
+        uint32_t carry = 0, written = 0;                             // bits in img[0] left by the step before; dwords stored
+        uint32_t w[4];
+        pw.load(src, w);
+        for (uint32_t d0 = 0; d0 < pw.n_dw; d0 += 256u) {
+            uint32_t code[8], len[8], at = pw.at, bits = 0;          // two bytes' codes together: at most 24 bits
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const uint4* T = reinterpret_cast<const uint4*>(tab + (4 * d + b) * 16);
-                    lim[b][0] = T[0];
-                    lim[b][1] = T[1];
+            for (int j = 0; j < 4; ++j) {
+                const uint16_t* e = tab + at * (4 * kRow);
+                uint32_t ent[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) ent[b] = e[b * kRow + ((w[j] >> (8 * b)) & 0xffu)];
+                const bool in = pw.dw + j < pw.n_dw;
+#pragma unroll
+                for (int b = 0; b < 4; b += 2) {
+                    const uint32_t l0 = ent[b] >> 12;
+                    code[2 * j + b / 2] = in ? (ent[b] & 0xfffu) | ((ent[b + 1] & 0xfffu) << l0) : 0u;
+                    len[2 * j + b / 2] = in ? l0 + (ent[b + 1] >> 12) : 0u;
+                    bits += len[2 * j + b / 2];
                 }
-                uint32_t nn[4], hi[4];
+                ++at;
+                if (at == pw.per_row) at = 0u;
+            }
+            pw.next();
+            if (d0 + 256u < pw.n_dw) pw.load(src, w);                // the next step's bytes travel under this step's string
+            const uint32_t incl = wave_inclusive_scan(bits);
+            const uint32_t pos = carry + incl - bits;
+            const uint32_t n_bits = carry + (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            // the string is built pre-shifted by pos % 32, so that whole dwords of the image are OR-ed in
+            uint64_t acc = 0;
+            uint32_t nacc = pos & 31u, dw = pos >> 5;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const uint32_t top = __builtin_bitreverse32((uint32_t)buf) >> 20;        // 12 bits, first bit on top
-                    const uint32_t lw[6] = {lim[b][0].x, lim[b][0].y, lim[b][0].z, lim[b][0].w, lim[b][1].x, lim[b][1].y};
-                    uint32_t n = 0;
+            for (int k = 0; k < 8; ++k) {
+                acc |= (uint64_t)code[k] << nacc;
+                nacc += len[k];
+                if (nacc >= 32u) {
+                    atomicOr(&img[dw], (uint32_t)acc);
+                    ++dw;
+                    acc >>= 32;
+                    nacc -= 32u;
+                }
+            }
+            if (nacc != 0u) atomicOr(&img[dw], (uint32_t)acc);
+            wave_fence();
+            const uint32_t full = n_bits >> 5;                       // at most 384
+            const uint32_t rest = img[full];
+            wave_fence();
+            for (uint32_t i = 4u * lane; i <= full; i += 256u) {
+                uint4* p = reinterpret_cast<uint4*>(img + i);
+                const uint4 q = *p;
+                *p = make_uint4(0u, 0u, 0u, 0u);
+                const uint32_t o = written + i;
+                if (i + 4u <= full && o + 4u <= n_out) {
+                    *reinterpret_cast<Dwords4*>(out + o) = Dwords4{{q.x, q.y, q.z, q.w}};
+                } else {
+                    const uint32_t qq[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-                    for (int q = 0; q < 6; ++q) n += (top >= (lw[q] & 0xffffu) ? 1u : 0u) + (top >= (lw[q] >> 16) ? 1u : 0u);
-                    const uint32_t len = n < (uint32_t)kMaxLen ? n + 1u : 1u;     // n = 12: a pattern no code starts with (damaged input)
-                    nn[b] = n;
-                    hi[b] = top >> (12u - len);
-                    buf >>= len;
-                    nbuf -= len;
-                    if (nbuf <= 32u) {
-                        buf |= (uint64_t)ahead << nbuf;
-                        nbuf += 32u;
-                        ++idx;
-                        ahead = word(idx);
+                    for (int j = 0; j < 4; ++j)
+                        if (i + j < full && o + j < n_out) out[o + j] = qq[j];
+                }
+            }
+            wave_fence();
+            if (lane == 0) img[0] = rest;
+            wave_fence();
+            written += full;
+            carry = n_bits & 31u;
+        }
+        if (lane == 0) {                                             // the last, partly filled dword
+            if (carry != 0u && written < n_out) out[written] = img[0];
+            img[0] = 0u;
+        }
+        wave_fence();
+    }
+}
+
+// decode: one wave per chunk, a lane per token.  Every read of the container is clamped to the job's bytes, so a damaged
+// container gives wrong bytes, never a fault.  A lane reads its own bit string straight from the container, two dwords ahead
+// of need: the strings of a chunk's tokens follow each other, so the wave's reads fall on a few lines that stay in the caches.
+// Rows are collected in LDS and stored 64 bytes at a time (stored 16 bytes at a time, straight from the lanes, a line's pieces
+// did not meet in the L2: five times the writes to memory, 0.57 ms).  No step of the walk branches but for the next four
+// dwords of the string.  256 MiB of records: 777 us with twelve comparisons per symbol, 336 now: 34 vector
+// instructions per symbol, which keep the vector units busy for 270 of them.
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+// the k-th of four values, k modulo 4 (by value: a choice between variables is one between addresses, and puts them in memory)
+__device__ __forceinline__ uint32_t pick(uint32_t k, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+    const uint32_t lo = (k & 1u) ? b : a, hi = (k & 1u) ? d : c;
+    return (k & 2u) ? hi : lo;
+}
+__global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs a) {
+    extern __shared__ uint32_t lds[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    const int R = a.R;
+    const JobView v = job_view(a, blockIdx.y);
+    const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
+    if (!v.ok || first >= v.n_chunks) return;
+    uint32_t* out = lds + wave * (kChunk * kDecPitch);
+    uint32_t* tab32 = lds + n_waves * (kChunk * kDecPitch);
+    const uint8_t* tab = reinterpret_cast<const uint8_t*>(tab32);
+    // the limits of four positions at a time, through the scalar unit (constant while the kernel runs)
+    typedef const u32x16 __attribute__((address_space(4))) const_u32x16;
+    const const_u32x16* lim = (const const_u32x16*)(uintptr_t)uniform_ptr(a.lim + v.table * 4);
+    const uint32_t per_row = (uint32_t)R / 4u;
+    for (int c = 0; c < a.chunks_per_wave; ++c) {              // the same number of rounds in every wave: there are barriers inside
+        const int64_t chunk = first + (int64_t)c * n_waves + wave;
+        const bool live = chunk < v.n_chunks;
+        uint32_t n_dw = 0, pos = 0;
+        const uint32_t* src = nullptr;
+        const int64_t t = chunk * kChunk + lane;
+        if (live) {
+            uint64_t begin = v.chunk_off[chunk], end = v.chunk_off[chunk + 1];
+            begin = begin < v.payload_cap ? begin : v.payload_cap;
+            end = end < begin ? begin : (end < v.payload_cap ? end : v.payload_cap);
+            n_dw = (uint32_t)((end - begin) / 4u);
+            src = reinterpret_cast<const uint32_t*>(v.payload + (begin & ~3ull));
+            const uint32_t own = v.len_bits[t];
+            pos = wave_inclusive_scan(own) - own;
+        }
+        const bool mine = live && t < v.T;
+        // the string four dwords at a time, from dword i on or, near its end, the last four (in front of a shorter string lies
+        // the container's directory); what is taken from behind its end is stray, and no code reads it
+        uint32_t at = 0u, h0 = 0u, h1 = 0u, h2 = 0u, h3 = 0u;  // first of the four dwords at hand; the dwords
+        auto fetch = [&](uint32_t i) {
+            at = (uint32_t)min((int)i, (int)n_dw - 4);
+            const Dwords4 v4 = *reinterpret_cast<const Dwords4*>(src + (int)at);
+            h0 = v4.w[0]; h1 = v4.w[1]; h2 = v4.w[2]; h3 = v4.w[3];
+        };
+        auto word = [&](uint32_t k) { return pick(k, h0, h1, h2, h3); };
+        // the next bits of the string in a register; at least 24 of them whenever two codes are taken
+        uint64_t buf = 0;
+        uint32_t nbuf = 64u - (pos & 31u);
+        uint32_t idx = pos >> 5;                               // next dword of the string
+        if (mine) {
+            fetch(idx);
+            const uint32_t lo = word(idx - at);
+            if (idx - at == 3u) fetch(idx + 1u);
+            const uint32_t hi = word(idx + 1u - at);
+            buf = (((uint64_t)hi << 32) | lo) >> (pos & 31u);
+            idx += 2u;
+            if (idx - at > 3u) fetch(idx);
+        }
+        // the four bytes of dword d (its table rows at byte `row` of the LDS)
+        auto four = [&](uint32_t row, const u32x16& L) {
+            uint32_t rev[4], len[4], w = 0u;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                if ((b & 1) == 0) {
+                    const bool need = nbuf <= 32u;
+                    const uint32_t k = idx - at;
+                    buf |= (uint64_t)(need ? word(k) : 0u) << (nbuf & 63u);
+                    if (need && k >= 3u) fetch(idx + 1u);
+                    nbuf += need ? 32u : 0u;
+                    idx += need ? 1u : 0u;
+                }
+                rev[b] = __builtin_bitreverse32((uint32_t)buf);
+                uint32_t n = tab[row + ((uint32_t)buf & 0xffu) + b * kDecRow];
+                n += rev[b] > L[4 * b] ? 1u : 0u;
+                n += rev[b] > L[4 * b + 1] ? 1u : 0u;
+                n += rev[b] > L[4 * b + 2] ? 1u : 0u;
+                buf >>= n;
+                nbuf -= n;
+                len[b] = n;
+            }
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const uint32_t off = tab[row + len[b] + (b * kDecRow + kDecOff)];
+                const uint32_t rank = ((rev[b] >> (32u - len[b])) - off) & 0xffu;
+                w |= (uint32_t)tab[row + rank + (b * kDecRow + kDecSym)] << (8 * b);
+            }
+            return w;
+        };
+        for (uint32_t p0 = 0; p0 < per_row; p0 += kDecSegment / 4) {
+            const uint32_t p1 = min(per_row, p0 + (uint32_t)kDecSegment / 4u);
+            if (c == 0 || per_row > (uint32_t)kDecSegment / 4u) {
+                __syncthreads();
+                const uint32_t* from = reinterpret_cast<const uint32_t*>(a.dec + (v.table + 4u * p0) * kDecRow);
+                for (uint32_t i = threadIdx.x; i < (p1 - p0) * kDecRow; i += blockDim.x) tab32[i] = from[i];
+                __syncthreads();
+            }
+            // kDecBatch dwords of every row at a time: collected in LDS, stored as whole 64-byte pieces
+            u32x16 L = lim[p0];
+            uint32_t row = 0u;
+            for (uint32_t d0 = p0; d0 < p1; d0 += kDecBatch) {
+                const uint32_t nd = min(p1 - d0, (uint32_t)kDecBatch);
+                if (mine) {
+                    for (uint32_t d = 0; d < nd; ++d) {
+                        const u32x16 Ln = lim[min(d0 + d + 1u, per_row - 1u)];
+                        out[lane * kDecPitch + d] = four(row, L);
+                        row += 4u * kDecRow;
+                        L = Ln;
                     }
                 }
-                // ranks: (code bits as a number) - off[length - 1]; per-lane LDS reads that the chain does not wait for
-                uint32_t w = 0;
+                wave_fence();
+                if (live) {
+                    const uint32_t n_rows = (uint32_t)min(v.T - chunk * kChunk, (int64_t)kChunk);
+                    uint32_t* to = v.rec + chunk * kChunk * per_row + d0;
+                    if (nd == kDecBatch) {
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int16_t* off = reinterpret_cast<const int16_t*>(tab + (4 * d + b) * 16 + 8);
-                    const uint32_t rank = nn[b] < (uint32_t)kMaxLen ? (hi[b] - (uint32_t)(int32_t)off[nn[b]]) & 0xffu : 0u;
-                    w |= rank << (8 * b);
+                        for (uint32_t i = 0; i < 4; ++i) {
+                            const uint32_t r = 16u * i + (lane >> 2), k = 4u * (lane & 3u);
+                            const uint4 q = *reinterpret_cast<const uint4*>(out + r * kDecPitch + k);
+                            if (r < n_rows) *reinterpret_cast<Dwords4*>(to + r * per_row + k) = Dwords4{{q.x, q.y, q.z, q.w}};
+                        }
+                    } else {
+                        const uint32_t k = lane & 15u;
+                        for (uint32_t r = lane >> 4; r < n_rows; r += 4u)
+                            if (k < nd) to[r * per_row + k] = out[r * kDecPitch + k];
+                    }
                 }
-                my[d] = w;
+                wave_fence();
             }
-            // pass B: ranks -> byte values
-#pragma unroll 4
-            for (int d = 0; d < R / 4; ++d) {
-                const uint32_t w = my[d];
-                const DecPos* P = v.dec + 4 * d;
-                my[d] = (uint32_t)P[0].sym[w & 0xffu] | ((uint32_t)P[1].sym[(w >> 8) & 0xffu] << 8) |
-                        ((uint32_t)P[2].sym[(w >> 16) & 0xffu] << 16) | ((uint32_t)P[3].sym[w >> 24] << 24);
-            }
-        }
-    }
-    __syncthreads();
-    if (live) {
-        // the chunk's records are contiguous in the output: whole dwords, row by row
-        const int64_t t0 = chunk * kChunk;
-        const uint32_t n_rows = (uint32_t)((v.T - t0) < kChunk ? (v.T - t0) : kChunk);
-        const uint32_t per_row = (uint32_t)R / 4u;
-        uint32_t* out = v.rec + t0 * per_row;
-        for (uint32_t i = lane; i < n_rows * per_row; i += 64) {
-            const uint32_t r = i / per_row, c = i - r * per_row;
-            out[i] = rows[r * rs + c];
         }
     }
 }
@@ -394,24 +528,54 @@ size_t bound_of(int R, int64_t n_tokens) {
     return (size_t)header_bytes(n_chunks) + (size_t)n_chunks * chunk_image_dwords(R) * 4;
 }
 
+// The shape of a launch over `n_chunks` chunks of each of n_jobs jobs: workgroups of 16 waves, or 8 where that lets more
+// waves share a compute unit's LDS; each wave takes as many chunks in turn (at most 8) as still leave every place on the chip
+// taken, because a workgroup first copies its table (64 KiB for 128-byte records, against 8 KiB of records per chunk).
+// A launch too small for that runs 4-wave workgroups: more compute units share the chunks.
+struct Shape { int waves, chunks_per_wave; unsigned blocks; size_t lds; };
+int compute_units() {
+    static int n[64] = {0};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    if (n[dev] == 0 && (hipDeviceGetAttribute(&n[dev], hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n[dev] <= 0)) n[dev] = 256;
+    return n[dev];
+}
+Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs) {
+    const int64_t total = n_chunks * n_jobs, cus = compute_units();
+    int waves = 16, wgs = 1, best = 0;
+    for (int w = 16; w >= 8; w -= 8) {
+        const size_t b = table_b + (size_t)w * wave_b;
+        if (b > (size_t)kLdsMost) continue;
+        const int fit = (int)((size_t)kLdsBudget / b), n = fit * w > 32 ? 32 / w : fit;
+        if (n * w > best) { best = n * w; waves = w; wgs = n; }
+    }
+    if (best == 0 || total < cus * waves) { waves = 4; wgs = 1; }
+    int64_t per = total / (cus * wgs * waves);
+    per = per < 1 ? 1 : (per > 8 ? 8 : per);
+    return {waves, (int)per, (unsigned)((n_chunks + waves * per - 1) / (waves * per)), table_b + (size_t)waves * wave_b};
+}
+
+kvtc_status launch(const char* who, void (*fn)(EntropyArgs), const Shape& sh, int n_jobs, EntropyArgs a, hipStream_t st) {
+    if (allow_full_lds(reinterpret_cast<const void*>(fn)) != hipSuccess) return set_error(KVTC_E_HIP, "%s: cannot size the LDS", who);
+    a.chunks_per_wave = sh.chunks_per_wave;
+    hipLaunchKernelGGL(fn, dim3(sh.blocks, (unsigned)n_jobs), dim3(64 * sh.waves), sh.lds, st, a);
+    return KVTC_OK;
+}
+
 kvtc_status run_encode(const char* who, const kvtc_entropy* e, const EntropyArgs& a_in, int n_jobs, int64_t max_tokens, hipStream_t st) {
     const int R = e->record_bytes;
     const int64_t max_chunks = (max_tokens + kChunk - 1) / kChunk;
-    const int waves = waves_per_wg(R, false);
     EntropyArgs a = a_in;
     a.max_tokens = max_tokens;
-    if (max_chunks > 0) {
-        if (allow_full_lds(reinterpret_cast<const void*>(&entropy_size_kernel)) != hipSuccess)
-            return set_error(KVTC_E_HIP, "%s: cannot size the LDS", who);
-        hipLaunchKernelGGL(entropy_size_kernel, dim3((unsigned)((max_chunks + 3) / 4), (unsigned)n_jobs), dim3(256),
-                           (size_t)4 * kChunk * row_stride_dwords(R) * 4, st, a);
-    }
+    kvtc_status rc = KVTC_OK;
+    if (max_chunks > 0) rc = launch(who, &entropy_size_kernel, launch_shape((size_t)R * kLenRow, kChunk * 4, max_chunks, n_jobs), n_jobs, a, st);
+    if (rc != KVTC_OK) return rc;
     hipLaunchKernelGGL(entropy_scan_kernel, dim3((unsigned)n_jobs), dim3(256), 0, st, a);
     if (max_chunks > 0) {
-        if (allow_full_lds(reinterpret_cast<const void*>(&entropy_write_kernel)) != hipSuccess)
-            return set_error(KVTC_E_HIP, "%s: cannot size the LDS", who);
-        hipLaunchKernelGGL(entropy_write_kernel, dim3((unsigned)((max_chunks + waves - 1) / waves), (unsigned)n_jobs), dim3(64 * waves),
-                           lds_bytes(R, waves, false), st, a);
+        const bool tab_lds = (size_t)R * kEncRow + 16u * kImageDw * 4u <= (size_t)kLdsMost;
+        rc = launch(who, tab_lds ? &entropy_write_kernel<true> : &entropy_write_kernel<false>,
+                    launch_shape(tab_lds ? (size_t)R * kEncRow : 0, kImageDw * 4, max_chunks, n_jobs), n_jobs, a, st);
+        if (rc != KVTC_OK) return rc;
     }
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return set_error(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(err));
@@ -424,11 +588,9 @@ kvtc_status run_decode(const char* who, const kvtc_entropy* e, const EntropyArgs
     a.max_tokens = max_tokens;
     const int64_t max_chunks = (max_tokens + kChunk - 1) / kChunk;
     if (max_chunks == 0) return KVTC_OK;
-    const int waves = waves_per_wg(R, true);
-    if (allow_full_lds(reinterpret_cast<const void*>(&entropy_decode_kernel)) != hipSuccess)
-        return set_error(KVTC_E_HIP, "%s: cannot size the LDS", who);
-    hipLaunchKernelGGL(entropy_decode_kernel, dim3((unsigned)((max_chunks + waves - 1) / waves), (unsigned)n_jobs), dim3(64 * waves),
-                       lds_bytes(R, waves, true), st, a);
+    Shape sh = launch_shape((size_t)(R < kDecSegment ? R : kDecSegment) * kDecRow, kChunk * kDecPitch * 4, max_chunks, n_jobs);
+    const kvtc_status rc = launch(who, &entropy_decode_kernel, sh, n_jobs, a, st);
+    if (rc != KVTC_OK) return rc;
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return set_error(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(err));
     return KVTC_OK;
@@ -438,7 +600,9 @@ EntropyArgs base_args(const kvtc_entropy* e) {
     EntropyArgs a;
     memset(&a, 0, sizeof(a));
     a.enc = e->enc_dev;
-    a.dec = static_cast<const DecPos*>(e->dec_dev);
+    a.len = e->len_dev;
+    a.dec = e->dec_dev;
+    a.lim = e->lim_dev;
     a.R = e->record_bytes;
     a.n_tables = e->n_tables;
     return a;
@@ -457,49 +621,72 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
     if (n_tables < 1 || n_tables > 4096) return set_error(KVTC_E_ARG, "kvtc_entropy_create: n_tables=%d outside 1..4096", n_tables);
     const size_t rows = (size_t)n_tables * R;
     std::vector<uint16_t> enc;
-    std::vector<DecPos> dec;
+    std::vector<uint8_t> dec;
+    std::vector<uint32_t> lim;
     try {
-        enc.assign(rows * 256, 0);
-        dec.resize(rows);
+        enc.resize(rows * 256);
+        dec.assign(rows * kDecRow, 0);
+        lim.assign(rows * 4, 0xffffffffu);
     } catch (const std::bad_alloc&) {
         return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: host allocation failed");
     }
     for (size_t k = 0; k < rows; ++k) {
         const uint8_t* L = code_len_host + k * 256;
         // canonical codes: by length, then by symbol (RFC 1951, section 3.2.2); Kraft's inequality must hold
-        uint64_t kraft = 0;
+        uint32_t count[kMaxLen + 1] = {0};
         for (int s = 0; s < 256; ++s) {
             if (L[s] < 1 || L[s] > kMaxLen)
                 return set_error(KVTC_E_ARG, "kvtc_entropy_create: table %d, position %d, symbol %d: length %d outside 1..%d", (int)(k / R), (int)(k % R), s, (int)L[s], kMaxLen);
-            kraft += 1ull << (kMaxLen - L[s]);
+            ++count[L[s]];
         }
-        if (kraft > (1ull << kMaxLen))
-            return set_error(KVTC_E_ARG, "kvtc_entropy_create: table %d, position %d: the lengths are not those of a prefix code", (int)(k / R), (int)(k % R));
-        DecPos& D = dec[k];
-        memset(&D, 0, sizeof(D));
-        for (int i = kMaxLen; i < 16; ++i) D.limit[i] = 0xffffu;
-        uint32_t code = 0, rank = 0;
+        uint32_t kraft = 0, next[kMaxLen + 1], rank[kMaxLen + 1], code = 0, shorter = 0;
+        uint8_t* D = &dec[k * kDecRow];
+        int least = 9;                                              // what the table says for codes of 9 bits or more
         for (int len = 1; len <= kMaxLen; ++len) {
-            D.off[len - 1] = (int16_t)((int32_t)code - (int32_t)rank);       // first code of this length - symbols with shorter codes
-            for (int s = 0; s < 256; ++s)
-                if (L[s] == len) {
-                    enc[k * 256 + s] = (uint16_t)(reverse_bits(code, len) | ((uint32_t)len << 12));
-                    D.sym[rank++] = (uint8_t)s;
-                    ++code;
-                }
-            D.limit[len - 1] = (uint16_t)(code << (kMaxLen - len));           // at most 4096
+            kraft += count[len] << (kMaxLen - len);
+            next[len] = code;                                       // first code of this length, and its rank
+            rank[len] = shorter;
+            D[kDecOff + len] = (uint8_t)(code - shorter);
+            code += count[len];
+            shorter += count[len];
+            if (len >= 9 && len < kMaxLen) {
+                if (code != 0) lim[k * 4 + len - 9] = (uint32_t)(((uint64_t)code << (32 - len)) - 1u);
+                else ++least;                                       // no code is as short: the table says so, the limit stays out of reach
+            }
             code <<= 1;
         }
+        if (kraft > (1u << kMaxLen))
+            return set_error(KVTC_E_ARG, "kvtc_entropy_create: table %d, position %d: the lengths are not those of a prefix code", (int)(k / R), (int)(k % R));
+        memset(D, least, 256);
+        for (int s = 0; s < 256; ++s) {
+            const int len = L[s];
+            const uint32_t rev = reverse_bits(next[len]++, len);
+            enc[k * 256 + s] = (uint16_t)(rev | ((uint32_t)len << 12));
+            D[kDecSym + rank[len]++] = (uint8_t)s;
+            if (len <= 8)
+                for (uint32_t i = rev; i < 256u; i += 1u << len) D[i] = (uint8_t)len;
+        }
     }
-    const size_t enc_b = enc.size() * 2, dec_b = dec.size() * sizeof(DecPos);
+    // one allocation: codes, the decoder's tables and limits, lengths
+    const size_t enc_b = enc.size() * 2, dec_b = dec.size(), lim_b = lim.size() * 4, len_b = rows * 256;
     char* blob = nullptr;
-    if (hipMalloc(reinterpret_cast<void**>(&blob), enc_b + dec_b) != hipSuccess) {
+    if (hipMalloc(reinterpret_cast<void**>(&blob), enc_b + dec_b + lim_b + len_b) != hipSuccess) {
         (void)hipGetLastError();
-        return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: hipMalloc of %zu bytes failed", enc_b + dec_b);
+        return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: hipMalloc of %zu bytes failed", enc_b + dec_b + lim_b + len_b);
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipError_t e = hipMemcpyAsync(blob, enc.data(), enc_b, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(blob + enc_b, dec.data(), dec_b, hipMemcpyHostToDevice, st);
+    hipError_t e = hipSuccess;
+    size_t at = 0;
+    auto put = [&](const void* src, size_t n) {
+        char* dst = blob + at;
+        if (e == hipSuccess) e = hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, st);
+        at += n;
+        return dst;
+    };
+    const char* enc_d = put(enc.data(), enc_b);
+    const char* lim_d = put(lim.data(), lim_b);
+    const char* dec_d = put(dec.data(), dec_b);
+    const char* len_d = put(code_len_host, len_b);
     if (e == hipSuccess) e = hipStreamSynchronize(st);           // the host images die with this call
     kvtc_entropy* h = e == hipSuccess ? new (std::nothrow) kvtc_entropy : nullptr;
     if (!h) {
@@ -510,8 +697,10 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
     h->record_bytes = R;
     h->n_tables = n_tables;
     h->blob = blob;
-    h->enc_dev = reinterpret_cast<const uint16_t*>(blob);
-    h->dec_dev = blob + enc_b;
+    h->enc_dev = reinterpret_cast<const uint16_t*>(enc_d);
+    h->lim_dev = reinterpret_cast<const uint32_t*>(lim_d);
+    h->dec_dev = reinterpret_cast<const uint8_t*>(dec_d);
+    h->len_dev = reinterpret_cast<const uint8_t*>(len_d);
     *out = h;
     return KVTC_OK;
 }
