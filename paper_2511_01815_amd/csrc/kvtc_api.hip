@@ -18,7 +18,11 @@
 namespace kvtc {
 hipError_t launch_encode(const KernelArgs& a, kvtc_dtype dtype, int key, int grid, size_t lds_bytes, hipStream_t stream);
 hipError_t launch_decode(const KernelArgs& a, kvtc_dtype dtype, int key, int grid, size_t lds_bytes, hipStream_t stream);
+hipError_t launch_encode_short(const KernelArgs& a, kvtc_dtype dtype, int ntw, int waves, int grid, size_t lds_bytes, hipStream_t stream);
 int encode_lds_bytes(int ntw, int wc, int nw, int n_groups, int rec_dwords, kvtc_dtype dtype);
+int encode_short_ntw(int ntp);
+int encode_short_waves(int ntp);
+int encode_short_lds_bytes(int ntp, int n_groups, int rec_dwords, kvtc_dtype dtype);
 int encode_tok_wg(int ntw, int wc, int nw);
 hipError_t launch_fp8_pack(const void* x, kvtc_dtype dtype, int64_t n_tokens, int p, int64_t ld_x, void* out, hipStream_t stream);
 hipError_t launch_fp8_unpack(const void* in, int64_t n_tokens, int p, void* x, kvtc_dtype dtype, int64_t ld_x, hipStream_t stream);
@@ -47,7 +51,7 @@ struct kvtc_plan {
     void* blob;             // one device allocation holding everything
     PlanDev* desc_dev;      // the descriptor inside the blob
     size_t record_bytes;
-    int enc_s_wgs;          // short-job encode variant (key in h.enc_s_key, 0 = none): workgroups per compute unit ...
+    int enc_s_waves;        // short-job encode kernel (h.enc_short, 0 = none): waves per workgroup ...
     int enc_s_lds[2];       // ... and dynamic LDS bytes per element dtype
 };
 
@@ -58,7 +62,7 @@ struct kvtc_batch {
     struct EncVariant { int key, wgs, lds[2]; };        // workgroups per compute unit; lds per element dtype
     struct DecVariant { int key, wgs, rec, ring; };     // workgroups per compute unit; record image, basis ring (the widest among the class's plans)
     std::vector<EncVariant> enc;
-    std::vector<EncVariant> enc_short;                  // the short-job variants among the plans (64-token tiles)
+    struct ShortVariant { int waves, lds[2]; } enc_short[3];     // short-job kernels by coordinate tiles per wave; waves = 0: no plan uses it
     std::vector<DecVariant> dec;
     int max_p;
     std::vector<int32_t> ps;                            // the distinct feature counts among the plans
@@ -315,22 +319,15 @@ static kvtc_status plan_create_impl(kvtc_plan** out, int p, int r, const float* 
                     "kvtc_plan_create: record of %d bytes with r=%d needs %d/%d/%d bytes of LDS, %d available",
                     d.rec_dwords * 4, r, d.enc_lds[0], d.enc_lds[1], dec_need, lds_cap);
 
-    // encode variant for short jobs: the same padded width with one wave across the tokens (64-token tiles);
-    // the two widest bulk variants already are of that shape
-    // {padded tiles, waves across coordinates, tiles per wave, waves per workgroup}
-    static const int enc_short_tab[][4] = {{2, 2, 1, 2}, {4, 4, 1, 4}, {6, 2, 3, 2}, {8, 4, 2, 4}, {10, 2, 5, 2},
-                                           {12, 4, 3, 4}, {16, 4, 4, 4}, {20, 4, 5, 4}};
-    d.enc_s_key = 0;
-    int s_wgs = 1, s_lds[2] = {0, 0};
-    for (auto& e : enc_short_tab)
-        if (e[0] == ntp && encode_tok_wg(e[2], e[1], e[3]) == kEncShortTile) {
-            s_lds[KVTC_BF16] = encode_lds_bytes(e[2], e[1], e[3], n_groups, d.rec_dwords, KVTC_BF16);
-            s_lds[KVTC_F32] = encode_lds_bytes(e[2], e[1], e[3], n_groups, d.rec_dwords, KVTC_F32);
-            if (s_lds[0] <= lds_cap && s_lds[1] <= lds_cap) {
-                d.enc_s_key = e[3] * 10000 + e[1] * 100 + e[2];
-                s_wgs = e[3] == 4 && ntp <= 10 ? 2 : 1;          // as the kernel's launch bounds
-            }
-        }
+    // the short-job kernel, where it serves the width and its images fit
+    int s_waves = 0, s_lds[2] = {0, 0};
+    d.enc_short = encode_short_ntw(ntp);
+    if (d.enc_short != 0) {
+        s_waves = encode_short_waves(ntp);
+        s_lds[KVTC_BF16] = encode_short_lds_bytes(ntp, n_groups, d.rec_dwords, KVTC_BF16);
+        s_lds[KVTC_F32] = encode_short_lds_bytes(ntp, n_groups, d.rec_dwords, KVTC_F32);
+        if (s_lds[0] > kLdsBudget || s_lds[1] > kLdsBudget) d.enc_short = 0;
+    }
 
     // ---- host images ---------------------------------------------------------------
     const size_t n_venc = (size_t)(p / 16) * ntp * 64 * 8;      // bf16 elements
@@ -436,7 +433,7 @@ static kvtc_status plan_create_impl(kvtc_plan** out, int p, int r, const float* 
     pl->blob = blob;
     pl->desc_dev = reinterpret_cast<PlanDev*>(blob + o_desc);
     pl->record_bytes = (size_t)d.rec_dwords * 4;
-    pl->enc_s_wgs = s_wgs;
+    pl->enc_s_waves = s_waves;
     pl->enc_s_lds[0] = s_lds[0];
     pl->enc_s_lds[1] = s_lds[1];
     *out = pl;
@@ -552,13 +549,11 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
     a.stream_buf = out_dev;
     a.cap = out_cap;
     a.status = nullptr;
-    // A tensor short enough for all its 64-token tiles to run at once (one wave of workgroups) runs the short-job variant.
+    // A tensor short enough for all its 64-token tiles to run at once (one wave of workgroups) runs the short-job kernel.
     const int64_t tiles_short = (n_tokens + kEncShortTile - 1) / kEncShortTile;
     hipError_t e;
-    if (plan->h.enc_s_key != 0 && tiles_short <= (int64_t)cu_count() * plan->enc_s_wgs) {
-        a.enc_short = 1;
-        a.enc_short_max = 0x7fffffff;
-        e = launch_encode(a, dtype, plan->h.enc_s_key, (int)tiles_short, (size_t)kJobTableBytes + 64 + plan->enc_s_lds[dtype], static_cast<hipStream_t>(stream));
+    if (plan->h.enc_short != 0 && tiles_short <= (int64_t)cu_count() * (plan->enc_s_waves <= 8 ? 2 : 1)) {
+        e = launch_encode_short(a, dtype, plan->h.enc_short, plan->enc_s_waves, (int)tiles_short, (size_t)plan->enc_s_lds[dtype], static_cast<hipStream_t>(stream));
     } else {
         const int64_t tiles = (n_tokens + plan->h.enc_tok_wg - 1) / plan->h.enc_tok_wg;
         const int slots = cu_count() * plan->h.enc_wgs;
@@ -634,6 +629,7 @@ kvtc_status kvtc_batch_create(kvtc_batch** out, const kvtc_plan* const* plans, i
     b->rec_dwords_dev = nullptr;
     b->n_plans = n_plans;
     b->max_p = 0;
+    for (auto& v : b->enc_short) v = {0, {0, 0}};
     try {
     for (int i = 0; i < n_plans; ++i) {
         if (!plans[i]) {
@@ -655,16 +651,11 @@ kvtc_status kvtc_batch_create(kvtc_batch** out, const kvtc_plan* const* plans, i
             for (int dt = 0; dt < 2; ++dt)
                 if (ph.enc_lds[dt] > v->lds[dt]) v->lds[dt] = ph.enc_lds[dt];
         }
-        if (ph.enc_s_key != 0) {
-            kvtc_batch::EncVariant* v = nullptr;
-            for (auto& e : b->enc_short)
-                if (e.key == ph.enc_s_key) v = &e;
-            if (!v) {
-                b->enc_short.push_back({ph.enc_s_key, plans[i]->enc_s_wgs, {0, 0}});
-                v = &b->enc_short.back();
-            }
+        if (ph.enc_short != 0) {
+            auto& v = b->enc_short[ph.enc_short];
+            if (plans[i]->enc_s_waves > v.waves) v.waves = plans[i]->enc_s_waves;
             for (int dt = 0; dt < 2; ++dt)
-                if (plans[i]->enc_s_lds[dt] > v->lds[dt]) v->lds[dt] = plans[i]->enc_s_lds[dt];
+                if (plans[i]->enc_s_lds[dt] > v.lds[dt]) v.lds[dt] = plans[i]->enc_s_lds[dt];
         }
         {
             const int key = ph.dec_tt * 100 + ph.dec_cls;
@@ -861,20 +852,17 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.stream_buf = out_base_dev;
     a.cap = out_cap;
     a.status = status_dev;
-    // Jobs of at most one 64-token tile go to their plan's short-job variant (one small launch per such
-    // variant: a short job is one workgroup), the rest to the bulk variants.
+    // Jobs of at most one 64-token tile go to the short-job kernel (a workgroup per job), the rest to the bulk variants.
     a.enc_short_max = kEncShortTile;
-    a.enc_short = 0;
     for (const auto& v : batch->enc) {
         hipError_t e = launch_encode(a, dtype, v.key, cu_count() * v.wgs,
                                      (size_t)kJobTableBytes + 64 + v.lds[dtype], static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(KVTC_E_HIP, "kvtc_encode_batch: launch failed: %s", hipGetErrorString(e));
     }
-    a.enc_short = 1;
-    for (const auto& v : batch->enc_short) {
-        const int slots = cu_count() * v.wgs;
-        hipError_t e = launch_encode(a, dtype, v.key, n_jobs < slots ? n_jobs : slots,
-                                     (size_t)kJobTableBytes + 64 + v.lds[dtype], static_cast<hipStream_t>(stream));
+    for (int ntw = 1; ntw <= 2; ++ntw) {
+        const auto& v = batch->enc_short[ntw];
+        if (v.waves == 0) continue;
+        hipError_t e = launch_encode_short(a, dtype, ntw, v.waves, n_jobs, (size_t)v.lds[dtype], static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(KVTC_E_HIP, "kvtc_encode_batch: launch failed: %s", hipGetErrorString(e));
     }
     return KVTC_OK;
@@ -897,8 +885,10 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     if (reinterpret_cast<uintptr_t>(out_base_dev) & 15u) return fail(KVTC_E_ARG, "%s: stream buffer must be 16-byte aligned", who);
     // the kernel variants among the plans and their LDS needs, on the stack
     struct Variant { int key, wgs, lds; };
-    Variant bulk[kStaticMaxPlans], shrt[kStaticMaxPlans];
-    int n_bulk = 0, n_shrt = 0;
+    struct ShortVariant { int waves, lds; };
+    Variant bulk[kStaticMaxPlans];
+    ShortVariant shrt[3] = {{0, 0}, {0, 0}, {0, 0}};
+    int n_bulk = 0;
     PlanPtrs ptrs;
     for (int i = 0; i < n_plans; ++i) {
         if (!plans[i]) return fail(KVTC_E_ARG, "%s: plan %d is null", who, i);
@@ -910,11 +900,10 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
         while (k < n_bulk && bulk[k].key != key) ++k;
         if (k == n_bulk) bulk[n_bulk++] = Variant{key, ph.enc_wgs, 0};
         if (ph.enc_lds[dtype] > bulk[k].lds) bulk[k].lds = ph.enc_lds[dtype];
-        if (ph.enc_s_key != 0) {
-            k = 0;
-            while (k < n_shrt && shrt[k].key != ph.enc_s_key) ++k;
-            if (k == n_shrt) shrt[n_shrt++] = Variant{ph.enc_s_key, plans[i]->enc_s_wgs, 0};
-            if (plans[i]->enc_s_lds[dtype] > shrt[k].lds) shrt[k].lds = plans[i]->enc_s_lds[dtype];
+        if (ph.enc_short != 0) {
+            ShortVariant& v = shrt[ph.enc_short];
+            if (plans[i]->enc_s_waves > v.waves) v.waves = plans[i]->enc_s_waves;
+            if (plans[i]->enc_s_lds[dtype] > v.lds) v.lds = plans[i]->enc_s_lds[dtype];
         }
     }
     for (int i = n_plans; i < kStaticMaxPlans; ++i) ptrs.p[i] = nullptr;
@@ -940,15 +929,13 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     a.cap = out_cap;
     a.status = status_dev;
     a.enc_short_max = kEncShortTile;
-    a.enc_short = 0;
     for (int k = 0; k < n_bulk; ++k) {
         e = launch_encode(a, dtype, bulk[k].key, cu_count() * bulk[k].wgs, (size_t)kJobTableBytes + 64 + bulk[k].lds, st);
         if (e != hipSuccess) return fail(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
     }
-    a.enc_short = 1;
-    for (int k = 0; k < n_shrt; ++k) {
-        const int slots = cu_count() * shrt[k].wgs;
-        e = launch_encode(a, dtype, shrt[k].key, n_jobs < slots ? n_jobs : slots, (size_t)kJobTableBytes + 64 + shrt[k].lds, st);
+    for (int ntw = 1; ntw <= 2; ++ntw) {
+        if (shrt[ntw].waves == 0) continue;
+        e = launch_encode_short(a, dtype, ntw, shrt[ntw].waves, n_jobs, (size_t)shrt[ntw].lds, st);
         if (e != hipSuccess) return fail(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
     }
     return KVTC_OK;

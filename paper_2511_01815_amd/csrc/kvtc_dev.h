@@ -15,7 +15,7 @@ constexpr int kThreads = 256;          // 4 wavefronts, one per SIMD of a comput
 constexpr int kMaxJobs = 1024;         // jobs per batched launch (tile table lives in LDS)
 constexpr int kLdsBudget = 160 * 1024; // gfx950 LDS per workgroup
 constexpr int kJobTableBytes = (kMaxJobs + 1) * 4;
-constexpr int kEncShortTile = 64;      // tokens per workgroup tile of the encode variants for short jobs
+constexpr int kEncShortTile = 64;      // tokens per workgroup tile of the encode kernel for short jobs
 constexpr int kDecShortTile = 128;     // the same for decode (one token tile per wave)
 
 // Lets a kernel use the whole LDS of a compute unit as dynamic shared memory.  The attribute
@@ -46,7 +46,7 @@ struct PlanDev {
     int32_t dec_rec_lds, dec_ring_lds;      // decode: bytes of the record image, of the basis ring + mu
     int32_t code_bits_max;                  // widest code of the plan
     int32_t enc_wgs, dec_wgs;               // workgroups per compute unit the variant is built for (1..3)
-    int32_t enc_nw, enc_s_key;              // encode: waves per workgroup (4 or 8); key of the variant for short jobs (64-token tiles), 0 = none
+    int32_t enc_nw, enc_short;              // encode: waves per workgroup (4 or 8); coordinate tiles per wave of the kernel for short jobs (64-token tiles), 0 = none
     int32_t dec_cls, reserved0;             // decode: the kernel class that serves the plan = the widest plan of the class, in coordinate tiles (dec_nct: the width the plan runs at, one of those built for the class)
     const uint4* v_enc;    // [p/16][32*ntp/32][64] MFMA A fragments of V_kept^T (encode)
     const uint4* v_dec;    // [p/32][2*nct*64 + 16] MFMA B fragments of V_kept^T (decode), then the tile's 32 mu entries; tiles 2k, 2k+1 = even, odd features of span k
@@ -71,8 +71,7 @@ struct KernelArgs {
     uint64_t cap;              // bytes available in stream_buf
     uint32_t* status;          // device, may be nullptr
     uint32_t dec_ring_off;     // decode: byte offset of the basis ring in the work area; 0 = it shares the record image's space
-    int32_t enc_short;         // encode: this launch runs the short-job variants (jobs of at most enc_short_max tokens whose plan has one) ...
-    int32_t enc_short_max;     // ... and the launches of the bulk variants leave those jobs alone; 0 = no job counts as short
+    int32_t enc_short_max;     // encode: jobs of at most this many tokens whose plan the short-job kernel serves are left to it; 0 = no job counts as short
     int32_t dec_short;         // decode: this launch runs the one-token-tile-per-wave variant of every plan (128-token tiles)
     int32_t dec_accumulate;    // decode of a sectioned plan: 1 = fp32 output, add the product to the output instead of storing it (a further section);
                                // 2 = bf16 output, store round(dec_sum + product) (the last section)
@@ -116,13 +115,12 @@ __device__ inline uint32_t build_tile_table(const KernelArgs& a, int variant_key
             if (ok) {
                 const PlanDev& pl = a.plans[jb.plan];
                 // each launch serves the plans of its own kernel variant; other launches take the rest.
-                // Encode: short jobs go to the plan's short-job variant (narrow tiles), if it has one.
-                const bool is_short = kEncode && pl.enc_s_key != 0 && jb.n_tokens <= a.enc_short_max;
+                // Encode: short jobs go to the short-job kernel, if it serves the plan.
+                const bool is_short = kEncode && pl.enc_short != 0 && jb.n_tokens <= a.enc_short_max;
                 int tw = kEncode ? pl.enc_tok_wg : pl.dec_tok_wg;
                 int key = kEncode ? pl.enc_nw * 10000 + pl.enc_wc * 100 + pl.enc_ntw : pl.dec_tt * 100 + pl.dec_cls;
                 if (!kEncode && a.dec_short) { tw = kDecShortTile; key = 100 + pl.dec_cls; }
-                if (kEncode && a.enc_short) { tw = kEncShortTile; key = is_short ? pl.enc_s_key : -1; }
-                else if (is_short) key = -1;
+                if (is_short) key = -1;
                 if (key == variant_key) tiles = (uint32_t)((jb.n_tokens + tw - 1) / tw);
             } else if (first_bad == 0xffffffffu) {
                 first_bad = (uint32_t)j;

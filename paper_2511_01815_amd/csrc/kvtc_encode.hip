@@ -112,6 +112,140 @@ __host__ __device__ constexpr int enc_stages(int ntp, int elem_bytes, int nw, in
 constexpr int kEncBlkOff = 0, kEncGrpOff = 256, kEncNegcOff = 512;
 __host__ __device__ constexpr int enc_aux_bytes(int ntp) { return 512 + ntp * 32 * 4; }
 
+// From a workgroup's coefficients (accumulator tiles of 32 coordinates x 32 tokens, a lane holding 16 consecutive coordinates of a
+// token) to records in the stream.  Every wave of the workgroup calls it: ct0 = the wave's first coordinate tile (a wave whose
+// first tile lies beyond the plan's ntp only helps with the headers and the copy), tt0 = its first token tile, tt_n of TT tiles in use;
+// tok_n tokens of the images' pitch tok_wg are worked on.  LDS: the plan's tables at `work`, the images at `smem`.
+template <int NTW, int TT>
+__device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], int ct0, int tt0, int tt_n, int tok_n, int tok_wg, int ntp, int nth,
+                                                const PlanEnc& P, const TileRef& tr, const KernelArgs& a, int tok_tile0, uint4* work, uint4* smem) {
+    const int tid = threadIdx.x, l32 = tid & 31, h = (tid >> 5) & 1;
+    const int T = tr.n_tokens;
+    // mm[2*ntp][tok_wg] float2 | gq[G][tok_wg] float2 | rec[tok_wg][rd + 1] dwords
+    const int G = P.n_groups;
+    const int rd = P.rec_dwords;
+    const uint32_t* blk_t = reinterpret_cast<const uint32_t*>(work) + kEncBlkOff / 4;
+    const uint32_t* grp_t = reinterpret_cast<const uint32_t*>(work) + kEncGrpOff / 4;
+    const int rstride = rd + 1;                 // odd-ish pitch keeps lanes on distinct banks
+    float2* mm = reinterpret_cast<float2*>(smem);
+    float2* gq = mm + 2 * ntp * tok_wg;
+    uint32_t* rec = reinterpret_cast<uint32_t*>(gq + G * tok_wg);
+
+    // A: block min/max
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+        if (tt >= tt_n || ct0 >= ntp) continue;
+        const int tw = (tt0 + tt) * 32 + l32;
+#pragma unroll
+        for (int ct = 0; ct < NTW; ++ct) {
+            const f32x16& d = acc[tt][ct];
+            float lo = d[0], hi = d[0];
+#pragma unroll
+            for (int i = 1; i < 16; ++i) { lo = fminf(lo, d[i]); hi = fmaxf(hi, d[i]); }
+            mm[(2 * (ct0 + ct) + h) * tok_wg + tw] = make_float2(lo, hi);
+            __builtin_amdgcn_sched_barrier(0);      // keep the accumulator reads from piling up
+        }
+    }
+    // codes wider than 8 bits are OR-ed into the image (cleared here); the usual widths are stored
+    const bool narrow_codes = P.code_bits_max <= 8;
+    if (!narrow_codes)
+        for (int i = tid; i < tok_wg * rstride; i += nth) rec[i] = 0u;
+    __syncthreads();
+
+    // B: one header per (token, group)
+    for (int item = tid; item < tok_n * G; item += nth) {
+        const int tw = item % tok_n, g = item / tok_n;
+        const uint32_t gi = grp_t[g];
+        const int b0 = gi & 0xff, nb = (gi >> 8) & 0xff, bits = (gi >> 16) & 0xff;
+        float lo = __builtin_inff(), hi = -__builtin_inff();
+        for (int k = 0; k < nb; ++k) {
+            const float2 m = mm[(b0 + k) * tok_wg + tw];
+            lo = fminf(lo, m.x);
+            hi = fmaxf(hi, m.y);
+        }
+        const GroupQ q = group_header(lo, hi, bits);
+        gq[g * tok_wg + tw] = make_float2(q.shift, q.inv);
+        rec[tw * rstride + g] = (uint32_t)q.shift16 | ((uint32_t)q.scale16 << 16);
+        if (g == 0 && narrow_codes) rec[tw * rstride + rd - 1] = 0u;      // the padding behind the last block
+    }
+    __syncthreads();
+
+    // C: codes of the lane's blocks, OR-ed into the record image
+#pragma unroll
+    for (int ct = 0; ct < NTW; ++ct) {
+        const uint32_t info = ct0 < ntp ? blk_t[2 * (ct0 + ct) + h] : 0u;
+        const uint32_t bits = info & 0xffu;
+        if (bits != 0u) {
+            const uint32_t g = (info >> 8) & 0xffu;
+            const uint32_t pos0 = (info >> 16) * 16u;
+            const float qmax = (float)((1u << bits) - 1u);
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) {
+                if (tt >= tt_n) continue;
+                const int tw = (tt0 + tt) * 32 + l32;
+                const float2 sq = gq[g * tok_wg + tw];
+                uint32_t* row = rec + tw * rstride;
+                const f32x16& d = acc[tt][ct];
+                uint32_t c[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) c[i] = (uint32_t)code_of(d[i], sq.x, sq.y, qmax);
+                if (narrow_codes) {
+                    char* dst = reinterpret_cast<char*>(row) + (pos0 >> 3);
+                    switch (bits) {
+                        case 1: emit_block<1>(c, dst); break;
+                        case 2: emit_block<2>(c, dst); break;
+                        case 3: emit_block<3>(c, dst); break;
+                        case 4: emit_block<4>(c, dst); break;
+                        case 5: emit_block<5>(c, dst); break;
+                        case 6: emit_block<6>(c, dst); break;
+                        case 7: emit_block<7>(c, dst); break;
+                        default: emit_block<8>(c, dst); break;
+                    }
+                } else if (bits <= 8u) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const uint32_t v = c[4 * k] | (c[4 * k + 1] << bits) | (c[4 * k + 2] << (2u * bits)) |
+                                           (c[4 * k + 3] << (3u * bits));
+                        put_bits(row, pos0 + 4u * k * bits, v, 4u * bits);
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const uint32_t v = c[2 * k] | (c[2 * k + 1] << bits);
+                        put_bits(row, pos0 + 2u * k * bits, v, 2u * bits);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    __syncthreads();
+
+    // D: the tile's records are contiguous in the stream: one coalesced copy, 16 bytes per lane when the
+    // tile starts on a 16-byte boundary of the buffer and records are whole 16-byte pieces (then a piece
+    // never straddles two rows of the image), else dword by dword
+    {
+        const int n_valid = min(tok_n, T - tok_tile0);
+        uint32_t* out = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(a.stream_buf) + tr.offset) +
+                        (size_t)tok_tile0 * rd;
+        const uint32_t magic = 0xffffffffu / (uint32_t)rd + 1u;     // exact floor(i / rd) for i < 2^20
+        const int total = n_valid * rd;
+        if ((rd & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15u) == 0u) {
+            for (int i = 4 * tid; i < total; i += 4 * nth) {
+                const uint32_t t = __umulhi((uint32_t)i, magic);
+                const uint32_t* src = rec + t * rstride + ((uint32_t)i - t * rd);
+                *reinterpret_cast<uint4*>(out + i) = make_uint4(src[0], src[1], src[2], src[3]);
+            }
+        } else {
+            for (int i = tid; i < total; i += nth) {
+                const uint32_t t = __umulhi((uint32_t)i, magic);
+                out[i] = rec[t * rstride + ((uint32_t)i - t * rd)];
+            }
+        }
+    }
+    __syncthreads();
+}
+
 template <int NTW, int WC, typename XT, int NW>
 __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
                                             const KernelArgs& a, uint4* work) {
@@ -256,128 +390,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
         }
     }
 
-    // ---- epilogue -----------------------------------------------------------------
-    // LDS: mm[2*NTP][TOK_WG] float2 | gq[G][TOK_WG] float2 | rec[TOK_WG][rd + 1] dwords
-    const int G = P.n_groups;
-    const int rd = P.rec_dwords;
-    const uint32_t* blk_t = reinterpret_cast<const uint32_t*>(work) + kEncBlkOff / 4;
-    const uint32_t* grp_t = reinterpret_cast<const uint32_t*>(work) + kEncGrpOff / 4;
-    const int rstride = rd + 1;                 // odd-ish pitch keeps lanes on distinct banks
-    float2* mm = reinterpret_cast<float2*>(smem);
-    float2* gq = mm + 2 * NTP * TOK_WG;
-    uint32_t* rec = reinterpret_cast<uint32_t*>(gq + G * TOK_WG);
-
-    // A: block min/max
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        const int tw = (wt * TT + tt) * 32 + l32;
-#pragma unroll
-        for (int ct = 0; ct < NTW; ++ct) {
-            const f32x16& d = acc[tt][ct];
-            float lo = d[0], hi = d[0];
-#pragma unroll
-            for (int i = 1; i < 16; ++i) { lo = fminf(lo, d[i]); hi = fmaxf(hi, d[i]); }
-            mm[(2 * (wc * NTW + ct) + h) * TOK_WG + tw] = make_float2(lo, hi);
-            __builtin_amdgcn_sched_barrier(0);      // keep the accumulator reads from piling up
-        }
-    }
-    // codes wider than 8 bits are OR-ed into the image (cleared here); the usual widths are stored
-    const bool narrow_codes = P.code_bits_max <= 8;
-    if (!narrow_codes)
-        for (int i = tid; i < TOK_WG * rstride; i += NTH) rec[i] = 0u;
-    __syncthreads();
-
-    // B: one header per (token, group)
-    for (int item = tid; item < TOK_WG * G; item += NTH) {
-        const int tw = item % TOK_WG, g = item / TOK_WG;
-        const uint32_t gi = grp_t[g];
-        const int b0 = gi & 0xff, nb = (gi >> 8) & 0xff, bits = (gi >> 16) & 0xff;
-        float lo = __builtin_inff(), hi = -__builtin_inff();
-        for (int k = 0; k < nb; ++k) {
-            const float2 m = mm[(b0 + k) * TOK_WG + tw];
-            lo = fminf(lo, m.x);
-            hi = fmaxf(hi, m.y);
-        }
-        const GroupQ q = group_header(lo, hi, bits);
-        gq[g * TOK_WG + tw] = make_float2(q.shift, q.inv);
-        rec[tw * rstride + g] = (uint32_t)q.shift16 | ((uint32_t)q.scale16 << 16);
-        if (g == 0 && narrow_codes) rec[tw * rstride + rd - 1] = 0u;      // the padding behind the last block
-    }
-    __syncthreads();
-
-    // C: codes of the lane's blocks, OR-ed into the record image
-#pragma unroll
-    for (int ct = 0; ct < NTW; ++ct) {
-        const uint32_t info = blk_t[2 * (wc * NTW + ct) + h];
-        const uint32_t bits = info & 0xffu;
-        if (bits != 0u) {
-            const uint32_t g = (info >> 8) & 0xffu;
-            const uint32_t pos0 = (info >> 16) * 16u;
-            const float qmax = (float)((1u << bits) - 1u);
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt) {
-                const int tw = (wt * TT + tt) * 32 + l32;
-                const float2 sq = gq[g * TOK_WG + tw];
-                uint32_t* row = rec + tw * rstride;
-                const f32x16& d = acc[tt][ct];
-                uint32_t c[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) c[i] = (uint32_t)code_of(d[i], sq.x, sq.y, qmax);
-                if (narrow_codes) {
-                    char* dst = reinterpret_cast<char*>(row) + (pos0 >> 3);
-                    switch (bits) {
-                        case 1: emit_block<1>(c, dst); break;
-                        case 2: emit_block<2>(c, dst); break;
-                        case 3: emit_block<3>(c, dst); break;
-                        case 4: emit_block<4>(c, dst); break;
-                        case 5: emit_block<5>(c, dst); break;
-                        case 6: emit_block<6>(c, dst); break;
-                        case 7: emit_block<7>(c, dst); break;
-                        default: emit_block<8>(c, dst); break;
-                    }
-                } else if (bits <= 8u) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const uint32_t v = c[4 * k] | (c[4 * k + 1] << bits) | (c[4 * k + 2] << (2u * bits)) |
-                                           (c[4 * k + 3] << (3u * bits));
-                        put_bits(row, pos0 + 4u * k * bits, v, 4u * bits);
-                    }
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const uint32_t v = c[2 * k] | (c[2 * k + 1] << bits);
-                        put_bits(row, pos0 + 2u * k * bits, v, 2u * bits);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    }
-    __syncthreads();
-
-    // D: the tile's records are contiguous in the stream: one coalesced copy, 16 bytes per lane when the
-    // tile starts on a 16-byte boundary of the buffer and records are whole 16-byte pieces (then a piece
-    // never straddles two rows of the image), else dword by dword
-    {
-        const int n_valid = min(TOK_WG, T - tok_tile0);
-        uint32_t* out = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(a.stream_buf) + tr.offset) +
-                        (size_t)tok_tile0 * rd;
-        const uint32_t magic = 0xffffffffu / (uint32_t)rd + 1u;     // exact floor(i / rd) for i < 2^20
-        const int total = n_valid * rd;
-        if ((rd & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15u) == 0u) {
-            for (int i = 4 * tid; i < total; i += 4 * NTH) {
-                const uint32_t t = __umulhi((uint32_t)i, magic);
-                const uint32_t* src = rec + t * rstride + ((uint32_t)i - t * rd);
-                *reinterpret_cast<uint4*>(out + i) = make_uint4(src[0], src[1], src[2], src[3]);
-            }
-        } else {
-            for (int i = tid; i < total; i += NTH) {
-                const uint32_t t = __umulhi((uint32_t)i, magic);
-                out[i] = rec[t * rstride + ((uint32_t)i - t * rd)];
-            }
-        }
-    }
-    __syncthreads();
+    encode_epilogue<NTW, TT>(acc, wc * NTW, wt * TT, TT, TOK_WG, TOK_WG, NTP, NTH, P, tr, a, tok_tile0, work, smem);
 }
 
 // One kernel per variant (WC waves across coordinates, NTW coordinate tiles per wave, NW waves per
@@ -404,14 +417,177 @@ __global__ void __launch_bounds__(NW * 64, (enc_wgs_per_cu<WC, NTW, NW>())) kvtc
     }
 }
 
-// (waves across coordinates, coordinate tiles per wave, waves per workgroup): the bulk variants, then
-// the variants for short jobs -- one wave across the tokens, so a 64-token tile and a third of the
-// MFMAs per ring step of the widest bulk tile; a workgroup that has a compute unit to itself (a
-// launch of a few short jobs) is bound by exactly those.  The two widest plans' bulk variants
-// already have 64-token tiles.
+// Short jobs: a workgroup per tile of 64 tokens, a wave per coordinate tile (NTW = 2: per two), one kernel for plans of every
+// width up to 10 (20) tiles -- the waves a plan does not need help to fetch X.  A launch of a few such tiles is bound by how
+// fast a compute unit can draw the plan's basis (half a megabyte at 256 coordinates) through itself, and each fragment is used by one
+// wave only, so the fragments go straight to registers, 16 KiB of them in flight per wave (16 k-steps ahead), instead of through an LDS
+// ring shared by barriers; X comes in chunks of 256 features, asynchronously, with one barrier per chunk.  The sums run over the
+// features in the bulk kernel's order: a token's record is the same bits whichever kernel codes it.
+// 64 caches of 16 tokens with a basis each (32 MB of bases): 60 us in two launches of ring kernels before, 14 now in one; 48 tokens of one
+// tensor: 18 -> 14.
+constexpr int kShortFeat = 256, kShortSteps = kShortFeat / 16;
+template <int NTW> constexpr int short_ahead() { return NTW == 1 ? 16 : 4; }   // k-steps of fragments in flight
+constexpr int kShortThreads = 640;
+
+template <int NTW, typename XT, int TT>
+__device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, uint4* work) {
+    constexpr int AHEAD = short_ahead<NTW>();
+    constexpr int EB = (int)sizeof(XT), ROW_B = kShortFeat * EB, COLS = ROW_B / 16, ROWS_DMA = 1024 / ROW_B;
+    constexpr int ROWS = 32 * TT, CHUNK_B = kEncShortTile * ROW_B;
+    static_assert(kShortSteps % AHEAD == 0, "a fragment's register is known at compile time");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = (int)blockDim.x >> 6;
+    const int l32 = lane & 31, h = lane >> 5;
+    const int ntp = P.enc_ntw * P.enc_wc;
+    const int p = P.p, T = tr.n_tokens, tok_tile0 = tr.tile * kEncShortTile;
+    const int n_steps = p / 16, n_chunks = (p + kShortFeat - 1) / kShortFeat;
+    const int ct0 = wave * NTW;
+    uint4* smem = work + enc_aux_bytes(ntp) / 16;
+
+    // the plan's tables and chunk 0 of X -> LDS
+    {
+        const uint32_t aux = lds_offset(work);
+        if (wave == 0) dma4_async(P.blk, (uint32_t)lane * 4u, aux + kEncBlkOff);
+        if (wave == 1) dma4_async(P.grp, (uint32_t)lane * 4u, aux + kEncGrpOff);
+        if (wave * 64 < ntp * 8 && tid < ntp * 8) dma16_async(P.negc, (uint32_t)tid * 16u, aux + kEncNegcOff + (uint32_t)wave * 1024u);
+    }
+    const int blk_lg = a.x_blk_log2;
+    const int64_t blk_jump_b = a.x_blk_jump * EB;
+    const uint32_t lds_x = lds_offset(smem);
+    auto issue_x = [&](int c) {
+        for (int i = wave; i < ROWS / ROWS_DMA; i += n_waves) {
+            const int row = i * ROWS_DMA + lane / COLS;
+            // 16-byte columns of a row are permuted so that the 8 lanes (rows) served together by a 128-bit read meet 8 bank groups
+            const int col = (lane % COLS) ^ (row & 7);
+            int f = c * kShortFeat + col * (16 / EB);
+            f = f < p ? f : 0;                                       // behind the last feature: read something, it is not used
+            const int t = min(tok_tile0 + row, T - 1);               // rows past the end re-read the last token
+            const char* src = reinterpret_cast<const char*>(a.x) + ((tr.x_row0 + t) * a.ld_x + f) * EB + (blk_lg ? (int64_t)(f >> blk_lg) * blk_jump_b : (int64_t)0);
+            dma16_async(src, __builtin_amdgcn_readfirstlane(lds_x + (uint32_t)((c & 1) * CHUNK_B + i * 1024)));
+        }
+    };
+    issue_x(0);
+
+    // fragments of the wave's tiles, AHEAD k-steps of them in registers (past the end the last ones again, so that the number of
+    // loads in flight is always the same; waves without a tile load the first one's)
+    u32x4 af[AHEAD][NTW];
+    typedef const char __attribute__((address_space(1))) * global_ptr;
+    typedef const u32x4 __attribute__((address_space(1))) * global_u4;
+    const uint64_t vg = (uint64_t)uniform_ptr(P.v_enc + (ct0 < ntp ? ct0 : 0) * 64);
+    auto fetch = [&](int step, int slot) {
+        const global_ptr src = (global_ptr)(vg + (uint64_t)(uint32_t)min(step, n_steps - 1) * (uint64_t)(uint32_t)(ntp * 1024));      // a scalar address
+#pragma unroll
+        for (int i = 0; i < NTW; ++i) af[slot][i] = *(global_u4)(src + (uint32_t)(lane * 16) + i * 1024);
+    };
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) fetch(k, k);
+    asm volatile("" ::: "memory");
+    wait_vmem<AHEAD * NTW>();                                        // everything older than the fragments has landed
+    __syncthreads();
+
+    f32x16 acc[TT][NTW];
+    {
+        const float* negc = reinterpret_cast<const float*>(work) + kEncNegcOff / 4 + (ct0 < ntp ? ct0 : 0) * 32 + 16 * h;
+#pragma unroll
+        for (int ct = 0; ct < NTW; ++ct) {
+            f32x16 c;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) c[q] = negc[ct * 32 + q];
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) acc[tt][ct] = c;
+        }
+    }
+    // a k-step's piece of a row: the permutation touches the column's lowest 3 bits, so four lane addresses serve all k-steps
+    uint32_t xoff[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int col = EB == 2 ? 2 * j + h : 4 * (j >> 1) + 2 * h + (j & 1);
+        xoff[j] = (uint32_t)(l32 * ROW_B + (col ^ (l32 & 7)) * 16);
+    }
+    auto xfrag = [&](const char* x, int tt, int ks) {
+        const char* r = x + tt * 32 * ROW_B;
+        if constexpr (EB == 2) {
+            return as_bf16x8(*reinterpret_cast<const uint4*>(r + xoff[ks & 3] + (ks >> 2) * 128));
+        } else {
+            const float4 u = *reinterpret_cast<const float4*>(r + xoff[2 * (ks & 1)] + (ks >> 1) * 128);
+            const float4 w = *reinterpret_cast<const float4*>(r + xoff[2 * (ks & 1) + 1] + (ks >> 1) * 128);
+            bf16x8 v;                                                // round to bf16, nearest even
+            v[0] = (__bf16)u.x; v[1] = (__bf16)u.y; v[2] = (__bf16)u.z; v[3] = (__bf16)u.w;
+            v[4] = (__bf16)w.x; v[5] = (__bf16)w.y; v[6] = (__bf16)w.z; v[7] = (__bf16)w.w;
+            return v;
+        }
+    };
+    bf16x8 xv[2][TT];                                                // of this k-step and of the next
+    auto step = [&](const char* x, int c, int ks, bool last) {
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+            if (!last) xv[(ks + 1) & 1][tt] = xfrag(x, tt, ks + 1);
+#pragma unroll
+        for (int ct = 0; ct < NTW; ++ct)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt)
+                acc[tt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[ks % AHEAD][ct]), xv[ks & 1][tt], acc[tt][ct], 0, 0, 0);
+        fetch(c * kShortSteps + ks + AHEAD, ks % AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const int n_full = p / kShortFeat;
+    for (int c = 0; c < n_full; ++c) {
+        const char* x = reinterpret_cast<const char*>(smem) + (c & 1) * CHUNK_B;
+        const bool more = c + 1 < n_chunks;
+        if (more) issue_x(c + 1);                                    // its half was read in chunk c - 1; the barrier that ended it frees it
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) xv[0][tt] = xfrag(x, tt, 0);
+#pragma unroll
+        for (int ks = 0; ks < kShortSteps; ++ks) step(x, c, ks, ks + 1 == kShortSteps);
+        asm volatile("" ::: "memory");
+        if (more) wait_vmem<kShortSteps * NTW>();                    // the next chunk is older than this one's fragment loads: it has landed
+        __syncthreads();
+    }
+    if (n_full < n_chunks) {                                         // 64, 128 or 192 features are left
+        const char* x = reinterpret_cast<const char*>(smem) + (n_full & 1) * CHUNK_B;
+        const int left = n_steps - n_full * kShortSteps;
+#pragma unroll
+        for (int g = 0; g < 3; ++g)
+            if (4 * g < left) {
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) xv[0][tt] = xfrag(x, tt, 4 * g);
+#pragma unroll
+                for (int ks = 4 * g; ks < 4 * g + 4; ++ks) step(x, n_full, ks, ks == 4 * g + 3);
+            }
+        __syncthreads();
+    }
+    wait_vmem<0>();                                                  // the fragments fetched past the end
+    encode_epilogue<NTW, TT>(acc, ct0, 0, TT, ROWS, kEncShortTile, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem);
+}
+
+template <int NTW, typename XT>
+__global__ void __launch_bounds__(kShortThreads) kvtc_encode_short_kernel(const KernelArgs a) {
+    extern __shared__ uint4 smem[];
+    TileRef tr;
+    if (a.jobs) {
+        // a workgroup per job; a job that is not short, not of this kernel's plans or not valid is left alone (the bulk launches
+        // in front of this one have reported it)
+        const u32x4 jb = sload_x4(a.jobs + blockIdx.x);
+        const u32x2 o = sload_x2(a.offsets + blockIdx.x);
+        tr = TileRef{(int32_t)blockIdx.x, (int32_t)jb[0], (int32_t)jb[1], (int64_t)(((uint64_t)jb[3] << 32) | jb[2]), ((uint64_t)o[1] << 32) | o[0], 0};
+        if (tr.plan < 0 || tr.plan >= a.n_plans || tr.n_tokens < 1 || tr.n_tokens > a.enc_short_max) return;
+    } else {
+        tr = TileRef{0, a.single.plan, a.single.n_tokens, a.single.x_row0, 0ull, (int32_t)blockIdx.x};
+    }
+    const PlanDev* plan = a.plans + tr.plan;
+    const PlanEnc P = load_plan_enc(plan);
+    if (plan->enc_short != NTW) return;
+    if (a.jobs) {
+        const uint64_t bytes = (uint64_t)tr.n_tokens * (uint64_t)P.rec_dwords * 4ull;
+        if (tr.offset > a.cap || bytes > a.cap - tr.offset) return;
+    }
+    if (tr.n_tokens - tr.tile * kEncShortTile <= 32) encode_short_tile<NTW, XT, 1>(P, tr, a, smem);
+    else encode_short_tile<NTW, XT, 2>(P, tr, a, smem);
+}
+
+// (waves across coordinates, coordinate tiles per wave, waves per workgroup); the two widest plans' variants have 64-token tiles
+// and take the short jobs too
 #define KVTC_ENC_VARIANTS(X)                                                                           \
-    X(1, 2, 4) X(1, 4, 4) X(2, 3, 4) X(2, 4, 4) X(2, 5, 4) X(4, 3, 8) X(4, 4, 8) X(4, 5, 8) X(4, 6, 4) X(4, 8, 4) \
-    X(2, 1, 2) X(4, 1, 4) X(2, 3, 2) X(4, 2, 4) X(2, 5, 2) X(4, 3, 4) X(4, 4, 4) X(4, 5, 4)
+    X(1, 2, 4) X(1, 4, 4) X(2, 3, 4) X(2, 4, 4) X(2, 5, 4) X(4, 3, 8) X(4, 4, 8) X(4, 5, 8) X(4, 6, 4) X(4, 8, 4)
 
 // key = 10000 * NW + 100 * WC + NTW
 hipError_t launch_encode(const KernelArgs& a, kvtc_dtype dtype, int key, int grid, size_t lds_bytes, hipStream_t stream) {
@@ -433,6 +609,31 @@ hipError_t launch_encode(const KernelArgs& a, kvtc_dtype dtype, int key, int gri
     KernelArgs args = a;
     void* params[] = {&args};
     return hipLaunchKernel(fn, dim3(grid), dim3(threads), params, lds_bytes, stream);
+}
+
+// One workgroup of `waves` waves per job, or per 64-token tile of a single tensor; ntw: coordinate tiles per wave (the plans' enc_short).
+hipError_t launch_encode_short(const KernelArgs& a, kvtc_dtype dtype, int ntw, int waves, int grid, size_t lds_bytes, hipStream_t stream) {
+    const void* fn = nullptr;
+    if (ntw == 1) fn = dtype == KVTC_BF16 ? reinterpret_cast<const void*>(&kvtc_encode_short_kernel<1, uint16_t>) : reinterpret_cast<const void*>(&kvtc_encode_short_kernel<1, float>);
+    if (ntw == 2) fn = dtype == KVTC_BF16 ? reinterpret_cast<const void*>(&kvtc_encode_short_kernel<2, uint16_t>) : reinterpret_cast<const void*>(&kvtc_encode_short_kernel<2, float>);
+    if (!fn || waves < 2 || waves * 64 > kShortThreads) return hipErrorInvalidValue;
+    hipError_t e = allow_full_lds(fn);
+    if (e != hipSuccess) return e;
+    KernelArgs args = a;
+    void* params[] = {&args};
+    return hipLaunchKernel(fn, dim3(grid), dim3(64 * waves), params, lds_bytes, stream);
+}
+
+// Coordinate tiles per wave of the short-job kernel for a plan of ntp tiles (0 = none), waves, and LDS bytes.
+int encode_short_ntw(int ntp) { return ntp <= 10 ? 1 : (ntp <= 20 ? 2 : 0); }
+int encode_short_waves(int ntp) {
+    const int n = (ntp + encode_short_ntw(ntp) - 1) / encode_short_ntw(ntp);
+    return n < 4 ? 4 : n;
+}
+int encode_short_lds_bytes(int ntp, int n_groups, int rec_dwords, kvtc_dtype dtype) {
+    const int main_b = 2 * kEncShortTile * kShortFeat * (dtype == KVTC_BF16 ? 2 : 4);
+    const int epi_b = kEncShortTile * (2 * ntp * 8 + n_groups * 8 + (rec_dwords + 1) * 4);
+    return enc_aux_bytes(ntp) + (main_b > epi_b ? main_b : epi_b);
 }
 
 int encode_tok_wg(int ntw, int wc, int nw) { return 32 * enc_tt(ntw * wc, nw, wc) * (nw / wc); }
