@@ -97,6 +97,16 @@ int cu_count() {
     return n[dev];
 }
 
+// 64-token tiles that each of n_jobs jobs may have and still all run at once on the short-job kernel (`pairs`: two workgroups
+// share a compute unit, those of up to 8 waves with a coordinate tile each), at least one: a job of no more is a short one.  The bulk tiles are three to four times as large: their
+// launch has fewer workgroups than the chip, each walking all features.  One tensor of 4096 tokens at 16x: 42 us on the bulk tile, 21 on
+// this;
+// where the tiles need a second round the bulk kernel, which reads the basis less often, is the faster one again.
+int short_tiles_per_job(int n_jobs, bool pairs) {
+    const int n = cu_count() * (pairs ? 2 : 1) / n_jobs;
+    return n < 1 ? 1 : n;
+}
+
 // Row pitch limit (elements): the kernels address a workgroup tile of up to 256 rows with 32-bit byte offsets.
 constexpr int kMaxPitch = 1 << 21;
 
@@ -552,7 +562,7 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
     // A tensor short enough for all its 64-token tiles to run at once (one wave of workgroups) runs the short-job kernel.
     const int64_t tiles_short = (n_tokens + kEncShortTile - 1) / kEncShortTile;
     hipError_t e;
-    if (plan->h.enc_short != 0 && tiles_short <= (int64_t)cu_count() * (plan->enc_s_waves <= 8 ? 2 : 1)) {
+    if (plan->h.enc_short != 0 && tiles_short <= short_tiles_per_job(1, plan->h.enc_short == 1 && plan->enc_s_waves <= 8)) {
         e = launch_encode_short(a, dtype, plan->h.enc_short, plan->enc_s_waves, (int)tiles_short, (size_t)plan->enc_s_lds[dtype], static_cast<hipStream_t>(stream));
     } else {
         const int64_t tiles = (n_tokens + plan->h.enc_tok_wg - 1) / plan->h.enc_tok_wg;
@@ -852,8 +862,9 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.stream_buf = out_base_dev;
     a.cap = out_cap;
     a.status = status_dev;
-    // Jobs of at most one 64-token tile go to the short-job kernel (a workgroup per job), the rest to the bulk variants.
-    a.enc_short_max = kEncShortTile;
+    // Short jobs go to the short-job kernel, the rest to the bulk variants.
+    const int s_tiles = short_tiles_per_job(n_jobs, batch->enc_short[1].waves <= 8 && batch->enc_short[2].waves == 0);
+    a.enc_short_max = s_tiles * kEncShortTile;
     for (const auto& v : batch->enc) {
         hipError_t e = launch_encode(a, dtype, v.key, cu_count() * v.wgs,
                                      (size_t)kJobTableBytes + 64 + v.lds[dtype], static_cast<hipStream_t>(stream));
@@ -862,7 +873,7 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     for (int ntw = 1; ntw <= 2; ++ntw) {
         const auto& v = batch->enc_short[ntw];
         if (v.waves == 0) continue;
-        hipError_t e = launch_encode_short(a, dtype, ntw, v.waves, n_jobs, (size_t)v.lds[dtype], static_cast<hipStream_t>(stream));
+        hipError_t e = launch_encode_short(a, dtype, ntw, v.waves, n_jobs * s_tiles, (size_t)v.lds[dtype], static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(KVTC_E_HIP, "kvtc_encode_batch: launch failed: %s", hipGetErrorString(e));
     }
     return KVTC_OK;
@@ -928,14 +939,15 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     a.stream_buf = out_base_dev;
     a.cap = out_cap;
     a.status = status_dev;
-    a.enc_short_max = kEncShortTile;
+    const int s_tiles = short_tiles_per_job(n_jobs, shrt[1].waves <= 8 && shrt[2].waves == 0);
+    a.enc_short_max = s_tiles * kEncShortTile;
     for (int k = 0; k < n_bulk; ++k) {
         e = launch_encode(a, dtype, bulk[k].key, cu_count() * bulk[k].wgs, (size_t)kJobTableBytes + 64 + bulk[k].lds, st);
         if (e != hipSuccess) return fail(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
     }
     for (int ntw = 1; ntw <= 2; ++ntw) {
         if (shrt[ntw].waves == 0) continue;
-        e = launch_encode_short(a, dtype, ntw, shrt[ntw].waves, n_jobs, (size_t)shrt[ntw].lds, st);
+        e = launch_encode_short(a, dtype, ntw, shrt[ntw].waves, n_jobs * s_tiles, (size_t)shrt[ntw].lds, st);
         if (e != hipSuccess) return fail(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
     }
     return KVTC_OK;

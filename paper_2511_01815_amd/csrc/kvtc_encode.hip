@@ -564,12 +564,14 @@ __global__ void __launch_bounds__(kShortThreads) kvtc_encode_short_kernel(const 
     extern __shared__ uint4 smem[];
     TileRef tr;
     if (a.jobs) {
-        // a workgroup per job; a job that is not short, not of this kernel's plans or not valid is left alone (the bulk launches
-        // in front of this one have reported it)
-        const u32x4 jb = sload_x4(a.jobs + blockIdx.x);
-        const u32x2 o = sload_x2(a.offsets + blockIdx.x);
-        tr = TileRef{(int32_t)blockIdx.x, (int32_t)jb[0], (int32_t)jb[1], (int64_t)(((uint64_t)jb[3] << 32) | jb[2]), ((uint64_t)o[1] << 32) | o[0], 0};
-        if (tr.plan < 0 || tr.plan >= a.n_plans || tr.n_tokens < 1 || tr.n_tokens > a.enc_short_max) return;
+        // a job that is not short, not of this kernel's plans or not valid is left alone (the bulk launches in front of this one have
+        // reported it)
+        // the first tiles of all jobs come first: they spread over the XCDs, and workgroups that find no tile wait behind them
+        const int tile = (int)blockIdx.x / a.n_jobs, job = (int)blockIdx.x - tile * a.n_jobs;
+        const u32x4 jb = sload_x4(a.jobs + job);
+        const u32x2 o = sload_x2(a.offsets + job);
+        tr = TileRef{job, (int32_t)jb[0], (int32_t)jb[1], (int64_t)(((uint64_t)jb[3] << 32) | jb[2]), ((uint64_t)o[1] << 32) | o[0], tile};
+        if (tr.plan < 0 || tr.plan >= a.n_plans || tr.n_tokens <= tr.tile * kEncShortTile || tr.n_tokens > a.enc_short_max) return;
     } else {
         tr = TileRef{0, a.single.plan, a.single.n_tokens, a.single.x_row0, 0ull, (int32_t)blockIdx.x};
     }
