@@ -41,6 +41,7 @@ hipError_t launch_calib_moments(const void* x, kvtc_dtype dtype, int64_t n_token
                                 double* sum, double* gram, hipStream_t stream);
 int decode_rec_bytes(int tt, int rec_dwords);
 int decode_ring_bytes(int nct);
+int decode_wide_bytes(int tt, int nct, int rec_dwords);
 int decode_stage_u4(int nct);
 }  // namespace kvtc
 
@@ -306,24 +307,28 @@ static kvtc_status plan_create_impl(kvtc_plan** out, int p, int r, const float* 
     // decode: the widths the kernels are built for, with the register class (= its widest member) that serves each;
     // odd widths where the calibrated plans of the 8B-shaped cache fall (224 = 7, 272 = 9, 528 = 17 tiles): in decode
     // the coordinates are the contraction index, so a tile less is that much less matrix work and basis traffic
-    // {token tiles per wave, coordinate tiles, class, workgroups per compute unit}
+    // {token tiles per wave (of the wide kernels, class above 10: per workgroup), coordinate tiles, class, workgroups per compute unit}
     static const int dec_tab[][4] = {{2, 2, 4, 3}, {2, 4, 4, 3}, {2, 6, 10, 2}, {2, 7, 10, 2}, {2, 8, 10, 2}, {2, 9, 10, 2}, {2, 10, 10, 2},
-                                     {2, 12, 18, 1}, {2, 16, 18, 1}, {2, 17, 18, 1}, {2, 18, 18, 1}, {2, 20, 24, 1}, {2, 24, 24, 1}, {1, 32, 32, 1}};
+                                     {4, 12, 18, 1}, {4, 14, 18, 1}, {4, 16, 18, 1}, {4, 18, 18, 1}, {2, 20, 32, 1}, {2, 24, 32, 1}, {2, 28, 32, 1}, {2, 32, 32, 1}};
     d.dec_tt = 0;
     for (auto& e : dec_tab)
         if (e[1] >= nt) { d.dec_tt = e[0]; d.dec_nct = e[1]; d.dec_cls = e[2]; d.dec_wgs = e[3]; break; }
     if (d.enc_wc == 0 || d.dec_tt == 0) return fail(KVTC_E_UNSUPPORTED, "kvtc_plan_create: no kernel variant for r=%d", r);
     const int ntp = d.enc_ntw * d.enc_wc;
     d.enc_tok_wg = encode_tok_wg(d.enc_ntw, d.enc_wc, d.enc_nw);
-    d.dec_tok_wg = 4 * 32 * d.dec_tt;
+    const bool dec_wide = d.dec_cls > 10;
+    d.dec_tok_wg = (dec_wide ? 1 : 4) * 32 * d.dec_tt;
     {
         d.enc_lds[KVTC_BF16] = encode_lds_bytes(d.enc_ntw, d.enc_wc, d.enc_nw, n_groups, d.rec_dwords, KVTC_BF16);
         d.enc_lds[KVTC_F32] = encode_lds_bytes(d.enc_ntw, d.enc_wc, d.enc_nw, n_groups, d.rec_dwords, KVTC_F32);
-        d.dec_rec_lds = decode_rec_bytes(d.dec_tt, d.rec_dwords);
-        d.dec_ring_lds = decode_ring_bytes(d.dec_nct);
+        d.dec_rec_lds = dec_wide ? decode_wide_bytes(d.dec_tt, d.dec_nct, d.rec_dwords) : decode_rec_bytes(d.dec_tt, d.rec_dwords);
+        d.dec_ring_lds = dec_wide ? 0 : decode_ring_bytes(d.dec_nct);
     }
     const int lds_cap = kLdsBudget - kJobTableBytes - 64;
-    const int dec_need = d.dec_rec_lds > d.dec_ring_lds ? d.dec_rec_lds : d.dec_ring_lds;
+    // the record sizes a plan may have: those whose image of 256 tokens (128 beyond 768 coordinates) fits the LDS, also where
+    // the wide kernels would get by with less
+    const int dec_limit = decode_rec_bytes(d.dec_nct > 24 ? 1 : 2, d.rec_dwords);
+    const int dec_need = std::max(std::max(d.dec_rec_lds, d.dec_ring_lds), dec_limit);
     if (d.enc_lds[0] > lds_cap || d.enc_lds[1] > lds_cap || dec_need > lds_cap)
         return fail(KVTC_E_UNSUPPORTED,
                     "kvtc_plan_create: record of %d bytes with r=%d needs %d/%d/%d bytes of LDS, %d available",
@@ -612,7 +617,8 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
     const int64_t spans = plan->h.p / 64;
     const int64_t tiles_short = (n_tokens + kDecShortTile - 1) / kDecShortTile;
     hipError_t e;
-    if (plan->h.dec_tt == 2 && tiles_short <= slots) {
+    const bool wide = plan->h.dec_cls > 10;
+    if (!wide && tiles_short <= slots) {
         const DecLayout lay = decode_layout(decode_rec_bytes(1, plan->h.rec_dwords), plan->h.dec_ring_lds, plan->h.dec_wgs);
         a.dec_ring_off = lay.ring_off;
         a.dec_short = 1;
@@ -620,7 +626,8 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
         e = launch_decode(a, dtype, 100 + plan->h.dec_cls, grid, lay.lds_bytes, static_cast<hipStream_t>(stream));
     } else {
         const int64_t tiles = (n_tokens + plan->h.dec_tok_wg - 1) / plan->h.dec_tok_wg;
-        const int grid = (int)(tiles * spans < slots ? tiles * spans : slots);
+        const int64_t shares = wide ? (spans < 4 ? 1 : spans / 4) : spans;       // workgroups a tile may be shared among
+        const int grid = (int)(tiles * shares < slots ? tiles * shares : slots);
         const DecLayout lay = decode_layout(plan->h.dec_rec_lds, plan->h.dec_ring_lds, plan->h.dec_wgs);
         a.dec_ring_off = lay.ring_off;
         e = launch_decode(a, dtype, plan->h.dec_tt * 100 + plan->h.dec_cls, grid, lay.lds_bytes, static_cast<hipStream_t>(stream));
