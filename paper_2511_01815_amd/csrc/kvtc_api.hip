@@ -295,12 +295,12 @@ static kvtc_status plan_create_impl(kvtc_plan** out, int p, int r, const float* 
     // Up to 320 padded coordinates a 4-wave workgroup keeps its tile (64 tokens per wave across the
     // tokens; 96 in the 8-tile variant) x all its coordinates in 256 registers per lane and two
     // workgroups share a compute unit (three where 168 registers suffice: measured 5 % faster on the
-    // 6-tile encode).  From 321 to 640, 8-wave workgroups (two waves per SIMD at 256 registers,
-    // 128-token tiles, four waves across the coordinates) measured twice as fast as 4-wave ones with
-    // 512 registers; beyond that only the latter hold a tile.
+    // 6-tile encode).  Wider plans get 8-wave workgroups (two waves per SIMD at 256 registers): 128-token tiles with four waves
+    // across the coordinates up to 640 of them, twice as fast as 4 waves of 512 registers; 64-token tiles with eight waves
+    // across up to 1024 (1024 of 4096 features, 32768 tokens: 390 us as 4 waves of 512, 345 so).
     // {waves across coordinates, tiles per wave, workgroups per compute unit, waves per workgroup}, ascending padded width
     static const int enc_tab[][4] = {{1, 2, 2, 4}, {1, 4, 2, 4}, {2, 3, 3, 4}, {2, 4, 2, 4}, {2, 5, 2, 4},
-                                     {4, 3, 1, 8}, {4, 4, 1, 8}, {4, 5, 1, 8}, {4, 6, 1, 4}, {4, 8, 1, 4}};
+                                     {4, 3, 1, 8}, {4, 4, 1, 8}, {4, 5, 1, 8}, {8, 3, 1, 8}, {8, 4, 1, 8}};
     d.enc_wc = 0;
     for (auto& e : enc_tab)
         if (e[0] * e[1] >= nt) { d.enc_wc = e[0]; d.enc_ntw = e[1]; d.enc_wgs = e[2]; d.enc_nw = e[3]; break; }

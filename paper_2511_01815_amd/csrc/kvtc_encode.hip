@@ -3,7 +3,7 @@
 // (Paper, Section "Method", mode "Compression"; Sections "Feature decorrelation" and
 // "Quantization".)
 //
-// Work decomposition.  A workgroup (4 wavefronts, or 8 for plans of 321..640 padded coordinates)
+// Work decomposition.  A workgroup (4 wavefronts, or 8 for plans of more than 320 padded coordinates)
 // owns a tile of tokens and ALL kept coordinates of those tokens, because a group's min/max
 // needs every coordinate of the group before any of its codes exists.
 // The product is computed transposed, D^T = V_kept^T X^T, with the 32x32x16 bf16 MFMA:
@@ -396,7 +396,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
 // One kernel per variant (WC waves across coordinates, NTW coordinate tiles per wave, NW waves per
 // workgroup): plans of up to 320 padded coordinates fit 4-wave workgroups with 256 registers per lane,
 // two per compute unit (one hides the other's memory waits and epilogue); wider plans get the compute
-// unit to themselves, as 8 waves of 256 registers or 4 of 512.  A batched launch serves only the jobs
+// unit to themselves, as 8 waves of 256 registers.  A batched launch serves only the jobs
 // whose plan uses its variant.
 // (must agree with the host's variant table)
 template <int WC, int NTW, int NW> constexpr int enc_wgs_per_cu() {
@@ -589,7 +589,7 @@ __global__ void __launch_bounds__(kShortThreads) kvtc_encode_short_kernel(const 
 // (waves across coordinates, coordinate tiles per wave, waves per workgroup); the two widest plans' variants have 64-token tiles
 // and take the short jobs too
 #define KVTC_ENC_VARIANTS(X)                                                                           \
-    X(1, 2, 4) X(1, 4, 4) X(2, 3, 4) X(2, 4, 4) X(2, 5, 4) X(4, 3, 8) X(4, 4, 8) X(4, 5, 8) X(4, 6, 4) X(4, 8, 4)
+    X(1, 2, 4) X(1, 4, 4) X(2, 3, 4) X(2, 4, 4) X(2, 5, 4) X(4, 3, 8) X(4, 4, 8) X(4, 5, 8) X(8, 3, 8) X(8, 4, 8)
 
 // key = 10000 * NW + 100 * WC + NTW
 hipError_t launch_encode(const KernelArgs& a, kvtc_dtype dtype, int key, int grid, size_t lds_bytes, hipStream_t stream) {
