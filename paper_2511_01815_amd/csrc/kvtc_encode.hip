@@ -113,13 +113,17 @@ constexpr int kEncBlkOff = 0, kEncGrpOff = 256, kEncNegcOff = 512;
 __host__ __device__ constexpr int enc_aux_bytes(int ntp) { return 512 + ntp * 32 * 4; }
 
 // From a workgroup's coefficients (accumulator tiles of 32 coordinates x 32 tokens, a lane holding 16 consecutive coordinates of a
-// token) to records in the stream.  Every wave of the workgroup calls it: ct0 = the wave's first coordinate tile (a wave whose
-// first tile lies beyond the plan's ntp only helps with the headers and the copy), tt0 = its first token tile, tt_n of TT tiles in use;
+// token) to records in the stream.  Every wave of the workgroup calls it: ct0 = the wave's first coordinate tile (HELPERS: a wave
+// whose first tile lies beyond the plan's ntp only helps with the headers and the copy), tt0 = its first of TT token tiles;
 // tok_n tokens of the images' pitch tok_wg are worked on.  LDS: the plan's tables at `work`, the images at `smem`.
-template <int NTW, int TT>
-__device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], int ct0, int tt0, int tt_n, int tok_n, int tok_wg, int ntp, int nth,
+template <int NTW, int TT, bool HELPERS>
+__device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], int ct0, int tt0, int tok_n, int tok_wg, int ntp, int nth,
                                                 const PlanEnc& P, const TileRef& tr, const KernelArgs& a, int tok_tile0, uint4* work, uint4* smem) {
-    const int tid = threadIdx.x, l32 = tid & 31, h = (tid >> 5) & 1;
+    // (through an empty asm, so that nothing of the epilogue's lane addresses is worked out ahead of the main loop and kept
+    // through it: its registers are all taken)
+    int tid = (int)threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int l32 = tid & 31, h = (tid >> 5) & 1;
     const int T = tr.n_tokens;
     // mm[2*ntp][tok_wg] float2 | gq[G][tok_wg] float2 | rec[tok_wg][rd + 1] dwords
     const int G = P.n_groups;
@@ -134,7 +138,7 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
     // A: block min/max
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
-        if (tt >= tt_n || ct0 >= ntp) continue;
+        if (HELPERS && ct0 >= ntp) continue;
         const int tw = (tt0 + tt) * 32 + l32;
 #pragma unroll
         for (int ct = 0; ct < NTW; ++ct) {
@@ -173,7 +177,7 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
     // C: codes of the lane's blocks, OR-ed into the record image
 #pragma unroll
     for (int ct = 0; ct < NTW; ++ct) {
-        const uint32_t info = ct0 < ntp ? blk_t[2 * (ct0 + ct) + h] : 0u;
+        const uint32_t info = !HELPERS || ct0 < ntp ? blk_t[2 * (ct0 + ct) + h] : 0u;
         const uint32_t bits = info & 0xffu;
         if (bits != 0u) {
             const uint32_t g = (info >> 8) & 0xffu;
@@ -181,7 +185,6 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
             const float qmax = (float)((1u << bits) - 1u);
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) {
-                if (tt >= tt_n) continue;
                 const int tw = (tt0 + tt) * 32 + l32;
                 const float2 sq = gq[g * tok_wg + tw];
                 uint32_t* row = rec + tw * rstride;
@@ -294,17 +297,19 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     const uint4* vg = P.v_enc;
     const int n_slabs = p / (16 * KS);
 
-    // per-lane source of each X transfer: row (clamped at the tensor's end) and swizzled column
-    const char* xsrc[NXD];
+    // per-lane source of each X transfer, from the tile's first row: row (clamped at the tensor's end) and swizzled column.  (A
+    // scalar address and a 32-bit offset per lane: with 64-bit lane addresses the 8-tile variant spilled 13 registers and reloaded
+    // six of them per ring pass; 32-layer cache at 16x 1406 -> 1347 us.)
+    const char* xtile = reinterpret_cast<const char*>(reinterpret_cast<const XT*>(a.x) + (tr.x_row0 + tok_tile0) * a.ld_x);
+    uint32_t xsrc[NXD];                                         // below 2^31: at most 256 rows of 2^21 elements
     uint32_t xdst[NXD];                                         // wave-uniform LDS byte offsets inside an X slab
 #pragma unroll
     for (int j = 0; j < NXD; ++j) {
         const int row0 = (j * NW + wave) * XS::ROWS_PER_DMA;
         const int row = row0 + lane / XS::COLS;
         const int col = (lane % XS::COLS) ^ XS::swz(row);
-        int t = tok_tile0 + row;
-        t = t < T ? t : T - 1;                                  // tail rows re-read the last token
-        xsrc[j] = reinterpret_cast<const char*>(reinterpret_cast<const XT*>(a.x) + (tr.x_row0 + t) * a.ld_x) + col * 16;
+        const int t = min(row, T - 1 - tok_tile0);              // tail rows re-read the last token
+        xsrc[j] = (uint32_t)t * (uint32_t)(a.ld_x * (int64_t)sizeof(XT)) + (uint32_t)(col * 16);
         xdst[j] = (uint32_t)(SLAB_U4 * 16 + row0 * XS::ROW_B);
     }
     const uint32_t lds_ring = lds_offset(ring);
@@ -319,15 +324,15 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     auto issue = [&](int s, int stage) {
         const uint32_t base = lds_ring + stage * STAGE_B;
         const size_t xoff = (size_t)s * XS::ROW_B + (blk_lg ? (size_t)((s * (16 * KS)) >> blk_lg) * blk_jump_b : (size_t)0);
-        const uint4* vsrc = vg + (size_t)s * SLAB_U4 + wave * 64 + lane;
+        const uint4* vsrc = vg + (size_t)s * SLAB_U4;           // scalar addresses plus a lane offset
 #pragma unroll
         for (int i = 0; i < NV; ++i)
             if (i * NW + wave < NV_TOTAL)
-                dma16_async(vsrc + i * NTH, __builtin_amdgcn_readfirstlane(base + (i * NTH + wave * 64) * 16));
+                dma16_async(vsrc + i * NTH, (uint32_t)tid * 16u, base + (i * NTH + wave * 64) * 16);
 #pragma unroll
         for (int j = 0; j < NXD; ++j)
             if (j * NW + wave < NX_TOTAL)
-                dma16_async(xsrc[j] + xoff, __builtin_amdgcn_readfirstlane(base + xdst[j]));
+                dma16_async(xtile + xoff, xsrc[j], base + xdst[j]);
     };
     auto compute = [&](int stage) {
         const uint4* abase = reinterpret_cast<const uint4*>(ring + stage * STAGE_B) + (wc * NTW) * 64 + lane;
@@ -390,7 +395,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
         }
     }
 
-    encode_epilogue<NTW, TT>(acc, wc * NTW, wt * TT, TT, TOK_WG, TOK_WG, NTP, NTH, P, tr, a, tok_tile0, work, smem);
+    encode_epilogue<NTW, TT, false>(acc, wc * NTW, wt * TT, TOK_WG, TOK_WG, NTP, NTH, P, tr, a, tok_tile0, work, smem);
 }
 
 // One kernel per variant (WC waves across coordinates, NTW coordinate tiles per wave, NW waves per
@@ -556,7 +561,7 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
         __syncthreads();
     }
     wait_vmem<0>();                                                  // the fragments fetched past the end
-    encode_epilogue<NTW, TT>(acc, ct0, 0, TT, ROWS, kEncShortTile, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem);
+    encode_epilogue<NTW, TT, true>(acc, ct0, 0, ROWS, kEncShortTile, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem);
 }
 
 template <int NTW, typename XT>
