@@ -352,7 +352,8 @@ kvtc_status kvtc_entropy_decode_batch(const kvtc_entropy* e, const kvtc_entropy_
  * part of calibration after the PCA: every (block, width) pair is a pass over the calibration tokens.
  *   coef_dev    [n_tokens][ld] fp32: the calibration coefficients P = (C - mu) V (device, 4-byte aligned)
  *   blocks_dev  n_blocks x {start, n} (device): 1 <= n <= 1024, start + n <= ld; a block outside these
- *               limits gets NaN in its row of the result (the list is not visible to the host)
+ *               limits gets NaN in its row of the result (the list is not visible to the host),
+ *               and so does a block that holds an infinite coefficient or a NaN
  *   change_dev  [n_blocks][max_bits] fp64 (device, 8-byte aligned); max_bits in 1..8
  * Fixed summation order: results are reproducible.  No allocation, no
  * synchronisation.  The PCA itself (an eigen-decomposition of a p x p matrix) is not part of this library.

@@ -84,6 +84,9 @@ __device__ __forceinline__ double block_error(const float* coef, int64_t t_begin
             if (mine == s) { lo = l; hi = h; }
         }
         const GroupQ q = group_header(lo, hi, bits);
+        // an infinite coefficient makes error and energy infinite and their difference not a number, where the form above would
+        // give -inf, the best value a minimising allocation can see (the subtraction in double: a finite range stays finite)
+        e = __builtin_fma((double)hi - (double)lo, 0.0, e);
 #pragma unroll
         for (int s = 0; s < kCalibTok; ++s) {
             const int from = (lane & ~3) | s;

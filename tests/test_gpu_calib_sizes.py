@@ -54,3 +54,34 @@ def test_moments_at_strip_and_token_edges(n_tok, p):
         # double-precision sums of n_tok terms: n_tok * 2^-53 of the sum of magnitudes at most
         assert np.all(np.abs(s.cpu().numpy() - x64.sum(0)) <= n_tok * 2.0 ** -52 * np.abs(x64).sum(0))
         assert np.all(np.abs(g.cpu().numpy() - x64.T @ x64) <= n_tok * 2.0 ** -52 * (np.abs(x64).T @ np.abs(x64)))
+
+
+@pytest.mark.parametrize("n_tok", [1, 5, 200])
+def test_blocks_with_coefficients_that_are_not_finite_come_out_as_nan(n_tok):
+    """The squared error and the energy of such a block are both infinite, so their difference is not a number -- for every block that
+    holds the coefficient, in any lane group, at any width and wherever the token stands, and for no other block."""
+    ld = 1100
+    rng = np.random.default_rng(n_tok)
+    cand = [(s, n) for n in (3, 16, 40, 64, 200, 256, 300, 1024) for s in (0, 16, ld - n)]
+    blocks = torch.tensor(cand, dtype=torch.int32, device=DEV)
+    P = rng.standard_normal((n_tok, ld)).astype(np.float32)
+
+    def table(p):
+        out = torch.full((len(cand), 8), -7.0, dtype=torch.float64, device=DEV)
+        kv.kvtc_calib_block_errors(torch.from_numpy(p).to(DEV), n_tok, ld, blocks, len(cand), 8, out)
+        return out.cpu().numpy()
+
+    clean = table(P)
+    assert np.all(np.isfinite(clean))
+    for bad in (np.inf, -np.inf, np.nan):
+        for t in {0, n_tok // 2, n_tok - 1}:
+            for at in (0, 17, ld - 1):
+                Q = P.copy()
+                Q[t, at] = bad
+                got = table(Q)
+                hit = np.array([s <= at < s + n for s, n in cand])
+                assert np.all(np.isnan(got[hit])), (bad, t, at)
+                assert np.array_equal(got[~hit], clean[~hit]), (bad, t, at)
+    big = P.copy()
+    big[0, 5], big[n_tok - 1, 6] = 3.4e38, -3.4e38                # the range of a block overflows fp32, its terms do not overflow
+    assert np.all(np.isfinite(table(big)))
