@@ -176,6 +176,7 @@ constexpr int kGramAhead = 8;
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 struct GramPair { double even, odd; };
+struct __attribute__((packed, aligned(8))) Doubles2 { double x, y; };       // two entries of the matrix: it is 8-byte aligned, no more
 __device__ __forceinline__ GramPair gram_pair(uint32_t v) { return {(double)bits_f32(v << 16), (double)bits_f32(v & 0xffff0000u)}; }
 __device__ __forceinline__ GramPair gram_pair(float2 v) { return {(double)v.x, (double)v.y}; }
 template <typename XT> struct GramVec { using type = uint32_t; };
@@ -262,10 +263,10 @@ __global__ void __launch_bounds__(64 * kGramWaves, 3) calib_gram_kernel(const XT
         for (int b = 0; b < 2; ++b) m[a][b] = total((a * 2 + b) * 4 + r, lane);
     const int i = bi * kGramStrip + 2 * (4 * r + k), j = bj * kGramStrip + 2 * l16;
 #pragma unroll
-    for (int a = 0; a < 2; ++a) *reinterpret_cast<double2*>(gram + (size_t)(i + a) * p + j) = make_double2(m[a][0], m[a][1]);
+    for (int a = 0; a < 2; ++a) *reinterpret_cast<Doubles2*>(gram + (size_t)(i + a) * p + j) = Doubles2{m[a][0], m[a][1]};
     if (!diag) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) *reinterpret_cast<double2*>(gram + (size_t)(j + b) * p + i) = make_double2(m[0][b], m[1][b]);
+        for (int b = 0; b < 2; ++b) *reinterpret_cast<Doubles2*>(gram + (size_t)(j + b) * p + i) = Doubles2{m[0][b], m[1][b]};
     } else if (tid < 32) {                                       // lane l16 + 16 k holds the tokens 4 g + k of feature pair l16
         const int v = 16 + (tid & 1), l = tid >> 1;
         sum[bi * kGramStrip + tid] = ((total(v, l) + total(v, l + 16)) + total(v, l + 32)) + total(v, l + 48);

@@ -85,3 +85,25 @@ def test_blocks_with_coefficients_that_are_not_finite_come_out_as_nan(n_tok):
     big = P.copy()
     big[0, 5], big[n_tok - 1, 6] = 3.4e38, -3.4e38                # the range of a block overflows fp32, its terms do not overflow
     assert np.all(np.isfinite(table(big)))
+
+
+@pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
+def test_moments_into_buffers_that_are_8_byte_aligned_only(dtype):
+    """sum_dev and gram_dev need 8-byte alignment, no more: results one double past a 16-byte boundary are the same bits, and
+    nothing around them is written."""
+    n_tok, p = 77, 192
+    x = torch.randn((n_tok, p), generator=torch.Generator(device=DEV).manual_seed(4), device=DEV)
+    x = x.to(torch.bfloat16) if dtype == kv.KVTC_BF16 else x
+
+    def moments(shift):
+        s = torch.full((p + 2,), -7.0, dtype=torch.float64, device=DEV)
+        g = torch.full((p * p + 2,), -7.0, dtype=torch.float64, device=DEV)
+        assert g.data_ptr() % 16 == 0
+        kv.kvtc_calib_moments(x, dtype, n_tok, p, kv.layout(p), s[shift:], g[shift:])
+        torch.cuda.synchronize()
+        for buf, n in ((s, p), (g, p * p)):
+            assert bool((buf[:shift] == -7.0).all()) and bool((buf[shift + n:] == -7.0).all())
+        return s[shift:shift + p], g[shift:shift + p * p]
+
+    for a, b in zip(moments(0), moments(1)):
+        assert torch.equal(a, b)
