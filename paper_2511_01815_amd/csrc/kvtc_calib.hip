@@ -29,6 +29,7 @@ namespace {
 constexpr int kCalibMaxBits = 8;
 constexpr int kCalibMaxN = 1024;
 constexpr int kCalibThreads = 1024;   // 16 waves: the pair with the longest block is the tail of the launch
+constexpr int kCalibMaxBlocks = 1 << 21;          // blocks per launch
 constexpr int kCalibTok = 4;          // tokens a lane group works on at once
 
 // Minimum or maximum over groups of L lanes (4, 16 or 64), in every lane: register exchanges inside a row of 16
@@ -302,8 +303,12 @@ kvtc_status kvtc_calib_block_errors(const float* coef_dev, int64_t n_tokens, int
         return set_error(KVTC_E_ARG, "kvtc_calib_block_errors: misaligned buffer");
     const int64_t n_out = (int64_t)n_blocks * max_bits;
     hipLaunchKernelGGL(calib_zero_kernel, dim3((unsigned)(n_out < 262144 ? (n_out + 255) / 256 : 1024)), dim3(256), 0, static_cast<hipStream_t>(stream), change_dev, n_out);
-    hipLaunchKernelGGL(calib_block_errors_kernel, dim3((unsigned)n_blocks, (unsigned)max_bits, 3), dim3(kCalibThreads), 0, static_cast<hipStream_t>(stream), coef_dev, n_tokens, ld,
-                       blocks_dev, max_bits, change_dev);
+    // a launch has fewer than 2^32 threads across: beyond 2^22 - 1 blocks of 1024 threads the list takes several
+    for (int64_t at = 0; at < n_blocks; at += kCalibMaxBlocks) {
+        const int n = n_blocks - at < kCalibMaxBlocks ? (int)(n_blocks - at) : kCalibMaxBlocks;
+        hipLaunchKernelGGL(calib_block_errors_kernel, dim3((unsigned)n, (unsigned)max_bits, 3), dim3(kCalibThreads), 0, static_cast<hipStream_t>(stream), coef_dev, n_tokens, ld,
+                           blocks_dev + at, max_bits, change_dev + at * max_bits);
+    }
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return set_error(KVTC_E_HIP, "kvtc_calib_block_errors: launch failed: %s", hipGetErrorString(err));
     return KVTC_OK;

@@ -107,3 +107,18 @@ def test_moments_into_buffers_that_are_8_byte_aligned_only(dtype):
 
     for a, b in zip(moments(0), moments(1)):
         assert torch.equal(a, b)
+
+
+def test_lists_longer_than_one_launch_takes():
+    """2^22 + 5 blocks, once more than 2^32 threads side by side: every row is that of the same block in a short list."""
+    n_tok, ld, n = 3, 64, (1 << 22) + 5
+    coef = torch.randn((n_tok, ld), generator=torch.Generator(device=DEV).manual_seed(9), device=DEV)
+    short = torch.tensor([(s, 16) for s in range(0, 49)] + [(60, 16)], dtype=torch.int32, device=DEV)        # the last one ends beyond the row
+    want = torch.zeros((len(short), 1), dtype=torch.float64, device=DEV)
+    kv.kvtc_calib_block_errors(coef, n_tok, ld, short, len(short), 1, want)
+    which = torch.arange(n, device=DEV) % len(short)
+    got = torch.full((n + 1, 1), -7.0, dtype=torch.float64, device=DEV)
+    kv.kvtc_calib_block_errors(coef, n_tok, ld, short[which].contiguous(), n, 1, got)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(want[-1]).all()) and float(got[n]) == -7.0
+    assert torch.equal(torch.nan_to_num(got[:n], nan=1e300), torch.nan_to_num(want[which], nan=1e300))
