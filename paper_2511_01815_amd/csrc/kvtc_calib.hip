@@ -107,7 +107,10 @@ __device__ __forceinline__ double block_error(const float* coef, int64_t t_begin
 }
 
 // Blocks of more than 256 coordinates are cut in two halves of the tokens, whose sums are ADDED to the zeroed result: with
-// two terms on top of zero the order of arrival cannot show, so the table stays reproducible.
+// two terms on top of zero the order of arrival cannot show, so the table stays reproducible.  Not where all tokens fit one step of
+// such a block's lane groups: a half would take as long as the whole, and the launch that zeroes would be a quarter of the call
+// (one block of 16 coordinates, 50 tokens, one width: 10.7 us with it, 8.5 without).
+constexpr int kCalibHalveAbove = kCalibThreads / 64 * kCalibTok;
 __device__ __forceinline__ bool calib_long_block(const kvtc_calib_block& b) { return b.n > 256; }
 __device__ __forceinline__ bool calib_bad_block(const kvtc_calib_block& b, int64_t ld) {
     return b.n < 1 || b.n > kCalibMaxN || b.start < 0 || (int64_t)b.start + b.n > ld;
@@ -120,24 +123,25 @@ __global__ void __launch_bounds__(256) calib_zero_kernel(double* change, int64_t
 // change[block][b - 1] = sum over tokens and the block's coordinates of (d - d_hat)^2 - d^2.  Grid: (block, width, part).
 // What bounds it is vector arithmetic (six fp32 and five half-rate fp64 instructions per coefficient and width) and, at the
 // end, the workgroups of the longest blocks: parts 0 and 1 are the halves of the long blocks, ahead of everything else
-// in the grid, part 2 all others.  175 blocks x 8 widths x 2048 tokens (the default set at 1024 features): 4.59 ms with
+// in the grid, part 2 all others (the only part where nothing is halved).  175 blocks x 8 widths x 2048 tokens (the default set at 1024 features): 4.59 ms with
 // a workgroup of 256 threads per block that evaluated all widths and 16 or 64 lanes per token, 0.386 ms with one of 1024
 // threads per block and width (half of it for the headers), 0.208 ms with 16 coordinates per lane.
 __global__ void __launch_bounds__(kCalibThreads) calib_block_errors_kernel(const float* coef, int64_t n_tokens, int64_t ld, const kvtc_calib_block* blocks,
                                                                           int max_bits, double* change) {
     __shared__ double red[kCalibThreads];
     const kvtc_calib_block blk = blocks[blockIdx.x];
-    const int start = blk.start, n = blk.n, bits = (int)blockIdx.y + 1, part = (int)blockIdx.z;
+    const int start = blk.start, n = blk.n, bits = (int)blockIdx.y + 1, part = gridDim.z == 1 ? 2 : (int)blockIdx.z;
     double* out = change + (size_t)blockIdx.x * max_bits + blockIdx.y;
     // the list lives on the device, out of the host's sight: a block outside a row (or longer than a lane group holds) gets NaN
     if (calib_bad_block(blk, ld)) {
         if (threadIdx.x == 0 && part == 2) *out = __builtin_nan("");
         return;
     }
-    if (calib_long_block(blk) != (part < 2)) return;
+    const bool halved = gridDim.z != 1 && calib_long_block(blk);
+    if (halved != (part < 2)) return;
     double e;
-    if (part < 2) {
-        const int64_t half = (n_tokens + 1) / 2, b = part ? half : 0, m = part ? n_tokens : half;
+    if (calib_long_block(blk)) {
+        const int64_t half = halved ? (n_tokens + 1) / 2 : n_tokens, b = part == 1 ? half : 0, m = part == 1 ? n_tokens : half;
         e = n == 1024 ? block_error<64, 16, true>(coef, b, m, ld, start, n, bits) : block_error<64, 16, false>(coef, b, m, ld, start, n, bits);
     } else if (n <= 16) {
         e = n == 16 ? block_error<4, 4, true>(coef, 0, n_tokens, ld, start, n, bits) : block_error<4, 4, false>(coef, 0, n_tokens, ld, start, n, bits);
@@ -154,7 +158,7 @@ __global__ void __launch_bounds__(kCalibThreads) calib_block_errors_kernel(const
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        if (part < 2) unsafeAtomicAdd(out, red[0]);
+        if (halved) unsafeAtomicAdd(out, red[0]);
         else *out = red[0];
     }
 }
@@ -302,11 +306,13 @@ kvtc_status kvtc_calib_block_errors(const float* coef_dev, int64_t n_tokens, int
     if ((reinterpret_cast<uintptr_t>(coef_dev) & 3u) || (reinterpret_cast<uintptr_t>(change_dev) & 7u) || (reinterpret_cast<uintptr_t>(blocks_dev) & 3u))
         return set_error(KVTC_E_ARG, "kvtc_calib_block_errors: misaligned buffer");
     const int64_t n_out = (int64_t)n_blocks * max_bits;
-    hipLaunchKernelGGL(calib_zero_kernel, dim3((unsigned)(n_out < 262144 ? (n_out + 255) / 256 : 1024)), dim3(256), 0, static_cast<hipStream_t>(stream), change_dev, n_out);
+    const bool halves = n_tokens > kCalibHalveAbove;
+    if (halves)
+        hipLaunchKernelGGL(calib_zero_kernel, dim3((unsigned)(n_out < 262144 ? (n_out + 255) / 256 : 1024)), dim3(256), 0, static_cast<hipStream_t>(stream), change_dev, n_out);
     // a launch has fewer than 2^32 threads across: beyond 2^22 - 1 blocks of 1024 threads the list takes several
     for (int64_t at = 0; at < n_blocks; at += kCalibMaxBlocks) {
         const int n = n_blocks - at < kCalibMaxBlocks ? (int)(n_blocks - at) : kCalibMaxBlocks;
-        hipLaunchKernelGGL(calib_block_errors_kernel, dim3((unsigned)n, (unsigned)max_bits, 3), dim3(kCalibThreads), 0, static_cast<hipStream_t>(stream), coef_dev, n_tokens, ld,
+        hipLaunchKernelGGL(calib_block_errors_kernel, dim3((unsigned)n, (unsigned)max_bits, halves ? 3 : 1), dim3(kCalibThreads), 0, static_cast<hipStream_t>(stream), coef_dev, n_tokens, ld,
                            blocks_dev + at, max_bits, change_dev + at * max_bits);
     }
     const hipError_t err = hipGetLastError();
