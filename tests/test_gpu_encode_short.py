@@ -1,13 +1,20 @@
 """The encode kernel for short jobs against the bulk kernels: the same bits, for plans of every width class, token counts around
-its tiles, feature counts with and without a part of a chunk left over, both input types and a heads-major layout."""
+its tiles, feature counts with and without a part of a chunk left over, both input types and a heads-major layout.  And the
+bulk kernels against each other in those types and layouts, at token counts that only they code."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2511_01815_amd as kv
-from test_gpu_parity import DEV, _gpu_plan, _manual
+from test_gpu_parity import DEV, VARIANT_RANKS, _from_dev, _gpu_plan, _manual, _variant_plan, check_stream
 
 pytestmark = pytest.mark.gpu
+
+
+def bulk_tokens():
+    """Tokens of a tensor, or of a lone job, that the bulk kernels code whatever its plan and type: more 64-token tiles than two for
+    every compute unit, the most that the short-job kernel is given."""
+    return 2 * 64 * torch.cuda.get_device_properties(0).multi_processor_count + 200
 
 WIDE = {64: [(32, 4)], 192: [(16, 8), (64, 4), (16, 2)], 320: [(64, 5), (96, 3)], 448: [(128, 5), (128, 3)], 1024: [(16, 8), (64, 5), (128, 3), (112, 2)],
         1088: [(64, 6), (256, 3), (64, 2)], 1152: [(256, 4), (240, 3)], 2048: [(64, 12), (512, 3), (64, 2)], 832: [(256, 3), (512, 1)]}
@@ -37,8 +44,12 @@ def test_short_jobs_are_coded_as_long_ones(p, dtype):
         assert int(status.item()) == 0 and bool((out[size:] == 0xA5).all())
         return out[:size], offs.cpu().tolist()
 
-    bulk, _ = coded([0], [T], [0])
-    bulk = bulk.view(T, R)
+    base, n_bulk = x, bulk_tokens()
+    x = base.repeat(n_bulk // T + 1, 1)                          # (read by coded())
+    bulk, _ = coded([0], [n_bulk], [0])
+    bulk = bulk.view(n_bulk, R)
+    assert torch.equal(bulk[T:], bulk[:-T])
+    x, bulk = base, bulk[:T]
     lens = [1, 16, 31, 32, 33, 63, 64, 0]
     row0 = [0, 5, 100, 168, 7, 137, 64, 0]
     out, offs = coded([0, 1] * len(lens), [n for n in lens for _ in (0, 1)], [r for r in row0 for _ in (0, 1)])
@@ -56,3 +67,42 @@ def test_short_jobs_are_coded_as_long_ones(p, dtype):
         kv.kvtc_encode_blocked(plan.handle, heads, dtype, T, kv.layout(64, 64, T * 64), got, got.numel())
         torch.cuda.synchronize()
         assert torch.equal(got, bulk), (p, "heads-major")
+
+
+@pytest.mark.parametrize("r", VARIANT_RANKS)
+def test_bulk_kernels_code_the_same_bits_from_every_type_and_layout(r):
+    """A tensor that no call gives to the short-job kernel: bf16 rows on sampled tokens against the oracle; the same values in
+    fp32, with a row pitch, heads-major and as jobs of a batch beside shorter ones must give the same records."""
+    oplan = _variant_plan(r)
+    plan = _gpu_plan(oplan)
+    p, R, T = 1024, plan.record_bytes, bulk_tokens()
+    mix = torch.from_numpy((np.arange(1, p + 1, dtype=np.float64)[:, None] ** -0.7 * np.linalg.qr(np.random.default_rng(77).standard_normal((p, p)))[0]).astype(np.float32))
+    x = (torch.randn((T, p), generator=torch.Generator(device=DEV).manual_seed(r), device=DEV) @ mix.to(DEV) + 0.05).to(torch.bfloat16)
+    ref = torch.zeros((T, R), dtype=torch.uint8, device=DEV)
+    kv.kvtc_encode(plan.handle, x, kv.KVTC_BF16, T, p, ref, ref.numel())
+    rows = np.unique(np.concatenate([[0, 63, 64, 127, 128, 191, 192, 255, 256, T - 2, T - 1], np.random.default_rng(r).integers(0, T, size=400)]))
+    idx = torch.from_numpy(rows).to(DEV)
+    check_stream(oplan, _from_dev(x.index_select(0, idx)), ref.index_select(0, idx).cpu().numpy(), f"bulk{r}")
+    batch = kv.Batch([plan])
+    lens = [300, T - 500, 5, 70]
+    row0 = [0, 300, T - 200, T - 195]
+    jobs = torch.from_numpy(kv.make_jobs([0] * 4, lens, row0).view(np.uint8)).to(DEV)
+    offs = torch.zeros(5, dtype=torch.int64, device=DEV)
+    kv.kvtc_offsets(batch.handle, jobs, 4, offs)
+    want = torch.cat([ref[a:a + n] for a, n in zip(row0, lens)])
+    assert T - 500 > bulk_tokens() // 4 + 64                     # beyond what one of four jobs may have on the short-job kernel
+    for dtype in (kv.KVTC_BF16, kv.KVTC_F32):
+        xd = x if dtype == kv.KVTC_BF16 else x.float()
+        pitched = torch.full((T, p + 72), float("nan"), dtype=xd.dtype, device=DEV)
+        pitched[:, :p] = xd
+        heads = xd.view(T, p // 128, 128).permute(1, 0, 2).contiguous()
+        for name, src, lay in (("plain", xd, kv.layout(p)), ("pitch", pitched, kv.layout(p + 72)), ("heads-major", heads, kv.layout(128, 128, T * 128))):
+            got = torch.full((T * R + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+            kv.kvtc_encode_blocked(plan.handle, src, dtype, T, lay, got, T * R)
+            status = torch.zeros(1, dtype=torch.int32, device=DEV)
+            out = torch.full((want.numel() + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+            kv.kvtc_encode_batch_blocked(batch.handle, jobs, 4, src, dtype, lay, offs, out, want.numel(), status)
+            torch.cuda.synchronize()
+            assert int(status.item()) == 0
+            assert torch.equal(got[:T * R].view(T, R), ref) and bool((got[T * R:] == 0xA5).all()), (name, dtype)
+            assert torch.equal(out[:want.numel()].view(-1, R), want) and bool((out[want.numel():] == 0xA5).all()), (name, dtype, "batch")

@@ -18,7 +18,7 @@ DEV = "cuda:0"
 def test_heads_major_cache_codes_like_the_token_major_tensor(dtype):
     """Config 2's key plan at 16x.  The same values laid out [T][8 * 128] and [8][T][128] must give byte-identical streams,
     and decoding into either layout the same values -- through single calls (narrow tiles) and through a batch of two jobs
-    inside one [8][T_total][128] arena (bulk tiles, a ragged tail)."""
+    inside one [8][T_total][128] arena (a ragged tail)."""
     H, d = 8, 128
     b = kb.load_plan_arrays("c2_K_cr16")
     oplan = ko.plan_from_arrays(b["mu32"], b["v_bits"], b["group_n"], b["group_bits"])

@@ -332,7 +332,8 @@ def test_every_kernel_variant_in_every_form(r):
       (a) a single call of 50 tokens: the short-job encode variant (where the width has one) and the one-tile decode;
       (b) a single call too long for the short-job path (more 64-token tiles than workgroup slots): bulk encode
           through the single-tensor arguments, checked on sampled rows and, whole, against form (c);
-      (c) a batch with jobs of 300, 70 and 5 tokens: bulk encode and the short-job launch side by side, bulk decode."""
+      (c) a batch with jobs of 300, 70 and 5 tokens: the short-job encode kernel through a job table (where the width has one),
+          bulk decode.  (Bulk encode in fp32 and beside short jobs: test_gpu_encode_short.py.)"""
     oplan = _variant_plan(r)
     plan = _gpu_plan(oplan)
     p, R = 1024, oplan.record_bytes
@@ -544,8 +545,8 @@ def test_batch_with_stream_starts_off_the_16_byte_grid():
 
 
 def test_batch_mixes_short_and_long_jobs_and_plans_without_a_short_variant():
-    """Jobs of at most 64 tokens run on narrow tiles when their plan has such a variant (a separate small
-    launch), others do not; every job must come out as from the single-tensor call."""
+    """Short jobs run on the kernel for them where it serves their plan (a separate launch), others do not; every job must come
+    out as from the single-tensor call."""
     p = 1024
     full = _manual(p, [(16, 8), (16, 6), (64, 5), (64, 4), (96, 3), (256, 2), (512, 1)], 11)   # full rank: bulk tiles only
     mid = _manual(p, [(64, 7), (128, 3)], 12)                                                  # 192 coordinates
