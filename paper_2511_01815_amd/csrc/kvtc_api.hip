@@ -98,10 +98,13 @@ int cu_count() {
     return n[dev];
 }
 
-// 64-token tiles that each of n_jobs jobs may have and still all run at once on the short-job kernel (`pairs`: two workgroups
-// share a compute unit, those of up to 8 waves with a coordinate tile each), at least one: a job of no more is a short one.  The bulk tiles are three to four times as large: their
-// launch has fewer workgroups than the chip, each walking all features.  One tensor of 4096 tokens at 16x: 42 us on the bulk tile, 21 on
-// this;
+// Whether two workgroups of the short-job kernel share a compute unit: up to 8 waves with a coordinate tile each, by their registers, and
+// by the LDS they ask for.
+bool short_pairs(int ntw, int waves, int lds) { return ntw == 1 && waves <= 8 && 2 * lds <= kLdsBudget; }
+
+// 64-token tiles that each of n_jobs jobs may have and still all run at once on the short-job kernel (`pairs`: two workgroups share a
+// compute unit), at least one: a job of no more is a short one.  The bulk tiles are three to four times as large: their launch has
+// fewer workgroups than the chip, each walking all features.  One tensor of 4096 tokens at 16x: 42 us on the bulk tile, 21 on this;
 // where the tiles need a second round the bulk kernel, which reads the basis less often, is the faster one again.
 int short_tiles_per_job(int n_jobs, bool pairs) {
     const int n = cu_count() * (pairs ? 2 : 1) / n_jobs;
@@ -567,7 +570,7 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
     // A tensor short enough for all its 64-token tiles to run at once (one wave of workgroups) runs the short-job kernel.
     const int64_t tiles_short = (n_tokens + kEncShortTile - 1) / kEncShortTile;
     hipError_t e;
-    if (plan->h.enc_short != 0 && tiles_short <= short_tiles_per_job(1, plan->h.enc_short == 1 && plan->enc_s_waves <= 8)) {
+    if (plan->h.enc_short != 0 && tiles_short <= short_tiles_per_job(1, short_pairs(plan->h.enc_short, plan->enc_s_waves, plan->enc_s_lds[dtype]))) {
         e = launch_encode_short(a, dtype, plan->h.enc_short, plan->enc_s_waves, (int)tiles_short, (size_t)plan->enc_s_lds[dtype], static_cast<hipStream_t>(stream));
     } else {
         const int64_t tiles = (n_tokens + plan->h.enc_tok_wg - 1) / plan->h.enc_tok_wg;
@@ -870,7 +873,7 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.cap = out_cap;
     a.status = status_dev;
     // Short jobs go to the short-job kernel, the rest to the bulk variants.
-    const int s_tiles = short_tiles_per_job(n_jobs, batch->enc_short[1].waves <= 8 && batch->enc_short[2].waves == 0);
+    const int s_tiles = short_tiles_per_job(n_jobs, batch->enc_short[2].waves == 0 && short_pairs(1, batch->enc_short[1].waves, batch->enc_short[1].lds[dtype]));
     a.enc_short_max = s_tiles * kEncShortTile;
     for (const auto& v : batch->enc) {
         hipError_t e = launch_encode(a, dtype, v.key, cu_count() * v.wgs,
@@ -946,7 +949,7 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     a.stream_buf = out_base_dev;
     a.cap = out_cap;
     a.status = status_dev;
-    const int s_tiles = short_tiles_per_job(n_jobs, shrt[1].waves <= 8 && shrt[2].waves == 0);
+    const int s_tiles = short_tiles_per_job(n_jobs, shrt[2].waves == 0 && short_pairs(1, shrt[1].waves, shrt[1].lds));
     a.enc_short_max = s_tiles * kEncShortTile;
     for (int k = 0; k < n_bulk; ++k) {
         e = launch_encode(a, dtype, bulk[k].key, cu_count() * bulk[k].wgs, (size_t)kJobTableBytes + 64 + bulk[k].lds, st);

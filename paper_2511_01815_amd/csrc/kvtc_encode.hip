@@ -426,25 +426,28 @@ __global__ void __launch_bounds__(NW * 64, (enc_wgs_per_cu<WC, NTW, NW>())) kvtc
 // width up to 10 (20) tiles -- the waves a plan does not need help to fetch X.  A launch of a few such tiles is bound by how
 // fast a compute unit can draw the plan's basis (half a megabyte at 256 coordinates) through itself, and each fragment is used by one
 // wave only, so the fragments go straight to registers, 16 KiB of them in flight per wave (16 k-steps ahead), instead of through an LDS
-// ring shared by barriers; X comes in chunks of 256 features, asynchronously, with one barrier per chunk.  The sums run over the
+// ring shared by barriers; X comes in chunks of 256 (fp32: 128) features, asynchronously, with one barrier per chunk.  The sums run over the
 // features in the bulk kernel's order: a token's record is the same bits whichever kernel codes it.
 // 64 caches of 16 tokens with a basis each (32 MB of bases): 60 us in two launches of ring kernels before, 14 now in one; 48 tokens of one
 // tensor: 18 -> 14.
-constexpr int kShortFeat = 256, kShortSteps = kShortFeat / 16;
+// (A chunk is 512 bytes of a token in either type, so that two workgroups' chunks fit a compute unit's LDS: with 1 KiB in fp32 only one
+// did, and launches of more tiles than compute units ran a second round: 20000 tokens of 240 coordinates 38 us, now 31.)
+template <typename XT> constexpr int short_feat() { return 512 / (int)sizeof(XT); }
 template <int NTW> constexpr int short_ahead() { return NTW == 1 ? 16 : 4; }   // k-steps of fragments in flight
 constexpr int kShortThreads = 640;
 
 template <int NTW, typename XT, int TT>
 __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, uint4* work) {
-    constexpr int AHEAD = short_ahead<NTW>();
-    constexpr int EB = (int)sizeof(XT), ROW_B = kShortFeat * EB, COLS = ROW_B / 16, ROWS_DMA = 1024 / ROW_B;
+    constexpr int AHEAD = short_ahead<NTW>(), FEAT = short_feat<XT>(), STEPS = FEAT / 16;
+    constexpr int UNROLL = AHEAD > STEPS ? AHEAD / STEPS : 1;        // chunks after which a fragment is in the same register again
+    constexpr int EB = (int)sizeof(XT), ROW_B = FEAT * EB, COLS = ROW_B / 16, ROWS_DMA = 1024 / ROW_B;
     constexpr int ROWS = 32 * TT, CHUNK_B = kEncShortTile * ROW_B;
-    static_assert(kShortSteps % AHEAD == 0, "a fragment's register is known at compile time");
+    static_assert(UNROLL * STEPS % AHEAD == 0, "a fragment's register is known at compile time");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = (int)blockDim.x >> 6;
     const int l32 = lane & 31, h = lane >> 5;
     const int ntp = P.enc_ntw * P.enc_wc;
     const int p = P.p, T = tr.n_tokens, tok_tile0 = tr.tile * kEncShortTile;
-    const int n_steps = p / 16, n_chunks = (p + kShortFeat - 1) / kShortFeat;
+    const int n_steps = p / 16, n_chunks = (p + FEAT - 1) / FEAT;
     const int ct0 = wave * NTW;
     uint4* smem = work + enc_aux_bytes(ntp) / 16;
 
@@ -463,7 +466,7 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
             const int row = i * ROWS_DMA + lane / COLS;
             // 16-byte columns of a row are permuted so that the 8 lanes (rows) served together by a 128-bit read meet 8 bank groups
             const int col = (lane % COLS) ^ (row & 7);
-            int f = c * kShortFeat + col * (16 / EB);
+            int f = c * FEAT + col * (16 / EB);
             f = f < p ? f : 0;                                       // behind the last feature: read something, it is not used
             const int t = min(tok_tile0 + row, T - 1);               // rows past the end re-read the last token
             const char* src = reinterpret_cast<const char*>(a.x) + ((tr.x_row0 + t) * a.ld_x + f) * EB + (blk_lg ? (int64_t)(f >> blk_lg) * blk_jump_b : (int64_t)0);
@@ -501,11 +504,13 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
             for (int tt = 0; tt < TT; ++tt) acc[tt][ct] = c;
         }
     }
-    // a k-step's piece of a row: the permutation touches the column's lowest 3 bits, so four lane addresses serve all k-steps
-    uint32_t xoff[4];
+    // a k-step's piece of a row: the permutation touches the column's lowest 3 bits, so four lane addresses serve all k-steps (fp32: two,
+    // the other column of a pair is one bit away: four are two registers too many)
+    constexpr int XOFF = EB == 2 ? 4 : 2;
+    uint32_t xoff[XOFF];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int col = EB == 2 ? 2 * j + h : 4 * (j >> 1) + 2 * h + (j & 1);
+    for (int j = 0; j < XOFF; ++j) {
+        const int col = EB == 2 ? 2 * j + h : 4 * j + 2 * h;
         xoff[j] = (uint32_t)(l32 * ROW_B + (col ^ (l32 & 7)) * 16);
     }
     auto xfrag = [&](const char* x, int tt, int ks) {
@@ -513,8 +518,8 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
         if constexpr (EB == 2) {
             return as_bf16x8(*reinterpret_cast<const uint4*>(r + xoff[ks & 3] + (ks >> 2) * 128));
         } else {
-            const float4 u = *reinterpret_cast<const float4*>(r + xoff[2 * (ks & 1)] + (ks >> 1) * 128);
-            const float4 w = *reinterpret_cast<const float4*>(r + xoff[2 * (ks & 1) + 1] + (ks >> 1) * 128);
+            const float4 u = *reinterpret_cast<const float4*>(r + xoff[ks & 1] + (ks >> 1) * 128);
+            const float4 w = *reinterpret_cast<const float4*>(r + (xoff[ks & 1] ^ 16u) + (ks >> 1) * 128);
             bf16x8 v;                                                // round to bf16, nearest even
             v[0] = (__bf16)u.x; v[1] = (__bf16)u.y; v[2] = (__bf16)u.z; v[3] = (__bf16)u.w;
             v[4] = (__bf16)w.x; v[5] = (__bf16)w.y; v[6] = (__bf16)w.z; v[7] = (__bf16)w.w;
@@ -522,7 +527,7 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
         }
     };
     bf16x8 xv[2][TT];                                                // of this k-step and of the next
-    auto step = [&](const char* x, int c, int ks, bool last) {
+    auto step = [&](const char* x, int c, int slot0, int ks, bool last) {      // slot0: where the chunk's first fragment is
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt)
             if (!last) xv[(ks + 1) & 1][tt] = xfrag(x, tt, ks + 1);
@@ -530,34 +535,43 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
         for (int ct = 0; ct < NTW; ++ct)
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
-                acc[tt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[ks % AHEAD][ct]), xv[ks & 1][tt], acc[tt][ct], 0, 0, 0);
-        fetch(c * kShortSteps + ks + AHEAD, ks % AHEAD);
+                acc[tt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[(slot0 + ks) % AHEAD][ct]), xv[ks & 1][tt], acc[tt][ct], 0, 0, 0);
+        fetch(c * STEPS + ks + AHEAD, (slot0 + ks) % AHEAD);
         __builtin_amdgcn_sched_barrier(0);
     };
-    const int n_full = p / kShortFeat;
-    for (int c = 0; c < n_full; ++c) {
-        const char* x = reinterpret_cast<const char*>(smem) + (c & 1) * CHUNK_B;
-        const bool more = c + 1 < n_chunks;
-        if (more) issue_x(c + 1);                                    // its half was read in chunk c - 1; the barrier that ended it frees it
+    const int n_full = p / FEAT;
+    for (int c0 = 0; c0 < n_full; c0 += UNROLL) {
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) xv[0][tt] = xfrag(x, tt, 0);
+        for (int u = 0; u < UNROLL; ++u) {
+            const int c = c0 + u;
+            if (c >= n_full) break;
+            const char* x = reinterpret_cast<const char*>(smem) + (c & 1) * CHUNK_B;
+            const bool more = c + 1 < n_chunks;
+            if (more) issue_x(c + 1);                                // its half was read in chunk c - 1; the barrier that ended it frees it
 #pragma unroll
-        for (int ks = 0; ks < kShortSteps; ++ks) step(x, c, ks, ks + 1 == kShortSteps);
-        asm volatile("" ::: "memory");
-        if (more) wait_vmem<kShortSteps * NTW>();                    // the next chunk is older than this one's fragment loads: it has landed
-        __syncthreads();
+            for (int tt = 0; tt < TT; ++tt) xv[0][tt] = xfrag(x, tt, 0);
+#pragma unroll
+            for (int ks = 0; ks < STEPS; ++ks) step(x, c, u * STEPS, ks, ks + 1 == STEPS);
+            asm volatile("" ::: "memory");
+            if (more) wait_vmem<STEPS * NTW>();                      // the next chunk is older than this one's fragment loads: it has landed
+            __syncthreads();
+        }
     }
-    if (n_full < n_chunks) {                                         // 64, 128 or 192 features are left
+    if (n_full < n_chunks) {                                         // 64 features are left, or (bf16) 128 or 192
         const char* x = reinterpret_cast<const char*>(smem) + (n_full & 1) * CHUNK_B;
-        const int left = n_steps - n_full * kShortSteps;
+        const int left = n_steps - n_full * STEPS;
+        auto rest = [&](int slot0) {
 #pragma unroll
-        for (int g = 0; g < 3; ++g)
-            if (4 * g < left) {
+            for (int g = 0; g < STEPS / 4 - 1; ++g)
+                if (4 * g < left) {
 #pragma unroll
-                for (int tt = 0; tt < TT; ++tt) xv[0][tt] = xfrag(x, tt, 4 * g);
+                    for (int tt = 0; tt < TT; ++tt) xv[0][tt] = xfrag(x, tt, 4 * g);
 #pragma unroll
-                for (int ks = 4 * g; ks < 4 * g + 4; ++ks) step(x, n_full, ks, ks == 4 * g + 3);
-            }
+                    for (int ks = 4 * g; ks < 4 * g + 4; ++ks) step(x, n_full, slot0, ks, ks == 4 * g + 3);
+                }
+        };
+        static_assert(UNROLL <= 2, "the register of the rest's first fragment: one of two");
+        if (UNROLL == 2 && (n_full & 1)) rest(STEPS); else rest(0);
         __syncthreads();
     }
     wait_vmem<0>();                                                  // the fragments fetched past the end
@@ -565,7 +579,8 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
 }
 
 template <int NTW, typename XT>
-__global__ void __launch_bounds__(kShortThreads) kvtc_encode_short_kernel(const KernelArgs a) {
+// (registers for four waves a SIMD where two workgroups of eight are to share a compute unit)
+__global__ void __launch_bounds__(kShortThreads) __attribute__((amdgpu_waves_per_eu(NTW == 1 ? 4 : 3))) kvtc_encode_short_kernel(const KernelArgs a) {
     extern __shared__ uint4 smem[];
     TileRef tr;
     if (a.jobs) {
@@ -638,7 +653,7 @@ int encode_short_waves(int ntp) {
     return n < 4 ? 4 : n;
 }
 int encode_short_lds_bytes(int ntp, int n_groups, int rec_dwords, kvtc_dtype dtype) {
-    const int main_b = 2 * kEncShortTile * kShortFeat * (dtype == KVTC_BF16 ? 2 : 4);
+    const int main_b = 2 * kEncShortTile * (dtype == KVTC_BF16 ? short_feat<uint16_t>() * 2 : short_feat<float>() * 4);
     const int epi_b = kEncShortTile * (2 * ntp * 8 + n_groups * 8 + (rec_dwords + 1) * 4);
     return enc_aux_bytes(ntp) + (main_b > epi_b ? main_b : epi_b);
 }
