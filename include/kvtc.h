@@ -122,9 +122,13 @@ kvtc_status kvtc_decode(const kvtc_plan* plan, const void* in_dev, size_t in_byt
 /*
  * Batched / ragged calls: many tensors (jobs), each with its own plan and length, in
  * one launch per direction and per kernel variant among the batch's plans (plans of
- * similar rank share a variant: usually one launch; encode adds one small launch, or
- * two, for the jobs of at most 64 tokens, which have a kernel of their own).  A kvtc_batch makes the plans' descriptors addressable
- * from the device; it copies what it needs, but the plans must outlive it.
+ * similar rank share a variant: usually one launch; encode adds a launch, or two, of the kernel
+ * for short jobs, which serves plans of up to 640 coordinates: jobs of at most 64 tokens, and of more
+ * where the 64-token tiles that each of the n_jobs may then have all run at once -- one job of up to
+ * 16384 or 32768 tokens, 64 jobs of up to 256 or 512, by the plans' widths -- unless a longer job of
+ * the same variant runs anyway and has room for them; a job's records do not depend on its kernel).
+ * A kvtc_batch makes the plans' descriptors addressable from the device; it copies what it needs,
+ * but the plans must outlive it.
  * At most 1024 jobs per call (KVTC_E_UNSUPPORTED beyond).
  */
 kvtc_status kvtc_batch_create(kvtc_batch** out, const kvtc_plan* const* plans, int n_plans,

@@ -875,6 +875,7 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     // Short jobs go to the short-job kernel, the rest to the bulk variants.
     const int s_tiles = short_tiles_per_job(n_jobs, batch->enc_short[2].waves == 0 && short_pairs(1, batch->enc_short[1].waves, batch->enc_short[1].lds[dtype]));
     a.enc_short_max = s_tiles * kEncShortTile;
+    a.enc_cus = cu_count();
     for (const auto& v : batch->enc) {
         hipError_t e = launch_encode(a, dtype, v.key, cu_count() * v.wgs,
                                      (size_t)kJobTableBytes + 64 + v.lds[dtype], static_cast<hipStream_t>(stream));
@@ -951,6 +952,7 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     a.status = status_dev;
     const int s_tiles = short_tiles_per_job(n_jobs, shrt[2].waves == 0 && short_pairs(1, shrt[1].waves, shrt[1].lds));
     a.enc_short_max = s_tiles * kEncShortTile;
+    a.enc_cus = cu_count();
     for (int k = 0; k < n_bulk; ++k) {
         e = launch_encode(a, dtype, bulk[k].key, cu_count() * bulk[k].wgs, (size_t)kJobTableBytes + 64 + bulk[k].lds, st);
         if (e != hipSuccess) return fail(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));

@@ -71,7 +71,8 @@ struct KernelArgs {
     uint64_t cap;              // bytes available in stream_buf
     uint32_t* status;          // device, may be nullptr
     uint32_t dec_ring_off;     // decode: byte offset of the basis ring in the work area; 0 = it shares the record image's space
-    int32_t enc_short_max;     // encode: jobs of at most this many tokens whose plan the short-job kernel serves are left to it; 0 = no job counts as short
+    int32_t enc_short_max;     // encode: jobs of at most this many tokens whose plan the short-job kernel serves may be left to it (bulk_takes_all); 0 = no job counts as short
+    int32_t enc_cus;           // encode of a batch: compute units (a bulk launch has this many workgroups times its plans' enc_wgs)
     int32_t dec_short;         // decode: this launch runs the one-token-tile-per-wave variant of every plan (128-token tiles)
     int32_t dec_accumulate;    // decode of a sectioned plan: 1 = fp32 output, add the product to the output instead of storing it (a further section);
                                // 2 = bf16 output, store round(dec_sum + product) (the last section)
@@ -86,86 +87,156 @@ struct TileRef {
     int32_t tile;      // tile index inside the job
 };
 
+// The bulk encode variant of a plan, in decimal positions.
+__device__ __forceinline__ int enc_key(const PlanDev& pl) { return pl.enc_nw * 10000 + pl.enc_wc * 100 + pl.enc_ntw; }
+
+// Whether a job can be coded at all: its plan, its token count, and its own extent inside the buffer (offsets need not be a running
+// sum: an append writes each job into its own region).
+__device__ __forceinline__ bool job_ok(const KernelArgs& a, int j, const kvtc_job& jb) {
+    bool ok = jb.plan >= 0 && jb.plan < a.n_plans && jb.n_tokens >= 0;
+    if (ok && a.offsets) {
+        const uint64_t off = a.offsets[j], bytes = (uint64_t)jb.n_tokens * (uint64_t)a.plans[jb.plan].rec_dwords * 4ull;
+        ok = off <= a.cap && bytes <= a.cap - off;
+    }
+    return ok;
+}
+
+// Which of a batch's jobs the short-job kernel codes: those of at most one of its tiles; and those of up to a.enc_short_max tokens,
+// unless a longer job needs their plan's bulk kernel anyway and its launch has room for them, that is, they do not make it run
+// another round of tiles.  (The bulk launch then takes them along, where the short-job launch behind it would add its own time;
+// another round costs more than that.  16x, jobs of 40000 and 10000 tokens: 57 us together, 65 apart; 63 of 400 and one of 4000: 43 and
+// 62; but 8x, 16 of 400 and 16 of 2000, 257 to 320 tiles on 256 places: 86 together, 71 apart.)
+// The bulk launches and the short-job launch decide it each for itself, from the same table: `longer` is whether there is such a
+// job, `bulk` the tiles of the jobs that the bulk launch takes in any case, `all` those with the jobs in question.
+__device__ __forceinline__ bool bulk_takes_all(uint32_t bulk, uint32_t all, uint32_t slots) { return (all + slots - 1u) / slots == (bulk + slots - 1u) / slots; }
+
+// The same for a wave of the short-job kernel: true if the bulk launch of variant `key` takes the jobs of more than one tile along.
+__device__ inline bool bulk_takes_mid_jobs(const KernelArgs& a, int key, uint32_t slots) {
+    if (a.n_jobs == 1) return false;
+    const int lane = (int)threadIdx.x & 63;
+    auto ours = [&](int j, const kvtc_job& jb) { return job_ok(a, j, jb) && enc_key(a.plans[jb.plan]) == key; };
+    bool longer = false;
+    for (int j = lane; j < a.n_jobs; j += 64) {
+        const kvtc_job jb = a.jobs[j];
+        if (jb.n_tokens > a.enc_short_max) longer |= ours(j, jb);
+    }
+    if (!__any(longer)) return false;
+    uint32_t bulk = 0, all = 0;
+    for (int j = lane; j < a.n_jobs; j += 64) {
+        const kvtc_job jb = a.jobs[j];
+        if (!ours(j, jb)) continue;
+        const PlanDev& pl = a.plans[jb.plan];
+        if (pl.enc_short != 0 && jb.n_tokens <= kEncShortTile) continue;
+        const uint32_t tiles = (uint32_t)((jb.n_tokens + pl.enc_tok_wg - 1) / pl.enc_tok_wg);
+        all += tiles;
+        if (pl.enc_short == 0 || jb.n_tokens > a.enc_short_max) bulk += tiles;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        bulk += (uint32_t)__shfl_xor((int)bulk, d, 64);
+        all += (uint32_t)__shfl_xor((int)all, d, 64);
+    }
+    return bulk_takes_all(bulk, all, slots);
+}
+
+// Exclusive prefix of the per-thread sums over the workgroup, and the total: inside the waves by lane exchange, then over the waves' totals --
+// one barrier, where a scan through LDS took two per doubling (an append step of 64 caches, three such launches: 23.2 us,
+// now 22.3).  With it go the minimum of `low` and the OR of two flags.
+struct BlockScan { uint32_t before, total, low, flags; };
+template <int NT>
+__device__ __forceinline__ BlockScan block_scan(uint32_t sum, uint32_t low, uint32_t flags, uint32_t* scratch /*[3 * NT / 64]*/) {
+    constexpr int NWAVE = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t incl = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t v = (uint32_t)__shfl_up((int)incl, d, 64);
+        if (lane >= d) incl += v;
+        low = min(low, (uint32_t)__shfl_xor((int)low, d, 64));
+    }
+    flags = (__any(flags & 1u) ? 1u : 0u) | (__any(flags & 2u) ? 2u : 0u);
+    if (lane == 63) {
+        scratch[wave] = incl;
+        scratch[NWAVE + wave] = low;
+        scratch[2 * NWAVE + wave] = flags;
+    }
+    __syncthreads();
+    BlockScan r{incl - sum, 0u, 0xffffffffu, 0u};
+#pragma unroll
+    for (int w = 0; w < NWAVE; ++w) {
+        const uint32_t n = scratch[w];
+        if (w < wave) r.before += n;
+        r.total += n;
+        r.low = min(r.low, scratch[NWAVE + w]);
+        r.flags |= scratch[2 * NWAVE + w];
+    }
+    return r;
+}
+
 // Builds the exclusive prefix of tiles per job in LDS (tile_start[0..n_jobs]) and returns
 // the total.  A job with a bad plan index, a negative token count or a stream that would end
 // beyond `cap` gets zero tiles, and so does a job whose plan belongs to another kernel variant
-// (variant_key: the variant's parameters in decimal positions); workgroup 0 reports the lowest bad job in *status.
+// (variant_key: the variant's parameters in decimal positions) or that the short-job kernel codes; workgroup 0 reports the
+// lowest bad job in *status.
 template <bool kEncode, int NT = kThreads>
-__device__ inline uint32_t build_tile_table(const KernelArgs& a, int variant_key, uint32_t* tile_start, uint32_t* scratch /*[NT / 32]*/) {
+__device__ inline uint32_t build_tile_table(const KernelArgs& a, int variant_key, uint32_t* tile_start, uint32_t* scratch /*[6 * NT / 64]*/) {
     const int tid = threadIdx.x;
     const int n_jobs = a.jobs ? a.n_jobs : 1;
     const int per = (n_jobs + NT - 1) / NT;
     const int j0 = tid * per;
-    uint32_t local[kMaxJobs / NT];
-    uint32_t sum = 0;
+    uint32_t local[kMaxJobs / NT], mid[kMaxJobs / NT];           // tiles; tiles of a job of more than one short tile that may go either way
+    uint32_t sum = 0, mids = 0;
     uint32_t first_bad = 0xffffffffu;
+    uint32_t flags = 0;                                          // 1: a job longer than the short-job launch's limit; 2: one that may go either way
 #pragma unroll
     for (int k = 0; k < kMaxJobs / NT; ++k) {
         uint32_t tiles = 0;
+        mid[k] = 0;
         const int j = j0 + k;
         if (k < per && j < n_jobs) {
             const kvtc_job jb = a.jobs ? a.jobs[j] : a.single;
-            bool ok = jb.plan >= 0 && jb.plan < a.n_plans && jb.n_tokens >= 0;
-            if (ok && a.offsets) {
-                // the job's own extent must lie inside the buffer (offsets need not be a running sum:
-                // an append writes each job into its own region)
-                const uint64_t off = a.offsets[j], bytes = (uint64_t)jb.n_tokens * (uint64_t)a.plans[jb.plan].rec_dwords * 4ull;
-                ok = off <= a.cap && bytes <= a.cap - off;
-            }
-            if (ok) {
+            if (job_ok(a, j, jb)) {
                 const PlanDev& pl = a.plans[jb.plan];
                 // each launch serves the plans of its own kernel variant; other launches take the rest.
-                // Encode: short jobs go to the short-job kernel, if it serves the plan.
-                const bool is_short = kEncode && pl.enc_short != 0 && jb.n_tokens <= a.enc_short_max;
                 int tw = kEncode ? pl.enc_tok_wg : pl.dec_tok_wg;
-                int key = kEncode ? pl.enc_nw * 10000 + pl.enc_wc * 100 + pl.enc_ntw : pl.dec_tt * 100 + pl.dec_cls;
+                int key = kEncode ? enc_key(pl) : pl.dec_tt * 100 + pl.dec_cls;
                 if (!kEncode && a.dec_short) { tw = kDecShortTile; key = 100 + pl.dec_cls; }
-                if (is_short) key = -1;
-                if (key == variant_key) tiles = (uint32_t)((jb.n_tokens + tw - 1) / tw);
+                // (no branches: the plan's fields are requested together)
+                const uint32_t t = (uint32_t)((jb.n_tokens + tw - 1) / tw);
+                const bool here = key == variant_key, shorter = kEncode & (pl.enc_short != 0) & (jb.n_tokens <= a.enc_short_max);
+                const bool either = here & shorter & (jb.n_tokens > kEncShortTile);
+                tiles = here & !shorter ? t : 0u;
+                mid[k] = either ? t : 0u;
+                flags |= (here & (jb.n_tokens > a.enc_short_max) ? 1u : 0u) | (either ? 2u : 0u);
             } else if (first_bad == 0xffffffffu) {
                 first_bad = (uint32_t)j;
             }
         }
         local[k] = tiles;
         sum += tiles;
+        mids += mid[k];
     }
-    // exclusive scan of the per-thread sums: inside the waves by lane exchange, then over the waves' totals -- one barrier, where a
-    // scan through LDS took two per doubling (an append step of 64 caches, three such launches: 23.2 us, now 22.3)
-    constexpr int NWAVE = NT / 64;
-    const int lane = tid & 63, wave = tid >> 6;
-    uint32_t incl = sum, bad = first_bad;
+    BlockScan sc = block_scan<NT>(sum, first_bad, flags, scratch);
+    // lowest bad job -> status (workgroup 0 only; a plain vector store)
+    if (a.status && blockIdx.x == 0 && tid == 0 && sc.low != 0xffffffffu) *a.status = sc.low + 1u;
+    if (kEncode && __builtin_expect(a.jobs && sc.flags == 3u, 0)) {
+        const BlockScan with = block_scan<NT>(sum + mids, 0u, 0u, scratch + 3 * NT / 64);
+        if (bulk_takes_all(sc.total, with.total, gridDim.x)) {
+            sc = with;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t v = (uint32_t)__shfl_up((int)incl, d, 64);
-        if (lane >= d) incl += v;
-        bad = min(bad, (uint32_t)__shfl_xor((int)bad, d, 64));
+            for (int k = 0; k < kMaxJobs / NT; ++k) local[k] += mid[k];
+        }
     }
-    if (lane == 63) {
-        scratch[wave] = incl;
-        scratch[NWAVE + wave] = bad;
-    }
-    __syncthreads();
-    uint32_t before = 0, total = 0;
-    bad = 0xffffffffu;
-#pragma unroll
-    for (int w = 0; w < NWAVE; ++w) {
-        const uint32_t n = scratch[w];
-        if (w < wave) before += n;
-        total += n;
-        bad = min(bad, scratch[NWAVE + w]);
-    }
-    uint32_t run = before + incl - sum;
+    uint32_t run = sc.before;
 #pragma unroll
     for (int k = 0; k < kMaxJobs / NT; ++k) {
         const int j = j0 + k;
         if (k < per && j < n_jobs) tile_start[j] = run;
         run += local[k];
     }
-    if (tid == 0) tile_start[n_jobs] = total;
-    // lowest bad job -> status (workgroup 0 only; a plain vector store)
-    if (a.status && blockIdx.x == 0 && tid == 0 && bad != 0xffffffffu) *a.status = bad + 1u;
+    if (tid == 0) tile_start[n_jobs] = sc.total;
     __syncthreads();
-    return total;
+    return sc.total;
 }
 
 // A pointer whose value is the same in every lane, moved into scalar registers.

@@ -599,6 +599,7 @@ __global__ void __launch_bounds__(kShortThreads) __attribute__((amdgpu_waves_per
     const PlanEnc P = load_plan_enc(plan);
     if (plan->enc_short != NTW) return;
     if (a.jobs) {
+        if (__builtin_expect(tr.n_tokens > kEncShortTile, 0) && bulk_takes_mid_jobs(a, enc_key(*plan), (uint32_t)(a.enc_cus * plan->enc_wgs))) return;
         const uint64_t bytes = (uint64_t)tr.n_tokens * (uint64_t)P.rec_dwords * 4ull;
         if (tr.offset > a.cap || bytes > a.cap - tr.offset) return;
     }

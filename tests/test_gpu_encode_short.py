@@ -106,3 +106,52 @@ def test_bulk_kernels_code_the_same_bits_from_every_type_and_layout(r):
             assert int(status.item()) == 0
             assert torch.equal(got[:T * R].view(T, R), ref) and bool((got[T * R:] == 0xA5).all()), (name, dtype)
             assert torch.equal(out[:want.numel()].view(-1, R), want) and bool((out[want.numel():] == 0xA5).all()), (name, dtype, "batch")
+
+
+@pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
+@pytest.mark.parametrize("form", ["batch", "static"])
+def test_batches_with_jobs_on_both_sides_of_the_limit(form, dtype):
+    """Jobs that fit the short-job kernel go to it unless a longer job needs their plan's bulk kernel anyway and has room for them: batches
+    in which that is so for no plan, for one and for all, in which the bulk kernel's round of tiles is full, with plans that have
+    no short-job kernel and jobs that are not valid (those are skipped and the lowest is reported).  Whatever the route, a job's records are those of its single call."""
+    plans = [_gpu_plan(_variant_plan(r)) for r in (64, 192, 544, 1024)]
+    batch, p = kv.Batch(plans), 1024
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    limit = cus // 11 * 64                                       # the batches below have 11 jobs, one wide plan among them
+    rows = max(2 * limit, cus * 128)
+    tdt = torch.bfloat16 if dtype == kv.KVTC_BF16 else torch.float32
+    x = torch.randn((rows, p), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV).to(tdt)
+    single = []
+    for plan in plans:
+        out = torch.zeros((rows, plan.record_bytes), dtype=torch.uint8, device=DEV)
+        kv.kvtc_encode(plan.handle, x, dtype, rows, p, out, out.numel())
+        single.append(out)
+    small = [(0, limit), (0, 3), (1, 200), (1, 64), (2, 65), (2, limit - 1), (3, 200), (3, 5)]
+    none = small + [(1, 0), (0, 64), (2, 1)]
+    one = small + [(1, limit + 1), (0, 64), (2, 1)]
+    all_ = small + [(1, 2 * limit), (0, limit + 64), (2, limit + 1)]
+    full = small + [(1, 2 * limit), (0, 64), (2, cus * 128)]     # one round of the 640-coordinate kernel's 128-token tiles
+    invalid = [(0, 500), (9, 3 * limit), (-1, 70), (1, -5), (1, limit)] + small[2:]
+    for jobs in (none, one, all_, full, invalid):
+        assert len(jobs) == 11
+        which, lens = [w for w, _ in jobs], [n for _, n in jobs]
+        row0 = [(37 * j) % max(1, rows - n + 1) if n > 0 else 0 for j, n in enumerate(lens)]
+        ok = [0 <= w < 4 and n >= 0 for w, n in jobs]
+        size = sum(n * plans[w].record_bytes for (w, n), v in zip(jobs, ok) if v)
+        dev = torch.from_numpy(kv.make_jobs(which, lens, row0).view(np.uint8)).to(DEV)
+        offs = torch.zeros(12, dtype=torch.int64, device=DEV)
+        out = torch.full((size + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+        status = torch.zeros(1, dtype=torch.int32, device=DEV)
+        if form == "batch":
+            kv.kvtc_offsets(batch.handle, dev, 11, offs)
+            kv.kvtc_encode_batch(batch.handle, dev, 11, x, dtype, p, offs, out, size, status)
+        else:
+            kv.kvtc_encode_batch_static([q.handle for q in plans], dev, 11, x, dtype, p, out, size, offs, status)
+        torch.cuda.synchronize()
+        assert int(status.item()) == (0 if all(ok) else 1 + ok.index(False))
+        assert bool((out[size:] == 0xA5).all())
+        at = offs.cpu().tolist()
+        for j, (w, n) in enumerate(jobs):
+            if ok[j]:
+                got = out[at[j]:at[j] + n * plans[w].record_bytes].view(n, plans[w].record_bytes)
+                assert torch.equal(got, single[w][row0[j]:row0[j] + n]), (j, w, n)
