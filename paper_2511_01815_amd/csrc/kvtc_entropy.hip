@@ -19,6 +19,7 @@
 // Nothing is allocated: the directory lives in the output buffer.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <new>
 #include <vector>
@@ -54,6 +55,8 @@ __host__ __device__ inline uint64_t header_bytes(int64_t n_chunks) { return 4ull
 constexpr int kLenRow = 256 + 4, kEncRow = 512 + 4;                          // bytes per byte position
 constexpr int kImageDw = 392;         // a wave's part of the bit string: 64 pieces of 16 codes of at most 12 bits, a carried dword, whole 16 bytes
 constexpr int kLdsMost = kLdsBudget - 1024;
+constexpr int kMaxLdsRecord = 264;    // bytes: the largest whose code table fits beside 16 waves' images
+static_assert(kMaxLdsRecord * kEncRow + 16 * kImageDw * 4 <= kLdsMost && (kMaxLdsRecord + 4) * kEncRow + 16 * kImageDw * 4 > kLdsMost, "the edge");
 static_assert(kMaxRecord * kLenRow + 16 * kChunk * 4 <= kLdsMost, "the length table of every record size fits");
 
 // Decoding data of one byte position.  Codes are canonical: those of L bits are first[L] .. first[L] + count[L] - 1.
@@ -67,6 +70,7 @@ static_assert(kMaxRecord * kLenRow + 16 * kChunk * 4 <= kLdsMost, "the length ta
 // A wave collects kDecBatch dwords of its 64 rows behind the table, at a pitch of whole 16-byte pieces.
 constexpr int kDecSym = 256, kDecOff = 512, kDecRow = 528;
 constexpr int kDecSegment = 144, kDecBatch = 16, kDecPitch = 20;
+static_assert(kDecRow % 16 == 0 && kChunk * kDecPitch % 4 == 0, "tables in 16-byte pieces");
 static_assert(kDecSegment % 16 == 0 && kDecSegment * kDecRow + 16 * kChunk * kDecPitch * 4 <= kLdsMost, "a segment's table and 16 waves' rows fit");
 
 struct EntropyArgs {
@@ -167,10 +171,20 @@ struct PieceWalk {
     }
 };
 
-// the workgroup's tables, global -> LDS: rows of `from` dwords, a dword of padding behind each
-__device__ __forceinline__ void stage_table(const uint32_t* src, int rows, int log2_from, uint32_t* dst) {
-    const int n = rows << log2_from;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i + (i >> log2_from)] = src[i];
+// the workgroup's tables, global -> LDS, in 16-byte pieces: rows of 2^log2_row dwords, a dword of padding behind each.  (Dword by dword
+// the copy was a quarter of a small call: one 64-token tensor of 128-byte records, encode 28 us, now 20, decode 26, now 19.)
+__device__ __forceinline__ void stage_table(const uint32_t* src, int rows, int log2_row, uint32_t* dst) {
+    const int n = (rows << log2_row) >> 2;
+    const uint4* from = reinterpret_cast<const uint4*>(src);
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const uint4 v = from[i];
+        uint32_t* to = dst + 4 * i + (4 * i >> log2_row);
+        to[0] = v.x;
+        to[1] = v.y;
+        to[2] = v.z;
+        to[3] = v.w;
+    }
 }
 
 // (1) bits of every token's code string -> len_bits[]; bytes of every chunk's bit string -> chunk_off[chunk] (sizes for now).
@@ -275,7 +289,7 @@ __global__ void __launch_bounds__(256) entropy_scan_kernel(const EntropyArgs a) 
 // needed size in coded_bytes).  Per step a wave builds the string of its 64 pieces (1 KiB of records) in LDS, starting at the
 // bits the step before left over, and stores the whole dwords coalesced: 1.5 KiB of LDS per wave, where the image of a whole
 // chunk and its rows took 20 and left a compute unit seven waves.  LDS_TAB: the codes come from the workgroup's copy of the
-// table (records of up to 268 bytes), else from global memory.  Bound by about 16 vector instructions per byte:
+// table (records of up to kMaxLdsRecord bytes), else from global memory.  Bound by about 16 vector instructions per byte:
 // 256 MiB in 634 us before, 167 now.
 template <bool LDS_TAB>
 __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a) {
@@ -378,7 +392,7 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
     }
 }
 
-// decode: one wave per chunk, a lane per token.  Every read of the container is clamped to the job's bytes, so a damaged
+// decode: one wave per chunk, a lane per token.  LDS_TAB: tables in LDS, else in global memory (jobs_wait).  Every read of the container is clamped to the job's bytes, so a damaged
 // container gives wrong bytes, never a fault.  A lane reads its own bit string straight from the container, two dwords ahead
 // of need: the strings of a chunk's tokens follow each other, so the wave's reads fall on a few lines that stay in the caches.
 // Rows are collected in LDS and stored 64 bytes at a time (stored 16 bytes at a time, straight from the lanes, a line's pieces
@@ -391,6 +405,7 @@ __device__ __forceinline__ uint32_t pick(uint32_t k, uint32_t a, uint32_t b, uin
     const uint32_t lo = (k & 1u) ? b : a, hi = (k & 1u) ? d : c;
     return (k & 2u) ? hi : lo;
 }
+template <bool LDS_TAB>
 __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
@@ -400,7 +415,7 @@ __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs 
     if (!v.ok || first >= v.n_chunks) return;
     uint32_t* out = lds + wave * (kChunk * kDecPitch);
     uint32_t* tab32 = lds + n_waves * (kChunk * kDecPitch);
-    const uint8_t* tab = reinterpret_cast<const uint8_t*>(tab32);
+    const uint8_t* tab = LDS_TAB ? reinterpret_cast<const uint8_t*>(tab32) : a.dec + v.table * kDecRow;
     // the limits of four positions at a time, through the scalar unit (constant while the kernel runs)
     typedef const u32x16 __attribute__((address_space(4))) const_u32x16;
     const const_u32x16* lim = (const const_u32x16*)(uintptr_t)uniform_ptr(a.lim + v.table * 4);
@@ -475,15 +490,16 @@ __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs 
         };
         for (uint32_t p0 = 0; p0 < per_row; p0 += kDecSegment / 4) {
             const uint32_t p1 = min(per_row, p0 + (uint32_t)kDecSegment / 4u);
-            if (c == 0 || per_row > (uint32_t)kDecSegment / 4u) {
+            if (LDS_TAB && (c == 0 || per_row > (uint32_t)kDecSegment / 4u)) {
                 __syncthreads();
-                const uint32_t* from = reinterpret_cast<const uint32_t*>(a.dec + (v.table + 4u * p0) * kDecRow);
-                for (uint32_t i = threadIdx.x; i < (p1 - p0) * kDecRow; i += blockDim.x) tab32[i] = from[i];
+                const uint4* from = reinterpret_cast<const uint4*>(a.dec + (v.table + 4u * p0) * kDecRow);
+#pragma unroll 4
+                for (uint32_t i = threadIdx.x; i < (p1 - p0) * kDecRow / 4u; i += blockDim.x) reinterpret_cast<uint4*>(tab32)[i] = from[i];
                 __syncthreads();
             }
             // kDecBatch dwords of every row at a time: collected in LDS, stored as whole 64-byte pieces
             u32x16 L = lim[p0];
-            uint32_t row = 0u;
+            uint32_t row = LDS_TAB ? 0u : 4u * p0 * kDecRow;
             for (uint32_t d0 = p0; d0 < p1; d0 += kDecBatch) {
                 const uint32_t nd = min(p1 - d0, (uint32_t)kDecBatch);
                 if (mine) {
@@ -528,10 +544,15 @@ size_t bound_of(int R, int64_t n_tokens) {
     return (size_t)header_bytes(n_chunks) + (size_t)n_chunks * chunk_image_dwords(R) * 4;
 }
 
-// The shape of a launch over `n_chunks` chunks of each of n_jobs jobs: workgroups of 16 waves, or 8 where that lets more
-// waves share a compute unit's LDS; each wave takes as many chunks in turn (at most 8) as still leave every place on the chip
-// taken, because a workgroup first copies its table (64 KiB for 128-byte records, against 8 KiB of records per chunk).
-// A launch too small for that runs 4-wave workgroups: more compute units share the chunks.
+// The shape of a launch over `n_chunks` chunks of each of n_jobs jobs.  A launch all of whose chunks can run at once does that, with
+// the fewest waves per workgroup, from four up, that allow it: the compute units share the chunks, and each of their waves has
+// more of its vector unit.  A larger one runs workgroups of 16 waves, or 8 where that lets more waves share a compute unit's LDS
+// (4 where the jobs have no more chunks), each wave taking as many chunks in turn (at most 8) as still leave every place on the chip
+// taken, because a workgroup first copies its table (64 KiB for 128-byte records, against 8 KiB of records per chunk).  Without a
+// table in LDS workgroups are as small as they can be, or, with more jobs than compute units, a job (of up to 16 chunks) each: then a
+// compute unit's caches hold few tables.
+// (2188 chunks of 128-byte records, encode and decode: 75 + 102 us with four waves that took two chunks in turn on one workgroup per
+// compute unit, 45 + 31 so; 64 tensors of 63 chunks 83 + 145, now 41 + 39.)
 struct Shape { int waves, chunks_per_wave; unsigned blocks; size_t lds; };
 int compute_units() {
     static int n[64] = {0};
@@ -542,18 +563,25 @@ int compute_units() {
 }
 Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs) {
     const int64_t total = n_chunks * n_jobs, cus = compute_units();
-    int waves = 16, wgs = 1, best = 0;
-    for (int w = 16; w >= 8; w -= 8) {
+    auto shape = [&](int waves, int64_t per) { return Shape{waves, (int)per, (unsigned)((n_chunks + waves * per - 1) / (waves * per)), table_b + (size_t)waves * wave_b}; };
+    if (table_b == 0) return shape(n_jobs > cus ? (int)std::clamp<int64_t>(n_chunks, 4, 16) : total > cus ? 2 : 1, 1);
+    auto places = [&](int w) -> int64_t {                        // workgroups a compute unit takes
         const size_t b = table_b + (size_t)w * wave_b;
-        if (b > (size_t)kLdsMost) continue;
-        const int fit = (int)((size_t)kLdsBudget / b), n = fit * w > 32 ? 32 / w : fit;
-        if (n * w > best) { best = n * w; waves = w; wgs = n; }
-    }
-    if (best == 0 || total < cus * waves) { waves = 4; wgs = 1; }
-    int64_t per = total / (cus * wgs * waves);
-    per = per < 1 ? 1 : (per > 8 ? 8 : per);
-    return {waves, (int)per, (unsigned)((n_chunks + waves * per - 1) / (waves * per)), table_b + (size_t)waves * wave_b};
+        return b > (size_t)kLdsMost ? 0 : std::min<int64_t>(kLdsBudget / b, 32 / w);
+    };
+    for (const int w : {4, 6, 8, 12, 16})
+        if ((n_chunks + w - 1) / w * n_jobs <= cus * places(w)) return shape(w, 1);
+    int waves = 4;
+    for (const int w : {8, 16})
+        if (n_chunks > w / 2 && places(w) > 0 && (waves == 4 || places(w) * w >= places(waves) * waves)) waves = w;
+    const int64_t per = total / (cus * std::max<int64_t>(places(waves), 1) * waves);
+    return shape(waves, per < 1 ? 1 : (per > 8 ? 8 : per));
 }
+
+// Whether jobs of a few chunks each, a workgroup per job, would wait for others to leave the LDS.  Then they read their tables from global
+// memory instead: 1000 tensors of one chunk, 128-byte records: encode 36 us with the tables in LDS, 28 without, decode 76 and 34;
+// with places for all, 250 tensors: 22 and 23, 21 and 31.  (At three chunks in encode, five in decode, the copy pays again.)
+bool jobs_wait(size_t table_b, size_t wave_b, int n_jobs) { return n_jobs > compute_units() * (int)(kLdsBudget / (table_b + 4 * wave_b)); }
 
 kvtc_status launch(const char* who, void (*fn)(EntropyArgs), const Shape& sh, int n_jobs, EntropyArgs a, hipStream_t st) {
     if (allow_full_lds(reinterpret_cast<const void*>(fn)) != hipSuccess) return set_error(KVTC_E_HIP, "%s: cannot size the LDS", who);
@@ -572,7 +600,8 @@ kvtc_status run_encode(const char* who, const kvtc_entropy* e, const EntropyArgs
     if (rc != KVTC_OK) return rc;
     hipLaunchKernelGGL(entropy_scan_kernel, dim3((unsigned)n_jobs), dim3(256), 0, st, a);
     if (max_chunks > 0) {
-        const bool tab_lds = (size_t)R * kEncRow + 16u * kImageDw * 4u <= (size_t)kLdsMost;
+        const bool tab_lds = R <= kMaxLdsRecord &&
+                             !(max_chunks <= 2 && jobs_wait((size_t)R * kEncRow, kImageDw * 4, n_jobs));
         rc = launch(who, tab_lds ? &entropy_write_kernel<true> : &entropy_write_kernel<false>,
                     launch_shape(tab_lds ? (size_t)R * kEncRow : 0, kImageDw * 4, max_chunks, n_jobs), n_jobs, a, st);
         if (rc != KVTC_OK) return rc;
@@ -588,8 +617,10 @@ kvtc_status run_decode(const char* who, const kvtc_entropy* e, const EntropyArgs
     a.max_tokens = max_tokens;
     const int64_t max_chunks = (max_tokens + kChunk - 1) / kChunk;
     if (max_chunks == 0) return KVTC_OK;
-    Shape sh = launch_shape((size_t)(R < kDecSegment ? R : kDecSegment) * kDecRow, kChunk * kDecPitch * 4, max_chunks, n_jobs);
-    const kvtc_status rc = launch(who, &entropy_decode_kernel, sh, n_jobs, a, st);
+    const size_t table_b = (size_t)(R < kDecSegment ? R : kDecSegment) * kDecRow, wave_b = kChunk * kDecPitch * 4;
+    const bool tab_lds = !(max_chunks <= 4 && jobs_wait(table_b, wave_b, n_jobs));
+    const kvtc_status rc = launch(who, tab_lds ? &entropy_decode_kernel<true> : &entropy_decode_kernel<false>,
+                                  launch_shape(tab_lds ? table_b : 0, wave_b, max_chunks, n_jobs), n_jobs, a, st);
     if (rc != KVTC_OK) return rc;
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return set_error(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(err));

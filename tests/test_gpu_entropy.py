@@ -213,7 +213,7 @@ def test_batched_jobs_equal_single_calls_and_bad_jobs_are_left_alone():
 
 @pytest.mark.parametrize("R,T", [(576, 130), (544, 64), (4, 1000), (36, 4097)])
 def test_record_sizes_at_the_limits(R, T):
-    """The largest record the stage takes (576 bytes: one wave per workgroup, 129 KB of LDS), the full-rank plans' 544, the
+    """The largest record the stage takes (576 bytes: 146 KiB of length table in LDS, decoded in four segments), the full-rank plans' 544, the
     smallest (4) and a size that is no power of two; synthetic bytes with a different skew at every position, tables from
     half of them."""
     rng = np.random.default_rng(R + T)

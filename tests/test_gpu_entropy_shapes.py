@@ -1,19 +1,22 @@
 """The lossless stage where its launches change shape: records of one and of two table segments with whole and partial store
-batches, code tables that fit the LDS and that do not, launches whose waves take several chunks each, and code lengths at
-both ends of what a table may hold.  Containers must equal the oracle's byte for byte."""
+batches, code tables that fit the LDS and that do not, workgroups of every number of waves, launches whose waves take several
+chunks each, jobs that read their tables from global memory, and code lengths at both ends of what a table may hold.
+Containers must equal the oracle's byte for byte."""
 import numpy as np
 import pytest
+import torch
 
 import kvtc_entropy as ke
 import paper_2511_01815_amd as kv
-from test_gpu_entropy import _gpu_decode, _gpu_encode
+from test_gpu_entropy import DEV, _gpu_decode, _gpu_encode
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("R,T", [(64, 65), (100, 1), (144, 200), (148, 130), (212, 64), (268, 129), (272, 129), (4, 525_000), (12, 263_000)])
+@pytest.mark.parametrize("R,T", [(64, 65), (100, 1), (144, 200), (148, 130), (212, 64), (264, 129), (268, 129), (272, 129), (4, 525_000), (12, 263_000)])
 def test_container_at_the_edges_of_the_launch_shapes(R, T):
-    """T = 525 000: 8204 chunks, two per 16-wave workgroup's wave on 256 compute units; 263 000: one."""
+    """264 bytes: the largest record whose code table fits the LDS.  T = 525 000: 8204 chunks, on 256 compute units a few more than
+    there are waves on the chip (8192 in encode); 263 000: 4110 chunks, all at once."""
     rng = np.random.default_rng(R + T)
     rec = np.stack([np.minimum(255, rng.geometric(1.0 / (1.2 + (11 * k) % 120), T) - 1) for k in range(R)], axis=1).astype(np.uint8)
     lengths = ke.calibrate_tables(rec[:4096])
@@ -47,3 +50,54 @@ def test_code_lengths_at_the_limits(kind):
     assert n == len(ref) and out[:n].tobytes() == ref
     assert np.array_equal(_gpu_decode(tab, ref, T, R), rec)
     tab.close()
+
+
+def _check_batch(R, lens, period):
+    """A batch whose job j codes tensor j % period (its first lens[j] tokens; lens repeats with the period too) with table set j % 2
+    against the oracle's containers, and back."""
+    n, rng = len(lens), np.random.default_rng(R + len(lens))
+    assert period % 2 == 0 and all(lens[j] == lens[j % period] for j in range(n))
+    recs = [np.stack([np.minimum(255, rng.geometric(1.0 / (1.2 + (11 * k + 17 * i) % 120), lens[i]) - 1) for k in range(R)], axis=1).astype(np.uint8)
+            for i in range(period)]
+    sample = np.concatenate(recs)[:4096]
+    tables = np.stack([ke.calibrate_tables(sample), ke.calibrate_tables(sample[:300])])
+    refs = [np.frombuffer(ke.encode(r, tables[i % 2]), dtype=np.uint8) for i, r in enumerate(recs)]
+    tab = kv.EntropyTables(R, tables)
+    rec_at = np.concatenate([[0], np.cumsum([v * R for v in lens])]).tolist()
+    caps = [ke.bound_bytes(v, R) for v in lens]
+    cod_at = np.concatenate([[0], np.cumsum(caps)]).tolist()
+    dev = torch.from_numpy(np.concatenate([r.reshape(-1) for r in recs])).to(DEV).repeat(n // period + 1)[:rec_at[-1]]
+    coded = torch.full((cod_at[-1] + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+    sizes = torch.zeros(n, dtype=torch.int64, device=DEV)
+
+    def jobs(room):
+        return torch.from_numpy(kv.make_entropy_jobs([j % 2 for j in range(n)], lens, rec_at[:-1], cod_at[:-1], room).view(np.uint8)).to(DEV)
+
+    kv.kvtc_entropy_encode_batch(tab.handle, jobs(caps), n, max(lens), dev, dev.numel(), coded, cod_at[-1], sizes)
+    torch.cuda.synchronize()
+    assert sizes.cpu().tolist() == [len(refs[j % period]) for j in range(n)]
+    want = [torch.from_numpy(r.copy()).to(DEV) for r in refs]
+    for j in range(n):
+        assert torch.equal(coded[cod_at[j]:cod_at[j] + len(refs[j % period])], want[j % period]), j
+    assert bool((coded[cod_at[-1]:] == 0xA5).all())
+    back = torch.full((dev.numel() + 64,), 0x5A, dtype=torch.uint8, device=DEV)
+    kv.kvtc_entropy_decode_batch(tab.handle, jobs([len(refs[j % period]) for j in range(n)]), n, max(lens), coded, cod_at[-1], back, dev.numel())
+    torch.cuda.synchronize()
+    assert torch.equal(back[:dev.numel()], dev) and bool((back[dev.numel():] == 0x5A).all())
+    tab.close()
+
+
+@pytest.mark.parametrize("chunks", [16, 20, 30, 45, 60, 70, 256])
+def test_workgroups_of_every_size_and_waves_of_several_chunks(chunks):
+    """64 tensors of 128-byte records.  Decode has one workgroup on each of 256 compute units: 4, 6, 8, 12 and 16 waves in turn, then
+    more workgroups than places, and with 256 chunks per tensor waves that take four chunks (strings four, sizes two)."""
+    _check_batch(128, [64 * chunks, 64 * chunks - 17] * 32, 2)
+
+
+@pytest.mark.parametrize("R,n_jobs", [(128, 600), (148, 600), (36, 1400)])
+@pytest.mark.parametrize("most", [64, 150, 250])
+def test_many_tensors_of_a_few_chunks(R, n_jobs, most):
+    """More jobs than places: up to two chunks the strings are coded from tables in global memory, up to four the records decoded."""
+    lens = np.random.default_rng(most).integers(1, most + 1, 10).tolist()
+    lens[3], lens[5] = most, max(1, most - 64)
+    _check_batch(R, [lens[j % 10] for j in range(n_jobs)], 10)
