@@ -85,19 +85,6 @@ kvtc_status fail(kvtc_status st, const char* fmt, ...) {
 
 float bf16_bits_to_float(uint16_t b) { return bits_f32((uint32_t)b << 16); }
 
-// Compute units of the current device (cached per device).
-int cu_count() {
-    static int n[64] = {0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    if (n[dev] == 0) {
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, dev) == hipSuccess) n[dev] = prop.multiProcessorCount;
-        if (n[dev] <= 0) n[dev] = 256;
-    }
-    return n[dev];
-}
-
 // Whether two workgroups of the short-job kernel share a compute unit: up to 8 waves with a coordinate tile each, by their registers, and
 // by the LDS they ask for.
 bool short_pairs(int ntw, int waves, int lds) { return ntw == 1 && waves <= 8 && 2 * lds <= kLdsBudget; }
@@ -107,7 +94,7 @@ bool short_pairs(int ntw, int waves, int lds) { return ntw == 1 && waves <= 8 &&
 // fewer workgroups than the chip, each walking all features.  One tensor of 4096 tokens at 16x: 42 us on the bulk tile, 21 on this;
 // where the tiles need a second round the bulk kernel, which reads the basis less often, is the faster one again.
 int short_tiles_per_job(int n_jobs, bool pairs) {
-    const int n = cu_count() * (pairs ? 2 : 1) / n_jobs;
+    const int n = compute_units() * (pairs ? 2 : 1) / n_jobs;
     return n < 1 ? 1 : n;
 }
 
@@ -574,7 +561,7 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
         e = launch_encode_short(a, dtype, plan->h.enc_short, plan->enc_s_waves, (int)tiles_short, (size_t)plan->enc_s_lds[dtype], static_cast<hipStream_t>(stream));
     } else {
         const int64_t tiles = (n_tokens + plan->h.enc_tok_wg - 1) / plan->h.enc_tok_wg;
-        const int slots = cu_count() * plan->h.enc_wgs;
+        const int slots = compute_units() * plan->h.enc_wgs;
         const int grid = (int)(tiles < slots ? tiles : slots);
         e = launch_encode(a, dtype, plan->h.enc_nw * 10000 + plan->h.enc_wc * 100 + plan->h.enc_ntw, grid, (size_t)kJobTableBytes + 64 + plan->h.enc_lds[dtype], static_cast<hipStream_t>(stream));
     }
@@ -613,7 +600,7 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
     a.dec_accumulate = accumulate;
     a.dec_sum = sum_dev;
     a.dec_sum_ld = sum_ld;
-    const int slots = cu_count() * plan->h.dec_wgs;
+    const int slots = compute_units() * plan->h.dec_wgs;
     // A tensor short enough for all its 128-token tiles to run at once takes the variant with one token
     // tile per wave (same plan data: it depends on the padded width only).  The workgroups beyond a launch's tiles
     // share the tiles' features (at most one workgroup per 64 of them).
@@ -792,7 +779,7 @@ kvtc_status kvtc_rope(void* x_dev, kvtc_dtype dtype, int64_t n_tokens, int n_hea
     for (int j = 0; j < d_head / 2; ++j) a.theta[j] = std::pow(base, -2.0 * (double)j / (double)d_head);
     const int64_t items = n_tokens * (int64_t)(d_head / 2);
     const int64_t want = (items + 255) / 256;
-    const int64_t cap = (int64_t)cu_count() * 16;
+    const int64_t cap = (int64_t)compute_units() * 16;
     hipError_t e = launch_rope(a, dtype, pairing == KVTC_ROPE_INTERLEAVED, (int)(want < cap ? want : cap), static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(KVTC_E_HIP, "kvtc_rope: launch failed: %s", hipGetErrorString(e));
     return KVTC_OK;
@@ -875,9 +862,9 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     // Short jobs go to the short-job kernel, the rest to the bulk variants.
     const int s_tiles = short_tiles_per_job(n_jobs, batch->enc_short[2].waves == 0 && short_pairs(1, batch->enc_short[1].waves, batch->enc_short[1].lds[dtype]));
     a.enc_short_max = s_tiles * kEncShortTile;
-    a.enc_cus = cu_count();
+    a.enc_cus = compute_units();
     for (const auto& v : batch->enc) {
-        hipError_t e = launch_encode(a, dtype, v.key, cu_count() * v.wgs,
+        hipError_t e = launch_encode(a, dtype, v.key, compute_units() * v.wgs,
                                      (size_t)kJobTableBytes + 64 + v.lds[dtype], static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(KVTC_E_HIP, "kvtc_encode_batch: launch failed: %s", hipGetErrorString(e));
     }
@@ -952,9 +939,9 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     a.status = status_dev;
     const int s_tiles = short_tiles_per_job(n_jobs, shrt[2].waves == 0 && short_pairs(1, shrt[1].waves, shrt[1].lds));
     a.enc_short_max = s_tiles * kEncShortTile;
-    a.enc_cus = cu_count();
+    a.enc_cus = compute_units();
     for (int k = 0; k < n_bulk; ++k) {
-        e = launch_encode(a, dtype, bulk[k].key, cu_count() * bulk[k].wgs, (size_t)kJobTableBytes + 64 + bulk[k].lds, st);
+        e = launch_encode(a, dtype, bulk[k].key, compute_units() * bulk[k].wgs, (size_t)kJobTableBytes + 64 + bulk[k].lds, st);
         if (e != hipSuccess) return fail(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
     }
     for (int ntw = 1; ntw <= 2; ++ntw) {
@@ -998,7 +985,7 @@ kvtc_status kvtc_decode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     for (const auto& v : batch->dec) {
         const DecLayout lay = decode_layout(v.rec, v.ring, v.wgs);
         a.dec_ring_off = lay.ring_off;
-        hipError_t e = launch_decode(a, dtype, v.key, cu_count() * v.wgs, lay.lds_bytes, static_cast<hipStream_t>(stream));
+        hipError_t e = launch_decode(a, dtype, v.key, compute_units() * v.wgs, lay.lds_bytes, static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(KVTC_E_HIP, "kvtc_decode_batch: launch failed: %s", hipGetErrorString(e));
     }
     return KVTC_OK;

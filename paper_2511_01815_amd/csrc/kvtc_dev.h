@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
+#include <atomic>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -32,6 +33,19 @@ inline hipError_t allow_full_lds(const void* fn) {
     e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBudget);
     if (e == hipSuccess) done.emplace_back(dev, fn);
     return e;
+}
+
+// Compute units of the current device, asked for once per device (any number of threads may).
+inline int compute_units() {
+    static std::atomic<int> known[64];
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    n = known[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        known[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
 }
 
 // Everything a kernel needs to know about a plan.  Lives in device memory and is read

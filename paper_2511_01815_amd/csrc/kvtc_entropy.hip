@@ -554,13 +554,6 @@ size_t bound_of(int R, int64_t n_tokens) {
 // (2188 chunks of 128-byte records, encode and decode: 75 + 102 us with four waves that took two chunks in turn on one workgroup per
 // compute unit, 45 + 31 so; 64 tensors of 63 chunks 83 + 145, now 41 + 39.)
 struct Shape { int waves, chunks_per_wave; unsigned blocks; size_t lds; };
-int compute_units() {
-    static int n[64] = {0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    if (n[dev] == 0 && (hipDeviceGetAttribute(&n[dev], hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n[dev] <= 0)) n[dev] = 256;
-    return n[dev];
-}
 Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs) {
     const int64_t total = n_chunks * n_jobs, cus = compute_units();
     auto shape = [&](int waves, int64_t per) { return Shape{waves, (int)per, (unsigned)((n_chunks + waves * per - 1) / (waves * per)), table_b + (size_t)waves * wave_b}; };
