@@ -607,8 +607,8 @@ __global__ void __launch_bounds__(kShortThreads) __attribute__((amdgpu_waves_per
     else encode_short_tile<NTW, XT, 2>(P, tr, a, smem);
 }
 
-// (waves across coordinates, coordinate tiles per wave, waves per workgroup); the two widest plans' variants have 64-token tiles
-// and take the short jobs too
+// (waves across coordinates, coordinate tiles per wave, waves per workgroup); no short-job kernel serves the plans of the last two, so
+// these, on 64-token tiles, code jobs of any length
 #define KVTC_ENC_VARIANTS(X)                                                                           \
     X(1, 2, 4) X(1, 4, 4) X(2, 3, 4) X(2, 4, 4) X(2, 5, 4) X(4, 3, 8) X(4, 4, 8) X(4, 5, 8) X(8, 3, 8) X(8, 4, 8)
 
@@ -634,7 +634,8 @@ hipError_t launch_encode(const KernelArgs& a, kvtc_dtype dtype, int key, int gri
     return hipLaunchKernel(fn, dim3(grid), dim3(threads), params, lds_bytes, stream);
 }
 
-// One workgroup of `waves` waves per job, or per 64-token tile of a single tensor; ntw: coordinate tiles per wave (the plans' enc_short).
+// `grid` workgroups of `waves` waves, one per 64-token tile: those of a single tensor, or of a batch the tiles a short job may have
+// times the jobs; ntw: coordinate tiles per wave (the plans' enc_short).
 hipError_t launch_encode_short(const KernelArgs& a, kvtc_dtype dtype, int ntw, int waves, int grid, size_t lds_bytes, hipStream_t stream) {
     const void* fn = nullptr;
     if (ntw == 1) fn = dtype == KVTC_BF16 ? reinterpret_cast<const void*>(&kvtc_encode_short_kernel<1, uint16_t>) : reinterpret_cast<const void*>(&kvtc_encode_short_kernel<1, float>);

@@ -1,5 +1,5 @@
 """Decode of few tiles, whose features are shared out among workgroups: feature counts of one span, of fewer and of more spans
-than workgroups per tile, token counts from one to where every tile has a workgroup of its own again.  A token's features are
+than workgroups per tile, token counts from one to where every tile has a workgroup to itself again.  A token's features are
 independent, so the output must not depend on the split: rows decoded in calls of other sizes must be the same bits, and
 they are held to the oracle once."""
 import numpy as np
@@ -26,7 +26,7 @@ def test_split_sweep_gives_the_bits_of_a_whole_sweep(p, groups, dtype):
     base = torch.randn((1200, p), generator=g, device=DEV).to(tdt)
     rec = torch.zeros((1200, R), dtype=torch.uint8, device=DEV)
     kv.kvtc_encode(plan.handle, base, dtype, 1200, p, rec, rec.numel())
-    stream = rec.repeat(T // 1200, 1)                      # 66000 records: more tiles than the chip has workgroup slots
+    stream = rec.repeat(T // 1200, 1)                      # 66000 records: more than one tile for every two workgroup slots, so no tile is shared
     whole = torch.full((T, p), 7.0, dtype=tdt, device=DEV)
     kv.kvtc_decode(plan.handle, stream, stream.numel(), T, whole, dtype, p)
     torch.cuda.synchronize()
