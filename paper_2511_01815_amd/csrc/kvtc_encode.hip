@@ -599,7 +599,10 @@ __global__ void __launch_bounds__(kShortThreads) __attribute__((amdgpu_waves_per
     const PlanEnc P = load_plan_enc(plan);
     if (plan->enc_short != NTW) return;
     if (a.jobs) {
-        if (__builtin_expect(tr.n_tokens > kEncShortTile, 0) && bulk_takes_mid_jobs(a, enc_key(*plan), (uint32_t)(a.enc_cus * plan->enc_wgs))) return;
+        // (one branch for the wave, which only this tells the compiler: as a choice per lane it cost the main loop of the wide form 3 %)
+        if (__builtin_expect(tr.n_tokens > kEncShortTile, 0) &&
+            __builtin_amdgcn_readfirstlane((int)bulk_takes_mid_jobs(a, enc_key(*plan), (uint32_t)(a.enc_cus * plan->enc_wgs))) != 0)
+            return;
         const uint64_t bytes = (uint64_t)tr.n_tokens * (uint64_t)P.rec_dwords * 4ull;
         if (tr.offset > a.cap || bytes > a.cap - tr.offset) return;
     }
