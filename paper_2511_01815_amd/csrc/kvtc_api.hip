@@ -561,6 +561,7 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
         e = launch_encode_short(a, dtype, plan->h.enc_short, plan->enc_s_waves, (int)tiles_short, (size_t)plan->enc_s_lds[dtype], static_cast<hipStream_t>(stream));
     } else {
         const int64_t tiles = (n_tokens + plan->h.enc_tok_wg - 1) / plan->h.enc_tok_wg;
+        a.single_tiles = (uint32_t)tiles;
         const int slots = compute_units() * plan->h.enc_wgs;
         const int grid = (int)(tiles < slots ? tiles : slots);
         e = launch_encode(a, dtype, plan->h.enc_nw * 10000 + plan->h.enc_wc * 100 + plan->h.enc_ntw, grid, (size_t)kJobTableBytes + 64 + plan->h.enc_lds[dtype], static_cast<hipStream_t>(stream));
@@ -612,10 +613,12 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
         const DecLayout lay = decode_layout(decode_rec_bytes(1, plan->h.rec_dwords), plan->h.dec_ring_lds, plan->h.dec_wgs);
         a.dec_ring_off = lay.ring_off;
         a.dec_short = 1;
+        a.single_tiles = (uint32_t)tiles_short;
         const int grid = (int)(tiles_short * spans < slots ? tiles_short * spans : slots);
         e = launch_decode(a, dtype, 100 + plan->h.dec_cls, grid, lay.lds_bytes, static_cast<hipStream_t>(stream));
     } else {
         const int64_t tiles = (n_tokens + plan->h.dec_tok_wg - 1) / plan->h.dec_tok_wg;
+        a.single_tiles = (uint32_t)tiles;
         const int64_t shares = wide ? (spans < 4 ? 1 : spans / 4) : spans;       // workgroups a tile may be shared among
         const int grid = (int)(tiles * shares < slots ? tiles * shares : slots);
         const DecLayout lay = decode_layout(plan->h.dec_rec_lds, plan->h.dec_ring_lds, plan->h.dec_wgs);

@@ -76,6 +76,7 @@ struct KernelArgs {
     const kvtc_job* jobs;      // device array, or nullptr -> `single`
     int32_t n_jobs;
     kvtc_job single;
+    uint32_t single_tiles;     // of `single`, at the launch's tile size
     const uint64_t* offsets;   // device, [n_jobs + 1], or nullptr (single job at offset 0)
     const void* x;             // feature array (encode: input, decode: output)
     int64_t ld_x;
@@ -102,7 +103,7 @@ struct TileRef {
 };
 
 // The bulk encode variant of a plan, in decimal positions.
-__device__ __forceinline__ int enc_key(const PlanDev& pl) { return pl.enc_nw * 10000 + pl.enc_wc * 100 + pl.enc_ntw; }
+template <typename P> __device__ __forceinline__ int enc_key(const P& pl) { return pl.enc_nw * 10000 + pl.enc_wc * 100 + pl.enc_ntw; }
 
 // Whether a job can be coded at all: its plan, its token count, and its own extent inside the buffer (offsets need not be a running
 // sum: an append writes each job into its own region).
@@ -191,11 +192,12 @@ __device__ __forceinline__ BlockScan block_scan(uint32_t sum, uint32_t low, uint
 // the total.  A job with a bad plan index, a negative token count or a stream that would end
 // beyond `cap` gets zero tiles, and so does a job whose plan belongs to another kernel variant
 // (variant_key: the variant's parameters in decimal positions) or that the short-job kernel codes; workgroup 0 reports the
-// lowest bad job in *status.
+// lowest bad job in *status.  (A single tensor's launch has no table: built from one job it was 1 us of a small call.)
 template <bool kEncode, int NT = kThreads>
 __device__ inline uint32_t build_tile_table(const KernelArgs& a, int variant_key, uint32_t* tile_start, uint32_t* scratch /*[6 * NT / 64]*/) {
+    if (!a.jobs) return a.single_tiles;      // the host has checked everything: no table
     const int tid = threadIdx.x;
-    const int n_jobs = a.jobs ? a.n_jobs : 1;
+    const int n_jobs = a.n_jobs;
     const int per = (n_jobs + NT - 1) / NT;
     const int j0 = tid * per;
     uint32_t local[kMaxJobs / NT], mid[kMaxJobs / NT];           // tiles; tiles of a job of more than one short tile that may go either way
@@ -208,7 +210,7 @@ __device__ inline uint32_t build_tile_table(const KernelArgs& a, int variant_key
         mid[k] = 0;
         const int j = j0 + k;
         if (k < per && j < n_jobs) {
-            const kvtc_job jb = a.jobs ? a.jobs[j] : a.single;
+            const kvtc_job jb = a.jobs[j];
             if (job_ok(a, j, jb)) {
                 const PlanDev& pl = a.plans[jb.plan];
                 // each launch serves the plans of its own kernel variant; other launches take the rest.
@@ -233,7 +235,7 @@ __device__ inline uint32_t build_tile_table(const KernelArgs& a, int variant_key
     BlockScan sc = block_scan<NT>(sum, first_bad, flags, scratch);
     // lowest bad job -> status (workgroup 0 only; a plain vector store)
     if (a.status && blockIdx.x == 0 && tid == 0 && sc.low != 0xffffffffu) *a.status = sc.low + 1u;
-    if (kEncode && __builtin_expect(a.jobs && sc.flags == 3u, 0)) {
+    if (kEncode && __builtin_expect(sc.flags == 3u, 0)) {
         const BlockScan with = block_scan<NT>(sum + mids, 0u, 0u, scratch + 3 * NT / 64);
         if (bulk_takes_all(sc.total, with.total, gridDim.x)) {
             sc = with;
@@ -266,22 +268,21 @@ template <typename T> __device__ __forceinline__ const T* uniform_ptr(const T* p
 // wait for nor disturb the vector-memory operations a kernel keeps in flight.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ u32x4 sload_x4(const void* p_uniform) {
-    u32x4 v;
-    asm volatile("s_load_dwordx4 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(uniform_ptr(reinterpret_cast<const char*>(p_uniform))) : "memory");
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+// 16 bytes and 8 bytes from two places, one round trip
+struct Words4And2 { u32x4 four; u32x2 two; };
+__device__ __forceinline__ Words4And2 sload_x4_x2(const void* p4_uniform, const void* p2_uniform) {
+    Words4And2 v;
+    asm volatile("s_load_dwordx4 %0, %2, 0x0\n\ts_load_dwordx2 %1, %3, 0x0\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(v.four), "=&s"(v.two)
+                 : "s"(uniform_ptr(reinterpret_cast<const char*>(p4_uniform))), "s"(uniform_ptr(reinterpret_cast<const char*>(p2_uniform))) : "memory");
     return v;
 }
-__device__ __forceinline__ u32x2 sload_x2(const void* p_uniform) {
-    u32x2 v;
-    asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(uniform_ptr(reinterpret_cast<const char*>(p_uniform))) : "memory");
-    return v;
-}
-template <typename T> __device__ __forceinline__ T* sload_ptr(const void* p_uniform) {
-    const u32x2 v = sload_x2(p_uniform);
-    return reinterpret_cast<T*>(((uint64_t)v[1] << 32) | v[0]);
-}
+template <typename T> __device__ __forceinline__ T* ptr_of(uint32_t lo, uint32_t hi) { return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo); }
 
-// The fields of a plan descriptor the decode kernel uses, in scalar registers.
+// The fields of a plan descriptor the decode kernel uses, in scalar registers.  (Its loads are issued together: one round trip to
+// the L2, where a wait behind each of six loads was six.  Small calls are chains of such round trips.)
 struct PlanDec {
     int32_t p, rec_dwords, dec_nct, dec_tt, dec_tok_wg, code_bits_max;
     const uint4* v_dec;
@@ -289,25 +290,27 @@ struct PlanDec {
 };
 __device__ __forceinline__ PlanDec load_plan_dec(const PlanDev* P) {
     static_assert(offsetof(PlanDev, p) == 0 && offsetof(PlanDev, rec_dwords) == 16 && offsetof(PlanDev, dec_nct) == 28 &&
-                  offsetof(PlanDev, dec_tt) == 32 && offsetof(PlanDev, dec_tok_wg) == 40, "descriptor layout");
-    const char* b = reinterpret_cast<const char*>(P);
-    static_assert(offsetof(PlanDev, code_bits_max) == 60, "descriptor layout");
-    const u32x4 q0 = sload_x4(b), q1 = sload_x4(b + 16), q2 = sload_x4(b + 32), q3 = sload_x4(b + 48);
+                  offsetof(PlanDev, dec_tt) == 32 && offsetof(PlanDev, dec_tok_wg) == 40 && offsetof(PlanDev, code_bits_max) == 60, "descriptor layout");
+    static_assert(offsetof(PlanDev, v_dec) == 96 && offsetof(PlanDev, blk) == 120, "descriptor layout");
+    u32x16 f;
+    u32x8 q;
+    asm volatile("s_load_dwordx16 %0, %2, 0x0\n\ts_load_dwordx8 %1, %2, 0x60\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(f), "=&s"(q) : "s"(uniform_ptr(reinterpret_cast<const char*>(P))) : "memory");
     PlanDec d;
-    d.p = (int32_t)q0[0];
-    d.rec_dwords = (int32_t)q1[0];
-    d.dec_nct = (int32_t)q1[3];
-    d.dec_tt = (int32_t)q2[0];
-    d.dec_tok_wg = (int32_t)q2[2];
-    d.code_bits_max = (int32_t)q3[3];
-    d.v_dec = sload_ptr<const uint4>(b + offsetof(PlanDev, v_dec));
-    d.blk = sload_ptr<const uint32_t>(b + offsetof(PlanDev, blk));
+    d.p = (int32_t)f[0];
+    d.rec_dwords = (int32_t)f[4];
+    d.dec_nct = (int32_t)f[7];
+    d.dec_tt = (int32_t)f[8];
+    d.dec_tok_wg = (int32_t)f[10];
+    d.code_bits_max = (int32_t)f[15];
+    d.v_dec = ptr_of<const uint4>(q[0], q[1]);
+    d.blk = ptr_of<const uint32_t>(q[6], q[7]);
     return d;
 }
 
 // The fields of a plan descriptor the encode kernel uses, in scalar registers.
 struct PlanEnc {
-    int32_t p, n_groups, rec_dwords, enc_ntw, enc_wc, code_bits_max;
+    int32_t p, n_groups, rec_dwords, enc_ntw, enc_wc, code_bits_max, enc_wgs, enc_nw, enc_short;
     const uint4* v_enc;
     const float* negc;
     const uint32_t* blk;
@@ -315,19 +318,26 @@ struct PlanEnc {
 };
 __device__ __forceinline__ PlanEnc load_plan_enc(const PlanDev* P) {
     static_assert(offsetof(PlanDev, n_groups) == 8 && offsetof(PlanDev, enc_ntw) == 20 && offsetof(PlanDev, enc_wc) == 24, "descriptor layout");
-    const char* b = reinterpret_cast<const char*>(P);
-    const u32x4 q0 = sload_x4(b), q1 = sload_x4(b + 16), q3 = sload_x4(b + 48);
+    static_assert(offsetof(PlanDev, enc_wgs) == 64 && offsetof(PlanDev, enc_short) == 76 && offsetof(PlanDev, v_enc) == 88 &&
+                  offsetof(PlanDev, negc) == 104 && offsetof(PlanDev, blk) == 120 && offsetof(PlanDev, grp) == 128, "descriptor layout");
+    u32x16 f, q;
+    u32x2 t;
+    asm volatile("s_load_dwordx16 %0, %3, 0x0\n\ts_load_dwordx16 %1, %3, 0x40\n\ts_load_dwordx2 %2, %3, 0x80\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(f), "=&s"(q), "=&s"(t) : "s"(uniform_ptr(reinterpret_cast<const char*>(P))) : "memory");
     PlanEnc d;
-    d.code_bits_max = (int32_t)q3[3];
-    d.p = (int32_t)q0[0];
-    d.n_groups = (int32_t)q0[2];
-    d.rec_dwords = (int32_t)q1[0];
-    d.enc_ntw = (int32_t)q1[1];
-    d.enc_wc = (int32_t)q1[2];
-    d.v_enc = sload_ptr<const uint4>(b + offsetof(PlanDev, v_enc));
-    d.negc = sload_ptr<const float>(b + offsetof(PlanDev, negc));
-    d.blk = sload_ptr<const uint32_t>(b + offsetof(PlanDev, blk));
-    d.grp = sload_ptr<const uint32_t>(b + offsetof(PlanDev, grp));
+    d.p = (int32_t)f[0];
+    d.n_groups = (int32_t)f[2];
+    d.rec_dwords = (int32_t)f[4];
+    d.enc_ntw = (int32_t)f[5];
+    d.enc_wc = (int32_t)f[6];
+    d.code_bits_max = (int32_t)f[15];
+    d.enc_wgs = (int32_t)q[0];
+    d.enc_nw = (int32_t)q[2];
+    d.enc_short = (int32_t)q[3];
+    d.v_enc = ptr_of<const uint4>(q[6], q[7]);
+    d.negc = ptr_of<const float>(q[10], q[11]);
+    d.blk = ptr_of<const uint32_t>(q[14], q[15]);
+    d.grp = ptr_of<const uint32_t>(t[0], t[1]);
     return d;
 }
 
@@ -347,33 +357,22 @@ __device__ __forceinline__ TileRange my_tiles(uint32_t total) {
 }
 
 __device__ inline TileRef find_tile(const KernelArgs& a, const uint32_t* tile_start, uint32_t tile) {
-    const int n_jobs = a.jobs ? a.n_jobs : 1;
-    int lo = 0, hi = n_jobs;                 // invariant: tile_start[lo] <= tile < tile_start[hi]
+    static_assert(sizeof(kvtc_job) == 16 && offsetof(kvtc_job, n_tokens) == 4 && offsetof(kvtc_job, x_row0) == 8, "job layout");
+    if (!a.jobs) return TileRef{0, a.single.plan, a.single.n_tokens, a.single.x_row0, 0ull, (int32_t)tile};
+    int lo = 0, hi = a.n_jobs;               // invariant: tile_start[lo] <= tile < tile_start[hi]
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (tile_start[mid] <= tile) lo = mid; else hi = mid;
     }
     lo = __builtin_amdgcn_readfirstlane(lo);
-    static_assert(sizeof(kvtc_job) == 16 && offsetof(kvtc_job, n_tokens) == 4 && offsetof(kvtc_job, x_row0) == 8, "job layout");
+    const Words4And2 v = sload_x4_x2(a.jobs + lo, a.offsets + lo);
     TileRef t;
     t.job = lo;
-    if (a.jobs) {
-        const u32x4 jb = sload_x4(a.jobs + lo);
-        t.plan = (int32_t)jb[0];
-        t.n_tokens = (int32_t)jb[1];
-        t.x_row0 = (int64_t)(((uint64_t)jb[3] << 32) | jb[2]);
-    } else {
-        t.plan = a.single.plan;
-        t.n_tokens = a.single.n_tokens;
-        t.x_row0 = a.single.x_row0;
-    }
-    t.offset = 0ull;
-    if (a.offsets) {
-        const u32x2 o = sload_x2(a.offsets + lo);
-        t.offset = ((uint64_t)o[1] << 32) | o[0];
-    }
-    t.tile = (int32_t)(tile - tile_start[lo]);
-    t.tile = __builtin_amdgcn_readfirstlane(t.tile);
+    t.plan = (int32_t)v.four[0];
+    t.n_tokens = (int32_t)v.four[1];
+    t.x_row0 = (int64_t)(((uint64_t)v.four[3] << 32) | v.four[2]);
+    t.offset = ((uint64_t)v.two[1] << 32) | v.two[0];
+    t.tile = __builtin_amdgcn_readfirstlane((int32_t)(tile - tile_start[lo]));
     return t;
 }
 

@@ -588,20 +588,20 @@ __global__ void __launch_bounds__(kShortThreads) __attribute__((amdgpu_waves_per
         // reported it)
         // the first tiles of all jobs come first: they spread over the XCDs, and workgroups that find no tile wait behind them
         const int tile = (int)blockIdx.x / a.n_jobs, job = (int)blockIdx.x - tile * a.n_jobs;
-        const u32x4 jb = sload_x4(a.jobs + job);
-        const u32x2 o = sload_x2(a.offsets + job);
+        const Words4And2 v = sload_x4_x2(a.jobs + job, a.offsets + job);
+        const u32x4 jb = v.four;
+        const u32x2 o = v.two;
         tr = TileRef{job, (int32_t)jb[0], (int32_t)jb[1], (int64_t)(((uint64_t)jb[3] << 32) | jb[2]), ((uint64_t)o[1] << 32) | o[0], tile};
         if (tr.plan < 0 || tr.plan >= a.n_plans || tr.n_tokens <= tr.tile * kEncShortTile || tr.n_tokens > a.enc_short_max) return;
     } else {
         tr = TileRef{0, a.single.plan, a.single.n_tokens, a.single.x_row0, 0ull, (int32_t)blockIdx.x};
     }
-    const PlanDev* plan = a.plans + tr.plan;
-    const PlanEnc P = load_plan_enc(plan);
-    if (plan->enc_short != NTW) return;
+    const PlanEnc P = load_plan_enc(a.plans + tr.plan);
+    if (P.enc_short != NTW) return;
     if (a.jobs) {
         // (one branch for the wave, which only this tells the compiler: as a choice per lane it cost the main loop of the wide form 3 %)
         if (__builtin_expect(tr.n_tokens > kEncShortTile, 0) &&
-            __builtin_amdgcn_readfirstlane((int)bulk_takes_mid_jobs(a, enc_key(*plan), (uint32_t)(a.enc_cus * plan->enc_wgs))) != 0)
+            __builtin_amdgcn_readfirstlane((int)bulk_takes_mid_jobs(a, enc_key(P), (uint32_t)(a.enc_cus * P.enc_wgs))) != 0)
             return;
         const uint64_t bytes = (uint64_t)tr.n_tokens * (uint64_t)P.rec_dwords * 4ull;
         if (tr.offset > a.cap || bytes > a.cap - tr.offset) return;

@@ -399,7 +399,6 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
 // did not meet in the L2: five times the writes to memory, 0.57 ms).  No step of the walk branches but for the next four
 // dwords of the string.  256 MiB of records: 777 us with twelve comparisons per symbol, 336 now: 34 vector
 // instructions per symbol, which keep the vector units busy for 270 of them.
-typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 // the k-th of four values, k modulo 4 (by value: a choice between variables is one between addresses, and puts them in memory)
 __device__ __forceinline__ uint32_t pick(uint32_t k, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
     const uint32_t lo = (k & 1u) ? b : a, hi = (k & 1u) ? d : c;
