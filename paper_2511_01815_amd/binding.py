@@ -153,10 +153,17 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+def _current_stream() -> int:
+    """The handle of torch's current stream.  Asked for without building a Stream object, where this torch has the call: 2.8 us of the
+    host's time per call of the library otherwise, 0.3 so (a short context's four calls: 32.7 us on the host, the GPU's work 28)."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(torch.cuda.current_device()) if raw is not None else torch.cuda.current_stream().cuda_stream
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
