@@ -66,6 +66,8 @@ struct kvtc_batch {
     struct ShortVariant { int waves, lds[2]; } enc_short[3];     // short-job kernels by coordinate tiles per wave; waves = 0: no plan uses it
     std::vector<DecVariant> dec;
     int max_p;
+    int min_rec_dwords;                                 // the shortest record among the plans
+    bool all_short;                                     // every plan has a short-job encode kernel
     std::vector<int32_t> ps;                            // the distinct feature counts among the plans
     std::vector<int32_t> rec_dwords;
     uint32_t* rec_dwords_dev;
@@ -96,6 +98,14 @@ bool short_pairs(int ntw, int waves, int lds) { return ntw == 1 && waves <= 8 &&
 int short_tiles_per_job(int n_jobs, bool pairs) {
     const int n = compute_units() * (pairs ? 2 : 1) / n_jobs;
     return n < 1 ? 1 : n;
+}
+
+// Workgroups of a batch's one short-job launch, or 0 if the batch cannot be shown to fit one round of them: jobs do not overlap in the
+// stream buffer, so its size bounds their tokens; each may end in a part of a tile; one workgroup more reports the jobs that are not valid.
+int short_table_grid(size_t cap, int min_rec_dwords, int n_jobs, bool pairs) {
+    const size_t tiles = cap / ((size_t)min_rec_dwords * 4 * kEncShortTile) + (size_t)n_jobs;
+    const size_t grid = (tiles + 7) / 8 * 8 + 1;                     // whole shares for the eight XCDs
+    return n_jobs <= kShortTableJobs && grid <= (size_t)compute_units() * (pairs ? 2 : 1) ? (int)grid : 0;
 }
 
 // Row pitch limit (elements): the kernels address a workgroup tile of up to 256 rows with 32-bit byte offsets.
@@ -639,6 +649,8 @@ kvtc_status kvtc_batch_create(kvtc_batch** out, const kvtc_plan* const* plans, i
     b->rec_dwords_dev = nullptr;
     b->n_plans = n_plans;
     b->max_p = 0;
+    b->min_rec_dwords = 1 << 30;
+    b->all_short = true;
     for (auto& v : b->enc_short) v = {0, {0, 0}};
     try {
     for (int i = 0; i < n_plans; ++i) {
@@ -649,6 +661,8 @@ kvtc_status kvtc_batch_create(kvtc_batch** out, const kvtc_plan* const* plans, i
         h.push_back(plans[i]->h);
         b->rec_dwords.push_back(plans[i]->h.rec_dwords);
         const PlanDev& ph = plans[i]->h;
+        b->min_rec_dwords = std::min(b->min_rec_dwords, ph.rec_dwords);
+        b->all_short = b->all_short && ph.enc_short != 0;
         {
             const int key = ph.enc_nw * 10000 + ph.enc_wc * 100 + ph.enc_ntw;
             kvtc_batch::EncVariant* v = nullptr;
@@ -814,6 +828,39 @@ kvtc_status kvtc_fp8_unpack(const void* in_dev, size_t in_bytes, int64_t n_token
     return KVTC_OK;
 }
 
+// The launches of a batched encode: the kernel variants among its plans.
+struct EncodeLaunches {
+    struct Bulk { int key, wgs, lds; } bulk[16];        // (a variant per row of the plans' table)
+    int n_bulk;
+    struct Short { int waves, lds; } shrt[3];            // by coordinate tiles per wave; waves = 0: none
+    bool all_short;
+    int min_rec_dwords;
+};
+
+static kvtc_status launch_encode_jobs(const char* who, const EncodeLaunches& l, KernelArgs& a, kvtc_dtype dtype, hipStream_t st) {
+    const bool pairs = l.shrt[2].waves == 0 && short_pairs(1, l.shrt[1].waves, l.shrt[1].lds);
+    const int grid = l.all_short ? short_table_grid(a.cap, l.min_rec_dwords, a.n_jobs, pairs) : 0;
+    hipError_t e = hipSuccess;
+    if (grid != 0) {
+        // few tokens in all: one round of the short-job kernel
+        a.enc_table = 1;
+        a.enc_max_tokens = (int32_t)(a.cap / ((size_t)l.min_rec_dwords * 4));
+        for (int ntw = 1; ntw <= 2 && e == hipSuccess; ++ntw)
+            if (l.shrt[ntw].waves != 0) e = launch_encode_short(a, dtype, ntw, l.shrt[ntw].waves, grid, (size_t)l.shrt[ntw].lds, st);
+    } else {
+        // short jobs go to the short-job kernel, the rest to the bulk variants
+        const int s_tiles = short_tiles_per_job(a.n_jobs, pairs);
+        a.enc_short_max = s_tiles * kEncShortTile;
+        a.enc_cus = compute_units();
+        for (int k = 0; k < l.n_bulk && e == hipSuccess; ++k)
+            e = launch_encode(a, dtype, l.bulk[k].key, compute_units() * l.bulk[k].wgs, (size_t)kJobTableBytes + 64 + l.bulk[k].lds, st);
+        for (int ntw = 1; ntw <= 2 && e == hipSuccess; ++ntw)
+            if (l.shrt[ntw].waves != 0) e = launch_encode_short(a, dtype, ntw, l.shrt[ntw].waves, a.n_jobs * s_tiles, (size_t)l.shrt[ntw].lds, st);
+    }
+    if (e != hipSuccess) return fail(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
+    return KVTC_OK;
+}
+
 static kvtc_status batch_common(const char* who, const kvtc_batch* batch, const kvtc_job* jobs_dev, int n_jobs,
                                 const void* x, kvtc_dtype dtype, const kvtc_layout* layout, const uint64_t* offsets_dev,
                                 const void* stream_buf, const uint32_t* status_dev, bool* nothing, XLayout* xl) {
@@ -862,22 +909,13 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.stream_buf = out_base_dev;
     a.cap = out_cap;
     a.status = status_dev;
-    // Short jobs go to the short-job kernel, the rest to the bulk variants.
-    const int s_tiles = short_tiles_per_job(n_jobs, batch->enc_short[2].waves == 0 && short_pairs(1, batch->enc_short[1].waves, batch->enc_short[1].lds[dtype]));
-    a.enc_short_max = s_tiles * kEncShortTile;
-    a.enc_cus = compute_units();
-    for (const auto& v : batch->enc) {
-        hipError_t e = launch_encode(a, dtype, v.key, compute_units() * v.wgs,
-                                     (size_t)kJobTableBytes + 64 + v.lds[dtype], static_cast<hipStream_t>(stream));
-        if (e != hipSuccess) return fail(KVTC_E_HIP, "kvtc_encode_batch: launch failed: %s", hipGetErrorString(e));
-    }
-    for (int ntw = 1; ntw <= 2; ++ntw) {
-        const auto& v = batch->enc_short[ntw];
-        if (v.waves == 0) continue;
-        hipError_t e = launch_encode_short(a, dtype, ntw, v.waves, n_jobs * s_tiles, (size_t)v.lds[dtype], static_cast<hipStream_t>(stream));
-        if (e != hipSuccess) return fail(KVTC_E_HIP, "kvtc_encode_batch: launch failed: %s", hipGetErrorString(e));
-    }
-    return KVTC_OK;
+    EncodeLaunches l;
+    l.n_bulk = 0;
+    l.all_short = batch->all_short;
+    l.min_rec_dwords = batch->min_rec_dwords;
+    for (int ntw = 1; ntw <= 2; ++ntw) l.shrt[ntw] = {batch->enc_short[ntw].waves, batch->enc_short[ntw].lds[dtype]};
+    for (const auto& v : batch->enc) l.bulk[l.n_bulk++] = {v.key, v.wgs, v.lds[dtype]};
+    return launch_encode_jobs("kvtc_encode_batch", l, a, dtype, static_cast<hipStream_t>(stream));
 }
 
 kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans, const kvtc_job* jobs_dev, int n_jobs,
@@ -896,11 +934,11 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     if (ld_x > kMaxPitch) return fail(KVTC_E_ARG, "%s: ld_x=%lld above %d", who, (long long)ld_x, kMaxPitch);
     if (reinterpret_cast<uintptr_t>(out_base_dev) & 15u) return fail(KVTC_E_ARG, "%s: stream buffer must be 16-byte aligned", who);
     // the kernel variants among the plans and their LDS needs, on the stack
-    struct Variant { int key, wgs, lds; };
-    struct ShortVariant { int waves, lds; };
-    Variant bulk[kStaticMaxPlans];
-    ShortVariant shrt[3] = {{0, 0}, {0, 0}, {0, 0}};
-    int n_bulk = 0;
+    EncodeLaunches l;
+    l.n_bulk = 0;
+    l.all_short = true;
+    l.min_rec_dwords = 1 << 30;
+    l.shrt[1] = l.shrt[2] = {0, 0};
     PlanPtrs ptrs;
     for (int i = 0; i < n_plans; ++i) {
         if (!plans[i]) return fail(KVTC_E_ARG, "%s: plan %d is null", who, i);
@@ -909,13 +947,15 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
         ptrs.p[i] = plans[i]->desc_dev;
         const int key = ph.enc_nw * 10000 + ph.enc_wc * 100 + ph.enc_ntw;
         int k = 0;
-        while (k < n_bulk && bulk[k].key != key) ++k;
-        if (k == n_bulk) bulk[n_bulk++] = Variant{key, ph.enc_wgs, 0};
-        if (ph.enc_lds[dtype] > bulk[k].lds) bulk[k].lds = ph.enc_lds[dtype];
+        while (k < l.n_bulk && l.bulk[k].key != key) ++k;
+        if (k == l.n_bulk) l.bulk[l.n_bulk++] = {key, ph.enc_wgs, 0};
+        l.bulk[k].lds = std::max(l.bulk[k].lds, ph.enc_lds[dtype]);
+        l.min_rec_dwords = std::min(l.min_rec_dwords, ph.rec_dwords);
+        l.all_short = l.all_short && ph.enc_short != 0;
         if (ph.enc_short != 0) {
-            ShortVariant& v = shrt[ph.enc_short];
-            if (plans[i]->enc_s_waves > v.waves) v.waves = plans[i]->enc_s_waves;
-            if (plans[i]->enc_s_lds[dtype] > v.lds) v.lds = plans[i]->enc_s_lds[dtype];
+            auto& v = l.shrt[ph.enc_short];
+            v.waves = std::max(v.waves, plans[i]->enc_s_waves);
+            v.lds = std::max(v.lds, plans[i]->enc_s_lds[dtype]);
         }
     }
     for (int i = n_plans; i < kStaticMaxPlans; ++i) ptrs.p[i] = nullptr;
@@ -940,19 +980,7 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     a.stream_buf = out_base_dev;
     a.cap = out_cap;
     a.status = status_dev;
-    const int s_tiles = short_tiles_per_job(n_jobs, shrt[2].waves == 0 && short_pairs(1, shrt[1].waves, shrt[1].lds));
-    a.enc_short_max = s_tiles * kEncShortTile;
-    a.enc_cus = compute_units();
-    for (int k = 0; k < n_bulk; ++k) {
-        e = launch_encode(a, dtype, bulk[k].key, compute_units() * bulk[k].wgs, (size_t)kJobTableBytes + 64 + bulk[k].lds, st);
-        if (e != hipSuccess) return fail(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
-    }
-    for (int ntw = 1; ntw <= 2; ++ntw) {
-        if (shrt[ntw].waves == 0) continue;
-        e = launch_encode_short(a, dtype, ntw, shrt[ntw].waves, n_jobs * s_tiles, (size_t)shrt[ntw].lds, st);
-        if (e != hipSuccess) return fail(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
-    }
-    return KVTC_OK;
+    return launch_encode_jobs(who, l, a, dtype, st);
 }
 
 kvtc_status kvtc_decode_batch(const kvtc_batch* batch, const kvtc_job* jobs_dev, int n_jobs, const void* in_base_dev,

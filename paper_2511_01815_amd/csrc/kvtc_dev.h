@@ -17,6 +17,7 @@ constexpr int kMaxJobs = 1024;         // jobs per batched launch (tile table li
 constexpr int kLdsBudget = 160 * 1024; // gfx950 LDS per workgroup
 constexpr int kJobTableBytes = (kMaxJobs + 1) * 4;
 constexpr int kEncShortTile = 64;      // tokens per workgroup tile of the encode kernel for short jobs
+constexpr int kShortTableJobs = 512;   // jobs of a batch that the short-job kernel codes alone, at most
 constexpr int kDecShortTile = 128;     // the same for decode (one token tile per wave)
 
 // Lets a kernel use the whole LDS of a compute unit as dynamic shared memory.  The attribute
@@ -87,6 +88,8 @@ struct KernelArgs {
     uint32_t* status;          // device, may be nullptr
     uint32_t dec_ring_off;     // decode: byte offset of the basis ring in the work area; 0 = it shares the record image's space
     int32_t enc_short_max;     // encode: jobs of at most this many tokens whose plan the short-job kernel serves may be left to it (bulk_takes_all); 0 = no job counts as short
+    int32_t enc_table;         // encode of a batch: 1 = the short-job launch codes every job (short_table); 0 = it codes the short ones, a workgroup per job and tile
+    int32_t enc_max_tokens;    // with enc_table: a job of more tokens cannot lie inside the stream buffer
     int32_t enc_cus;           // encode of a batch: compute units (a bulk launch has this many workgroups times its plans' enc_wgs)
     int32_t dec_short;         // decode: this launch runs the one-token-tile-per-wave variant of every plan (128-token tiles)
     int32_t dec_accumulate;    // decode of a sectioned plan: 1 = fp32 output, add the product to the output instead of storing it (a further section);
@@ -186,6 +189,17 @@ __device__ __forceinline__ BlockScan block_scan(uint32_t sum, uint32_t low, uint
         r.flags |= scratch[2 * NWAVE + w];
     }
     return r;
+}
+
+// inclusive prefix sum over the 64 lanes, on the vector unit alone
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);      // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+    return v;
 }
 
 // Builds the exclusive prefix of tiles per job in LDS (tile_start[0..n_jobs]) and returns

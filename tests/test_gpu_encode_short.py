@@ -155,3 +155,56 @@ def test_batches_with_jobs_on_both_sides_of_the_limit(form, dtype):
             if ok[j]:
                 got = out[at[j]:at[j] + n * plans[w].record_bytes].view(n, plans[w].record_bytes)
                 assert torch.equal(got, single[w][row0[j]:row0[j] + n]), (j, w, n)
+
+
+@pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
+@pytest.mark.parametrize("ranks", [(64, 192, 240), (192, 544)])
+@pytest.mark.parametrize("form", ["batch", "static"])
+def test_small_batches_are_coded_by_one_launch(form, ranks, dtype):
+    """A stream buffer that can hold only a few tiles of records sends the whole batch to the short-job kernel, a larger one sends the
+    same jobs through the bulk kernels: the same bytes and the same status, for jobs of one to many tiles, empty, not valid and beyond
+    the buffer, in lists of less and more than a wave's lanes, up to the most that one round takes."""
+    plans = [_gpu_plan(_variant_plan(r)) for r in ranks]
+    batch, p = kv.Batch(plans), 1024
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tdt = torch.bfloat16 if dtype == kv.KVTC_BF16 else torch.float32
+    rows = 64 * cus
+    x = torch.randn((rows, p), generator=torch.Generator(device=DEV).manual_seed(9), device=DEV).to(tdt)
+    rng = np.random.default_rng(len(ranks))
+    k = len(plans)
+    lists = [[(0, 1)], [(k - 1, 64 * cus // 4)], [(j % k, 16) for j in range(64)], [(j % k, int(rng.integers(0, 130))) for j in range(65)],
+             [(j % k, int(n)) for j, n in enumerate(rng.integers(0, 40, size=190))],
+             [(0, 65), (7, 40), (1, -3), (-1, 200), (1, 700), (0, 0), (1, 64)]]
+    for jobs in lists:
+        n_jobs = len(jobs)
+        which, lens = [w for w, _ in jobs], [n for _, n in jobs]
+        row0 = [(101 * j) % max(1, rows - n + 1) if n > 0 else 0 for j, n in enumerate(lens)]
+        dev = torch.from_numpy(kv.make_jobs(which, lens, row0).view(np.uint8)).to(DEV)
+        ok = [0 <= w < k and n >= 0 for w, n in jobs]
+        size = sum(n * plans[w].record_bytes for (w, n), v in zip(jobs, ok) if v)
+        for short_by in (0, 4):                                  # the last job that codes anything does not fit
+            got = []
+            for room in (0, 16 << 20):
+                out = torch.full((size + room + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+                offs = torch.zeros(n_jobs + 1, dtype=torch.int64, device=DEV)
+                status = torch.zeros(1, dtype=torch.int32, device=DEV)
+                cap = size + room
+                if form == "batch":
+                    kv.kvtc_offsets(batch.handle, dev, n_jobs, offs)
+                    if short_by:
+                        last = max(j for j in range(n_jobs) if ok[j] and lens[j] > 0)
+                        offs[last] = cap - lens[last] * plans[which[last]].record_bytes + short_by
+                    kv.kvtc_encode_batch(batch.handle, dev, n_jobs, x, dtype, p, offs, out, cap, status)
+                else:
+                    kv.kvtc_encode_batch_static([q.handle for q in plans], dev, n_jobs, x, dtype, p, out, cap - short_by if room == 0 else cap, offs, status)
+                torch.cuda.synchronize()
+                assert bool((out[cap:] == 0xA5).all())
+                got.append((out, int(status.item())))
+            (a, sa), (b, sb) = got
+            if short_by == 0:
+                assert torch.equal(a[:size], b[:size]) and sa == sb == (0 if all(ok) else 1 + ok.index(False)), (jobs[:8], sa, sb)
+            else:
+                last = max(j for j in range(n_jobs) if ok[j] and lens[j] > 0)
+                n = lens[last] * plans[which[last]].record_bytes
+                bad = min([last] + [j for j in range(n_jobs) if not ok[j]])
+                assert sa == 1 + bad and torch.equal(a[:size - n], b[:size - n]) and bool((a[size - n:] == 0xA5).all()), (jobs[:8], sa)
