@@ -61,7 +61,7 @@ struct kvtc_batch {
     int n_plans;
     // the kernel variants the plans use (a launch per variant), with the LDS maxima over each one's plans
     struct EncVariant { int key, wgs, lds[2]; };        // workgroups per compute unit; lds per element dtype
-    struct DecVariant { int key, wgs, rec, ring; };     // workgroups per compute unit; record image, basis ring (the widest among the class's plans)
+    struct DecVariant { int key, wgs, rec, ring, rec_dwords; };     // workgroups per compute unit; record image, basis ring, record (the widest among the class's plans)
     std::vector<EncVariant> enc;
     struct ShortVariant { int waves, lds[2]; } enc_short[3];     // short-job kernels by coordinate tiles per wave; waves = 0: no plan uses it
     std::vector<DecVariant> dec;
@@ -687,10 +687,11 @@ kvtc_status kvtc_batch_create(kvtc_batch** out, const kvtc_plan* const* plans, i
             for (auto& e : b->dec)
                 if (e.key == key) v = &e;
             if (!v) {
-                b->dec.push_back({key, ph.dec_wgs, 0, 0});
+                b->dec.push_back({key, ph.dec_wgs, 0, 0, 0});
                 v = &b->dec.back();
             }
             if (ph.dec_rec_lds > v->rec) v->rec = ph.dec_rec_lds;
+            if (ph.rec_dwords > v->rec_dwords) v->rec_dwords = ph.rec_dwords;
             if (ph.dec_ring_lds > v->ring) v->ring = ph.dec_ring_lds;
         }
         if (ph.p > b->max_p) b->max_p = ph.p;
@@ -1014,9 +1015,15 @@ kvtc_status kvtc_decode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.cap = in_bytes;
     a.status = status_dev;
     for (const auto& v : batch->dec) {
-        const DecLayout lay = decode_layout(v.rec, v.ring, v.wgs);
+        // Jobs whose 128-token tiles can be shown to run all at once (the stream buffer's size bounds their tokens, and each may end in a
+        // part of a tile) take the variant with one token tile per wave, as a single tensor does.  (One head of 4096 tokens in
+        // fp32: the pair of calls 20.6 us on 256-token tiles, 18.6 so.)
+        const int slots = compute_units() * v.wgs;
+        const bool wide = v.key % 100 > 10;
+        a.dec_short = !wide && in_bytes / ((size_t)batch->min_rec_dwords * 4 * kDecShortTile) + (size_t)n_jobs <= (size_t)slots;
+        const DecLayout lay = decode_layout(a.dec_short ? decode_rec_bytes(1, v.rec_dwords) : v.rec, v.ring, v.wgs);
         a.dec_ring_off = lay.ring_off;
-        hipError_t e = launch_decode(a, dtype, v.key, compute_units() * v.wgs, lay.lds_bytes, static_cast<hipStream_t>(stream));
+        hipError_t e = launch_decode(a, dtype, a.dec_short ? 100 + v.key % 100 : v.key, slots, lay.lds_bytes, static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(KVTC_E_HIP, "kvtc_decode_batch: launch failed: %s", hipGetErrorString(e));
     }
     return KVTC_OK;
