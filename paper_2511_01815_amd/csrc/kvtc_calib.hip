@@ -15,6 +15,7 @@
 // decorrelation", eq. 2: mean and SVD of the centred matrix; its right singular vectors are the
 // eigenvectors of the centred second-moment matrix, which the caller forms and decomposes on the host).
 #include <hip/hip_runtime.h>
+#include <type_traits>
 
 #include "kvtc_dev.h"
 #include "kvtc_numeric.h"
@@ -171,111 +172,159 @@ __global__ void __launch_bounds__(kCalibThreads) calib_block_errors_kernel(const
 // of each 32-feature strip, so that a lane's operands for both are one dword (bf16) of its token's row and a wave reads
 // 64 contiguous bytes of four tokens.  Operands go straight from memory to registers, kGramAhead groups of four tokens
 // ahead of their use; strips are re-read from L2.  A diagonal tile also sums its own operands: the first moment.
-// Bound by the fp64 matrix rate: 8192 tokens x 1024 features are 8.9 GFLOP = 0.11 ms at 78 TFLOP/s, and 528 tiles on
-// 256 compute units end as three.  Measured: 1.24 ms with vector fp64 from LDS over the whole matrix, plus 2.03 ms for a
-// separate pass of sums; 0.25 ms for both this way.
+// Bound by the fp64 matrix rate -- 8192 tokens x 1024 features are 8.9 GFLOP = 0.11 ms at 78 TFLOP/s -- behind which hides no vector
+// instruction: every one counts, so addresses are scalar and a whole group's loads carry no mask.  Tiles that
+// do not fill another round of the compute units are split, by the parity of their features, in halves or quarters where those still fit
+// one to a compute unit: 528 tiles on 256 of them end as two rounds and a quarter, not three.
+// Measured: 1.24 ms with vector fp64 from LDS over the whole matrix, plus 2.03 ms for a separate pass of sums; both
+// together 0.25 ms with whole tiles and masked loads, 0.20 with the last tiles split, 0.167 without masks and without the
+// diagonal's sums in every tile (300 tiles: 171, 127, 103 us; 10 tiles: 77, 53, 38).
 constexpr int kGramStrip = 32;
 constexpr int kGramWaves = 4;
 constexpr int kGramAhead = 8;
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-struct GramPair { double even, odd; };
 struct __attribute__((packed, aligned(8))) Doubles2 { double x, y; };       // two entries of the matrix: it is 8-byte aligned, no more
-__device__ __forceinline__ GramPair gram_pair(uint32_t v) { return {(double)bits_f32(v << 16), (double)bits_f32(v & 0xffff0000u)}; }
-__device__ __forceinline__ GramPair gram_pair(float2 v) { return {(double)v.x, (double)v.y}; }
+__device__ __forceinline__ double gram_value(uint32_t v, int odd) { return (double)bits_f32(odd ? v & 0xffff0000u : v << 16); }
+__device__ __forceinline__ double gram_value(f32x2 v, int odd) { return (double)v[odd]; }
 template <typename XT> struct GramVec { using type = uint32_t; };
-template <> struct GramVec<float> { using type = float2; };
+template <> struct GramVec<float> { using type = f32x2; };
 
 // element offset of feature f inside a token (blocks of 2^blk_log2 features lie blk_jump elements apart; 0 = contiguous)
 __device__ __forceinline__ int64_t feature_offset(int f, int blk_log2, int64_t blk_jump) {
     return (int64_t)f + (blk_log2 ? (int64_t)(f >> blk_log2) * blk_jump : (int64_t)0);
 }
 
-template <typename XT>
-__global__ void __launch_bounds__(64 * kGramWaves, 3) calib_gram_kernel(const XT* x, int64_t n_tokens, int p, int64_t ld, int blk_log2, int64_t blk_jump,
-                                                                     double* sum, double* gram) {
+// Features of parity a0 .. a0 + MA - 1 of strip bi against parity b0 .. b0 + MB - 1 of strip bj.
+template <typename XT, int MA, int MB>
+__device__ __forceinline__ void gram_tile(const XT* x, int64_t n_tokens, int p, int64_t ld, int blk_log2, int64_t blk_jump, int tile, int a0, int b0,
+                                          double (*red)[18][64], double* sum, double* gram) {
     using V = typename GramVec<XT>::type;
-    __shared__ double red[kGramWaves][18][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, k = lane >> 4;
     // tile number -> (bi <= bj): column bj of the triangle starts at bj (bj + 1) / 2
-    const int tile = blockIdx.x;
     int bj = (int)((__builtin_sqrtf(8.0f * (float)tile + 1.0f) - 1.0f) * 0.5f);
     while ((int64_t)bj * (bj + 1) / 2 > tile) --bj;
     while ((int64_t)(bj + 1) * (bj + 2) / 2 <= tile) ++bj;
     const int bi = tile - (int)((int64_t)bj * (bj + 1) / 2);
     const bool diag = bi == bj;
-    const XT* xa = x + feature_offset(bi * kGramStrip + 2 * l16, blk_log2, blk_jump);
-    const XT* xb = x + feature_offset(bj * kGramStrip + 2 * l16, blk_log2, blk_jump);
+    // a strip lies inside one block of the layout: its offset is the same for all lanes, and a lane's own is below 2^26 bytes
+    typedef const char __attribute__((address_space(1))) * global_ptr;
+    typedef const V __attribute__((address_space(1))) * global_v;
+    const uint64_t xa = (uint64_t)uniform_ptr(x + feature_offset(bi * kGramStrip, blk_log2, blk_jump));
+    const uint64_t xb = (uint64_t)uniform_ptr(x + feature_offset(bj * kGramStrip, blk_log2, blk_jump));
+    const uint32_t own = (uint32_t)(k * (int)ld + 2 * l16) * (uint32_t)sizeof(XT);
     const int64_t quarter = (n_tokens + 4 * kGramWaves - 1) / (4 * kGramWaves) * 4;          // whole groups of four tokens
-    const int64_t t_begin = wave * quarter, t_end = t_begin + quarter < n_tokens ? t_begin + quarter : n_tokens;
+    const int64_t first = __builtin_amdgcn_readfirstlane(wave) * quarter;
+    const int64_t left = n_tokens - first < quarter ? n_tokens - first : quarter;
+    const int n_groups = left > 0 ? (int)(left / 4) : 0, n_blocks = n_groups / kGramAhead;
 
-    f64x4 acc[2][2];
+    f64x4 acc[MA][MB];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < MA; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-    double s_even = 0.0, s_odd = 0.0;
+        for (int b = 0; b < MB; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    double s[MA];
+#pragma unroll
+    for (int a = 0; a < MA; ++a) s[a] = 0.0;
     V va[kGramAhead], vb[kGramAhead];
-    auto fetch = [&](int64_t t0, int u) {                        // tokens past the end read as zeros
-        const int64_t t = t0 + 4 * u + k;
-        va[u] = V{};
-        vb[u] = V{};
-        if (t < t_end) {
-            va[u] = *reinterpret_cast<const V*>(xa + t * ld);
-            vb[u] = *reinterpret_cast<const V*>(xb + t * ld);
+    auto fetch = [&](int g, int u) {                             // whole group g; behind the last one the last one again
+        const uint64_t at = (uint64_t)(first + 4 * (int64_t)(g < n_groups ? g : n_groups - 1)) * (uint64_t)(ld * (int64_t)sizeof(XT));      // scalar addresses
+        va[u] = *(global_v)((global_ptr)(xa + at) + own);
+        vb[u] = *(global_v)((global_ptr)(xb + at) + own);
+    };
+    auto step = [&](const V& a_in, const V& b_in, auto diag_tag) {
+        double da[MA], db[MB];
+#pragma unroll
+        for (int a = 0; a < MA; ++a) da[a] = gram_value(a_in, a0 + a);
+#pragma unroll
+        for (int b = 0; b < MB; ++b) db[b] = gram_value(b_in, b0 + b);
+#pragma unroll
+        for (int a = 0; a < MA; ++a)
+#pragma unroll
+            for (int b = 0; b < MB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(da[a], db[b], acc[a][b], 0, 0, 0);
+        if constexpr (decltype(diag_tag)::value) {
+#pragma unroll
+            for (int a = 0; a < MA; ++a) s[a] += da[a];
         }
     };
+    // a copy of the sweep for the diagonal: as a choice per step the sums were computed in every tile and dropped
+    auto sweep = [&](auto diag_tag) {
+        if (n_groups > 0) {
 #pragma unroll
-    for (int u = 0; u < kGramAhead; ++u) fetch(t_begin, u);
-    for (int64_t t0 = t_begin; t0 < t_end; t0 += 4 * kGramAhead) {
+            for (int u = 0; u < kGramAhead; ++u) fetch(u, u);
+            for (int b = 0; b < n_blocks; ++b) {
 #pragma unroll
-        for (int u = 0; u < kGramAhead; ++u) {
-            const GramPair a = gram_pair(va[u]), b = gram_pair(vb[u]);
-            fetch(t0 + 4 * kGramAhead, u);
-            acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.even, b.even, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.even, b.odd, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.odd, b.even, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.odd, b.odd, acc[1][1], 0, 0, 0);
-            if (diag) {
-                s_even += a.even;
-                s_odd += a.odd;
+                for (int u = 0; u < kGramAhead; ++u) {
+                    const V a_in = va[u], b_in = vb[u];
+                    step(a_in, b_in, diag_tag);
+                    fetch((b + 1) * kGramAhead + u, u);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
+#pragma unroll
+            for (int u = 0; u < kGramAhead; ++u)
+                if (u < n_groups - n_blocks * kGramAhead) step(va[u], vb[u], diag_tag);
         }
-    }
+        if (left > 4 * (int64_t)n_groups) {                      // one to three tokens: the rest of the group reads as zeros
+            V a_in = V{}, b_in = V{};
+            if (4 * n_groups + k < left) {
+                const uint64_t at = (uint64_t)(first + 4 * (int64_t)n_groups) * (uint64_t)(ld * (int64_t)sizeof(XT));
+                a_in = *(global_v)((global_ptr)(xa + at) + own);
+                b_in = *(global_v)((global_ptr)(xb + at) + own);
+            }
+            step(a_in, b_in, diag_tag);
+        }
+    };
+    if (diag) sweep(std::true_type()); else sweep(std::false_type());
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < MA; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < MB; ++b)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) red[wave][(a * 2 + b) * 4 + r][lane] = acc[a][b][r];
-    red[wave][16][lane] = s_even;
-    red[wave][17][lane] = s_odd;
+            for (int r = 0; r < 4; ++r) red[wave][(a * MB + b) * 4 + r][lane] = acc[a][b][r];
+#pragma unroll
+    for (int a = 0; a < MA; ++a) red[wave][16 + a][lane] = s[a];
     __syncthreads();
     auto total = [&](int v, int l) {
-        double s = red[0][v][l];
+        double t = red[0][v][l];
 #pragma unroll
-        for (int w = 1; w < kGramWaves; ++w) s += red[w][v][l];
-        return s;
+        for (int w = 1; w < kGramWaves; ++w) t += red[w][v][l];
+        return t;
     };
     // wave r stores accumulator register r: rows 4 r + lane / 16 of the 16 x 16 results, columns lane % 16
     static_assert(kGramWaves == 4, "a wave per accumulator register");
     const int r = wave;
-    double m[2][2];
+    double m[MA][MB];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < MA; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) m[a][b] = total((a * 2 + b) * 4 + r, lane);
-    const int i = bi * kGramStrip + 2 * (4 * r + k), j = bj * kGramStrip + 2 * l16;
+        for (int b = 0; b < MB; ++b) m[a][b] = total((a * MB + b) * 4 + r, lane);
+    const int i = bi * kGramStrip + 2 * (4 * r + k) + a0, j = bj * kGramStrip + 2 * l16 + b0;
+    auto put = [&](double* to, double u, double v, int n) {      // n neighbours
+        if (n == 2) *reinterpret_cast<Doubles2*>(to) = Doubles2{u, v};
+        else *to = u;
+    };
 #pragma unroll
-    for (int a = 0; a < 2; ++a) *reinterpret_cast<Doubles2*>(gram + (size_t)(i + a) * p + j) = Doubles2{m[a][0], m[a][1]};
+    for (int a = 0; a < MA; ++a) put(gram + (size_t)(i + a) * p + j, m[a][0], m[a][MB - 1], MB);
     if (!diag) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) *reinterpret_cast<Doubles2*>(gram + (size_t)(j + b) * p + i) = Doubles2{m[0][b], m[1][b]};
-    } else if (tid < 32) {                                       // lane l16 + 16 k holds the tokens 4 g + k of feature pair l16
-        const int v = 16 + (tid & 1), l = tid >> 1;
-        sum[bi * kGramStrip + tid] = ((total(v, l) + total(v, l + 16)) + total(v, l + 32)) + total(v, l + 48);
+        for (int b = 0; b < MB; ++b) put(gram + (size_t)(j + b) * p + i, m[0][b], m[MA - 1][b], MA);
+    } else if (a0 >= b0 && a0 < b0 + MB && tid < 16 * MA) {      // (one of the parts that see these features) lane l16 + 16 k holds the tokens 4 g + k of feature pair l16
+        const int v = 16 + tid % MA, l = tid / MA;
+        sum[bi * kGramStrip + 2 * l + a0 + tid % MA] = ((total(v, l) + total(v, l + 16)) + total(v, l + 32)) + total(v, l + 48);
     }
+}
+
+template <typename XT>
+__global__ void __launch_bounds__(64 * kGramWaves, 3) calib_gram_kernel(const XT* x, int64_t n_tokens, int p, int64_t ld, int blk_log2, int64_t blk_jump,
+                                                                     int n_whole, int split, double* sum, double* gram) {
+    __shared__ double red[kGramWaves][18][64];
+    const int b = (int)blockIdx.x - n_whole;
+    if (b < 0) gram_tile<XT, 2, 2>(x, n_tokens, p, ld, blk_log2, blk_jump, (int)blockIdx.x, 0, 0, red, sum, gram);
+    else if (split == 2) gram_tile<XT, 2, 1>(x, n_tokens, p, ld, blk_log2, blk_jump, n_whole + b / 2, 0, b % 2, red, sum, gram);
+    else gram_tile<XT, 1, 1>(x, n_tokens, p, ld, blk_log2, blk_jump, n_whole + b / 4, b / 2 % 2, b % 2, red, sum, gram);
 }
 
 }  // namespace
@@ -284,12 +333,14 @@ namespace kvtc {
 // x: n_tokens tokens of p features (p a multiple of 64) at the given layout; sum [p], gram [p][p]
 hipError_t launch_calib_moments(const void* x, kvtc_dtype dtype, int64_t n_tokens, int p, int64_t ld, int blk_log2, int64_t blk_jump,
                                 double* sum, double* gram, hipStream_t stream) {
-    const unsigned strips = (unsigned)(p / kGramStrip);
-    const dim3 grid(strips * (strips + 1) / 2), threads(64 * kGramWaves);
+    const int64_t strips = p / kGramStrip, tiles = strips * (strips + 1) / 2, cus = compute_units(), rest = tiles % cus;
+    const int split = rest * 4 <= cus ? 4 : (rest * 2 <= cus ? 2 : 1);
+    const int64_t whole = split == 1 ? tiles : tiles - rest;
+    const dim3 grid((unsigned)(whole + (tiles - whole) * split)), threads(64 * kGramWaves);
     if (dtype == KVTC_BF16)
-        hipLaunchKernelGGL(calib_gram_kernel<uint16_t>, grid, threads, 0, stream, static_cast<const uint16_t*>(x), n_tokens, p, ld, blk_log2, blk_jump, sum, gram);
+        hipLaunchKernelGGL(calib_gram_kernel<uint16_t>, grid, threads, 0, stream, static_cast<const uint16_t*>(x), n_tokens, p, ld, blk_log2, blk_jump, (int)whole, split, sum, gram);
     else
-        hipLaunchKernelGGL(calib_gram_kernel<float>, grid, threads, 0, stream, static_cast<const float*>(x), n_tokens, p, ld, blk_log2, blk_jump, sum, gram);
+        hipLaunchKernelGGL(calib_gram_kernel<float>, grid, threads, 0, stream, static_cast<const float*>(x), n_tokens, p, ld, blk_log2, blk_jump, (int)whole, split, sum, gram);
     return hipGetLastError();
 }
 }  // namespace kvtc
