@@ -53,18 +53,33 @@ template <int L, typename F> __device__ __forceinline__ float group_reduce(float
     return v;
 }
 
-// This thread's part of sum (d - d_hat)^2 - d^2 = d_hat (d_hat - 2 d) over its tokens, at one width.  L lanes own a
+// min and max of a lane's next two values.  (The instructions themselves: of a value that comes from memory the compiler first makes a quiet NaN if it is
+// a signalling one, an instruction per value that changes nothing here -- either makes the block's error not a number.)
+__device__ __forceinline__ void min_max_of(float a, float b, float& lo, float& hi) {
+    asm("v_min3_f32 %0, %1, %2, %0" : "+v"(lo) : "v"(a), "v"(b));
+    asm("v_max3_f32 %0, %1, %2, %0" : "+v"(hi) : "v"(a), "v"(b));
+}
+
+// This thread's part of sum (d - d_hat)^2 - d^2 = d_hat (d_hat - 2 d) over its tokens, at W widths from `bits` on.  L lanes own a
 // token, PER coordinates each (n <= L * PER; FULL: n == L * PER).  kCalibTok tokens at a time, so that the header --
 // two directed fp16 roundings and two correctly rounded divides, as many instructions as eight codes -- is worked out
-// once per token by one lane of four and handed round, and not by all lanes that share the token.
+// once per token and width by one lane of four and handed round, and not by all lanes that share the token.
 // d_hat = shift + code * scale is exact in double: all its terms are multiples of 2^-24 below 2^26.
-template <int L, int PER, bool FULL>
-__device__ __forceinline__ double block_error(const float* coef, int64_t t_begin, int64_t n_tokens, int64_t ld, int start, int n, int bits) {
+// The code is rounded by adding 2^23 (to nearest even, as code_of does it: the sum's last place is 1), clamped there, and its bits are the low
+// half of the double 2^52 + 0x4b000000 + code: a subtraction in place of a conversion, which takes twice as long.
+template <int L, int PER, bool FULL, int W>
+__device__ __forceinline__ void block_error(const float* coef, int64_t t_begin, int64_t n_tokens, int64_t ld, int start, int n, int bits, double (&e)[W]) {
+#pragma clang fp contract(off)               // (a product is rounded before the 2^23 is added)
     constexpr int GRP = kCalibThreads / L, STEP = GRP * kCalibTok;
+    constexpr float kMagic = 8388608.0f;
+    const double kMagicD = __builtin_bit_cast(double, 0x433000004b000000ull);
     const int tid = threadIdx.x, grp = tid / L, gl = tid % L, lane = tid & 63, mine = lane & 3;
-    const float qmax = (float)((1u << bits) - 1u);
+    float top[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) top[w] = kMagic + (float)((1u << (bits + w)) - 1u);
     auto coord = [&](int k) { return (k >> 2) * 4 * L + 4 * gl + (k & 3); };         // four neighbours at a time: 16-byte loads
-    double e = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) e[w] = 0.0;
     for (int64_t s0 = t_begin; s0 < n_tokens; s0 += STEP) {          // every lane runs the same trips
         const int64_t t0 = s0 + grp * kCalibTok;
         float d[kCalibTok][PER];
@@ -74,45 +89,72 @@ __device__ __forceinline__ double block_error(const float* coef, int64_t t_begin
             const float* row = coef + (t0 + s < n_tokens ? t0 + s : n_tokens - 1) * ld + start;
             float l = __builtin_inff(), h = -__builtin_inff();
 #pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                const int j = coord(k);
-                const bool in = FULL || j < n;
-                d[s][k] = in ? row[j] : 0.0f;
-                l = fminf(l, in ? d[s][k] : l);
-                h = fmaxf(h, in ? d[s][k] : h);
+            for (int k = 0; k < PER; ++k) d[s][k] = FULL || coord(k) < n ? row[coord(k)] : 0.0f;
+#pragma unroll
+            for (int k = 0; k < PER; k += 2) {
+                if (FULL) {
+                    min_max_of(d[s][k], d[s][k + 1], l, h);
+                } else {
+                    const bool in0 = coord(k) < n, in1 = coord(k + 1) < n;
+                    min_max_of(in0 ? d[s][k] : __builtin_nanf(""), in1 ? d[s][k + 1] : __builtin_nanf(""), l, h);      // (passed over)
+                }
             }
             l = group_reduce<L>(l, [](float a, float b) { return fminf(a, b); });
             h = group_reduce<L>(h, [](float a, float b) { return fmaxf(a, b); });
             if (mine == s) { lo = l; hi = h; }
         }
-        const GroupQ q = group_header(lo, hi, bits);
-        // an infinite coefficient makes error and energy infinite and their difference not a number, where the form above would
-        // give -inf, the best value a minimising allocation can see (the subtraction in double: a finite range stays finite)
-        e = __builtin_fma((double)hi - (double)lo, 0.0, e);
+        // a token behind the last one counts nothing: without shift and scale its d_hat is zero
+        const bool counts = t0 + mine < n_tokens;
+        GroupQ q[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            q[w] = group_header(lo, hi, bits + w);
+            q[w].shift = counts ? q[w].shift : 0.0f;
+            q[w].scale16 = counts ? q[w].scale16 : (uint16_t)0;
+            // an infinite coefficient makes error and energy infinite and their difference not a number, where the form above would
+            // give -inf, the best value a minimising allocation can see (the subtraction in double: a finite range stays finite)
+            e[w] = __builtin_fma((double)hi - (double)lo, 0.0, e[w]);
+        }
 #pragma unroll
         for (int s = 0; s < kCalibTok; ++s) {
             const int from = (lane & ~3) | s;
-            const float shift = __shfl(q.shift, from, 64), inv = __shfl(q.inv, from, 64);
-            const double sh = (double)shift, sc = (double)f16_bits_to_f32((uint16_t)__shfl((int)q.scale16, from, 64));
-            const bool live = t0 + s < n_tokens;
+            const float shift = __shfl(q[0].shift, from, 64);
+            const double sh = (double)shift;
+            float inv[W];
+            double sc[W];
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                inv[w] = __shfl(q[w].inv, from, 64);
+                sc[w] = (double)f16_bits_to_f32((uint16_t)__shfl((int)q[w].scale16, from, 64));
+            }
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                const double dh = __builtin_fma((double)code_of(d[s][k], shift, inv, qmax), sc, sh);
-                const double term = __builtin_fma(-2.0, (double)d[s][k], dh);
-                const bool in = live && (FULL || coord(k) < n);
-                e = __builtin_fma(in ? dh : 0.0, term, e);
+                const double dd = (double)d[s][k];
+                const float over = __fsub_rn(d[s][k], shift);
+                const bool in = FULL || coord(k) < n;
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    const float q_f = over * inv[w], m = __builtin_amdgcn_fmed3f(q_f + kMagic, kMagic, top[w]);
+                    const double code = __builtin_bit_cast(double, 0x4330000000000000ull | f32_bits(m)) - kMagicD;
+                    const double dh = __builtin_fma(code, sc[w], sh);
+                    e[w] = __builtin_fma(in ? dh : 0.0, __builtin_fma(-2.0, dd, dh), e[w]);
+                }
             }
         }
     }
-    return e;
 }
 
-// Blocks of more than 256 coordinates are cut in two halves of the tokens, whose sums are ADDED to the zeroed result: with
+// Grid in z: parts 0 to 3 are the halves of the halved blocks, ahead of everything else -- a block of more than 256 coordinates has a workgroup
+// per half and width, or its workgroups would be the tail of the launch --, part 4 all others (the only part where nothing is halved).
+constexpr int kCalibParts = 5;
+// Blocks of more than 64 coordinates are cut in two halves of the tokens, whose sums are ADDED to the zeroed result: with
 // two terms on top of zero the order of arrival cannot show, so the table stays reproducible.  Not where all tokens fit one step of
 // such a block's lane groups: a half would take as long as the whole, and the launch that zeroes would be a quarter of the call
 // (one block of 16 coordinates, 50 tokens, one width: 10.7 us with it, 8.5 without).
 constexpr int kCalibHalveAbove = kCalibThreads / 64 * kCalibTok;
-__device__ __forceinline__ bool calib_long_block(const kvtc_calib_block& b) { return b.n > 256; }
+__device__ __forceinline__ bool calib_halved(const kvtc_calib_block& b, int64_t n_tokens) {
+    return b.n > 64 && n_tokens > (b.n > 256 ? kCalibHalveAbove : kCalibThreads / 16 * kCalibTok);
+}
 __device__ __forceinline__ bool calib_bad_block(const kvtc_calib_block& b, int64_t ld) {
     return b.n < 1 || b.n > kCalibMaxN || b.start < 0 || (int64_t)b.start + b.n > ld;
 }
@@ -121,46 +163,60 @@ __global__ void __launch_bounds__(256) calib_zero_kernel(double* change, int64_t
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) change[i] = 0.0;
 }
 
-// change[block][b - 1] = sum over tokens and the block's coordinates of (d - d_hat)^2 - d^2.  Grid: (block, width, part).
-// What bounds it is vector arithmetic (six fp32 and five half-rate fp64 instructions per coefficient and width) and, at the
-// end, the workgroups of the longest blocks: parts 0 and 1 are the halves of the long blocks, ahead of everything else
-// in the grid, part 2 all others (the only part where nothing is halved).  175 blocks x 8 widths x 2048 tokens (the default set at 1024 features): 4.59 ms with
+// change[block][b - 1] = sum over tokens and the block's coordinates of (d - d_hat)^2 - d^2.  Grid: (block, W widths, part).
+// What bounds it is vector arithmetic (per coefficient: six fp32 instructions and one in fp64 for both widths, four and four for each).
+// 175 blocks x 8 widths x 2048 tokens (the default set at 1024 features): 4.59 ms with
 // a workgroup of 256 threads per block that evaluated all widths and 16 or 64 lanes per token, 0.386 ms with one of 1024
-// threads per block and width (half of it for the headers), 0.208 ms with 16 coordinates per lane.
+// threads per block and width (half of it for the headers), 0.206 ms with 16 coordinates per lane, 0.165 ms with two widths to a workgroup, which
+// share the loads, the minima and maxima and the conversions, and without conversions of the codes (126 blocks at 768 features: 147 -> 97 us).
+template <int W>
 __global__ void __launch_bounds__(kCalibThreads) calib_block_errors_kernel(const float* coef, int64_t n_tokens, int64_t ld, const kvtc_calib_block* blocks,
                                                                           int max_bits, double* change) {
-    __shared__ double red[kCalibThreads];
+    __shared__ double red[W][kCalibThreads];
     const kvtc_calib_block blk = blocks[blockIdx.x];
-    const int start = blk.start, n = blk.n, bits = (int)blockIdx.y + 1, part = gridDim.z == 1 ? 2 : (int)blockIdx.z;
-    double* out = change + (size_t)blockIdx.x * max_bits + blockIdx.y;
+    const int start = blk.start, n = blk.n, bits = W * (int)blockIdx.y + 1, part = gridDim.z == 1 ? kCalibParts - 1 : (int)blockIdx.z;
+    double* out = change + (size_t)blockIdx.x * max_bits + bits - 1;
+    const int n_out = min(W, max_bits - (bits - 1));      // (an odd number of widths: the last workgroup's second one is not stored)
     // the list lives on the device, out of the host's sight: a block outside a row (or longer than a lane group holds) gets NaN
     if (calib_bad_block(blk, ld)) {
-        if (threadIdx.x == 0 && part == 2) *out = __builtin_nan("");
+        if ((int)threadIdx.x < n_out && part == kCalibParts - 1) out[threadIdx.x] = __builtin_nan("");
         return;
     }
-    const bool halved = gridDim.z != 1 && calib_long_block(blk);
-    if (halved != (part < 2)) return;
-    double e;
-    if (calib_long_block(blk)) {
-        const int64_t half = halved ? (n_tokens + 1) / 2 : n_tokens, b = part == 1 ? half : 0, m = part == 1 ? n_tokens : half;
-        e = n == 1024 ? block_error<64, 16, true>(coef, b, m, ld, start, n, bits) : block_error<64, 16, false>(coef, b, m, ld, start, n, bits);
+    const bool halved = gridDim.z != 1 && calib_halved(blk, n_tokens), alone = halved && n > 256;          // alone: one width
+    if (halved != (part < kCalibParts - 1) || (part >= 2 && halved && !alone)) return;
+    const int w0 = alone ? part / 2 : 0, w1 = alone ? w0 + 1 : n_out;      // the widths this workgroup stores
+    const int64_t half = halved ? (n_tokens + 1) / 2 : n_tokens, b = halved && part % 2 ? half : 0, m = halved && part % 2 ? n_tokens : half;
+    static_assert(W == 1 || W == 2, "the widths of a long block");
+    double e[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) e[w] = 0.0;
+    if (n > 256) {
+        for (int w = w0; w < w1; ++w) {
+            double one[1];
+            if (n == 1024) block_error<64, 16, true>(coef, b, m, ld, start, n, bits + w, one); else block_error<64, 16, false>(coef, b, m, ld, start, n, bits + w, one);
+            (w == 0 ? e[0] : e[W - 1]) = one[0];
+        }
     } else if (n <= 16) {
-        e = n == 16 ? block_error<4, 4, true>(coef, 0, n_tokens, ld, start, n, bits) : block_error<4, 4, false>(coef, 0, n_tokens, ld, start, n, bits);
+        if (n == 16) block_error<4, 4, true>(coef, b, m, ld, start, n, bits, e); else block_error<4, 4, false>(coef, b, m, ld, start, n, bits, e);
     } else if (n <= 64) {
-        e = n == 64 ? block_error<4, 16, true>(coef, 0, n_tokens, ld, start, n, bits) : block_error<4, 16, false>(coef, 0, n_tokens, ld, start, n, bits);
+        if (n == 64) block_error<4, 16, true>(coef, b, m, ld, start, n, bits, e); else block_error<4, 16, false>(coef, b, m, ld, start, n, bits, e);
     } else {
-        e = n == 256 ? block_error<16, 16, true>(coef, 0, n_tokens, ld, start, n, bits) : block_error<16, 16, false>(coef, 0, n_tokens, ld, start, n, bits);
+        if (n == 256) block_error<16, 16, true>(coef, b, m, ld, start, n, bits, e); else block_error<16, 16, false>(coef, b, m, ld, start, n, bits, e);
     }
     // fixed-order reduction over the workgroup
-    red[threadIdx.x] = e;
+#pragma unroll
+    for (int w = 0; w < W; ++w) red[w][threadIdx.x] = e[w];
     __syncthreads();
     for (int d = kCalibThreads / 2; d > 0; d >>= 1) {
-        if ((int)threadIdx.x < d) red[threadIdx.x] += red[threadIdx.x + d];
+        if ((int)threadIdx.x < d) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) red[w][threadIdx.x] += red[w][threadIdx.x + d];
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        if (halved) unsafeAtomicAdd(out, red[0]);
-        else *out = red[0];
+    if ((int)threadIdx.x >= w0 && (int)threadIdx.x < w1 && (int)threadIdx.x < n_out) {
+        if (halved) unsafeAtomicAdd(out + threadIdx.x, red[threadIdx.x][0]);
+        else out[threadIdx.x] = red[threadIdx.x][0];
     }
 }
 
@@ -360,10 +416,13 @@ kvtc_status kvtc_calib_block_errors(const float* coef_dev, int64_t n_tokens, int
     const bool halves = n_tokens > kCalibHalveAbove;
     if (halves)
         hipLaunchKernelGGL(calib_zero_kernel, dim3((unsigned)(n_out < 262144 ? (n_out + 255) / 256 : 1024)), dim3(256), 0, static_cast<hipStream_t>(stream), change_dev, n_out);
+    // two widths to a workgroup, unless the compute units take a workgroup each with one (13 blocks x 8 widths: 25 us with two, 18 with one; 30 blocks: 45 and 32)
+    const int widths = (int64_t)n_blocks * max_bits <= compute_units() ? 1 : 2;
+    void (*const fn)(const float*, int64_t, int64_t, const kvtc_calib_block*, int, double*) = widths == 1 ? &calib_block_errors_kernel<1> : &calib_block_errors_kernel<2>;
     // a launch has fewer than 2^32 threads across: beyond 2^22 - 1 blocks of 1024 threads the list takes several
     for (int64_t at = 0; at < n_blocks; at += kCalibMaxBlocks) {
         const int n = n_blocks - at < kCalibMaxBlocks ? (int)(n_blocks - at) : kCalibMaxBlocks;
-        hipLaunchKernelGGL(calib_block_errors_kernel, dim3((unsigned)n, (unsigned)max_bits, halves ? 3 : 1), dim3(kCalibThreads), 0, static_cast<hipStream_t>(stream), coef_dev, n_tokens, ld,
+        hipLaunchKernelGGL(fn, dim3((unsigned)n, (unsigned)((max_bits + widths - 1) / widths), halves ? kCalibParts : 1), dim3(kCalibThreads), 0, static_cast<hipStream_t>(stream), coef_dev, n_tokens, ld,
                            blocks_dev + at, max_bits, change_dev + at * max_bits);
     }
     const hipError_t err = hipGetLastError();
