@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "kvtc_dev.h"
@@ -36,7 +37,7 @@ struct kvtc_entropy {
     void* blob;                 // device: the four tables below
     const uint16_t* enc_dev;    // [n_tables][R][256] reversed code | length << 12
     const uint8_t* len_dev;     // [n_tables][R][256] length
-    const uint8_t* dec_dev;     // [n_tables][R][kDecRow], staged in LDS by the decoder
+    const uint8_t* dec_dev;     // the decoder's tables, one behind the other, each [n_tables][R]: lengths, symbols, offsets
     const uint32_t* lim_dev;    // [n_tables][R][4]
 };
 
@@ -60,18 +61,18 @@ static_assert(kMaxLdsRecord * kEncRow + 16 * kImageDw * 4 <= kLdsMost && (kMaxLd
 static_assert(kMaxRecord * kLenRow + 16 * kChunk * 4 <= kLdsMost, "the length table of every record size fits");
 
 // Decoding data of one byte position.  Codes are canonical: those of L bits are first[L] .. first[L] + count[L] - 1.
-// In LDS, kDecRow bytes: [256] by the next 8 bits of the string, the code's length, 9 for every code of 9 bits or more (10 .. 12 if none is
-// shorter);
+// Three tables, kDecRow bytes in all, in LDS behind the waves' rows (each from a multiple of 256 bytes on, so that an index is OR-ed in):
+// [256] by the next 8 bits of the string, the code's length, 9 for every code of 9 bits or more (10 .. 12 if none is shorter);
 // [256] symbols by rank, i.e. ordered by (length, value); [16] at L: first[L] - (number of symbols with shorter codes), modulo
 // 256, so that the rank of a code of L bits is its value minus this.  (All lanes look up the same position at a time: rows
 // need no padding.)  Records too long for one table in LDS are decoded in segments of kDecSegment bytes.
 // In scalar registers, four dwords: ((first[L] + count[L]) << (32 - L)) - 1 for L = 9, 10, 11: a string whose next 32 bits, first
 // bit on top, exceed it begins with a code of more than L bits.
-// A wave collects kDecBatch dwords of its 64 rows behind the table, at a pitch of whole 16-byte pieces.
-constexpr int kDecSym = 256, kDecOff = 512, kDecRow = 528;
+// A wave collects kDecBatch dwords of its 64 rows in front of the tables, at a pitch of whole 16-byte pieces.
+constexpr int kDecOff = 16, kDecRow = 256 + 256 + kDecOff;
 constexpr int kDecSegment = 144, kDecBatch = 16, kDecPitch = 20;
-static_assert(kDecRow % 16 == 0 && kChunk * kDecPitch % 4 == 0, "tables in 16-byte pieces");
-static_assert(kDecSegment % 16 == 0 && kDecSegment * kDecRow + 16 * kChunk * kDecPitch * 4 <= kLdsMost, "a segment's table and 16 waves' rows fit");
+static_assert(kChunk * kDecPitch * 4 % 256 == 0, "tables from a multiple of 256 bytes on");
+static_assert(kDecSegment % 16 == 0 && kDecBatch % 2 == 0 && kDecSegment * kDecRow + 16 * kChunk * kDecPitch * 4 <= kLdsMost, "a segment's table and 16 waves' rows fit");
 
 struct EntropyArgs {
     const kvtc_entropy_job* jobs;     // device, or nullptr -> `single`
@@ -382,29 +383,44 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
     }
 }
 
-// decode: one wave per chunk, a lane per token.  LDS_TAB: tables in LDS, else in global memory (jobs_wait).  Every read of the container is clamped to the job's bytes, so a damaged
-// container gives wrong bytes, never a fault.  A lane reads its own bit string straight from the container, two dwords ahead
-// of need: the strings of a chunk's tokens follow each other, so the wave's reads fall on a few lines that stay in the caches.
+// decode: one wave per chunk, a lane per token.  LDS_TAB: tables in LDS, else in global memory (jobs_wait).  Every read of the container is clamped
+// to the job's bytes, so a damaged container gives wrong bytes, never a fault.  A lane decodes eight bytes from a window of four dwords of its
+// string in registers (eight codes are at most 96 bits, behind at most 31).  The dwords that the next window may begin in, and those behind,
+// are requested when half the codes are taken, and the window is chosen from them at the end: nothing branches, and a wave waits for memory once
+// in eight bytes.  (A 64-bit buffer per lane, refilled dword by dword from four that a lane fetched when it had used them up, waited at every
+// second byte, because some lane had always just fetched.)
 // Rows are collected in LDS and stored 64 bytes at a time (stored 16 bytes at a time, straight from the lanes, a line's pieces
-// did not meet in the L2: five times the writes to memory, 0.57 ms).  No step of the walk branches but for the next four
-// dwords of the string.  256 MiB of records: 777 us with twelve comparisons per symbol, 336 now: 34 vector
-// instructions per symbol, which keep the vector units busy for 270 of them.
-// the k-th of four values, k modulo 4 (by value: a choice between variables is one between addresses, and puts them in memory)
-__device__ __forceinline__ uint32_t pick(uint32_t k, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-    const uint32_t lo = (k & 1u) ? b : a, hi = (k & 1u) ? d : c;
-    return (k & 2u) ? hi : lo;
+// did not meet in the L2: five times the writes to memory, 0.57 ms).
+// 256 MiB of records: 777 us with twelve comparisons per symbol, 326 with three and the buffer, 290 now.  Vector instructions: 21 per symbol (34 with the buffer), half of the cycles; the lanes'
+// 24-byte reads come from the L2, a line as often as it is read, because 16 waves' strings do not fit the L1.
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));       // on any dword boundary
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+// a byte of a table, at a byte offset that is a multiple of 256 or-ed with an index, plus a constant
+template <bool LDS_TAB> __device__ __forceinline__ uint32_t table_byte(const uint8_t* base, uint32_t off, int constant) {
+    if constexpr (LDS_TAB) {
+        typedef const uint8_t __attribute__((address_space(3))) * lds_ptr;
+        return ((lds_ptr)off)[constant];
+    } else {
+        return base[off + constant];
+    }
 }
 template <bool LDS_TAB>
 __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
     const int R = a.R;
     const JobView v = job_view(a, blockIdx.y);
     const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
     if (!v.ok || first >= v.n_chunks) return;
     uint32_t* out = lds + wave * (kChunk * kDecPitch);
     uint32_t* tab32 = lds + n_waves * (kChunk * kDecPitch);
-    const uint8_t* tab = LDS_TAB ? reinterpret_cast<const uint8_t*>(tab32) : a.dec + v.table * kDecRow;
+    const size_t rows = (size_t)a.n_tables * R;
+    const uint8_t* g_len = a.dec + v.table * 256;
+    const uint8_t* g_sym = a.dec + (rows + v.table) * 256;
+    const uint8_t* g_off = a.dec + rows * 512 + v.table * kDecOff;
+    // tables at `tab` in LDS, else at g_..: byte offsets of a segment's first row
+    const uint32_t seg = (uint32_t)(R < kDecSegment ? R : kDecSegment), tab = LDS_TAB ? lds_offset(tab32) : 0u;
+    const uint32_t tab_sym = LDS_TAB ? tab + seg * 256u : 0u, tab_off = LDS_TAB ? tab + seg * 512u : 0u;
     // the limits of four positions at a time, through the scalar unit (constant while the kernel runs)
     typedef const u32x16 __attribute__((address_space(4))) const_u32x16;
     const const_u32x16* lim = (const const_u32x16*)(uintptr_t)uniform_ptr(a.lim + v.table * 4);
@@ -412,95 +428,161 @@ __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs 
     for (int c = 0; c < a.chunks_per_wave; ++c) {              // the same number of rounds in every wave: there are barriers inside
         const int64_t chunk = first + (int64_t)c * n_waves + wave;
         const bool live = chunk < v.n_chunks;
-        uint32_t n_dw = 0, pos = 0;
-        const uint32_t* src = nullptr;
-        const int64_t t = chunk * kChunk + lane;
+        int last = 0;                                          // the last dword of the payload, from the chunk's string on, with five behind it
+        uint32_t pos = 0;                                      // the lane's next bit, from there
+        uint64_t src = 0;                                      // the chunk's string, less the six dwords
         if (live) {
-            uint64_t begin = v.chunk_off[chunk], end = v.chunk_off[chunk + 1];
-            begin = begin < v.payload_cap ? begin : v.payload_cap;
-            end = end < begin ? begin : (end < v.payload_cap ? end : v.payload_cap);
-            n_dw = (uint32_t)((end - begin) / 4u);
-            src = reinterpret_cast<const uint32_t*>(v.payload + (begin & ~3ull));
-            const uint32_t own = v.len_bits[t];
+            uint64_t begin = (uint32_t)__builtin_amdgcn_readfirstlane(v.chunk_off[chunk]);
+            begin = (begin < v.payload_cap ? begin : v.payload_cap) & ~3ull;
+            const uint64_t left = (v.payload_cap - begin) / 4u;
+            last = (int)(left < 0x7fffffffull ? left : 0x7fffffffull) - 6;       // (of a shorter payload: in the directory in front of it)
+            src = (uint64_t)uniform_ptr(v.payload + begin) - 24u;
+            const uint32_t own = v.len_bits[chunk * kChunk + lane];
             pos = wave_inclusive_scan(own) - own;
         }
-        const bool mine = live && t < v.T;
-        // the string four dwords at a time, from dword i on or, near its end, the last four (in front of a shorter string lies
-        // the container's directory); what is taken from behind its end is stray, and no code reads it
-        uint32_t at = 0u, h0 = 0u, h1 = 0u, h2 = 0u, h3 = 0u;  // first of the four dwords at hand; the dwords
-        auto fetch = [&](uint32_t i) {
-            at = (uint32_t)min((int)i, (int)n_dw - 4);
-            const Dwords4 v4 = *reinterpret_cast<const Dwords4*>(src + (int)at);
-            h0 = v4.w[0]; h1 = v4.w[1]; h2 = v4.w[2]; h3 = v4.w[3];
+        // (lanes behind the last token run along: they read inside the payload, as all do, and their rows are not stored)
+        uint32_t w0 = 0u, w1 = 0u, w2 = 0u, w3 = 0u;           // the window: dwords pos / 32 and the three behind it
+        uint32_t g0 = 0u, g1 = 0u, g2 = 0u, g3 = 0u, g4 = 0u, g5 = 0u;
+        int at = 0;                                            // dword of g0
+        auto request = [&]() {
+            at = min((int)(pos >> 5), last);
+            typedef const char __attribute__((address_space(1))) * global_ptr;
+            const global_ptr from = (global_ptr)src + (uint32_t)(at + 6) * 4u;
+            const u32x4_any lo = *reinterpret_cast<const u32x4_any __attribute__((address_space(1)))*>(from);
+            const u32x2_any hi = *reinterpret_cast<const u32x2_any __attribute__((address_space(1)))*>(from + 16);
+            g0 = lo[0]; g1 = lo[1]; g2 = lo[2]; g3 = lo[3]; g4 = hi[0]; g5 = hi[1];
         };
-        auto word = [&](uint32_t k) { return pick(k, h0, h1, h2, h3); };
-        // the next bits of the string in a register; at least 24 of them whenever two codes are taken
-        uint64_t buf = 0;
-        uint32_t nbuf = 64u - (pos & 31u);
-        uint32_t idx = pos >> 5;                               // next dword of the string
-        if (mine) {
-            fetch(idx);
-            const uint32_t lo = word(idx - at);
-            if (idx - at == 3u) fetch(idx + 1u);
-            const uint32_t hi = word(idx + 1u - at);
-            buf = (((uint64_t)hi << 32) | lo) >> (pos & 31u);
-            idx += 2u;
-            if (idx - at > 3u) fetch(idx);
-        }
-        // the four bytes of dword d (its table rows at byte `row` of the LDS)
-        auto four = [&](uint32_t row, const u32x16& L) {
-            uint32_t rev[4], len[4], w = 0u;
+        auto choose = [&]() {                                  // (what lies behind the payload's end is stray, and no code reads it)
+            int d = (int)(pos >> 5) - at;                      // 0 .. 2, but near the payload's end
+            while (__builtin_expect(__any(d > 2), 0)) {
+                const bool on = d > 2;
+                g0 = on ? g1 : g0;
+                g1 = on ? g2 : g1;
+                g2 = on ? g3 : g2;
+                g3 = on ? g4 : g3;
+                g4 = on ? g5 : g4;
+                d -= on ? (d > 8 ? d - 2 : 1) : 0;              // far behind the end everything is stray
+            }
+            const bool one = d == 1, two = d == 2;
+            w0 = two ? g2 : (one ? g1 : g0);
+            w1 = two ? g3 : (one ? g2 : g1);
+            w2 = two ? g4 : (one ? g3 : g2);
+            w3 = two ? g5 : (one ? g4 : g3);
+        };
+        // the codes of the four bytes of a dword whose rows of the length table begin here: reversed bits and lengths
+        auto lengths = [&](uint32_t t_len, const u32x16& L, uint32_t (&rev)[4], uint32_t (&len)[4]) {
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                if ((b & 1) == 0) {
-                    const bool need = nbuf <= 32u;
-                    const uint32_t k = idx - at;
-                    buf |= (uint64_t)(need ? word(k) : 0u) << (nbuf & 63u);
-                    if (need && k >= 3u) fetch(idx + 1u);
-                    nbuf += need ? 32u : 0u;
-                    idx += need ? 1u : 0u;
+            for (int pair = 0; pair < 2; ++pair) {
+                uint32_t view = __builtin_amdgcn_alignbit(w1, w0, pos);          // the next 32 bits
+#pragma unroll
+                for (int b = 2 * pair; b < 2 * pair + 2; ++b) {
+                    rev[b] = __builtin_bitreverse32(view);
+                    uint32_t n = table_byte<LDS_TAB>(g_len, t_len | (view & 0xffu), b * 256);
+                    n += rev[b] > L[4 * b] ? 1u : 0u;
+                    n += rev[b] > L[4 * b + 1] ? 1u : 0u;
+                    n += rev[b] > L[4 * b + 2] ? 1u : 0u;
+                    len[b] = n;
+                    view >>= n;
                 }
-                rev[b] = __builtin_bitreverse32((uint32_t)buf);
-                uint32_t n = tab[row + ((uint32_t)buf & 0xffu) + b * kDecRow];
-                n += rev[b] > L[4 * b] ? 1u : 0u;
-                n += rev[b] > L[4 * b + 1] ? 1u : 0u;
-                n += rev[b] > L[4 * b + 2] ? 1u : 0u;
-                buf >>= n;
-                nbuf -= n;
-                len[b] = n;
+                const uint32_t was = pos >> 5;
+                pos += len[2 * pair] + len[2 * pair + 1];
+                const bool on = (pos >> 5) != was;
+                w0 = on ? w1 : w0;
+                w1 = on ? w2 : w1;
+                w2 = on ? w3 : w2;
             }
+        };
+        auto offsets = [&](uint32_t t_off, const uint32_t (&len)[4], uint32_t (&off)[4]) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) off[b] = table_byte<LDS_TAB>(g_off, t_off + len[b], b * kDecOff);
+        };
+        auto symbols = [&](uint32_t t_sym, const uint32_t (&rev)[4], const uint32_t (&len)[4], const uint32_t (&off)[4], uint32_t (&byte)[4]) {
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-                const uint32_t off = tab[row + len[b] + (b * kDecRow + kDecOff)];
-                const uint32_t rank = ((rev[b] >> (32u - len[b])) - off) & 0xffu;
-                w |= (uint32_t)tab[row + rank + (b * kDecRow + kDecSym)] << (8 * b);
+                const uint32_t rank = (rev[b] >> ((32u - len[b]) & 31u)) - off[b];
+                byte[b] = table_byte<LDS_TAB>(g_sym, t_sym | (rank & 0xffu), b * 256);
             }
-            return w;
         };
+        auto joined = [](const uint32_t (&byte)[4]) { return byte[0] | (byte[1] << 8) | (byte[2] << 16) | (byte[3] << 24); };
+        if (live) {
+            request();
+            choose();
+        }
         for (uint32_t p0 = 0; p0 < per_row; p0 += kDecSegment / 4) {
             const uint32_t p1 = min(per_row, p0 + (uint32_t)kDecSegment / 4u);
             if (LDS_TAB && (c == 0 || per_row > (uint32_t)kDecSegment / 4u)) {
                 __syncthreads();
-                const uint4* from = reinterpret_cast<const uint4*>(a.dec + (v.table + 4u * p0) * kDecRow);
+                const uint32_t n = 4u * (p1 - p0);             // rows
+                auto stage = [&](const uint8_t* from8, uint32_t to_byte, uint32_t bytes) {
+                    const uint4* from = reinterpret_cast<const uint4*>(from8);
+                    uint4* to = reinterpret_cast<uint4*>(tab32) + to_byte / 16u;
 #pragma unroll 4
-                for (uint32_t i = threadIdx.x; i < (p1 - p0) * kDecRow / 4u; i += blockDim.x) reinterpret_cast<uint4*>(tab32)[i] = from[i];
+                    for (uint32_t i = threadIdx.x; i < bytes / 16u; i += blockDim.x) to[i] = from[i];
+                };
+                stage(g_len + 4u * p0 * 256u, 0u, n * 256u);
+                stage(g_sym + 4u * p0 * 256u, seg * 256u, n * 256u);
+                stage(g_off + 4u * p0 * kDecOff, seg * 512u, n * kDecOff);
                 __syncthreads();
             }
+            if (!live) continue;
             // kDecBatch dwords of every row at a time: collected in LDS, stored as whole 64-byte pieces
-            u32x16 L = lim[p0];
-            uint32_t row = LDS_TAB ? 0u : 4u * p0 * kDecRow;
+            const uint32_t row0 = LDS_TAB ? 0u : 4u * p0;
             for (uint32_t d0 = p0; d0 < p1; d0 += kDecBatch) {
                 const uint32_t nd = min(p1 - d0, (uint32_t)kDecBatch);
-                if (mine) {
-                    for (uint32_t d = 0; d < nd; ++d) {
-                        const u32x16 Ln = lim[min(d0 + d + 1u, per_row - 1u)];
-                        out[lane * kDecPitch + d] = four(row, L);
-                        row += 4u * kDecRow;
-                        L = Ln;
+                uint32_t* to = out + lane * kDecPitch;
+                uint32_t rev[2][4], len[2][4], off[2][4], byte[2][4];           // of the dwords whose lengths were found last
+                uint32_t row = row0 + 4u * (d0 - p0), d = 0;
+                // the symbols of two dwords are looked up while the lengths of the next two are found: only those wait for each other
+                auto pair_of = [&](auto first_tag, auto both_tag) {
+                    constexpr bool kFirst = decltype(first_tag)::value, kBoth = decltype(both_tag)::value;
+                    const u32x16 La = lim[d0 + d], Lb = lim[min(d0 + d + 1u, per_row - 1u)];
+                    uint32_t rev_n[2][4], len_n[2][4];
+                    if constexpr (!kFirst) {
+                        offsets(tab_off + (row - 8u) * kDecOff, len[0], off[0]);
+                        offsets(tab_off + (row - 4u) * kDecOff, len[1], off[1]);
                     }
+                    lengths(tab + row * 256u, La, rev_n[0], len_n[0]);
+                    const bool more = d0 + d + (kBoth ? 2u : 1u) < per_row;
+                    if (more) request();
+                    if constexpr (!kFirst) {
+                        symbols(tab_sym + (row - 8u) * 256u, rev[0], len[0], off[0], byte[0]);
+                        symbols(tab_sym + (row - 4u) * 256u, rev[1], len[1], off[1], byte[1]);
+                    }
+                    if constexpr (kBoth) lengths(tab + row * 256u + 1024u, Lb, rev_n[1], len_n[1]);
+                    if constexpr (!kFirst) {
+                        to[d - 2u] = joined(byte[0]);
+                        to[d - 1u] = joined(byte[1]);
+                    }
+                    if (more) choose();
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        rev[0][b] = rev_n[0][b];
+                        len[0][b] = len_n[0][b];
+                        if constexpr (kBoth) {
+                            rev[1][b] = rev_n[1][b];
+                            len[1][b] = len_n[1][b];
+                        }
+                    }
+                    d += kBoth ? 2u : 1u;
+                    row += kBoth ? 8u : 4u;
+                };
+                auto rest = [&](uint32_t at_d, uint32_t at_row, int k) {
+                    offsets(tab_off + at_row * kDecOff, len[k], off[k]);
+                    symbols(tab_sym + at_row * 256u, rev[k], len[k], off[k], byte[k]);
+                    to[at_d] = joined(byte[k]);
+                };
+                if (nd >= 2u) {
+                    pair_of(std::true_type(), std::true_type());
+                    while (d + 2u <= nd) pair_of(std::false_type(), std::true_type());
+                    rest(d - 2u, row - 8u, 0);
+                    rest(d - 1u, row - 4u, 1);
+                }
+                if (d < nd) {
+                    pair_of(std::true_type(), std::false_type());
+                    rest(d - 1u, row - 4u, 0);
                 }
                 wave_fence();
-                if (live) {
+                {
                     const uint32_t n_rows = (uint32_t)min(v.T - chunk * kChunk, (int64_t)kChunk);
                     uint32_t* to = v.rec + chunk * kChunk * per_row + d0;
                     if (nd == kDecBatch) {
@@ -653,13 +735,13 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
             ++count[L[s]];
         }
         uint32_t kraft = 0, next[kMaxLen + 1], rank[kMaxLen + 1], code = 0, shorter = 0;
-        uint8_t* D = &dec[k * kDecRow];
+        uint8_t *D = &dec[k * 256], *S = &dec[(rows + k) * 256], *O = &dec[rows * 512 + k * kDecOff];      // lengths, symbols, offsets
         int least = 9;                                              // what the table says for codes of 9 bits or more
         for (int len = 1; len <= kMaxLen; ++len) {
             kraft += count[len] << (kMaxLen - len);
             next[len] = code;                                       // first code of this length, and its rank
             rank[len] = shorter;
-            D[kDecOff + len] = (uint8_t)(code - shorter);
+            O[len] = (uint8_t)(code - shorter);
             code += count[len];
             shorter += count[len];
             if (len >= 9 && len < kMaxLen) {
@@ -675,7 +757,7 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
             const int len = L[s];
             const uint32_t rev = reverse_bits(next[len]++, len);
             enc[k * 256 + s] = (uint16_t)(rev | ((uint32_t)len << 12));
-            D[kDecSym + rank[len]++] = (uint8_t)s;
+            S[rank[len]++] = (uint8_t)s;
             if (len <= 8)
                 for (uint32_t i = rev; i < 256u; i += 1u << len) D[i] = (uint8_t)len;
         }
