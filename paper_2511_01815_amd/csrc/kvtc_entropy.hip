@@ -184,7 +184,7 @@ __device__ __forceinline__ void stage_table(const uint32_t* src, int rows, int l
 // dword and at the token's before it.
 __global__ void __launch_bounds__(1024, 2) entropy_size_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
     const int R = a.R;
     const JobView v = job_view(a, blockIdx.y);
     const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
@@ -201,22 +201,23 @@ __global__ void __launch_bounds__(1024, 2) entropy_size_kernel(const EntropyArgs
         const uint32_t* src = v.rec + chunk * kChunk * pw.per_row;
         uint32_t token = pw.dw / pw.per_row;
         const uint32_t token_step = 256u / pw.per_row;
+        const uint32_t rows_end = pw.per_row * (4u * kLenRow);
         uint32_t run = 0;                                            // bits of the pieces before this step
         uint32_t w[4];
         pw.load(src, w);
         for (uint32_t d0 = 0; d0 < pw.n_dw; d0 += 256u) {
             const PieceWalk cur = pw;
             const uint32_t tok0 = token;
-            uint32_t s[4], at = cur.at, tok = tok0, last = 0u, end_tok[4];
+            uint32_t s[4], row = __umul24(cur.at, 4u * kLenRow), tok = tok0, last = 0u, end_tok[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint8_t* e = tab + at * (4 * kLenRow);
+                const uint8_t* e = tab + row;
                 const uint32_t bits = (uint32_t)e[w[j] & 0xffu] + (uint32_t)e[kLenRow + ((w[j] >> 8) & 0xffu)] +
                                       (uint32_t)e[2 * kLenRow + ((w[j] >> 16) & 0xffu)] + (uint32_t)e[3 * kLenRow + (w[j] >> 24)];
                 s[j] = cur.dw + j < cur.n_dw ? bits : 0u;
-                ++at;
-                end_tok[j] = at == cur.per_row && cur.dw + j < cur.n_dw ? tok : ~0u;
-                if (at == cur.per_row) { at = 0u; ++tok; }
+                row += 4u * kLenRow;
+                end_tok[j] = row == rows_end && cur.dw + j < cur.n_dw ? tok : ~0u;
+                if (row == rows_end) { row = 0u; ++tok; }
                 last += s[j];
             }
             token += token_step + (pw.at + pw.step >= pw.per_row ? 1u : 0u);
@@ -280,12 +281,14 @@ __global__ void __launch_bounds__(256) entropy_scan_kernel(const EntropyArgs a) 
 // needed size in coded_bytes).  Per step a wave builds the string of its 64 pieces (1 KiB of records) in LDS, starting at the
 // bits the step before left over, and stores the whole dwords coalesced: 1.5 KiB of LDS per wave, where the image of a whole
 // chunk and its rows took 20 and left a compute unit seven waves.  LDS_TAB: the codes come from the workgroup's copy of the
-// table (records of up to kMaxLdsRecord bytes), else from global memory.  Bound by about 16 vector instructions per byte:
-// 256 MiB in 634 us before, 167 now.
+// table (records of up to kMaxLdsRecord bytes), else from global memory.  Bound by vector instructions, 11 per byte: four bytes' codes are
+// put together and OR-ed in at once, where a 64-bit buffer emptied behind every second byte made it 16 with nine branches for each lane's 16
+// bytes, and everything that is one for the wave stays in scalar registers.  256 MiB of records: 634 us in a chunk image, 163 with the
+// buffer, 136 so.
 template <bool LDS_TAB>
 __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
     const int R = a.R;
     const JobView v = job_view(a, blockIdx.y);
     const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
@@ -309,53 +312,59 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
         uint32_t* out = reinterpret_cast<uint32_t*>(v.payload + begin);
         PieceWalk pw(v.T, chunk, R);
         const uint32_t* src = v.rec + chunk * kChunk * pw.per_row;
+        const uint32_t rows_end = pw.per_row * (4u * kRow);
         uint32_t carry = 0, written = 0;                             // bits in img[0] left by the step before; dwords stored
         uint32_t w[4];
         pw.load(src, w);
         for (uint32_t d0 = 0; d0 < pw.n_dw; d0 += 256u) {
-            uint32_t code[8], len[8], at = pw.at, bits = 0;          // two bytes' codes together: at most 24 bits
+            // four bytes' codes together: at most 48 bits
+            uint64_t code[4];
+            uint32_t len[4], row = __umul24(pw.at, 4u * kRow), bits = 0;       // the dword's first entry in the table
+            auto codes = [&](auto whole_tag) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint16_t* e = tab + at * (4 * kRow);
-                uint32_t ent[4];
+                for (int j = 0; j < 4; ++j) {
+                    const uint16_t* e = tab + row;
+                    uint32_t ent[4], two[2], n_two[2];
 #pragma unroll
-                for (int b = 0; b < 4; ++b) ent[b] = e[b * kRow + ((w[j] >> (8 * b)) & 0xffu)];
-                const bool in = pw.dw + j < pw.n_dw;
+                    for (int b = 0; b < 4; ++b) ent[b] = e[b * kRow + ((w[j] >> (8 * b)) & 0xffu)];
 #pragma unroll
-                for (int b = 0; b < 4; b += 2) {
-                    const uint32_t l0 = ent[b] >> 12;
-                    code[2 * j + b / 2] = in ? (ent[b] & 0xfffu) | ((ent[b + 1] & 0xfffu) << l0) : 0u;
-                    len[2 * j + b / 2] = in ? l0 + (ent[b + 1] >> 12) : 0u;
-                    bits += len[2 * j + b / 2];
+                    for (int b = 0; b < 2; ++b) {
+                        const uint32_t l0 = ent[2 * b] >> 12;
+                        two[b] = (ent[2 * b] & 0xfffu) | ((ent[2 * b + 1] & 0xfffu) << l0);
+                        n_two[b] = l0 + (ent[2 * b + 1] >> 12);
+                    }
+                    const bool in = decltype(whole_tag)::value || pw.dw + j < pw.n_dw;
+                    code[j] = in ? (uint64_t)two[0] | ((uint64_t)two[1] << n_two[0]) : 0ull;
+                    len[j] = in ? n_two[0] + n_two[1] : 0u;
+                    bits += len[j];
+                    row += 4u * kRow;
+                    if (row == rows_end) row = 0u;
                 }
-                ++at;
-                if (at == pw.per_row) at = 0u;
-            }
+            };
+            if (d0 + 256u <= pw.n_dw) codes(std::true_type()); else codes(std::false_type());
             pw.next();
             if (d0 + 256u < pw.n_dw) pw.load(src, w);                // the next step's bytes travel under this step's string
             const uint32_t incl = wave_inclusive_scan(bits);
-            const uint32_t pos = carry + incl - bits;
+            uint32_t pos = carry + incl - bits;
             const uint32_t n_bits = carry + (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-            // the string is built pre-shifted by pos % 32, so that whole dwords of the image are OR-ed in
-            uint64_t acc = 0;
-            uint32_t nacc = pos & 31u, dw = pos >> 5;
+            // shifted to their place and OR-ed in, two dwords at a time whether or not a bit falls into both; into a third for few
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                acc |= (uint64_t)code[k] << nacc;
-                nacc += len[k];
-                if (nacc >= 32u) {
-                    atomicOr(&img[dw], (uint32_t)acc);
-                    ++dw;
-                    acc >>= 32;
-                    nacc -= 32u;
-                }
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t shift = pos & 31u;
+                const uint64_t at_place = code[j] << shift;
+                uint32_t* to = img + (pos >> 5);
+                atomicOr(to, (uint32_t)at_place);
+                atomicOr(to + 1, (uint32_t)(at_place >> 32));
+                if (shift + len[j] > 64u) atomicOr(to + 2, (uint32_t)(code[j] >> 32) >> (32u - shift));
+                pos += len[j];
             }
-            if (nacc != 0u) atomicOr(&img[dw], (uint32_t)acc);
             wave_fence();
             const uint32_t full = n_bits >> 5;                       // at most 384
             const uint32_t rest = img[full];
             wave_fence();
-            for (uint32_t i = 4u * lane; i <= full; i += 256u) {
+            for (uint32_t i0 = 0; i0 <= full; i0 += 256u) {
+                const uint32_t i = i0 + 4u * lane;
+                if (i > full) break;
                 uint4* p = reinterpret_cast<uint4*>(img + i);
                 const uint4 q = *p;
                 *p = make_uint4(0u, 0u, 0u, 0u);
