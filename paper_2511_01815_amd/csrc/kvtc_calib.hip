@@ -185,6 +185,7 @@ __global__ void __launch_bounds__(kCalibThreads) calib_block_errors_kernel(const
     const bool halved = gridDim.z != 1 && calib_halved(blk, n_tokens), alone = halved && n > 256;          // alone: one width
     if (halved != (part < kCalibParts - 1) || (part >= 2 && halved && !alone)) return;
     const int w0 = alone ? part / 2 : 0, w1 = alone ? w0 + 1 : n_out;      // the widths this workgroup stores
+    if (w0 >= n_out) return;
     const int64_t half = halved ? (n_tokens + 1) / 2 : n_tokens, b = halved && part % 2 ? half : 0, m = halved && part % 2 ? n_tokens : half;
     static_assert(W == 1 || W == 2, "the widths of a long block");
     double e[W];

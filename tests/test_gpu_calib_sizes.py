@@ -38,6 +38,32 @@ def test_block_errors_at_every_lane_group_edge(n_tok):
             assert abs(got[i, b - 1] - ref) <= 1e-12 * (energy + abs(ref)), (n_tok, s, n, b)
 
 
+@pytest.mark.parametrize("n_tok", [50, 1030])
+@pytest.mark.parametrize("max_bits", [1, 2, 3, 7])
+def test_tables_of_fewer_widths_hold_the_same_rows(max_bits, n_tok):
+    """One width to a workgroup (lists that leave compute units idle) or two, the last of them alone where their number is odd: an
+    entry has the same bits in the table of eight widths, in a short list and in a long one (a width's sums keep their order), and
+    nothing beyond the table is written."""
+    rng = np.random.default_rng(n_tok + max_bits)
+    ld = 1030
+    coef = torch.from_numpy(rng.standard_normal((n_tok, ld)).astype(np.float32)).to(DEV)
+    cand = [(s, n) for n in (3, 16, 17, 64, 65, 256, 257, 1024) for s in (0, ld - n)]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+
+    def table(reps, widths):
+        blocks = torch.tensor(cand * reps, dtype=torch.int32, device=DEV)
+        out = torch.full((len(blocks) * widths + 3,), -7.0, dtype=torch.float64, device=DEV)
+        kv.kvtc_calib_block_errors(coef, n_tok, ld, blocks, len(blocks), widths, out)
+        torch.cuda.synchronize()
+        assert bool((out[len(blocks) * widths:] == -7.0).all())
+        return out[:len(blocks) * widths].view(reps, len(cand), widths)
+
+    want = table(1, 8)[0, :, :max_bits]
+    for reps in (1, cus // (len(cand) * max_bits) + 1):
+        got = table(reps, max_bits)
+        assert all(torch.equal(g, want) for g in got), (reps, (got - want).abs().max().item())
+
+
 @pytest.mark.parametrize("n_tok,p", [(1, 64), (3, 64), (4, 128), (17, 192), (130, 64), (515, 320)])
 def test_moments_at_strip_and_token_edges(n_tok, p):
     rng = np.random.default_rng(n_tok + p)
