@@ -296,7 +296,8 @@ __device__ __forceinline__ Words4And2 sload_x4_x2(const void* p4_uniform, const 
 template <typename T> __device__ __forceinline__ T* ptr_of(uint32_t lo, uint32_t hi) { return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo); }
 
 // The fields of a plan descriptor the decode kernel uses, in scalar registers.  (Its loads are issued together: one round trip to
-// the L2, where a wait behind each of six loads was six.  Small calls are chains of such round trips.)
+// the L2, where a wait behind each of six loads was six.  Small calls are chains of such round trips.  No more is loaded than is used:
+// with the descriptor's 24 dwords in one piece the fp32 kernel of ten blocks parked scalars in vector lanes 2011 times, not 876.)
 struct PlanDec {
     int32_t p, rec_dwords, dec_nct, dec_tt, dec_tok_wg, code_bits_max;
     const uint4* v_dec;
@@ -306,19 +307,20 @@ __device__ __forceinline__ PlanDec load_plan_dec(const PlanDev* P) {
     static_assert(offsetof(PlanDev, p) == 0 && offsetof(PlanDev, rec_dwords) == 16 && offsetof(PlanDev, dec_nct) == 28 &&
                   offsetof(PlanDev, dec_tt) == 32 && offsetof(PlanDev, dec_tok_wg) == 40 && offsetof(PlanDev, code_bits_max) == 60, "descriptor layout");
     static_assert(offsetof(PlanDev, v_dec) == 96 && offsetof(PlanDev, blk) == 120, "descriptor layout");
-    u32x16 f;
-    u32x8 q;
-    asm volatile("s_load_dwordx16 %0, %2, 0x0\n\ts_load_dwordx8 %1, %2, 0x60\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&s"(f), "=&s"(q) : "s"(uniform_ptr(reinterpret_cast<const char*>(P))) : "memory");
+    uint32_t p, rd, tok, cb;
+    u32x2 nt, v, k;
+    asm volatile("s_load_dword %0, %7, 0x0\n\ts_load_dword %1, %7, 0x10\n\ts_load_dwordx2 %4, %7, 0x1c\n\ts_load_dword %2, %7, 0x28\n\t"
+                 "s_load_dword %3, %7, 0x3c\n\ts_load_dwordx2 %5, %7, 0x60\n\ts_load_dwordx2 %6, %7, 0x78\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(p), "=&s"(rd), "=&s"(tok), "=&s"(cb), "=&s"(nt), "=&s"(v), "=&s"(k) : "s"(uniform_ptr(reinterpret_cast<const char*>(P))) : "memory");
     PlanDec d;
-    d.p = (int32_t)f[0];
-    d.rec_dwords = (int32_t)f[4];
-    d.dec_nct = (int32_t)f[7];
-    d.dec_tt = (int32_t)f[8];
-    d.dec_tok_wg = (int32_t)f[10];
-    d.code_bits_max = (int32_t)f[15];
-    d.v_dec = ptr_of<const uint4>(q[0], q[1]);
-    d.blk = ptr_of<const uint32_t>(q[6], q[7]);
+    d.p = (int32_t)p;
+    d.rec_dwords = (int32_t)rd;
+    d.dec_nct = (int32_t)nt[0];
+    d.dec_tt = (int32_t)nt[1];
+    d.dec_tok_wg = (int32_t)tok;
+    d.code_bits_max = (int32_t)cb;
+    d.v_dec = ptr_of<const uint4>(v[0], v[1]);
+    d.blk = ptr_of<const uint32_t>(k[0], k[1]);
     return d;
 }
 
@@ -332,26 +334,29 @@ struct PlanEnc {
 };
 __device__ __forceinline__ PlanEnc load_plan_enc(const PlanDev* P) {
     static_assert(offsetof(PlanDev, n_groups) == 8 && offsetof(PlanDev, enc_ntw) == 20 && offsetof(PlanDev, enc_wc) == 24, "descriptor layout");
-    static_assert(offsetof(PlanDev, enc_wgs) == 64 && offsetof(PlanDev, enc_short) == 76 && offsetof(PlanDev, v_enc) == 88 &&
+    static_assert(offsetof(PlanDev, code_bits_max) == 60 && offsetof(PlanDev, enc_wgs) == 64 && offsetof(PlanDev, enc_nw) == 72 && offsetof(PlanDev, enc_short) == 76 && offsetof(PlanDev, v_enc) == 88 &&
                   offsetof(PlanDev, negc) == 104 && offsetof(PlanDev, blk) == 120 && offsetof(PlanDev, grp) == 128, "descriptor layout");
-    u32x16 f, q;
-    u32x2 t;
-    asm volatile("s_load_dwordx16 %0, %3, 0x0\n\ts_load_dwordx16 %1, %3, 0x40\n\ts_load_dwordx2 %2, %3, 0x80\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&s"(f), "=&s"(q), "=&s"(t) : "s"(uniform_ptr(reinterpret_cast<const char*>(P))) : "memory");
+    // (the lines of the descriptor that are used, not all of it: scalar registers are short in the bulk kernels)
+    u32x8 f, q;
+    u32x4 w, t;
+    uint32_t m;
+    asm volatile("s_load_dwordx8 %0, %5, 0x0\n\ts_load_dword %4, %5, 0x3c\n\ts_load_dwordx4 %2, %5, 0x40\n\ts_load_dwordx8 %1, %5, 0x58\n\t"
+                 "s_load_dwordx4 %3, %5, 0x78\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(f), "=&s"(q), "=&s"(w), "=&s"(t), "=&s"(m) : "s"(uniform_ptr(reinterpret_cast<const char*>(P))) : "memory");
     PlanEnc d;
     d.p = (int32_t)f[0];
     d.n_groups = (int32_t)f[2];
     d.rec_dwords = (int32_t)f[4];
     d.enc_ntw = (int32_t)f[5];
     d.enc_wc = (int32_t)f[6];
-    d.code_bits_max = (int32_t)f[15];
-    d.enc_wgs = (int32_t)q[0];
-    d.enc_nw = (int32_t)q[2];
-    d.enc_short = (int32_t)q[3];
-    d.v_enc = ptr_of<const uint4>(q[6], q[7]);
-    d.negc = ptr_of<const float>(q[10], q[11]);
-    d.blk = ptr_of<const uint32_t>(q[14], q[15]);
-    d.grp = ptr_of<const uint32_t>(t[0], t[1]);
+    d.code_bits_max = (int32_t)m;
+    d.enc_wgs = (int32_t)w[0];
+    d.enc_nw = (int32_t)w[2];
+    d.enc_short = (int32_t)w[3];
+    d.v_enc = ptr_of<const uint4>(q[0], q[1]);
+    d.negc = ptr_of<const float>(q[4], q[5]);
+    d.blk = ptr_of<const uint32_t>(t[0], t[1]);
+    d.grp = ptr_of<const uint32_t>(t[2], t[3]);
     return d;
 }
 
