@@ -632,7 +632,7 @@ size_t bound_of(int R, int64_t n_tokens) {
 // table in LDS workgroups are as small as they can be, or, with more jobs than compute units, a job (of up to 16 chunks) each: then a
 // compute unit's caches hold few tables.
 // (2188 chunks of 128-byte records, encode and decode: 75 + 102 us with four waves that took two chunks in turn on one workgroup per
-// compute unit, 45 + 31 so; 64 tensors of 63 chunks 83 + 145, now 41 + 39.)
+// compute unit, 45 + 31 so, 40 + 24 with the kernels as they are; 64 tensors of 63 chunks 83 + 145, 41 + 39, 34 + 32.)
 struct Shape { int waves, chunks_per_wave; unsigned blocks; size_t lds; };
 Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs) {
     const int64_t total = n_chunks * n_jobs, cus = compute_units();
@@ -652,8 +652,8 @@ Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs) 
 }
 
 // Whether jobs of a few chunks each, a workgroup per job, would wait for others to leave the LDS.  Then they read their tables from global
-// memory instead: 1000 tensors of one chunk, 128-byte records: encode 36 us with the tables in LDS, 28 without, decode 76 and 34;
-// with places for all, 250 tensors: 22 and 23, 21 and 31.  (At three chunks in encode, five in decode, the copy pays again.)
+// memory instead: 1000 tensors of one chunk, 128-byte records: encode 36 us with the tables in LDS, 28 without, decode 76 and 34
+// (25 and 26 without, with the kernels as they are); with places for all, 250 tensors: 22 and 23, 21 and 31.  (At three chunks in encode, five in decode, the copy pays again.)
 bool jobs_wait(size_t table_b, size_t wave_b, int n_jobs) { return n_jobs > compute_units() * (int)(kLdsBudget / (table_b + 4 * wave_b)); }
 
 kvtc_status launch(const char* who, void (*fn)(EntropyArgs), const Shape& sh, int n_jobs, EntropyArgs a, hipStream_t st) {
