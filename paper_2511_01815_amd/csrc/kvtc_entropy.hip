@@ -401,10 +401,11 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
 // string in registers (eight codes are at most 96 bits, behind at most 31).  The dwords that the next window may begin in, and those behind,
 // are requested when half the codes are taken, and the window is chosen from them at the end: nothing branches, and a wave waits for memory once
 // in eight bytes.  (A 64-bit buffer per lane, refilled dword by dword from four that a lane fetched when it had used them up, waited at every
-// second byte, because some lane had always just fetched.)
+// second byte, because some lane had always just fetched.)  PIECES: a lane keeps eight dwords and requests four more when it has used up as many
+// (decode_in_pieces).
 // Rows are collected in LDS and stored 64 bytes at a time (stored 16 bytes at a time, straight from the lanes, a line's pieces
 // did not meet in the L2: five times the writes to memory, 0.57 ms).
-// 256 MiB of records: 777 us with twelve comparisons per symbol, 326 with three and the buffer, 290 now.  Vector instructions: 21 per symbol (34 with the buffer), half of the cycles; the lanes'
+// 256 MiB of records of 128 bytes: 777 us with twelve comparisons per symbol, 326 with three and the buffer, 271 now.  Vector instructions: 21 per symbol (34 with the buffer), half of the cycles; the lanes'
 // 24-byte reads come from the L2, a line as often as it is read, because 16 waves' strings do not fit the L1.
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));       // on any dword boundary
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(4)));
@@ -417,7 +418,7 @@ template <bool LDS_TAB> __device__ __forceinline__ uint32_t table_byte(const uin
         return base[off + constant];
     }
 }
-template <bool LDS_TAB>
+template <bool LDS_TAB, bool PIECES>
 __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
@@ -457,32 +458,82 @@ __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs 
         // (lanes behind the last token run along on the first token's string, and their rows are not stored: from the end of the strings on they
         // made the whole wave choose every window the long way.  60 tokens of 36 bytes: 9.2 us there, 8.1 so; of 128: 17.5 and 17.1.)
         uint32_t w0 = 0u, w1 = 0u, w2 = 0u, w3 = 0u;           // the window: dwords pos / 32 and the three behind it
+        int at = 0;                                            // dword of the first one at hand
+        typedef const char __attribute__((address_space(1))) * global_ptr;
+        // PIECES: the eight dwords from `at` on are at hand.  Between two windows pos moves by three dwords at most, two of them behind the request; it
+        // asks for four more where fewer than five would be left in front of the window.  (The window's own first dword is carried over.)
+        u32x4 lo{}, hi{};
+        int behind = 0;                                        // of `hi`: its dwords that lie behind the payload's end
+        auto piece = [&](int d) {
+            const int from = min(d, last + 2);
+            behind = d - from;
+            return (u32x4)*reinterpret_cast<const u32x4_any __attribute__((address_space(1)))*>((global_ptr)src + (uint32_t)(from + 6) * 4u);
+        };
+        auto settle = [&]() {
+            while (__builtin_expect(__any(behind > 0), 0)) {
+                const bool on = behind > 0;
+                hi[0] = on ? hi[1] : hi[0];
+                hi[1] = on ? hi[2] : hi[1];
+                hi[2] = on ? hi[3] : hi[2];
+                behind = min(behind, 3) - 1;                   // far behind the end everything is stray
+            }
+        };
         uint32_t g0 = 0u, g1 = 0u, g2 = 0u, g3 = 0u, g4 = 0u, g5 = 0u;
-        int at = 0;                                            // dword of g0
         auto request = [&]() {
-            at = min((int)(pos >> 5), last);
-            typedef const char __attribute__((address_space(1))) * global_ptr;
-            const global_ptr from = (global_ptr)src + (uint32_t)(at + 6) * 4u;
-            const u32x4_any lo = *reinterpret_cast<const u32x4_any __attribute__((address_space(1)))*>(from);
-            const u32x2_any hi = *reinterpret_cast<const u32x2_any __attribute__((address_space(1)))*>(from + 16);
-            g0 = lo[0]; g1 = lo[1]; g2 = lo[2]; g3 = lo[3]; g4 = hi[0]; g5 = hi[1];
+            if constexpr (PIECES) {
+                if ((int)(pos >> 5) - at >= 3) {
+                    lo = hi;
+                    at += 4;
+                    hi = piece(at + 4);
+                }
+            } else {
+                at = min((int)(pos >> 5), last);
+                const global_ptr from = (global_ptr)src + (uint32_t)(at + 6) * 4u;
+                const u32x4_any four = *reinterpret_cast<const u32x4_any __attribute__((address_space(1)))*>(from);
+                const u32x2_any two = *reinterpret_cast<const u32x2_any __attribute__((address_space(1)))*>(from + 16);
+                g0 = four[0]; g1 = four[1]; g2 = four[2]; g3 = four[3]; g4 = two[0]; g5 = two[1];
+            }
         };
         auto choose = [&]() {                                  // (what lies behind the payload's end is stray, and no code reads it)
-            int d = (int)(pos >> 5) - at;                      // 0 .. 2, but near the payload's end
-            while (__builtin_expect(__any(d > 2), 0)) {
-                const bool on = d > 2;
-                g0 = on ? g1 : g0;
-                g1 = on ? g2 : g1;
-                g2 = on ? g3 : g2;
-                g3 = on ? g4 : g3;
-                g4 = on ? g5 : g4;
-                d -= on ? (d > 8 ? d - 2 : 1) : 0;              // far behind the end everything is stray
+            if constexpr (PIECES) {
+                settle();
+                const int i = (int)(pos >> 5) + 1 - at;        // 0 .. 5
+                const bool b0 = (i & 1) != 0, b1 = (i & 2) != 0, b2 = (i & 4) != 0;
+                const uint32_t x0 = b2 ? hi[0] : lo[0], x1 = b2 ? hi[1] : lo[1], x2 = b2 ? hi[2] : lo[2], x3 = b2 ? hi[3] : lo[3];
+                const uint32_t y0 = b1 ? x2 : x0, y1 = b1 ? x3 : x1, y2 = b1 ? hi[0] : x2, y3 = b1 ? hi[1] : x3;
+                w1 = b0 ? y1 : y0;
+                w2 = b0 ? y2 : y1;
+                w3 = b0 ? y3 : y2;
+            } else {
+                int d = (int)(pos >> 5) - at;                  // 0 .. 2, but near the payload's end
+                while (__builtin_expect(__any(d > 2), 0)) {
+                    const bool on = d > 2;
+                    g0 = on ? g1 : g0;
+                    g1 = on ? g2 : g1;
+                    g2 = on ? g3 : g2;
+                    g3 = on ? g4 : g3;
+                    g4 = on ? g5 : g4;
+                    d -= on ? (d > 8 ? d - 2 : 1) : 0;          // far behind the end everything is stray
+                }
+                const bool one = d == 1, two = d == 2;
+                w0 = two ? g2 : (one ? g1 : g0);
+                w1 = two ? g3 : (one ? g2 : g1);
+                w2 = two ? g4 : (one ? g3 : g2);
+                w3 = two ? g5 : (one ? g4 : g3);
             }
-            const bool one = d == 1, two = d == 2;
-            w0 = two ? g2 : (one ? g1 : g0);
-            w1 = two ? g3 : (one ? g2 : g1);
-            w2 = two ? g4 : (one ? g3 : g2);
-            w3 = two ? g5 : (one ? g4 : g3);
+        };
+        auto first_window = [&]() {
+            if constexpr (PIECES) {
+                at = (int)(pos >> 5);
+                hi = piece(at);
+                settle();
+                lo = hi;
+                w0 = lo[0];
+                hi = piece(at + 4);
+            } else {
+                request();
+            }
+            choose();
         };
         // the codes of the four bytes of a dword whose rows of the length table begin here: reversed bits and lengths
         auto lengths = [&](uint32_t t_len, const u32x16& L, uint32_t (&rev)[4], uint32_t (&len)[4]) {
@@ -519,10 +570,7 @@ __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs 
             }
         };
         auto joined = [](const uint32_t (&byte)[4]) { return byte[0] | (byte[1] << 8) | (byte[2] << 16) | (byte[3] << 24); };
-        if (live) {
-            request();
-            choose();
-        }
+        if (live) first_window();
         for (uint32_t p0 = 0; p0 < per_row; p0 += kDecSegment / 4) {
             const uint32_t p1 = min(per_row, p0 + (uint32_t)kDecSegment / 4u);
             if (LDS_TAB && (c == 0 || per_row > (uint32_t)kDecSegment / 4u)) {
@@ -662,6 +710,20 @@ Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs) 
 // (25 and 26 without, with the kernels as they are); with places for all, 250 tensors: 22 and 23, 21 and 31.  (At three chunks in encode, five in decode, the copy pays again.)
 bool jobs_wait(size_t table_b, size_t wave_b, int n_jobs) { return n_jobs > compute_units() * (int)(kLdsBudget / (table_b + 4 * wave_b)); }
 
+// Whether decode reads its strings in pieces of 16 bytes, each once, and not a whole window for every eight bytes: where the records that the
+// chip works on at a time, and their strings, do not fit the L2s (4 MiB on each of 8 XCDs), so that a line read again comes from behind them.  Waves of
+// a launch of one round go through their records in step; a second round is shorter, or the first one's last waves run beside it; in more the
+// waves are spread over their records.  Records shorter than a line share it with their neighbours' strings.
+// Both sides, us, whole windows and pieces: 4096 chunks at once of records of 120 bytes 34.4 and 36.6, 128 bytes 43.3 and 35.1, 200 bytes 107 and 74;
+// 3008 chunks of 160 bytes 41.6 and 42.6, 176 bytes 49.4 and 46.9; two rounds of 3008 chunks of 140 bytes 75.5 and 77.2, 148 bytes 91.2 and 87.3; 12032 chunks
+// of 148 bytes 161 and 165, 160 bytes 184 and 171, 256 bytes 418 and 276 (326 with a 64-bit buffer per lane).
+bool decode_in_pieces(const Shape& sh, int R, int64_t n_chunks, int n_jobs) {
+    const int64_t places = compute_units() * std::min<int64_t>(kLdsBudget / sh.lds, 32 / sh.waves);        // workgroups at once
+    const int64_t rounds = ((int64_t)sh.blocks * n_jobs + places - 1) / places * sh.chunks_per_wave;
+    const int64_t at_once = (rounds <= 2 ? n_chunks * n_jobs / rounds : places * sh.waves) * kChunk * R;
+    return R >= 128 && (rounds == 1 ? at_once > 30 << 20 : rounds == 2 ? at_once > 26 << 20 : at_once >= 40 << 20);
+}
+
 kvtc_status launch(const char* who, void (*fn)(EntropyArgs), const Shape& sh, int n_jobs, EntropyArgs a, hipStream_t st) {
     if (allow_full_lds(reinterpret_cast<const void*>(fn)) != hipSuccess) return set_error(KVTC_E_HIP, "%s: cannot size the LDS", who);
     a.chunks_per_wave = sh.chunks_per_wave;
@@ -698,8 +760,11 @@ kvtc_status run_decode(const char* who, const kvtc_entropy* e, const EntropyArgs
     if (max_chunks == 0) return KVTC_OK;
     const size_t table_b = (size_t)(R < kDecSegment ? R : kDecSegment) * kDecRow, wave_b = kChunk * kDecPitch * 4;
     const bool tab_lds = !(max_chunks <= 4 && jobs_wait(table_b, wave_b, n_jobs));
-    const kvtc_status rc = launch(who, tab_lds ? &entropy_decode_kernel<true> : &entropy_decode_kernel<false>,
-                                  launch_shape(tab_lds ? table_b : 0, wave_b, max_chunks, n_jobs), n_jobs, a, st);
+    const Shape sh = launch_shape(tab_lds ? table_b : 0, wave_b, max_chunks, n_jobs);
+    void (*const fn)(EntropyArgs) = !tab_lds                                        ? &entropy_decode_kernel<false, false>
+                                    : decode_in_pieces(sh, R, max_chunks, n_jobs) ? &entropy_decode_kernel<true, true>
+                                                                                    : &entropy_decode_kernel<true, false>;
+    const kvtc_status rc = launch(who, fn, sh, n_jobs, a, st);
     if (rc != KVTC_OK) return rc;
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return set_error(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(err));

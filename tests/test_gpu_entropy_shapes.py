@@ -101,3 +101,57 @@ def test_many_tensors_of_a_few_chunks(R, n_jobs, most):
     lens = np.random.default_rng(most).integers(1, most + 1, 10).tolist()
     lens[3], lens[5] = most, max(1, most - 64)
     _check_batch(R, [lens[j % 10] for j in range(n_jobs)], 10)
+
+
+@pytest.mark.parametrize("R,T", [(128, 262_100), (200, 172_101), (256, 140_000), (576, 62_300), (576, 123_000)])
+def test_strings_read_a_piece_at_a_time(R, T):
+    """One long tensor whose records, of one to four table segments, do not fit the L2s of 256 compute units, in one round and in two, and short
+    ones of the same launch, whose payloads are a few dwords or end in a chunk of few tokens."""
+    lens = [T, 1, 2, 63, 64, 65, 129, 200]
+    n = len(lens)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(R)
+    mean = 1.2 + (11 * torch.arange(R, device=DEV)) % 120
+    rec = torch.cat([torch.zeros((m, R), device=DEV).exponential_(generator=gen).mul_(mean).clamp_(max=255).to(torch.uint8).view(-1) for m in lens])
+    tab = kv.EntropyTables(R, ke.calibrate_tables(rec[:4096 * R].view(-1, R).cpu().numpy()))
+    rec_at = np.concatenate([[0], np.cumsum([m * R for m in lens])]).tolist()
+    caps = [ke.bound_bytes(m, R) for m in lens]
+    cod_at = np.concatenate([[0], np.cumsum(caps)]).tolist()
+    coded = torch.zeros(cod_at[-1], dtype=torch.uint8, device=DEV)
+    sizes = torch.zeros(n, dtype=torch.int64, device=DEV)
+
+    def jobs(room):
+        return torch.from_numpy(kv.make_entropy_jobs([0] * n, lens, rec_at[:-1], cod_at[:-1], room).view(np.uint8)).to(DEV)
+
+    kv.kvtc_entropy_encode_batch(tab.handle, jobs(caps), n, T, rec, rec.numel(), coded, cod_at[-1], sizes)
+    torch.cuda.synchronize()
+    back = torch.full((rec.numel() + 64,), 0x5A, dtype=torch.uint8, device=DEV)
+    kv.kvtc_entropy_decode_batch(tab.handle, jobs(sizes.cpu().tolist()), n, T, coded, cod_at[-1], back, rec.numel())
+    torch.cuda.synchronize()
+    assert torch.equal(back[:rec.numel()], rec) and bool((back[rec.numel():] == 0x5A).all())
+    tab.close()
+
+
+@pytest.mark.parametrize("R,T", [(100, 300), (576, 62_300)])
+def test_damaged_container_stays_inside_its_buffers(R, T):
+    """Random token lengths (up to 65535 bits, far behind a short payload), random chunk offsets and a payload cut short: the records are wrong,
+    but nothing else is written, and the tensor decoded beside it is right.  The second size reads a piece at a time."""
+    rng = np.random.default_rng(R)
+    rec = np.stack([np.minimum(255, rng.geometric(1.0 / (1.2 + (11 * k) % 120), 2048) - 1) for k in range(R)], axis=1).astype(np.uint8)
+    lengths = ke.calibrate_tables(rec)
+    tab = kv.EntropyTables(R, lengths)
+    good = np.frombuffer(ke.encode(rec[:130], lengths), dtype=np.uint8)
+    n_chunks = (T + 63) // 64
+    for payload in (0, 4, 24, 4000):
+        offs = rng.integers(0, 2 ** 32, n_chunks + 1, dtype=np.uint64).astype(np.uint32)
+        offs[::3] = rng.integers(0, payload + 8, len(offs[::3]))
+        bits = rng.integers(0, 65536, 64 * n_chunks).astype(np.uint16)
+        bad = np.concatenate([offs.view(np.uint8), bits.view(np.uint8), rng.integers(0, 256, payload).astype(np.uint8)])
+        blob = torch.from_numpy(np.concatenate([bad, good])).to(DEV)
+        back = torch.full((T * R + 130 * R + 64,), 0x5A, dtype=torch.uint8, device=DEV)
+        jobs = kv.make_entropy_jobs([0, 0], [T, 130], [0, T * R], [0, len(bad)], [len(bad), len(good)])
+        kv.kvtc_entropy_decode_batch(tab.handle, torch.from_numpy(jobs.view(np.uint8)).to(DEV), 2, T, blob, blob.numel(), back, T * R + 130 * R)
+        torch.cuda.synchronize()
+        assert np.array_equal(back[T * R:T * R + 130 * R].cpu().numpy().reshape(130, R), rec[:130]), payload
+        assert bool((back[T * R + 130 * R:] == 0x5A).all()), payload
+    tab.close()
