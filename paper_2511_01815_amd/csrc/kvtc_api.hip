@@ -1016,11 +1016,18 @@ kvtc_status kvtc_decode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.status = status_dev;
     for (const auto& v : batch->dec) {
         // Jobs whose 128-token tiles can be shown to run all at once (the stream buffer's size bounds their tokens, and each may end in a
-        // part of a tile) take the variant with one token tile per wave, as a single tensor does.  (One head of 4096 tokens in
-        // fp32: the pair of calls 20.6 us on 256-token tiles, 18.6 so.)
-        const int slots = compute_units() * v.wgs;
-        const bool wide = v.key % 100 > 10;
-        a.dec_short = !wide && in_bytes / ((size_t)batch->min_rec_dwords * 4 * kDecShortTile) + (size_t)n_jobs <= (size_t)slots;
+        // part of a tile) take the variant with one token tile per wave, as a single tensor does, where the mean job is no more than one such tile
+        // or the tiles, twice as many with twice the basis traffic, are few: one per compute unit; of more plans than there are XCDs fewer, and
+        // most of each job's second tile used; all of the narrow class, but for jobs of two tiles.
+        // Both sides, us, 256-token tiles and 128-token tiles: a head of 4096 tokens in fp32 11.6 and 8.6; one tensor of 32768 tokens at 16x 28.5 and 27.2, of 34000
+        // 31.6 and 36.0, of 40000 at 40x 25.6 and 22.9; 200 of 130 tokens at 40x 26.1 and 27.9; 64 with a plan each, 16x, of 300 tokens 33.1
+        // and 29.8, of 500 34.3 and 38.7, 20x in fp32 of 130 tokens 21.0 and 24.3, of 200 23.1 and 24.7.
+        const int cus = compute_units(), slots = cus * v.wgs;
+        const bool wide = v.key % 100 > 10, many = batch->n_plans > 8;
+        const size_t tokens = in_bytes / ((size_t)batch->min_rec_dwords * 4), jobs = (size_t)n_jobs, mean = (tokens + jobs - 1) / jobs;
+        const size_t few = v.wgs == 3 && mean > 2 * kDecShortTile ? slots : !many ? cus : mean > 7 * kDecShortTile / 4 ? cus * 3 / 4 : 0;
+        a.dec_short = !wide && tokens / kDecShortTile + jobs <= (size_t)slots &&
+                      (mean <= kDecShortTile || (mean + kDecShortTile - 1) / kDecShortTile * jobs <= few);
         const DecLayout lay = decode_layout(a.dec_short ? decode_rec_bytes(1, v.rec_dwords) : v.rec, v.ring, v.wgs);
         a.dec_ring_off = lay.ring_off;
         hipError_t e = launch_decode(a, dtype, a.dec_short ? 100 + v.key % 100 : v.key, slots, lay.lds_bytes, static_cast<hipStream_t>(stream));
