@@ -580,22 +580,33 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
     encode_epilogue<NTW, TT, true>(acc, ct0, 0, ROWS, kEncShortTile, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem);
 }
 
+// the lane's number, worked out where it is used and not kept through a loop
+__device__ __forceinline__ uint32_t lane_id() {
+    uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
 // A batch whose jobs all together are few enough tiles for one round of this kernel -- the host knows from the size of the stream buffer, the
 // jobs' lengths are on the device -- is coded by this launch alone.  The tiles of all jobs are numbered through; every wave finds its
 // workgroup's by a prefix sum over the jobs' tiles, a job per lane and round (bounded by the load and six lane exchanges).  Workgroups go
 // round-robin over the eight XCDs, each of which takes an eighth of the tiles, neighbours: the tiles of a job share an L2 and its basis.
 // (With a launch per bulk variant, which found no job, in front of it: an append step of 64 tensors 21.8 us, now 17.9; a head of 4096
 // tokens in fp32, encode and decode, 24.0, now 20.6.)
+// KEEP: the lane's number, and with it the addresses of its jobs, may be kept through the loop over tiles.  In fp32 there are no registers for them:
+// with them, and with `upto` left as it is for rounds that a list does not have, up to 18 went to scratch memory, four of them inside the loop over
+// chunks.  (12000 tokens, us, kept and not: fp32, 240 coordinates 22.2 and 19.5; bf16, 160 coordinates, six waves, 13.4 and 15.4.)
+template <bool KEEP>
 struct ShortTable {
     uint32_t tiles[kShortTableJobs / 64], upto[kShortTableJobs / 64];       // of the lane's job in each round: its tiles; those of the jobs up to it
     uint32_t total;
     __device__ __forceinline__ explicit ShortTable(const KernelArgs& a) {
-        const int lane = (int)threadIdx.x & 63;
+        const uint32_t lane = KEEP ? (uint32_t)threadIdx.x & 63u : lane_id();
 #pragma unroll
         for (int k = 0; k < kShortTableJobs / 64; ++k) {
-            const int j = 64 * k + lane;
-            tiles[k] = 0u;
-            if (64 * k < a.n_jobs && j < a.n_jobs) {
+            const uint32_t j = 64u * k + lane;
+            tiles[k] = upto[k] = 0u;
+            if (64 * k < a.n_jobs && j < (uint32_t)a.n_jobs) {
                 const int n = a.jobs[j].n_tokens;                    // (what else is wrong with a job is seen at its tiles)
                 tiles[k] = n > 0 && n <= a.enc_max_tokens ? (uint32_t)(n + kEncShortTile - 1) / kEncShortTile : 0u;
             }
@@ -704,10 +715,12 @@ __global__ void KVTC_SHORT_BOUNDS(NTW) kvtc_encode_small_batch_kernel(const Kern
         const KernelArgs a = __builtin_bit_cast(KernelArgs, words);
         TileRef tr;
         PlanEnc P;
-        const ShortTable t(a);
+        const ShortTable<sizeof(XT) == 2> t(a);
         const uint32_t per_xcd = (t.total + 7u) / 8u;
         if (i >= per_xcd || !t.find(a, (blockIdx.x & 7u) * per_xcd + i, tr)) return;
+        const bool last = i + (gridDim.x - 1u) / 8u >= per_xcd;       // (seen at the table of the next one it was half a microsecond)
         if (short_tile<NTW, true>(a, 0u, tr, P)) short_tile_code<NTW, XT>(P, tr, a, smem);
+        if (last) return;
     }
 }
 

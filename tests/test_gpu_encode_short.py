@@ -208,3 +208,40 @@ def test_small_batches_are_coded_by_one_launch(form, ranks, dtype):
                 n = lens[last] * plans[which[last]].record_bytes
                 bad = min([last] + [j for j in range(n_jobs) if not ok[j]])
                 assert sa == 1 + bad and torch.equal(a[:size - n], b[:size - n]) and bool((a[size - n:] == 0xA5).all()), (jobs[:8], sa)
+
+
+@pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
+@pytest.mark.parametrize("layout", ["pitched", "heads-major"])
+def test_small_batches_of_long_lists_and_other_layouts(layout, dtype):
+    """Lists of up to the most jobs that one launch takes, with jobs at both ends of each 64 that a wave looks at together and empty ones between:
+    the bytes of the bulk kernels, which a larger buffer gets."""
+    plans = [_gpu_plan(_variant_plan(r)) for r in (64, 192, 240)]
+    batch, p, block = kv.Batch(plans), 1024, 128
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tdt = torch.bfloat16 if dtype == kv.KVTC_BF16 else torch.float32
+    rows = 700
+    x = torch.randn((rows, p), generator=torch.Generator(device=DEV).manual_seed(4), device=DEV).to(tdt)
+    if layout == "pitched":
+        buf = torch.zeros((rows, p + 64), dtype=tdt, device=DEV)
+        buf[:, :p] = x
+        lay = kv.layout(p + 64)
+    else:
+        buf, lay = x.view(rows, p // block, block).transpose(0, 1).contiguous(), kv.layout(block, block, rows * block)
+    for n_jobs in (64, 65, 256, 257, 449, min(512, 2 * cus - 24)):
+        lens = np.zeros(n_jobs, dtype=int)
+        lens[[0, 63] + [j for j in (64, 127, 255, 256, 319, 447, 448) if j < n_jobs] + [n_jobs - 1]] = 5
+        lens[n_jobs // 2] = 70
+        which, row0 = [j % 3 for j in range(n_jobs)], [(29 * j) % (rows - 70) for j in range(n_jobs)]
+        dev = torch.from_numpy(kv.make_jobs(which, lens.tolist(), row0).view(np.uint8)).to(DEV)
+        size = sum(int(n) * plans[w].record_bytes for w, n in zip(which, lens))
+        got = []
+        for room in (0, 16 << 20):
+            out = torch.full((size + room + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+            offs = torch.zeros(n_jobs + 1, dtype=torch.int64, device=DEV)
+            status = torch.zeros(1, dtype=torch.int32, device=DEV)
+            kv.kvtc_offsets(batch.handle, dev, n_jobs, offs)
+            kv.kvtc_encode_batch_blocked(batch.handle, dev, n_jobs, buf, dtype, lay, offs, out, size + room, status)
+            torch.cuda.synchronize()
+            assert int(status.item()) == 0 and bool((out[size:] == 0xA5).all())
+            got.append(out[:size])
+        assert torch.equal(*got), n_jobs
