@@ -4,8 +4,8 @@
 // PCA coordinates and every quantiser type, the block of calibration coefficients is quantised as the
 // coder would quantise it, and the squared error is compared with dropping the block.)
 //
-// A workgroup owns a (candidate block, width) pair, so every sum has a fixed order and the table is
-// reproducible.  Four lanes or more own a token: its coefficients sit in registers, min and max come
+// A workgroup owns a candidate block at one width or at two neighbouring ones, a long block's tokens by halves, so every sum has a
+// fixed order and the table is reproducible.  Four lanes or more own a token: its coefficients sit in registers, min and max come
 // from lane exchanges, and the errors use the coder's own scalar numerics (fp16 shift rounded down,
 // scale rounded up, code by subtract, multiply by the rounded reciprocal, round to even, clamp),
 // accumulated in double from exactly representable terms.
@@ -144,9 +144,10 @@ __device__ __forceinline__ void block_error(const float* coef, int64_t t_begin, 
     }
 }
 
-// Grid in z: parts 0 to 3 are the halves of the halved blocks, ahead of everything else -- a block of more than 256 coordinates has a workgroup
-// per half and width, or its workgroups would be the tail of the launch --, part 4 all others (the only part where nothing is halved).
-constexpr int kCalibParts = 5;
+// Grid in z: parts 0 to 2 W - 1 are the halves of the halved blocks, ahead of everything else -- a block of more than 256 coordinates has a workgroup
+// per half and width, or its workgroups would be the tail of the launch --, the last part all others (the only part where nothing is halved).
+// (A part more costs a microsecond for 400 workgroups that find nothing to do.)
+template <int W> constexpr int kCalibParts = 2 * W + 1;
 // Blocks of more than 64 coordinates are cut in two halves of the tokens, whose sums are ADDED to the zeroed result: with
 // two terms on top of zero the order of arrival cannot show, so the table stays reproducible.  Not where all tokens fit one step of
 // such a block's lane groups: a half would take as long as the whole, and the launch that zeroes would be a quarter of the call
@@ -163,6 +164,18 @@ __global__ void __launch_bounds__(256) calib_zero_kernel(double* change, int64_t
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) change[i] = 0.0;
 }
 
+// block_error of a block of at most 256 coordinates
+template <int W>
+__device__ __forceinline__ void short_block_error(const float* coef, int64_t b, int64_t m, int64_t ld, int start, int n, int bits, double (&e)[W]) {
+    if (n <= 16) {
+        if (n == 16) block_error<4, 4, true>(coef, b, m, ld, start, n, bits, e); else block_error<4, 4, false>(coef, b, m, ld, start, n, bits, e);
+    } else if (n <= 64) {
+        if (n == 64) block_error<4, 16, true>(coef, b, m, ld, start, n, bits, e); else block_error<4, 16, false>(coef, b, m, ld, start, n, bits, e);
+    } else {
+        if (n == 256) block_error<16, 16, true>(coef, b, m, ld, start, n, bits, e); else block_error<16, 16, false>(coef, b, m, ld, start, n, bits, e);
+    }
+}
+
 // change[block][b - 1] = sum over tokens and the block's coordinates of (d - d_hat)^2 - d^2.  Grid: (block, W widths, part).
 // What bounds it is vector arithmetic (per coefficient: six fp32 instructions and one in fp64 for both widths, four and four for each).
 // 175 blocks x 8 widths x 2048 tokens (the default set at 1024 features): 4.59 ms with
@@ -174,16 +187,16 @@ __global__ void __launch_bounds__(kCalibThreads) calib_block_errors_kernel(const
                                                                           int max_bits, double* change) {
     __shared__ double red[W][kCalibThreads];
     const kvtc_calib_block blk = blocks[blockIdx.x];
-    const int start = blk.start, n = blk.n, bits = W * (int)blockIdx.y + 1, part = gridDim.z == 1 ? kCalibParts - 1 : (int)blockIdx.z;
+    const int start = blk.start, n = blk.n, bits = W * (int)blockIdx.y + 1, part = gridDim.z == 1 ? kCalibParts<W> - 1 : (int)blockIdx.z;
     double* out = change + (size_t)blockIdx.x * max_bits + bits - 1;
-    const int n_out = min(W, max_bits - (bits - 1));      // (an odd number of widths: the last workgroup's second one is not stored)
+    const int n_out = min(W, max_bits - (bits - 1));      // (an odd number of widths: the last workgroup has one)
     // the list lives on the device, out of the host's sight: a block outside a row (or longer than a lane group holds) gets NaN
     if (calib_bad_block(blk, ld)) {
-        if ((int)threadIdx.x < n_out && part == kCalibParts - 1) out[threadIdx.x] = __builtin_nan("");
+        if ((int)threadIdx.x < n_out && part == kCalibParts<W> - 1) out[threadIdx.x] = __builtin_nan("");
         return;
     }
     const bool halved = gridDim.z != 1 && calib_halved(blk, n_tokens), alone = halved && n > 256;          // alone: one width
-    if (halved != (part < kCalibParts - 1) || (part >= 2 && halved && !alone)) return;
+    if (halved != (part < kCalibParts<W> - 1) || (part >= 2 && halved && !alone)) return;
     const int w0 = alone ? part / 2 : 0, w1 = alone ? w0 + 1 : n_out;      // the widths this workgroup stores
     if (w0 >= n_out) return;
     const int64_t half = halved ? (n_tokens + 1) / 2 : n_tokens, b = halved && part % 2 ? half : 0, m = halved && part % 2 ? n_tokens : half;
@@ -197,12 +210,12 @@ __global__ void __launch_bounds__(kCalibThreads) calib_block_errors_kernel(const
             if (n == 1024) block_error<64, 16, true>(coef, b, m, ld, start, n, bits + w, one); else block_error<64, 16, false>(coef, b, m, ld, start, n, bits + w, one);
             (w == 0 ? e[0] : e[W - 1]) = one[0];
         }
-    } else if (n <= 16) {
-        if (n == 16) block_error<4, 4, true>(coef, b, m, ld, start, n, bits, e); else block_error<4, 4, false>(coef, b, m, ld, start, n, bits, e);
-    } else if (n <= 64) {
-        if (n == 64) block_error<4, 16, true>(coef, b, m, ld, start, n, bits, e); else block_error<4, 16, false>(coef, b, m, ld, start, n, bits, e);
+    } else if (W == 1 || n_out == W) {
+        short_block_error<W>(coef, b, m, ld, start, n, bits, e);
     } else {
-        if (n == 256) block_error<16, 16, true>(coef, b, m, ld, start, n, bits, e); else block_error<16, 16, false>(coef, b, m, ld, start, n, bits, e);
+        double one[1];
+        short_block_error<1>(coef, b, m, ld, start, n, bits, one);
+        e[0] = one[0];
     }
     // fixed-order reduction over the workgroup
 #pragma unroll
@@ -417,13 +430,15 @@ kvtc_status kvtc_calib_block_errors(const float* coef_dev, int64_t n_tokens, int
     const bool halves = n_tokens > kCalibHalveAbove;
     if (halves)
         hipLaunchKernelGGL(calib_zero_kernel, dim3((unsigned)(n_out < 262144 ? (n_out + 255) / 256 : 1024)), dim3(256), 0, static_cast<hipStream_t>(stream), change_dev, n_out);
-    // two widths to a workgroup, unless the compute units take a workgroup each with one (13 blocks x 8 widths: 25 us with two, 18 with one; 30 blocks: 45 and 32)
-    const int widths = (int64_t)n_blocks * max_bits <= compute_units() ? 1 : 2;
+    // two widths to a workgroup (the last one's alone where their number is odd), unless there is one or the compute units take a workgroup each with one
+    // (13 blocks x 8 widths: 25 us with two, 18 with one; 30 blocks: 45 and 32; 300 blocks of 256 coordinates x 1 width x 2048 tokens: 132 with two, 87
+    // with one; 175 blocks x 5 widths x 150 tokens: 39.1 with six widths evaluated, 32.8 with five)
+    const int widths = max_bits == 1 || (int64_t)n_blocks * max_bits <= compute_units() ? 1 : 2;
     void (*const fn)(const float*, int64_t, int64_t, const kvtc_calib_block*, int, double*) = widths == 1 ? &calib_block_errors_kernel<1> : &calib_block_errors_kernel<2>;
     // a launch has fewer than 2^32 threads across: beyond 2^22 - 1 blocks of 1024 threads the list takes several
     for (int64_t at = 0; at < n_blocks; at += kCalibMaxBlocks) {
         const int n = n_blocks - at < kCalibMaxBlocks ? (int)(n_blocks - at) : kCalibMaxBlocks;
-        hipLaunchKernelGGL(fn, dim3((unsigned)n, (unsigned)((max_bits + widths - 1) / widths), halves ? kCalibParts : 1), dim3(kCalibThreads), 0, static_cast<hipStream_t>(stream), coef_dev, n_tokens, ld,
+        hipLaunchKernelGGL(fn, dim3((unsigned)n, (unsigned)((max_bits + widths - 1) / widths), halves ? 2 * widths + 1 : 1), dim3(kCalibThreads), 0, static_cast<hipStream_t>(stream), coef_dev, n_tokens, ld,
                            blocks_dev + at, max_bits, change_dev + at * max_bits);
     }
     const hipError_t err = hipGetLastError();
