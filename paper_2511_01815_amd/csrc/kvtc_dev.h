@@ -324,37 +324,54 @@ __device__ __forceinline__ PlanDec load_plan_dec(const PlanDev* P) {
     return d;
 }
 
-// The fields of a plan descriptor the encode kernel uses, in scalar registers.
+// The fields of a plan descriptor the encode kernels use, in scalar registers; SHORT: with those that only the short-job kernels look at.  (An
+// output of the statement is loaded and kept whether or not it is used, and scalar registers are short in the bulk kernels: with one list for
+// both, 13 of the 25 dwords that a bulk tile asked for were dead; two tensors of 131072 tokens at 20x, encode and decode, 339.7 us so and 337.3 now.)
 struct PlanEnc {
-    int32_t p, n_groups, rec_dwords, enc_ntw, enc_wc, code_bits_max, enc_wgs, enc_nw, enc_short;
+    int32_t p, n_groups, rec_dwords, code_bits_max;
+    int32_t enc_ntw, enc_wc, enc_wgs, enc_nw, enc_short;     // SHORT
     const uint4* v_enc;
     const float* negc;
     const uint32_t* blk;
     const uint32_t* grp;
 };
-__device__ __forceinline__ PlanEnc load_plan_enc(const PlanDev* P) {
-    static_assert(offsetof(PlanDev, n_groups) == 8 && offsetof(PlanDev, enc_ntw) == 20 && offsetof(PlanDev, enc_wc) == 24, "descriptor layout");
+template <bool SHORT> __device__ __forceinline__ PlanEnc load_plan_enc(const PlanDev* P) {
+    static_assert(offsetof(PlanDev, p) == 0 && offsetof(PlanDev, n_groups) == 8 && offsetof(PlanDev, rec_dwords) == 16 && offsetof(PlanDev, enc_ntw) == 20 && offsetof(PlanDev, enc_wc) == 24, "descriptor layout");
     static_assert(offsetof(PlanDev, code_bits_max) == 60 && offsetof(PlanDev, enc_wgs) == 64 && offsetof(PlanDev, enc_nw) == 72 && offsetof(PlanDev, enc_short) == 76 && offsetof(PlanDev, v_enc) == 88 &&
                   offsetof(PlanDev, negc) == 104 && offsetof(PlanDev, blk) == 120 && offsetof(PlanDev, grp) == 128, "descriptor layout");
-    // (the lines of the descriptor that are used, not all of it: scalar registers are short in the bulk kernels)
-    u32x8 f, q;
-    u32x4 w, t;
-    uint32_t m;
-    asm volatile("s_load_dwordx8 %0, %5, 0x0\n\ts_load_dword %4, %5, 0x3c\n\ts_load_dwordx4 %2, %5, 0x40\n\ts_load_dwordx8 %1, %5, 0x58\n\t"
-                 "s_load_dwordx4 %3, %5, 0x78\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&s"(f), "=&s"(q), "=&s"(w), "=&s"(t), "=&s"(m) : "s"(uniform_ptr(reinterpret_cast<const char*>(P))) : "memory");
+    const char* from = uniform_ptr(reinterpret_cast<const char*>(P));
     PlanEnc d;
-    d.p = (int32_t)f[0];
-    d.n_groups = (int32_t)f[2];
-    d.rec_dwords = (int32_t)f[4];
-    d.enc_ntw = (int32_t)f[5];
-    d.enc_wc = (int32_t)f[6];
-    d.code_bits_max = (int32_t)m;
-    d.enc_wgs = (int32_t)w[0];
-    d.enc_nw = (int32_t)w[2];
-    d.enc_short = (int32_t)w[3];
-    d.v_enc = ptr_of<const uint4>(q[0], q[1]);
-    d.negc = ptr_of<const float>(q[4], q[5]);
+    u32x4 t;
+    u32x2 v, c;
+    if constexpr (SHORT) {
+        u32x8 f;
+        u32x4 w;
+        uint32_t m;
+        asm volatile("s_load_dwordx8 %0, %6, 0x0\n\ts_load_dword %1, %6, 0x3c\n\ts_load_dwordx4 %2, %6, 0x40\n\ts_load_dwordx2 %3, %6, 0x58\n\t"
+                     "s_load_dwordx2 %4, %6, 0x68\n\ts_load_dwordx4 %5, %6, 0x78\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&s"(f), "=&s"(m), "=&s"(w), "=&s"(v), "=&s"(c), "=&s"(t) : "s"(from) : "memory");
+        d.p = (int32_t)f[0];
+        d.n_groups = (int32_t)f[2];
+        d.rec_dwords = (int32_t)f[4];
+        d.enc_ntw = (int32_t)f[5];
+        d.enc_wc = (int32_t)f[6];
+        d.code_bits_max = (int32_t)m;
+        d.enc_wgs = (int32_t)w[0];
+        d.enc_nw = (int32_t)w[2];
+        d.enc_short = (int32_t)w[3];
+    } else {
+        uint32_t p, g, rd, m;
+        asm volatile("s_load_dword %0, %7, 0x0\n\ts_load_dword %1, %7, 0x8\n\ts_load_dword %2, %7, 0x10\n\ts_load_dword %3, %7, 0x3c\n\t"
+                     "s_load_dwordx2 %4, %7, 0x58\n\ts_load_dwordx2 %5, %7, 0x68\n\ts_load_dwordx4 %6, %7, 0x78\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&s"(p), "=&s"(g), "=&s"(rd), "=&s"(m), "=&s"(v), "=&s"(c), "=&s"(t) : "s"(from) : "memory");
+        d.p = (int32_t)p;
+        d.n_groups = (int32_t)g;
+        d.rec_dwords = (int32_t)rd;
+        d.code_bits_max = (int32_t)m;
+        d.enc_ntw = d.enc_wc = d.enc_wgs = d.enc_nw = d.enc_short = 0;
+    }
+    d.v_enc = ptr_of<const uint4>(v[0], v[1]);
+    d.negc = ptr_of<const float>(c[0], c[1]);
     d.blk = ptr_of<const uint32_t>(t[0], t[1]);
     d.grp = ptr_of<const uint32_t>(t[2], t[3]);
     return d;

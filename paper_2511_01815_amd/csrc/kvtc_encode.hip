@@ -417,7 +417,7 @@ __global__ void __launch_bounds__(NW * 64, (enc_wgs_per_cu<WC, NTW, NW>())) kvtc
     const TileRange mine = my_tiles(total);
     for (uint32_t tile = mine.first; tile < mine.end; tile += mine.step) {
         const TileRef tr = find_tile(a, tile_start, tile);
-        const PlanEnc P = load_plan_enc(a.plans + tr.plan);
+        const PlanEnc P = load_plan_enc<false>(a.plans + tr.plan);
         encode_tile<NTW, WC, XT, NW>(P, tr, a, work);
     }
 }
@@ -670,7 +670,7 @@ __device__ __forceinline__ bool short_tile(const KernelArgs& a, uint32_t number,
         tr.offset = ((uint64_t)v.two[1] << 32) | v.two[0];
         if (tr.plan < 0 || tr.plan >= a.n_plans || tr.n_tokens <= tr.tile * kEncShortTile || (!TABLE && tr.n_tokens > a.enc_short_max)) return false;
     }
-    P = load_plan_enc(a.plans + tr.plan);
+    P = load_plan_enc<true>(a.plans + tr.plan);
     if (P.enc_short != NTW) return false;
     if (TABLE || a.jobs) {
         // (one branch for the wave, which only this tells the compiler: as a choice per lane it cost the main loop of the wide form 3 %)
