@@ -82,13 +82,16 @@ def test_moments_at_strip_and_token_edges(n_tok, p):
         assert np.all(np.abs(g.cpu().numpy() - x64.T @ x64) <= n_tok * 2.0 ** -52 * (np.abs(x64).T @ np.abs(x64)))
 
 
-@pytest.mark.parametrize("n_tok", [1, 5, 200])
-def test_blocks_with_coefficients_that_are_not_finite_come_out_as_nan(n_tok):
+@pytest.mark.parametrize("n_tok,long_list", [(1, False), (5, False), (200, False), (259, False), (5, True), (259, True)])
+def test_blocks_with_coefficients_that_are_not_finite_come_out_as_nan(n_tok, long_list):
     """The squared error and the energy of such a block are both infinite, so their difference is not a number -- for every block that
-    holds the coefficient, in any lane group, at any width and wherever the token stands, and for no other block."""
+    holds the coefficient, in any lane group, at any width and wherever the token stands, and for no other block.  259 tokens: all blocks of more than
+    64 coordinates in halves, the first of which ends at the middle token.  A long list: two widths to a workgroup."""
     ld = 1100
     rng = np.random.default_rng(n_tok)
     cand = [(s, n) for n in (3, 16, 40, 64, 200, 256, 300, 1024) for s in (0, 16, ld - n)]
+    if long_list:
+        cand *= torch.cuda.get_device_properties(0).multi_processor_count // (8 * len(cand)) + 1
     blocks = torch.tensor(cand, dtype=torch.int32, device=DEV)
     P = rng.standard_normal((n_tok, ld)).astype(np.float32)
 
@@ -113,11 +116,45 @@ def test_blocks_with_coefficients_that_are_not_finite_come_out_as_nan(n_tok):
     assert np.all(np.isfinite(table(big)))
 
 
+def _features_of_split(parts):
+    """The smallest number of features whose tiles, or those of its last round, run in this many parts."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for p in range(192, 4096, 64):
+        rest = (p // 32) * (p // 32 + 1) // 2 % cus
+        if parts == (4 if rest * 4 <= cus else 2 if rest * 2 <= cus else 1):
+            return p
+    raise AssertionError(parts)
+
+
 @pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
-def test_moments_into_buffers_that_are_8_byte_aligned_only(dtype):
+@pytest.mark.parametrize("parts", [1, 2, 4])
+def test_moments_of_whole_tiles_halves_and_quarters(parts, dtype):
+    """The number of features decides whether tiles run whole or in parts: every form against double precision, for rows with a pitch and, the same
+    bits, heads-major."""
+    n_tok, p, block = 131, _features_of_split(parts), 64
+    x = torch.randn((n_tok, p + 8), generator=torch.Generator(device=DEV).manual_seed(p), device=DEV)
+    x = x.to(torch.bfloat16) if dtype == kv.KVTC_BF16 else x
+    heads = x[:, :p].reshape(n_tok, p // block, block).transpose(0, 1).contiguous()
+    got = []
+    for buf, lay in ((x, kv.layout(p + 8)), (heads, kv.layout(block, block, n_tok * block))):
+        s = torch.full((p,), -7.0, dtype=torch.float64, device=DEV)
+        g = torch.full((p, p), -7.0, dtype=torch.float64, device=DEV)
+        kv.kvtc_calib_moments(buf, dtype, n_tok, p, lay, s, g)
+        torch.cuda.synchronize()
+        got.append((s, g))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    x64 = x.double().cpu().numpy()[:, :p]
+    # double-precision sums of n_tok terms: n_tok * 2^-53 of the sum of magnitudes at most
+    assert np.all(np.abs(got[0][0].cpu().numpy() - x64.sum(0)) <= n_tok * 2.0 ** -52 * np.abs(x64).sum(0))
+    assert np.all(np.abs(got[0][1].cpu().numpy() - x64.T @ x64) <= n_tok * 2.0 ** -52 * (np.abs(x64).T @ np.abs(x64)))
+
+
+@pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
+@pytest.mark.parametrize("parts", [1, 2, 4])
+def test_moments_into_buffers_that_are_8_byte_aligned_only(parts, dtype):
     """sum_dev and gram_dev need 8-byte alignment, no more: results one double past a 16-byte boundary are the same bits, and
-    nothing around them is written."""
-    n_tok, p = 77, 192
+    nothing around them is written (whole tiles and halves store pairs, quarters single entries)."""
+    n_tok, p = 77, _features_of_split(parts)
     x = torch.randn((n_tok, p), generator=torch.Generator(device=DEV).manual_seed(4), device=DEV)
     x = x.to(torch.bfloat16) if dtype == kv.KVTC_BF16 else x
 
