@@ -127,6 +127,16 @@ kvtc_status kvtc_decode(const kvtc_plan* plan, const void* in_dev, size_t in_byt
  * where the 64-token tiles that each of the n_jobs may then have all run at once -- one job of up to
  * 16384 or 32768 tokens, 64 jobs of up to 256 or 512, by the plans' widths -- unless a longer job of
  * the same variant runs anyway and has room for them; a job's records do not depend on its kernel).
+ * The lengths are on the device; what the host knows of them is that the jobs fit the stream buffer.
+ * Where that is enough, a small batch is cheaper, so size out_cap and in_bytes by what the jobs of the
+ * call can need, if that is little (the results do not depend on them):
+ *   encode  the launches for short jobs alone, if every plan has such a kernel, n_jobs <= 512 and
+ *           out_cap / (64 records of the shortest plan) + n_jobs <= 248, or 504 by the plans' widths
+ *           (256 compute units): 64 tensors with room for up to 184 or 440 tokens each.  With more
+ *           room the launches per variant stand in front, also if they find no job (4 us each): an
+ *           append step into regions of the length of a context pays for them.
+ *   decode  tiles of 128 tokens where they are the faster ones, by the mean room per job, n_jobs and
+ *           the number of plans; plans of more than 320 coordinates excepted.
  * A kvtc_batch makes the plans' descriptors addressable from the device; it copies what it needs,
  * but the plans must outlive it.
  * At most 1024 jobs per call (KVTC_E_UNSUPPORTED beyond).
