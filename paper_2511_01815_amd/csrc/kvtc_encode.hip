@@ -591,8 +591,8 @@ __device__ __forceinline__ uint32_t lane_id() {
 // jobs' lengths are on the device -- is coded by this launch alone.  The tiles of all jobs are numbered through; every wave finds its
 // workgroup's by a prefix sum over the jobs' tiles, a job per lane and round (bounded by the load and six lane exchanges).  Workgroups go
 // round-robin over the eight XCDs, each of which takes an eighth of the tiles, neighbours: the tiles of a job share an L2 and its basis.
-// (With a launch per bulk variant, which found no job, in front of it: an append step of 64 tensors 21.8 us, now 17.9; a head of 4096
-// tokens in fp32, encode and decode, 24.0, now 20.6.)
+// (With a launch per bulk variant, which found no job, in front of it: an append step of 64 tensors 21.8 us, now 16.4; a head of 4096
+// tokens in fp32, encode and decode, 24.0, now 17.9, two of it by the decode's tiles.)
 // KEEP: the lane's number, and with it the addresses of its jobs, may be kept through the loop over tiles.  In fp32 there are no registers for them:
 // with them, and with `upto` left as it is for rounds that a list does not have, up to 18 went to scratch memory, four of them inside the loop over
 // chunks.  (12000 tokens, us, kept and not: fp32, 240 coordinates 22.2 and 19.5; bf16, 160 coordinates, six waves, 13.4 and 15.4.)

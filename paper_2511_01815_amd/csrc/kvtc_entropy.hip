@@ -405,7 +405,7 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
 // (decode_in_pieces).
 // Rows are collected in LDS and stored 64 bytes at a time (stored 16 bytes at a time, straight from the lanes, a line's pieces
 // did not meet in the L2: five times the writes to memory, 0.57 ms).
-// 256 MiB of records of 128 bytes: 777 us with twelve comparisons per symbol, 326 with three and the buffer, 271 now.  Vector instructions: 21 per symbol (34 with the buffer), half of the cycles; the lanes'
+// 256 MiB of records of 128 bytes: 777 us with twelve comparisons per symbol, 326 with three and the buffer, 268 now.  Vector instructions: 21 per symbol (34 with the buffer), half of the cycles; the lanes'
 // 24-byte reads come from the L2, a line as often as it is read, because 16 waves' strings do not fit the L1.
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));       // on any dword boundary
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(4)));
