@@ -21,6 +21,7 @@
 // -> codes -> written into the record image in LDS -> one contiguous, coalesced store of the
 // tile's records.
 #include <hip/hip_runtime.h>
+#include <type_traits>
 #include "kvtc_dev.h"
 #include "kvtc_numeric.h"
 
@@ -66,24 +67,39 @@ __device__ __forceinline__ void put_bits(uint32_t* rec, uint32_t pos, uint32_t v
     if (s + len > 32u) atomicOr(rec + dw + 1, v >> (32u - s));
 }
 
-// The 16 codes of a block, BITS wide each, as a bit string of BITS halfwords written to the record
+// The code of a coefficient as the low bits of a float: with the reciprocal scaled by 2^-bits, (d - shift) / scale lies in [0, 1), and adding
+// 2^(23 - bits), whose last place is 2^-bits, rounds it to nearest even exactly as code_of rounds (a power of two moves no rounding).  The clamp of
+// the multiplication does the rest of code_of: below zero and not a number give 0.  Above the largest code is nothing unless the scale is saturated (such tiles
+// take another way): a scale rounded up covers the group's range.  Four instructions with the one that packs it, where
+// round, clamp and convert to an integer made six.
+__device__ __forceinline__ uint32_t code_float(float d, float shift, float inv_b, float base) {
+    const float t = __builtin_amdgcn_fmed3f(__fmul_rn(__fsub_rn(d, shift), inv_b), 0.0f, 1.0f);
+    return __float_as_uint(__fadd_rn(t, base));
+}
+__host__ __device__ constexpr uint32_t code_base_bits(uint32_t bits) { return (150u - bits) << 23; }      // 2^(23 - bits)
+
+// The 16 codes of a block, BITS wide each and given as code_float makes them, as a bit string of BITS halfwords written to the record
 // image at a halfword address (blocks start and end on halfword boundaries: 16 codes x BITS bits).
-// Plain 16-bit LDS stores: two blocks may share a dword but never a halfword, so nothing is OR-ed
-// and the image needs no clearing.
+// Plain LDS stores: two blocks may share a dword but never a halfword, so nothing is OR-ed
+// and the image needs no clearing.  (Codes are added up, shifted, with the floats' upper bits; what those come to is subtracted at the end.)
 template <int BITS>
-__device__ __forceinline__ void emit_block(const uint32_t (&c)[16], char* dst) {
-    uint32_t q[(BITS + 1) / 2];
+__device__ __forceinline__ void emit_block(const uint32_t (&u)[16], char* dst) {
+    constexpr int ND = (BITS + 1) / 2;
+    constexpr uint32_t BASE = code_base_bits(BITS);
+    uint32_t q[ND], extra[ND];
 #pragma unroll
-    for (int j = 0; j < (BITS + 1) / 2; ++j) q[j] = 0u;
+    for (int j = 0; j < ND; ++j) extra[j] = 0u;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int pos = i * BITS, dw = pos >> 5, sh = pos & 31;
-        q[dw] |= c[i] << sh;
-        if (sh + BITS > 32) q[dw + 1] |= c[i] >> (32 - sh);
+        if (sh == 0) q[dw] = u[i];
+        else asm("v_lshl_add_u32 %0, %1, %2, %0" : "+v"(q[dw]) : "v"(u[i]), "n"(sh));        // (of two of these sums the compiler makes three instructions)
+        extra[dw] += BASE << sh;
+        if (sh + BITS > 32) q[dw + 1] = __builtin_amdgcn_ubfe(u[i], 32 - sh, BITS - (32 - sh));
     }
 #pragma unroll
-    for (int j = 0; j < BITS; ++j)
-        *reinterpret_cast<uint16_t*>(dst + 2 * j) = (uint16_t)(q[j >> 1] >> (16 * (j & 1)));
+    for (int j = 0; j < ND; ++j) q[j] -= extra[j];
+    __builtin_memcpy(__builtin_assume_aligned(dst, 2), q, 2 * BITS);
 }
 
 // k-steps (16 features each) per pipeline stage, and stages in the LDS ring.  Sized so that a
@@ -152,6 +168,8 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
     }
     // codes wider than 8 bits are OR-ed into the image (cleared here); the usual widths are stored
     const bool narrow_codes = P.code_bits_max <= 8;
+    uint32_t* saturated = reinterpret_cast<uint32_t*>(work) + kEncNegcOff / 4;       // (-(mu^T V_kept) has been used)
+    if (tid == 0) *saturated = 0u;
     if (!narrow_codes)
         for (int i = tid; i < tok_wg * rstride; i += nth) rec[i] = 0u;
     __syncthreads();
@@ -162,65 +180,85 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
         const uint32_t gi = grp_t[g];
         const int b0 = gi & 0xff, nb = (gi >> 8) & 0xff, bits = (gi >> 16) & 0xff;
         float lo = __builtin_inff(), hi = -__builtin_inff();
-        for (int k = 0; k < nb; ++k) {
-            const float2 m = mm[(b0 + k) * tok_wg + tw];
-            lo = fminf(lo, m.x);
-            hi = fmaxf(hi, m.y);
+        for (int k0 = 0; k0 < nb; k0 += 4) {            // four reads in flight; behind the last block the last one again
+            float2 m[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) m[k] = mm[(b0 + min(k0 + k, nb - 1)) * tok_wg + tw];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                lo = fminf(lo, m[k].x);
+                hi = fmaxf(hi, m[k].y);
+            }
         }
         const GroupQ q = group_header(lo, hi, bits);
-        gq[g * tok_wg + tw] = make_float2(q.shift, q.inv);
+        gq[g * tok_wg + tw] = make_float2(q.shift, __builtin_ldexpf(q.inv, -bits));      // exact
         rec[tw * rstride + g] = (uint32_t)q.shift16 | ((uint32_t)q.scale16 << 16);
+        if (__builtin_expect(q.scale16 == 0x7bffu, 0)) *saturated = 1u;
         if (g == 0 && narrow_codes) rec[tw * rstride + rd - 1] = 0u;      // the padding behind the last block
     }
     __syncthreads();
 
-    // C: codes of the lane's blocks, OR-ed into the record image
+    // C: codes of the lane's blocks, put into the record image.  (The halves of a wave have a block each: one width in most
+    // tiles, two at most.  The choice by width is one for the wave, made for either half in turn -- as a choice per lane it was six levels of masks.)
+    auto codes = [&](auto narrow_tag) {
 #pragma unroll
-    for (int ct = 0; ct < NTW; ++ct) {
-        const uint32_t info = !HELPERS || ct0 < ntp ? blk_t[2 * (ct0 + ct) + h] : 0u;
-        const uint32_t bits = info & 0xffu;
-        if (bits != 0u) {
+        for (int ct = 0; ct < NTW; ++ct) {
+            const uint32_t info = !HELPERS || ct0 < ntp ? blk_t[2 * (ct0 + ct) + h] : 0u;
+            const uint32_t bits = info & 0xffu;
+            const uint32_t bits0 = (uint32_t)__builtin_amdgcn_readlane((int)bits, 0), bits1 = (uint32_t)__builtin_amdgcn_readlane((int)bits, 32);
+            if ((bits0 | bits1) == 0u) continue;
             const uint32_t g = (info >> 8) & 0xffu;
             const uint32_t pos0 = (info >> 16) * 16u;
-            const float qmax = (float)((1u << bits) - 1u);
+            const float base = __uint_as_float(code_base_bits(bits)), qmax = (float)((1u << bits) - 1u);
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) {
                 const int tw = (tt0 + tt) * 32 + l32;
                 const float2 sq = gq[g * tok_wg + tw];
                 uint32_t* row = rec + tw * rstride;
                 const f32x16& d = acc[tt][ct];
-                uint32_t c[16];
+                uint32_t u[16];
+                if constexpr (decltype(narrow_tag)::value) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) c[i] = (uint32_t)code_of(d[i], sq.x, sq.y, qmax);
-                if (narrow_codes) {
+                    for (int i = 0; i < 16; ++i) u[i] = code_float(d[i], sq.x, sq.y, base);
                     char* dst = reinterpret_cast<char*>(row) + (pos0 >> 3);
-                    switch (bits) {
-                        case 1: emit_block<1>(c, dst); break;
-                        case 2: emit_block<2>(c, dst); break;
-                        case 3: emit_block<3>(c, dst); break;
-                        case 4: emit_block<4>(c, dst); break;
-                        case 5: emit_block<5>(c, dst); break;
-                        case 6: emit_block<6>(c, dst); break;
-                        case 7: emit_block<7>(c, dst); break;
-                        default: emit_block<8>(c, dst); break;
-                    }
-                } else if (bits <= 8u) {
+#pragma unroll 1
+                    for (uint32_t b = bits0;;) {
+                        const bool mine = bits == b;
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const uint32_t v = c[4 * k] | (c[4 * k + 1] << bits) | (c[4 * k + 2] << (2u * bits)) |
-                                           (c[4 * k + 3] << (3u * bits));
-                        put_bits(row, pos0 + 4u * k * bits, v, 4u * bits);
+                        for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(u[i]));      // (or every width's part codes are cut out ahead of the choice)
+                        switch (b) {
+                            case 0: break;
+                            case 1: if (mine) emit_block<1>(u, dst); break;
+                            case 2: if (mine) emit_block<2>(u, dst); break;
+                            case 3: if (mine) emit_block<3>(u, dst); break;
+                            case 4: if (mine) emit_block<4>(u, dst); break;
+                            case 5: if (mine) emit_block<5>(u, dst); break;
+                            case 6: if (mine) emit_block<6>(u, dst); break;
+                            case 7: if (mine) emit_block<7>(u, dst); break;
+                            default: if (mine) emit_block<8>(u, dst); break;
+                        }
+                        if (b == bits1) break;
+                        b = bits1;
                     }
-                } else {
+                } else if (bits != 0u) {
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const uint32_t v = c[2 * k] | (c[2 * k + 1] << bits);
-                        put_bits(row, pos0 + 2u * k * bits, v, 2u * bits);
-                    }
+                    for (int i = 0; i < 16; ++i) u[i] = (uint32_t)code_of(d[i], sq.x, __builtin_ldexpf(sq.y, (int)bits), qmax);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) put_bits(row, pos0 + 2u * k * bits, u[2 * k] | (u[2 * k + 1] << bits), 2u * bits);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+    };
+    if (__builtin_expect(narrow_codes && *saturated == 0u, 1)) {
+        codes(std::true_type());
+    } else {
+        if (narrow_codes) {                  // a scale of 65504: its codes have to be clamped.  (The image has not been cleared.)
+            for (int i = tid; i < tok_wg * rstride; i += nth)
+                if (i % rstride >= G) rec[i] = 0u;
+            __syncthreads();
+        }
+        codes(std::false_type());
     }
     __syncthreads();
 

@@ -1,0 +1,60 @@
+"""Headers and codes at the edges of fp16 and of every width, bit for bit: with unit columns for a basis and no mean a coefficient IS
+its feature, so the records of chosen features are known without a tolerance."""
+import numpy as np
+import pytest
+import torch
+
+import kvtc_oracle as ko
+import paper_2511_01815_amd as kv
+from test_gpu_encode_short import bulk_tokens
+from test_gpu_parity import DEV, _gpu_plan
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(n, p):
+    """Tokens whose values span fp16's normal, subnormal and saturated ranges (bf16 numbers, no -0, nothing bf16 cannot hold as a normal)."""
+    rng = np.random.default_rng(41)
+    x = rng.standard_normal((n, p)) * 10.0 ** rng.uniform(-9, 6, (n, 1))
+    x[::7] = np.abs(x[::7])                                      # shift above zero
+    x[1::7] = -np.abs(x[1::7])
+    x[2::7] += 10.0 ** rng.uniform(-3, 5, (len(x[2::7]), 1))     # a narrow range far from zero
+    x[3::35, :] = x[3::35, :1]                                   # a range of nothing
+    x[8::35, 5] = 3e38                                           # one value beyond any scale
+    x[13::35, 2] = -3e38
+    x[18::35] = np.where(rng.random((len(x[18::35]), p)) < 0.5, 65504.0, -70000.0)
+    x[23::35] *= 1e30
+    x[28::35] = rng.integers(0, 256, (len(x[28::35]), p)) * 0.5  # ties of the code's rounding
+    return torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16).float().numpy() + 0.0
+
+
+@pytest.mark.parametrize("groups", [[(16, 1), (16, 2), (16, 3), (16, 4)], [(16, 5), (16, 6), (16, 7), (16, 8)], [(32, 8), (32, 8)], [(16, 8), (48, 3)],
+                                    [(16, 9), (16, 10), (16, 11), (16, 12)], [(16, 13), (16, 14), (16, 15), (16, 16)], [(48, 4), (16, 13)]])
+def test_records_of_known_coefficients(groups):
+    p, T = 64, bulk_tokens()
+    blocks, at = [], 0
+    for n, b in groups:
+        blocks.append(ko.Block(at, n, b))
+        at += n
+    oplan = ko.compile_plan(np.zeros(p), np.eye(p), blocks)
+    plan = _gpu_plan(oplan)
+    n = 1400
+    x = _rows(n, p)
+    x[-1, 3] = np.nan                                            # every product with it: a token of nothing but NaN
+    with np.errstate(all="ignore"):
+        shift, scale, codes = ko.quantise(oplan, x)
+    want = ko.pack(oplan, shift, scale, codes)
+    # no minimum and no maximum: infinity and its opposite saturate, the scale is negative and the codes are 0
+    shift[-1], scale[-1], codes[-1] = np.float16(65504.0), np.float16(-65504.0), 0
+    want[-1] = ko.pack(oplan, shift[-1:], scale[-1:], codes[-1:])
+    x_dev = torch.from_numpy(x).to(DEV)
+    for tokens in (n, T):                                        # the short-job kernel, the bulk kernel
+        for dtype, src in ((kv.KVTC_F32, x_dev), (kv.KVTC_BF16, x_dev.to(torch.bfloat16))):
+            src = src.repeat(tokens // n + 1, 1)[:tokens].contiguous()
+            out = torch.zeros((tokens, plan.record_bytes), dtype=torch.uint8, device=DEV)
+            kv.kvtc_encode(plan.handle, src, dtype, tokens, p, out, out.numel())
+            got = out.cpu().numpy()
+            bad = np.nonzero((got[:n] != want).any(axis=1))[0]
+            assert bad.size == 0, (tokens, dtype, bad[:5], x[bad[0]], got[bad[0]], want[bad[0]])
+            for t0 in range(n, tokens - n + 1, n):
+                assert np.array_equal(got[t0:t0 + n], want), (tokens, dtype, t0)
