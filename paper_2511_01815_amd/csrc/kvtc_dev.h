@@ -328,7 +328,7 @@ __device__ __forceinline__ PlanDec load_plan_dec(const PlanDev* P) {
 // output of the statement is loaded and kept whether or not it is used, and scalar registers are short in the bulk kernels: with one list for
 // both, 13 of the 25 dwords that a bulk tile asked for were dead; two tensors of 131072 tokens at 20x, encode and decode, 339.7 us so and 337.3 now.)
 struct PlanEnc {
-    int32_t p, n_groups, rec_dwords, code_bits_max;
+    int32_t p, r, n_groups, rec_dwords, code_bits_max;
     int32_t enc_ntw, enc_wc, enc_wgs, enc_nw, enc_short;     // SHORT
     const uint4* v_enc;
     const float* negc;
@@ -336,7 +336,7 @@ struct PlanEnc {
     const uint32_t* grp;
 };
 template <bool SHORT> __device__ __forceinline__ PlanEnc load_plan_enc(const PlanDev* P) {
-    static_assert(offsetof(PlanDev, p) == 0 && offsetof(PlanDev, n_groups) == 8 && offsetof(PlanDev, rec_dwords) == 16 && offsetof(PlanDev, enc_ntw) == 20 && offsetof(PlanDev, enc_wc) == 24, "descriptor layout");
+    static_assert(offsetof(PlanDev, p) == 0 && offsetof(PlanDev, r) == 4 && offsetof(PlanDev, n_groups) == 8 && offsetof(PlanDev, rec_dwords) == 16 && offsetof(PlanDev, enc_ntw) == 20 && offsetof(PlanDev, enc_wc) == 24, "descriptor layout");
     static_assert(offsetof(PlanDev, code_bits_max) == 60 && offsetof(PlanDev, enc_wgs) == 64 && offsetof(PlanDev, enc_nw) == 72 && offsetof(PlanDev, enc_short) == 76 && offsetof(PlanDev, v_enc) == 88 &&
                   offsetof(PlanDev, negc) == 104 && offsetof(PlanDev, blk) == 120 && offsetof(PlanDev, grp) == 128, "descriptor layout");
     const char* from = uniform_ptr(reinterpret_cast<const char*>(P));
@@ -351,6 +351,7 @@ template <bool SHORT> __device__ __forceinline__ PlanEnc load_plan_enc(const Pla
                      "s_load_dwordx2 %4, %6, 0x68\n\ts_load_dwordx4 %5, %6, 0x78\n\ts_waitcnt lgkmcnt(0)"
                      : "=&s"(f), "=&s"(m), "=&s"(w), "=&s"(v), "=&s"(c), "=&s"(t) : "s"(from) : "memory");
         d.p = (int32_t)f[0];
+        d.r = (int32_t)f[1];
         d.n_groups = (int32_t)f[2];
         d.rec_dwords = (int32_t)f[4];
         d.enc_ntw = (int32_t)f[5];
@@ -360,11 +361,13 @@ template <bool SHORT> __device__ __forceinline__ PlanEnc load_plan_enc(const Pla
         d.enc_nw = (int32_t)w[2];
         d.enc_short = (int32_t)w[3];
     } else {
-        uint32_t p, g, rd, m;
-        asm volatile("s_load_dword %0, %7, 0x0\n\ts_load_dword %1, %7, 0x8\n\ts_load_dword %2, %7, 0x10\n\ts_load_dword %3, %7, 0x3c\n\t"
+        uint32_t g, rd, m;
+        u32x2 p;
+        asm volatile("s_load_dwordx2 %0, %7, 0x0\n\ts_load_dword %1, %7, 0x8\n\ts_load_dword %2, %7, 0x10\n\ts_load_dword %3, %7, 0x3c\n\t"
                      "s_load_dwordx2 %4, %7, 0x58\n\ts_load_dwordx2 %5, %7, 0x68\n\ts_load_dwordx4 %6, %7, 0x78\n\ts_waitcnt lgkmcnt(0)"
                      : "=&s"(p), "=&s"(g), "=&s"(rd), "=&s"(m), "=&s"(v), "=&s"(c), "=&s"(t) : "s"(from) : "memory");
-        d.p = (int32_t)p;
+        d.p = (int32_t)p[0];
+        d.r = (int32_t)p[1];
         d.n_groups = (int32_t)g;
         d.rec_dwords = (int32_t)rd;
         d.code_bits_max = (int32_t)m;

@@ -120,6 +120,24 @@ __host__ __device__ constexpr int enc_stages(int ntp, int elem_bytes, int nw, in
     return n < 2 ? 2 : (n > 4 ? 4 : n);
 }
 
+// Fewest coordinate tiles worked on for a plan that runs as ntp of them (the padding is left out in the variants of 6, 8 and 10), and what
+// follows for the transfers of a stage's basis pieces: whether every wave has an i-th one whatever the plan, and how many a wave has at least.
+__host__ __device__ constexpr int enc_min_tiles(int ntp) { return ntp > 4 && ntp <= 10 ? ntp - 1 : ntp; }
+template <int NTP, int NW, int TOTAL> __host__ __device__ constexpr bool enc_basis_pieces(int i) {
+    for (int w = 0; w < NW; ++w)
+        if (i * NW + w >= TOTAL || (i * NW + w) % NTP >= enc_min_tiles(NTP)) return false;
+    return true;
+}
+template <int NTP, int NW, int TOTAL> __host__ __device__ constexpr int enc_least_pieces() {
+    int least = TOTAL;
+    for (int w = 0; w < NW; ++w) {
+        int n = 0;
+        for (int i = w; i < TOTAL; i += NW) n += i % NTP < enc_min_tiles(NTP);
+        least = n < least ? n : least;
+    }
+    return least;
+}
+
 // LDS work area (behind the job table): [tables of the tile's plan: block table 64 dwords, group
 // table 64 dwords, -(mu^T V_kept) of the padded coordinates][ring / epilogue images].  The tables
 // arrive by asynchronous transfers at the start of a tile, ahead of the first ring stage, so
@@ -129,11 +147,11 @@ constexpr int kEncBlkOff = 0, kEncGrpOff = 256, kEncNegcOff = 512;
 __host__ __device__ constexpr int enc_aux_bytes(int ntp) { return 512 + ntp * 32 * 4; }
 
 // From a workgroup's coefficients (accumulator tiles of 32 coordinates x 32 tokens, a lane holding 16 consecutive coordinates of a
-// token) to records in the stream.  Every wave of the workgroup calls it: ct0 = the wave's first coordinate tile (HELPERS: a wave
-// whose first tile lies beyond the plan's ntp only helps with the headers and the copy), tt0 = its first of TT token tiles;
+// token) to records in the stream.  Every wave of the workgroup calls it: ct0 = the wave's first coordinate tile, n_ct = how many it has (NTW or one
+// fewer; HELPERS: any number, a wave with none only helps with the headers and the copy), tt0 = its first of TT token tiles;
 // tok_n tokens of the images' pitch tok_wg are worked on.  LDS: the plan's tables at `work`, the images at `smem`.
 template <int NTW, int TT, bool HELPERS>
-__device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], int ct0, int tt0, int tok_n, int tok_wg, int ntp, int nth,
+__device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], int ct0, int n_ct, int tt0, int tok_n, int tok_wg, int ntp, int nth,
                                                 const PlanEnc& P, const TileRef& tr, const KernelArgs& a, int tok_tile0, uint4* work, uint4* smem) {
     // (through an empty asm, so that nothing of the epilogue's lane addresses is worked out ahead of the main loop and kept
     // through it: its registers are all taken)
@@ -154,10 +172,10 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
     // A: block min/max
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
-        if (HELPERS && ct0 >= ntp) continue;
         const int tw = (tt0 + tt) * 32 + l32;
 #pragma unroll
         for (int ct = 0; ct < NTW; ++ct) {
+            if (ct >= (HELPERS ? 0 : NTW - 1) && ct >= n_ct) continue;
             const f32x16& d = acc[tt][ct];
             float lo = d[0], hi = d[0];
 #pragma unroll
@@ -203,7 +221,8 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
     auto codes = [&](auto narrow_tag) {
 #pragma unroll
         for (int ct = 0; ct < NTW; ++ct) {
-            const uint32_t info = !HELPERS || ct0 < ntp ? blk_t[2 * (ct0 + ct) + h] : 0u;
+            if (ct >= (HELPERS ? 0 : NTW - 1) && ct >= n_ct) continue;
+            const uint32_t info = blk_t[2 * (ct0 + ct) + h];
             const uint32_t bits = info & 0xffu;
             const uint32_t bits0 = (uint32_t)__builtin_amdgcn_readlane((int)bits, 0), bits1 = (uint32_t)__builtin_amdgcn_readlane((int)bits, 32);
             if ((bits0 | bits1) == 0u) continue;
@@ -300,7 +319,14 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     constexpr int SLAB_U4 = KS * NTP * 64;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wc = wave % WC, wt = wave / WC;
+    const int wt = wave / WC;
+    // The plan's coordinate tiles are shared out evenly: a wave has NTW of them or one fewer, whose place it does not multiply, and the padding is
+    // not fetched.  What these kernels have at their disposal is power -- the clock gives way, to 1.5 GHz, under matrix instructions and a stream
+    // from HBM at once --, so work that can be left out counts although it would fit the time (32-layer cache at 16x, plans of 7, 8 and 9 tiles that
+    // run as 8 and 10: 1283 -> 1256 us).  Not up to four tiles, which are bound by HBM, nor in the 8-wave variants: the conditions cost those 0.5 %.
+    const int nt = enc_min_tiles(NTP) < NTP ? (P.r + 31) / 32 : NTP, wc = wave % WC;
+    const int ct0 = wc * (nt / WC) + min(wc, nt % WC), n_ct = nt / WC + (wc < nt % WC ? 1 : 0);
+    const bool full = enc_min_tiles(NTP) == NTP || n_ct >= NTW;
     const int l32 = lane & 31, h = lane >> 5;
     const int p = P.p;
     const int T = tr.n_tokens;
@@ -327,7 +353,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     constexpr int NXD = (NX_TOTAL + NW - 1) / NW;
     constexpr int NV_TOTAL = SLAB_U4 / 64;                      // basis transfers per stage (1 KB each), dealt the same way
     constexpr int NV = (NV_TOTAL + NW - 1) / NW;
-    constexpr int NDMA_MIN = NV_TOTAL / NW + NX_TOTAL / NW;     // transfers per wave per stage, lower bound over waves
+    constexpr int NDMA_MIN = enc_least_pieces<NTP, NW, NV_TOTAL>() + NX_TOTAL / NW;     // transfers per wave per stage, lower bound over waves and plans
     static_assert(TOK_WG % XS::ROWS_PER_DMA == 0, "whole transfers");
     static_assert(3 * (NV + NXD) < 64, "vmcnt range");
     static_assert(NW >= 2, "waves 0 and 1 fetch the plan's tables");
@@ -365,15 +391,16 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
         const uint4* vsrc = vg + (size_t)s * SLAB_U4;           // scalar addresses plus a lane offset
 #pragma unroll
         for (int i = 0; i < NV; ++i)
-            if (i * NW + wave < NV_TOTAL)
+            if (enc_basis_pieces<NTP, NW, NV_TOTAL>(i) || (i * NW + wave < NV_TOTAL && (i * NW + wave) % NTP < nt))
                 dma16_async(vsrc + i * NTH, (uint32_t)tid * 16u, base + (i * NTH + wave * 64) * 16);
 #pragma unroll
         for (int j = 0; j < NXD; ++j)
-            if (j * NW + wave < NX_TOTAL)
+            if ((j + 1) * NW <= NX_TOTAL || j * NW + wave < NX_TOTAL)
                 dma16_async(xtile + xoff, xsrc[j], base + xdst[j]);
     };
+    // (a wave with a tile fewer than NTW reads the next wave's, or padding, in its place)
     auto compute = [&](int stage) {
-        const uint4* abase = reinterpret_cast<const uint4*>(ring + stage * STAGE_B) + (wc * NTW) * 64 + lane;
+        const uint4* abase = reinterpret_cast<const uint4*>(ring + stage * STAGE_B) + ct0 * 64 + lane;
         const char* xs = ring + stage * STAGE_B + SLAB_U4 * 16;
         constexpr int NSTEP = KS * NTW;
         bf16x8 xv[KS][TT];
@@ -390,9 +417,11 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
             const int ks = j / NTW, ct = j % NTW;
             if (j + 2 < NSTEP) af[(j + 2) % 3] = abase[(((j + 2) / NTW) * NTP + ((j + 2) % NTW)) * 64];
             const bf16x8 av = as_bf16x8(af[j % 3]);
+            if (ct + 1 < NTW || full) {
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
-                acc[tt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, xv[ks][tt], acc[tt][ct], 0, 0, 0);
+                for (int tt = 0; tt < TT; ++tt)
+                    acc[tt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, xv[ks][tt], acc[tt][ct], 0, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -406,7 +435,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
 
     // ---- accumulators start at -(mu^T V_kept): centring folded into the product ------
     {
-        const float* negc = reinterpret_cast<const float*>(work) + kEncNegcOff / 4 + (wc * NTW) * 32 + 16 * h;
+        const float* negc = reinterpret_cast<const float*>(work) + kEncNegcOff / 4 + ct0 * 32 + 16 * h;
 #pragma unroll
         for (int ct = 0; ct < NTW; ++ct) {
             f32x16 c;
@@ -433,7 +462,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
         }
     }
 
-    encode_epilogue<NTW, TT, false>(acc, wc * NTW, wt * TT, TOK_WG, TOK_WG, NTP, NTH, P, tr, a, tok_tile0, work, smem);
+    encode_epilogue<NTW, TT, false>(acc, ct0, n_ct, wt * TT, TOK_WG, TOK_WG, NTP, NTH, P, tr, a, tok_tile0, work, smem);
 }
 
 // One kernel per variant (WC waves across coordinates, NTW coordinate tiles per wave, NW waves per
@@ -488,7 +517,7 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
     const int ntp = P.enc_ntw * P.enc_wc;
     const int p = P.p, T = tr.n_tokens, tok_tile0 = tr.tile * kEncShortTile;
     const int n_steps = p / 16, n_chunks = (p + FEAT - 1) / FEAT;
-    const int ct0 = wave * NTW;
+    const int nt = (P.r + 31) / 32, ct0 = wave * NTW, n_ct = min(max(nt - ct0, 0), NTW);      // (a wave without a tile only helps)
     uint4* smem = work + enc_aux_bytes(ntp) / 16;
 
     // the plan's tables and chunk 0 of X -> LDS
@@ -520,7 +549,7 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
     u32x4 af[AHEAD][NTW];
     typedef const char __attribute__((address_space(1))) * global_ptr;
     typedef const u32x4 __attribute__((address_space(1))) * global_u4;
-    const uint64_t vg = (uint64_t)uniform_ptr(P.v_enc + (ct0 < ntp ? ct0 : 0) * 64);
+    const uint64_t vg = (uint64_t)uniform_ptr(P.v_enc + (n_ct > 0 ? ct0 : 0) * 64);
     auto fetch = [&](int step, int slot) {
         const global_ptr src = (global_ptr)(vg + (uint64_t)(uint32_t)min(step, n_steps - 1) * (uint64_t)(uint32_t)(ntp * 1024));      // a scalar address
 #pragma unroll
@@ -534,7 +563,7 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
 
     f32x16 acc[TT][NTW];
     {
-        const float* negc = reinterpret_cast<const float*>(work) + kEncNegcOff / 4 + (ct0 < ntp ? ct0 : 0) * 32 + 16 * h;
+        const float* negc = reinterpret_cast<const float*>(work) + kEncNegcOff / 4 + (n_ct > 0 ? ct0 : 0) * 32 + 16 * h;
 #pragma unroll
         for (int ct = 0; ct < NTW; ++ct) {
             f32x16 c;
@@ -615,7 +644,7 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
         __syncthreads();
     }
     wait_vmem<0>();                                                  // the fragments fetched past the end
-    encode_epilogue<NTW, TT, true>(acc, ct0, 0, ROWS, kEncShortTile, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem);
+    encode_epilogue<NTW, TT, true>(acc, ct0, n_ct, 0, ROWS, kEncShortTile, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem);
 }
 
 // the lane's number, worked out where it is used and not kept through a loop
