@@ -23,6 +23,7 @@ namespace kvtc {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2_d __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ bf16x8 as_bf16x8_d(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -114,27 +115,39 @@ __device__ __forceinline__ int issue_records(const KernelArgs& a, const TileRef&
     return n;
 }
 
-// The 16 values of a record's block (its width, group and first bit as in the block table) as bf16 pairs; a block without bits gives zeros.
-// Codes of up to 8 bits (kNarrow) come four to a 32-bit window, wider ones two.
-template <bool kNarrow>
-__device__ __forceinline__ void unpack_block(const uint32_t* row, uint32_t bits, uint32_t g, uint32_t pos0, uint32_t (&q)[8]) {
-    constexpr int PER = kNarrow ? 4 : 2;                   // codes per window
-    const uint32_t hdr = bits != 0u ? row[g] : 0u;      // a block without bits decodes to zeros
-    const float shift = f16_bits_to_f32((uint16_t)(hdr & 0xffffu));
-    const float scale = f16_bits_to_f32((uint16_t)(hdr >> 16));
+// A record's block (its width, group and first bit as in the block table): the dwords its 16 codes lie in and its header; then its values as bf16
+// pairs (a block without bits gives zeros).  Codes of up to 8 bits (kNarrow) come four to a 32-bit window, wider ones two.  Reading and converting
+// are apart, so that the reads of the next block travel under the conversions of this one (in turn, each window waited for its own read).
+template <bool kNarrow> struct RecBlock {
+    static constexpr int PER = kNarrow ? 4 : 2, N = 16 / PER;      // codes per window, windows
+    uint32_t bits, pos0, hdr, lo[N], hi[N];
+    __device__ __forceinline__ void read(const uint32_t* row, uint32_t info) {
+        bits = info & 0xffu;
+        pos0 = (info >> 16) * 16u;
+        hdr = row[(info >> 8) & 0xffu];
 #pragma unroll
-    for (int k = 0; k < 16 / PER; ++k) {
-        const uint32_t pos = pos0 + (uint32_t)(PER * k) * bits;
-        const uint32_t dw = pos >> 5;
-        const uint32_t w = __builtin_amdgcn_alignbit(row[dw + 1], row[dw], pos & 31u);
-#pragma unroll
-        for (int m = 0; m < PER; m += 2) {
-            const float d0 = __fmaf_rn((float)__builtin_amdgcn_ubfe(w, m * bits, bits), scale, shift);
-            const float d1 = __fmaf_rn((float)__builtin_amdgcn_ubfe(w, (m + 1) * bits, bits), scale, shift);
-            q[(PER * k + m) / 2] = pack_bf16x2(d0, d1);
+        for (int k = 0; k < N; ++k) {
+            const uint32_t dw = (pos0 + (uint32_t)(PER * k) * bits) >> 5;
+            lo[k] = row[dw];
+            hi[k] = row[dw + 1];
         }
     }
-}
+    __device__ __forceinline__ void values(uint32_t (&q)[8]) const {
+        const uint32_t head = bits != 0u ? hdr : 0u;
+        const float shift = (float)__builtin_bit_cast(_Float16, (uint16_t)head);
+        const float scale = (float)__builtin_bit_cast(_Float16, (uint16_t)(head >> 16));
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const uint32_t w = __builtin_amdgcn_alignbit(hi[k], lo[k], (pos0 + (uint32_t)(PER * k) * bits) & 31u);
+#pragma unroll
+            for (int m = 0; m < PER; m += 2) {
+                const float d0 = __fmaf_rn((float)__builtin_amdgcn_ubfe(w, m * bits, bits), scale, shift);
+                const float d1 = __fmaf_rn((float)__builtin_amdgcn_ubfe(w, (m + 1) * bits, bits), scale, shift);
+                q[(PER * k + m) / 2] = pack_bf16x2(d0, d1);
+            }
+        }
+    }
+};
 
 
 // The earlier sections' sum for accumulator register i of token tile tt: the lane's two features (rows past the end: the last row's).
@@ -146,7 +159,7 @@ __device__ __forceinline__ float2 load_part(const char* sb, uint32_t lrow, int t
 // The results of a pair of feature tiles (acc0: the even, acc1: the odd features of 64-feature span `span`) to the output.
 template <int TT, typename OT, int ACC>
 __device__ __forceinline__ void store_pair(const KernelArgs& a, const TileRef& tr, const f32x16 (&acc0)[TT], const f32x16 (&acc1)[TT], char* obase, int span,
-                                           uint32_t lane_row, uint32_t lane_col, uint32_t last_row, int tok_tile0) {
+                                           uint32_t lane_row, uint32_t lane_col, uint32_t last_row, uint32_t tok_rows, int tok_tile0) {
     const uint32_t ldb = (uint32_t)a.ld_x * (uint32_t)sizeof(OT);
     // the 64-feature span span of the token's features; with a blocked layout (heads or layers apart in
     // memory) every whole block before it adds the gap between blocks
@@ -192,6 +205,18 @@ __device__ __forceinline__ void store_pair(const KernelArgs& a, const TileRef& t
                 *reinterpret_cast<uint32_t*>(ob + (__umul24(row, ldb) + lane_col)) = pack_bf16x2(part[k - k0].x + acc0[tt][i], part[k - k0].y + acc1[tt][i]);
             }
         }
+    } else if (last_row + 1u == tok_rows) {
+        // no row past the end: a row's address is a scalar and the lane's offset the same for all
+        typedef char __attribute__((address_space(1))) * global_ptr;
+        const uint64_t rows = (uint64_t)uniform_ptr(ob);
+        const uint32_t lane_off = __umul24(lrow, ldb) + lane_col;          // row < 256, ldb <= 2^23
+#pragma unroll
+        for (int k = 0; k < 16 * TT; ++k) {
+            const int tt = k / 16, i = k % 16;
+            const global_ptr dst = (global_ptr)(rows + (uint64_t)(uint32_t)(tt * 32 + 8 * (i / 4) + i % 4) * (uint64_t)ldb) + lane_off;
+            if constexpr (sizeof(OT) == 2) *(uint32_t __attribute__((address_space(1)))*)dst = pack_bf16x2(acc0[tt][i], acc1[tt][i]);
+            else *(f32x2_d __attribute__((address_space(1)))*)dst = f32x2_d{acc0[tt][i], acc1[tt][i]};
+        }
     } else {
 #pragma unroll
         for (int k = 0; k < 16 * TT; ++k) {
@@ -236,7 +261,7 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
         const uint32_t dst = lds_ring + (uint32_t)(stage * STAGE_U4) * 16u;
 #pragma unroll
         for (int i = 0; i < NV; ++i)
-            if (i * kThreads + wave * 64 < SLAB_U4)
+            if ((i + 1) * kThreads <= SLAB_U4 || i * kThreads + wave * 64 < SLAB_U4)
                 dma16_async(vsrc + i * kThreads, (uint32_t)tid * 16u, dst + (uint32_t)(i * kThreads + wave * 64) * 16u);
         if (wave == 0 && lane < kMuU4) dma16_async(vsrc + SLAB_U4, (uint32_t)lane * 16u, dst + (uint32_t)SLAB_U4 * 16u);
     };
@@ -250,24 +275,27 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
     // codes of up to 8 bits (all that calibration produces) come four to a 32-bit window, wider
     // ones two; the choice is made once per plan
     auto unpack = [&](auto narrow_tag) {
-        constexpr bool kNarrow = decltype(narrow_tag)::value;
+        const uint32_t* row[TT];
 #pragma unroll
-        for (int c = 0; c < NCT; ++c) {
-            const uint32_t info = blk[2 * c + h];
-            const uint32_t bits = info & 0xffu;
-            const uint32_t g = (info >> 8) & 0xffu;
-            const uint32_t pos0 = (info >> 16) * 16u;
+        for (int tt = 0; tt < TT; ++tt)
+            row[tt] = rec + (uint32_t)min(wave * TOK_W + tt * 32 + l32, n_valid - 1) * im.stride_dw;   // tail rows: the last token's record
+        uint32_t info[NCT];
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt) {
-                const uint32_t* row = rec + (uint32_t)min(wave * TOK_W + tt * 32 + l32, n_valid - 1) * im.stride_dw;   // tail rows: the last token's record
-                uint32_t q[8];                                      // the block's 16 values as bf16 pairs
-                unpack_block<kNarrow>(row, bits, g, pos0, q);
-                // (through an empty asm: the conversions are done here, block by block, instead of all the
-                // fp32 values staying live until the end of the unpacking)
-                asm volatile("" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]), "+v"(q[5]), "+v"(q[6]), "+v"(q[7]));
-                aop[tt][2 * c] = __builtin_bit_cast(bf16x8, make_uint4(q[0], q[1], q[2], q[3]));
-                aop[tt][2 * c + 1] = __builtin_bit_cast(bf16x8, make_uint4(q[4], q[5], q[6], q[7]));
-            }
+        for (int c = 0; c < NCT; ++c) info[c] = blk[2 * c + h];
+        RecBlock<decltype(narrow_tag)::value> b[2];              // this item's and the next one's
+        b[0].read(row[0], info[0]);
+#pragma unroll
+        for (int k = 0; k < NCT * TT; ++k) {
+            const int c = k / TT, tt = k % TT;
+            if (k + 1 < NCT * TT) b[(k + 1) & 1].read(row[(k + 1) % TT], info[(k + 1) / TT]);
+            __builtin_amdgcn_sched_barrier(0);
+            uint32_t q[8];                                      // the block's 16 values as bf16 pairs
+            b[k & 1].values(q);
+            // (through an empty asm: the conversions are done here, block by block, instead of all the
+            // fp32 values staying live until the end of the unpacking)
+            asm volatile("" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]), "+v"(q[5]), "+v"(q[6]), "+v"(q[7]));
+            aop[tt][2 * c] = __builtin_bit_cast(bf16x8, make_uint4(q[0], q[1], q[2], q[3]));
+            aop[tt][2 * c + 1] = __builtin_bit_cast(bf16x8, make_uint4(q[4], q[5], q[6], q[7]));
         }
     };
     if (P.code_bits_max <= 8) unpack(std::true_type()); else unpack(std::false_type());
@@ -292,12 +320,11 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
     // One 32-feature tile: the accumulators start from mu and sweep the coordinates.
     auto tile_step = [&](int stage, f32x16 (&acc)[TT]) {
         const uint4* bbase = ring + stage * STAGE_U4 + lane;
+        f32x16 start;                                           // (one copy of mu for all token tiles)
         {
             const float m = reinterpret_cast<const float*>(ring + stage * STAGE_U4 + SLAB_U4)[l32];
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[tt][i] = m;
+            for (int i = 0; i < 16; ++i) start[i] = m;
         }
         constexpr int NSTEP = 2 * NCT;
         uint4 bf[3];
@@ -310,7 +337,7 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
             const bf16x8 bv = as_bf16x8_d(bf[ks % 3]);
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
-                acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aop[tt][ks], bv, acc[tt], 0, 0, 0);
+                acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aop[tt][ks], bv, ks == 0 ? start : acc[tt], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -332,7 +359,7 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
         if (more) issue_slab(f0 + 2, 0);
         tile_step(1, acc1);
         {
-            store_pair<TT, OT, ACC>(a, tr, acc0, acc1, obase, SHARE ? f0 / 2 + first_span : f0 / 2, lane_row, lane_col, last_row, tok_tile0);
+            store_pair<TT, OT, ACC>(a, tr, acc0, acc1, obase, SHARE ? f0 / 2 + first_span : f0 / 2, lane_row, lane_col, last_row, (uint32_t)TOK_WG, tok_tile0);
         }
         // (the adds are a data-dependent number of operations, so after them the wait is for everything)
         if (more && ACC == 0) wait_vmem<NST>(); else wait_vmem<0>();
@@ -459,16 +486,21 @@ __device__ __forceinline__ void decode_wide_tile(const PlanDec& P, const TileRef
         const RecImage im = rec_image(P.rec_dwords, tr.offset + (uint64_t)tok_tile0 * (uint64_t)P.rec_dwords * 4ull);
         const uint32_t* blk = reinterpret_cast<const uint32_t*>(work);
         const uint32_t* rec = blk + kAuxBytes / 4 + im.skew_dw;
-        uint32_t q[ITEMS][8];
+        uint32_t q[ITEMS][8], info[ITEMS];                       // (an item beyond the plan's tiles reads the last tile's blocks for nothing)
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) info[k] = blk[2 * min((wave + 8 * k) / TT, nct - 1) + h];
         auto unpack = [&](auto narrow_tag) {
-            constexpr bool kNarrow = decltype(narrow_tag)::value;
+            RecBlock<decltype(narrow_tag)::value> b[2];          // this item's and the next one's
+            auto read = [&](int k) {
+                const int tt = (wave + 8 * k) % TT;
+                b[k & 1].read(rec + (uint32_t)min(tt * 32 + l32, n_valid - 1) * im.stride_dw, info[k]);      // tail rows: the last token's record
+            };
+            read(0);
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
-                const int item = wave + 8 * k, c = item / TT, tt = item % TT;
-                if (c >= nct) continue;
-                const uint32_t info = blk[2 * c + h];
-                const uint32_t* row = rec + (uint32_t)min(tt * 32 + l32, n_valid - 1) * im.stride_dw;      // tail rows: the last token's record
-                unpack_block<kNarrow>(row, info & 0xffu, (info >> 8) & 0xffu, (info >> 16) * 16u, q[k]);
+                if (k + 1 < ITEMS) read(k + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                b[k & 1].values(q[k]);
                 asm volatile("" : "+v"(q[k][0]), "+v"(q[k][1]), "+v"(q[k][2]), "+v"(q[k][3]), "+v"(q[k][4]), "+v"(q[k][5]), "+v"(q[k][6]), "+v"(q[k][7]));
             }
         };
@@ -547,20 +579,33 @@ __device__ __forceinline__ void decode_wide_tile(const PlanDec& P, const TileRef
             float2 part[TT][16];
             uint32_t lrow = lane_row;
             asm volatile("" : "+v"(lrow));
+            if (last_row + 1u == (uint32_t)TOK) {                // (as in store_pair: scalar row addresses where no row lies past the end)
+                typedef const f32x2_d __attribute__((address_space(1))) * global_f2;
+                const uint64_t rows = (uint64_t)uniform_ptr(sb);
+                const uint32_t lane_off = lrow * sld + 2u * lane_col;                      // below 64 rows of 2^23 bytes
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
+                for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) part[tt][i] = load_part(sb, lrow, tt, i, sld, lane_col, last_row);
+                    for (int i = 0; i < 16; ++i) {
+                        const f32x2_d v = *(global_f2)((global_ptr)(rows + (uint64_t)(uint32_t)(tt * 32 + 8 * (i / 4) + i % 4) * (uint64_t)sld) + lane_off);
+                        part[tt][i] = make_float2(v[0], v[1]);
+                    }
+            } else {
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) part[tt][i] = load_part(sb, lrow, tt, i, sld, lane_col, last_row);
+            }
             __builtin_amdgcn_sched_barrier(0);
             block(n_ks - DEPTH);
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) { acc0[tt][i] = part[tt][i].x + acc0[tt][i]; acc1[tt][i] = part[tt][i].y + acc1[tt][i]; }
-            store_pair<TT, OT, 0>(a, tr, acc0, acc1, obase, q, lane_row, lane_col, last_row, tok_tile0);
+            store_pair<TT, OT, 0>(a, tr, acc0, acc1, obase, q, lane_row, lane_col, last_row, (uint32_t)TOK, tok_tile0);
         } else {
             for (int s = 0; s < n_ks; s += DEPTH) block(s);
-            store_pair<TT, OT, ACC>(a, tr, acc0, acc1, obase, q, lane_row, lane_col, last_row, tok_tile0);
+            store_pair<TT, OT, ACC>(a, tr, acc0, acc1, obase, q, lane_row, lane_col, last_row, (uint32_t)TOK, tok_tile0);
         }
     }
     wait_vmem<0>();                                              // the fragments fetched past the last pair

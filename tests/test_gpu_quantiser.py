@@ -6,6 +6,7 @@ import torch
 
 import kvtc_oracle as ko
 import paper_2511_01815_amd as kv
+import test_gpu_encode_short as es
 from test_gpu_encode_short import bulk_tokens
 from test_gpu_parity import DEV, _gpu_plan
 
@@ -58,3 +59,9 @@ def test_records_of_known_coefficients(groups):
             assert bad.size == 0, (tokens, dtype, bad[:5], x[bad[0]], got[bad[0]], want[bad[0]])
             for t0 in range(n, tokens - n + 1, n):
                 assert np.array_equal(got[t0:t0 + n], want), (tokens, dtype, t0)
+
+
+@pytest.mark.parametrize("r", [144, 160, 208, 272, 304])
+def test_plans_of_fewer_tiles_than_their_variant(r):
+    """5, 7 and 9 coordinate tiles (whole and half a last one) run in the variants of 6, 8 and 10, which leave the padding out."""
+    es.test_bulk_kernels_code_the_same_bits_from_every_type_and_layout(r)
