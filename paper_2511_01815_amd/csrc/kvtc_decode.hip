@@ -156,10 +156,20 @@ __device__ __forceinline__ float2 load_part(const char* sb, uint32_t lrow, int t
     return *reinterpret_cast<const float2*>(sb + ((size_t)row * sld + 2u * lane_col));
 }
 
-// The results of a pair of feature tiles (acc0: the even, acc1: the odd features of 64-feature span `span`) to the output.
-template <int TT, typename OT, int ACC>
+// Whether a launch's output passes the caches by (non-temporal stores; whole tiles only): where it is more than half of the 256 MB last-level cache.
+// What is decoded next to it -- the bases, in an L2 of 4 MB -- is then not pushed out by output that nobody finds there again: 32-layer cache at
+// 16x 1265 -> 1131 us, 64 tensors of 8000 tokens at 20x 323 -> 228, four layers under one basis, both ways, 1364 -> 1261.  Below, what reads the output next
+// does find it (the keys of 32768 tokens, 64 MB, decoded and rotated: 122 us, 131 with such stores; of 60000, 123 MB: 259 and 256).
+__device__ __forceinline__ bool output_streams(uint32_t tiles, int tile_tokens, int p, int elem_bytes) {
+    return (uint64_t)tiles * (uint64_t)(uint32_t)(tile_tokens * elem_bytes) * (uint64_t)(uint32_t)p > (128ull << 20);
+}
+
+// The results of a pair of feature tiles (acc0: the even, acc1: the odd features of 64-feature span `span`) to the output.  `fast`: every row of
+// the tile is one of the tensor's, and with STREAM the output is to pass the caches by.  (Stores of either kind side by side, chosen per tile, cost the
+// 16x cache 4 %: tiles that are neither take the form that looks after the rows' end, whose addresses are half of the sweep's vector instructions.)
+template <int TT, typename OT, int ACC, bool STREAM>
 __device__ __forceinline__ void store_pair(const KernelArgs& a, const TileRef& tr, const f32x16 (&acc0)[TT], const f32x16 (&acc1)[TT], char* obase, int span,
-                                           uint32_t lane_row, uint32_t lane_col, uint32_t last_row, uint32_t tok_rows, int tok_tile0) {
+                                           uint32_t lane_row, uint32_t lane_col, uint32_t last_row, int tok_tile0, bool fast) {
     const uint32_t ldb = (uint32_t)a.ld_x * (uint32_t)sizeof(OT);
     // the 64-feature span span of the token's features; with a blocked layout (heads or layers apart in
     // memory) every whole block before it adds the gap between blocks
@@ -205,17 +215,20 @@ __device__ __forceinline__ void store_pair(const KernelArgs& a, const TileRef& t
                 *reinterpret_cast<uint32_t*>(ob + (__umul24(row, ldb) + lane_col)) = pack_bf16x2(part[k - k0].x + acc0[tt][i], part[k - k0].y + acc1[tt][i]);
             }
         }
-    } else if (last_row + 1u == tok_rows) {
+    } else if (fast) {
         // no row past the end: a row's address is a scalar and the lane's offset the same for all
         typedef char __attribute__((address_space(1))) * global_ptr;
+        typedef std::conditional_t<sizeof(OT) == 2, uint32_t, f32x2_d> V;
+        typedef V __attribute__((address_space(1))) * global_v;
         const uint64_t rows = (uint64_t)uniform_ptr(ob);
         const uint32_t lane_off = __umul24(lrow, ldb) + lane_col;          // row < 256, ldb <= 2^23
 #pragma unroll
         for (int k = 0; k < 16 * TT; ++k) {
             const int tt = k / 16, i = k % 16;
-            const global_ptr dst = (global_ptr)(rows + (uint64_t)(uint32_t)(tt * 32 + 8 * (i / 4) + i % 4) * (uint64_t)ldb) + lane_off;
-            if constexpr (sizeof(OT) == 2) *(uint32_t __attribute__((address_space(1)))*)dst = pack_bf16x2(acc0[tt][i], acc1[tt][i]);
-            else *(f32x2_d __attribute__((address_space(1)))*)dst = f32x2_d{acc0[tt][i], acc1[tt][i]};
+            const global_v dst = (global_v)((global_ptr)(rows + (uint64_t)(uint32_t)(tt * 32 + 8 * (i / 4) + i % 4) * (uint64_t)ldb) + lane_off);
+            V v;
+            if constexpr (sizeof(OT) == 2) v = pack_bf16x2(acc0[tt][i], acc1[tt][i]); else v = f32x2_d{acc0[tt][i], acc1[tt][i]};
+            if constexpr (STREAM) __builtin_nontemporal_store(v, dst); else *dst = v;
         }
     } else {
 #pragma unroll
@@ -235,7 +248,7 @@ __device__ __forceinline__ void store_pair(const KernelArgs& a, const TileRef& t
 // the first step of the feature sweep.
 template <int NCT, int TT, typename OT, int ACC, bool SHARE>
 __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr, const KernelArgs& a, uint4* work, uint4* ring,
-                                            bool prefetch, bool has_next, const TileRef& next, const PlanDec& Pn, int first_span) {
+                                            bool prefetch, bool has_next, const TileRef& next, const PlanDec& Pn, int first_span, bool streamed) {
     constexpr int TOK_W = 32 * TT;
     constexpr int TOK_WG = 4 * TOK_W;
     constexpr int SLAB_U4 = 2 * NCT * 64;          // one 32-feature tile of V_kept
@@ -316,6 +329,7 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
     const uint32_t lane_row = (uint32_t)(wave * TOK_W + 4 * h);
     const uint32_t lane_col = (uint32_t)(2 * l32 * (int)sizeof(OT));
     const uint32_t last_row = (uint32_t)(n_valid - 1);
+    const bool fast = n_valid == TOK_WG && (TT == 1 || (!SHARE && streamed));
 
     // One 32-feature tile: the accumulators start from mu and sweep the coordinates.
     auto tile_step = [&](int stage, f32x16 (&acc)[TT]) {
@@ -359,7 +373,7 @@ __device__ __forceinline__ void decode_tile(const PlanDec& P, const TileRef& tr,
         if (more) issue_slab(f0 + 2, 0);
         tile_step(1, acc1);
         {
-            store_pair<TT, OT, ACC>(a, tr, acc0, acc1, obase, SHARE ? f0 / 2 + first_span : f0 / 2, lane_row, lane_col, last_row, (uint32_t)TOK_WG, tok_tile0);
+            store_pair<TT, OT, ACC, (TT > 1)>(a, tr, acc0, acc1, obase, SHARE ? f0 / 2 + first_span : f0 / 2, lane_row, lane_col, last_row, tok_tile0, fast);
         }
         // (the adds are a data-dependent number of operations, so after them the wait is for everything)
         if (more && ACC == 0) wait_vmem<NST>(); else wait_vmem<0>();
@@ -383,12 +397,12 @@ template <int TT, int CLS> constexpr int dec_wgs_per_cu() { return CLS <= 4 ? 3 
 // The widths built for each class; a plan's tile count is rounded up to the next of them at plan creation.
 template <int CLS, int TT, typename OT, int ACC, bool SHARE>
 __device__ __forceinline__ void decode_tile_of_class(const PlanDec& P, const TileRef& tr, const KernelArgs& a, uint4* work, uint4* ring,
-                                                     bool prefetch, bool has_next, const TileRef& next, const PlanDec& Pn, int first_span) {
-#define KVTC_W(N) case N: decode_tile<N, TT, OT, ACC, SHARE>(P, tr, a, work, ring, prefetch, has_next, next, Pn, first_span); break;
+                                                     bool prefetch, bool has_next, const TileRef& next, const PlanDec& Pn, int first_span, bool streamed) {
+#define KVTC_W(N) case N: decode_tile<N, TT, OT, ACC, SHARE>(P, tr, a, work, ring, prefetch, has_next, next, Pn, first_span, streamed); break;
     if constexpr (CLS == 4) {
-        switch (P.dec_nct) { KVTC_W(2) default: decode_tile<4, TT, OT, ACC, SHARE>(P, tr, a, work, ring, prefetch, has_next, next, Pn, first_span); break; }
+        switch (P.dec_nct) { KVTC_W(2) default: decode_tile<4, TT, OT, ACC, SHARE>(P, tr, a, work, ring, prefetch, has_next, next, Pn, first_span, streamed); break; }
     } else if constexpr (CLS == 10) {
-        switch (P.dec_nct) { KVTC_W(6) KVTC_W(7) KVTC_W(8) KVTC_W(9) default: decode_tile<10, TT, OT, ACC, SHARE>(P, tr, a, work, ring, prefetch, has_next, next, Pn, first_span); break; }
+        switch (P.dec_nct) { KVTC_W(6) KVTC_W(7) KVTC_W(8) KVTC_W(9) default: decode_tile<10, TT, OT, ACC, SHARE>(P, tr, a, work, ring, prefetch, has_next, next, Pn, first_span, streamed); break; }
     }
 #undef KVTC_W
 }
@@ -420,7 +434,7 @@ __global__ void __launch_bounds__(kThreads, (dec_wgs_per_cu<TT, CLS>())) kvtc_de
         issue_records(a, tr, P, lds_offset(work));
         wait_vmem<0>();
         __syncthreads();
-        decode_tile_of_class<CLS, TT, OT, ACC, true>(P, tr, a, work, ring, prefetch, false, tr, P, (int)begin);
+        decode_tile_of_class<CLS, TT, OT, ACC, true>(P, tr, a, work, ring, prefetch, false, tr, P, (int)begin, false);
         return;
     }
     const TileRange mine = my_tiles(total);
@@ -428,6 +442,7 @@ __global__ void __launch_bounds__(kThreads, (dec_wgs_per_cu<TT, CLS>())) kvtc_de
     if (tile >= mine.end) return;
     TileRef tr = find_tile(a, tile_start, tile);
     PlanDec P = load_plan_dec(a.plans + tr.plan);
+    const bool streamed = TT > 1 && output_streams(total, 4 * 32 * TT, P.p, (int)sizeof(OT));
     P.dec_tok_wg = 4 * 32 * TT;
     issue_records(a, tr, P, lds_offset(work));
     wait_vmem<0>();
@@ -442,7 +457,7 @@ __global__ void __launch_bounds__(kThreads, (dec_wgs_per_cu<TT, CLS>())) kvtc_de
             Pn = load_plan_dec(a.plans + trn.plan);
             Pn.dec_tok_wg = 4 * 32 * TT;
         }
-        decode_tile_of_class<CLS, TT, OT, ACC, false>(P, tr, a, work, ring, prefetch, has_next && prefetch, trn, Pn, 0);
+        decode_tile_of_class<CLS, TT, OT, ACC, false>(P, tr, a, work, ring, prefetch, has_next && prefetch, trn, Pn, 0, streamed);
         if (!has_next) break;
         tile = next;
         tr = trn;
@@ -469,7 +484,7 @@ template <int TT, int ACC> constexpr int wide_depth() { return TT == 4 || ACC ==
 constexpr int kWideThreads = 512;
 
 template <int TT, typename OT, int ACC>
-__device__ __forceinline__ void decode_wide_tile(const PlanDec& P, const TileRef& tr, const KernelArgs& a, uint4* work, int q_begin, int q_end) {
+__device__ __forceinline__ void decode_wide_tile(const PlanDec& P, const TileRef& tr, const KernelArgs& a, uint4* work, int q_begin, int q_end, bool streamed) {
     constexpr int DEPTH = wide_depth<TT, ACC>(), TOK = 32 * TT, ITEMS = (TT == 4 ? 18 * 4 : 32 * 2) / 8;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
@@ -543,6 +558,7 @@ __device__ __forceinline__ void decode_wide_tile(const PlanDec& P, const TileRef
 
     char* obase = reinterpret_cast<char*>(const_cast<void*>(a.x)) + (size_t)(tr.x_row0 + tok_tile0) * (size_t)a.ld_x * sizeof(OT);
     const uint32_t lane_row = (uint32_t)(4 * h), lane_col = (uint32_t)(2 * l32 * (int)sizeof(OT)), last_row = (uint32_t)(n_valid - 1);
+    const bool fast = n_valid == TOK && streamed;
     for (; q < q_end; q += 8) {
         const int qn = q + 8 < q_end ? q + 8 : q;
         f32x16 acc0[TT], acc1[TT];
@@ -602,10 +618,10 @@ __device__ __forceinline__ void decode_wide_tile(const PlanDec& P, const TileRef
             for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) { acc0[tt][i] = part[tt][i].x + acc0[tt][i]; acc1[tt][i] = part[tt][i].y + acc1[tt][i]; }
-            store_pair<TT, OT, 0>(a, tr, acc0, acc1, obase, q, lane_row, lane_col, last_row, (uint32_t)TOK, tok_tile0);
+            store_pair<TT, OT, 0, true>(a, tr, acc0, acc1, obase, q, lane_row, lane_col, last_row, tok_tile0, fast);
         } else {
             for (int s = 0; s < n_ks; s += DEPTH) block(s);
-            store_pair<TT, OT, ACC>(a, tr, acc0, acc1, obase, q, lane_row, lane_col, last_row, (uint32_t)TOK, tok_tile0);
+            store_pair<TT, OT, ACC, true>(a, tr, acc0, acc1, obase, q, lane_row, lane_col, last_row, tok_tile0, fast);
         }
     }
     wait_vmem<0>();                                              // the fragments fetched past the last pair
@@ -630,7 +646,8 @@ __global__ void __launch_bounds__(kWideThreads, 1) kvtc_decode_wide_kernel(const
         PlanDec P = load_plan_dec(a.plans + tr.plan);
         const uint32_t pairs = (uint32_t)P.p / 64u, n = min(max(parts, 1u), max(pairs / 4u, 1u));
         if (part >= n) return;
-        decode_wide_tile<TT, OT, ACC>(P, tr, a, work, (int)(part * pairs / n), (int)((part + 1u) * pairs / n));
+        decode_wide_tile<TT, OT, ACC>(P, tr, a, work, (int)(part * pairs / n), (int)((part + 1u) * pairs / n),
+                                      output_streams(total, 32 * TT, P.p, (int)sizeof(OT)));
     }
 }
 

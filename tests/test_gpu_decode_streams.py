@@ -1,0 +1,40 @@
+"""Decode of an output beyond half of the last-level cache, whose whole tiles are stored past the caches: the same bits as in calls of a part of
+the tokens each, for a width of every kernel, both types, a token count that is no multiple of a tile, with a row pitch and as jobs of a batch."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2511_01815_amd as kv
+from test_gpu_parity import DEV, _gpu_plan, _variant_plan
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("r", [64, 160, 224, 240, 272, 480, 1024])
+@pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
+def test_large_outputs_hold_what_small_ones_hold(r, dtype):
+    plan = _gpu_plan(_variant_plan(r))
+    p, R, T, ld = 1024, plan.record_bytes, 70001, 1088
+    tdt = torch.bfloat16 if dtype == kv.KVTC_BF16 else torch.float32
+    x = torch.randn((T, p), generator=torch.Generator(device=DEV).manual_seed(r), device=DEV)
+    rec = torch.zeros((T, R), dtype=torch.uint8, device=DEV)
+    kv.kvtc_encode(plan.handle, x, kv.KVTC_F32, T, p, rec, rec.numel())
+    del x
+    want = torch.empty((T, p), dtype=tdt, device=DEV)
+    for t0 in range(0, T, 14000):
+        n = min(14000, T - t0)
+        part = rec[t0:t0 + n].clone()                            # (a tile's records start where they start in a call of their own)
+        kv.kvtc_decode(plan.handle, part, part.numel(), n, want[t0:], dtype, p)
+    got = torch.full((T + 1, ld), 7.0, dtype=tdt, device=DEV)
+    kv.kvtc_decode(plan.handle, rec, rec.numel(), T, got, dtype, ld)
+    assert torch.equal(got[:T, :p], want) and bool((got[:, p:] == 7.0).all()) and bool((got[T] == 7.0).all())
+    lens = [30000, 1, 255, 39745]
+    jobs = torch.from_numpy(kv.make_jobs([0] * 4, lens, [0, 30000, 30001, 30256]).view(np.uint8)).to(DEV)
+    offs = torch.zeros(5, dtype=torch.int64, device=DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=DEV)
+    batch = kv.Batch([plan])
+    got.fill_(7.0)
+    kv.kvtc_offsets(batch.handle, jobs, 4, offs)
+    kv.kvtc_decode_batch(batch.handle, jobs, 4, rec, rec.numel(), offs, got, dtype, ld, status)
+    assert int(status.item()) == 0
+    assert torch.equal(got[:T, :p], want) and bool((got[:, p:] == 7.0).all()) and bool((got[T] == 7.0).all())
