@@ -306,7 +306,13 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
     __syncthreads();
 }
 
-template <int NTW, int WC, typename XT, int NW>
+// ONCE (the variants of 11 to 20 tiles, bf16): the launch's input is more than the last-level cache, 256 MB, holds; its lines, which are read once, are
+// then not to push the basis, of a megabyte, out of the L2s (16 tensors of 32768 tokens at 8x, 1 GB, encode and decode: 1228 -> 1180 us; of
+// 4000 tokens, whose 131 MB a call finds in that cache: 115 without, 122 with).  Not in the 4-wave variants: they ask for a line's
+// halves at two times, and the second had to fetch it again (32-layer cache at 16x: 1290 -> 1750).  A copy of the whole tile: as a choice per transfer it
+// cost the small calls 2 to 4 %, as two main loops in front of one epilogue all calls half of their speed, in moves of accumulators.
+template <typename XT, int WC, int NW> constexpr bool enc_once() { return NW == 8 && WC == 4 && sizeof(XT) == 2; }
+template <int NTW, int WC, typename XT, int NW, bool ONCE>
 __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
                                             const KernelArgs& a, uint4* work) {
     constexpr int NTP = NTW * WC;            // coordinate tiles of the padded plan
@@ -396,7 +402,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
 #pragma unroll
         for (int j = 0; j < NXD; ++j)
             if ((j + 1) * NW <= NX_TOTAL || j * NW + wave < NX_TOTAL)
-                dma16_async(xtile + xoff, xsrc[j], base + xdst[j]);
+                ONCE ? dma16_async_once(xtile + xoff, xsrc[j], base + xdst[j]) : dma16_async(xtile + xoff, xsrc[j], base + xdst[j]);
     };
     // (a wave with a tile fewer than NTW reads the next wave's, or padding, in its place)
     auto compute = [&](int stage) {
@@ -485,7 +491,9 @@ __global__ void __launch_bounds__(NW * 64, (enc_wgs_per_cu<WC, NTW, NW>())) kvtc
     for (uint32_t tile = mine.first; tile < mine.end; tile += mine.step) {
         const TileRef tr = find_tile(a, tile_start, tile);
         const PlanEnc P = load_plan_enc<false>(a.plans + tr.plan);
-        encode_tile<NTW, WC, XT, NW>(P, tr, a, work);
+        const uint64_t launch_bytes = (uint64_t)total * (uint64_t)(uint32_t)(32 * enc_tt(NTW * WC, NW, WC) * (NW / WC)) * (uint64_t)((uint32_t)P.p * (uint32_t)sizeof(XT));
+        if (enc_once<XT, WC, NW>() && launch_bytes > (256ull << 20)) encode_tile<NTW, WC, XT, NW, enc_once<XT, WC, NW>()>(P, tr, a, work);
+        else encode_tile<NTW, WC, XT, NW, false>(P, tr, a, work);
     }
 }
 
