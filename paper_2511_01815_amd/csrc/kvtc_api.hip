@@ -297,7 +297,8 @@ static kvtc_status plan_create_impl(kvtc_plan** out, int p, int r, const float* 
     // workgroups share a compute unit (three where 168 registers suffice: measured 5 % faster on the
     // 6-tile encode).  Wider plans get 8-wave workgroups (two waves per SIMD at 256 registers): 128-token tiles with four waves
     // across the coordinates up to 640 of them, twice as fast as 4 waves of 512 registers; 64-token tiles with eight waves
-    // across up to 1024 (1024 of 4096 features, 32768 tokens: 390 us as 4 waves of 512, 345 so).
+    // across up to 1024, the basis straight to their registers (1024 of 4096 features, 32768 tokens: 390 us as 4 waves of 512, 340 with the basis
+    // by way of LDS, 285 so; eight waves of two tiles on 128 tokens that way for 448 to 512 coordinates: 4 % slower than these).
     // {waves across coordinates, tiles per wave, workgroups per compute unit, waves per workgroup}, ascending padded width
     static const int enc_tab[][4] = {{1, 2, 2, 4}, {1, 4, 2, 4}, {2, 3, 3, 4}, {2, 4, 2, 4}, {2, 5, 2, 4},
                                      {4, 3, 1, 8}, {4, 4, 1, 8}, {4, 5, 1, 8}, {8, 3, 1, 8}, {8, 4, 1, 8}};

@@ -442,6 +442,10 @@ __device__ __forceinline__ void dma16_async(const void* base_uniform, uint32_t l
 }
 
 // The same for data that is read once: the caches are asked not to keep it.
+__device__ __forceinline__ void dma16_async_once(const void* gsrc, uint32_t lds_byte_addr) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
+                 :: "v"(gsrc), "s"(lds_byte_addr) : "memory");
+}
 __device__ __forceinline__ void dma16_async_once(const void* base_uniform, uint32_t lane_byte_off, uint32_t lds_byte_addr) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                  :: "v"(lane_byte_off), "s"(uniform_ptr(reinterpret_cast<const char*>(base_uniform))),

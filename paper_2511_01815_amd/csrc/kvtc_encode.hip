@@ -481,6 +481,9 @@ template <int WC, int NTW, int NW> constexpr int enc_wgs_per_cu() {
     return NW == 4 && WC == 2 && NTW == 3 ? 3 : (NW == 4 && WC * NTW <= 10 ? 2 : 1);
 }
 
+template <int NTW, typename XT, int TT, int TOK, int AHEAD, bool BULK>
+__device__ __forceinline__ void encode_register_tile(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, uint4* work, bool once);
+
 template <typename XT, int WC, int NTW, int NW>
 __global__ void __launch_bounds__(NW * 64, (enc_wgs_per_cu<WC, NTW, NW>())) kvtc_encode_kernel(const KernelArgs a) {
     extern __shared__ uint4 smem[];
@@ -492,7 +495,10 @@ __global__ void __launch_bounds__(NW * 64, (enc_wgs_per_cu<WC, NTW, NW>())) kvtc
         const TileRef tr = find_tile(a, tile_start, tile);
         const PlanEnc P = load_plan_enc<false>(a.plans + tr.plan);
         const uint64_t launch_bytes = (uint64_t)total * (uint64_t)(uint32_t)(32 * enc_tt(NTW * WC, NW, WC) * (NW / WC)) * (uint64_t)((uint32_t)P.p * (uint32_t)sizeof(XT));
-        if (enc_once<XT, WC, NW>() && launch_bytes > (256ull << 20)) encode_tile<NTW, WC, XT, NW, enc_once<XT, WC, NW>()>(P, tr, a, work);
+        const bool once = launch_bytes >= (256ull << 20);
+        if constexpr (WC == 8)
+            encode_register_tile<NTW, XT, enc_tt(NTW * WC, NW, WC), 32 * enc_tt(NTW * WC, NW, WC), 4, true>(P, tr, a, work, once);
+        else if (enc_once<XT, WC, NW>() && once) encode_tile<NTW, WC, XT, NW, enc_once<XT, WC, NW>()>(P, tr, a, work);
         else encode_tile<NTW, WC, XT, NW, false>(P, tr, a, work);
     }
 }
@@ -511,21 +517,29 @@ template <typename XT> constexpr int short_feat() { return 512 / (int)sizeof(XT)
 template <int NTW> constexpr int short_ahead() { return NTW == 1 ? 16 : 4; }   // k-steps of fragments in flight
 constexpr int kShortThreads = 640;
 
-template <int NTW, typename XT, int TT>
-__device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, uint4* work) {
-    constexpr int AHEAD = short_ahead<NTW>(), FEAT = short_feat<XT>(), STEPS = FEAT / 16;
+// BULK: the same as the bulk kernels' tile of plans of more than 20 tiles, those shared out evenly among 8 waves (NTW of them or one fewer).  By way of LDS
+// the basis of 1024 coordinates came into a compute unit at 26 bytes a cycle, 1300 cycles for a k-step whose matrix instructions take 512; it comes
+// twice as fast so.  1024 of 4096 features, two sections of 32768 tokens, both ways: 1268 -> 1164 us, with X (once: an input of the
+// last-level cache's 256 MB and more) not kept by the caches 1136; 1024 of 1024, 65536 tokens 165 -> 146; 4096 of 8192 in four sections, 1000 tokens, both ways
+// 1080 -> 915.
+template <int NTW, typename XT, int TT, int TOK, int AHEAD, bool BULK>
+__device__ __forceinline__ void encode_register_tile(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, uint4* work, bool once) {
+    constexpr int FEAT = short_feat<XT>(), STEPS = FEAT / 16;
     constexpr int UNROLL = AHEAD > STEPS ? AHEAD / STEPS : 1;        // chunks after which a fragment is in the same register again
     constexpr int EB = (int)sizeof(XT), ROW_B = FEAT * EB, COLS = ROW_B / 16, ROWS_DMA = 1024 / ROW_B;
-    constexpr int ROWS = 32 * TT, CHUNK_B = kEncShortTile * ROW_B;
+    constexpr int ROWS = 32 * TT, CHUNK_B = TOK * ROW_B;
     static_assert(UNROLL * STEPS % AHEAD == 0, "a fragment's register is known at compile time");
     int tid = (int)threadIdx.x;
     asm volatile("" : "+v"(tid));            // (lane addresses are worked out here, not kept through a loop over tiles)
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = (int)blockDim.x >> 6;
     const int l32 = lane & 31, h = lane >> 5;
-    const int ntp = P.enc_ntw * P.enc_wc;
-    const int p = P.p, T = tr.n_tokens, tok_tile0 = tr.tile * kEncShortTile;
+    const int ntp = BULK ? 8 * NTW : P.enc_ntw * P.enc_wc;
+    const int p = P.p, T = tr.n_tokens, tok_tile0 = tr.tile * TOK;
     const int n_steps = p / 16, n_chunks = (p + FEAT - 1) / FEAT;
-    const int nt = (P.r + 31) / 32, ct0 = wave * NTW, n_ct = min(max(nt - ct0, 0), NTW);      // (a wave without a tile only helps)
+    const int nt = (P.r + 31) / 32;
+    const int ct0 = BULK ? wave * (nt / 8) + min(wave, nt % 8) : wave * NTW;
+    const int n_ct = BULK ? nt / 8 + (wave < nt % 8 ? 1 : 0) : min(max(nt - ct0, 0), NTW);      // (a wave without a tile only helps)
+    const bool full = !BULK || n_ct >= NTW;
     uint4* smem = work + enc_aux_bytes(ntp) / 16;
 
     // the plan's tables and chunk 0 of X -> LDS
@@ -547,7 +561,8 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
             f = f < p ? f : 0;                                       // behind the last feature: read something, it is not used
             const int t = min(tok_tile0 + row, T - 1);               // rows past the end re-read the last token
             const char* src = reinterpret_cast<const char*>(a.x) + ((tr.x_row0 + t) * a.ld_x + f) * EB + (blk_lg ? (int64_t)(f >> blk_lg) * blk_jump_b : (int64_t)0);
-            dma16_async(src, __builtin_amdgcn_readfirstlane(lds_x + (uint32_t)((c & 1) * CHUNK_B + i * 1024)));
+            const uint32_t to = __builtin_amdgcn_readfirstlane(lds_x + (uint32_t)((c & 1) * CHUNK_B + i * 1024));
+            if (BULK && once) dma16_async_once(src, to); else dma16_async(src, to);
         }
     };
     issue_x(0);
@@ -610,9 +625,11 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
             if (!last) xv[(ks + 1) & 1][tt] = xfrag(x, tt, ks + 1);
 #pragma unroll
         for (int ct = 0; ct < NTW; ++ct)
+            if (ct + 1 < NTW || full) {
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
-                acc[tt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[(slot0 + ks) % AHEAD][ct]), xv[ks & 1][tt], acc[tt][ct], 0, 0, 0);
+                for (int tt = 0; tt < TT; ++tt)
+                    acc[tt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[(slot0 + ks) % AHEAD][ct]), xv[ks & 1][tt], acc[tt][ct], 0, 0, 0);
+            }
         fetch(c * STEPS + ks + AHEAD, (slot0 + ks) % AHEAD);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -630,7 +647,7 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
 #pragma unroll
             for (int ks = 0; ks < STEPS; ++ks) step(x, c, u * STEPS, ks, ks + 1 == STEPS);
             asm volatile("" ::: "memory");
-            if (more) wait_vmem<STEPS * NTW>();                      // the next chunk is older than this one's fragment loads: it has landed
+            if (more) wait_vmem<(STEPS * NTW < 63 ? STEPS * NTW : 63)>();                      // the next chunk is older than this one's fragment loads: it has landed
             __syncthreads();
         }
     }
@@ -652,7 +669,7 @@ __device__ __forceinline__ void encode_short_tile(const PlanEnc& P, const TileRe
         __syncthreads();
     }
     wait_vmem<0>();                                                  // the fragments fetched past the end
-    encode_epilogue<NTW, TT, true>(acc, ct0, n_ct, 0, ROWS, kEncShortTile, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem);
+    encode_epilogue<NTW, TT, !BULK>(acc, ct0, n_ct, 0, ROWS, TOK, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem);
 }
 
 // the lane's number, worked out where it is used and not kept through a loop
@@ -759,8 +776,8 @@ __device__ __forceinline__ bool short_tile(const KernelArgs& a, uint32_t number,
 }
 template <int NTW, typename XT>
 __device__ __forceinline__ void short_tile_code(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, uint4* smem) {
-    if (tr.n_tokens - tr.tile * kEncShortTile <= 32) encode_short_tile<NTW, XT, 1>(P, tr, a, smem);
-    else encode_short_tile<NTW, XT, 2>(P, tr, a, smem);
+    if (tr.n_tokens - tr.tile * kEncShortTile <= 32) encode_register_tile<NTW, XT, 1, kEncShortTile, short_ahead<NTW>(), false>(P, tr, a, smem, false);
+    else encode_register_tile<NTW, XT, 2, kEncShortTile, short_ahead<NTW>(), false>(P, tr, a, smem, false);
 }
 
 // (registers for four waves a SIMD where two workgroups of eight are to share a compute unit)
@@ -862,7 +879,7 @@ int encode_lds_bytes(int ntw, int wc, int nw, int n_groups, int rec_dwords, kvtc
     const int eb = dtype == KVTC_BF16 ? 2 : 4;
     const int ks = enc_ks(ntp, eb);
     const int tok_wg = 32 * enc_tt(ntp, nw, wc) * (nw / wc);
-    const int main_b = enc_stages(ntp, eb, nw, wc) * (ks * ntp * 1024 + tok_wg * ks * (dtype == KVTC_BF16 ? 32 : 64));
+    const int main_b = wc == 8 ? 2 * tok_wg * 512 : enc_stages(ntp, eb, nw, wc) * (ks * ntp * 1024 + tok_wg * ks * (dtype == KVTC_BF16 ? 32 : 64));
     const int epi_b = tok_wg * (2 * ntp * 8 + n_groups * 8 + (rec_dwords + 1) * 4);
     return enc_aux_bytes(ntp) + (main_b > epi_b ? main_b : epi_b);
 }

@@ -1,5 +1,5 @@
-"""Decode of an output beyond half of the last-level cache, whose whole tiles are stored past the caches: the same bits as in calls of a part of
-the tokens each, for a width of every kernel, both types, a token count that is no multiple of a tile, with a row pitch and as jobs of a batch."""
+"""Tensors beyond the last-level cache: decode stores the whole tiles of an output of more than half of it past the caches, encode of many coordinates
+reads an input of all of it and more without keeping it.  The same bits as in calls of a part of the tokens each."""
 import numpy as np
 import pytest
 import torch
@@ -38,3 +38,17 @@ def test_large_outputs_hold_what_small_ones_hold(r, dtype):
     kv.kvtc_decode_batch(batch.handle, jobs, 4, rec, rec.numel(), offs, got, dtype, ld, status)
     assert int(status.item()) == 0
     assert torch.equal(got[:T, :p], want) and bool((got[:, p:] == 7.0).all()) and bool((got[T] == 7.0).all())
+
+
+@pytest.mark.parametrize("r", [384, 512, 544, 736, 768, 800, 1024])
+def test_large_inputs_are_coded_as_small_ones(r):
+    plan = _gpu_plan(_variant_plan(r))
+    p, R, T = 1024, plan.record_bytes, 131072 + 77                # 256 MB and some
+    x = torch.randn((T, p), generator=torch.Generator(device=DEV).manual_seed(r), device=DEV).to(torch.bfloat16)
+    got = torch.zeros((T, R), dtype=torch.uint8, device=DEV)
+    kv.kvtc_encode(plan.handle, x, kv.KVTC_BF16, T, p, got, got.numel())
+    part = torch.zeros((20001, R), dtype=torch.uint8, device=DEV)
+    for t0 in range(0, T, 20001):
+        n = min(20001, T - t0)
+        kv.kvtc_encode(plan.handle, x[t0:], kv.KVTC_BF16, n, p, part, part.numel())
+        assert torch.equal(got[t0:t0 + n], part[:n]), (r, t0)
