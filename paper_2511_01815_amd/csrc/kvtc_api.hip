@@ -293,7 +293,7 @@ static kvtc_status plan_create_impl(kvtc_plan** out, int p, int r, const float* 
 
     // encode variant: NTW coordinate tiles per wave, WC waves across coordinates, NW waves per workgroup.
     // Up to 320 padded coordinates a 4-wave workgroup keeps its tile (64 tokens per wave across the
-    // tokens; 96 in the 8-tile variant) x all its coordinates in 256 registers per lane and two
+    // tokens; 96 in the 8-tile variant, 32 in the 2-tile one) x all its coordinates in 256 registers per lane and two
     // workgroups share a compute unit (three where 168 registers suffice: measured 5 % faster on the
     // 6-tile encode).  Wider plans get 8-wave workgroups (two waves per SIMD at 256 registers): 128-token tiles with four waves
     // across the coordinates up to 640 of them, twice as fast as 4 waves of 512 registers; 64-token tiles with eight waves

@@ -102,22 +102,41 @@ __device__ __forceinline__ void emit_block(const uint32_t (&u)[16], char* dst) {
     __builtin_memcpy(__builtin_assume_aligned(dst, 2), q, 2 * BITS);
 }
 
-// k-steps (16 features each) per pipeline stage, and stages in the LDS ring.  Sized so that a
-// narrow plan (<= 10 coordinate tiles, two workgroups per compute unit) stays within ~72 KB
-// and a wide one (one workgroup) within ~150 KB.
-// token tiles (of 32) per wave: three where the registers allow it (8 coordinate tiles over two
-// waves: 192 accumulator registers), which cuts the basis traffic per token by a third
-__host__ __device__ constexpr int enc_tt(int ntp, int nw, int wc) { return nw == 4 && wc == 2 && ntp == 8 ? 3 : 2; }
-__host__ __device__ constexpr int enc_ks(int ntp, int elem_bytes) {
+// The LDS rings of the bulk encode: stages of the basis, some k-steps (16 features each) to a stage, and slabs of X, sized so that a narrow plan (<= 10
+// coordinate tiles, two workgroups per compute unit; three of 6 tiles) stays within 72 KB (44 KB) and a wide one (one workgroup) within 152 KB.
+// token tiles (of 32) per wave: three where the registers allow it (8 coordinate tiles over two waves: 192 accumulator registers), which cuts the
+// basis traffic per token by a third; one where a plan is so narrow that X is all there is to fetch, and half as much LDS holds its whole lines
+__host__ __device__ constexpr int enc_tt(int ntp, int nw, int wc) { return nw == 4 && wc == 2 && ntp == 8 ? 3 : (ntp <= 2 ? 1 : 2); }
+// X by whole lines of 128 bytes (bf16): eight rows of four k-steps to a transfer.  By half lines, a stage's two k-steps, every line is asked for at
+// two times; its first half leaves it in the L2 in place of some of the basis, and with reads that do not, the second half is fetched from HBM again (32-layer
+// cache at 16x: 1290 -> 1750 us).  By whole lines an input beyond the last-level cache goes past the L2s (ONCE).  Of 4, 8 and 10 tiles only then: their
+// slabs of X, 64 KB at two workgroups to a compute unit, leave the basis a stage of one or two k-steps ahead, and an input that comes from that cache was
+// faster by half lines (one tensor of 50000 tokens at 16x: 49 us, by lines 55).  Not of 6 tiles: by lines a third workgroup does not fit the LDS
+// (two of 75000 tokens at 20x: 92 us with three, 108 with two).  us, before and after: 32-layer cache, encode, 16x 1280 -> 1224; 16 tensors of 32768 at
+// 8x, both ways, 1196 -> 1170; two-tile plans at 40x, 16 tensors of 20000 tokens: 147 -> 123, fp32 319 -> 270 (there by smaller tiles alone).
+__host__ __device__ constexpr bool enc_lines(int ntp, int elem_bytes, bool once) { return elem_bytes == 2 && ntp != 6 && (once || ntp <= 2 || ntp > 10); }
+// k-steps per stage of the basis ring, and k-steps whose X is fetched together: four where it comes by lines, else those of a stage
+__host__ __device__ constexpr int enc_ks(int ntp, int elem_bytes, bool once) {
+    if (enc_lines(ntp, elem_bytes, once)) return ntp <= 2 ? 4 : (ntp == 8 || ntp == 4 ? 1 : 2);
     return ntp < 8 || (ntp == 8 && elem_bytes == 2) || (ntp > 10 && ntp <= (elem_bytes == 2 ? 20 : 16)) ? 2 : 1;      // fp32 X slabs are twice as large
 }
-// stages: as many as fit the variant's LDS share (three workgroups per compute unit: ~44 KB, two: ~72 KB, one: ~150 KB), 2..4
-__host__ __device__ constexpr int enc_stages(int ntp, int elem_bytes, int nw, int wc) {
-    const int ks = enc_ks(ntp, elem_bytes);
-    const int stage_b = ks * ntp * 1024 + 32 * enc_tt(ntp, nw, wc) * (nw / wc) * ks * 16 * elem_bytes;
-    const int budget = (nw == 4 && wc == 2 && ntp == 6 ? 44 : (nw == 4 && ntp <= 10 ? 72 : 150)) * 1024;
-    const int n = budget / stage_b;
+__host__ __device__ constexpr int enc_kx(int ntp, int elem_bytes, bool once) { return enc_lines(ntp, elem_bytes, once) ? 4 : enc_ks(ntp, elem_bytes, once); }
+// stages of the basis ring, and slabs of the X ring: as many of the former as fit the variant's LDS share, 2..4; of the latter as many where a slab is
+// a stage's X, else two
+__host__ __device__ constexpr int enc_x_slab(int ntp, int elem_bytes, int nw, int wc, bool once) {
+    return 32 * enc_tt(ntp, nw, wc) * (nw / wc) * enc_kx(ntp, elem_bytes, once) * 16 * elem_bytes;
+}
+__host__ __device__ constexpr int enc_stages(int ntp, int elem_bytes, int nw, int wc, bool once) {
+    const bool same = enc_kx(ntp, elem_bytes, once) == enc_ks(ntp, elem_bytes, once);
+    const int v_b = enc_ks(ntp, elem_bytes, once) * ntp * 1024, x_b = enc_x_slab(ntp, elem_bytes, nw, wc, once);
+    const int budget = (nw == 4 && wc == 2 && ntp == 6 ? 44 : (nw == 4 ? 72 : 152)) * 1024;
+    const int n = same ? budget / (v_b + x_b) : (budget - 2 * x_b) / v_b;
     return n < 2 ? 2 : (n > 4 ? 4 : n);
+}
+__host__ __device__ constexpr int enc_ring_bytes(int ntp, int elem_bytes, int nw, int wc, bool once) {
+    const int n = enc_stages(ntp, elem_bytes, nw, wc, once);
+    return n * enc_ks(ntp, elem_bytes, once) * ntp * 1024 +
+           (enc_kx(ntp, elem_bytes, once) == enc_ks(ntp, elem_bytes, once) ? n : 2) * enc_x_slab(ntp, elem_bytes, nw, wc, once);
 }
 
 // Fewest coordinate tiles worked on for a plan that runs as ntp of them (the padding is left out in the variants of 6, 8 and 10), and what
@@ -136,6 +155,21 @@ template <int NTP, int NW, int TOTAL> __host__ __device__ constexpr int enc_leas
         least = n < least ? n : least;
     }
     return least;
+}
+
+// Steps after which basis ring and X ring are where they began.
+__host__ __device__ constexpr int enc_common(int a, int b) {
+    int n = a;
+    while (n % b != 0) n += a;
+    return n;
+}
+// Transfers a wave may have in flight at the end of step u (of a loop that is unrolled by a multiple of spc, and in which step t asks for the basis of step t + d
+// and, where t is a multiple of spc, then for the next slab of X): those younger than the basis of step u + 1 and, where that begins a slab, than the slab.
+__host__ __device__ constexpr int enc_in_flight(int u, int d, int spc, int nv, int nx) {
+    int n = 0;
+    for (int t = u + 1 - d; t <= u; ++t) n += (t > u + 1 - d ? nv : 0) + ((t + 64 * spc) % spc == 0 ? nx : 0);
+    const int slab = (spc - 1) * nv;
+    return (u + 1) % spc == 0 && slab < n ? slab : n;
 }
 
 // LDS work area (behind the job table): [tables of the tile's plan: block table 64 dwords, group
@@ -306,12 +340,11 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
     __syncthreads();
 }
 
-// ONCE (the variants of 11 to 20 tiles, bf16): the launch's input is more than the last-level cache, 256 MB, holds; its lines, which are read once, are
-// then not to push the basis, of a megabyte, out of the L2s (16 tensors of 32768 tokens at 8x, 1 GB, encode and decode: 1228 -> 1180 us; of
-// 4000 tokens, whose 131 MB a call finds in that cache: 115 without, 122 with).  Not in the 4-wave variants: they ask for a line's
-// halves at two times, and the second had to fetch it again (32-layer cache at 16x: 1290 -> 1750).  A copy of the whole tile: as a choice per transfer it
-// cost the small calls 2 to 4 %, as two main loops in front of one epilogue all calls half of their speed, in moves of accumulators.
-template <typename XT, int WC, int NW> constexpr bool enc_once() { return NW == 8 && WC == 4 && sizeof(XT) == 2; }
+// ONCE (bf16, where X comes by whole lines): the launch's input is as much as the last-level cache, 256 MB, holds, or more; its lines, which are read
+// once, are then not to push the basis, of up to a megabyte a tensor, out of the L2s (11 to 20 tiles, 16 tensors of 32768 tokens at 8x, 1 GB, encode and
+// decode: 1228 -> 1180 us; of 4000 tokens, whose 131 MB a call finds in that cache: 115 without, 122 with).  A copy of the whole tile: as a choice per
+// transfer it cost the small calls 2 to 4 %, as two main loops in front of one epilogue all calls half of their speed, in moves of accumulators.
+template <typename XT, int NTP> constexpr bool enc_once() { return sizeof(XT) == 2 && NTP != 6; }
 template <int NTW, int WC, typename XT, int NW, bool ONCE>
 __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
                                             const KernelArgs& a, uint4* work) {
@@ -320,9 +353,11 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     constexpr int NTH = NW * 64;             // threads of the workgroup
     constexpr int WT = NW / WC;              // waves across tokens
     constexpr int TOK_WG = 32 * TT * WT;
-    constexpr int KS = enc_ks(NTP, (int)sizeof(XT));
-    constexpr int NSTAGE = enc_stages(NTP, (int)sizeof(XT), NW, WC);
+    constexpr int KS = enc_ks(NTP, (int)sizeof(XT), ONCE);
+    constexpr int NSTAGE = enc_stages(NTP, (int)sizeof(XT), NW, WC, ONCE);
     constexpr int SLAB_U4 = KS * NTP * 64;
+    constexpr int KX = enc_kx(NTP, (int)sizeof(XT), ONCE), SPC = KX / KS;      // k-steps whose X comes together; steps (stages) to them
+    constexpr int NXS = SPC == 1 ? NSTAGE : 2;                  // slabs of the X ring
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wt = wave / WC;
@@ -351,16 +386,15 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
 
     f32x16 acc[TT][NTW];
 
-    // ---- LDS: a ring of NSTAGE stages, each one basis slab and one X slab ----------
-    using XS = XSlab<XT, KS>;
+    // ---- LDS: a ring of NSTAGE basis slabs (a stage each) and one of NXS X slabs ----------
+    using XS = XSlab<XT, KX>;
     constexpr int XSLAB_B = TOK_WG * XS::ROW_B;
-    constexpr int STAGE_B = SLAB_U4 * 16 + XSLAB_B;
-    constexpr int NX_TOTAL = TOK_WG / XS::ROWS_PER_DMA;         // X transfers per stage, dealt round-robin to the waves
+    constexpr int NX_TOTAL = TOK_WG / XS::ROWS_PER_DMA;         // X transfers per slab, dealt round-robin to the waves
     constexpr int NXD = (NX_TOTAL + NW - 1) / NW;
     constexpr int NV_TOTAL = SLAB_U4 / 64;                      // basis transfers per stage (1 KB each), dealt the same way
     constexpr int NV = (NV_TOTAL + NW - 1) / NW;
-    constexpr int NDMA_MIN = enc_least_pieces<NTP, NW, NV_TOTAL>() + NX_TOTAL / NW;     // transfers per wave per stage, lower bound over waves and plans
-    static_assert(TOK_WG % XS::ROWS_PER_DMA == 0, "whole transfers");
+    constexpr int NV_MIN = enc_least_pieces<NTP, NW, NV_TOTAL>(), NX_MIN = NX_TOTAL / NW;       // transfers per wave, lower bound over waves and plans
+    static_assert(TOK_WG % XS::ROWS_PER_DMA == 0 && KX % KS == 0, "whole transfers, whole steps");
     static_assert(3 * (NV + NXD) < 64, "vmcnt range");
     static_assert(NW >= 2, "waves 0 and 1 fetch the plan's tables");
     char* ring = reinterpret_cast<char*>(smem);
@@ -380,7 +414,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
         const int col = (lane % XS::COLS) ^ XS::swz(row);
         const int t = min(row, T - 1 - tok_tile0);              // tail rows re-read the last token
         xsrc[j] = (uint32_t)t * (uint32_t)(a.ld_x * (int64_t)sizeof(XT)) + (uint32_t)(col * 16);
-        xdst[j] = (uint32_t)(SLAB_U4 * 16 + row0 * XS::ROW_B);
+        xdst[j] = (uint32_t)(NSTAGE * SLAB_U4 * 16 + row0 * XS::ROW_B);
     }
     const uint32_t lds_ring = lds_offset(ring);
 
@@ -391,29 +425,32 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     // (heads or layers apart in memory) every whole block before it adds the gap between blocks
     const int blk_lg = a.x_blk_log2;
     const size_t blk_jump_b = (size_t)a.x_blk_jump * sizeof(XT);
-    auto issue = [&](int s, int stage) {
-        const uint32_t base = lds_ring + stage * STAGE_B;
-        const size_t xoff = (size_t)s * XS::ROW_B + (blk_lg ? (size_t)((s * (16 * KS)) >> blk_lg) * blk_jump_b : (size_t)0);
+    auto issue_basis = [&](int s, int stage) {
+        const uint32_t base = lds_ring + stage * SLAB_U4 * 16;
         const uint4* vsrc = vg + (size_t)s * SLAB_U4;           // scalar addresses plus a lane offset
 #pragma unroll
         for (int i = 0; i < NV; ++i)
             if (enc_basis_pieces<NTP, NW, NV_TOTAL>(i) || (i * NW + wave < NV_TOTAL && (i * NW + wave) % NTP < nt))
                 dma16_async(vsrc + i * NTH, (uint32_t)tid * 16u, base + (i * NTH + wave * 64) * 16);
+    };
+    auto issue_x = [&](int c, int slab) {
+        const uint32_t base = lds_ring + slab * XSLAB_B;
+        const size_t xoff = (size_t)c * XS::ROW_B + (blk_lg ? (size_t)((c * (16 * KX)) >> blk_lg) * blk_jump_b : (size_t)0);
 #pragma unroll
         for (int j = 0; j < NXD; ++j)
             if ((j + 1) * NW <= NX_TOTAL || j * NW + wave < NX_TOTAL)
                 ONCE ? dma16_async_once(xtile + xoff, xsrc[j], base + xdst[j]) : dma16_async(xtile + xoff, xsrc[j], base + xdst[j]);
     };
     // (a wave with a tile fewer than NTW reads the next wave's, or padding, in its place)
-    auto compute = [&](int stage) {
-        const uint4* abase = reinterpret_cast<const uint4*>(ring + stage * STAGE_B) + ct0 * 64 + lane;
-        const char* xs = ring + stage * STAGE_B + SLAB_U4 * 16;
+    auto compute = [&](int stage, int slab, int ks0) {          // ks0: the step's first k-step inside the X slab
+        const uint4* abase = reinterpret_cast<const uint4*>(ring + stage * SLAB_U4 * 16) + ct0 * 64 + lane;
+        const char* xs = ring + NSTAGE * SLAB_U4 * 16 + slab * XSLAB_B;
         constexpr int NSTEP = KS * NTW;
         bf16x8 xv[KS][TT];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt) xv[ks][tt] = XS::frag(xs, (wt * TT + tt) * 32 + l32, ks, h);
+            for (int tt = 0; tt < TT; ++tt) xv[ks][tt] = XS::frag(xs, (wt * TT + tt) * 32 + l32, ks0 + ks, h);
         uint4 af[3];
         af[0] = abase[0];
         if (NSTEP > 1) af[1] = abase[((1 / NTW) * NTP + (1 % NTW)) * 64];
@@ -433,10 +470,22 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     };
 
     constexpr int D = NSTAGE - 1;                               // prefetch distance in steps
+    const int n_chunks = n_slabs / SPC;
+    if constexpr (SPC == 1) {
 #pragma unroll
-    for (int u = 0; u < D; ++u)
-        if (u < n_slabs) issue(u, u);
-    wait_vmem_times<NDMA_MIN>(min(D - 1, n_slabs - 1));         // stage 0 has landed, and the tables before it
+        for (int u = 0; u < D; ++u)
+            if (u < n_slabs) { issue_basis(u, u); issue_x(u, u); }
+        wait_vmem_times<NV_MIN + NX_MIN>(min(D - 1, n_slabs - 1));       // stage 0 has landed, and the tables before it
+    } else {
+        // in the order of the loop's steps, which D of them would have been in front of it: a slab of X goes out behind the basis of step SPC * c - SPC + D
+        if (SPC > D) issue_x(0, 0);
+#pragma unroll
+        for (int t = -D; t < 0; ++t) {
+            if (t + D < n_slabs) issue_basis(t + D, t + D);
+            if (t == -SPC) issue_x(0, 0);
+        }
+        wait_vmem<0>();
+    }
     __syncthreads();
 
     // ---- accumulators start at -(mu^T V_kept): centring folded into the product ------
@@ -454,15 +503,25 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
             for (int tt = 0; tt < TT; ++tt) acc[tt][ct] = c;
         }
     }
-    for (int s0 = 0; s0 < n_slabs; s0 += NSTAGE) {
+    constexpr int UNROLL = SPC == 1 ? NSTAGE : enc_common(NSTAGE, 2 * SPC);
+    for (int s0 = 0; s0 < n_slabs; s0 += UNROLL) {
 #pragma unroll
-        for (int u = 0; u < NSTAGE; ++u) {
+        for (int u = 0; u < UNROLL; ++u) {
             const int s = s0 + u;
             if (s < n_slabs) {
-                // stage (u + D) % NSTAGE was read in step s - 1; the barrier that ended it frees it
-                if (s + D < n_slabs) issue(s + D, (u + D) % NSTAGE);
-                compute(u);
-                wait_vmem_times<NDMA_MIN>(min(D - 1, n_slabs - 2 - s));   // stage of step s + 1 has landed
+                // stage (u + D) % NSTAGE was read in step s - 1; the barrier that ended it frees it, and so the other X slab at a slab's end
+                if (s + D < n_slabs) issue_basis(s + D, (u + D) % NSTAGE);
+                if constexpr (SPC == 1) {
+                    if (s + D < n_slabs) issue_x(s + D, (u + D) % NSTAGE);
+                    compute(u, u, 0);
+                    wait_vmem_times<NV_MIN + NX_MIN>(min(D - 1, n_slabs - 2 - s));   // stage of step s + 1 has landed
+                } else {
+                    const bool more = s / SPC + 1 < n_chunks;
+                    if (u % SPC == 0 && more) issue_x(s / SPC + 1, (u / SPC + 1) & 1);
+                    compute(u % NSTAGE, (u / SPC) & 1, (u % SPC) * KS);
+                    // the basis of step s + 1 has landed and, in front of a new slab of X, that: what is younger may be in flight
+                    if (more && s + D < n_slabs) wait_vmem_dyn(enc_in_flight(u, D, SPC, NV_MIN, NX_MIN)); else wait_vmem<0>();      // (a constant: the loop is unrolled)
+                }
                 __syncthreads();
             }
         }
@@ -478,7 +537,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
 // whose plan uses its variant.
 // (must agree with the host's variant table)
 template <int WC, int NTW, int NW> constexpr int enc_wgs_per_cu() {
-    return NW == 4 && WC == 2 && NTW == 3 ? 3 : (NW == 4 && WC * NTW <= 10 ? 2 : 1);
+    return NW != 4 ? 1 : (WC == 2 && NTW == 3 ? 3 : 2);
 }
 
 template <int NTW, typename XT, int TT, int TOK, int AHEAD, bool BULK>
@@ -498,7 +557,7 @@ __global__ void __launch_bounds__(NW * 64, (enc_wgs_per_cu<WC, NTW, NW>())) kvtc
         const bool once = launch_bytes >= (256ull << 20);
         if constexpr (WC == 8)
             encode_register_tile<NTW, XT, enc_tt(NTW * WC, NW, WC), 32 * enc_tt(NTW * WC, NW, WC), 4, true>(P, tr, a, work, once);
-        else if (enc_once<XT, WC, NW>() && once) encode_tile<NTW, WC, XT, NW, enc_once<XT, WC, NW>()>(P, tr, a, work);
+        else if (enc_once<XT, NTW * WC>() && once) encode_tile<NTW, WC, XT, NW, enc_once<XT, NTW * WC>()>(P, tr, a, work);
         else encode_tile<NTW, WC, XT, NW, false>(P, tr, a, work);
     }
 }
@@ -877,9 +936,9 @@ int encode_tok_wg(int ntw, int wc, int nw) { return 32 * enc_tt(ntw * wc, nw, wc
 int encode_lds_bytes(int ntw, int wc, int nw, int n_groups, int rec_dwords, kvtc_dtype dtype) {
     const int ntp = ntw * wc;
     const int eb = dtype == KVTC_BF16 ? 2 : 4;
-    const int ks = enc_ks(ntp, eb);
     const int tok_wg = 32 * enc_tt(ntp, nw, wc) * (nw / wc);
-    const int main_b = wc == 8 ? 2 * tok_wg * 512 : enc_stages(ntp, eb, nw, wc) * (ks * ntp * 1024 + tok_wg * ks * (dtype == KVTC_BF16 ? 32 : 64));
+    const int ring_b = enc_ring_bytes(ntp, eb, nw, wc, false), ring_once_b = enc_ring_bytes(ntp, eb, nw, wc, true);
+    const int main_b = wc == 8 ? 2 * tok_wg * 512 : (ring_b > ring_once_b ? ring_b : ring_once_b);
     const int epi_b = tok_wg * (2 * ntp * 8 + n_groups * 8 + (rec_dwords + 1) * 4);
     return enc_aux_bytes(ntp) + (main_b > epi_b ? main_b : epi_b);
 }

@@ -1,5 +1,5 @@
-"""Tensors beyond the last-level cache: decode stores the whole tiles of an output of more than half of it past the caches, encode of many coordinates
-reads an input of all of it and more without keeping it.  The same bits as in calls of a part of the tokens each."""
+"""Tensors beyond the last-level cache: decode stores the whole tiles of an output of more than half of it past the caches, encode
+reads a bf16 input of all of it and more without keeping it, by whole lines.  The same bits as in calls of a part of the tokens each."""
 import numpy as np
 import pytest
 import torch
@@ -40,7 +40,7 @@ def test_large_outputs_hold_what_small_ones_hold(r, dtype):
     assert torch.equal(got[:T, :p], want) and bool((got[:, p:] == 7.0).all()) and bool((got[T] == 7.0).all())
 
 
-@pytest.mark.parametrize("r", [384, 512, 544, 736, 768, 800, 1024])
+@pytest.mark.parametrize("r", [64, 128, 192, 224, 256, 272, 304, 384, 512, 544, 736, 768, 800, 1024])
 def test_large_inputs_are_coded_as_small_ones(r):
     plan = _gpu_plan(_variant_plan(r))
     p, R, T = 1024, plan.record_bytes, 131072 + 77                # 256 MB and some
