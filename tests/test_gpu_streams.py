@@ -1,11 +1,11 @@
 """Tensors beyond the last-level cache: decode stores the whole tiles of an output of more than half of it past the caches, encode
-reads a bf16 input of all of it and more without keeping it, by whole lines.  The same bits as in calls of a part of the tokens each."""
+reads an input of all of it and more without keeping it, by whole lines.  The same bits as in calls of a part of the tokens each."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2511_01815_amd as kv
-from test_gpu_parity import DEV, _gpu_plan, _variant_plan
+from test_gpu_parity import DEV, _gpu_plan, _manual, _variant_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -40,15 +40,17 @@ def test_large_outputs_hold_what_small_ones_hold(r, dtype):
     assert torch.equal(got[:T, :p], want) and bool((got[:, p:] == 7.0).all()) and bool((got[T] == 7.0).all())
 
 
-@pytest.mark.parametrize("r", [64, 128, 192, 224, 256, 272, 304, 384, 512, 544, 736, 768, 800, 1024])
-def test_large_inputs_are_coded_as_small_ones(r):
-    plan = _gpu_plan(_variant_plan(r))
-    p, R, T = 1024, plan.record_bytes, 131072 + 77                # 256 MB and some
-    x = torch.randn((T, p), generator=torch.Generator(device=DEV).manual_seed(r), device=DEV).to(torch.bfloat16)
+@pytest.mark.parametrize("r,dtype", [(r, kv.KVTC_BF16) for r in (64, 128, 192, 224, 256, 272, 304, 384, 512, 544, 736, 768, 800, 1024)] +
+                         [(r, kv.KVTC_F32) for r in (32, 64, 96, 128)])
+def test_large_inputs_are_coded_as_small_ones(r, dtype):
+    plan = _gpu_plan(_variant_plan(r) if r >= 64 else _manual(1024, [(16, 4)] * (r // 16), 100 + r))
+    p, R, T = 1024, plan.record_bytes, (131072 if dtype == kv.KVTC_BF16 else 81920) + 77      # 256 (fp32: 320) MB and some
+    x = torch.randn((T, p), generator=torch.Generator(device=DEV).manual_seed(r), device=DEV)
+    x = x.to(torch.bfloat16) if dtype == kv.KVTC_BF16 else x
     got = torch.zeros((T, R), dtype=torch.uint8, device=DEV)
-    kv.kvtc_encode(plan.handle, x, kv.KVTC_BF16, T, p, got, got.numel())
+    kv.kvtc_encode(plan.handle, x, dtype, T, p, got, got.numel())
     part = torch.zeros((20001, R), dtype=torch.uint8, device=DEV)
     for t0 in range(0, T, 20001):
         n = min(20001, T - t0)
-        kv.kvtc_encode(plan.handle, x[t0:], kv.KVTC_BF16, n, p, part, part.numel())
+        kv.kvtc_encode(plan.handle, x[t0:], dtype, n, p, part, part.numel())
         assert torch.equal(got[t0:t0 + n], part[:n]), (r, t0)
