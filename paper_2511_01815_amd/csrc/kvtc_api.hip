@@ -481,6 +481,16 @@ static kvtc_status check_x(const char* who, const void* x, kvtc_dtype dtype, int
 // gap between a block's end and the token's next block.
 struct XLayout { int64_t ld; int32_t blk_log2; int64_t blk_jump; };
 
+// Whether the 128 bytes of a row that a kernel asks for or writes at once are always one cache line (a row's offset is a multiple of the pitch; what
+// precedes a block in its row is whole pieces of 64 features and gaps between blocks).  The kernels pass the caches by only then: a piece on two
+// lines is two parts of lines, and every line would be fetched again or written in parts.  150000 tokens of bf16 with rows of 2064 bytes, us, kept by
+// the caches and past them: decode of 64, 128, 240 and 272 coordinates 111, 119, 140 and 142 against 315, 313, 320 and 321; encode of 64, 128 and 240
+// 87, 120 and 132 against 106, 133 and 147 (of 272 174 against 151, with rows of 2048 bytes on an odd base 145 against 155).
+static int32_t whole_lines(const void* x, kvtc_dtype dtype, const XLayout& xl) {
+    const uint64_t eb = elem_size(dtype);
+    return ((reinterpret_cast<uintptr_t>(x) | (uint64_t)xl.ld * eb | (uint64_t)xl.blk_jump * eb) & 127u) == 0 ? 1 : 0;
+}
+
 // Checks a kvtc_layout for a tensor of p features (n_tokens < 0: unknown, as in a batched call) and converts it.
 static kvtc_status check_layout(const char* who, const void* x, kvtc_dtype dtype, const kvtc_layout* lay, int p, int64_t n_tokens,
                                 XLayout* out) {
@@ -518,6 +528,12 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
 static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const void* in_dev, size_t in_bytes, int64_t n_tokens,
                                  void* x_out_dev, kvtc_dtype dtype, const kvtc_layout* layout, kvtc_stream stream, int accumulate = 0,
                                  const float* sum_dev = nullptr, int64_t sum_ld = 0);
+
+int kvtc_host_whole_lines(uint64_t x_address, kvtc_dtype dtype, int p, const kvtc_layout* layout) {
+    XLayout xl;
+    const void* x = reinterpret_cast<const void*>(static_cast<uintptr_t>(x_address));
+    return check_layout("kvtc_host_whole_lines", x, dtype, layout, p, -1, &xl) == KVTC_OK ? whole_lines(x, dtype, xl) : -1;
+}
 
 kvtc_status kvtc_encode(const kvtc_plan* plan, const void* x_dev, kvtc_dtype dtype, int64_t n_tokens, int64_t ld_x,
                         void* out_dev, size_t out_cap, kvtc_stream stream) {
@@ -562,6 +578,7 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
     a.ld_x = xl.ld;
     a.x_blk_log2 = xl.blk_log2;
     a.x_blk_jump = xl.blk_jump;
+    a.x_lines = whole_lines(x_dev, dtype, xl);
     a.stream_buf = out_dev;
     a.cap = out_cap;
     a.status = nullptr;
@@ -607,6 +624,7 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
     a.ld_x = xl.ld;
     a.x_blk_log2 = xl.blk_log2;
     a.x_blk_jump = xl.blk_jump;
+    a.x_lines = whole_lines(x_out_dev, dtype, xl);
     a.stream_buf = const_cast<void*>(in_dev);
     a.cap = in_bytes;
     a.dec_accumulate = accumulate;
@@ -908,6 +926,7 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.ld_x = ld_x;
     a.x_blk_log2 = xl.blk_log2;
     a.x_blk_jump = xl.blk_jump;
+    a.x_lines = whole_lines(x_base_dev, dtype, xl);
     a.stream_buf = out_base_dev;
     a.cap = out_cap;
     a.status = status_dev;
@@ -979,6 +998,7 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     a.offsets = sc->offsets;
     a.x = x_base_dev;
     a.ld_x = ld_x;
+    a.x_lines = whole_lines(x_base_dev, dtype, XLayout{ld_x, 0, 0});
     a.stream_buf = out_base_dev;
     a.cap = out_cap;
     a.status = status_dev;
@@ -1012,6 +1032,7 @@ kvtc_status kvtc_decode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.ld_x = ld_x;
     a.x_blk_log2 = xl.blk_log2;
     a.x_blk_jump = xl.blk_jump;
+    a.x_lines = whole_lines(x_out_base_dev, dtype, xl);
     a.stream_buf = const_cast<void*>(in_base_dev);
     a.cap = in_bytes;
     a.status = status_dev;

@@ -160,8 +160,8 @@ __device__ __forceinline__ float2 load_part(const char* sb, uint32_t lrow, int t
 // What is decoded next to it -- the bases, in an L2 of 4 MB -- is then not pushed out by output that nobody finds there again: 32-layer cache at
 // 16x 1265 -> 1131 us, 64 tensors of 8000 tokens at 20x 323 -> 228, four layers under one basis, both ways, 1364 -> 1261.  Below, what reads the output next
 // does find it (the keys of 32768 tokens, 64 MB, decoded and rotated: 122 us, 131 with such stores; of 60000, 123 MB: 259 and 256).
-__device__ __forceinline__ bool output_streams(uint32_t tiles, int tile_tokens, int p, int elem_bytes) {
-    return (uint64_t)tiles * (uint64_t)(uint32_t)(tile_tokens * elem_bytes) * (uint64_t)(uint32_t)p > (128ull << 20);
+__device__ __forceinline__ bool output_streams(const KernelArgs& a, uint32_t tiles, int tile_tokens, int p, int elem_bytes) {
+    return a.x_lines != 0 && (uint64_t)tiles * (uint64_t)(uint32_t)(tile_tokens * elem_bytes) * (uint64_t)(uint32_t)p > (128ull << 20);
 }
 
 // The results of a pair of feature tiles (acc0: the even, acc1: the odd features of 64-feature span `span`) to the output.  `fast`: every row of
@@ -442,7 +442,7 @@ __global__ void __launch_bounds__(kThreads, (dec_wgs_per_cu<TT, CLS>())) kvtc_de
     if (tile >= mine.end) return;
     TileRef tr = find_tile(a, tile_start, tile);
     PlanDec P = load_plan_dec(a.plans + tr.plan);
-    const bool streamed = TT > 1 && output_streams(total, 4 * 32 * TT, P.p, (int)sizeof(OT));
+    const bool streamed = TT > 1 && output_streams(a, total, 4 * 32 * TT, P.p, (int)sizeof(OT));
     P.dec_tok_wg = 4 * 32 * TT;
     issue_records(a, tr, P, lds_offset(work));
     wait_vmem<0>();
@@ -647,7 +647,7 @@ __global__ void __launch_bounds__(kWideThreads, 1) kvtc_decode_wide_kernel(const
         const uint32_t pairs = (uint32_t)P.p / 64u, n = min(max(parts, 1u), max(pairs / 4u, 1u));
         if (part >= n) return;
         decode_wide_tile<TT, OT, ACC>(P, tr, a, work, (int)(part * pairs / n), (int)((part + 1u) * pairs / n),
-                                      output_streams(total, 32 * TT, P.p, (int)sizeof(OT)));
+                                      output_streams(a, total, 32 * TT, P.p, (int)sizeof(OT)));
     }
 }
 

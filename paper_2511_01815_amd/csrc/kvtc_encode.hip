@@ -557,7 +557,7 @@ __global__ void __launch_bounds__(NW * 64, (enc_wgs_per_cu<WC, NTW, NW>())) kvtc
         const uint64_t launch_bytes = (uint64_t)total * (uint64_t)(uint32_t)(32 * enc_tt(NTW * WC, NW, WC) * (NW / WC)) * (uint64_t)((uint32_t)P.p * (uint32_t)sizeof(XT));
         // (the caches keep some of an fp32 input of a little more than their size from one call to the next: two tensors of 35000 tokens at 40x, 287 MB, 63 us
         // and 81 without keeping it, of 41000, 336 MB, 84.4 and 83.7; bf16: of 67000, 274 MB, 53.9 and 55.5, of 75000, 307 MB, 71 and 64)
-        const bool once = launch_bytes >= ((sizeof(XT) == 2 ? 256ull : 320ull) << 20);
+        const bool once = a.x_lines != 0 && launch_bytes >= ((sizeof(XT) == 2 ? 256ull : 320ull) << 20);
         if constexpr (WC == 8)
             encode_register_tile<NTW, XT, enc_tt(NTW * WC, NW, WC), 32 * enc_tt(NTW * WC, NW, WC), 4, true>(P, tr, a, work, once);
         else if (enc_once<XT, NTW * WC>() && once) encode_tile<NTW, WC, XT, NW, enc_once<XT, NTW * WC>()>(P, tr, a, work);

@@ -66,6 +66,25 @@ def test_header_and_code_decision_match_oracle(bits):
         assert got == codes[t].tolist(), t
 
 
+@pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
+def test_only_arrays_on_whole_cache_lines_pass_the_caches(dtype):
+    """Base, row pitch and the gap between blocks: all multiples of 128 bytes, or a piece of a row is two parts of lines."""
+    per_line = 64 if dtype == kv.KVTC_BF16 else 32
+    base, eb = 1 << 40, 128 // per_line
+
+    def whole(address, layout):
+        return kv.lib().kvtc_host_whole_lines(address, dtype, 1024, C.byref(layout))
+
+    for skip in (0, per_line // 8, per_line // 2, per_line, 3 * per_line):                   # elements; multiples of 16 bytes
+        on = 1 if skip % per_line == 0 else 0
+        assert whole(base + skip * eb, kv.layout(1024)) == on, skip
+        assert whole(base, kv.layout(1024 + skip)) == on, skip
+        assert whole(base, kv.layout(128 + skip, 128, 5000 * (128 + skip))) == on, skip      # heads-major, rows apart
+        assert whole(base, kv.layout(128, 128, 5000 * 128 + skip)) == on, skip               # heads-major, heads apart
+        assert whole(base, kv.layout(8 * (128 + skip), 128, 128 + skip)) == on, skip         # heads apart inside a token's row
+    assert whole(base + 2, kv.layout(1024)) == -1 and whole(base, kv.layout(1000)) == -1
+
+
 def test_argument_errors_need_no_gpu():
     L = kv.lib()
     p, r = 64, 16
