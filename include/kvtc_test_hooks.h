@@ -1,5 +1,5 @@
 /*
- * kvtc_test_hooks.h -- internal: exports of the library that let tests run, without a GPU, the
+ * kvtc_test_hooks.h -- internal: exports of the library that let tests run, for the most part without a GPU, the
  * scalar quantiser numerics (csrc/kvtc_numeric.h: the directed fp32 -> fp16 roundings of the shared
  * shift (down) and scale (up), paper Section "Quantization", the group header, and the code decision
  * for one value) and the rules by which a call's route is chosen.  Not part of the coder's API;
@@ -23,6 +23,11 @@ uint32_t kvtc_host_code(float d, uint16_t shift16, uint16_t scale16, int bits);
 /* 1: a feature array at this address lies on whole cache lines, so a large one is read or written past the
  * caches; 0: it does not, so none is; -1: the library refuses the array. */
 int kvtc_host_whole_lines(uint64_t x_address, kvtc_dtype dtype, int p, const kvtc_layout* layout);
+
+/* On the GPU: *passes_dev = 1 if a launch over these jobs takes a call's features, tokens times features over all jobs that
+ * are valid, for `elements` or more, else 0. */
+kvtc_status kvtc_test_batch_passes(const kvtc_batch* batch, const kvtc_job* jobs_dev, int n_jobs, const uint64_t* offsets_dev, size_t stream_bytes,
+                                   uint64_t elements, uint32_t* passes_dev, kvtc_stream stream);
 
 #ifdef __cplusplus
 }

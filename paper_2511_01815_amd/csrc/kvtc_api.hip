@@ -24,6 +24,8 @@ int encode_short_ntw(int ntp);
 int encode_short_waves(int ntp);
 int encode_short_lds_bytes(int ntp, int n_groups, int rec_dwords, kvtc_dtype dtype);
 int encode_tok_wg(int ntw, int wc, int nw);
+uint64_t encode_pass_bytes(int ntp, kvtc_dtype dtype);
+uint64_t decode_pass_bytes();
 hipError_t launch_fp8_pack(const void* x, kvtc_dtype dtype, int64_t n_tokens, int p, int64_t ld_x, void* out, hipStream_t stream);
 hipError_t launch_fp8_unpack(const void* in, int64_t n_tokens, int p, void* x, kvtc_dtype dtype, int64_t ld_x, hipStream_t stream);
 hipError_t launch_offsets_append(const uint32_t* rec_dwords, int n_plans, const kvtc_job* jobs, int n_jobs, const uint64_t* region,
@@ -179,6 +181,13 @@ static __device__ __align__(256) unsigned char scratch[sizeof(StaticScratch)];
 struct PlanPtrs { const PlanDev* p[kStaticMaxPlans]; };
 
 // descriptor of plan i (inside the plan's own device blob) -> table entry i; one thread per dword
+// (for a test of the table's count)
+__global__ void __launch_bounds__(kThreads) batch_passes_kernel(const KernelArgs a, int variant_key, uint32_t* passes) {
+    __shared__ uint32_t tile_start[kMaxJobs + 1], scratch[8 * kThreads / 64];
+    const TileTable table = build_tile_table<true>(a, variant_key, tile_start, scratch);
+    if (threadIdx.x == 0) *passes = table.pass ? 1u : 0u;
+}
+
 __global__ void __launch_bounds__(256) gather_plans_kernel(const PlanPtrs src, int n_plans, StaticScratch* sc) {
     constexpr int kDw = (int)(sizeof(PlanDev) / 4);
     static_assert(sizeof(PlanDev) % 4 == 0, "descriptor is whole dwords");
@@ -486,9 +495,20 @@ struct XLayout { int64_t ld; int32_t blk_log2; int64_t blk_jump; };
 // lines is two parts of lines, and every line would be fetched again or written in parts.  150000 tokens of bf16 with rows of 2064 bytes, us, kept by
 // the caches and past them: decode of 64, 128, 240 and 272 coordinates 111, 119, 140 and 142 against 315, 313, 320 and 321; encode of 64, 128 and 240
 // 87, 120 and 132 against 106, 133 and 147 (of 272 174 against 151, with rows of 2048 bytes on an odd base 145 against 155).
-static int32_t whole_lines(const void* x, kvtc_dtype dtype, const XLayout& xl) {
+static bool whole_lines(const void* x, kvtc_dtype dtype, const XLayout& xl) {
     const uint64_t eb = elem_size(dtype);
-    return ((reinterpret_cast<uintptr_t>(x) | (uint64_t)xl.ld * eb | (uint64_t)xl.blk_jump * eb) & 127u) == 0 ? 1 : 0;
+    return ((reinterpret_cast<uintptr_t>(x) | (uint64_t)xl.ld * eb | (uint64_t)xl.blk_jump * eb) & 127u) == 0;
+}
+
+// KernelArgs::x_pass_from of a launch whose variant passes the caches from `from` bytes of the call's features on: a tensor of `elements`, or a batch,
+// whose elements are on the device and can't be more than that.
+static float pass_from(bool lines, uint64_t from, kvtc_dtype dtype, uint64_t elements, bool batch) {
+    const bool may = lines && from / elem_size(dtype) <= elements;
+    return !may ? HUGE_VALF : batch ? (float)(from / elem_size(dtype)) : 0.0f;
+}
+// Tokens of a batch at most, by the size of its stream buffer (jobs do not overlap there), times features.
+static uint64_t most_elements(size_t stream_bytes, int min_rec_dwords, int max_p) {
+    return (uint64_t)(stream_bytes / ((size_t)min_rec_dwords * 4)) * (uint64_t)max_p;
 }
 
 // Checks a kvtc_layout for a tensor of p features (n_tokens < 0: unknown, as in a batched call) and converts it.
@@ -532,7 +552,7 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
 int kvtc_host_whole_lines(uint64_t x_address, kvtc_dtype dtype, int p, const kvtc_layout* layout) {
     XLayout xl;
     const void* x = reinterpret_cast<const void*>(static_cast<uintptr_t>(x_address));
-    return check_layout("kvtc_host_whole_lines", x, dtype, layout, p, -1, &xl) == KVTC_OK ? whole_lines(x, dtype, xl) : -1;
+    return check_layout("kvtc_host_whole_lines", x, dtype, layout, p, -1, &xl) == KVTC_OK ? (int)whole_lines(x, dtype, xl) : -1;
 }
 
 kvtc_status kvtc_encode(const kvtc_plan* plan, const void* x_dev, kvtc_dtype dtype, int64_t n_tokens, int64_t ld_x,
@@ -578,7 +598,6 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
     a.ld_x = xl.ld;
     a.x_blk_log2 = xl.blk_log2;
     a.x_blk_jump = xl.blk_jump;
-    a.x_lines = whole_lines(x_dev, dtype, xl);
     a.stream_buf = out_dev;
     a.cap = out_cap;
     a.status = nullptr;
@@ -590,6 +609,7 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
     } else {
         const int64_t tiles = (n_tokens + plan->h.enc_tok_wg - 1) / plan->h.enc_tok_wg;
         a.single_tiles = (uint32_t)tiles;
+        a.x_pass_from = pass_from(whole_lines(x_dev, dtype, xl), encode_pass_bytes(plan->h.enc_ntw * plan->h.enc_wc, dtype), dtype, (uint64_t)n_tokens * (uint64_t)plan->h.p, false);
         const int slots = compute_units() * plan->h.enc_wgs;
         const int grid = (int)(tiles < slots ? tiles : slots);
         e = launch_encode(a, dtype, plan->h.enc_nw * 10000 + plan->h.enc_wc * 100 + plan->h.enc_ntw, grid, (size_t)kJobTableBytes + 64 + plan->h.enc_lds[dtype], static_cast<hipStream_t>(stream));
@@ -624,7 +644,6 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
     a.ld_x = xl.ld;
     a.x_blk_log2 = xl.blk_log2;
     a.x_blk_jump = xl.blk_jump;
-    a.x_lines = whole_lines(x_out_dev, dtype, xl);
     a.stream_buf = const_cast<void*>(in_dev);
     a.cap = in_bytes;
     a.dec_accumulate = accumulate;
@@ -643,11 +662,13 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
         a.dec_ring_off = lay.ring_off;
         a.dec_short = 1;
         a.single_tiles = (uint32_t)tiles_short;
+        a.x_pass_from = HUGE_VALF;
         const int grid = (int)(tiles_short * spans < slots ? tiles_short * spans : slots);
         e = launch_decode(a, dtype, 100 + plan->h.dec_cls, grid, lay.lds_bytes, static_cast<hipStream_t>(stream));
     } else {
         const int64_t tiles = (n_tokens + plan->h.dec_tok_wg - 1) / plan->h.dec_tok_wg;
         a.single_tiles = (uint32_t)tiles;
+        a.x_pass_from = pass_from(whole_lines(x_out_dev, dtype, xl), decode_pass_bytes(), dtype, (uint64_t)n_tokens * (uint64_t)plan->h.p, false);
         const int64_t shares = wide ? (spans < 4 ? 1 : spans / 4) : spans;       // workgroups a tile may be shared among
         const int grid = (int)(tiles * shares < slots ? tiles * shares : slots);
         const DecLayout lay = decode_layout(plan->h.dec_rec_lds, plan->h.dec_ring_lds, plan->h.dec_wgs);
@@ -854,7 +875,8 @@ struct EncodeLaunches {
     int n_bulk;
     struct Short { int waves, lds; } shrt[3];            // by coordinate tiles per wave; waves = 0: none
     bool all_short;
-    int min_rec_dwords;
+    int min_rec_dwords, max_p;
+    bool lines;                                          // the feature array lies on whole cache lines
 };
 
 static kvtc_status launch_encode_jobs(const char* who, const EncodeLaunches& l, KernelArgs& a, kvtc_dtype dtype, hipStream_t st) {
@@ -872,8 +894,11 @@ static kvtc_status launch_encode_jobs(const char* who, const EncodeLaunches& l, 
         const int s_tiles = short_tiles_per_job(a.n_jobs, pairs);
         a.enc_short_max = s_tiles * kEncShortTile;
         a.enc_cus = compute_units();
-        for (int k = 0; k < l.n_bulk && e == hipSuccess; ++k)
+        for (int k = 0; k < l.n_bulk && e == hipSuccess; ++k) {
+            const int key = l.bulk[k].key, ntp = key / 100 % 100 * (key % 100);
+            a.x_pass_from = pass_from(l.lines, encode_pass_bytes(ntp, dtype), dtype, most_elements(a.cap, l.min_rec_dwords, l.max_p), true);
             e = launch_encode(a, dtype, l.bulk[k].key, compute_units() * l.bulk[k].wgs, (size_t)kJobTableBytes + 64 + l.bulk[k].lds, st);
+        }
         for (int ntw = 1; ntw <= 2 && e == hipSuccess; ++ntw)
             if (l.shrt[ntw].waves != 0) e = launch_encode_short(a, dtype, ntw, l.shrt[ntw].waves, a.n_jobs * s_tiles, (size_t)l.shrt[ntw].lds, st);
     }
@@ -926,7 +951,6 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.ld_x = ld_x;
     a.x_blk_log2 = xl.blk_log2;
     a.x_blk_jump = xl.blk_jump;
-    a.x_lines = whole_lines(x_base_dev, dtype, xl);
     a.stream_buf = out_base_dev;
     a.cap = out_cap;
     a.status = status_dev;
@@ -934,6 +958,8 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     l.n_bulk = 0;
     l.all_short = batch->all_short;
     l.min_rec_dwords = batch->min_rec_dwords;
+    l.max_p = batch->max_p;
+    l.lines = whole_lines(x_base_dev, dtype, xl);
     for (int ntw = 1; ntw <= 2; ++ntw) l.shrt[ntw] = {batch->enc_short[ntw].waves, batch->enc_short[ntw].lds[dtype]};
     for (const auto& v : batch->enc) l.bulk[l.n_bulk++] = {v.key, v.wgs, v.lds[dtype]};
     return launch_encode_jobs("kvtc_encode_batch", l, a, dtype, static_cast<hipStream_t>(stream));
@@ -959,6 +985,8 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     l.n_bulk = 0;
     l.all_short = true;
     l.min_rec_dwords = 1 << 30;
+    l.max_p = 0;
+    l.lines = whole_lines(x_base_dev, dtype, XLayout{ld_x, 0, 0});
     l.shrt[1] = l.shrt[2] = {0, 0};
     PlanPtrs ptrs;
     for (int i = 0; i < n_plans; ++i) {
@@ -972,6 +1000,7 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
         if (k == l.n_bulk) l.bulk[l.n_bulk++] = {key, ph.enc_wgs, 0};
         l.bulk[k].lds = std::max(l.bulk[k].lds, ph.enc_lds[dtype]);
         l.min_rec_dwords = std::min(l.min_rec_dwords, ph.rec_dwords);
+        l.max_p = std::max(l.max_p, ph.p);
         l.all_short = l.all_short && ph.enc_short != 0;
         if (ph.enc_short != 0) {
             auto& v = l.shrt[ph.enc_short];
@@ -998,11 +1027,27 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
     a.offsets = sc->offsets;
     a.x = x_base_dev;
     a.ld_x = ld_x;
-    a.x_lines = whole_lines(x_base_dev, dtype, XLayout{ld_x, 0, 0});
     a.stream_buf = out_base_dev;
     a.cap = out_cap;
     a.status = status_dev;
     return launch_encode_jobs(who, l, a, dtype, st);
+}
+
+kvtc_status kvtc_test_batch_passes(const kvtc_batch* batch, const kvtc_job* jobs_dev, int n_jobs, const uint64_t* offsets_dev, size_t stream_bytes,
+                                   uint64_t elements, uint32_t* passes_dev, kvtc_stream stream) {
+    if (!batch || !jobs_dev || !offsets_dev || !passes_dev || n_jobs < 1 || n_jobs > kMaxJobs) return fail(KVTC_E_ARG, "kvtc_test_batch_passes: bad argument");
+    KernelArgs a;
+    memset(&a, 0, sizeof(a));
+    a.plans = batch->plans_dev;
+    a.n_plans = batch->n_plans;
+    a.jobs = jobs_dev;
+    a.n_jobs = n_jobs;
+    a.offsets = offsets_dev;
+    a.cap = stream_bytes;
+    a.x_pass_from = (float)elements;
+    hipLaunchKernelGGL(batch_passes_kernel, dim3(1), dim3(kThreads), 0, static_cast<hipStream_t>(stream), a, batch->enc[0].key, passes_dev);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? KVTC_OK : fail(KVTC_E_HIP, "kvtc_test_batch_passes: launch failed: %s", hipGetErrorString(e));
 }
 
 kvtc_status kvtc_decode_batch(const kvtc_batch* batch, const kvtc_job* jobs_dev, int n_jobs, const void* in_base_dev,
@@ -1032,11 +1077,11 @@ kvtc_status kvtc_decode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.ld_x = ld_x;
     a.x_blk_log2 = xl.blk_log2;
     a.x_blk_jump = xl.blk_jump;
-    a.x_lines = whole_lines(x_out_base_dev, dtype, xl);
     a.stream_buf = const_cast<void*>(in_base_dev);
     a.cap = in_bytes;
     a.status = status_dev;
     for (const auto& v : batch->dec) {
+        a.x_pass_from = pass_from(whole_lines(x_out_base_dev, dtype, xl), decode_pass_bytes(), dtype, most_elements(in_bytes, batch->min_rec_dwords, batch->max_p), true);
         // Jobs whose 128-token tiles can be shown to run all at once (the stream buffer's size bounds their tokens, and each may end in a
         // part of a tile) take the variant with one token tile per wave, as a single tensor does, where the mean job is no more than one such tile
         // or the tiles, twice as many with twice the basis traffic, are few: one per compute unit; of more plans than there are XCDs fewer, and

@@ -156,13 +156,13 @@ __device__ __forceinline__ float2 load_part(const char* sb, uint32_t lrow, int t
     return *reinterpret_cast<const float2*>(sb + ((size_t)row * sld + 2u * lane_col));
 }
 
-// Whether a launch's output passes the caches by (non-temporal stores; whole tiles only): where it is more than half of the 256 MB last-level cache.
+// Bytes of a call's output from which on it passes the caches by (non-temporal stores; whole tiles only): a little more than half of the 256 MB last-level cache.
 // What is decoded next to it -- the bases, in an L2 of 4 MB -- is then not pushed out by output that nobody finds there again: 32-layer cache at
 // 16x 1265 -> 1131 us, 64 tensors of 8000 tokens at 20x 323 -> 228, four layers under one basis, both ways, 1364 -> 1261.  Below, what reads the output next
 // does find it (the keys of 32768 tokens, 64 MB, decoded and rotated: 122 us, 131 with such stores; of 60000, 123 MB: 259 and 256).
-__device__ __forceinline__ bool output_streams(const KernelArgs& a, uint32_t tiles, int tile_tokens, int p, int elem_bytes) {
-    return a.x_lines != 0 && (uint64_t)tiles * (uint64_t)(uint32_t)(tile_tokens * elem_bytes) * (uint64_t)(uint32_t)p > (128ull << 20);
-}
+#if KVTC_DECODE_PART == 0
+uint64_t decode_pass_bytes() { return 129ull << 20; }
+#endif
 
 // The results of a pair of feature tiles (acc0: the even, acc1: the odd features of 64-feature span `span`) to the output.  `fast`: every row of
 // the tile is one of the tensor's, and with STREAM the output is to pass the caches by.  (Stores of either kind side by side, chosen per tile, cost the
@@ -412,7 +412,8 @@ __global__ void __launch_bounds__(kThreads, (dec_wgs_per_cu<TT, CLS>())) kvtc_de
     extern __shared__ uint4 smem[];
     uint32_t* tile_start = reinterpret_cast<uint32_t*>(smem);
     uint4* work = smem + kJobTableBytes / 16 + 1;
-    const uint32_t total = build_tile_table<false>(a, TT * 100 + CLS, tile_start, reinterpret_cast<uint32_t*>(work));
+    const TileTable table = build_tile_table<false>(a, TT * 100 + CLS, tile_start, reinterpret_cast<uint32_t*>(work));
+    const uint32_t total = table.total;
     const bool prefetch = a.dec_ring_off != 0u;
     uint4* ring = work + a.dec_ring_off / 16u;
     // Few tiles: every token tile is given to `parts` workgroups, each of which unpacks it again and sweeps its own share
@@ -442,7 +443,7 @@ __global__ void __launch_bounds__(kThreads, (dec_wgs_per_cu<TT, CLS>())) kvtc_de
     if (tile >= mine.end) return;
     TileRef tr = find_tile(a, tile_start, tile);
     PlanDec P = load_plan_dec(a.plans + tr.plan);
-    const bool streamed = TT > 1 && output_streams(a, total, 4 * 32 * TT, P.p, (int)sizeof(OT));
+    const bool streamed = TT > 1 && table.pass;
     P.dec_tok_wg = 4 * 32 * TT;
     issue_records(a, tr, P, lds_offset(work));
     wait_vmem<0>();
@@ -632,7 +633,8 @@ __global__ void __launch_bounds__(kWideThreads, 1) kvtc_decode_wide_kernel(const
     extern __shared__ uint4 smem[];
     uint32_t* tile_start = reinterpret_cast<uint32_t*>(smem);
     uint4* work = smem + kJobTableBytes / 16 + 1;
-    const uint32_t total = build_tile_table<false, kWideThreads>(a, TT * 100 + CLS, tile_start, reinterpret_cast<uint32_t*>(work));
+    const TileTable table = build_tile_table<false, kWideThreads>(a, TT * 100 + CLS, tile_start, reinterpret_cast<uint32_t*>(work));
+    const uint32_t total = table.total;
     // few tiles: several workgroups share a tile's features, as above, but no fewer than four pairs each (a wave per SIMD)
     const uint32_t parts = total ? gridDim.x / total : 0u;
     TileRange mine = my_tiles(total);
@@ -646,8 +648,7 @@ __global__ void __launch_bounds__(kWideThreads, 1) kvtc_decode_wide_kernel(const
         PlanDec P = load_plan_dec(a.plans + tr.plan);
         const uint32_t pairs = (uint32_t)P.p / 64u, n = min(max(parts, 1u), max(pairs / 4u, 1u));
         if (part >= n) return;
-        decode_wide_tile<TT, OT, ACC>(P, tr, a, work, (int)(part * pairs / n), (int)((part + 1u) * pairs / n),
-                                      output_streams(a, total, 32 * TT, P.p, (int)sizeof(OT)));
+        decode_wide_tile<TT, OT, ACC>(P, tr, a, work, (int)(part * pairs / n), (int)((part + 1u) * pairs / n), table.pass);
     }
 }
 

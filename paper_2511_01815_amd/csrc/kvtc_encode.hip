@@ -340,12 +340,13 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
     __syncthreads();
 }
 
-// ONCE (where X comes by whole lines: bf16 but of 6 tiles; fp32, whose two k-steps are one, up to 4): the launch's input is as much as the last-level cache, 256 MB, holds, or more (fp32: a quarter more); its lines, which are read
+// ONCE (where X comes by whole lines: bf16 but of 6 tiles; fp32, whose two k-steps are one, up to 4): the call's input is as much as the last-level cache, 256 MB, holds, or more (fp32: a quarter more); its lines, which are read
 // once, are then not to push the basis, of up to a megabyte a tensor, out of the L2s (11 to 20 tiles, 16 tensors of 32768 tokens at 8x, 1 GB, encode and
 // decode: 1228 -> 1180 us; of 4000 tokens, whose 131 MB a call finds in that cache: 115 without, 122 with).  fp32
 // at 40x: two tiles, 16 tensors of 20000 tokens, 268 -> 252, four tiles, two of 40000, 116 -> 110; of 6 and 16 tiles 1 to 4 % slower so.  A copy of the whole tile: as a choice per
 // transfer it cost the small calls 2 to 4 %, as two main loops in front of one epilogue all calls half of their speed, in moves of accumulators.
-template <typename XT, int NTP> constexpr bool enc_once() { return sizeof(XT) == 2 ? NTP != 6 : NTP <= 4; }
+constexpr bool enc_can_pass(int ntp, int elem_bytes) { return elem_bytes == 2 ? ntp != 6 : ntp <= 4; }
+template <typename XT, int NTP> constexpr bool enc_once() { return enc_can_pass(NTP, (int)sizeof(XT)); }
 template <int NTW, int WC, typename XT, int NW, bool ONCE>
 __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
                                             const KernelArgs& a, uint4* work) {
@@ -549,15 +550,12 @@ __global__ void __launch_bounds__(NW * 64, (enc_wgs_per_cu<WC, NTW, NW>())) kvtc
     extern __shared__ uint4 smem[];
     uint32_t* tile_start = reinterpret_cast<uint32_t*>(smem);
     uint4* work = smem + kJobTableBytes / 16 + 1;
-    const uint32_t total = build_tile_table<true, NW * 64>(a, NW * 10000 + WC * 100 + NTW, tile_start, reinterpret_cast<uint32_t*>(work));
-    const TileRange mine = my_tiles(total);
+    const TileTable table = build_tile_table<true, NW * 64>(a, NW * 10000 + WC * 100 + NTW, tile_start, reinterpret_cast<uint32_t*>(work));
+    const TileRange mine = my_tiles(table.total);
+    const bool once = table.pass;
     for (uint32_t tile = mine.first; tile < mine.end; tile += mine.step) {
         const TileRef tr = find_tile(a, tile_start, tile);
         const PlanEnc P = load_plan_enc<false>(a.plans + tr.plan);
-        const uint64_t launch_bytes = (uint64_t)total * (uint64_t)(uint32_t)(32 * enc_tt(NTW * WC, NW, WC) * (NW / WC)) * (uint64_t)((uint32_t)P.p * (uint32_t)sizeof(XT));
-        // (the caches keep some of an fp32 input of a little more than their size from one call to the next: two tensors of 35000 tokens at 40x, 287 MB, 63 us
-        // and 81 without keeping it, of 41000, 336 MB, 84.4 and 83.7; bf16: of 67000, 274 MB, 53.9 and 55.5, of 75000, 307 MB, 71 and 64)
-        const bool once = a.x_lines != 0 && launch_bytes >= ((sizeof(XT) == 2 ? 256ull : 320ull) << 20);
         if constexpr (WC == 8)
             encode_register_tile<NTW, XT, enc_tt(NTW * WC, NW, WC), 32 * enc_tt(NTW * WC, NW, WC), 4, true>(P, tr, a, work, once);
         else if (enc_once<XT, NTW * WC>() && once) encode_tile<NTW, WC, XT, NW, enc_once<XT, NTW * WC>()>(P, tr, a, work);
@@ -931,6 +929,14 @@ int encode_short_lds_bytes(int ntp, int n_groups, int rec_dwords, kvtc_dtype dty
     const int main_b = 2 * kEncShortTile * (dtype == KVTC_BF16 ? short_feat<uint16_t>() * 2 : short_feat<float>() * 4);
     const int epi_b = kEncShortTile * (2 * ntp * 8 + n_groups * 8 + (rec_dwords + 1) * 4);
     return enc_aux_bytes(ntp) + (main_b > epi_b ? main_b : epi_b);
+}
+
+// Bytes of a call's features from which on the variant reads them without keeping them.  (The caches keep some of an fp32 input of a little more than
+// their size from one call to the next: two tensors of 35000 tokens at 40x, 287 MB, 63 us and 81 without keeping it, of 41000, 336 MB, 84.4 and
+// 83.7; bf16: of 67000, 274 MB, 53.9 and 55.5, of 75000, 307 MB, 71 and 64.)
+uint64_t encode_pass_bytes(int ntp, kvtc_dtype dtype) {
+    const int eb = dtype == KVTC_BF16 ? 2 : 4;
+    return ntp > 20 || enc_can_pass(ntp, eb) ? (eb == 2 ? 256ull : 320ull) << 20 : ~0ull;
 }
 
 int encode_tok_wg(int ntw, int wc, int nw) { return 32 * enc_tt(ntw * wc, nw, wc) * (nw / wc); }

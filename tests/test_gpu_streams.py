@@ -54,3 +54,20 @@ def test_large_inputs_are_coded_as_small_ones(r, dtype):
         n = min(20001, T - t0)
         kv.kvtc_encode(plan.handle, x[t0:], dtype, n, p, part, part.numel())
         assert torch.equal(got[t0:t0 + n], part[:n]), (r, t0)
+
+
+def test_a_batch_counts_its_jobs_tokens():
+    """Not whole tiles, not one launch's jobs alone, and no job that is not valid: plans of two variants and of two numbers of features, jobs of a
+    token more than a tile."""
+    plans = [_gpu_plan(_variant_plan(64)), _gpu_plan(_variant_plan(272)), kv.Plan(128, 16, np.zeros(128, np.float32), np.zeros((128, 16), np.uint16), [(16, 4)])]
+    p = [1024, 1024, 128]
+    batch = kv.Batch(plans)
+    which = [j % 3 for j in range(300)] + [7, -1, 0, 1]
+    lens = [129 + 64 * (j % 5) for j in range(300)] + [500, 500, -1, 1 << 30]                   # unknown plans, negative, beyond the stream buffer
+    jobs = torch.from_numpy(kv.make_jobs(which, lens, [0] * len(lens)).view(np.uint8)).to(DEV)
+    elements = sum(n * p[w] for n, w in zip(lens[:300], which))
+    offs = torch.zeros(len(lens) + 1, dtype=torch.int64, device=DEV)
+    out = torch.full((1,), 9, dtype=torch.int32, device=DEV)
+    for at, passes in ((elements, 1), (elements // 2, 1), (elements * 101 // 100, 0), (1 << 60, 0)):
+        st = kv.lib().kvtc_test_batch_passes(batch.handle, jobs.data_ptr(), len(lens), offs.data_ptr(), 1 << 22, at, out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        assert st == 0 and int(out.item()) == passes, at
