@@ -25,7 +25,7 @@ int encode_short_waves(int ntp);
 int encode_short_lds_bytes(int ntp, int n_groups, int rec_dwords, kvtc_dtype dtype);
 int encode_tok_wg(int ntw, int wc, int nw);
 uint64_t encode_pass_bytes(int ntp, kvtc_dtype dtype);
-uint64_t decode_pass_bytes();
+uint64_t decode_pass_bytes(int cls, int least_tiles, kvtc_dtype dtype, uint64_t bases);
 hipError_t launch_fp8_pack(const void* x, kvtc_dtype dtype, int64_t n_tokens, int p, int64_t ld_x, void* out, hipStream_t stream);
 hipError_t launch_fp8_unpack(const void* in, int64_t n_tokens, int p, void* x, kvtc_dtype dtype, int64_t ld_x, hipStream_t stream);
 hipError_t launch_offsets_append(const uint32_t* rec_dwords, int n_plans, const kvtc_job* jobs, int n_jobs, const uint64_t* region,
@@ -63,7 +63,8 @@ struct kvtc_batch {
     int n_plans;
     // the kernel variants the plans use (a launch per variant), with the LDS maxima over each one's plans
     struct EncVariant { int key, wgs, lds[2]; };        // workgroups per compute unit; lds per element dtype
-    struct DecVariant { int key, wgs, rec, ring, rec_dwords; };     // workgroups per compute unit; record image, basis ring, record (the widest among the class's plans)
+    // workgroups per compute unit; record image, basis ring, record (the widest among the class's plans); the narrowest's coordinate tiles, all their bases' bytes
+    struct DecVariant { int key, wgs, rec, ring, rec_dwords, least_tiles; uint64_t bases; };
     std::vector<EncVariant> enc;
     struct ShortVariant { int waves, lds[2]; } enc_short[3];     // short-job kernels by coordinate tiles per wave; waves = 0: no plan uses it
     std::vector<DecVariant> dec;
@@ -506,6 +507,8 @@ static float pass_from(bool lines, uint64_t from, kvtc_dtype dtype, uint64_t ele
     const bool may = lines && from / elem_size(dtype) <= elements;
     return !may ? HUGE_VALF : batch ? (float)(from / elem_size(dtype)) : 0.0f;
 }
+// Bytes of the basis that a decode with this plan reads.
+static uint64_t basis_bytes(const PlanDev& h) { return (uint64_t)h.p * (uint64_t)h.dec_nct * 64u; }
 // Tokens of a batch at most, by the size of its stream buffer (jobs do not overlap there), times features.
 static uint64_t most_elements(size_t stream_bytes, int min_rec_dwords, int max_p) {
     return (uint64_t)(stream_bytes / ((size_t)min_rec_dwords * 4)) * (uint64_t)max_p;
@@ -549,6 +552,9 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
                                  void* x_out_dev, kvtc_dtype dtype, const kvtc_layout* layout, kvtc_stream stream, int accumulate = 0,
                                  const float* sum_dev = nullptr, int64_t sum_ld = 0);
 
+uint64_t kvtc_host_decode_pass_bytes(int tiles, kvtc_dtype dtype, uint64_t bases) {
+    return decode_pass_bytes(tiles <= 4 ? 4 : tiles <= 10 ? 10 : 18, tiles, dtype, bases);
+}
 int kvtc_host_whole_lines(uint64_t x_address, kvtc_dtype dtype, int p, const kvtc_layout* layout) {
     XLayout xl;
     const void* x = reinterpret_cast<const void*>(static_cast<uintptr_t>(x_address));
@@ -668,7 +674,8 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
     } else {
         const int64_t tiles = (n_tokens + plan->h.dec_tok_wg - 1) / plan->h.dec_tok_wg;
         a.single_tiles = (uint32_t)tiles;
-        a.x_pass_from = pass_from(whole_lines(x_out_dev, dtype, xl), decode_pass_bytes(), dtype, (uint64_t)n_tokens * (uint64_t)plan->h.p, false);
+        a.x_pass_from = pass_from(whole_lines(x_out_dev, dtype, xl), decode_pass_bytes(plan->h.dec_cls, plan->h.dec_nct, dtype, basis_bytes(plan->h)), dtype,
+                                  (uint64_t)n_tokens * (uint64_t)plan->h.p, false);
         const int64_t shares = wide ? (spans < 4 ? 1 : spans / 4) : spans;       // workgroups a tile may be shared among
         const int grid = (int)(tiles * shares < slots ? tiles * shares : slots);
         const DecLayout lay = decode_layout(plan->h.dec_rec_lds, plan->h.dec_ring_lds, plan->h.dec_wgs);
@@ -727,12 +734,14 @@ kvtc_status kvtc_batch_create(kvtc_batch** out, const kvtc_plan* const* plans, i
             for (auto& e : b->dec)
                 if (e.key == key) v = &e;
             if (!v) {
-                b->dec.push_back({key, ph.dec_wgs, 0, 0, 0});
+                b->dec.push_back({key, ph.dec_wgs, 0, 0, 0, ph.dec_nct, 0});
                 v = &b->dec.back();
             }
             if (ph.dec_rec_lds > v->rec) v->rec = ph.dec_rec_lds;
             if (ph.rec_dwords > v->rec_dwords) v->rec_dwords = ph.rec_dwords;
             if (ph.dec_ring_lds > v->ring) v->ring = ph.dec_ring_lds;
+            v->least_tiles = std::min(v->least_tiles, ph.dec_nct);
+            v->bases += basis_bytes(ph);
         }
         if (ph.p > b->max_p) b->max_p = ph.p;
         {
@@ -1081,7 +1090,8 @@ kvtc_status kvtc_decode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.cap = in_bytes;
     a.status = status_dev;
     for (const auto& v : batch->dec) {
-        a.x_pass_from = pass_from(whole_lines(x_out_base_dev, dtype, xl), decode_pass_bytes(), dtype, most_elements(in_bytes, batch->min_rec_dwords, batch->max_p), true);
+        a.x_pass_from = pass_from(whole_lines(x_out_base_dev, dtype, xl), decode_pass_bytes(v.key % 100, v.least_tiles, dtype, v.bases), dtype,
+                                  most_elements(in_bytes, batch->min_rec_dwords, batch->max_p), true);
         // Jobs whose 128-token tiles can be shown to run all at once (the stream buffer's size bounds their tokens, and each may end in a
         // part of a tile) take the variant with one token tile per wave, as a single tensor does, where the mean job is no more than one such tile
         // or the tiles, twice as many with twice the basis traffic, are few: one per compute unit; of more plans than there are XCDs fewer, and

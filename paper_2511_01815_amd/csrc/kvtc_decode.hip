@@ -156,12 +156,27 @@ __device__ __forceinline__ float2 load_part(const char* sb, uint32_t lrow, int t
     return *reinterpret_cast<const float2*>(sb + ((size_t)row * sld + 2u * lane_col));
 }
 
-// Bytes of a call's output from which on it passes the caches by (non-temporal stores; whole tiles only): a little more than half of the 256 MB last-level cache.
-// What is decoded next to it -- the bases, in an L2 of 4 MB -- is then not pushed out by output that nobody finds there again: 32-layer cache at
-// 16x 1265 -> 1131 us, 64 tensors of 8000 tokens at 20x 323 -> 228, four layers under one basis, both ways, 1364 -> 1261.  Below, what reads the output next
-// does find it (the keys of 32768 tokens, 64 MB, decoded and rotated: 122 us, 131 with such stores; of 60000, 123 MB: 259 and 256).
+// Bytes of a call's output from which on it passes the caches by (non-temporal stores; whole tiles only; ~0: never).  cls: the kernel class; least_tiles:
+// the narrowest of the launch's plans, as it runs; bases: bytes of all their bases.  Output that nobody finds in a cache again pushes the bases out of
+// the L2s, 4 MB each, that every workgroup reads them from; but stores that pass the last-level cache, 256 MB, by go no faster than HBM, and what is left
+// of the output there is found by who reads or writes it next.  So it pays where matrix work or many bases are in the way, and not where the
+// stores are all there is.  us, kept and past the caches, one buffer again and again / buffers in turn:
+//   wide plans, both types: 400 coordinates, one tensor of 70000 tokens (137 MB) 92 88 / 94 89; never slower
+//   bf16, 7 to 10 tiles: 240 coordinates, 137 MB 63 56 / 64 56, 312 MB 114 89 / 112 91; 64 tensors and plans of 4000 190 121
+//   bf16, 5 and 6 tiles: 160, 234 MB 59.5 65.4 / 64 63, 253 MB 61 65 / 66 66, 390 MB 115 111 / 114 110; 64 plans, 150 MB 60 61 / 61 58, 500 MB 179 111
+//   bf16, up to 4 tiles: 64, 234 MB 41 57 / 53 58, 600 MB 129 134 / 128 135, 1.2 GB 254 248 / 254 252 (16: 283 298 / 281 288 at 1.4), 2 GB 424 413 / 422 417; 16 plans (2 MB of
+//     bases) 300 MB 73 70 / 72 70, 64 plans 500 MB 150 107
+//   fp32, 5 to 10 tiles: 160 to 240, 312 MB 95 116 / 94 111, 976 MB 258 298 / 248 278, 2 GB 450 456 / 447 450; 8 plans of 240 (4 MB) 300 MB 98 101 /
+//     102 102; 16 (8 MB) 109 99 / 109 102
+//   fp32, up to 4 tiles: 64, 470 MB 117 132 / 123 136, 1.6 GB 333 342 / 326 338, 4 GB 828 830 / 837 859; 64 plans (8 MB) 300 MB 97 98 / 93 92, 500 MB 158 135
 #if KVTC_DECODE_PART == 0
-uint64_t decode_pass_bytes() { return 129ull << 20; }
+uint64_t decode_pass_bytes(int cls, int least_tiles, kvtc_dtype dtype, uint64_t bases) {
+    const bool bf16 = dtype == KVTC_BF16, many = bf16 ? bases >= (2u << 20) : bases > (4u << 20);
+    uint64_t mib = 129;
+    if (cls <= 4) mib = bf16 ? (many ? 256 : 1536) : (many ? 384 : 0);
+    else if (cls <= 10) mib = bf16 ? (many || least_tiles > 6 ? 129 : 256) : (many ? 256 : 1536);
+    return mib ? mib << 20 : ~0ull;
+}
 #endif
 
 // The results of a pair of feature tiles (acc0: the even, acc1: the odd features of 64-feature span `span`) to the output.  `fast`: every row of

@@ -85,6 +85,24 @@ def test_only_arrays_on_whole_cache_lines_pass_the_caches(dtype):
     assert whole(base + 2, kv.layout(1024)) == -1 and whole(base, kv.layout(1000)) == -1
 
 
+def test_output_passes_the_caches_where_that_was_measured_faster():
+    """Light kernels -- few coordinates, or fp32 -- with the bases of a few plans store a few times the last-level cache's 256 MB through it; with many
+    bases, or more matrix work than stores, they pass it by from about half of it."""
+    MB, never = 1 << 20, (1 << 64) - 1
+
+    def at(tiles, dtype, plans):
+        return kv.lib().kvtc_host_decode_pass_bytes(tiles, dtype, plans * tiles * 32 * 1024 * 2)
+
+    for tiles in (2, 4):
+        assert at(tiles, kv.KVTC_BF16, 1) > 900 * MB and at(tiles, kv.KVTC_BF16, 64) <= 256 * MB
+        assert at(tiles, kv.KVTC_F32, 1) == never and 300 * MB < at(tiles, kv.KVTC_F32, 64) <= 500 * MB
+    assert at(6, kv.KVTC_BF16, 1) == 256 * MB and at(6, kv.KVTC_BF16, 64) <= 150 * MB
+    for tiles in (6, 8, 10):
+        assert at(tiles, kv.KVTC_F32, 1) > 1000 * MB and at(tiles, kv.KVTC_F32, 4) > 1000 * MB and at(tiles, kv.KVTC_F32, 64) <= 300 * MB
+    for tiles, dtype in ((7, kv.KVTC_BF16), (10, kv.KVTC_BF16), (12, kv.KVTC_BF16), (12, kv.KVTC_F32), (32, kv.KVTC_F32)):
+        assert 128 * MB < at(tiles, dtype, 1) <= 137 * MB
+
+
 def test_argument_errors_need_no_gpu():
     L = kv.lib()
     p, r = 64, 16
