@@ -24,6 +24,10 @@ uint32_t kvtc_host_code(float d, uint16_t shift16, uint16_t scale16, int bits);
  * caches; 0: it does not, so none is; -1: the library refuses the array. */
 int kvtc_host_whole_lines(uint64_t x_address, kvtc_dtype dtype, int p, const kvtc_layout* layout);
 
+/* Bytes of a call's features from which on its encode reads them past the caches, for a plan that runs as this many tiles of
+ * 32 coordinates (2, 4, 6, 8, 10, 12, 16, 20, 24 or 32); UINT64_MAX: never. */
+uint64_t kvtc_host_encode_pass_bytes(int tiles, kvtc_dtype dtype);
+
 /* Bytes of a call's output from which on its decode stores past the caches, for plans of this many tiles of 32 coordinates whose
  * bases have this many bytes together; UINT64_MAX: never. */
 uint64_t kvtc_host_decode_pass_bytes(int tiles, kvtc_dtype dtype, uint64_t bases);

@@ -129,6 +129,8 @@ def lib() -> C.CDLL:
         L.kvtc_host_code.restype = C.c_uint32
         L.kvtc_host_whole_lines.argtypes = [C.c_uint64, C.c_int, C.c_int, lp]
         L.kvtc_host_whole_lines.restype = C.c_int
+        L.kvtc_host_encode_pass_bytes.argtypes = [C.c_int, C.c_int]
+        L.kvtc_host_encode_pass_bytes.restype = C.c_uint64
         L.kvtc_host_decode_pass_bytes.argtypes = [C.c_int, C.c_int, C.c_uint64]
         L.kvtc_host_decode_pass_bytes.restype = C.c_uint64
         L.kvtc_test_batch_passes.argtypes = [vp, vp, C.c_int, vp, sz, C.c_uint64, vp, vp]

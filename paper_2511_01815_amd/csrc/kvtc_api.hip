@@ -552,6 +552,7 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
                                  void* x_out_dev, kvtc_dtype dtype, const kvtc_layout* layout, kvtc_stream stream, int accumulate = 0,
                                  const float* sum_dev = nullptr, int64_t sum_ld = 0);
 
+uint64_t kvtc_host_encode_pass_bytes(int tiles, kvtc_dtype dtype) { return encode_pass_bytes(tiles, dtype); }
 uint64_t kvtc_host_decode_pass_bytes(int tiles, kvtc_dtype dtype, uint64_t bases) {
     return decode_pass_bytes(tiles <= 4 ? 4 : tiles <= 10 ? 10 : 18, tiles, dtype, bases);
 }

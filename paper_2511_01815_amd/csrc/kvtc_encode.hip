@@ -933,10 +933,12 @@ int encode_short_lds_bytes(int ntp, int n_groups, int rec_dwords, kvtc_dtype dty
 
 // Bytes of a call's features from which on the variant reads them without keeping them.  (The caches keep some of an fp32 input of a little more than
 // their size from one call to the next: two tensors of 35000 tokens at 40x, 287 MB, 63 us and 81 without keeping it, of 41000, 336 MB, 84.4 and
-// 83.7; bf16: of 67000, 274 MB, 53.9 and 55.5, of 75000, 307 MB, 71 and 64.)
+// 83.7; bf16: of 67000, 274 MB, 53.9 and 55.5, of 75000, 307 MB, 71 and 64.  bf16 of 4 tiles: its ring by lines has the basis one k-step ahead, which
+// shows in launches of one round of tiles or two.  64 tensors of 128 coordinates, one plan and 64, kept and not: of 2100 tokens, 275 MB, 78 88 and 89 102, of 3000 97 97
+// and 102.5 106 (375 MB; in another run 100 99 and 111 107), of 5000 171.6 163 and 174 167; one tensor of 140000 82 87, of 180000, 351 MB, 96 92, of 200000 113 107.)
 uint64_t encode_pass_bytes(int ntp, kvtc_dtype dtype) {
     const int eb = dtype == KVTC_BF16 ? 2 : 4;
-    return ntp > 20 || enc_can_pass(ntp, eb) ? (eb == 2 ? 256ull : 320ull) << 20 : ~0ull;
+    return ntp > 20 || enc_can_pass(ntp, eb) ? (eb == 4 ? 320ull : ntp == 4 ? 340ull : 256ull) << 20 : ~0ull;
 }
 
 int encode_tok_wg(int ntw, int wc, int nw) { return 32 * enc_tt(ntw * wc, nw, wc) * (nw / wc); }

@@ -103,6 +103,20 @@ def test_output_passes_the_caches_where_that_was_measured_faster():
         assert 128 * MB < at(tiles, dtype, 1) <= 137 * MB
 
 
+def test_input_passes_the_caches_where_that_was_measured_faster():
+    """No sooner than the last-level cache's 256 MB; later where a variant's ring for whole lines is short, or the caches keep some of an input of a
+    little more; never where a line is asked for at two times."""
+    MB, never = 1 << 20, (1 << 64) - 1
+    at = kv.lib().kvtc_host_encode_pass_bytes
+    for tiles in (2, 8, 10, 12, 16, 20, 24, 32):
+        assert at(tiles, kv.KVTC_BF16) == 256 * MB
+    assert 325 * MB < at(4, kv.KVTC_BF16) <= 351 * MB and at(6, kv.KVTC_BF16) == never
+    for tiles in (2, 4, 24, 32):
+        assert at(tiles, kv.KVTC_F32) == 320 * MB
+    for tiles in (6, 8, 10, 12, 16, 20):
+        assert at(tiles, kv.KVTC_F32) == never
+
+
 def test_argument_errors_need_no_gpu():
     L = kv.lib()
     p, r = 64, 16
