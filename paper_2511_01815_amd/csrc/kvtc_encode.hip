@@ -395,7 +395,14 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     constexpr int NXD = (NX_TOTAL + NW - 1) / NW;
     constexpr int NV_TOTAL = SLAB_U4 / 64;                      // basis transfers per stage (1 KB each), dealt the same way
     constexpr int NV = (NV_TOTAL + NW - 1) / NW;
-    constexpr int NV_MIN = enc_least_pieces<NTP, NW, NV_TOTAL>(), NX_MIN = NX_TOTAL / NW;       // transfers per wave, lower bound over waves and plans
+    // transfers per wave, lower bounds over waves: of the basis for any plan, and for a wave none of whose pieces is padding.  (With the first alone a wave that
+    // had all its pieces waited, every step, for one that it had only just asked for: fp32 of 8 tiles, 64 tensors of 2100 tokens of 240 coordinates 179 us, so 161.)
+    constexpr int NV_MIN = enc_least_pieces<NTP, NW, NV_TOTAL>(), NV_ALL = NV_TOTAL / NW, NX_MIN = NX_TOTAL / NW;
+    bool pads = false;                                          // some of the wave's pieces are
+    if constexpr (NV_MIN < NV_ALL) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) pads = pads || (i * NW + wave < NV_TOTAL && (i * NW + wave) % NTP >= nt);
+    }
     static_assert(TOK_WG % XS::ROWS_PER_DMA == 0 && KX % KS == 0, "whole transfers, whole steps");
     static_assert(3 * (NV + NXD) < 64, "vmcnt range");
     static_assert(NW >= 2, "waves 0 and 1 fetch the plan's tables");
@@ -477,7 +484,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
 #pragma unroll
         for (int u = 0; u < D; ++u)
             if (u < n_slabs) { issue_basis(u, u); issue_x(u, u); }
-        wait_vmem_times<NV_MIN + NX_MIN>(min(D - 1, n_slabs - 1));       // stage 0 has landed, and the tables before it
+        if (pads) wait_vmem_times<NV_MIN + NX_MIN>(min(D - 1, n_slabs - 1)); else wait_vmem_times<NV_ALL + NX_MIN>(min(D - 1, n_slabs - 1));       // stage 0 has landed, and the tables before it
     } else {
         // in the order of the loop's steps, which D of them would have been in front of it: a slab of X goes out behind the basis of step SPC * c - SPC + D
         if (SPC > D) issue_x(0, 0);
@@ -516,13 +523,16 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
                 if constexpr (SPC == 1) {
                     if (s + D < n_slabs) issue_x(s + D, (u + D) % NSTAGE);
                     compute(u, u, 0);
-                    wait_vmem_times<NV_MIN + NX_MIN>(min(D - 1, n_slabs - 2 - s));   // stage of step s + 1 has landed
+                    const int later = min(D - 1, n_slabs - 2 - s);
+                    if (pads) wait_vmem_times<NV_MIN + NX_MIN>(later); else wait_vmem_times<NV_ALL + NX_MIN>(later);   // stage of step s + 1 has landed
                 } else {
                     const bool more = s / SPC + 1 < n_chunks;
                     if (u % SPC == 0 && more) issue_x(s / SPC + 1, (u / SPC + 1) & 1);
                     compute(u % NSTAGE, (u / SPC) & 1, (u % SPC) * KS);
                     // the basis of step s + 1 has landed and, in front of a new slab of X, that: what is younger may be in flight
-                    if (more && s + D < n_slabs) wait_vmem_dyn(enc_in_flight(u, D, SPC, NV_MIN, NX_MIN)); else wait_vmem<0>();      // (a constant: the loop is unrolled)
+                    if (!(more && s + D < n_slabs)) wait_vmem<0>();
+                    else if (pads) wait_vmem_dyn(enc_in_flight(u, D, SPC, NV_MIN, NX_MIN));      // (constants: the loop is unrolled)
+                    else wait_vmem_dyn(enc_in_flight(u, D, SPC, NV_ALL, NX_MIN));
                 }
                 __syncthreads();
             }
