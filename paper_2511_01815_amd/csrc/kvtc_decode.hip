@@ -517,7 +517,8 @@ __device__ __forceinline__ void decode_wide_tile(const PlanDec& P, const TileRef
         const RecImage im = rec_image(P.rec_dwords, tr.offset + (uint64_t)tok_tile0 * (uint64_t)P.rec_dwords * 4ull);
         const uint32_t* blk = reinterpret_cast<const uint32_t*>(work);
         const uint32_t* rec = blk + kAuxBytes / 4 + im.skew_dw;
-        uint32_t q[ITEMS][8], info[ITEMS];                       // (an item beyond the plan's tiles reads the last tile's blocks for nothing)
+        const int n_items = (nct * TT - wave + 7) / 8;           // (unpacking the class's most items instead cost plans of 19 to 24 tiles, which have 5 or 6 of the 8, 1 to 2 % of a small call)
+        uint32_t q[ITEMS][8], info[ITEMS];
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) info[k] = blk[2 * min((wave + 8 * k) / TT, nct - 1) + h];
         auto unpack = [&](auto narrow_tag) {
@@ -529,7 +530,8 @@ __device__ __forceinline__ void decode_wide_tile(const PlanDec& P, const TileRef
             read(0);
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
-                if (k + 1 < ITEMS) read(k + 1);
+                if (k >= n_items) break;
+                if (k + 1 < ITEMS && k + 1 < n_items) read(k + 1);
                 __builtin_amdgcn_sched_barrier(0);
                 b[k & 1].values(q[k]);
                 asm volatile("" : "+v"(q[k][0]), "+v"(q[k][1]), "+v"(q[k][2]), "+v"(q[k][3]), "+v"(q[k][4]), "+v"(q[k][5]), "+v"(q[k][6]), "+v"(q[k][7]));
