@@ -29,8 +29,8 @@ int kvtc_host_whole_lines(uint64_t x_address, kvtc_dtype dtype, int p, const kvt
 uint64_t kvtc_host_encode_pass_bytes(int tiles, kvtc_dtype dtype);
 
 /* Bytes of a call's output from which on its decode stores past the caches, for plans of this many tiles of 32 coordinates whose
- * bases have this many bytes together; UINT64_MAX: never. */
-uint64_t kvtc_host_decode_pass_bytes(int tiles, kvtc_dtype dtype, uint64_t bases);
+ * bases have this many bytes together, in one tensor's call (single) or a batch; UINT64_MAX: never. */
+uint64_t kvtc_host_decode_pass_bytes(int tiles, kvtc_dtype dtype, uint64_t bases, int single);
 
 /* On the GPU: *passes_dev = 1 if a launch over these jobs takes a call's features, tokens times features over all jobs that
  * are valid, for `elements` or more, else 0. */

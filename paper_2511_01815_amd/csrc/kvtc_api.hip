@@ -25,7 +25,7 @@ int encode_short_waves(int ntp);
 int encode_short_lds_bytes(int ntp, int n_groups, int rec_dwords, kvtc_dtype dtype);
 int encode_tok_wg(int ntw, int wc, int nw);
 uint64_t encode_pass_bytes(int ntp, kvtc_dtype dtype);
-uint64_t decode_pass_bytes(int cls, int least_tiles, kvtc_dtype dtype, uint64_t bases);
+uint64_t decode_pass_bytes(int cls, int least_tiles, kvtc_dtype dtype, uint64_t bases, bool single);
 hipError_t launch_fp8_pack(const void* x, kvtc_dtype dtype, int64_t n_tokens, int p, int64_t ld_x, void* out, hipStream_t stream);
 hipError_t launch_fp8_unpack(const void* in, int64_t n_tokens, int p, void* x, kvtc_dtype dtype, int64_t ld_x, hipStream_t stream);
 hipError_t launch_offsets_append(const uint32_t* rec_dwords, int n_plans, const kvtc_job* jobs, int n_jobs, const uint64_t* region,
@@ -553,8 +553,8 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
                                  const float* sum_dev = nullptr, int64_t sum_ld = 0);
 
 uint64_t kvtc_host_encode_pass_bytes(int tiles, kvtc_dtype dtype) { return encode_pass_bytes(tiles, dtype); }
-uint64_t kvtc_host_decode_pass_bytes(int tiles, kvtc_dtype dtype, uint64_t bases) {
-    return decode_pass_bytes(tiles <= 4 ? 4 : tiles <= 10 ? 10 : 18, tiles, dtype, bases);
+uint64_t kvtc_host_decode_pass_bytes(int tiles, kvtc_dtype dtype, uint64_t bases, int single) {
+    return decode_pass_bytes(tiles <= 4 ? 4 : tiles <= 10 ? 10 : 18, tiles, dtype, bases, single != 0);
 }
 int kvtc_host_whole_lines(uint64_t x_address, kvtc_dtype dtype, int p, const kvtc_layout* layout) {
     XLayout xl;
@@ -675,7 +675,7 @@ static kvtc_status decode_single(const char* who, const kvtc_plan* plan, const v
     } else {
         const int64_t tiles = (n_tokens + plan->h.dec_tok_wg - 1) / plan->h.dec_tok_wg;
         a.single_tiles = (uint32_t)tiles;
-        a.x_pass_from = pass_from(whole_lines(x_out_dev, dtype, xl), decode_pass_bytes(plan->h.dec_cls, plan->h.dec_nct, dtype, basis_bytes(plan->h)), dtype,
+        a.x_pass_from = pass_from(whole_lines(x_out_dev, dtype, xl), decode_pass_bytes(plan->h.dec_cls, plan->h.dec_nct, dtype, basis_bytes(plan->h), true), dtype,
                                   (uint64_t)n_tokens * (uint64_t)plan->h.p, false);
         const int64_t shares = wide ? (spans < 4 ? 1 : spans / 4) : spans;       // workgroups a tile may be shared among
         const int grid = (int)(tiles * shares < slots ? tiles * shares : slots);
@@ -1091,7 +1091,7 @@ kvtc_status kvtc_decode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     a.cap = in_bytes;
     a.status = status_dev;
     for (const auto& v : batch->dec) {
-        a.x_pass_from = pass_from(whole_lines(x_out_base_dev, dtype, xl), decode_pass_bytes(v.key % 100, v.least_tiles, dtype, v.bases), dtype,
+        a.x_pass_from = pass_from(whole_lines(x_out_base_dev, dtype, xl), decode_pass_bytes(v.key % 100, v.least_tiles, dtype, v.bases, false), dtype,
                                   most_elements(in_bytes, batch->min_rec_dwords, batch->max_p), true);
         // Jobs whose 128-token tiles can be shown to run all at once (the stream buffer's size bounds their tokens, and each may end in a
         // part of a tile) take the variant with one token tile per wave, as a single tensor does, where the mean job is no more than one such tile

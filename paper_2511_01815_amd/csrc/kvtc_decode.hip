@@ -157,24 +157,27 @@ __device__ __forceinline__ float2 load_part(const char* sb, uint32_t lrow, int t
 }
 
 // Bytes of a call's output from which on it passes the caches by (non-temporal stores; whole tiles only; ~0: never).  cls: the kernel class; least_tiles:
-// the narrowest of the launch's plans, as it runs; bases: bytes of all their bases.  Output that nobody finds in a cache again pushes the bases out of
-// the L2s, 4 MB each, that every workgroup reads them from; but stores that pass the last-level cache, 256 MB, by go no faster than HBM, and what is left
-// of the output there is found by who reads or writes it next.  So it pays where matrix work or many bases are in the way, and not where the
-// stores are all there is.  us, kept and past the caches, one buffer again and again / buffers in turn:
+// the narrowest of the launch's plans, as it runs; bases: bytes of all their bases; single: one tensor's call.  Output that nobody finds in a cache again
+// pushes the bases out of the L2s, 4 MB each, that every workgroup reads them from; but stores that pass the last-level cache, 256 MB, by go no faster
+// than HBM, and what is left of the output there is found by who reads or writes it next.  So it pays where matrix work or many bases are in the way,
+// and not where the stores are all there is.  us, kept and past the caches, one buffer again and again / buffers in turn:
 //   wide plans, both types: 400 coordinates, one tensor of 70000 tokens (137 MB) 92 88 / 94 89; never slower
 //   bf16, 7 to 10 tiles: 240 coordinates, 137 MB 63 56 / 64 56, 312 MB 114 89 / 112 91; 64 tensors and plans of 4000 190 121
-//   bf16, 5 and 6 tiles: 160, 234 MB 59.5 65.4 / 64 63, 253 MB 61 65 / 66 66, 390 MB 115 111 / 114 110; 64 plans, 150 MB 60 61 / 61 58, 500 MB 179 111
-//   bf16, up to 4 tiles: 64, 234 MB 41 57 / 53 58, 600 MB 129 134 / 128 135, 1.2 GB 254 248 / 254 252 (16: 283 298 / 281 288 at 1.4), 2 GB 424 413 / 422 417; 16 plans (2 MB of
-//     bases) 300 MB 73 70 / 72 70, 64 plans 500 MB 150 107
-//   fp32, 5 to 10 tiles: 160 to 240, 312 MB 95 116 / 94 111, 976 MB 258 298 / 248 278, 2 GB 450 456 / 447 450; 8 plans of 240 (4 MB) 300 MB 98 101 /
-//     102 102; 16 (8 MB) 109 99 / 109 102
+//   bf16, 5 and 6 tiles: 160, one tensor, 195 MB 51 57 / 54.5 56, 253 MB 61 65 / 66 66, 390 MB 115 111 / 114 110; batches, 4 of 18000 54 53 / 52 48,
+//     31 of 4000 73 62 / 66 61; 64 plans, 150 MB 60 61 / 61 58, 500 MB 179 111
+//   bf16, 3 and 4 tiles: 80, one tensor, 585 MB 130 143 / 130 142, 781 MB 167 175 / 168 176, 878 MB 207 208 / 205 206; 2 of 100000 (390 MB) 118 102 / 114
+//     103, but 8 of 32000 (500 MB) 113 125 / 114 121, and before there were such stores 118 / 118; 2 of 140000 135 134 / 136 136; 31 of 12000 (726 MB) 162 170 / 165 171, 128 179 169 / 178 169
+//   bf16, up to 2 tiles: 64, 234 MB 41 57 / 53 58, 600 MB 129 134 / 128 135, 1.2 GB 254 248 / 254 252 (16: 283 298 / 281 288 at 1.4), 2 GB 424 413 / 422 417
+//   bf16, up to 4 tiles, many plans: 64, 16 plans (2 MB of bases) 300 MB 73 70 / 72 70, 64 plans 500 MB 150 107
+//   fp32, 5 to 10 tiles: 160 to 240, 312 MB 95 116 / 94 111, 898 MB 254 275 / 255 280, 1 GB 254 256 / 253 256 (240: 271 260 / 272 261), 1.1 GB 307 290 / 297 286;
+//     8 plans of 240 (4 MB) 300 MB 98 101 / 102 102; 16 (8 MB) 109 99 / 109 102
 //   fp32, up to 4 tiles: 64, 470 MB 117 132 / 123 136, 1.6 GB 333 342 / 326 338, 4 GB 828 830 / 837 859; 64 plans (8 MB) 300 MB 97 98 / 93 92, 500 MB 158 135
 #if KVTC_DECODE_PART == 0
-uint64_t decode_pass_bytes(int cls, int least_tiles, kvtc_dtype dtype, uint64_t bases) {
+uint64_t decode_pass_bytes(int cls, int least_tiles, kvtc_dtype dtype, uint64_t bases, bool single) {
     const bool bf16 = dtype == KVTC_BF16, many = bf16 ? bases >= (2u << 20) : bases > (4u << 20);
     uint64_t mib = 129;
-    if (cls <= 4) mib = bf16 ? (many ? 256 : 1536) : (many ? 384 : 0);
-    else if (cls <= 10) mib = bf16 ? (many || least_tiles > 6 ? 129 : 256) : (many ? 256 : 1536);
+    if (cls <= 4) mib = !bf16 ? (many ? 384 : 0) : many ? 256 : least_tiles <= 2 ? 1536 : 840;
+    else if (cls <= 10) mib = !bf16 ? (many ? 256 : 1024) : single && least_tiles <= 6 ? 256 : 129;
     return mib ? mib << 20 : ~0ull;
 }
 #endif

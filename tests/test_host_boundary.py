@@ -90,17 +90,18 @@ def test_output_passes_the_caches_where_that_was_measured_faster():
     bases, or more matrix work than stores, they pass it by from about half of it."""
     MB, never = 1 << 20, (1 << 64) - 1
 
-    def at(tiles, dtype, plans):
-        return kv.lib().kvtc_host_decode_pass_bytes(tiles, dtype, plans * tiles * 32 * 1024 * 2)
+    def at(tiles, dtype, plans, single=False):
+        return kv.lib().kvtc_host_decode_pass_bytes(tiles, dtype, plans * tiles * 32 * 1024 * 2, single)
 
     for tiles in (2, 4):
-        assert at(tiles, kv.KVTC_BF16, 1) > 900 * MB and at(tiles, kv.KVTC_BF16, 64) <= 256 * MB
-        assert at(tiles, kv.KVTC_F32, 1) == never and 300 * MB < at(tiles, kv.KVTC_F32, 64) <= 500 * MB
-    assert at(6, kv.KVTC_BF16, 1) == 256 * MB and at(6, kv.KVTC_BF16, 64) <= 150 * MB
+        assert at(tiles, kv.KVTC_BF16, 1, True) > 800 * MB and at(tiles, kv.KVTC_BF16, 2) > 800 * MB and at(tiles, kv.KVTC_BF16, 64) <= 256 * MB
+        assert at(tiles, kv.KVTC_F32, 1, True) == at(tiles, kv.KVTC_F32, 2) == never and 300 * MB < at(tiles, kv.KVTC_F32, 64) <= 500 * MB
+    assert at(6, kv.KVTC_BF16, 1, True) == 256 * MB and at(6, kv.KVTC_BF16, 2) <= 137 * MB
     for tiles in (6, 8, 10):
-        assert at(tiles, kv.KVTC_F32, 1) > 1000 * MB and at(tiles, kv.KVTC_F32, 4) > 1000 * MB and at(tiles, kv.KVTC_F32, 64) <= 300 * MB
+        assert at(tiles, kv.KVTC_F32, 1, True) > 1000 * MB and at(tiles, kv.KVTC_F32, 4) > 1000 * MB and at(tiles, kv.KVTC_F32, 64) <= 300 * MB
     for tiles, dtype in ((7, kv.KVTC_BF16), (10, kv.KVTC_BF16), (12, kv.KVTC_BF16), (12, kv.KVTC_F32), (32, kv.KVTC_F32)):
-        assert 128 * MB < at(tiles, dtype, 1) <= 137 * MB
+        for single in (False, True):
+            assert 128 * MB < at(tiles, dtype, 1, single) <= 137 * MB
 
 
 def test_input_passes_the_caches_where_that_was_measured_faster():
