@@ -32,6 +32,11 @@ uint64_t kvtc_host_encode_pass_bytes(int tiles, kvtc_dtype dtype);
  * bases have this many bytes together, in one tensor's call (single) or a batch; UINT64_MAX: never. */
 uint64_t kvtc_host_decode_pass_bytes(int tiles, kvtc_dtype dtype, uint64_t bases, int single);
 
+/* On the GPU, over all fp32 bit patterns: adds to counts_dev[0] how many of them are numbers, and to [1], [2] and [3] how many
+ * roundings to fp16, group headers and codes of this many bits come out differently as the kernels work them out and as the
+ * kvtc_host_* functions do. */
+kvtc_status kvtc_test_numeric(int bits, uint64_t* counts_dev, kvtc_stream stream);
+
 /* On the GPU: *passes_dev = 1 if a launch over these jobs takes a call's features, tokens times features over all jobs that
  * are valid, for `elements` or more, else 0. */
 kvtc_status kvtc_test_batch_passes(const kvtc_batch* batch, const kvtc_job* jobs_dev, int n_jobs, const uint64_t* offsets_dev, size_t stream_bytes,

@@ -133,6 +133,8 @@ def lib() -> C.CDLL:
         L.kvtc_host_encode_pass_bytes.restype = C.c_uint64
         L.kvtc_host_decode_pass_bytes.argtypes = [C.c_int, C.c_int, C.c_uint64, C.c_int]
         L.kvtc_host_decode_pass_bytes.restype = C.c_uint64
+        L.kvtc_test_numeric.argtypes = [C.c_int, vp, vp]
+        L.kvtc_test_numeric.restype = C.c_int
         L.kvtc_test_batch_passes.argtypes = [vp, vp, C.c_int, vp, sz, C.c_uint64, vp, vp]
         L.kvtc_test_batch_passes.restype = C.c_int
         L.kvtc_probe_stream.argtypes = [C.c_int, vp, vp, sz, vp]

@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvtc.so")
 # (source, object, macros): the decode kernels' many widths are compiled in parts, side by side
-SOURCES = [(f"{s}.hip", f"{s}.o", []) for s in ("kvtc_api", "kvtc_encode", "kvtc_fp8", "kvtc_rope", "kvtc_probe", "kvtc_entropy", "kvtc_calib")]
+SOURCES = [(f"{s}.hip", f"{s}.o", []) for s in ("kvtc_api", "kvtc_encode", "kvtc_fp8", "kvtc_rope", "kvtc_probe", "kvtc_entropy", "kvtc_calib", "kvtc_test")]
 SOURCES += [("kvtc_decode.hip", f"kvtc_decode_{k}.o", [f"-DKVTC_DECODE_PART={k}"]) for k in range(5)]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

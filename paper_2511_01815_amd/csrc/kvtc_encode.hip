@@ -67,17 +67,6 @@ __device__ __forceinline__ void put_bits(uint32_t* rec, uint32_t pos, uint32_t v
     if (s + len > 32u) atomicOr(rec + dw + 1, v >> (32u - s));
 }
 
-// The code of a coefficient as the low bits of a float: with the reciprocal scaled by 2^-bits, (d - shift) / scale lies in [0, 1), and adding
-// 2^(23 - bits), whose last place is 2^-bits, rounds it to nearest even exactly as code_of rounds (a power of two moves no rounding).  The clamp of
-// the multiplication does the rest of code_of: below zero and not a number give 0.  Above the largest code is nothing unless the scale is saturated (such tiles
-// take another way): a scale rounded up covers the group's range.  Four instructions with the one that packs it, where
-// round, clamp and convert to an integer made six.
-__device__ __forceinline__ uint32_t code_float(float d, float shift, float inv_b, float base) {
-    const float t = __builtin_amdgcn_fmed3f(__fmul_rn(__fsub_rn(d, shift), inv_b), 0.0f, 1.0f);
-    return __float_as_uint(__fadd_rn(t, base));
-}
-__host__ __device__ constexpr uint32_t code_base_bits(uint32_t bits) { return (150u - bits) << 23; }      // 2^(23 - bits)
-
 // The 16 codes of a block, BITS wide each and given as code_float makes them, as a bit string of BITS halfwords written to the record
 // image at a halfword address (blocks start and end on halfword boundaries: 16 codes x BITS bits).
 // Plain LDS stores: two blocks may share a dword but never a halfword, so nothing is OR-ed

@@ -1,5 +1,7 @@
-// Scalar numerics of the quantiser, shared by the gfx950 kernels and the host-side
-// test helpers of the library (one definition, compiled for both).
+// Scalar numerics of the quantiser.  Each step is defined once for host and device in plain terms (integer
+// arithmetic, correctly rounded division): the host-side test helpers run these.  The gfx950 kernels run forms of a
+// few instructions with the same results, in front of each of which stands what it leaves out; a test compares the two on the
+// GPU for every fp32 bit pattern and every width.
 //
 // The paper (Section "Quantization") fixes "16-bit shift and scaling factors" per
 // group and uniform min-max quantisation; the concrete choices are:
@@ -62,7 +64,7 @@ KVTC_HD float f16_bits_to_f32(uint16_t hbits) {
 }
 
 #if defined(__HIPCC__)
-// The device's forms of what follows: the same results, instruction for instruction what the hardware does in one.
+// The device's forms of what stands above and below.
 // fp32 -> fp16 with directed rounding: truncated towards zero, and one step away from it where that lost something on the side asked
 // for (the value clamped first, so there is no step beyond 65504).  Not for NaN.  5 instructions for 20 and three branches.
 __device__ __forceinline__ uint32_t f16_round_dir_dev(float x, bool up, float& back) {
@@ -74,7 +76,7 @@ __device__ __forceinline__ uint32_t f16_round_dir_dev(float x, bool up, float& b
     return h;
 }
 // 1 / v to nearest, for the values that occur here: 2^b - 1 (b <= 16) and the positive fp16 numbers (one step of Newton's method on the
-// hardware's estimate; checked for every one of them).
+// hardware's estimate).
 __device__ __forceinline__ float rcp_rn_dev(float v) {
     const float y = __builtin_amdgcn_rcpf(v);
     return __builtin_fmaf(__builtin_fmaf(-v, y, 1.0f), y, y);
@@ -95,9 +97,23 @@ KVTC_HD float div_rn(float a, float b) {
 }
 
 // Header of one (token, group) from the group's fp32 min and max.
-KVTC_HD GroupQ group_header(float lo, float hi, int bits) {
+KVTC_HD GroupQ group_header_plain(float lo, float hi, int bits) {
     GroupQ g;
+    g.shift16 = f16_round_dir(lo, false);
+    g.shift = f16_bits_to_f32(g.shift16);
+    const float qmax = (float)((1u << bits) - 1u);
+    const float range = hi - g.shift;                    // one fp32 subtraction
+    g.scale16 = f16_round_dir(div_rn(range, qmax), true);
+    const float sc = f16_bits_to_f32(g.scale16);
+    g.inv = sc > 0.0f ? div_rn(1.0f, sc) : 0.0f;
+    return g;
+}
+
+// The same as the kernels work it out, but for a range of -0, whose scale has no sign here; no group has one (its minimum would have to be +0 and its
+// maximum -0).
+KVTC_HD GroupQ group_header(float lo, float hi, int bits) {
 #if defined(__HIP_DEVICE_COMPILE__)
+    GroupQ g;
     // (range / qmax to nearest: quotient by the reciprocal, corrected by its exact remainder.  From 1e10 on a scale has long reached 65504,
     // and the remainder of infinity would not be a number.)
     g.shift16 = (uint16_t)f16_round_dir_dev(lo, false, g.shift);
@@ -109,14 +125,7 @@ KVTC_HD GroupQ group_header(float lo, float hi, int bits) {
     g.inv = sc > 0.0f ? rcp_rn_dev(sc) : 0.0f;
     return g;
 #else
-    g.shift16 = f16_round_dir(lo, false);
-    g.shift = f16_bits_to_f32(g.shift16);
-    const float qmax = (float)((1u << bits) - 1u);
-    const float range = hi - g.shift;                    // one fp32 subtraction
-    g.scale16 = f16_round_dir(div_rn(range, qmax), true);
-    const float sc = f16_bits_to_f32(g.scale16);
-    g.inv = sc > 0.0f ? div_rn(1.0f, sc) : 0.0f;
-    return g;
+    return group_header_plain(lo, hi, bits);
 #endif
 }
 
@@ -136,5 +145,18 @@ KVTC_HD float code_of(float d, float shift, float inv, float qmax) {
     return rq;
 #endif
 }
+
+#if defined(__HIPCC__)
+// The code of a coefficient as the low bits of a float: with the reciprocal scaled by 2^-bits, (d - shift) / scale lies in [0, 1), and adding
+// 2^(23 - bits), whose last place is 2^-bits, rounds it to nearest even exactly as code_of rounds (a power of two moves no rounding).  The clamp of
+// the multiplication does the rest of code_of: below zero and not a number give 0.  Above the largest code is nothing unless the scale is saturated (such tiles
+// take another way): a scale rounded up covers the group's range.  Four instructions with the one that packs it, where
+// round, clamp and convert to an integer made six.
+__device__ __forceinline__ uint32_t code_float(float d, float shift, float inv_b, float base) {
+    const float t = __builtin_amdgcn_fmed3f(__fmul_rn(__fsub_rn(d, shift), inv_b), 0.0f, 1.0f);
+    return __float_as_uint(__fadd_rn(t, base));
+}
+__host__ __device__ constexpr uint32_t code_base_bits(uint32_t bits) { return (150u - bits) << 23; }      // 2^(23 - bits)
+#endif
 
 }  // namespace kvtc

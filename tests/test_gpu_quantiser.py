@@ -65,3 +65,11 @@ def test_records_of_known_coefficients(groups):
 def test_plans_of_fewer_tiles_than_their_variant(r):
     """5, 7 and 9 coordinate tiles (whole and half a last one) run in the variants of 6, 8 and 10, which leave the padding out."""
     es.test_bulk_kernels_code_the_same_bits_from_every_type_and_layout(r)
+
+
+@pytest.mark.parametrize("bits", range(1, 17))
+def test_the_kernels_numerics_are_the_plain_ones_for_every_value(bits):
+    """Directed roundings, headers and codes as the kernels work them out against the definitions that the CPU tests hold to the oracle."""
+    counts = torch.zeros(4, dtype=torch.int64, device=DEV)
+    assert kv.lib().kvtc_test_numeric(bits, counts.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    assert counts.tolist() == [2 ** 32 - 2 * (2 ** 23 - 1), 0, 0, 0]
