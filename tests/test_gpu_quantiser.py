@@ -61,6 +61,46 @@ def test_records_of_known_coefficients(groups):
                 assert np.array_equal(got[t0:t0 + n], want), (tokens, dtype, t0)
 
 
+@pytest.mark.parametrize("p,r,tokens", [(128, 112, 150_000), (192, 160, 120_000), (192, 192, 120_000), (256, 224, 220_000), (256, 256, 220_000), (320, 304, 150_000),
+                                        (448, 400, 70_000), (512, 512, 70_000), (640, 608, 70_000), (704, 672, 40_000), (1024, 1024, 40_000)])
+def test_records_of_known_coefficients_in_every_kernel(p, r, tokens):
+    """The same in kernels whose waves share a token's record, in whole plans and in plans whose last wave has a tile fewer; tiles with a scale of
+    65504 and tiles without follow each other in a workgroup."""
+    groups, at = [], 0
+    for k in range(64):
+        n = min([16, 32, 16, 48, 16, 16, 64, 16][k % 8] if r < 600 else [16, 64, 96, 16][k % 4], r - at)
+        if n == 0:
+            break
+        groups.append((n, [3, 1, 7, 2, 5, 8, 4, 6][k % 8] if r < 600 else [6, 3, 2, 5][k % 4]))
+        at += n
+    assert at == r
+    blocks, at = [], 0
+    for n, b in groups:
+        blocks.append(ko.Block(at, n, b))
+        at += n
+    oplan = ko.compile_plan(np.zeros(p), np.eye(p), blocks)
+    plan = _gpu_plan(oplan)
+    n = 700
+    mixed = _rows(n, p)
+    tame = torch.from_numpy(np.random.default_rng(p).standard_normal((n, p)).astype(np.float32) * 3).to(torch.bfloat16).float().numpy() + 0.0
+    x = np.concatenate([mixed, tame, tame])                       # tiles are of 64 to 256 tokens
+    with np.errstate(all="ignore"):
+        shift, scale, codes = ko.quantise(oplan, x)
+    want = torch.from_numpy(ko.pack(oplan, shift, scale, codes)).to(DEV)
+    saturated = (np.abs(scale.astype(np.float32)) == 65504).any(axis=1)
+    assert saturated[:n].any() and not saturated[n:].any()
+    x_dev = torch.from_numpy(x).to(DEV)
+    for dtype, src in ((kv.KVTC_BF16, x_dev.to(torch.bfloat16)), (kv.KVTC_F32, x_dev)):
+        for T in (tokens, 3 * n):                                 # the bulk kernel, several tiles to a workgroup; where there is one, the short-job kernel
+            rows = src.repeat(T // (3 * n) + 1, 1)[:T].contiguous()
+            out = torch.zeros((T, plan.record_bytes), dtype=torch.uint8, device=DEV)
+            kv.kvtc_encode(plan.handle, rows, dtype, T, p, out, out.numel())
+            for t0 in range(0, T, 3 * n):
+                part = out[t0:t0 + 3 * n]
+                bad = torch.nonzero((part != want[:len(part)]).any(dim=1))[:, 0]
+                assert bad.numel() == 0, (dtype, T, t0, bad[:5].tolist())
+
+
 @pytest.mark.parametrize("r", [144, 160, 208, 272, 304])
 def test_plans_of_fewer_tiles_than_their_variant(r):
     """5, 7 and 9 coordinate tiles (whole and half a last one) run in the variants of 6, 8 and 10, which leave the padding out."""
