@@ -385,8 +385,9 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     constexpr int NV_TOTAL = SLAB_U4 / 64;                      // basis transfers per stage (1 KB each), dealt the same way
     constexpr int NV = (NV_TOTAL + NW - 1) / NW;
     // transfers per wave, lower bounds over waves: of the basis for any plan, and for a wave none of whose pieces is padding.  (With the first alone a wave that
-    // had all its pieces waited, every step, for one that it had only just asked for: fp32 of 8 tiles, 64 tensors of 2100 tokens of 240 coordinates 179 us, so 161.)
-    constexpr int NV_MIN = enc_least_pieces<NTP, NW, NV_TOTAL>(), NV_ALL = NV_TOTAL / NW, NX_MIN = NX_TOTAL / NW;
+    // had all its pieces waited, every step, for one that it had only just asked for: fp32 of 8 tiles, 64 tensors of 2100 tokens of 240 coordinates 179 us, so 161.
+    // Where at most a third of a wave's pieces may be padding it made no difference, and the choice cost half a percent.)
+    constexpr int NV_MIN = enc_least_pieces<NTP, NW, NV_TOTAL>(), NV_ALL = 2 * NV_MIN <= NV_TOTAL / NW ? NV_TOTAL / NW : NV_MIN, NX_MIN = NX_TOTAL / NW;
     bool pads = false;                                          // some of the wave's pieces are
     if constexpr (NV_MIN < NV_ALL) {
 #pragma unroll
