@@ -62,8 +62,8 @@ __device__ __forceinline__ void min_max_of(float a, float b, float& lo, float& h
 
 // This thread's part of sum (d - d_hat)^2 - d^2 = d_hat (d_hat - 2 d) over its tokens, at W widths from `bits` on.  L lanes own a
 // token, PER coordinates each (n <= L * PER; FULL: n == L * PER).  kCalibTok tokens at a time, so that the header --
-// two directed fp16 roundings and two correctly rounded divides, as many instructions as eight codes -- is worked out
-// once per token and width by one lane of four and handed round, and not by all lanes that share the token.
+// 40 instructions, as many as eight codes -- is worked out once per token and width by one lane of four and handed round, and not by all
+// lanes that share the token.
 // d_hat = shift + code * scale is exact in double: all its terms are multiples of 2^-24 below 2^26.
 // The code is rounded by adding 2^23 (to nearest even, as code_of does it: the sum's last place is 1), clamped there, and its bits are the low
 // half of the double 2^52 + 0x4b000000 + code: a subtraction in place of a conversion, which takes twice as long.

@@ -11,10 +11,12 @@
 // permuting the rows of the A operand, 16 *consecutive* coordinates of it per 32-coordinate
 // tile -- exactly one 16-coordinate block of the record format, so quantisation and packing
 // are lane-local with static bit offsets.
-//   * V_kept is pre-swizzled at plan creation into A-operand fragments.  Slabs of it and the
-//     matching columns of the tile's X rows move global -> LDS without register staging, a ring
-//     stage or two ahead of the MFMAs; every byte of X is read from HBM once, the basis slabs
-//     are re-read (from L2) once per tile, so larger token tiles mean less traffic per token.
+//   * V_kept is pre-swizzled at plan creation into A-operand fragments.  Up to 640 padded coordinates
+//     slabs of it move global -> LDS without register staging, a ring stage or two ahead of the
+//     MFMAs; beyond, and in the kernel for short jobs, every fragment is used by one wave alone and
+//     goes straight to its registers.  The tile's X rows move global -> LDS.  Every byte of X is read
+//     from HBM once, the basis is re-read (from L2) once per tile, so larger token tiles mean less
+//     traffic per token.
 //   * The coordinates are split over WC wavefronts that share the tokens; the other wavefronts
 //     take further tokens.  A wavefront holds TT x NTW accumulator tiles of 32 x 32.
 // Epilogue: block min/max -> LDS -> per (token, group) header (fp16 shift down, scale up)
@@ -329,8 +331,8 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
     __syncthreads();
 }
 
-// ONCE (where X comes by whole lines: bf16 but of 6 tiles; fp32, whose two k-steps are one, up to 4): the call's input is as much as the last-level cache, 256 MB, holds, or more (fp32: a quarter more); its lines, which are read
-// once, are then not to push the basis, of up to a megabyte a tensor, out of the L2s (11 to 20 tiles, 16 tensors of 32768 tokens at 8x, 1 GB, encode and
+// ONCE (where X comes by whole lines: bf16 but of 6 tiles; fp32, whose two k-steps are one, up to 4; and where the features lie on whole lines): the call's
+// input is as much as the last-level cache, 256 MB, holds, or more (encode_pass_bytes); its lines, which are read once, are then not to push the basis, of up to a megabyte a tensor, out of the L2s (11 to 20 tiles, 16 tensors of 32768 tokens at 8x, 1 GB, encode and
 // decode: 1228 -> 1180 us; of 4000 tokens, whose 131 MB a call finds in that cache: 115 without, 122 with).  fp32
 // at 40x: two tiles, 16 tensors of 20000 tokens, 268 -> 252, four tiles, two of 40000, 116 -> 110; of 6 and 16 tiles 1 to 4 % slower so.  A copy of the whole tile: as a choice per
 // transfer it cost the small calls 2 to 4 %, as two main loops in front of one epilogue all calls half of their speed, in moves of accumulators.
@@ -355,7 +357,7 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     // The plan's coordinate tiles are shared out evenly: a wave has NTW of them or one fewer, whose place it does not multiply, and the padding is
     // not fetched.  What these kernels have at their disposal is power -- the clock gives way, to 1.5 GHz, under matrix instructions and a stream
     // from HBM at once --, so work that can be left out counts although it would fit the time (32-layer cache at 16x, plans of 7, 8 and 9 tiles that
-    // run as 8 and 10: 1283 -> 1256 us).  Not up to four tiles, which are bound by HBM, nor in the 8-wave variants: the conditions cost those 0.5 %.
+    // run as 8 and 10: 1300 -> 1282 us).  Not up to four tiles, which are bound by HBM, nor in the 8-wave variants: the conditions cost those 0.5 %.
     const int nt = enc_min_tiles(NTP) < NTP ? (P.r + 31) / 32 : NTP, wc = wave % WC;
     const int ct0 = wc * (nt / WC) + min(wc, nt % WC), n_ct = nt / WC + (wc < nt % WC ? 1 : 0);
     const bool full = enc_min_tiles(NTP) == NTP || n_ct >= NTW;
@@ -579,8 +581,8 @@ constexpr int kShortThreads = 640;
 
 // BULK: the same as the bulk kernels' tile of plans of more than 20 tiles, those shared out evenly among 8 waves (NTW of them or one fewer).  By way of LDS
 // the basis of 1024 coordinates came into a compute unit at 26 bytes a cycle, 1300 cycles for a k-step whose matrix instructions take 512; it comes
-// twice as fast so.  1024 of 4096 features, two sections of 32768 tokens, both ways: 1268 -> 1164 us, with X (once: an input of the
-// last-level cache's 256 MB and more) not kept by the caches 1136; 1024 of 1024, 65536 tokens 165 -> 146; 4096 of 8192 in four sections, 1000 tokens, both ways
+// twice as fast so.  1024 of 4096 features, two sections of 32768 tokens, both ways: 1268 -> 1164 us, with X (once: an input of
+// encode_pass_bytes and more) not kept by the caches 1136; 1024 of 1024, 65536 tokens 165 -> 146; 4096 of 8192 in four sections, 1000 tokens, both ways
 // 1080 -> 915.
 template <int NTW, typename XT, int TT, int TOK, int AHEAD, bool BULK>
 __device__ __forceinline__ void encode_register_tile(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, uint4* work, bool once) {
