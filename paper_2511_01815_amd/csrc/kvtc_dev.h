@@ -160,10 +160,10 @@ __device__ inline bool bulk_takes_mid_jobs(const KernelArgs& a, int key, uint32_
 
 // Exclusive prefix of the per-thread sums over the workgroup, and the total: inside the waves by lane exchange, then over the waves' totals --
 // one barrier, where a scan through LDS took two per doubling (an append step of 64 caches, three such launches: 23.2 us,
-// now 22.3).  With it go the minimum of `low`, the OR of two flags and the sum of `amount`, which is the same number in every workgroup.
-struct BlockScan { uint32_t before, total, low, flags; float amount; };
+// now 22.3).  With it go the minimum of `low` and the OR of two flags.
+struct BlockScan { uint32_t before, total, low, flags; };
 template <int NT>
-__device__ __forceinline__ BlockScan block_scan(uint32_t sum, uint32_t low, uint32_t flags, float amount, uint32_t* scratch /*[4 * NT / 64]*/) {
+__device__ __forceinline__ BlockScan block_scan(uint32_t sum, uint32_t low, uint32_t flags, uint32_t* scratch /*[3 * NT / 64]*/) {
     constexpr int NWAVE = NT / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t incl = sum;
@@ -172,17 +172,15 @@ __device__ __forceinline__ BlockScan block_scan(uint32_t sum, uint32_t low, uint
         const uint32_t v = (uint32_t)__shfl_up((int)incl, d, 64);
         if (lane >= d) incl += v;
         low = min(low, (uint32_t)__shfl_xor((int)low, d, 64));
-        amount += __shfl_xor(amount, d, 64);
     }
     flags = (__any(flags & 1u) ? 1u : 0u) | (__any(flags & 2u) ? 2u : 0u);
     if (lane == 63) {
         scratch[wave] = incl;
         scratch[NWAVE + wave] = low;
         scratch[2 * NWAVE + wave] = flags;
-        scratch[3 * NWAVE + wave] = __float_as_uint(amount);
     }
     __syncthreads();
-    BlockScan r{incl - sum, 0u, 0xffffffffu, 0u, 0.0f};
+    BlockScan r{incl - sum, 0u, 0xffffffffu, 0u};
 #pragma unroll
     for (int w = 0; w < NWAVE; ++w) {
         const uint32_t n = scratch[w];
@@ -190,9 +188,21 @@ __device__ __forceinline__ BlockScan block_scan(uint32_t sum, uint32_t low, uint
         r.total += n;
         r.low = min(r.low, scratch[NWAVE + w]);
         r.flags |= scratch[2 * NWAVE + w];
-        r.amount += __uint_as_float(scratch[3 * NWAVE + w]);
     }
     return r;
+}
+
+// Sum over the workgroup, the same number in every thread and every workgroup.
+template <int NT>
+__device__ __forceinline__ float block_sum(float v, float* scratch /*[NT / 64]*/) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float sum = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) sum += scratch[w];
+    return sum;
 }
 
 // inclusive prefix sum over the 64 lanes, on the vector unit alone
@@ -214,7 +224,7 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
 // lowest bad job in *status.  (A single tensor's launch has no table: built from one job it was 1 us of a small call.)
 struct TileTable { uint32_t total; bool pass; };
 template <bool kEncode, int NT = kThreads>
-__device__ inline TileTable build_tile_table(const KernelArgs& a, int variant_key, uint32_t* tile_start, uint32_t* scratch /*[8 * NT / 64]*/) {
+__device__ inline TileTable build_tile_table(const KernelArgs& a, int variant_key, uint32_t* tile_start, uint32_t* scratch /*[7 * NT / 64]*/) {
     if (!a.jobs) return {a.single_tiles, a.x_pass_from == 0.0f};      // the host has checked everything: no table
     const int tid = threadIdx.x;
     const int n_jobs = a.n_jobs;
@@ -222,6 +232,7 @@ __device__ inline TileTable build_tile_table(const KernelArgs& a, int variant_ke
     const int j0 = tid * per;
     uint32_t local[kMaxJobs / NT], mid[kMaxJobs / NT];           // tiles; tiles of a job of more than one short tile that may go either way
     uint32_t sum = 0, mids = 0;
+    const bool counts = a.x_pass_from < __builtin_huge_valf();       // (the host knows that a call is too small for it: half a microsecond of every launch)
     float amount = 0.0f;
     uint32_t first_bad = 0xffffffffu;
     uint32_t flags = 0;                                          // 1: a job longer than the short-job launch's limit; 2: one that may go either way
@@ -234,7 +245,7 @@ __device__ inline TileTable build_tile_table(const KernelArgs& a, int variant_ke
             const kvtc_job jb = a.jobs[j];
             if (job_ok(a, j, jb)) {
                 const PlanDev& pl = a.plans[jb.plan];
-                amount += (float)jb.n_tokens * (float)pl.p;
+                if (counts) amount += (float)jb.n_tokens * (float)pl.p;
                 // each launch serves the plans of its own kernel variant; other launches take the rest.
                 int tw = kEncode ? pl.enc_tok_wg : pl.dec_tok_wg;
                 int key = kEncode ? enc_key(pl) : pl.dec_tt * 100 + pl.dec_cls;
@@ -254,12 +265,12 @@ __device__ inline TileTable build_tile_table(const KernelArgs& a, int variant_ke
         sum += tiles;
         mids += mid[k];
     }
-    BlockScan sc = block_scan<NT>(sum, first_bad, flags, amount, scratch);
-    const bool pass = __builtin_amdgcn_readfirstlane(sc.amount >= a.x_pass_from ? 1 : 0) != 0;
+    BlockScan sc = block_scan<NT>(sum, first_bad, flags, scratch);
+    const bool pass = counts && __builtin_amdgcn_readfirstlane(block_sum<NT>(amount, reinterpret_cast<float*>(scratch + 6 * NT / 64)) >= a.x_pass_from ? 1 : 0) != 0;
     // lowest bad job -> status (workgroup 0 only; a plain vector store)
     if (a.status && blockIdx.x == 0 && tid == 0 && sc.low != 0xffffffffu) *a.status = sc.low + 1u;
     if (kEncode && __builtin_expect(sc.flags == 3u, 0)) {
-        const BlockScan with = block_scan<NT>(sum + mids, 0u, 0u, 0.0f, scratch + 4 * NT / 64);
+        const BlockScan with = block_scan<NT>(sum + mids, 0u, 0u, scratch + 3 * NT / 64);
         if (bulk_takes_all(sc.total, with.total, gridDim.x)) {
             sc = with;
 #pragma unroll
