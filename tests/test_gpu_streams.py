@@ -1,5 +1,6 @@
-"""Tensors beyond the last-level cache: decode stores the whole tiles of an output of more than half of it past the caches, encode
-reads an input of all of it and more without keeping it, by whole lines.  The same bits as in calls of a part of the tokens each."""
+"""Tensors beyond the last-level cache, which encode reads and decode stores past the caches from a size on that depends on the kernel
+(kvtc_host_encode_pass_bytes, kvtc_host_decode_pass_bytes; the outputs here of plans of up to 4 tiles, of one tensor of 5 and 6, and in fp32 of up to
+10, stay in the caches: test_gpu_streams_shapes.py has those beyond).  The same bits as in calls of a part of the tokens each."""
 import numpy as np
 import pytest
 import torch
