@@ -39,6 +39,7 @@ struct kvtc_entropy {
     const uint8_t* len_dev;     // [n_tables][R][256] length
     const uint8_t* dec_dev;     // the decoder's tables, one behind the other, each [n_tables][R]: lengths, symbols, offsets
     const uint32_t* lim_dev;    // [n_tables][R][4]
+    const uint8_t* log_dev;     // the staged decoder's tables, or nullptr: [n_tables] of kLogRow * R bytes
 };
 
 namespace {
@@ -74,6 +75,24 @@ constexpr int kDecSegment = 144, kDecBatch = 16, kDecPitch = 20;
 static_assert(kChunk * kDecPitch * 4 % 256 == 0, "tables from a multiple of 256 bytes on");
 static_assert(kDecSegment % 16 == 0 && kDecBatch % 2 == 0 && kDecSegment * kDecRow + 16 * kChunk * kDecPitch * 4 <= kLdsMost, "a segment's table and 16 waves' rows fit");
 
+// The staged decoder (entropy_decode_staged_kernel) finds a code's length with one lookup and no comparison.  u, the complement of the string's
+// next 12 bits read as a number with the first bit on top, is small where codes are long.  Codes longer than L bits, at most 256 of at most 2^(11 - L)
+// such numbers each, take those below a multiple of 2^(12 - L) that is at most 64 * 2^(13 - L), so it is enough to know u to one part in 64: the
+// bits of a float, exponent and six of mantissa, where u = 64 is the smallest normal number and everything below lies in the denormals' even steps.
+// 448 entries to a position, 32 - length each.  (A code with strings that begin no code has its bounds elsewhere: such tables are not built, and
+// the other decoder serves them.)  Behind the length all is as above, with the offsets by 32 - length, 16 + 4 .. 16 + 15.
+// LDS: kLogMost rows each of symbols, offsets and lengths, those of the last R rows only, so that a row is a constant of an instruction; then the waves' strings,
+// kLogString dwords of every lane's, dword-major: free of conflicts whatever the lanes read.
+constexpr int kLogMost = 128, kLogEntries = 448, kLogRow = 256 + kDecOff + kLogEntries;
+constexpr int kLogSym = 0, kLogOff = kLogMost * 256, kLogLen = kLogOff + kLogMost * kDecOff;
+constexpr int kLogUnit = 32, kLogAhead = 8, kLogString = 17;           // positions decoded from a slot; of those, still to come when the next is requested; its dwords
+constexpr int kLogSlot = kLogString * 256;
+static_assert((31 + (kLogAhead + kLogUnit - 4) * kMaxLen) / 32 + 2 < kLogString, "the window of a unit's last four codes lies in its slot");
+static_assert(kLogSlot >= kChunk * 64 && kLogLen % 256 == 0 && kLogMost * kLogEntries % 256 == 0, "64 bytes of every row fit a slot; slots on multiples of 256");
+static_assert(kLogLen >= 32768 && kLogLen - 32768 + kLogMost * kLogEntries <= 65536, "the lengths lie within an instruction's offset of 32768");
+__host__ __device__ constexpr size_t log_bytes(int R) { return (size_t)(kLogLen + R * kLogEntries + 255) / 256 * 256; }        // the tables in LDS
+static_assert(log_bytes(kLogMost) + 16 * kLogSlot <= kLdsMost, "all of it fits");
+
 struct EntropyArgs {
     const kvtc_entropy_job* jobs;     // device, or nullptr -> `single`
     int32_t n_jobs;
@@ -87,6 +106,7 @@ struct EntropyArgs {
     const uint8_t* len;
     const uint8_t* dec;
     const uint32_t* lim;
+    const uint8_t* log;
     int32_t R, n_tables;
     int32_t chunks_per_wave;          // chunks a wave takes one after the other, so that a workgroup's tables serve several
     int64_t max_tokens;               // the launch covers this many tokens per job; a longer job is left alone
@@ -673,10 +693,250 @@ __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs 
     }
 }
 
+// decode of records of up to kLogMost bytes under complete codes: a lane per token as above, but the string comes through LDS, where a code's window is one read
+// whatever the lane's place in it, and a length is one lookup (kLogRow): 9 vector instructions to a symbol where the form above has 21.  A lane fetches 68
+// bytes for every 32 positions, eight positions ahead of their use, or under the chunk before; the records leave as the flat runs of bytes that they are,
+// whole lines, past the caches (they pushed the strings out of the L2s that are read up to four times).  A wave takes four codes from a window of 64 bits, and looks
+// up four symbols meanwhile.  Bound by the LDS, 3.9 reads to a symbol and in use for half of the time, with four waves to a SIMD, as many as the strings leave room
+// for, that wait for each other's lookups.
+// 256 MiB of records of 128 bytes: 264 us by the form above, 162 so (192 with 64-byte pieces of rows and windows of two codes, 171 with stores that the
+// caches keep); 64 tensors of 30000 tokens of 100 bytes 292 and 117; one of 64 tokens 16 and 13.  (With a reader behind it that finds 30 to 125 MB of
+// records in the caches, the pair gains nothing by the stores past them, and loses 2 %.)
+template <int N> using row_of = std::integral_constant<int, N>;
+__global__ void __launch_bounds__(1024) entropy_decode_staged_kernel(const EntropyArgs a) {
+    extern __shared__ uint32_t lds[];
+    typedef const uint8_t __attribute__((address_space(3))) * lds_u8;
+    typedef uint32_t __attribute__((address_space(3))) * lds_u32;
+    typedef const char __attribute__((address_space(1))) * global_ptr;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+    const uint32_t R = (uint32_t)a.R, per_row = R / 4u;
+    const JobView v = job_view(a, blockIdx.y);
+    const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
+    if (!v.ok || first >= v.n_chunks || lds_offset(lds) != 0u) return;         // (there is no other LDS: the tables are at 0)
+    const uint32_t slot = (uint32_t)log_bytes((int)R) + wave * kLogSlot, slot_bit = slot / 8u, lane4 = lane * 4u;
+
+    // the chunk being decoded: its string less a dword, the last dword of the payload from its first on; the slot's first dword
+    uint64_t src = 0;
+    int last = 0;
+    uint32_t base = 0, at = 0;                                     // at: slot_bit + the lane's next bit from the slot's first on, less 32 for every code since
+    uint32_t q[kLogString];                                        // the slot's next content
+    auto request = [&](uint32_t d) {
+        if (__all((int)d <= last - (kLogString - 1))) {
+            const global_ptr from = (global_ptr)src + (d * 4u + 4u);
+#pragma unroll
+            for (int i = 0; i < kLogString / 4; ++i) {
+                const u32x4_any w = reinterpret_cast<const u32x4_any __attribute__((address_space(1)))*>(from)[i];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) q[4 * i + k] = w[k];
+            }
+            q[kLogString - 1] = reinterpret_cast<const uint32_t __attribute__((address_space(1)))*>(from)[kLogString - 1];
+        } else {                                                    // near the payload's end: dword by dword, none behind it
+#pragma unroll
+            for (int i = 0; i < kLogString; ++i)
+                q[i] = *reinterpret_cast<const uint32_t __attribute__((address_space(1)))*>((global_ptr)src + (uint32_t)(min((int)d + i, last) + 1) * 4u);
+        }
+    };
+    uint32_t next_off = 0, next_own = 0;                            // of the next chunk, on their way
+    auto directory = [&](int64_t chunk) {
+        next_off = v.chunk_off[chunk];
+        next_own = v.len_bits[chunk * kChunk + lane];
+    };
+    // the next chunk's first string; returns the lane's first bit in it
+    auto enter = [&](int64_t chunk) {
+        uint64_t begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_off);
+        begin = (begin < v.payload_cap ? begin : v.payload_cap) & ~3ull;
+        const uint64_t left = (v.payload_cap - begin) / 4u;
+        last = (int)(left < 0x7fffffffull ? left : 0x7fffffffull) - 1;
+        src = (uint64_t)uniform_ptr(v.payload + begin) - 4u;        // (of an empty payload: the directory's last dword)
+        uint32_t bit = wave_inclusive_scan(next_own) - next_own;
+        if (chunk * kChunk + lane >= v.T) bit = 0u;                 // (lanes behind the last token run along on the first one's string)
+        base = bit >> 5;
+        request(base);
+        return bit & 31u;
+    };
+
+    int64_t chunk = first + wave;
+    const bool live = chunk < v.n_chunks;
+    if (live) directory(chunk);
+    {
+        const uint4* from = reinterpret_cast<const uint4*>(a.log + v.table * kLogRow);
+        uint4* to = reinterpret_cast<uint4*>(lds);
+        const uint32_t n_sym = R * 16u, n_off = n_sym + R * (kDecOff / 16), n = R * (kLogRow / 16);
+#pragma unroll 6
+        for (uint32_t i = threadIdx.x; i < n; i += blockDim.x)
+            to[i < n_sym ? i : (i < n_off ? i - n_sym + kLogOff / 16 : i - n_off + kLogLen / 16)] = from[i];
+    }
+    if (live) at = slot_bit + enter(chunk);
+    __syncthreads();
+    for (int c = 0; c < a.chunks_per_wave; ++c, chunk += n_waves) {
+        if (chunk >= v.n_chunks) break;
+        const bool follows = c + 1 < a.chunks_per_wave && chunk + n_waves < v.n_chunks;
+        uint32_t o[kLogMost / 4];                                   // the row
+        uint32_t rev[4], m[4];                                      // of the four codes found last: the string from there, first bit on top; 32 - length
+        auto length = [&](uint32_t bits, auto row_tag) {
+            // 1 + half the string's first 22 bits as a fraction, taken from 1.5 - 2^-23: half of their complement; times 2^-119, all of it exact
+            const float x = __uint_as_float(__builtin_amdgcn_alignbit(0x3f800000u >> 22, bits, 10));
+            const float f = __builtin_fmaf(x, -0x1p-119f, (float)(1.5 - 0x1p-23) * 0x1p-119f);
+            return (uint32_t)((lds_u8)__builtin_amdgcn_alignbit(1u, __float_as_uint(f), 17))[kLogLen - 32768 + decltype(row_tag)::value * kLogEntries];
+        };
+        // the ranks of two symbols: the code less its length's offset, modulo 256.  (The wait state is for a vector instruction that reads the second.)
+        auto ranks = [&](int b, const uint32_t (&off)[4], uint32_t (&rank)[4]) {
+            asm("v_sub_u16_sdwa %0, %2, %3 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_0\n\t"
+                "v_sub_u16_sdwa %1, %4, %5 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_0\n\t"
+                "s_nop 0"
+                : "=&v"(rank[b]), "=v"(rank[b + 1])
+                : "v"(rev[b] >> (m[b] & 31u)), "v"(off[b]), "v"(rev[b + 1] >> (m[b + 1] & 31u)), "v"(off[b + 1]));
+        };
+        // the codes of positions row .. row + 3, and meanwhile the symbols of the four before, two at a time
+        auto four = [&](auto row_tag) {
+            constexpr int row = decltype(row_tag)::value, k = row % kLogUnit;
+            constexpr bool before = row > 0;
+            const lds_u32 w = (lds_u32)(((at << 3) & ~255u) | lane4);
+            const uint32_t w0 = w[k * 64], w1 = w[k * 64 + 64], w2 = w[k * 64 + 128];
+            uint32_t off[4], rank[4], byte[4];
+            if constexpr (before) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) off[b] = ((lds_u8)m[b])[kLogOff - 16 + (row - 4 + b) * kDecOff];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            uint32_t r[4], n[4];
+            r[0] = __builtin_bitreverse32(__builtin_amdgcn_alignbit(w1, w0, at));
+            n[0] = length(r[0], row_of<row>());
+            uint32_t low = __builtin_bitreverse32(__builtin_amdgcn_alignbit(w2, w1, at));
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (before) {
+                ranks(0, off, rank);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) byte[b] = ((lds_u8)rank[b])[kLogSym + (row - 4 + b) * 256];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            r[1] = __builtin_amdgcn_alignbit(r[0], low, n[0]);
+            n[1] = length(r[1], row_of<row + 1>());
+            low = __builtin_amdgcn_alignbit(low, 0u, n[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (before) {
+                ranks(2, off, rank);
+#pragma unroll
+                for (int b = 2; b < 4; ++b) byte[b] = ((lds_u8)rank[b])[kLogSym + (row - 4 + b) * 256];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            r[2] = __builtin_amdgcn_alignbit(r[1], low, n[1]);
+            n[2] = length(r[2], row_of<row + 2>());
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (before) o[row / 4 - 1] = byte[0] | (byte[1] << 8) | (byte[2] << 16) | (byte[3] << 24);
+            __builtin_amdgcn_sched_barrier(0);
+            r[3] = __builtin_amdgcn_alignbit(r[2], 0u, n[2]);
+            n[3] = length(r[3], row_of<row + 3>());
+            __builtin_amdgcn_sched_barrier(0);
+            at -= n[0] + n[1] + n[2] + n[3];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                rev[b] = r[b];
+                m[b] = n[b];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto has = [&](uint32_t row) {                              // (compared where it is asked: 32 answers kept through the loop are too many)
+            uint32_t r = R;
+            asm volatile("" : "+s"(r));
+            return row < r;
+        };
+        uint32_t then = 0;                                          // where the next chunk begins
+        auto unit = [&](auto row_tag) {
+            constexpr int row = decltype(row_tag)::value;
+#pragma unroll
+            for (int i = 0; i < kLogString; ++i) ((lds_u32)(slot + lane4))[i * 64] = q[i];
+            if (row == 0 && follows) directory(chunk + n_waves);
+            const bool final = !has(row + kLogUnit);
+            if (final && follows) then = slot_bit + enter(chunk + n_waves);
+            four(row_of<row>());
+            if (has(row + 4u)) four(row_of<row + 4>());
+            if (has(row + 8u)) four(row_of<row + 8>());
+            if (has(row + 12u)) four(row_of<row + 12>());
+            if (has(row + 16u)) four(row_of<row + 16>());
+            if (has(row + 20u)) four(row_of<row + 20>());
+            uint32_t moved = 0;
+            if (!final) {
+                moved = (uint32_t)((int)(at - slot_bit) >> 5) + (kLogUnit - kLogAhead);
+                base += moved;
+                request(base);
+            }
+            if (has(row + 24u)) four(row_of<row + 24>());
+            if (has(row + 28u)) four(row_of<row + 28>());
+            at += 32u * (kLogUnit - moved);
+        };
+        unit(row_of<0>());
+        if (has(32u)) unit(row_of<32>());
+        if (has(64u)) unit(row_of<64>());
+        if (has(96u)) unit(row_of<96>());
+        uint32_t tail = 0;                                          // the row's last dword, whose symbols are still to be looked up
+#pragma unroll
+        for (uint32_t b = 0; b < 4; ++b) {
+            const uint32_t row = R - 4u + b, off = ((lds_u8)(m[b] + row * kDecOff))[kLogOff - 16];
+            tail |= (uint32_t)((lds_u8)((((rev[b] >> (m[b] & 31u)) - off) & 0xffu) + row * 256u))[kLogSym] << (8 * b);
+        }
+        at = then;
+        // (the next string has landed by now: waited for in front of the stores, so that nothing waits for those)
+#pragma unroll
+        for (int i = 0; i < kLogString; ++i) asm volatile("" : "+v"(q[i]));
+        // the rows, 32 at a time, through the slot, and from there as the flat run of bytes that they are.  (16-byte pieces of rows of a power of two are
+        // permuted, so that 16 rows' pieces lie on different banks.)
+        const uint32_t n_rows = (uint32_t)min(v.T - chunk * kChunk, (int64_t)kChunk);
+        uint32_t* const img = lds + slot / 4u;
+        const uint32_t swizzle = per_row == 32u ? 7u : (per_row == 16u ? 3u : 0u);
+        uint32_t l = lane;
+        asm volatile("" : "+v"(l));                                 // (addresses are worked out here, not kept through the loop)
+        for (uint32_t r0 = 0; r0 < n_rows; r0 += 32u) {
+            if ((l & 32u) == r0) {
+                const uint32_t r = l & 31u, x = (per_row == 32u ? r >> 1 : r >> 2) & swizzle;
+                if (per_row % 4u == 0u) {
+#pragma unroll
+                    for (uint32_t k = 0; k < kLogMost / 16; ++k)
+                        if (has(16u * k)) *reinterpret_cast<uint4*>(img + r * per_row + 4u * (k ^ x)) = make_uint4(o[4 * k], o[4 * k + 1], o[4 * k + 2], o[4 * k + 3]);
+                } else {
+#pragma unroll
+                    for (uint32_t d = 0; d < kLogMost / 4; ++d)
+                        if (has(4u * d)) img[r * per_row + d] = o[d];
+                }
+                img[r * per_row + (per_row - 1u ^ 4u * x)] = tail;
+            }
+            wave_fence();
+            const uint32_t n = min(n_rows - r0, 32u) * per_row;
+            uint32_t* to = v.rec + (chunk * kChunk + r0) * per_row;
+#pragma unroll
+            for (uint32_t i = 0; i < kLogMost / 32; ++i) {
+                const uint32_t f = 64u * i + l, d = 4u * f;
+                if (d >= n) break;
+                const uint4 w = *reinterpret_cast<const uint4*>(img + 4u * (f ^ ((f >> 4) & swizzle)));
+                if (d + 4u <= n) {
+                    __builtin_nontemporal_store(u32x4{w.x, w.y, w.z, w.w}, reinterpret_cast<u32x4_any*>(to + d));
+                } else {
+                    to[d] = w.x;
+                    if (d + 1u < n) to[d + 1] = w.y;
+                    if (d + 2u < n) to[d + 2] = w.z;
+                }
+            }
+            wave_fence();
+        }
+    }
+}
+
 uint32_t reverse_bits(uint32_t v, int n) {
     uint32_t r = 0;
     for (int i = 0; i < n; ++i) { r = (r << 1) | (v & 1u); v >>= 1; }
     return r;
+}
+
+// 32 - length by the float index of u, for a complete code with count[L] codes of L bits
+void log_lengths(const uint32_t (&count)[kMaxLen + 1], uint8_t* entries) {
+    uint32_t below = 0;                                             // u is below this for codes of `len` bits and more
+    int len = kMaxLen;
+    for (int i = 0; i < kLogEntries; ++i) {
+        const int octave = i < 64 ? 0 : i / 64 - 1;
+        const uint32_t u = i < 64 ? (uint32_t)i : (uint32_t)(64 + i % 64) << octave;
+        while (len > 1 && u >= below + (count[len] << (kMaxLen - len))) below += count[len] << (kMaxLen - len), --len;
+        entries[i] = (uint8_t)(32 - len);
+    }
 }
 
 size_t bound_of(int R, int64_t n_tokens) {
@@ -687,8 +947,10 @@ size_t bound_of(int R, int64_t n_tokens) {
 // The shape of a launch over `n_chunks` chunks of each of n_jobs jobs.  A launch all of whose chunks can run at once does that, with
 // the fewest waves per workgroup, from four up, that allow it: the compute units share the chunks, and each of their waves has
 // more of its vector unit.  A larger one runs workgroups of 16 waves, or 8 where that lets more waves share a compute unit's LDS
-// (4 where the jobs have no more chunks), each wave taking as many chunks in turn (at most 8) as still leave every place on the chip
-// taken, because a workgroup first copies its table (64 KiB for 128-byte records, against 8 KiB of records per chunk).  Without a
+// (4 where the jobs have no more chunks).  Each wave takes as many chunks in turn (at most 16) as end soonest: every compute unit works through its
+// workgroups, each of which first copies its table (64 KiB for 128-byte records, against 8 KiB of records per chunk; counted as a fifth of a round of chunks),
+// as long as every place on the chip is taken.  (Rounded down from the chunks to a place, 64 tensors of 469 chunks of 100 bytes were 320 workgroups on 256 compute units:
+// encode 178 us and 168 now, 37 of 360 of 120 bytes 130 and 102.)  Without a
 // table in LDS workgroups are as small as they can be, or, with more jobs than compute units, a job (of up to 16 chunks) each: then a
 // compute unit's caches hold few tables.
 // (2188 chunks of 128-byte records, encode and decode: 75 + 102 us with four waves that took two chunks in turn on one workgroup per
@@ -707,8 +969,13 @@ Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs) 
     int waves = 4;
     for (const int w : {8, 16})
         if (n_chunks > w / 2 && places(w) > 0 && (waves == 4 || places(w) * w >= places(waves) * waves)) waves = w;
-    const int64_t per = total / (cus * std::max<int64_t>(places(waves), 1) * waves);
-    return shape(waves, per < 1 ? 1 : (per > 8 ? 8 : per));
+    int64_t best = 1, least = INT64_MAX;
+    for (int64_t per = 1; per <= 16; ++per) {
+        const int64_t to_each = ((n_chunks + waves * per - 1) / (waves * per) * n_jobs + cus - 1) / cus, cost = to_each * (5 * per + 1);
+        if (per > 1 && to_each < places(waves)) break;
+        if (cost < least) least = cost, best = per;
+    }
+    return shape(waves, best);
 }
 
 // Whether jobs of a few chunks each, a workgroup per job, would wait for others to leave the LDS.  Then they read their tables from global
@@ -728,6 +995,17 @@ bool decode_in_pieces(const Shape& sh, int R, int64_t n_chunks, int n_jobs) {
     const int64_t rounds = ((int64_t)sh.blocks * n_jobs + places - 1) / places * sh.chunks_per_wave;
     const int64_t at_once = (rounds <= 2 ? n_chunks * n_jobs / rounds : places * sh.waves) * kChunk * R;
     return R >= 128 && (rounds == 1 ? at_once > 30 << 20 : rounds == 2 ? at_once > 26 << 20 : at_once >= 40 << 20);
+}
+
+// Whether the staged decoder, with more LDS to a workgroup, would run jobs of a few chunks in more rounds of workgroups than the other, each of which copies its
+// tables for little work.  us, the other and the staged: 1000 jobs of one chunk of 36 bytes 9.2 and 13.3, 400 of four of 100 bytes 18.6 and 24.3 (two rounds against
+// one); 300 of five of 64 bytes, as many, 19.3 and 15.4; three rounds against two, 600 of seven of 36 bytes, 17.9 and 19.7, of sixteen 36.7 and 27.4.
+bool small_jobs_wait(const Shape& staged, const Shape& other, int64_t n_chunks, int n_jobs) {
+    auto rounds = [&](const Shape& s) {
+        const int64_t places = compute_units() * std::min<int64_t>(kLdsBudget / s.lds, 32 / s.waves);
+        return ((int64_t)s.blocks * n_jobs + places - 1) / places;
+    };
+    return n_chunks <= 8 && rounds(staged) >= (n_chunks <= 4 ? 2 : 3) && rounds(staged) > rounds(other);
 }
 
 kvtc_status launch(const char* who, void (*fn)(EntropyArgs), const Shape& sh, int n_jobs, EntropyArgs a, hipStream_t st) {
@@ -770,7 +1048,9 @@ kvtc_status run_decode(const char* who, const kvtc_entropy* e, const EntropyArgs
     void (*const fn)(EntropyArgs) = !tab_lds                                        ? &entropy_decode_kernel<false, false>
                                     : decode_in_pieces(sh, R, max_chunks, n_jobs) ? &entropy_decode_kernel<true, true>
                                                                                     : &entropy_decode_kernel<true, false>;
-    const kvtc_status rc = launch(who, fn, sh, n_jobs, a, st);
+    const Shape staged = a.log && tab_lds ? launch_shape(log_bytes(R), kLogSlot, max_chunks, n_jobs) : Shape{};
+    const kvtc_status rc = staged.waves && !small_jobs_wait(staged, sh, max_chunks, n_jobs) ? launch(who, &entropy_decode_staged_kernel, staged, n_jobs, a, st)
+                                                                                           : launch(who, fn, sh, n_jobs, a, st);
     if (rc != KVTC_OK) return rc;
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return set_error(KVTC_E_HIP, "%s: launch failed: %s", who, hipGetErrorString(err));
@@ -784,6 +1064,7 @@ EntropyArgs base_args(const kvtc_entropy* e) {
     a.len = e->len_dev;
     a.dec = e->dec_dev;
     a.lim = e->lim_dev;
+    a.log = e->log_dev;
     a.R = e->record_bytes;
     a.n_tables = e->n_tables;
     return a;
@@ -804,10 +1085,12 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
     std::vector<uint16_t> enc;
     std::vector<uint8_t> dec;
     std::vector<uint32_t> lim;
+    std::vector<uint8_t> log;
     try {
         enc.resize(rows * 256);
         dec.assign(rows * kDecRow, 0);
         lim.assign(rows * 4, 0xffffffffu);
+        if (R <= kLogMost) log.resize(rows * kLogRow);
     } catch (const std::bad_alloc&) {
         return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: host allocation failed");
     }
@@ -836,6 +1119,7 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
             }
             code <<= 1;
         }
+        if (kraft != (1u << kMaxLen)) log.clear();
         if (kraft > (1u << kMaxLen))
             return set_error(KVTC_E_ARG, "kvtc_entropy_create: table %d, position %d: the lengths are not those of a prefix code", (int)(k / R), (int)(k % R));
         memset(D, least, 256);
@@ -847,13 +1131,20 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
             if (len <= 8)
                 for (uint32_t i = rev; i < 256u; i += 1u << len) D[i] = (uint8_t)len;
         }
+        if (!log.empty()) {
+            uint8_t* const set = &log[k / R * R * kLogRow];
+            const size_t pos = k % R;
+            memcpy(set + pos * 256, S, 256);
+            for (int len = 1; len <= kMaxLen; ++len) set[(size_t)R * 256 + pos * kDecOff + 16 - len] = O[len];
+            log_lengths(count, set + (size_t)R * (256 + kDecOff) + pos * kLogEntries);
+        }
     }
-    // one allocation: codes, the decoder's tables and limits, lengths
-    const size_t enc_b = enc.size() * 2, dec_b = dec.size(), lim_b = lim.size() * 4, len_b = rows * 256;
+    // one allocation: codes, the decoders' tables and limits, lengths
+    const size_t enc_b = enc.size() * 2, dec_b = dec.size(), lim_b = lim.size() * 4, len_b = rows * 256, log_b = log.size();
     char* blob = nullptr;
-    if (hipMalloc(reinterpret_cast<void**>(&blob), enc_b + dec_b + lim_b + len_b) != hipSuccess) {
+    if (hipMalloc(reinterpret_cast<void**>(&blob), enc_b + dec_b + lim_b + len_b + log_b) != hipSuccess) {
         (void)hipGetLastError();
-        return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: hipMalloc of %zu bytes failed", enc_b + dec_b + lim_b + len_b);
+        return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: hipMalloc of %zu bytes failed", enc_b + dec_b + lim_b + len_b + log_b);
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = hipSuccess;
@@ -868,6 +1159,7 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
     const char* lim_d = put(lim.data(), lim_b);
     const char* dec_d = put(dec.data(), dec_b);
     const char* len_d = put(code_len_host, len_b);
+    const char* log_d = log_b ? put(log.data(), log_b) : nullptr;
     if (e == hipSuccess) e = hipStreamSynchronize(st);           // the host images die with this call
     kvtc_entropy* h = e == hipSuccess ? new (std::nothrow) kvtc_entropy : nullptr;
     if (!h) {
@@ -882,6 +1174,7 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
     h->lim_dev = reinterpret_cast<const uint32_t*>(lim_d);
     h->dec_dev = reinterpret_cast<const uint8_t*>(dec_d);
     h->len_dev = reinterpret_cast<const uint8_t*>(len_d);
+    h->log_dev = reinterpret_cast<const uint8_t*>(log_d);
     *out = h;
     return KVTC_OK;
 }
