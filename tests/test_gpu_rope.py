@@ -116,3 +116,35 @@ def test_key_path_rotation_undone_coded_decoded_rotated_again():
     # and the point of it all: the round trip is as close to the cached keys as the coder is to the un-rotated ones
     rel = np.linalg.norm(got - k_rot) / np.linalg.norm(k_rot - k_rot.mean(0))
     assert rel < 0.3, rel
+
+
+@pytest.mark.parametrize("d,H,T,offset,pairing,base,bits", [
+    (16, 1, 1, 0, "half", 1e4, 17), (16, 9, 513, 0, "interleaved", 256.0, 31),    # one lane to a token; heads in shares with one left over
+    (80, 3, 260, 0, "half", 5e5, 17), (256, 5, 130, 0, "interleaved", 1e4, 17),   # lanes of a token that are no power of two; the widest head
+    (128, 8, 3000, 0, "half", 2.0 ** 64, 31),                                     # a share's heads more than are on their way at a time
+    (128, 2, 70, 1, "half", 1e4, 17), (24, 4, 70, 0, "half", 1e4, 17),            # an address, a head that whole pieces do not fit
+    (64, 2, 70, 0, "interleaved", 0.9, 17),                                       # angles above the positions
+])
+def test_whole_pieces_and_what_they_do_not_fit_bf16(d, H, T, offset, pairing, base, bits):
+    """Scattered positions, token-major and heads-major.  The kernel's sine and cosine are within 1e-15, and only a value within that of a
+    rounding boundary can come out otherwise: no entry of these may.  Positions of all 31 bits come with frequencies that are powers of two:
+    another base's differ from the oracle's by 2^-53 where two libraries' powers do, and angles of 2^31 then by 2e-7, which moves one
+    entry in 10^4 to 10^5."""
+    rng = np.random.default_rng(d * H + T)
+    x = ko.bf16_round(rng.standard_normal((T, H * d)).astype(np.float32))
+    pos = rng.integers(0, 2 ** bits - 1, size=T).astype(np.int32)
+    pos[:2] = (2 ** bits - 1, 0)[:T]
+    pos_dev = torch.from_numpy(pos).to(DEV)
+    for inverse in (False, True):
+        want = _bf16_bits(ko.bf16_round(kr.rope(x, pos, H, d, base=base, pairing=pairing, inverse=inverse)).astype(np.float32))
+        for heads_major in (False, True):
+            src = kr.heads_first(x, H, d) if heads_major else x
+            room = torch.zeros(offset + src.size, dtype=torch.bfloat16, device=DEV)
+            xd = room[offset:]
+            xd.copy_(_to_dev_bf16(np.ascontiguousarray(src)).reshape(-1))
+            ts, hs = (d, T * d) if heads_major else (H * d, d)
+            kv.kvtc_rope(xd, kv.KVTC_BF16, T, H, d, ts, hs, pos_dev, 0, base, kv.ROPE_HALF if pairing == "half" else kv.ROPE_INTERLEAVED, inverse)
+            torch.cuda.synchronize()
+            got = _from_dev_bf16(xd).reshape(src.shape)
+            got = kr.tokens_first(got) if heads_major else got
+            assert np.array_equal(_bf16_bits(got), want), (inverse, heads_major, (_bf16_bits(got) != want).mean())
