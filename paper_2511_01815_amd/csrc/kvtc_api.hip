@@ -20,6 +20,9 @@ hipError_t launch_encode(const KernelArgs& a, kvtc_dtype dtype, int key, int gri
 hipError_t launch_decode(const KernelArgs& a, kvtc_dtype dtype, int key, int grid, size_t lds_bytes, hipStream_t stream);
 hipError_t launch_encode_short(const KernelArgs& a, kvtc_dtype dtype, int ntw, int waves, int grid, size_t lds_bytes, hipStream_t stream);
 int encode_lds_bytes(int ntw, int wc, int nw, int n_groups, int rec_dwords, kvtc_dtype dtype);
+hipError_t launch_encode_parts(const KernelArgs& a, kvtc_dtype dtype, int waves, int grid, size_t lds_bytes, hipStream_t stream);
+int encode_part_waves_most();
+int encode_part_lds_bytes(int p, int ntp, int n_groups, int rec_dwords, kvtc_dtype dtype);
 int encode_short_ntw(int ntp);
 int encode_short_waves(int ntp);
 int encode_short_lds_bytes(int ntp, int n_groups, int rec_dwords, kvtc_dtype dtype);
@@ -56,6 +59,19 @@ struct kvtc_plan {
     size_t record_bytes;
     int enc_s_waves;        // short-job encode kernel (h.enc_short, 0 = none): waves per workgroup ...
     int enc_s_lds[2];       // ... and dynamic LDS bytes per element dtype
+    int enc_p_waves;        // the same by parts (h.enc_parts, 0 = none)
+    int enc_p_lds[2];       // 0: not of this type
+};
+
+// The encode by parts of a set of plans; split = 0: some plan's groups cannot be shared out so.
+struct PartVariant {
+    int split = -1, waves = 0, lds = 0;                 // workgroups to a tile, waves, LDS bytes: the most of any plan.  (-1: no plan yet)
+    void add(const kvtc_plan& plan, kvtc_dtype dtype) {
+        const bool can = split != 0 && plan.h.enc_parts != 0 && plan.enc_p_lds[dtype] != 0;
+        split = can ? std::max(split, plan.h.enc_parts) : 0;
+        waves = std::max(waves, plan.enc_p_waves);
+        lds = std::max(lds, plan.enc_p_lds[dtype]);
+    }
 };
 
 struct kvtc_batch {
@@ -67,6 +83,7 @@ struct kvtc_batch {
     struct DecVariant { int key, wgs, rec, ring, rec_dwords, least_tiles; uint64_t bases; };
     std::vector<EncVariant> enc;
     struct ShortVariant { int waves, lds[2]; } enc_short[3];     // short-job kernels by coordinate tiles per wave; waves = 0: no plan uses it
+    PartVariant enc_part[2];                            // by parts, per element dtype
     std::vector<DecVariant> dec;
     int max_p;
     int min_rec_dwords;                                 // the shortest record among the plans
@@ -109,6 +126,52 @@ int short_table_grid(size_t cap, int min_rec_dwords, int n_jobs, bool pairs) {
     const size_t tiles = cap / ((size_t)min_rec_dwords * 4 * kEncShortTile) + (size_t)n_jobs;
     const size_t grid = (tiles + 7) / 8 * 8 + 1;                     // whole shares for the eight XCDs
     return n_jobs <= kShortTableJobs && grid <= (size_t)compute_units() * (pairs ? 2 : 1) ? (int)grid : 0;
+}
+
+// Workgroups by parts that run at once: two to a compute unit of four waves whose LDS allows it.
+int part_places(int waves, int lds) { return compute_units() * (waves <= 4 && 2 * lds <= kLdsBudget ? 2 : 1); }
+
+// The grid of a batch's one launch by parts, or 0.  The jobs' lengths are on the device; jobs of the length that the stream buffer has room for must all run
+// at once -- with tiles of up to 32 tokens, which the short-job kernel also codes in half the time, in five workgroups to four compute units.  (Tiles beyond that wait
+// for a workgroup.  64 tensors at 16x, four parts, us, against the short-job launch: room for 64 tokens each, 16 coded, 256 workgroups, 9.8 and 13.3; 33 to 64, 512
+// workgroups, 13.8 and 16.7; of 100, 1024 workgroups, 22.9 and 17.4.  90 of 31, 360 workgroups, 15.6 and 15.1; of 33, 720, 20.0 and 17.7; 12 of 340, 528, 17.9 and 14.4.)
+int short_part_grid(size_t cap, int min_rec_dwords, int n_jobs, int split, int places) {
+    const size_t each = (cap / ((size_t)min_rec_dwords * 4) + n_jobs - 1) / n_jobs, groups = (each + kEncPartTile - 1) / kEncPartTile * n_jobs * split;
+    const size_t most = each > kEncPartTile ? places : std::min(places, compute_units() * 5 / 4);
+    return n_jobs <= kShortTableJobs && groups <= most ? (int)((groups + 7) / 8 * 8 + 1) : 0;
+}
+
+// Shares out a plan's groups, in order, over up to kEncParts workgroups so that the largest share has as few coordinate tiles as can be, with as few
+// shares as that takes; returns the waves that takes, a coordinate tile to a wave, and at least four, or leaves enc_parts 0 where those are too many.
+int share_groups(PlanDev* d, const kvtc_group* groups) {
+    const int n = d->n_groups;
+    std::vector<int> first(n + 1, 0), half(n + 1, 2 * n);           // a group's first block; the first halfword of its codes
+    for (int g = 0; g < n; ++g) {
+        first[g + 1] = first[g] + groups[g].n / 16;
+        half[g + 1] = half[g] + groups[g].n / 16 * groups[g].bits;
+    }
+    auto tiles = [&](int g0, int g1) { return (first[g1] + 1) / 2 - first[g0] / 2; };
+    // the fewest shares, in order, of at most `most` tiles each; their ends -> cut
+    auto shares = [&](int most, int* cut) {
+        int k = 0;
+        for (int g0 = 0; g0 < n; ++k) {
+            int g1 = g0;
+            while (g1 < n && tiles(g0, g1 + 1) <= most) ++g1;
+            if (g1 == g0 || k == kEncParts) return kEncParts + 1;
+            cut[k] = g0 = g1;
+        }
+        return k;
+    };
+    int cut[kEncParts], k = kEncParts + 1, most = 0;
+    while (most < encode_part_waves_most() && k > kEncParts) k = shares(++most, cut);
+    if (k > kEncParts) return 0;
+    d->enc_parts = k;
+    for (int i = 0; i < k; ++i) {
+        const int g0 = i ? cut[i - 1] : 0, g1 = cut[i];
+        d->enc_part[2 * i] = (uint32_t)g0 | (uint32_t)g1 << 8 | (uint32_t)(first[g0] / 2) << 16 | (uint32_t)((first[g1] + 1) / 2) << 24;
+        d->enc_part[2 * i + 1] = (uint32_t)half[g0] | (uint32_t)(g1 == n ? 2 * d->rec_dwords : half[g1]) << 16;
+    }
+    return most < 4 ? 4 : most;
 }
 
 // Row pitch limit (elements): the kernels address a workgroup tile of up to 256 rows with 32-bit byte offsets.
@@ -355,6 +418,13 @@ static kvtc_status plan_create_impl(kvtc_plan** out, int p, int r, const float* 
         if (s_lds[0] > kLdsBudget || s_lds[1] > kLdsBudget) d.enc_short = 0;
     }
 
+    const int p_waves = share_groups(&d, groups_host);
+    int p_lds[2] = {0, 0};
+    if (d.enc_parts != 0) {
+        p_lds[KVTC_BF16] = encode_part_lds_bytes(p, ntp, n_groups, d.rec_dwords, KVTC_BF16);
+        p_lds[KVTC_F32] = encode_part_lds_bytes(p, ntp, n_groups, d.rec_dwords, KVTC_F32);
+    }
+
     // ---- host images ---------------------------------------------------------------
     const size_t n_venc = (size_t)(p / 16) * ntp * 64 * 8;      // bf16 elements
     const int stage_u4 = decode_stage_u4(d.dec_nct);              // fragments of a 32-feature tile, then its mu entries
@@ -462,6 +532,9 @@ static kvtc_status plan_create_impl(kvtc_plan** out, int p, int r, const float* 
     pl->enc_s_waves = s_waves;
     pl->enc_s_lds[0] = s_lds[0];
     pl->enc_s_lds[1] = s_lds[1];
+    pl->enc_p_waves = p_waves;
+    pl->enc_p_lds[0] = p_lds[0];
+    pl->enc_p_lds[1] = p_lds[1];
     *out = pl;
     return KVTC_OK;
 }
@@ -611,7 +684,15 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
     // A tensor short enough for all its 64-token tiles to run at once (one wave of workgroups) runs the short-job kernel.
     const int64_t tiles_short = (n_tokens + kEncShortTile - 1) / kEncShortTile;
     hipError_t e;
-    if (plan->h.enc_short != 0 && tiles_short <= short_tiles_per_job(1, short_pairs(plan->h.enc_short, plan->enc_s_waves, plan->enc_s_lds[dtype]))) {
+    // One shorter still, up to a workgroup for every compute unit, or, where two share one, half as many again, has its tiles' groups shared out as well.  (Tensors of
+    // 48, 2700 and 4000 tokens at 16x, us: 12.9, 13.6 and 13.7 on the short-job kernel, 7.8, 8.9 and 12.1 so; of 5400 13.9 and 13.5, at 20x 13.1 and 13.3; fp32 of 4000, one
+    // workgroup to a compute unit, 16.3 and 20.8.)
+    const int64_t tiles_part = (n_tokens + kEncPartTile - 1) / kEncPartTile;
+    if (plan->h.enc_parts != 0 && plan->enc_p_lds[dtype] != 0 &&
+        2 * tiles_part * plan->h.enc_parts <= part_places(plan->enc_p_waves, plan->enc_p_lds[dtype]) + compute_units()) {
+        a.enc_split = plan->h.enc_parts;
+        e = launch_encode_parts(a, dtype, plan->enc_p_waves, (int)tiles_part * plan->h.enc_parts, (size_t)plan->enc_p_lds[dtype], static_cast<hipStream_t>(stream));
+    } else if (plan->h.enc_short != 0 && tiles_short <= short_tiles_per_job(1, short_pairs(plan->h.enc_short, plan->enc_s_waves, plan->enc_s_lds[dtype]))) {
         e = launch_encode_short(a, dtype, plan->h.enc_short, plan->enc_s_waves, (int)tiles_short, (size_t)plan->enc_s_lds[dtype], static_cast<hipStream_t>(stream));
     } else {
         const int64_t tiles = (n_tokens + plan->h.enc_tok_wg - 1) / plan->h.enc_tok_wg;
@@ -711,6 +792,7 @@ kvtc_status kvtc_batch_create(kvtc_batch** out, const kvtc_plan* const* plans, i
         const PlanDev& ph = plans[i]->h;
         b->min_rec_dwords = std::min(b->min_rec_dwords, ph.rec_dwords);
         b->all_short = b->all_short && ph.enc_short != 0;
+        for (const kvtc_dtype dt : {KVTC_BF16, KVTC_F32}) b->enc_part[dt].add(*plans[i], dt);
         {
             const int key = ph.enc_nw * 10000 + ph.enc_wc * 100 + ph.enc_ntw;
             kvtc_batch::EncVariant* v = nullptr;
@@ -884,6 +966,7 @@ struct EncodeLaunches {
     struct Bulk { int key, wgs, lds; } bulk[16];        // (a variant per row of the plans' table)
     int n_bulk;
     struct Short { int waves, lds; } shrt[3];            // by coordinate tiles per wave; waves = 0: none
+    PartVariant part;
     bool all_short;
     int min_rec_dwords, max_p;
     bool lines;                                          // the feature array lies on whole cache lines
@@ -892,8 +975,14 @@ struct EncodeLaunches {
 static kvtc_status launch_encode_jobs(const char* who, const EncodeLaunches& l, KernelArgs& a, kvtc_dtype dtype, hipStream_t st) {
     const bool pairs = l.shrt[2].waves == 0 && short_pairs(1, l.shrt[1].waves, l.shrt[1].lds);
     const int grid = l.all_short ? short_table_grid(a.cap, l.min_rec_dwords, a.n_jobs, pairs) : 0;
+    const int part_grid = l.part.split > 0 ? short_part_grid(a.cap, l.min_rec_dwords, a.n_jobs, l.part.split, part_places(l.part.waves, l.part.lds)) : 0;
     hipError_t e = hipSuccess;
-    if (grid != 0) {
+    if (part_grid != 0) {
+        a.enc_table = 1;
+        a.enc_split = l.part.split;
+        a.enc_max_tokens = (int32_t)(a.cap / ((size_t)l.min_rec_dwords * 4));
+        e = launch_encode_parts(a, dtype, l.part.waves, part_grid, (size_t)l.part.lds, st);
+    } else if (grid != 0) {
         // few tokens in all: one round of the short-job kernel
         a.enc_table = 1;
         a.enc_max_tokens = (int32_t)(a.cap / ((size_t)l.min_rec_dwords * 4));
@@ -969,6 +1058,7 @@ kvtc_status kvtc_encode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
     l.all_short = batch->all_short;
     l.min_rec_dwords = batch->min_rec_dwords;
     l.max_p = batch->max_p;
+    l.part = batch->enc_part[dtype];
     l.lines = whole_lines(x_base_dev, dtype, xl);
     for (int ntw = 1; ntw <= 2; ++ntw) l.shrt[ntw] = {batch->enc_short[ntw].waves, batch->enc_short[ntw].lds[dtype]};
     for (const auto& v : batch->enc) l.bulk[l.n_bulk++] = {v.key, v.wgs, v.lds[dtype]};
@@ -1012,6 +1102,7 @@ kvtc_status kvtc_encode_batch_static(const kvtc_plan* const* plans, int n_plans,
         l.min_rec_dwords = std::min(l.min_rec_dwords, ph.rec_dwords);
         l.max_p = std::max(l.max_p, ph.p);
         l.all_short = l.all_short && ph.enc_short != 0;
+        l.part.add(*plans[i], dtype);
         if (ph.enc_short != 0) {
             auto& v = l.shrt[ph.enc_short];
             v.waves = std::max(v.waves, plans[i]->enc_s_waves);

@@ -18,6 +18,8 @@ constexpr int kLdsBudget = 160 * 1024; // gfx950 LDS per workgroup
 constexpr int kJobTableBytes = (kMaxJobs + 1) * 4;
 constexpr int kEncShortTile = 64;      // tokens per workgroup tile of the encode kernel for short jobs
 constexpr int kShortTableJobs = 512;   // jobs of a batch that the short-job kernel codes alone, at most
+constexpr int kEncPartTile = 32;       // tokens per workgroup tile of the encode by parts
+constexpr int kEncParts = 4;           // workgroups that share the groups of a tile of a few tokens, at most
 constexpr int kDecShortTile = 128;     // the same for decode (one token tile per wave)
 
 // Lets a kernel use the whole LDS of a compute unit as dynamic shared memory.  The attribute
@@ -62,13 +64,14 @@ struct PlanDev {
     int32_t code_bits_max;                  // widest code of the plan
     int32_t enc_wgs, dec_wgs;               // workgroups per compute unit the variant is built for (1..3)
     int32_t enc_nw, enc_short;              // encode: waves per workgroup (4 or 8); coordinate tiles per wave of the kernel for short jobs (64-token tiles), 0 = none
-    int32_t dec_cls, reserved0;             // decode: the kernel class that serves the plan = the widest plan of the class, in coordinate tiles (dec_nct: the width the plan runs at, one of those built for the class)
+    int32_t dec_cls, enc_parts;             // decode: the kernel class that serves the plan = the widest plan of the class, in coordinate tiles (dec_nct: the width the plan runs at, one of those built for the class); encode: shares of whole groups that workgroups of their own can code, 0 = none
     const uint4* v_enc;    // [p/16][32*ntp/32][64] MFMA A fragments of V_kept^T (encode)
     const uint4* v_dec;    // [p/32][2*nct*64 + 16] MFMA B fragments of V_kept^T (decode), then the tile's 32 mu entries; tiles 2k, 2k+1 = even, odd features of span k
     const float* negc;     // [32*ntp]  -(mu^T V_kept), zero in the padding
     const float* mu;       // [p]
     const uint32_t* blk;   // [64] per 16-coordinate block: bits | group << 8 | halfword offset << 16; 0 = padding
     const uint32_t* grp;   // [n_groups] first block | n blocks << 8 | bits << 16
+    uint32_t enc_part[2 * kEncParts];       // of each: first group | last + 1 << 8 | first coordinate tile << 16 | last + 1 << 24; first halfword of its codes | last + 1 << 16
 };
 
 struct KernelArgs {
@@ -90,6 +93,7 @@ struct KernelArgs {
     uint32_t dec_ring_off;     // decode: byte offset of the basis ring in the work area; 0 = it shares the record image's space
     int32_t enc_short_max;     // encode: jobs of at most this many tokens whose plan the short-job kernel serves may be left to it (bulk_takes_all); 0 = no job counts as short
     int32_t enc_table;         // encode of a batch: 1 = the short-job launch codes every job (short_table); 0 = it codes the short ones, a workgroup per job and tile
+    int32_t enc_split;         // encode by parts: workgroups to a tile (the most of any plan; of one tensor, its plan's)
     int32_t enc_max_tokens;    // with enc_table: a job of more tokens cannot lie inside the stream buffer
     int32_t enc_cus;           // encode of a batch: compute units (a bulk launch has this many workgroups times its plans' enc_wgs)
     int32_t dec_short;         // decode: this launch runs the one-token-tile-per-wave variant of every plan (128-token tiles)

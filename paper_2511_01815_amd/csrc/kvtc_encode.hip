@@ -175,9 +175,16 @@ __host__ __device__ constexpr int enc_aux_bytes(int ntp) { return 512 + ntp * 32
 // token) to records in the stream.  Every wave of the workgroup calls it: ct0 = the wave's first coordinate tile, n_ct = how many it has (NTW or one
 // fewer; HELPERS: any number, a wave with none only helps with the headers and the copy), tt0 = its first of TT token tiles;
 // tok_n tokens of the images' pitch tok_wg are worked on.  LDS: the plan's tables at `work`, the images at `smem`.
-template <int NTW, int TT, bool HELPERS>
+// PART: of the groups and record bytes, those of `part` only.
+struct EncPart {
+    int g0, g1, ct0, ct1, hw0, hw1;         // groups, coordinate tiles, halfwords of codes: first and last + 1
+    __device__ __forceinline__ EncPart(uint32_t a, uint32_t b)
+        : g0((int)(a & 0xffu)), g1((int)((a >> 8) & 0xffu)), ct0((int)((a >> 16) & 0xffu)), ct1((int)(a >> 24)), hw0((int)(b & 0xffffu)), hw1((int)(b >> 16)) {}
+};
+template <int NTW, int TT, bool HELPERS, bool PART = false>
 __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], int ct0, int n_ct, int tt0, int tok_n, int tok_wg, int ntp, int nth,
-                                                const PlanEnc& P, const TileRef& tr, const KernelArgs& a, int tok_tile0, uint4* work, uint4* smem) {
+                                                const PlanEnc& P, const TileRef& tr, const KernelArgs& a, int tok_tile0, uint4* work, uint4* smem,
+                                                const EncPart& part = EncPart(0u, 0u)) {
     // (through an empty asm, so that nothing of the epilogue's lane addresses is worked out ahead of the main loop and kept
     // through it: its registers are all taken)
     int tid = (int)threadIdx.x;
@@ -218,8 +225,9 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
     __syncthreads();
 
     // B: one header per (token, group)
-    for (int item = tid; item < tok_n * G; item += nth) {
-        const int tw = item % tok_n, g = item / tok_n;
+    const int g_first = PART ? part.g0 : 0, g_last = PART ? part.g1 : G;
+    for (int item = tid; item < tok_n * (g_last - g_first); item += nth) {
+        const int tw = item % tok_n, g = item / tok_n + g_first;
         const uint32_t gi = grp_t[g];
         const int b0 = gi & 0xff, nb = (gi >> 8) & 0xff, bits = (gi >> 16) & 0xff;
         float lo = __builtin_inff(), hi = -__builtin_inff();
@@ -237,7 +245,7 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
         gq[g * tok_wg + tw] = make_float2(q.shift, __builtin_ldexpf(q.inv, -bits));      // exact
         rec[tw * rstride + g] = (uint32_t)q.shift16 | ((uint32_t)q.scale16 << 16);
         if (__builtin_expect(q.scale16 == 0x7bffu, 0)) *saturated = 1u;
-        if (g == 0 && narrow_codes) rec[tw * rstride + rd - 1] = 0u;      // the padding behind the last block
+        if (g == g_first && narrow_codes) rec[tw * rstride + rd - 1] = 0u;      // the padding behind the last block
     }
     __syncthreads();
 
@@ -248,7 +256,7 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
         for (int ct = 0; ct < NTW; ++ct) {
             if (ct >= (HELPERS ? 0 : NTW - 1) && ct >= n_ct) continue;
             const uint32_t info = blk_t[2 * (ct0 + ct) + h];
-            const uint32_t bits = info & 0xffu;
+            const uint32_t bits = PART && ((int)((info >> 8) & 0xffu) < part.g0 || (int)((info >> 8) & 0xffu) >= part.g1) ? 0u : info & 0xffu;
             const uint32_t bits0 = (uint32_t)__builtin_amdgcn_readlane((int)bits, 0), bits1 = (uint32_t)__builtin_amdgcn_readlane((int)bits, 32);
             if ((bits0 | bits1) == 0u) continue;
             const uint32_t g = (info >> 8) & 0xffu;
@@ -315,7 +323,18 @@ __device__ __forceinline__ void encode_epilogue(const f32x16 (&acc)[TT][NTW], in
                         (size_t)tok_tile0 * rd;
         const uint32_t magic = 0xffffffffu / (uint32_t)rd + 1u;     // exact floor(i / rd) for i < 2^20
         const int total = n_valid * rd;
-        if ((rd & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15u) == 0u) {
+        if constexpr (PART) {
+            // the headers, then the dwords that hold the part's codes: a first or last one that it shares by its half
+            const int n_head = part.g1 - part.g0, d0 = part.hw0 / 2, per = n_head + (part.hw1 + 1) / 2 - d0;
+            for (int i = tid; i < n_valid * per; i += nth) {
+                const int t = i / per, k = i - t * per, d = k < n_head ? part.g0 + k : d0 + k - n_head;
+                const uint32_t w = rec[t * rstride + d];
+                uint32_t* to = out + (size_t)t * rd + d;
+                const bool low = k < n_head || 2 * d >= part.hw0, high = k < n_head || 2 * d + 1 < part.hw1;
+                if (low && high) *to = w;
+                else reinterpret_cast<uint16_t*>(to)[low ? 0 : 1] = (uint16_t)(low ? w : w >> 16);
+            }
+        } else if ((rd & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15u) == 0u) {
             for (int i = 4 * tid; i < total; i += 4 * nth) {
                 const uint32_t t = __umulhi((uint32_t)i, magic);
                 const uint32_t* src = rec + t * rstride + ((uint32_t)i - t * rd);
@@ -734,6 +753,99 @@ __device__ __forceinline__ void encode_register_tile(const PlanEnc& P, const Til
     encode_epilogue<NTW, TT, !BULK>(acc, ct0, n_ct, 0, ROWS, TOK, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem);
 }
 
+// A share of the groups of a tile of 32 tokens.  A launch of a few tiles is bound by what one compute unit can draw (half a megabyte of basis at 256 coordinates, and
+// X) and by the round trips it takes to do that.  Groups are quantised each for themselves and own their bytes of a record, so where there are compute
+// units enough, workgroups of their own code a tile's groups, a coordinate tile to a wave, and each draws a share of the basis; all of X, which is small, is asked for at
+// once, so that the main loop has no barrier, and AHEAD k-steps of fragments.  Sums and roundings are the bulk kernels', and so are the bits.  One tensor of 48
+// tokens, 240 coordinates: 12.9 us as a tile of 64 tokens of the short-job kernel, 12.3 in three shares of that tile, 7.8 so; of 528 coordinates 20.3 and 9.9; an
+// append step of 64 tensors with 16 tokens each 13.3 and 9.7 (10.3 in up to three shares, for four).
+template <typename XT, int AHEAD>
+__device__ __forceinline__ void encode_part_tile(const PlanEnc& P, const EncPart& part, const TileRef& tr, const KernelArgs& a, uint4* work) {
+    constexpr int FEAT = short_feat<XT>(), STEPS = FEAT / 16;
+    constexpr int EB = (int)sizeof(XT), ROW_B = FEAT * EB, COLS = ROW_B / 16, ROWS_DMA = 1024 / ROW_B;
+    constexpr int ROWS = kEncPartTile, CHUNK_B = ROWS * ROW_B;
+    static_assert(AHEAD % STEPS == 0, "a chunk's fragments are in registers known at compile time");
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = (int)blockDim.x >> 6;
+    const int l32 = lane & 31, h = lane >> 5;
+    const int ntp = P.enc_ntw * P.enc_wc;
+    const int p = P.p, T = tr.n_tokens, tok_tile0 = tr.tile * kEncPartTile, n_valid = min(T - tok_tile0, ROWS);
+    const int n_steps = p / 16, n_chunks = (p + FEAT - 1) / FEAT;
+    const int ct0 = min(part.ct0 + wave, part.ct1 - 1), n_ct = part.ct0 + wave < part.ct1 ? 1 : 0;      // (a wave without a tile only helps)
+    uint4* smem = work + enc_aux_bytes(ntp) / 16;
+    {
+        const uint32_t aux = lds_offset(work);
+        if (wave == 0) dma4_async(P.blk, (uint32_t)lane * 4u, aux + kEncBlkOff);
+        if (wave == 1) dma4_async(P.grp, (uint32_t)lane * 4u, aux + kEncGrpOff);
+        for (int w = wave; w * 64 < ntp * 8; w += n_waves)
+            if (w * 64 + lane < ntp * 8) dma16_async(P.negc, (uint32_t)(w * 64 + lane) * 16u, aux + kEncNegcOff + (uint32_t)w * 1024u);
+    }
+    const uint32_t lds_x = lds_offset(smem);
+    for (int i = wave; i < n_chunks * (ROWS / ROWS_DMA); i += n_waves) {
+        const int c = i / (ROWS / ROWS_DMA), row = i % (ROWS / ROWS_DMA) * ROWS_DMA + lane / COLS;
+        const int col = (lane % COLS) ^ (row & 7);                   // (permuted as in encode_register_tile)
+        int f = c * FEAT + col * (16 / EB);
+        f = f < p ? f : 0;                                           // behind the last feature: read something, it is not used
+        if (i % (ROWS / ROWS_DMA) * ROWS_DMA >= n_valid) continue;   // (rows past the end are whatever the LDS holds: nothing of theirs is used)
+        const int t = min(tok_tile0 + row, T - 1);
+        const char* src = reinterpret_cast<const char*>(a.x) + ((tr.x_row0 + t) * a.ld_x + f) * EB + (a.x_blk_log2 ? (int64_t)(f >> a.x_blk_log2) * a.x_blk_jump * EB : (int64_t)0);
+        dma16_async(src, __builtin_amdgcn_readfirstlane(lds_x + (uint32_t)(i * 1024)));
+    }
+    u32x4 af[AHEAD];
+    typedef const char __attribute__((address_space(1))) * global_ptr;
+    typedef const u32x4 __attribute__((address_space(1))) * global_u4;
+    const uint64_t vg = (uint64_t)uniform_ptr(P.v_enc + ct0 * 64);
+    auto fetch = [&](int step, int slot) {
+        const global_ptr src = (global_ptr)(vg + (uint64_t)(uint32_t)min(step, n_steps - 1) * (uint64_t)(uint32_t)(ntp * 1024));      // a scalar address
+        af[slot] = *(global_u4)(src + (uint32_t)(lane * 16));
+    };
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) fetch(k, k);
+    asm volatile("" ::: "memory");
+    wait_vmem<AHEAD>();                                              // everything older than the fragments has landed
+    __syncthreads();
+
+    f32x16 acc[1][1];
+    {
+        const float* negc = reinterpret_cast<const float*>(work) + kEncNegcOff / 4 + ct0 * 32 + 16 * h;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[0][0][q] = negc[q];
+    }
+    auto xfrag = [&](const char* x, int ks) {
+        const char* r = x + l32 * ROW_B;
+        if constexpr (EB == 2) {
+            return as_bf16x8(*reinterpret_cast<const uint4*>(r + (((2 * ks + h) ^ (l32 & 7)) * 16)));
+        } else {
+            const float4 u = *reinterpret_cast<const float4*>(r + (((4 * ks + 2 * h) ^ (l32 & 7)) * 16));
+            const float4 w = *reinterpret_cast<const float4*>(r + (((4 * ks + 2 * h + 1) ^ (l32 & 7)) * 16));
+            bf16x8 v;                                                // round to bf16, nearest even
+            v[0] = (__bf16)u.x; v[1] = (__bf16)u.y; v[2] = (__bf16)u.z; v[3] = (__bf16)u.w;
+            v[4] = (__bf16)w.x; v[5] = (__bf16)w.y; v[6] = (__bf16)w.z; v[7] = (__bf16)w.w;
+            return v;
+        }
+    };
+    const char* x = reinterpret_cast<const char*>(smem);
+    for (int s0 = 0; s0 < n_steps; s0 += AHEAD) {
+#pragma unroll
+        for (int g = 0; g < AHEAD / 4; ++g) {                        // (features come in multiples of 64: four k-steps)
+            if (s0 + 4 * g >= n_steps) continue;
+            const char* xc = x + (s0 / STEPS + 4 * g / STEPS) * CHUNK_B;
+            bf16x8 xv[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) xv[k] = xfrag(xc, (4 * g + k) % STEPS);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[4 * g + k]), xv[k], acc[0][0], 0, 0, 0);
+                fetch(s0 + 4 * g + k + AHEAD, 4 * g + k);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    wait_vmem<0>();                                                  // the fragments fetched past the end
+    __syncthreads();
+    encode_epilogue<1, 1, true, true>(acc, ct0, n_ct, 0, n_valid, ROWS, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem, part);
+}
+
 // the lane's number, worked out where it is used and not kept through a loop
 __device__ __forceinline__ uint32_t lane_id() {
     uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
@@ -750,7 +862,7 @@ __device__ __forceinline__ uint32_t lane_id() {
 // KEEP: the lane's number, and with it the addresses of its jobs, may be kept through the loop over tiles.  In fp32 there are no registers for them:
 // with them, and with `upto` left as it is for rounds that a list does not have, up to 18 went to scratch memory, four of them inside the loop over
 // chunks.  (12000 tokens, us, kept and not: fp32, 240 coordinates 22.2 and 19.5; bf16, 160 coordinates, six waves, 13.4 and 15.4.)
-template <bool KEEP>
+template <bool KEEP, int TILE = kEncShortTile>
 struct ShortTable {
     uint32_t tiles[kShortTableJobs / 64], upto[kShortTableJobs / 64];       // of the lane's job in each round: its tiles; those of the jobs up to it
     uint32_t total;
@@ -762,7 +874,7 @@ struct ShortTable {
             tiles[k] = upto[k] = 0u;
             if (64 * k < a.n_jobs && j < (uint32_t)a.n_jobs) {
                 const int n = a.jobs[j].n_tokens;                    // (what else is wrong with a job is seen at its tiles)
-                tiles[k] = n > 0 && n <= a.enc_max_tokens ? (uint32_t)(n + kEncShortTile - 1) / kEncShortTile : 0u;
+                tiles[k] = n > 0 && n <= a.enc_max_tokens ? (uint32_t)(n + TILE - 1) / TILE : 0u;
             }
         }
         total = 0u;
@@ -808,7 +920,7 @@ __device__ inline void report_bad_job(const KernelArgs& a) {
 // Workgroup `number`'s tile of one tensor or of short jobs, or, TABLE, the tile that tr names; false: none for this kernel.
 // A job that is not short, not of this kernel's plans or not valid is left alone (the bulk launches in front of this one, or the last
 // workgroup, report it).
-template <int NTW, bool TABLE>
+template <int NTW, bool TABLE, int TILE = kEncShortTile>
 __device__ __forceinline__ bool short_tile(const KernelArgs& a, uint32_t number, TileRef& tr, PlanEnc& P) {
     if constexpr (!TABLE) tr = TileRef{0, a.single.plan, a.single.n_tokens, a.single.x_row0, 0ull, (int32_t)number};
     if (TABLE || a.jobs) {
@@ -822,10 +934,10 @@ __device__ __forceinline__ bool short_tile(const KernelArgs& a, uint32_t number,
         tr.n_tokens = (int32_t)v.four[1];
         tr.x_row0 = (int64_t)(((uint64_t)v.four[3] << 32) | v.four[2]);
         tr.offset = ((uint64_t)v.two[1] << 32) | v.two[0];
-        if (tr.plan < 0 || tr.plan >= a.n_plans || tr.n_tokens <= tr.tile * kEncShortTile || (!TABLE && tr.n_tokens > a.enc_short_max)) return false;
+        if (tr.plan < 0 || tr.plan >= a.n_plans || tr.n_tokens <= tr.tile * TILE || (!TABLE && tr.n_tokens > a.enc_short_max)) return false;
     }
     P = load_plan_enc<true>(a.plans + tr.plan);
-    if (P.enc_short != NTW) return false;
+    if (NTW != 0 && P.enc_short != NTW) return false;
     if (TABLE || a.jobs) {
         // (one branch for the wave, which only this tells the compiler: as a choice per lane it cost the main loop of the wide form 3 %)
         if (!TABLE && __builtin_expect(tr.n_tokens > kEncShortTile, 0) &&
@@ -878,6 +990,43 @@ __global__ void KVTC_SHORT_BOUNDS(NTW) kvtc_encode_small_batch_kernel(const Kern
     }
 }
 
+// The same by parts: a.enc_split workgroups to a tile, each a share of its plan's groups.
+template <typename XT, int AHEAD>
+__device__ __forceinline__ void part_code(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, int part, uint4* smem) {
+    const PlanDev __attribute__((address_space(4)))* pd = (const PlanDev __attribute__((address_space(4)))*)(uintptr_t)uniform_ptr(a.plans + tr.plan);
+    if (part >= pd->enc_parts) return;
+    const EncPart ep(pd->enc_part[2 * part], pd->enc_part[2 * part + 1]);
+    encode_part_tile<XT, AHEAD>(P, ep, tr, a, smem);
+}
+// (with up to four waves a SIMD's registers are one wave's, and 32 k-steps of fragments, twice as many, are on their way)
+constexpr int kPartThreads = 640;
+template <typename XT, int AHEAD>
+__global__ void __launch_bounds__(AHEAD == 32 ? 256 : kPartThreads) kvtc_encode_parts_kernel(const KernelArgs a) {
+    extern __shared__ uint4 smem[];
+    const TileRef tr{0, a.single.plan, a.single.n_tokens, a.single.x_row0, 0ull, (int32_t)(blockIdx.x / (uint32_t)a.enc_split)};
+    const PlanEnc P = load_plan_enc<true>(a.plans + tr.plan);
+    part_code<XT, AHEAD>(P, tr, a, (int)(blockIdx.x % (uint32_t)a.enc_split), smem);
+}
+template <typename XT, int AHEAD>
+__global__ void __launch_bounds__(AHEAD == 32 ? 256 : kPartThreads) kvtc_encode_small_batch_parts_kernel(const KernelArgs a) {
+    extern __shared__ uint4 smem[];
+    if (blockIdx.x + 1u == gridDim.x) {
+        if (threadIdx.x < 64) report_bad_job(a);
+        return;
+    }
+    const uint32_t split = (uint32_t)a.enc_split;
+    for (uint32_t i = blockIdx.x / 8u;; i += (gridDim.x - 1u) / 8u) {
+        TileRef tr;
+        PlanEnc P;
+        const ShortTable<false, kEncPartTile> t(a);
+        const uint32_t per_xcd = (t.total * split + 7u) / 8u, number = (blockIdx.x & 7u) * per_xcd + i;
+        if (i >= per_xcd || !t.find(a, number / split, tr)) return;
+        const bool last = i + (gridDim.x - 1u) / 8u >= per_xcd;
+        if (short_tile<0, true, kEncPartTile>(a, 0u, tr, P)) part_code<XT, AHEAD>(P, tr, a, (int)(number % split), smem);
+        if (last) return;
+    }
+}
+
 // (waves across coordinates, coordinate tiles per wave, waves per workgroup); no short-job kernel serves the plans of the last two, so
 // these, on 64-token tiles, code jobs of any length
 #define KVTC_ENC_VARIANTS(X)                                                                           \
@@ -919,6 +1068,28 @@ hipError_t launch_encode_short(const KernelArgs& a, kvtc_dtype dtype, int ntw, i
     KernelArgs args = a;
     void* params[] = {&args};
     return hipLaunchKernel(fn, dim3(grid), dim3(64 * waves), params, lds_bytes, stream);
+}
+
+// `grid` workgroups of `waves` waves: a.enc_split for every tile of a tensor or of a batch, as for launch_encode_short
+hipError_t launch_encode_parts(const KernelArgs& a, kvtc_dtype dtype, int waves, int grid, size_t lds_bytes, hipStream_t stream) {
+#define KVTC_X(XT, AHEAD) (a.enc_table ? reinterpret_cast<const void*>(&kvtc_encode_small_batch_parts_kernel<XT, AHEAD>) : reinterpret_cast<const void*>(&kvtc_encode_parts_kernel<XT, AHEAD>))
+    const void* fn = waves <= 4 ? (dtype == KVTC_BF16 ? KVTC_X(uint16_t, 32) : KVTC_X(float, 32)) : (dtype == KVTC_BF16 ? KVTC_X(uint16_t, 16) : KVTC_X(float, 16));
+#undef KVTC_X
+    if (waves < 2 || waves * 64 > kPartThreads || a.enc_split < 1) return hipErrorInvalidValue;
+    hipError_t e = allow_full_lds(fn);
+    if (e != hipSuccess) return e;
+    KernelArgs args = a;
+    void* params[] = {&args};
+    return hipLaunchKernel(fn, dim3(grid), dim3(64 * waves), params, lds_bytes, stream);
+}
+int encode_part_waves_most() { return kPartThreads / 64; }
+// LDS bytes of a tile of a plan of p features, or 0 where X does not fit
+int encode_part_lds_bytes(int p, int ntp, int n_groups, int rec_dwords, kvtc_dtype dtype) {
+    const int feat = dtype == KVTC_BF16 ? short_feat<uint16_t>() : short_feat<float>();
+    const int main_b = (p + feat - 1) / feat * kEncPartTile * 512;
+    const int epi_b = kEncPartTile * (2 * ntp * 8 + n_groups * 8 + (rec_dwords + 1) * 4);
+    const int b = enc_aux_bytes(ntp) + (main_b > epi_b ? main_b : epi_b);
+    return b <= kLdsBudget ? b : 0;
 }
 
 // Coordinate tiles per wave of the short-job kernel for a plan of ntp tiles (0 = none), waves, and LDS bytes.

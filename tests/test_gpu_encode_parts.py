@@ -1,0 +1,60 @@
+"""Small calls whose tiles' groups are shared out over workgroups, against the bulk kernels: the same bits.  Shares that begin and end inside a
+coordinate tile, a dword and a halfword pair of the record, codes of more than 8 bits, many groups, plans of more coordinates than the
+short-job kernel takes, one group alone (one share of ten tiles), groups that are too many tiles (no shares); tiles of 1, 31, 32 and 33
+tokens, a saturated group in a share beside others, appends between regions that must stay as they are."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2511_01815_amd as kv
+from test_gpu_encode_short import bulk_tokens
+from test_gpu_parity import DEV, _gpu_plan, _manual
+
+pytestmark = pytest.mark.gpu
+
+PLANS = {"odd blocks": [(16, 3), (48, 5), (16, 1), (80, 7), (16, 2), (96, 3)], "wide codes": [(16, 16), (48, 9), (64, 12), (16, 1)], "small groups": [(16, 1 + k % 7) for k in range(40)],
+         "wide plan": [(64, 5), (112, 4), (48, 3)] * 4, "one group": [(320, 3)], "too wide a group": [(336, 2), (16, 4)]}
+
+
+@pytest.mark.parametrize("name", sorted(PLANS))
+@pytest.mark.parametrize("p,dtype", [(1024, kv.KVTC_BF16), (320, kv.KVTC_F32), (1088, kv.KVTC_BF16), (1152, kv.KVTC_F32)])
+def test_shares_of_groups_are_coded_as_whole_tiles(name, p, dtype):
+    """1152 features in fp32 are more than the LDS holds of 32 tokens: no shares there either."""
+    groups = PLANS[name]
+    if sum(n for n, _ in groups) > p:
+        pytest.skip("more coordinates than features")
+    plan = _gpu_plan(_manual(p, groups, 5))
+    R, n_bulk = plan.record_bytes, bulk_tokens()
+    gen = torch.Generator(device=DEV).manual_seed(p)
+    x = torch.randn((200, p), generator=gen, device=DEV)
+    x[40] *= 3e4                                                     # scales of 65504: every code is clamped
+    x = x.to(torch.bfloat16 if dtype == kv.KVTC_BF16 else torch.float32)
+    rows = x.repeat(n_bulk // 200 + 1, 1)[:n_bulk]
+    bulk = torch.zeros((n_bulk, R), dtype=torch.uint8, device=DEV)
+    kv.kvtc_encode(plan.handle, rows, dtype, n_bulk, p, bulk, bulk.numel())
+    bulk = bulk[:200]
+    for n in (1, 31, 32, 33, 97):
+        got = torch.full((n * R + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+        kv.kvtc_encode(plan.handle, x, dtype, n, p, got, n * R)
+        torch.cuda.synchronize()
+        assert torch.equal(got[:n * R].view(n, R), bulk[:n]), n
+        assert bool((got[n * R:] == 0xA5).all()), n
+    # appends of 1, 16 and 33 tokens, each between records that a region holds and room that it has left; one without room
+    lens, before = [1, 16, 33, 5], [2, 0, 7, 60]
+    jobs = torch.from_numpy(kv.make_jobs([0] * 4, lens, [3, 30, 100, 0]).view(np.uint8)).to(DEV)
+    region = torch.arange(5, dtype=torch.int64, device=DEV) * (64 * R + 16 - 64 * R % 16)
+    coded = torch.tensor(before, dtype=torch.int64, device=DEV)
+    offs = torch.zeros(5, dtype=torch.int64, device=DEV)
+    out = torch.full((int(region[-1].item()) + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=DEV)
+    batch = kv.Batch([plan])
+    kv.kvtc_offsets_append(batch.handle, jobs, 4, region, coded, offs)
+    kv.kvtc_encode_batch(batch.handle, jobs, 4, x, dtype, p, offs, out, out.numel() - 64, status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 4
+    want = torch.full_like(out, 0xA5)
+    for n, row, b, at in list(zip(lens, [3, 30, 100, 0], before, region.tolist()))[:3]:
+        want[at + b * R:at + (b + n) * R] = bulk[row:row + n].reshape(-1)
+    assert torch.equal(out, want)
+    batch.close()
+    plan.close()
