@@ -108,6 +108,7 @@ struct EntropyArgs {
     const uint32_t* lim;
     const uint8_t* log;
     int32_t R, n_tables;
+    int32_t waves;                    // of a workgroup that take chunks; any others only help to copy its tables
     int32_t chunks_per_wave;          // chunks a wave takes one after the other, so that a workgroup's tables serve several
     int64_t max_tokens;               // the launch covers this many tokens per job; a longer job is left alone
 };
@@ -204,7 +205,7 @@ __device__ __forceinline__ void stage_table(const uint32_t* src, int rows, int l
 // dword and at the token's before it.
 __global__ void __launch_bounds__(1024, 2) entropy_size_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = a.waves;
     const int R = a.R;
     const JobView v = job_view(a, blockIdx.y);
     const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
@@ -214,6 +215,7 @@ __global__ void __launch_bounds__(1024, 2) entropy_size_kernel(const EntropyArgs
     stage_table(reinterpret_cast<const uint32_t*>(a.len + v.table * 256), R, 6, tab32);
     const uint8_t* tab = reinterpret_cast<const uint8_t*>(tab32);
     __syncthreads();
+    if (wave >= n_waves) return;
     for (int c = 0; c < a.chunks_per_wave; ++c) {
         const int64_t chunk = first + (int64_t)c * n_waves + wave;
         if (chunk >= v.n_chunks) break;
@@ -263,33 +265,28 @@ __global__ void __launch_bounds__(1024, 2) entropy_size_kernel(const EntropyArgs
 
 // (2) sizes -> offsets, in place, one workgroup per job; the container's length -> coded_bytes[job] (all ones for a job
 // that was left alone)
-__global__ void __launch_bounds__(256) entropy_scan_kernel(const EntropyArgs a) {
-    __shared__ uint32_t s[256];
-    __shared__ uint32_t carry;
-    const int tid = threadIdx.x;
+__global__ void __launch_bounds__(1024) entropy_scan_kernel(const EntropyArgs a) {
+    __shared__ uint32_t sums[2][16];                                 // of the waves' 64 chunks each, in turn
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
     const JobView v = job_view(a, blockIdx.x);
     if (!v.ok) {
         if (tid == 0 && a.coded_bytes) a.coded_bytes[blockIdx.x] = ~0ull;
         return;
     }
-    if (tid == 0) carry = 0;
-    __syncthreads();
-    for (int64_t base = 0; base < v.n_chunks; base += 256) {
+    uint32_t carry = 0;
+    int turn = 0;
+    for (int64_t base = 0; base < v.n_chunks; base += blockDim.x, turn ^= 1) {
         const int64_t j = base + tid;
-        const uint32_t x = j < v.n_chunks ? v.chunk_off[j] : 0u;
-        s[tid] = x;
+        const uint32_t x = j < v.n_chunks ? v.chunk_off[j] : 0u, incl = wave_inclusive_scan(x);
+        if (lane == 63) sums[turn][wave] = incl;
         __syncthreads();
-        for (int d = 1; d < 256; d <<= 1) {
-            const uint32_t o = tid >= d ? s[tid - d] : 0u;
-            __syncthreads();
-            s[tid] += o;
-            __syncthreads();
+        uint32_t before = carry;
+        for (int w = 0; w < n_waves; ++w) {
+            const uint32_t s = sums[turn][w];
+            before += w < wave ? s : 0u;
+            carry += s;
         }
-        const uint32_t c = carry;
-        if (j < v.n_chunks) v.chunk_off[j] = c + s[tid] - x;
-        __syncthreads();
-        if (tid == 255) carry = c + s[255];
-        __syncthreads();
+        if (j < v.n_chunks) v.chunk_off[j] = before + incl - x;
     }
     if (tid == 0) {
         v.chunk_off[v.n_chunks] = carry;
@@ -308,7 +305,7 @@ __global__ void __launch_bounds__(256) entropy_scan_kernel(const EntropyArgs a) 
 template <bool LDS_TAB>
 __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = a.waves;
     const int R = a.R;
     const JobView v = job_view(a, blockIdx.y);
     const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
@@ -321,8 +318,10 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
         stage_table(reinterpret_cast<const uint32_t*>(tab), R, 7, tab32);
         tab = reinterpret_cast<const uint16_t*>(tab32);
     }
-    for (int i = lane; i < kImageDw; i += 64) img[i] = 0u;
+    if (wave < n_waves)
+        for (int i = lane; i < kImageDw; i += 64) img[i] = 0u;
     __syncthreads();
+    if (wave >= n_waves) return;
     for (int c = 0; c < a.chunks_per_wave; ++c) {
         const int64_t chunk = first + (int64_t)c * n_waves + wave;
         if (chunk >= v.n_chunks) break;
@@ -708,7 +707,7 @@ __global__ void __launch_bounds__(1024) entropy_decode_staged_kernel(const Entro
     typedef const uint8_t __attribute__((address_space(3))) * lds_u8;
     typedef uint32_t __attribute__((address_space(3))) * lds_u32;
     typedef const char __attribute__((address_space(1))) * global_ptr;
-    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = a.waves;
     const uint32_t R = (uint32_t)a.R, per_row = R / 4u;
     const JobView v = job_view(a, blockIdx.y);
     const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
@@ -756,7 +755,7 @@ __global__ void __launch_bounds__(1024) entropy_decode_staged_kernel(const Entro
     };
 
     int64_t chunk = first + wave;
-    const bool live = chunk < v.n_chunks;
+    const bool live = wave < n_waves && chunk < v.n_chunks;
     if (live) directory(chunk);
     {
         const uint4* from = reinterpret_cast<const uint4*>(a.log + v.table * kLogRow);
@@ -768,6 +767,7 @@ __global__ void __launch_bounds__(1024) entropy_decode_staged_kernel(const Entro
     }
     if (live) at = slot_bit + enter(chunk);
     __syncthreads();
+    if (wave >= n_waves) return;
     for (int c = 0; c < a.chunks_per_wave; ++c, chunk += n_waves) {
         if (chunk >= v.n_chunks) break;
         const bool follows = c + 1 < a.chunks_per_wave && chunk + n_waves < v.n_chunks;
@@ -1008,10 +1008,13 @@ bool small_jobs_wait(const Shape& staged, const Shape& other, int64_t n_chunks, 
     return n_chunks <= 8 && rounds(staged) >= (n_chunks <= 4 ? 2 : 3) && rounds(staged) > rounds(other);
 }
 
-kvtc_status launch(const char* who, void (*fn)(EntropyArgs), const Shape& sh, int n_jobs, EntropyArgs a, hipStream_t st) {
+// helpers: the kernel copies tables once and lets waves that take no chunk go, so that the launch may have more of them.
+kvtc_status launch(const char* who, void (*fn)(EntropyArgs), const Shape& sh, int n_jobs, EntropyArgs a, hipStream_t st, bool helpers = false) {
     if (allow_full_lds(reinterpret_cast<const void*>(fn)) != hipSuccess) return set_error(KVTC_E_HIP, "%s: cannot size the LDS", who);
+    a.waves = sh.waves;
     a.chunks_per_wave = sh.chunks_per_wave;
-    hipLaunchKernelGGL(fn, dim3(sh.blocks, (unsigned)n_jobs), dim3(64 * sh.waves), sh.lds, st, a);
+    const int waves = helpers && (int64_t)sh.blocks * n_jobs <= compute_units() ? 16 : sh.waves;
+    hipLaunchKernelGGL(fn, dim3(sh.blocks, (unsigned)n_jobs), dim3(64 * waves), sh.lds, st, a);
     return KVTC_OK;
 }
 
@@ -1021,14 +1024,14 @@ kvtc_status run_encode(const char* who, const kvtc_entropy* e, const EntropyArgs
     EntropyArgs a = a_in;
     a.max_tokens = max_tokens;
     kvtc_status rc = KVTC_OK;
-    if (max_chunks > 0) rc = launch(who, &entropy_size_kernel, launch_shape((size_t)R * kLenRow, kChunk * 4, max_chunks, n_jobs), n_jobs, a, st);
+    if (max_chunks > 0) rc = launch(who, &entropy_size_kernel, launch_shape((size_t)R * kLenRow, kChunk * 4, max_chunks, n_jobs), n_jobs, a, st, true);
     if (rc != KVTC_OK) return rc;
-    hipLaunchKernelGGL(entropy_scan_kernel, dim3((unsigned)n_jobs), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(entropy_scan_kernel, dim3((unsigned)n_jobs), dim3(max_chunks <= 64 ? 64 : max_chunks <= 256 ? 256 : 1024), 0, st, a);
     if (max_chunks > 0) {
         const bool tab_lds = R <= kMaxLdsRecord &&
                              !(max_chunks <= 2 && jobs_wait((size_t)R * kEncRow, kImageDw * 4, n_jobs));
         rc = launch(who, tab_lds ? &entropy_write_kernel<true> : &entropy_write_kernel<false>,
-                    launch_shape(tab_lds ? (size_t)R * kEncRow : 0, kImageDw * 4, max_chunks, n_jobs), n_jobs, a, st);
+                    launch_shape(tab_lds ? (size_t)R * kEncRow : 0, kImageDw * 4, max_chunks, n_jobs), n_jobs, a, st, tab_lds);
         if (rc != KVTC_OK) return rc;
     }
     const hipError_t err = hipGetLastError();
@@ -1049,7 +1052,7 @@ kvtc_status run_decode(const char* who, const kvtc_entropy* e, const EntropyArgs
                                     : decode_in_pieces(sh, R, max_chunks, n_jobs) ? &entropy_decode_kernel<true, true>
                                                                                     : &entropy_decode_kernel<true, false>;
     const Shape staged = a.log && tab_lds ? launch_shape(log_bytes(R), kLogSlot, max_chunks, n_jobs) : Shape{};
-    const kvtc_status rc = staged.waves && !small_jobs_wait(staged, sh, max_chunks, n_jobs) ? launch(who, &entropy_decode_staged_kernel, staged, n_jobs, a, st)
+    const kvtc_status rc = staged.waves && !small_jobs_wait(staged, sh, max_chunks, n_jobs) ? launch(who, &entropy_decode_staged_kernel, staged, n_jobs, a, st, true)
                                                                                            : launch(who, fn, sh, n_jobs, a, st);
     if (rc != KVTC_OK) return rc;
     const hipError_t err = hipGetLastError();
