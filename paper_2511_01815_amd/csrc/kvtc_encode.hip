@@ -130,9 +130,9 @@ __host__ __device__ constexpr int enc_ring_bytes(int ntp, int elem_bytes, int nw
            (enc_kx(ntp, elem_bytes, once) == enc_ks(ntp, elem_bytes, once) ? n : 2) * enc_x_slab(ntp, elem_bytes, nw, wc, once);
 }
 
-// Fewest coordinate tiles worked on for a plan that runs as ntp of them (the padding is left out in the variants of 6, 8 and 10), and what
+// Fewest coordinate tiles worked on for a plan that runs as ntp of them (the padding is left out in the variants of 6, 8, 10 and 20), and what
 // follows for the transfers of a stage's basis pieces: whether every wave has an i-th one whatever the plan, and how many a wave has at least.
-__host__ __device__ constexpr int enc_min_tiles(int ntp) { return ntp > 4 && ntp <= 10 ? ntp - 1 : ntp; }
+__host__ __device__ constexpr int enc_min_tiles(int ntp) { return ntp > 4 && ntp <= 10 ? ntp - 1 : (ntp == 20 ? 17 : ntp); }
 template <int NTP, int NW, int TOTAL> __host__ __device__ constexpr bool enc_basis_pieces(int i) {
     for (int w = 0; w < NW; ++w)
         if (i * NW + w >= TOTAL || (i * NW + w) % NTP >= enc_min_tiles(NTP)) return false;
@@ -376,8 +376,10 @@ __device__ __forceinline__ void encode_tile(const PlanEnc& P, const TileRef& tr,
     // The plan's coordinate tiles are shared out evenly: a wave has NTW of them or one fewer, whose place it does not multiply, and the padding is
     // not fetched.  What these kernels have at their disposal is power -- the clock gives way, to 1.5 GHz, under matrix instructions and a stream
     // from HBM at once --, so work that can be left out counts although it would fit the time (32-layer cache at 16x, plans of 7, 8 and 9 tiles that
-    // run as 8 and 10: 1300 -> 1282 us).  Not up to four tiles, which are bound by HBM, nor in the 8-wave variants: the conditions cost those 0.5 %.
-    const int nt = enc_min_tiles(NTP) < NTP ? (P.r + 31) / 32 : NTP, wc = wave % WC;
+    // run as 8 and 10: 1300 -> 1282 us).  Not up to four tiles, which are bound by HBM, nor in the 8-wave variants of 12 and 16: the conditions cost those 0.5 %.
+    // In that of 20 the two waves of a SIMD are two places apart in the coordinates, or the ones with a tile more would share one: plans of 528 coordinates, 17 tiles, 16 tensors
+    // of 32768 tokens 702 us as 20 tiles, 686 without the padding, 673 so.  (By turns in the two workgroups of a compute unit, for those of 7 and 9 tiles, it gave nothing.)
+    const int nt = enc_min_tiles(NTP) < NTP ? (P.r + 31) / 32 : NTP, wc = (wave + (NTP == 20 ? 2 * wt : 0)) % WC;
     const int ct0 = wc * (nt / WC) + min(wc, nt % WC), n_ct = nt / WC + (wc < nt % WC ? 1 : 0);
     const bool full = enc_min_tiles(NTP) == NTP || n_ct >= NTW;
     const int l32 = lane & 31, h = lane >> 5;

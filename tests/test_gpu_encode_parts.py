@@ -58,3 +58,20 @@ def test_shares_of_groups_are_coded_as_whole_tiles(name, p, dtype):
     assert torch.equal(out, want)
     batch.close()
     plan.close()
+
+
+@pytest.mark.parametrize("r", [528, 560, 592, 608, 640])
+@pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
+def test_bulk_plans_of_17_to_20_tiles_leave_the_padding_out(r, dtype):
+    """Whole tiles and a half, shared out over four waves as 5 and 4: the short-job kernels' bits, which a call of a tile or two takes."""
+    plan = _gpu_plan(_manual(1024, [(16, 8), (r - 144, 3), (128, 2)], r))
+    R, n_bulk = plan.record_bytes, bulk_tokens()
+    x = torch.randn((130, 1024), generator=torch.Generator(device=DEV).manual_seed(r), device=DEV).to(torch.bfloat16 if dtype == kv.KVTC_BF16 else torch.float32)
+    want = torch.zeros((130, R), dtype=torch.uint8, device=DEV)
+    kv.kvtc_encode(plan.handle, x, dtype, 130, 1024, want, want.numel())
+    rows = x.repeat(n_bulk // 130 + 1, 1)[:n_bulk].contiguous()
+    got = torch.zeros((n_bulk, R), dtype=torch.uint8, device=DEV)
+    kv.kvtc_encode(plan.handle, rows, dtype, n_bulk, 1024, got, got.numel())
+    torch.cuda.synchronize()
+    assert torch.equal(got, want.repeat(n_bulk // 130 + 1, 1)[:n_bulk])
+    plan.close()
