@@ -55,7 +55,7 @@ __host__ __device__ inline uint64_t header_bytes(int64_t n_chunks) { return 4ull
 // Tables in LDS: the rows of successive byte positions are a dword apart from a multiple of the banks, so that lanes that
 // look up like bytes of different positions do not all meet on one bank.
 constexpr int kLenRow = 256 + 4, kEncRow = 512 + 4;                          // bytes per byte position
-constexpr int kImageDw = 392;         // a wave's part of the bit string: 64 pieces of 16 codes of at most 12 bits, a carried dword, whole 16 bytes
+constexpr int kImageDw = 392;         // a wave's part of the bit string: 64 pieces of 16 codes of at most 12 bits, 16 carried bytes, and 16 for zeros beyond them
 constexpr int kLdsMost = kLdsBudget - 1024;
 constexpr int kMaxLdsRecord = 264;    // bytes: the largest whose code table fits beside 16 waves' images
 static_assert(kMaxLdsRecord * kEncRow + 16 * kImageDw * 4 <= kLdsMost && (kMaxLdsRecord + 4) * kEncRow + 16 * kImageDw * 4 > kLdsMost, "the edge");
@@ -233,9 +233,8 @@ __global__ void __launch_bounds__(1024, 2) entropy_size_kernel(const EntropyArgs
             uint32_t s[4], row = __umul24(cur.at, 4u * kLenRow), tok = tok0, last = 0u, end_tok[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint8_t* e = tab + row;
-                const uint32_t bits = (uint32_t)e[w[j] & 0xffu] + (uint32_t)e[kLenRow + ((w[j] >> 8) & 0xffu)] +
-                                      (uint32_t)e[2 * kLenRow + ((w[j] >> 16) & 0xffu)] + (uint32_t)e[3 * kLenRow + (w[j] >> 24)];
+                auto entry = [&](int b) { return (uint32_t)tab[__builtin_amdgcn_udot4(w[j], 1u << (8 * b), row, false) + b * kLenRow]; };
+                const uint32_t bits = entry(0) + entry(1) + entry(2) + entry(3);
                 s[j] = cur.dw + j < cur.n_dw ? bits : 0u;
                 row += 4u * kLenRow;
                 end_tok[j] = row == rows_end && cur.dw + j < cur.n_dw ? tok : ~0u;
@@ -296,12 +295,14 @@ __global__ void __launch_bounds__(1024) entropy_scan_kernel(const EntropyArgs a)
 
 // (3) the code strings.  A chunk whose string would end beyond the job's room is left unwritten (the caller sees the
 // needed size in coded_bytes).  Per step a wave builds the string of its 64 pieces (1 KiB of records) in LDS, starting at the
-// bits the step before left over, and stores the whole dwords coalesced: 1.5 KiB of LDS per wave, where the image of a whole
+// bits the step before left over, and stores the whole 16-byte pieces coalesced: 1.5 KiB of LDS per wave, where the image of a whole
 // chunk and its rows took 20 and left a compute unit seven waves.  LDS_TAB: the codes come from the workgroup's copy of the
-// table (records of up to kMaxLdsRecord bytes), else from global memory.  Bound by vector instructions, 11 per byte: four bytes' codes are
-// put together and OR-ed in at once, where a 64-bit buffer emptied behind every second byte made it 16 with nine branches for each lane's 16
-// bytes, and everything that is one for the wave stays in scalar registers.  256 MiB of records: 634 us in a chunk image, 163 with the
-// buffer, 136 so.
+// table (records of up to kMaxLdsRecord bytes), else from global memory.  Four bytes' codes are
+// put together and OR-ed in at once, where a 64-bit buffer emptied behind every second byte made it 16 instructions a byte with nine branches for each lane's 16
+// bytes, and everything that is one for the wave stays in scalar registers; a step's 16 lookups are on their way together, and it waits for no store.
+// Bound by the LDS (lookups of random bytes meet on banks) and, at 256 MiB in and 226 out, not far from what a copy of as much takes, 100 us.
+// 256 MiB of records: 634 us in a chunk image, 163 with the buffer, 136 with dwords stored by and by, the last one or more of a step each by a branch, and
+// lookups in three turns, 127 so (nine vector instructions to a byte for eleven).
 template <bool LDS_TAB>
 __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
@@ -311,12 +312,12 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
     const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
     if (!v.ok || first >= v.n_chunks) return;
     uint32_t* img = lds + wave * kImageDw;
-    constexpr int kRow = LDS_TAB ? kEncRow / 2 : 256;                // entries from one byte position to the next
-    const uint16_t* tab = a.enc + v.table * 256;
+    constexpr uint32_t kRowB = LDS_TAB ? kEncRow : 512;              // bytes from one byte position's entries to the next's
+    const char* tab = reinterpret_cast<const char*>(a.enc + v.table * 256);
     if constexpr (LDS_TAB) {
         uint32_t* tab32 = lds + n_waves * kImageDw;
         stage_table(reinterpret_cast<const uint32_t*>(tab), R, 7, tab32);
-        tab = reinterpret_cast<const uint16_t*>(tab32);
+        tab = reinterpret_cast<const char*>(tab32);
     }
     if (wave < n_waves)
         for (int i = lane; i < kImageDw; i += 64) img[i] = 0u;
@@ -331,38 +332,59 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
         uint32_t* out = reinterpret_cast<uint32_t*>(v.payload + begin);
         PieceWalk pw(v.T, chunk, R);
         const uint32_t* src = v.rec + chunk * kChunk * pw.per_row;
-        const uint32_t rows_end = pw.per_row * (4u * kRow);
-        uint32_t carry = 0, written = 0;                             // bits in img[0] left by the step before; dwords stored
-        uint32_t w[4];
+        const uint32_t rows_end = pw.per_row * (4u * kRowB);
+        uint32_t carry = 0, written = 0;                             // bits in img[0 .. 3] left by the step before; dwords stored
+        uint32_t w[4], ahead[4] = {0u, 0u, 0u, 0u};
         pw.load(src, w);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(w[j]));   // (here, so that no step begins by waiting)
         for (uint32_t d0 = 0; d0 < pw.n_dw; d0 += 256u) {
-            // four bytes' codes together: at most 48 bits
-            uint64_t code[4];
-            uint32_t len[4], row = __umul24(pw.at, 4u * kRow), bits = 0;       // the dword's first entry in the table
-            auto codes = [&](auto whole_tag) {
+            // all 16 lookups on their way at once.  An entry's address is one dot product: the row's, and twice the byte.
+            uint32_t row = __umul24(pw.at, 4u * kRowB), ent[4][4];   // row: of the dword's first byte
+            auto lookups = [&](auto wrap_tag) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const uint16_t* e = tab + row;
-                    uint32_t ent[4], two[2], n_two[2];
 #pragma unroll
-                    for (int b = 0; b < 4; ++b) ent[b] = e[b * kRow + ((w[j] >> (8 * b)) & 0xffu)];
-#pragma unroll
-                    for (int b = 0; b < 2; ++b) {
-                        const uint32_t l0 = ent[2 * b] >> 12;
-                        two[b] = (ent[2 * b] & 0xfffu) | ((ent[2 * b + 1] & 0xfffu) << l0);
-                        n_two[b] = l0 + (ent[2 * b + 1] >> 12);
+                    for (int b = 0; b < 4; ++b)
+                        ent[j][b] = *reinterpret_cast<const uint16_t*>(tab + __builtin_amdgcn_udot4(w[j], 2u << (8 * b), row, false) +
+                                                                       (decltype(wrap_tag)::value ? b : 4 * j + b) * kRowB);
+                    if (decltype(wrap_tag)::value) {
+                        row += 4u * kRowB;
+                        if (row == rows_end) row = 0u;
                     }
-                    const bool in = decltype(whole_tag)::value || pw.dw + j < pw.n_dw;
-                    code[j] = in ? (uint64_t)two[0] | ((uint64_t)two[1] << n_two[0]) : 0ull;
-                    len[j] = in ? n_two[0] + n_two[1] : 0u;
-                    bits += len[j];
-                    row += 4u * kRow;
-                    if (row == rows_end) row = 0u;
                 }
             };
-            if (d0 + 256u <= pw.n_dw) codes(std::true_type()); else codes(std::false_type());
+            if (pw.per_row % 4u == 0u) {                             // (a piece is within its record: its rows' distances are in the instructions)
+                lookups(std::false_type());
+                asm volatile("; rows of one record");                // (keeps the two forms' reads from being made one, behind registers of addresses)
+            } else {
+                lookups(std::true_type());
+            }
+            const uint32_t dw = pw.dw;
             pw.next();
-            if (d0 + 256u < pw.n_dw) pw.load(src, w);                // the next step's bytes travel under this step's string
+            if (d0 + 256u < pw.n_dw) pw.load(src, ahead);            // the next step's bytes travel under this step's string
+            __builtin_amdgcn_sched_barrier(0);
+            // four bytes' codes together: at most 48 bits
+            uint64_t code[4];
+            uint32_t len[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                uint32_t two[2], n_two[2];
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const uint32_t l0 = ent[j][2 * b] >> 12;
+                    two[b] = (ent[j][2 * b] & 0xfffu) | ((ent[j][2 * b + 1] & 0xfffu) << l0);
+                    n_two[b] = l0 + (ent[j][2 * b + 1] >> 12);
+                }
+                code[j] = (uint64_t)two[0] | ((uint64_t)two[1] << n_two[0]);
+                len[j] = n_two[0] + n_two[1];
+            }
+            if (d0 + 256u > pw.n_dw) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (dw + j >= pw.n_dw) code[j] = 0ull, len[j] = 0u;
+            }
+            const uint32_t bits = (len[0] + len[1]) + (len[2] + len[3]);
             const uint32_t incl = wave_inclusive_scan(bits);
             uint32_t pos = carry + incl - bits;
             const uint32_t n_bits = carry + (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
@@ -382,34 +404,31 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
                 }
             }
             wave_fence();
-            const uint32_t full = n_bits >> 5;                       // at most 384
-            const uint32_t rest = img[full];
+            // whole pieces of 16 bytes leave, the one that is not full stays for the next step
+            const uint32_t full = (n_bits >> 7) * 4u;                // dwords, at most 384
+            const uint4 rest = *reinterpret_cast<const uint4*>(img + full);
             wave_fence();
+            // (waited for here: behind the stores it would have to wait for those as well, which have the next step's time so)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                asm volatile("" : "+v"(ahead[j]));
+                w[j] = ahead[j];
+            }
             for (uint32_t i0 = 0; i0 <= full; i0 += 256u) {
                 const uint32_t i = i0 + 4u * lane;
                 if (i > full) break;
                 uint4* p = reinterpret_cast<uint4*>(img + i);
                 const uint4 q = *p;
-                *p = make_uint4(0u, 0u, 0u, 0u);
-                const uint32_t o = written + i;
-                if (i + 4u <= full && o + 4u <= n_out) {
-                    *reinterpret_cast<Dwords4*>(out + o) = Dwords4{{q.x, q.y, q.z, q.w}};
-                } else {
-                    const uint32_t qq[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (i + j < full && o + j < n_out) out[o + j] = qq[j];
-                }
+                *p = i == 0u ? rest : make_uint4(0u, 0u, 0u, 0u);
+                if (i < full && written + i + 4u <= n_out) *reinterpret_cast<Dwords4*>(out + written + i) = Dwords4{{q.x, q.y, q.z, q.w}};
             }
             wave_fence();
-            if (lane == 0) img[0] = rest;
-            wave_fence();
             written += full;
-            carry = n_bits & 31u;
+            carry = n_bits & 127u;
         }
-        if (lane == 0) {                                             // the last, partly filled dword
-            if (carry != 0u && written < n_out) out[written] = img[0];
-            img[0] = 0u;
+        if (lane < 4) {                                              // the last piece
+            if (32u * (uint32_t)lane < carry && written + lane < n_out) out[written + lane] = img[lane];
+            img[lane] = 0u;
         }
         wave_fence();
     }
@@ -699,7 +718,7 @@ __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs 
 // up four symbols meanwhile.  Bound by the LDS, 3.9 reads to a symbol and in use for half of the time, with four waves to a SIMD, as many as the strings leave room
 // for, that wait for each other's lookups.
 // 256 MiB of records of 128 bytes: 264 us by the form above, 162 so (192 with 64-byte pieces of rows and windows of two codes, 171 with stores that the
-// caches keep); 64 tensors of 30000 tokens of 100 bytes 292 and 117; one of 64 tokens 16 and 13.  (With a reader behind it that finds 30 to 125 MB of
+// caches keep); 64 tensors of 30000 tokens of 100 bytes 292 and 117; one of 64 tokens 16 and 13, with waves that help to copy the tables 11.  (With a reader behind it that finds 30 to 125 MB of
 // records in the caches, the pair gains nothing by the stores past them, and loses 2 %.)
 template <int N> using row_of = std::integral_constant<int, N>;
 __global__ void __launch_bounds__(1024) entropy_decode_staged_kernel(const EntropyArgs a) {
@@ -954,7 +973,8 @@ size_t bound_of(int R, int64_t n_tokens) {
 // table in LDS workgroups are as small as they can be, or, with more jobs than compute units, a job (of up to 16 chunks) each: then a
 // compute unit's caches hold few tables.
 // (2188 chunks of 128-byte records, encode and decode: 75 + 102 us with four waves that took two chunks in turn on one workgroup per
-// compute unit, 45 + 31 so, 40 + 24 with the kernels as they are; 64 tensors of 63 chunks 83 + 145, 41 + 39, 34 + 32.)
+// compute unit, 45 + 31 so, 35 + 18 with the kernels as they are; 64 tensors of 63 chunks 83 + 145, 41 + 39, 39 + 26 (of 64).  Ten waves in a workgroup, two of which a
+// compute unit has room for at 128 bytes, 20 waves instead of 16, but twice the copies of the table: encode of 64 tensors of 512 chunks 211 us and 215 so.)
 struct Shape { int waves, chunks_per_wave; unsigned blocks; size_t lds; };
 Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs) {
     const int64_t total = n_chunks * n_jobs, cus = compute_units();
