@@ -592,8 +592,10 @@ __global__ void __launch_bounds__(NW * 64, (enc_wgs_per_cu<WC, NTW, NW>())) kvtc
 // wave only, so the fragments go straight to registers, 16 KiB of them in flight per wave (16 k-steps ahead), instead of through an LDS
 // ring shared by barriers; X comes in chunks of 256 (fp32: 128) features, asynchronously, with one barrier per chunk.  The sums run over the
 // features in the bulk kernel's order: a token's record is the same bits whichever kernel codes it.
-// 64 caches of 16 tokens with a basis each (32 MB of bases): 60 us in two launches of ring kernels before, 14 now in one; 48 tokens of one
-// tensor: 18 -> 14.
+// 64 caches of 16 tokens with a basis each (32 MB of bases): 60 us in two launches of ring kernels before, 14 in one; 48 tokens of one
+// tensor: 18 -> 14.  (Both have their tiles' groups shared out now, further down: 10 and 8.)
+// Tiles of 128 tokens, a workgroup to a compute unit, which draw half as much of the basis: 17000 and 32768 tokens of 240 coordinates 25.7 -> 22.6 and 29.1 -> 28.0 us,
+// of 192 22.8 -> 22.4 and 26.4 -> 26.5, fp32 of 240 31.6 -> 31.9 and 36.3 -> 38.4, heads of 128 features 6.4 -> 7.7: the gain is for one width of one type.
 // (A chunk is 512 bytes of a token in either type, so that two workgroups' chunks fit a compute unit's LDS: with 1 KiB in fp32 only one
 // did, and launches of more tiles than compute units ran a second round: 20000 tokens of 240 coordinates 38 us, now 31.)
 template <typename XT> constexpr int short_feat() { return 512 / (int)sizeof(XT); }
@@ -859,7 +861,7 @@ __device__ __forceinline__ uint32_t lane_id() {
 // jobs' lengths are on the device -- is coded by this launch alone.  The tiles of all jobs are numbered through; every wave finds its
 // workgroup's by a prefix sum over the jobs' tiles, a job per lane and round (bounded by the load and six lane exchanges).  Workgroups go
 // round-robin over the eight XCDs, each of which takes an eighth of the tiles, neighbours: the tiles of a job share an L2 and its basis.
-// (With a launch per bulk variant, which found no job, in front of it: an append step of 64 tensors 21.8 us, now 16.4; a head of 4096
+// (With a launch per bulk variant, which found no job, in front of it: an append step of 64 tensors 21.8 us, then 16.4 (13.5 with groups shared out); a head of 4096
 // tokens in fp32, encode and decode, 24.0, now 17.9, two of it by the decode's tiles.)
 // KEEP: the lane's number, and with it the addresses of its jobs, may be kept through the loop over tiles.  In fp32 there are no registers for them:
 // with them, and with `upto` left as it is for rounds that a list does not have, up to 18 went to scratch memory, four of them inside the loop over

@@ -12,10 +12,12 @@
 //   flat run of its records' bytes, dealt to the lanes in 16-byte pieces (coalesced loads, no staging, no idle lanes
 //   whatever the record size): a chunk's bit string is the concatenation of its bytes' codes in that very order, so one
 //   prefix sum over the wave places every lane's string.
-//   decode = one launch: a lane walks the string of one token, all lanes at the same byte position.  A code's length is
-//   what a 256-entry table says for the next 8 bits (9 for every longer code) plus a count of comparisons: with canonical
+//   decode = one launch: a lane walks the string of one token, all lanes at the same byte position.  With canonical
 //   codes the next 12 bits, read as a number with the first bit on top, are below limit[L] exactly when the code has at most
-//   L bits.  Length and bits give the symbol's rank, the rank the symbol; the walk waits for neither.
+//   L bits.  Records of up to 128 bytes under complete codes find the length by one lookup, in a table indexed by the complement of
+//   those bits as a float, and their strings come through LDS (entropy_decode_staged_kernel).  In the general form a code's length is
+//   what a 256-entry table says for the next 8 bits (9 for every longer code) plus a count of comparisons.  Length and bits give the
+//   symbol's rank, the rank the symbol; the walk waits for neither.
 // Nothing is allocated: the directory lives in the output buffer.
 #include <hip/hip_runtime.h>
 
