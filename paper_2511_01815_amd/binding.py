@@ -165,21 +165,20 @@ def _ptr(t) -> Optional[int]:
         raise
 
 
-_raw_stream = _raw_device = None
-
-
-def _current_stream() -> int:
+def _first_current_stream() -> int:
     """The handle of torch's current stream.  Asked for without building a Stream object, where this torch has the call, and without the
     module's checks once it has been initialised: 2.8 us of the host's time per call of the library with the object, 0.46 with the checks,
-    0.15 so (a short context's four calls: 32.7 us on the host at first, 21.9 with the checks)."""
-    global _raw_stream, _raw_device
-    if _raw_stream is None:
-        import torch
-        torch.cuda.current_device()                      # (initialises torch's side of the GPU, or says why it cannot)
-        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
-        _raw_stream = raw if raw is not None else lambda _: torch.cuda.current_stream().cuda_stream
-        _raw_device = device if device is not None else torch.cuda.current_device
-    return _raw_stream(_raw_device())
+    0.15 so (a short context's four calls: 32.7 us on the host at first, 21.9 with the checks).  This is the process's first call; what it
+    finds takes its place in one assignment, so that no thread sees half of it."""
+    global _current_stream
+    import torch
+    torch.cuda.current_device()                          # (initialises torch's side of the GPU, or says why it cannot)
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+    _current_stream = (lambda: raw(device())) if raw is not None else lambda: torch.cuda.current_stream().cuda_stream
+    return _current_stream()
+
+
+_current_stream = _first_current_stream
 
 
 def _stream(stream) -> Optional[int]:

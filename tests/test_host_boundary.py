@@ -4,9 +4,11 @@ header the kernels use) agree bit for bit with the oracle's."""
 import ctypes as C
 import os
 import re
+import sys
 
 import numpy as np
 import pytest
+import torch
 
 import kvtc_oracle as ko
 import paper_2511_01815_amd as kv
@@ -273,3 +275,38 @@ def test_bench_refuses_more_than_one_gpu():
     import sys
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def _trace_of(fn, of_code, seen):
+    """Runs fn with `seen` called before every line of, and at every exception in, the Python frames whose code is of_code."""
+    def local(frame, event, arg):
+        seen(event)
+        return local
+
+    old = sys.gettrace()
+    sys.settrace(lambda frame, event, arg: local if frame.f_code is of_code else None)
+    try:
+        return fn()
+    finally:
+        sys.settrace(old)
+
+
+def test_a_second_thread_finds_the_current_stream_at_any_moment_of_the_first_ones_search(monkeypatch):
+    """The first call looks up torch's calls for the current stream; whatever line of it another thread's call comes in at must not matter."""
+    from paper_2511_01815_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 70 + device, raising=False)
+    monkeypatch.setattr(binding, "_current_stream", binding._first_current_stream)
+    first, others = binding._current_stream, []
+    found = set(vars(binding))
+
+    def other_thread(event):
+        if event == "line":
+            before = {k: v for k, v in vars(binding).items() if k in found}
+            others.append(binding._current_stream())                 # (untraced: a trace function is not traced itself)
+            vars(binding).update(before)                             # (what it found is its own: the first call goes on from where it was)
+
+    assert _trace_of(first, first.__code__, other_thread) == 73
+    assert len(others) >= 4 and set(others) == {73}
+    assert binding._current_stream() == 73
