@@ -181,6 +181,14 @@ def _first_current_stream() -> int:
 _current_stream = _first_current_stream
 
 
+def _forget_current_stream() -> None:
+    global _current_stream
+    _current_stream = _first_current_stream
+
+
+os.register_at_fork(after_in_child=_forget_current_stream)      # (a child may not use its parent's GPU: torch says so when it is asked first)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         return _current_stream()

@@ -310,3 +310,30 @@ def test_a_second_thread_finds_the_current_stream_at_any_moment_of_the_first_one
     assert _trace_of(first, first.__code__, other_thread) == 73
     assert len(others) >= 4 and set(others) == {73}
     assert binding._current_stream() == 73
+
+
+def test_a_forked_child_asks_torch_before_it_uses_the_gpu(monkeypatch):
+    """A child of a process that has made calls must hear torch's refusal, not use a stream of its parent's GPU."""
+    from paper_2511_01815_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 70 + device, raising=False)
+    monkeypatch.setattr(binding, "_current_stream", binding._first_current_stream)
+    assert binding._current_stream() == 73
+
+    def refuse():
+        raise RuntimeError("Cannot re-initialize CUDA in forked subprocess")
+
+    monkeypatch.setattr(torch.cuda, "current_device", refuse)
+    assert binding._current_stream() == 73
+    child = os.fork()
+    if child == 0:
+        try:
+            binding._current_stream()
+            os._exit(1)
+        except RuntimeError:
+            os._exit(0)
+        finally:
+            os._exit(2)
+    assert os.waitstatus_to_exitcode(os.waitpid(child, 0)[1]) == 0
+    assert binding._current_stream() == 73
