@@ -153,14 +153,16 @@ def _check(status: int) -> None:
 
 
 def _ptr(t) -> Optional[int]:
-    """Device/host address of a torch tensor, numpy array, int or None.  (Tensors, the most of all, without a look at the others: 0.15 us
-    with three type checks, 0.07 so.)"""
+    """Device/host address of a torch tensor, numpy array, int or None.  (A plain integer and None by one look each, then tensors, the most
+    of all, without a look at the others: 0.21 us with three type checks, 0.14 so; an integer 0.07, and 0.44 where an exception tells it apart.)"""
+    if t is None or t.__class__ is int:
+        return t
     try:
         return t.data_ptr()
     except AttributeError:
         if isinstance(t, np.ndarray):
             return t.ctypes.data
-        if t is None or isinstance(t, int):
+        if isinstance(t, int):
             return t
         raise
 

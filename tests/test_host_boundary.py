@@ -337,3 +337,15 @@ def test_a_forked_child_asks_torch_before_it_uses_the_gpu(monkeypatch):
             os._exit(2)
     assert os.waitstatus_to_exitcode(os.waitpid(child, 0)[1]) == 0
     assert binding._current_stream() == 73
+
+
+def test_addresses_of_every_kind_and_no_exception_for_a_plain_integer():
+    from paper_2511_01815_amd import binding
+    array, tensor, events = np.zeros(3), torch.zeros(3), []
+    assert binding._ptr(array) == array.ctypes.data and binding._ptr(tensor) == tensor.data_ptr() and binding._ptr(True) is True
+    for t in (1 << 40, 0, None):
+        assert _trace_of(lambda: binding._ptr(t), binding._ptr.__code__, events.append) is t
+    assert "line" in events and "exception" not in events
+    for t in ("address", 1.5, np.int64(8)):
+        with pytest.raises(AttributeError):
+            binding._ptr(t)
