@@ -20,7 +20,7 @@ hipError_t launch_encode(const KernelArgs& a, kvtc_dtype dtype, int key, int gri
 hipError_t launch_decode(const KernelArgs& a, kvtc_dtype dtype, int key, int grid, size_t lds_bytes, hipStream_t stream);
 hipError_t launch_encode_short(const KernelArgs& a, kvtc_dtype dtype, int ntw, int waves, int grid, size_t lds_bytes, hipStream_t stream);
 int encode_lds_bytes(int ntw, int wc, int nw, int n_groups, int rec_dwords, kvtc_dtype dtype);
-hipError_t launch_encode_parts(const KernelArgs& a, kvtc_dtype dtype, int waves, int grid, size_t lds_bytes, hipStream_t stream);
+hipError_t launch_encode_parts(const KernelArgs& a, kvtc_dtype dtype, int waves, int max_p, int grid, size_t lds_bytes, hipStream_t stream);
 int encode_part_waves_most();
 int encode_part_lds_bytes(int p, int ntp, int n_groups, int rec_dwords, kvtc_dtype dtype);
 int encode_short_ntw(int ntp);
@@ -691,7 +691,7 @@ static kvtc_status encode_single(const char* who, const kvtc_plan* plan, const v
     if (plan->h.enc_parts != 0 && plan->enc_p_lds[dtype] != 0 &&
         2 * tiles_part * plan->h.enc_parts <= part_places(plan->enc_p_waves, plan->enc_p_lds[dtype]) + compute_units()) {
         a.enc_split = plan->h.enc_parts;
-        e = launch_encode_parts(a, dtype, plan->enc_p_waves, (int)tiles_part * plan->h.enc_parts, (size_t)plan->enc_p_lds[dtype], static_cast<hipStream_t>(stream));
+        e = launch_encode_parts(a, dtype, plan->enc_p_waves, plan->h.p, (int)tiles_part * plan->h.enc_parts, (size_t)plan->enc_p_lds[dtype], static_cast<hipStream_t>(stream));
     } else if (plan->h.enc_short != 0 && tiles_short <= short_tiles_per_job(1, short_pairs(plan->h.enc_short, plan->enc_s_waves, plan->enc_s_lds[dtype]))) {
         e = launch_encode_short(a, dtype, plan->h.enc_short, plan->enc_s_waves, (int)tiles_short, (size_t)plan->enc_s_lds[dtype], static_cast<hipStream_t>(stream));
     } else {
@@ -981,7 +981,7 @@ static kvtc_status launch_encode_jobs(const char* who, const EncodeLaunches& l, 
         a.enc_table = 1;
         a.enc_split = l.part.split;
         a.enc_max_tokens = (int32_t)(a.cap / ((size_t)l.min_rec_dwords * 4));
-        e = launch_encode_parts(a, dtype, l.part.waves, part_grid, (size_t)l.part.lds, st);
+        e = launch_encode_parts(a, dtype, l.part.waves, l.max_p, part_grid, (size_t)l.part.lds, st);
     } else if (grid != 0) {
         // few tokens in all: one round of the short-job kernel
         a.enc_table = 1;

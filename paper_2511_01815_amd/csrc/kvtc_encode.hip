@@ -768,7 +768,7 @@ __device__ __forceinline__ void encode_part_tile(const PlanEnc& P, const EncPart
     constexpr int FEAT = short_feat<XT>(), STEPS = FEAT / 16;
     constexpr int EB = (int)sizeof(XT), ROW_B = FEAT * EB, COLS = ROW_B / 16, ROWS_DMA = 1024 / ROW_B;
     constexpr int ROWS = kEncPartTile, CHUNK_B = ROWS * ROW_B;
-    static_assert(AHEAD % STEPS == 0, "a chunk's fragments are in registers known at compile time");
+    static_assert(AHEAD % STEPS == 0 || STEPS % AHEAD == 0, "a round of the main loop is whole chunks, or within one");
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = (int)blockDim.x >> 6;
     const int l32 = lane & 31, h = lane >> 5;
     const int ntp = P.enc_ntw * P.enc_wc;
@@ -828,23 +828,29 @@ __device__ __forceinline__ void encode_part_tile(const PlanEnc& P, const EncPart
             return v;
         }
     };
+    // one round: AHEAD steps, and (MORE) the fragments of as many after them
     const char* x = reinterpret_cast<const char*>(smem);
-    for (int s0 = 0; s0 < n_steps; s0 += AHEAD) {
+    auto round = [&](int s0, auto more_tag) {
+        constexpr bool MORE = decltype(more_tag)::value;
+        const int k0 = AHEAD % STEPS == 0 ? 0 : s0 % STEPS;
 #pragma unroll
         for (int g = 0; g < AHEAD / 4; ++g) {                        // (features come in multiples of 64: four k-steps)
-            if (s0 + 4 * g >= n_steps) continue;
+            if (!MORE && s0 + 4 * g >= n_steps) continue;
             const char* xc = x + (s0 / STEPS + 4 * g / STEPS) * CHUNK_B;
             bf16x8 xv[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) xv[k] = xfrag(xc, (4 * g + k) % STEPS);
+            for (int k = 0; k < 4; ++k) xv[k] = xfrag(xc, k0 + (4 * g + k) % STEPS);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[4 * g + k]), xv[k], acc[0][0], 0, 0, 0);
-                fetch(s0 + 4 * g + k + AHEAD, 4 * g + k);
+                if constexpr (MORE) fetch(s0 + 4 * g + k + AHEAD, 4 * g + k);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-    }
+    };
+    int s0 = 0;
+    for (; s0 + AHEAD < n_steps; s0 += AHEAD) round(s0, std::true_type());
+    round(s0, std::false_type());                                    // (nothing to come: of 64 steps, 32 ahead, a third of all the fragments were fetched for nothing)
     wait_vmem<0>();                                                  // the fragments fetched past the end
     __syncthreads();
     encode_epilogue<1, 1, true, true>(acc, ct0, n_ct, 0, n_valid, ROWS, ntp, (int)blockDim.x, P, tr, a, tok_tile0, work, smem, part);
@@ -1002,8 +1008,11 @@ __device__ __forceinline__ void part_code(const PlanEnc& P, const TileRef& tr, c
     const EncPart ep(pd->enc_part[2 * part], pd->enc_part[2 * part + 1]);
     encode_part_tile<XT, AHEAD>(P, ep, tr, a, smem);
 }
-// (with up to four waves a SIMD's registers are one wave's, and 32 k-steps of fragments, twice as many, are on their way)
+// k-steps of fragments on their way: with up to four waves a SIMD's registers are one wave's, and 32 are; with more waves 16; and hardly more than there are, which are
+// fetched all the same and keep a small call waiting.  (One token of 64, 128 and 320 features, us, 32 ahead whatever there are, 8, 8 and 16, and the short-job kernel:
+// 4.4, 4.6 and 5.1; 3.5, 3.8 and 4.5; 4.0, 4.2 and 5.0.)
 constexpr int kPartThreads = 640;
+inline int part_ahead(int waves, int p) { return p <= 8 * 16 ? 8 : waves > 4 || p < 32 * 16 ? 16 : 32; }
 template <typename XT, int AHEAD>
 __global__ void __launch_bounds__(AHEAD == 32 ? 256 : kPartThreads) kvtc_encode_parts_kernel(const KernelArgs a) {
     extern __shared__ uint4 smem[];
@@ -1074,10 +1083,15 @@ hipError_t launch_encode_short(const KernelArgs& a, kvtc_dtype dtype, int ntw, i
     return hipLaunchKernel(fn, dim3(grid), dim3(64 * waves), params, lds_bytes, stream);
 }
 
-// `grid` workgroups of `waves` waves: a.enc_split for every tile of a tensor or of a batch, as for launch_encode_short
-hipError_t launch_encode_parts(const KernelArgs& a, kvtc_dtype dtype, int waves, int grid, size_t lds_bytes, hipStream_t stream) {
+// `grid` workgroups of `waves` waves: a.enc_split for every tile of a tensor or of a batch, as for launch_encode_short; max_p: features of a token, the most of any plan
+hipError_t launch_encode_parts(const KernelArgs& a, kvtc_dtype dtype, int waves, int max_p, int grid, size_t lds_bytes, hipStream_t stream) {
+    const void* fn = nullptr;
 #define KVTC_X(XT, AHEAD) (a.enc_table ? reinterpret_cast<const void*>(&kvtc_encode_small_batch_parts_kernel<XT, AHEAD>) : reinterpret_cast<const void*>(&kvtc_encode_parts_kernel<XT, AHEAD>))
-    const void* fn = waves <= 4 ? (dtype == KVTC_BF16 ? KVTC_X(uint16_t, 32) : KVTC_X(float, 32)) : (dtype == KVTC_BF16 ? KVTC_X(uint16_t, 16) : KVTC_X(float, 16));
+    switch (part_ahead(waves, max_p)) {
+        case 8: fn = dtype == KVTC_BF16 ? KVTC_X(uint16_t, 8) : KVTC_X(float, 8); break;
+        case 16: fn = dtype == KVTC_BF16 ? KVTC_X(uint16_t, 16) : KVTC_X(float, 16); break;
+        default: fn = dtype == KVTC_BF16 ? KVTC_X(uint16_t, 32) : KVTC_X(float, 32);
+    }
 #undef KVTC_X
     if (waves < 2 || waves * 64 > kPartThreads || a.enc_split < 1) return hipErrorInvalidValue;
     hipError_t e = allow_full_lds(fn);

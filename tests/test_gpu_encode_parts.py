@@ -60,6 +60,33 @@ def test_shares_of_groups_are_coded_as_whole_tiles(name, p, dtype):
     plan.close()
 
 
+@pytest.mark.parametrize("p", [64, 128, 192, 256, 320, 448, 512, 576, 1536])
+@pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
+def test_features_on_both_sides_of_what_is_fetched_ahead(p, dtype):
+    """8, 16 and 32 k-steps of 16 features ahead: fewer steps than that, as many, and rounds of the main loop that end with less than a whole one."""
+    plan = _gpu_plan(_manual(p, [(16, 6), (32, 3), (16, 2)], p))
+    R, n_bulk = plan.record_bytes, bulk_tokens()
+    x = torch.randn((70, p), generator=torch.Generator(device=DEV).manual_seed(p), device=DEV).to(torch.bfloat16 if dtype == kv.KVTC_BF16 else torch.float32)
+    rows = x.repeat(n_bulk // 70 + 1, 1)[:n_bulk].contiguous()
+    bulk = torch.zeros((n_bulk, R), dtype=torch.uint8, device=DEV)
+    kv.kvtc_encode(plan.handle, rows, dtype, n_bulk, p, bulk, bulk.numel())
+    batch = kv.Batch([plan])
+    for n in (1, 32, 70):
+        got = torch.zeros((n, R), dtype=torch.uint8, device=DEV)
+        kv.kvtc_encode(plan.handle, x, dtype, n, p, got, got.numel())
+        jobs = torch.from_numpy(kv.make_jobs([0, 0], [n, 17], [0, 50]).view(np.uint8)).to(DEV)
+        offs = torch.zeros(3, dtype=torch.int64, device=DEV)
+        out = torch.zeros((n + 17, R), dtype=torch.uint8, device=DEV)
+        status = torch.zeros(1, dtype=torch.int32, device=DEV)
+        kv.kvtc_offsets(batch.handle, jobs, 2, offs)
+        kv.kvtc_encode_batch(batch.handle, jobs, 2, x, dtype, p, offs, out, out.numel(), status)
+        torch.cuda.synchronize()
+        assert torch.equal(got, bulk[:n]) and int(status.item()) == 0, n
+        assert torch.equal(out, torch.cat([bulk[:n], bulk[50:67]])), n
+    batch.close()
+    plan.close()
+
+
 @pytest.mark.parametrize("r", [528, 560, 592, 608, 640])
 @pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
 def test_bulk_plans_of_17_to_20_tiles_leave_the_padding_out(r, dtype):
