@@ -131,15 +131,14 @@ int short_table_grid(size_t cap, int min_rec_dwords, int n_jobs, bool pairs) {
 // Workgroups by parts that run at once: two to a compute unit of four waves whose LDS allows it.
 int part_places(int waves, int lds) { return compute_units() * (waves <= 4 && 2 * lds <= kLdsBudget ? 2 : 1); }
 
-// The grid of a batch's one launch by parts, or 0.  The jobs' lengths are on the device; jobs of the length that the stream buffer has room for must all run
-// at once -- with tiles of up to 32 tokens, which the short-job kernel also codes in half the time, in five workgroups to four compute units.  (Tiles beyond that wait
-// for a workgroup.  64 tensors at 16x, four parts, us, against the short-job launch: room for 64 tokens each, 16 coded, 256 workgroups, 9.8 and 13.3; 33 to 64, 512
-// workgroups, 13.8 and 16.7; of 100, 1024 workgroups, 22.9 and 17.4.  90 of 31, 360 workgroups, 15.6 and 15.1; of 33, 720, 20.0 and 17.7; 12 of 340, 528, 17.9 and 14.4.)
-int short_part_grid(size_t cap, int min_rec_dwords, int n_jobs, int split, int places) {
-    const size_t each = (cap / ((size_t)min_rec_dwords * 4) + n_jobs - 1) / n_jobs, groups = (each + kEncPartTile - 1) / kEncPartTile * n_jobs * split;
-    const size_t most = each > kEncPartTile ? places : std::min(places, compute_units() * 5 / 4);
-    return n_jobs <= kShortTableJobs && groups <= most ? (int)((groups + 7) / 8 * 8 + 1) : 0;
+// Tokens of a job, by the stream buffer's size, and shares of tiles, in all, that a batch coded by parts has: at most, if its jobs are equal, and if their last
+// tiles are a quarter full on average.  (The jobs' lengths are on the device.)
+struct PartShares { size_t each, most, equal, mixed; };
+PartShares part_shares(size_t cap, int min_rec_dwords, int n_jobs, int split) {
+    const size_t jobs = (size_t)n_jobs, tokens = cap / ((size_t)min_rec_dwords * 4), each = (tokens + jobs - 1) / jobs, whole = tokens / kEncPartTile;
+    return {each, (whole + jobs) * split, (each + kEncPartTile - 1) / kEncPartTile * jobs * split, (whole + jobs * 3 / 4) * split};
 }
+int whole_shares(size_t n) { return (int)((n + 7) / 8 * 8 + 1); }        // for the eight XCDs; one workgroup more reports the jobs that are not valid
 
 // Shares out a plan's groups, in order, over up to kEncParts workgroups so that the largest share has as few coordinate tiles as can be, with as few
 // shares as that takes; returns the waves that takes, a coordinate tile to a wave, and at least four, or leaves enc_parts 0 where those are too many.
@@ -965,7 +964,7 @@ kvtc_status kvtc_fp8_unpack(const void* in_dev, size_t in_bytes, int64_t n_token
 struct EncodeLaunches {
     struct Bulk { int key, wgs, lds; } bulk[16];        // (a variant per row of the plans' table)
     int n_bulk;
-    struct Short { int waves, lds; } shrt[3];            // by coordinate tiles per wave; waves = 0: none
+    struct Short { int waves, lds; } shrt[3] = {};       // by coordinate tiles per wave; waves = 0: none
     PartVariant part;
     bool all_short;
     int min_rec_dwords, max_p;
@@ -975,13 +974,35 @@ struct EncodeLaunches {
 static kvtc_status launch_encode_jobs(const char* who, const EncodeLaunches& l, KernelArgs& a, kvtc_dtype dtype, hipStream_t st) {
     const bool pairs = l.shrt[2].waves == 0 && short_pairs(1, l.shrt[1].waves, l.shrt[1].lds);
     const int grid = l.all_short ? short_table_grid(a.cap, l.min_rec_dwords, a.n_jobs, pairs) : 0;
-    const int part_grid = l.part.split > 0 ? short_part_grid(a.cap, l.min_rec_dwords, a.n_jobs, l.part.split, part_places(l.part.waves, l.part.lds)) : 0;
+    // By parts: where equal jobs would run at once -- with tiles of up to 32 tokens, which the short-job kernel also codes in half the time, one to a compute unit --
+    // and so would jobs of mixed lengths; a lone share of many features in one workgroup to a compute unit, or two draw its basis in place of one.  Where jobs
+    // may be more than that, the device counts them and codes them by parts or as the short-job kernel does, if the plans and the type have that kernel.  Plans of
+    // two coordinate tiles to a wave, one workgroup of which a compute unit has room for, are faster by parts in two rounds as well.
+    // (us, the short-job launch and by parts with a workgroup for each share.  At once: 64 tensors at 16x, room for 32 tokens each, all of 31 12.6 and 9.8, 48 and 16 in
+    // turn 13.1 and 9.7; 256 heads of 16 to 48 6.4 and 5.6.  Not all at once: 128 of 256 features, 100 and 20 in turn, 7.1 and 9.5; 64 at 16x 15.1 and 16.8; in fp32 of 48 and
+    // 16 in turn 17.8 and 18.9; 128 at 40x, one share each, of 64 12.1 and 10.7, of 32 to 96, 312 shares, 12.0 and 13.1; 64 of 512 coordinates, 100 and 20 in turn, 20.2 and 18.7.
+    // Counted on the device: 64 at 16x, room for 64 tokens each, 16 coded, 12.0, 9.2 and 10.5, of 32 to 96 15.3, 16.8 and 15.7; 16 in fp32 of 100 16.8, 10.3 and 11.3.)
+    enum { kNot, kParts, kEither } by = kNot;
+    const size_t cus = (size_t)compute_units(), places = (size_t)part_places(l.part.waves, l.part.lds);
+    const PartShares ps = l.part.split > 0 ? part_shares(a.cap, l.min_rec_dwords, a.n_jobs, l.part.split) : PartShares{};
+    const size_t at_once = l.part.split == 1 && l.max_p > 512 ? cus : places;
+    if (l.part.split > 0 && a.n_jobs <= kShortTableJobs && ps.equal <= (ps.each > kEncPartTile ? at_once : std::min(at_once, cus))) {
+        const bool either = ps.each > kEncPartTile && l.part.split > 2 && l.shrt[2].waves == 0 && grid != 0 && (dtype == KVTC_BF16 || places == cus);
+        if ((either ? ps.most : ps.mixed) <= at_once || l.shrt[1].waves == 0) by = kParts;
+        else if (either) by = kEither;
+    }
     hipError_t e = hipSuccess;
-    if (part_grid != 0) {
+    a.enc_split = l.part.split;
+    if (by == kParts) {
         a.enc_table = 1;
-        a.enc_split = l.part.split;
         a.enc_max_tokens = (int32_t)(a.cap / ((size_t)l.min_rec_dwords * 4));
-        e = launch_encode_parts(a, dtype, l.part.waves, l.max_p, part_grid, (size_t)l.part.lds, st);
+        e = launch_encode_parts(a, dtype, l.part.waves, l.max_p, whole_shares(std::min(ps.most, places)), (size_t)l.part.lds, st);
+    } else if (by == kEither) {
+        a.enc_table = 1;
+        a.enc_max_tokens = (int32_t)(a.cap / ((size_t)l.min_rec_dwords * 4));
+        const int waves = std::max(l.part.waves, l.shrt[1].waves), lds = std::max(l.part.lds, l.shrt[1].lds);
+        a.enc_part_most = (int32_t)(short_pairs(1, waves, lds) ? cus * 3 / 2 : cus);
+        e = launch_encode_short(a, dtype, 1, waves, std::max(grid, whole_shares((size_t)a.enc_part_most)), (size_t)lds, st);
     } else if (grid != 0) {
         // few tokens in all: one round of the short-job kernel
         a.enc_table = 1;

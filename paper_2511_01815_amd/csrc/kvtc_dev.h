@@ -94,6 +94,7 @@ struct KernelArgs {
     int32_t enc_short_max;     // encode: jobs of at most this many tokens whose plan the short-job kernel serves may be left to it (bulk_takes_all); 0 = no job counts as short
     int32_t enc_table;         // encode of a batch: 1 = the short-job launch codes every job (short_table); 0 = it codes the short ones, a workgroup per job and tile
     int32_t enc_split;         // encode by parts: workgroups to a tile (the most of any plan; of one tensor, its plan's)
+    int32_t enc_part_most;     // encode by parts or the short-job kernel, as the jobs' lengths have it: shares of tiles, in all, up to which by parts; 0 = the launch has one form
     int32_t enc_max_tokens;    // with enc_table: a job of more tokens cannot lie inside the stream buffer
     int32_t enc_cus;           // encode of a batch: compute units (a bulk launch has this many workgroups times its plans' enc_wgs)
     int32_t dec_short;         // decode: this launch runs the one-token-tile-per-wave variant of every plan (128-token tiles)

@@ -964,6 +964,14 @@ __device__ __forceinline__ void short_tile_code(const PlanEnc& P, const TileRef&
     else encode_register_tile<NTW, XT, 2, kEncShortTile, short_ahead<NTW>(), false>(P, tr, a, smem, false);
 }
 
+// By parts: a.enc_split workgroups to a tile, each a share of its plan's groups.
+template <typename XT, int AHEAD>
+__device__ __forceinline__ void part_code(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, int part, uint4* smem) {
+    const PlanDev __attribute__((address_space(4)))* pd = (const PlanDev __attribute__((address_space(4)))*)(uintptr_t)uniform_ptr(a.plans + tr.plan);
+    if (part >= pd->enc_parts) return;
+    const EncPart ep(pd->enc_part[2 * part], pd->enc_part[2 * part + 1]);
+    encode_part_tile<XT, AHEAD>(P, ep, tr, a, smem);
+}
 // (registers for four waves a SIMD where two workgroups of eight are to share a compute unit)
 #define KVTC_SHORT_BOUNDS(NTW) __launch_bounds__(kShortThreads) __attribute__((amdgpu_waves_per_eu((NTW) == 1 ? 4 : 3)))
 template <int NTW, typename XT>
@@ -973,12 +981,31 @@ __global__ void KVTC_SHORT_BOUNDS(NTW) kvtc_encode_short_kernel(const KernelArgs
     PlanEnc P;
     if (short_tile<NTW, false>(a, blockIdx.x, tr, P)) short_tile_code<NTW, XT>(P, tr, a, smem);
 }
-template <int NTW, typename XT>
-__global__ void KVTC_SHORT_BOUNDS(NTW) kvtc_encode_small_batch_kernel(const KernelArgs args) {
+// EITHER: by parts where the jobs, whose lengths only the device knows, then are one round of workgroups.  (Counting them costs 0.3 us, and the parts have this launch's waves
+// and registers, 16 k-steps ahead: an append step of 64 tensors with room for four 10.5 us, 9.2 in a launch of their own, 12.0 as the short-job kernel.)
+template <int NTW, typename XT, bool EITHER>
+__global__ void KVTC_SHORT_BOUNDS(EITHER && sizeof(XT) == 4 ? 2 : NTW) kvtc_encode_small_batch_kernel(const KernelArgs args) {
     extern __shared__ uint4 smem[];
     if (blockIdx.x + 1u == gridDim.x) {
         if (threadIdx.x < 64) report_bad_job(args);
         return;
+    }
+    if constexpr (EITHER) {
+        uint32_t tiles = 0u;                                         // of the lane's jobs
+        for (uint32_t j = threadIdx.x & 63u; j < (uint32_t)args.n_jobs; j += 64u) {
+            const int n = args.jobs[j].n_tokens;
+            tiles += n > 0 && n <= args.enc_max_tokens ? (uint32_t)(n + kEncPartTile - 1) / kEncPartTile : 0u;
+        }
+        const uint32_t split = (uint32_t)args.enc_split, shares = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(tiles), 63) * split;
+        if (shares <= (uint32_t)args.enc_part_most) {
+            const uint32_t per_xcd = (shares + 7u) / 8u, i = blockIdx.x / 8u, number = (blockIdx.x & 7u) * per_xcd + i;
+            if (i >= per_xcd) return;
+            const ShortTable<false, kEncPartTile> t(args);
+            TileRef tr;
+            PlanEnc P;
+            if (t.find(args, number / split, tr) && short_tile<0, true, kEncPartTile>(args, 0u, tr, P)) part_code<XT, 16>(P, tr, args, (int)(number % split), smem);
+            return;
+        }
     }
     // One tile a workgroup, unless jobs overlap in the stream buffer, which is not allowed but ends all the same.  (The arguments are read
     // again for every tile, or the compiler keeps more of them through the loop than there are registers.)
@@ -1000,19 +1027,11 @@ __global__ void KVTC_SHORT_BOUNDS(NTW) kvtc_encode_small_batch_kernel(const Kern
     }
 }
 
-// The same by parts: a.enc_split workgroups to a tile, each a share of its plan's groups.
-template <typename XT, int AHEAD>
-__device__ __forceinline__ void part_code(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, int part, uint4* smem) {
-    const PlanDev __attribute__((address_space(4)))* pd = (const PlanDev __attribute__((address_space(4)))*)(uintptr_t)uniform_ptr(a.plans + tr.plan);
-    if (part >= pd->enc_parts) return;
-    const EncPart ep(pd->enc_part[2 * part], pd->enc_part[2 * part + 1]);
-    encode_part_tile<XT, AHEAD>(P, ep, tr, a, smem);
-}
 // k-steps of fragments on their way: with up to four waves a SIMD's registers are one wave's, and 32 are; with more waves 16; and hardly more than there are, which are
 // fetched all the same and keep a small call waiting.  (One token of 64, 128 and 320 features, us, 32 ahead whatever there are, 8, 8 and 16, and the short-job kernel:
 // 4.4, 4.6 and 5.1; 3.5, 3.8 and 4.5; 4.0, 4.2 and 5.0.)
 constexpr int kPartThreads = 640;
-inline int part_ahead(int waves, int p) { return p <= 8 * 16 ? 8 : waves > 4 || p < 32 * 16 ? 16 : 32; }
+inline int part_ahead(int waves, int p) { return p <= 8 * 16 ? 8 : waves > 4 || p <= 32 * 16 ? 16 : 32; }
 template <typename XT, int AHEAD>
 __global__ void __launch_bounds__(AHEAD == 32 ? 256 : kPartThreads) kvtc_encode_parts_kernel(const KernelArgs a) {
     extern __shared__ uint4 smem[];
@@ -1071,9 +1090,11 @@ hipError_t launch_encode(const KernelArgs& a, kvtc_dtype dtype, int key, int gri
 // times the jobs; ntw: coordinate tiles per wave (the plans' enc_short).
 hipError_t launch_encode_short(const KernelArgs& a, kvtc_dtype dtype, int ntw, int waves, int grid, size_t lds_bytes, hipStream_t stream) {
     const void* fn = nullptr;
-#define KVTC_X(NTW, XT) (a.enc_table ? reinterpret_cast<const void*>(&kvtc_encode_small_batch_kernel<NTW, XT>) : reinterpret_cast<const void*>(&kvtc_encode_short_kernel<NTW, XT>))
-    if (ntw == 1) fn = dtype == KVTC_BF16 ? KVTC_X(1, uint16_t) : KVTC_X(1, float);
-    if (ntw == 2) fn = dtype == KVTC_BF16 ? KVTC_X(2, uint16_t) : KVTC_X(2, float);
+#define KVTC_X(NTW, XT) (a.enc_table ? reinterpret_cast<const void*>(&kvtc_encode_small_batch_kernel<NTW, XT, false>) : reinterpret_cast<const void*>(&kvtc_encode_short_kernel<NTW, XT>))
+    if (a.enc_part_most != 0 && ntw == 1) fn = dtype == KVTC_BF16 ? reinterpret_cast<const void*>(&kvtc_encode_small_batch_kernel<1, uint16_t, true>) : reinterpret_cast<const void*>(&kvtc_encode_small_batch_kernel<1, float, true>);
+    else if (a.enc_part_most != 0) fn = nullptr;
+    else if (ntw == 1) fn = dtype == KVTC_BF16 ? KVTC_X(1, uint16_t) : KVTC_X(1, float);
+    else if (ntw == 2) fn = dtype == KVTC_BF16 ? KVTC_X(2, uint16_t) : KVTC_X(2, float);
 #undef KVTC_X
     if (!fn || waves < 2 || waves * 64 > kShortThreads) return hipErrorInvalidValue;
     hipError_t e = allow_full_lds(fn);

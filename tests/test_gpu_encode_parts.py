@@ -87,6 +87,40 @@ def test_features_on_both_sides_of_what_is_fetched_ahead(p, dtype):
     plan.close()
 
 
+@pytest.mark.parametrize("dtype,jobs_of,lens,room", [
+    (kv.KVTC_BF16, 4, [16], 4), (kv.KVTC_BF16, 4, [17, 0, 33, 5], 4),                     # room for 64 tokens a job: a share for every compute unit, and fewer
+    (kv.KVTC_BF16, 4, [48], 1), (kv.KVTC_BF16, 4, [100, 20, 64, 1], 1),                   # no room left: more shares than run at once
+    (kv.KVTC_F32, 16, [40, 7, 64, 1], 4), (kv.KVTC_F32, 16, [97, 129], 1),
+])
+def test_small_batches_whose_form_the_jobs_lengths_decide(dtype, jobs_of, lens, room):
+    """Batches that may be more shares than run at once: the kernel that counts them, on both sides of its line, in a buffer of just their records
+    and in a roomy one, and as a job more or fewer for the launches on either side of it.  The bulk kernels' bits."""
+    p = 1024
+    plan = _gpu_plan(_manual(p, [(16, 8), (16, 6), (80, 4), (64, 3), (64, 2)], 9))        # four shares
+    R, n_bulk = plan.record_bytes, bulk_tokens()
+    x = torch.randn((400, p), generator=torch.Generator(device=DEV).manual_seed(room), device=DEV).to(torch.bfloat16 if dtype == kv.KVTC_BF16 else torch.float32)
+    rows = x.repeat(n_bulk // 400 + 1, 1)[:n_bulk].contiguous()
+    bulk = torch.zeros((n_bulk, R), dtype=torch.uint8, device=DEV)
+    kv.kvtc_encode(plan.handle, rows, dtype, n_bulk, p, bulk, bulk.numel())
+    batch = kv.Batch([plan])
+    most = torch.cuda.get_device_properties(0).multi_processor_count // jobs_of
+    for n_jobs in (most, most - 1, most + 1, most // 3):
+        ns = [lens[j % len(lens)] for j in range(n_jobs)]
+        row0 = [(37 * j) % (400 - max(lens)) for j in range(n_jobs)]
+        jobs = torch.from_numpy(kv.make_jobs([0] * n_jobs, ns, row0).view(np.uint8)).to(DEV)
+        offs = torch.zeros(n_jobs + 1, dtype=torch.int64, device=DEV)
+        size = sum(ns) * R
+        out = torch.full((room * size + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+        status = torch.zeros(1, dtype=torch.int32, device=DEV)
+        kv.kvtc_offsets(batch.handle, jobs, n_jobs, offs)
+        kv.kvtc_encode_batch(batch.handle, jobs, n_jobs, x, dtype, p, offs, out, room * size, status)
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0 and torch.equal(out[:size].view(-1, R), torch.cat([bulk[a:a + n] for a, n in zip(row0, ns)])), n_jobs
+        assert bool((out[size:] == 0xA5).all()), n_jobs
+    batch.close()
+    plan.close()
+
+
 @pytest.mark.parametrize("r", [528, 560, 592, 608, 640])
 @pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
 def test_bulk_plans_of_17_to_20_tiles_leave_the_padding_out(r, dtype):
