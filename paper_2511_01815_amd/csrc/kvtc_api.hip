@@ -1220,10 +1220,12 @@ kvtc_status kvtc_decode_batch_blocked(const kvtc_batch* batch, const kvtc_job* j
                       (mean <= kDecShortTile || (mean + kDecShortTile - 1) / kDecShortTile * jobs <= few);
         const DecLayout lay = decode_layout(a.dec_short ? decode_rec_bytes(1, v.rec_dwords) : v.rec, v.ring, v.wgs);
         a.dec_ring_off = lay.ring_off;
-        // no more workgroups than there may be shares of tiles, 64 features each: every one reads the job table before it knows that it has none.  (A head of 4096
-        // tokens in fp32, 66 for 768: 7.5 -> 6.7 us, four tensors of 16 tokens at 16x 8.5 -> 7.4.)
-        const size_t shares = (tokens / kDecShortTile + jobs) * (size_t)(batch->max_p / 64);
-        hipError_t e = launch_decode(a, dtype, a.dec_short ? 100 + v.key % 100 : v.key, (int)std::min<size_t>(slots, shares), lay.lds_bytes, static_cast<hipStream_t>(stream));
+        // Where there may be few shares of tiles, 64 features each, no more workgroups than that: every one reads the job table before it knows that it has none.  Two to a
+        // tile at least, or the kernel's form for few tiles is not taken.  Of a few more than the compute units some would be two to one and others idle.  (us, all
+        // and so: a head of 4096 tokens in fp32, 66 for 768, 7.5 -> 6.7, four tensors of 16 tokens at 16x 8.5 -> 7.4, 90 heads of 64, 270, 8.3 -> 7.0, of 256 features 64 of 33,
+        // 320, 8.1 -> 7.8; not so: 128 heads of 64, 384, 6.9 7.1, 16 tensors of 16 at 40x, 288, 6.3 6.7, at 16x in fp32 8.8 10.1; one of 64 features, one workgroup, 5.0 5.4.)
+        const size_t shares = (tokens / kDecShortTile + jobs) * (size_t)std::max(batch->max_p / 64, 2), grid = shares <= (size_t)(batch->max_p <= 256 ? cus * 5 / 4 : cus) ? shares : slots;
+        hipError_t e = launch_decode(a, dtype, a.dec_short ? 100 + v.key % 100 : v.key, (int)std::min<size_t>(slots, grid), lay.lds_bytes, static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return fail(KVTC_E_HIP, "kvtc_decode_batch: launch failed: %s", hipGetErrorString(e));
     }
     return KVTC_OK;
