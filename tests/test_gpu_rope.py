@@ -124,6 +124,12 @@ def test_key_path_rotation_undone_coded_decoded_rotated_again():
     (128, 8, 3000, 0, "half", 2.0 ** 64, 31),                                     # a share's heads more than are on their way at a time
     (128, 2, 70, 1, "half", 1e4, 17), (24, 4, 70, 0, "half", 1e4, 17),            # an address, a head that whole pieces do not fit
     (64, 2, 70, 0, "interleaved", 0.9, 17),                                       # angles above the positions
+    (64, 2, 3600, 0, "interleaved", 0.9, 17), (128, 2, 1800, 1, "half", 1e4, 17), # (these and the address, with tokens enough for whole pieces)
+    (16, 1, 20001, 0, "half", 1e4, 17), (128, 1, 2500, 0, "half", 1e4, 17), (128, 1, 2499, 0, "interleaved", 1e4, 17),          # from 20000 items of eight pairs on
+    (128, 2, 1750, 0, "interleaved", 1e4, 17), (128, 3, 15, 0, "half", 1e4, 17), (128, 3, 16, 0, "half", 1e4, 17), (128, 5, 4, 0, "half", 1e4, 17),
+    (128, 6, 1, 0, "interleaved", 1e4, 17), (48, 7, 300, 0, "half", 1e4, 17),     # a row's heads over neighbouring lanes: all of them, and shares that are not equal
+    (64, 33, 130, 0, "half", 1e4, 17), (128, 17, 1100, 0, "interleaved", 1e4, 17),  # long rows
+    (16, 2, 16385, 0, "half", 1e4, 17), (32, 16, 16385, 0, "half", 1e4, 17),      # narrow heads of many tokens
 ])
 def test_whole_pieces_and_what_they_do_not_fit_bf16(d, H, T, offset, pairing, base, bits):
     """Scattered positions, token-major and heads-major.  The kernel's sine and cosine are within 1e-15, and only a value within that of a
@@ -148,3 +154,30 @@ def test_whole_pieces_and_what_they_do_not_fit_bf16(d, H, T, offset, pairing, ba
             got = _from_dev_bf16(xd).reshape(src.shape)
             got = kr.tokens_first(got) if heads_major else got
             assert np.array_equal(_bf16_bits(got), want), (inverse, heads_major, (_bf16_bits(got) != want).mean())
+
+
+@pytest.mark.parametrize("pairing", ["half", "interleaved"])
+def test_values_of_every_kind_and_positions_below_zero_bf16(pairing):
+    """NaN, infinities, zeros of both signs, subnormal and the largest numbers, at position 0 too, where an infinity meets a sine of 0; positions from below
+    zero on, by position0 and by an array.  A result is NaN where the oracle's is, and otherwise the same bits."""
+    rng = np.random.default_rng(8)
+    H, d, T = 8, 128, 600
+    bits = rng.integers(0, 65536, size=(T, H * d)).astype(np.uint16)                                     # every kind of number
+    kinds = np.array([0x7f80, 0xff80, 0x7fc0, 0xffff, 0x7f81, 0x0000, 0x8000, 0x0001, 0x807f, 0x7f7f, 0xff7f, 0x3f80], dtype=np.uint16)
+    bits[::3] = rng.choice(kinds, size=bits[::3].shape)
+    bits[1::3] = (bits[1::3] & 0x80ff)                                                                   # subnormal, and the smallest normal ones
+    x = (bits.astype(np.uint32) << 16).view(np.float32)
+    pos = np.arange(T) - 299
+    with np.errstate(all="ignore"):
+        want64 = kr.rope(x, pos, H, d, base=10000.0, pairing=pairing)
+        want = torch.from_numpy(want64.astype(np.float32)).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
+    nan = np.isnan(want64)
+    assert 0.01 < nan.mean() < 0.9 and (np.abs(want64[~nan]) < 2.0 ** -126).any()
+    for positions in (None, torch.from_numpy(pos.astype(np.int32)).to(DEV)):
+        xd = torch.from_numpy(bits.view(np.int16)).to(DEV).view(torch.bfloat16).clone()
+        kv.kvtc_rope(xd, kv.KVTC_BF16, T, H, d, H * d, d, positions, -299, 10000.0, kv.ROPE_HALF if pairing == "half" else kv.ROPE_INTERLEAVED, False)
+        torch.cuda.synchronize()
+        got = xd.view(torch.int16).cpu().numpy().view(np.uint16)
+        assert np.array_equal((got & 0x7fff) > 0x7f80, nan)
+        bad = (got != want) & ~nan
+        assert not bad.any(), (bad.sum(), x[bad][:4], got[bad][:4], want[bad][:4])
