@@ -990,17 +990,18 @@ size_t bound_of(int R, int64_t n_tokens) {
 // The shape of a launch over `n_chunks` chunks of each of n_jobs jobs.  A launch all of whose chunks can run at once does that, with
 // the fewest waves per workgroup, from four up, that allow it: the compute units share the chunks, and each of their waves has
 // more of its vector unit.  A larger one runs workgroups of 16 waves, or 8 where that lets more waves share a compute unit's LDS
-// (4 where the jobs have no more chunks).  Each wave takes as many chunks in turn (at most 16) as end soonest: every compute unit works through its
+// (4 where the jobs have no more chunks).  Each wave takes as many chunks in turn (at most in_turn) as end soonest: every compute unit works through its
 // workgroups, each of which first copies its table (64 KiB for 128-byte records, against 8 KiB of records per chunk; counted as a fifth of a round of chunks),
 // as long as every place on the chip is taken.  (Rounded down from the chunks to a place, 64 tensors of 469 chunks of 100 bytes were 320 workgroups on 256 compute units:
-// encode 178 us and 168 now, 37 of 360 of 120 bytes 130 and 102.)  Without a
+// encode 178 us and 168 now, 37 of 360 of 120 bytes 130 and 102.  The general decoder's tables of short records are small: at most eight chunks, 1000 tensors of 8000 tokens
+// of 4 bytes 79 us, 91 with sixteen.)  Without a
 // table in LDS workgroups are as small as they can be, or, with more jobs than compute units, a job (of up to 16 chunks) each: then a
 // compute unit's caches hold few tables.
 // (2188 chunks of 128-byte records, encode and decode: 75 + 102 us with four waves that took two chunks in turn on one workgroup per
 // compute unit, 45 + 31 so, 35 + 18 with the kernels as they are; 64 tensors of 63 chunks 83 + 145, 41 + 39, 39 + 26 (of 64).  Ten waves in a workgroup, two of which a
 // compute unit has room for at 128 bytes, 20 waves instead of 16, but twice the copies of the table: encode of 64 tensors of 512 chunks 211 us and 215 so.)
 struct Shape { int waves, chunks_per_wave; unsigned blocks; size_t lds; };
-Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs) {
+Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs, int in_turn = 16) {
     const int64_t total = n_chunks * n_jobs, cus = compute_units();
     auto shape = [&](int waves, int64_t per) { return Shape{waves, (int)per, (unsigned)((n_chunks + waves * per - 1) / (waves * per)), table_b + (size_t)waves * wave_b}; };
     if (table_b == 0) return shape(n_jobs > cus ? (int)std::clamp<int64_t>(n_chunks, 4, 16) : total > cus ? 2 : 1, 1);
@@ -1014,7 +1015,7 @@ Shape launch_shape(size_t table_b, size_t wave_b, int64_t n_chunks, int n_jobs) 
     for (const int w : {8, 16})
         if (n_chunks > w / 2 && places(w) > 0 && (waves == 4 || places(w) * w >= places(waves) * waves)) waves = w;
     int64_t best = 1, least = INT64_MAX;
-    for (int64_t per = 1; per <= 16; ++per) {
+    for (int64_t per = 1; per <= in_turn; ++per) {
         const int64_t to_each = ((n_chunks + waves * per - 1) / (waves * per) * n_jobs + cus - 1) / cus, cost = to_each * (5 * per + 1);
         if (per > 1 && to_each < places(waves)) break;
         if (cost < least) least = cost, best = per;
@@ -1042,15 +1043,22 @@ bool decode_in_pieces(const Shape& sh, int R, int64_t n_chunks, int n_jobs) {
 }
 
 // Whether the staged decoder, with more LDS to a workgroup, would run jobs of a few chunks in more rounds of workgroups than the other, each of which copies its
-// tables for little work.  us, the other and the staged: 1000 jobs of one chunk of 36 bytes 9.2 and 13.3, 400 of four of 100 bytes 18.6 and 24.3 (two rounds against
-// one); 300 of five of 64 bytes, as many, 19.3 and 15.4; three rounds against two, 600 of seven of 36 bytes, 17.9 and 19.7, of sixteen 36.7 and 27.4.
+// tables for little work.  (LDS is given out in pieces of 1280 bytes.)  us, the other and the staged, one round against two: 1000 jobs of one chunk of 36 bytes 9.2 and 13.3, 400 of
+// four of 100 bytes 18.6 and 24.3, of five of 64 bytes 13.4 and 15.4, 257 of seven of 36 bytes 9.7 and 12.8, of twelve 11.5 and 15.0, 400 of twelve 15.1 and 15.5, of eight
+// of 48 bytes 13.9 and 13.7; two against three, 600 of seven of 36 bytes, 17.9 and 19.7, of sixteen, three and three, 36.7 and 27.4.
 bool small_jobs_wait(const Shape& staged, const Shape& other, int64_t n_chunks, int n_jobs) {
     auto rounds = [&](const Shape& s) {
-        const int64_t places = compute_units() * std::min<int64_t>(kLdsBudget / s.lds, 32 / s.waves);
+        const int64_t places = compute_units() * std::min<int64_t>(kLdsBudget / ((s.lds + 1279) / 1280 * 1280), 32 / s.waves);
         return ((int64_t)s.blocks * n_jobs + places - 1) / places;
     };
-    return n_chunks <= 8 && rounds(staged) >= (n_chunks <= 4 ? 2 : 3) && rounds(staged) > rounds(other);
+    return n_chunks <= 12 && rounds(staged) > rounds(other);
 }
+
+// Records of less than a piece of 16 bytes gain little by the staged decoder, or lose by its larger tables where there are more jobs than compute units.
+// (us, the other and the staged: 4 bytes, a tensor of one token 3.2 and 3.6, 64 of 1000 4.7 and 5.1, of 30000 25.4 and 25.3, 1000 of 1000 14.4 and 19.3; 8 bytes 3.7 and 3.9, 5.1
+// and 5.0, 31.1 and 27.2, 16.9 and 20.8; 12 bytes 4.1 and 4.0, 5.7 and 5.5, 37.5 and 29.2, 19.8 and 22.7; 16 bytes 4.3 and 3.9, 5.9 and 4.8, 40.8 and 27.0, 21.9 and 21.1.)
+constexpr int kLogLeast = 12;
+bool log_pays(int R, int n_jobs) { return R >= 16 || (R >= kLogLeast && n_jobs <= compute_units()); }
 
 // helpers: the kernel copies tables once and lets waves that take no chunk go, so that the launch may have more of them.
 kvtc_status launch(const char* who, void (*fn)(EntropyArgs), const Shape& sh, int n_jobs, EntropyArgs a, hipStream_t st, bool helpers = false) {
@@ -1091,11 +1099,11 @@ kvtc_status run_decode(const char* who, const kvtc_entropy* e, const EntropyArgs
     if (max_chunks == 0) return KVTC_OK;
     const size_t table_b = (size_t)(R < kDecSegment ? R : kDecSegment) * kDecRow, wave_b = kChunk * kDecPitch * 4;
     const bool tab_lds = !(max_chunks <= 4 && jobs_wait(table_b, wave_b, n_jobs));
-    const Shape sh = launch_shape(tab_lds ? table_b : 0, wave_b, max_chunks, n_jobs);
+    const Shape sh = launch_shape(tab_lds ? table_b : 0, wave_b, max_chunks, n_jobs, 8);
     void (*const fn)(EntropyArgs) = !tab_lds                                        ? &entropy_decode_kernel<false, false>
                                     : decode_in_pieces(sh, R, max_chunks, n_jobs) ? &entropy_decode_kernel<true, true>
                                                                                     : &entropy_decode_kernel<true, false>;
-    const Shape staged = a.log && tab_lds ? launch_shape(log_bytes(R), kLogSlot, max_chunks, n_jobs) : Shape{};
+    const Shape staged = a.log && tab_lds && log_pays(R, n_jobs) ? launch_shape(log_bytes(R), kLogSlot, max_chunks, n_jobs) : Shape{};
     const kvtc_status rc = staged.waves && !small_jobs_wait(staged, sh, max_chunks, n_jobs) ? launch(who, &entropy_decode_staged_kernel, staged, n_jobs, a, st, true)
                                                                                            : launch(who, fn, sh, n_jobs, a, st);
     if (rc != KVTC_OK) return rc;
@@ -1137,7 +1145,7 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
         enc.resize(rows * 256);
         dec.assign(rows * kDecRow, 0);
         lim.assign(rows * 4, 0xffffffffu);
-        if (R <= kLogMost) log.resize(rows * kLogRow);
+        if (R >= kLogLeast && R <= kLogMost) log.resize(rows * kLogRow);
     } catch (const std::bad_alloc&) {
         return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: host allocation failed");
     }

@@ -103,6 +103,14 @@ def test_many_tensors_of_a_few_chunks(R, n_jobs, most):
     _check_batch(R, [lens[j % 10] for j in range(n_jobs)], 10)
 
 
+@pytest.mark.parametrize("R,n_jobs,most", [(8, 40, 130), (12, 40, 130), (12, 300, 130), (16, 300, 130), (36, 260, 385), (36, 260, 449), (36, 260, 833), (64, 300, 321), (200, 300, 130)])
+def test_both_sides_of_what_the_staged_decoder_takes(R, n_jobs, most):
+    """Records of less than 16 bytes in few jobs and in more than there are compute units; jobs of 7, 8 and 14 chunks of which the staged decoder runs one round of
+    workgroups and two; records too long for it, and strings from tables in global memory, in more jobs than compute units."""
+    lens = [most, 1, max(1, most - 64), most, 65, most - 1]
+    _check_batch(R, [lens[j % 6] for j in range(n_jobs)], 6)
+
+
 @pytest.mark.parametrize("R,T", [(128, 262_100), (200, 172_101), (256, 140_000), (576, 62_300), (576, 123_000)])
 def test_strings_read_a_piece_at_a_time(R, T):
     """One long tensor whose records, of one to four table segments, do not fit the L2s of 256 compute units, in one round and in two, and short
