@@ -205,8 +205,9 @@ __device__ __forceinline__ void stage_table(const uint32_t* src, int rows, int l
 // Bound by the table lookups: one LDS gather per byte (looked up in global memory, with a lane per token and the rows staged
 // in LDS, the same 256 MiB took 237 us; now 75).  A token's length is the difference of the running bit count at its last
 // dword and at the token's before it.
-// Records of whole 16 bytes have pieces within a record: one end at most, and rows at distances that stand in the instructions.  Bound by vector instructions and the
+// LONG: records of whole 16 bytes have pieces within a record: one end at most, and rows at distances that stand in the instructions.  Bound by vector instructions and the
 // LDS alike: 256 MiB 75 us, 80 where each dword of a piece was looked at for a record's end; of 64 tensors of 30000 tokens of 32 bytes, encode 53.3 -> 50.6.
+template <bool LONG>
 __global__ void __launch_bounds__(1024, 2) entropy_size_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = a.waves;
@@ -228,7 +229,7 @@ __global__ void __launch_bounds__(1024, 2) entropy_size_kernel(const EntropyArgs
         uint32_t token = pw.dw / pw.per_row;
         const uint32_t token_step = 256u / pw.per_row;
         const uint32_t rows_end = pw.per_row * (4u * kLenRow);
-        const bool within = pw.per_row % 4u == 0u;                   // every piece within a record
+        const bool within = LONG && pw.per_row % 4u == 0u;           // every piece within a record
         uint32_t run = 0;                                            // bits of the pieces before this step
         uint32_t w[4];
         pw.load(src, w);
@@ -237,7 +238,10 @@ __global__ void __launch_bounds__(1024, 2) entropy_size_kernel(const EntropyArgs
             const uint32_t tok0 = token;
             uint32_t s[4], row = __umul24(cur.at, 4u * kLenRow), tok = tok0, last = 0u, end_tok[4];
             auto dword_bits = [&](int j, int rows) {                 // an entry's address: the row's, and the byte, by one dot product
-                auto entry = [&](int b) { return (uint32_t)tab[__builtin_amdgcn_udot4(w[j], 1u << (8 * b), row, false) + (4 * rows + b) * kLenRow]; };
+                auto entry = [&](int b) {
+                    return LONG ? (uint32_t)tab[__builtin_amdgcn_udot4(w[j], 1u << (8 * b), row, false) + (4 * rows + b) * kLenRow]
+                                : (uint32_t)(tab + row)[((w[j] >> (8 * b)) & 0xffu) + (4 * rows + b) * kLenRow];
+                };
                 return entry(0) + entry(1) + entry(2) + entry(3);
             };
             if (within) {
@@ -448,6 +452,111 @@ __global__ void __launch_bounds__(1024) entropy_write_kernel(const EntropyArgs a
         if (lane < 4) {                                              // the last piece
             if (32u * (uint32_t)lane < carry && written + lane < n_out) out[written + lane] = img[lane];
             img[lane] = 0u;
+        }
+        wave_fence();
+    }
+}
+
+// (3) with the codes in global memory, and more jobs than compute units, whose tables push each other out of the caches: a dword's four lookups at a time, and the string's
+// dwords as they become whole.  (The form above and this one, us: 1000 jobs of 128 records of 200 bytes 91 and 84, 700 of 192 of 400 bytes 199 and 193; 64 of 4000 of 400
+// bytes, with the other two launches, 640 and 712, one of 64 43 and 46.)
+__global__ void __launch_bounds__(1024) entropy_write_global_kernel(const EntropyArgs a) {
+    extern __shared__ uint32_t lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+    const int R = a.R;
+    const JobView v = job_view(a, blockIdx.y);
+    const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
+    if (!v.ok || first >= v.n_chunks) return;
+    uint32_t* img = lds + wave * kImageDw;
+    constexpr int kRow = 256;                                        // entries from one byte position to the next
+    const uint16_t* tab = a.enc + v.table * 256;
+    for (int i = lane; i < kImageDw; i += 64) img[i] = 0u;
+    wave_fence();
+    for (int c = 0; c < a.chunks_per_wave; ++c) {
+        const int64_t chunk = first + (int64_t)c * n_waves + wave;
+        if (chunk >= v.n_chunks) break;
+        const uint32_t begin = __builtin_amdgcn_readfirstlane(v.chunk_off[chunk]), end = __builtin_amdgcn_readfirstlane(v.chunk_off[chunk + 1]);
+        if (end < begin || (uint64_t)end > v.payload_cap) continue;
+        const uint32_t n_out = (end - begin) / 4u;
+        uint32_t* out = reinterpret_cast<uint32_t*>(v.payload + begin);
+        PieceWalk pw(v.T, chunk, R);
+        const uint32_t* src = v.rec + chunk * kChunk * pw.per_row;
+        const uint32_t rows_end = pw.per_row * (4u * kRow);
+        uint32_t carry = 0, written = 0;                             // bits in img[0] left by the step before; dwords stored
+        uint32_t w[4];
+        pw.load(src, w);
+        for (uint32_t d0 = 0; d0 < pw.n_dw; d0 += 256u) {
+            // four bytes' codes together: at most 48 bits
+            uint64_t code[4];
+            uint32_t len[4], row = __umul24(pw.at, 4u * kRow), bits = 0;       // the dword's first entry in the table
+            auto codes = [&](auto whole_tag) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint16_t* e = tab + row;
+                    uint32_t ent[4], two[2], n_two[2];
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) ent[b] = e[b * kRow + ((w[j] >> (8 * b)) & 0xffu)];
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        const uint32_t l0 = ent[2 * b] >> 12;
+                        two[b] = (ent[2 * b] & 0xfffu) | ((ent[2 * b + 1] & 0xfffu) << l0);
+                        n_two[b] = l0 + (ent[2 * b + 1] >> 12);
+                    }
+                    const bool in = decltype(whole_tag)::value || pw.dw + j < pw.n_dw;
+                    code[j] = in ? (uint64_t)two[0] | ((uint64_t)two[1] << n_two[0]) : 0ull;
+                    len[j] = in ? n_two[0] + n_two[1] : 0u;
+                    bits += len[j];
+                    row += 4u * kRow;
+                    if (row == rows_end) row = 0u;
+                }
+            };
+            if (d0 + 256u <= pw.n_dw) codes(std::true_type()); else codes(std::false_type());
+            pw.next();
+            if (d0 + 256u < pw.n_dw) pw.load(src, w);                // the next step's bytes travel under this step's string
+            const uint32_t incl = wave_inclusive_scan(bits);
+            uint32_t pos = carry + incl - bits;
+            const uint32_t n_bits = carry + (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            if (bits != 0u) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t shift = pos & 31u;
+                    const uint64_t at_place = code[j] << shift;
+                    uint32_t* to = img + (pos >> 5);
+                    atomicOr(to, (uint32_t)at_place);
+                    atomicOr(to + 1, (uint32_t)(at_place >> 32));
+                    if (shift + len[j] > 64u) atomicOr(to + 2, (uint32_t)(code[j] >> 32) >> (32u - shift));
+                    pos += len[j];
+                }
+            }
+            wave_fence();
+            const uint32_t full = n_bits >> 5;                       // at most 384
+            const uint32_t rest = img[full];
+            wave_fence();
+            for (uint32_t i0 = 0; i0 <= full; i0 += 256u) {
+                const uint32_t i = i0 + 4u * lane;
+                if (i > full) break;
+                uint4* p = reinterpret_cast<uint4*>(img + i);
+                const uint4 q = *p;
+                *p = make_uint4(0u, 0u, 0u, 0u);
+                const uint32_t o = written + i;
+                if (i + 4u <= full && o + 4u <= n_out) {
+                    *reinterpret_cast<Dwords4*>(out + o) = Dwords4{{q.x, q.y, q.z, q.w}};
+                } else {
+                    const uint32_t qq[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (i + j < full && o + j < n_out) out[o + j] = qq[j];
+                }
+            }
+            wave_fence();
+            if (lane == 0) img[0] = rest;
+            wave_fence();
+            written += full;
+            carry = n_bits & 31u;
+        }
+        if (lane == 0) {                                             // the last, partly filled dword
+            if (carry != 0u && written < n_out) out[written] = img[0];
+            img[0] = 0u;
         }
         wave_fence();
     }
@@ -1076,13 +1185,18 @@ kvtc_status run_encode(const char* who, const kvtc_entropy* e, const EntropyArgs
     EntropyArgs a = a_in;
     a.max_tokens = max_tokens;
     kvtc_status rc = KVTC_OK;
-    if (max_chunks > 0) rc = launch(who, &entropy_size_kernel, launch_shape((size_t)R * kLenRow, kChunk * 4, max_chunks, n_jobs), n_jobs, a, st, true);
+    if (max_chunks > 0) {
+        // (of long records with a chunk to a wave, where a workgroup's copy of the table and the kernel's first pass through the code are most of it, the plain form: 1000 jobs
+        // of 128 records of 200 bytes 18.9 us, 21.9 in the other, 700 of 192 of 400 bytes 44 and 50; of 32768 of 128 bytes 80 and 75, one of 64 of 256 bytes, all three launches, 26.5 and 25.5)
+        const Shape sh = launch_shape((size_t)R * kLenRow, kChunk * 4, max_chunks, n_jobs);
+        rc = launch(who, sh.chunks_per_wave > 1 || R <= 128 || max_chunks * n_jobs <= 2 * compute_units() ? &entropy_size_kernel<true> : &entropy_size_kernel<false>, sh, n_jobs, a, st, true);
+    }
     if (rc != KVTC_OK) return rc;
     hipLaunchKernelGGL(entropy_scan_kernel, dim3((unsigned)n_jobs), dim3(max_chunks <= 64 ? 64 : max_chunks <= 256 ? 256 : 1024), 0, st, a);
     if (max_chunks > 0) {
         const bool tab_lds = R <= kMaxLdsRecord &&
                              !(max_chunks <= 2 && jobs_wait((size_t)R * kEncRow, kImageDw * 4, n_jobs));
-        rc = launch(who, tab_lds ? &entropy_write_kernel<true> : &entropy_write_kernel<false>,
+        rc = launch(who, tab_lds ? &entropy_write_kernel<true> : n_jobs > compute_units() ? &entropy_write_global_kernel : &entropy_write_kernel<false>,
                     launch_shape(tab_lds ? (size_t)R * kEncRow : 0, kImageDw * 4, max_chunks, n_jobs), n_jobs, a, st, tab_lds);
         if (rc != KVTC_OK) return rc;
     }
