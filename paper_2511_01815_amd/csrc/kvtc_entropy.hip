@@ -1259,9 +1259,12 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
         enc.resize(rows * 256);
         dec.assign(rows * kDecRow, 0);
         lim.assign(rows * 4, 0xffffffffu);
-        if (R >= kLogLeast && R <= kLogMost) log.resize(rows * kLogRow);
     } catch (const std::bad_alloc&) {
         return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: host allocation failed");
+    }
+    try {
+        if (R >= kLogLeast && R <= kLogMost) log.resize(rows * kLogRow);
+    } catch (const std::bad_alloc&) {                           // (the other decoder needs none of it)
     }
     for (size_t k = 0; k < rows; ++k) {
         const uint8_t* L = code_len_host + k * 256;
@@ -1309,12 +1312,17 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
         }
     }
     // one allocation: codes, the decoders' tables and limits, lengths
-    const size_t enc_b = enc.size() * 2, dec_b = dec.size(), lim_b = lim.size() * 4, len_b = rows * 256, log_b = log.size();
+    const size_t enc_b = enc.size() * 2, dec_b = dec.size(), lim_b = lim.size() * 4, len_b = rows * 256, least_b = enc_b + dec_b + lim_b + len_b;
     char* blob = nullptr;
-    if (hipMalloc(reinterpret_cast<void**>(&blob), enc_b + dec_b + lim_b + len_b + log_b) != hipSuccess) {
+    if (!log.empty() && hipMalloc(reinterpret_cast<void**>(&blob), least_b + log.size()) != hipSuccess) {
         (void)hipGetLastError();
-        return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: hipMalloc of %zu bytes failed", enc_b + dec_b + lim_b + len_b + log_b);
+        log.clear();                                            // no room for the staged decoder's: the other decoder serves these records
     }
+    if (log.empty() && hipMalloc(reinterpret_cast<void**>(&blob), least_b) != hipSuccess) {
+        (void)hipGetLastError();
+        return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: hipMalloc of %zu bytes failed", least_b);
+    }
+    const size_t log_b = log.size();
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = hipSuccess;
     size_t at = 0;

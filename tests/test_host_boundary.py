@@ -349,3 +349,13 @@ def test_addresses_of_every_kind_and_no_exception_for_a_plain_integer():
     for t in ("address", 1.5, np.int64(8)):
         with pytest.raises(AttributeError):
             binding._ptr(t)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the device has room for the tables")
+def test_entropy_tables_are_asked_for_without_the_staged_decoders_before_they_are_refused():
+    """The staged decoder's tables, as much again as all others, are left out where they do not fit; what is refused is the memory that records cannot do without."""
+    R = 64
+    with pytest.raises(kv.KvtcError) as e:
+        kv.kvtc_entropy_create(R, np.full((R, 256), 8, dtype=np.uint8), stream=0)
+    codes, decoder, limits, lengths = 512, 256 + 256 + 16, 16, 256
+    assert f"hipMalloc of {R * (codes + decoder + limits + lengths)} bytes failed" in str(e.value)
