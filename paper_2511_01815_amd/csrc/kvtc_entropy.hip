@@ -23,6 +23,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <type_traits>
 #include <vector>
@@ -1068,11 +1069,7 @@ __global__ void __launch_bounds__(1024) entropy_decode_staged_kernel(const Entro
     }
 }
 
-uint32_t reverse_bits(uint32_t v, int n) {
-    uint32_t r = 0;
-    for (int i = 0; i < n; ++i) { r = (r << 1) | (v & 1u); v >>= 1; }
-    return r;
-}
+uint32_t reverse_bits(uint32_t v, int n) { return __builtin_bitreverse32(v) >> (32 - n); }      // n from 1 up
 
 // 32 - length by the float index of u, for a complete code with count[L] codes of L bits.  (Length by length, not entry by entry: 64 tensors' tables of 128
 // positions would take 4 ms more to create.)
@@ -1251,21 +1248,14 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
     if (R > kMaxRecord) return set_error(KVTC_E_UNSUPPORTED, "kvtc_entropy_create: record_bytes=%d above %d", R, kMaxRecord);
     if (n_tables < 1 || n_tables > 4096) return set_error(KVTC_E_ARG, "kvtc_entropy_create: n_tables=%d outside 1..4096", n_tables);
     const size_t rows = (size_t)n_tables * R;
-    std::vector<uint16_t> enc;
-    std::vector<uint8_t> dec;
-    std::vector<uint32_t> lim;
-    std::vector<uint8_t> log;
-    try {
-        enc.resize(rows * 256);
-        dec.assign(rows * kDecRow, 0);
-        lim.assign(rows * 4, 0xffffffffu);
-    } catch (const std::bad_alloc&) {
-        return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: host allocation failed");
-    }
-    try {
-        if (R >= kLogLeast && R <= kLogMost) log.resize(rows * kLogRow);
-    } catch (const std::bad_alloc&) {                           // (the other decoder needs none of it)
-    }
+    // (not cleared first, which for 64 tables of 128 positions is a millisecond: all of it is written below)
+    const size_t enc_b = rows * 512, dec_b = rows * kDecRow, lim_b = rows * 16, len_b = rows * 256;
+    size_t log_b = R >= kLogLeast && R <= kLogMost ? rows * kLogRow : 0;
+    const std::unique_ptr<uint16_t[]> enc(new (std::nothrow) uint16_t[rows * 256]);
+    const std::unique_ptr<uint8_t[]> dec(new (std::nothrow) uint8_t[dec_b]), log(log_b ? new (std::nothrow) uint8_t[log_b] : nullptr);
+    const std::unique_ptr<uint32_t[]> lim(new (std::nothrow) uint32_t[rows * 4]);
+    if (!enc || !dec || !lim) return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: host allocation failed");
+    if (!log) log_b = 0;                                            // (the other decoder needs none of it)
     for (size_t k = 0; k < rows; ++k) {
         const uint8_t* L = code_len_host + k * 256;
         // canonical codes: by length, then by symbol (RFC 1951, section 3.2.2); Kraft's inequality must hold
@@ -1278,6 +1268,8 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
         uint32_t kraft = 0, next[kMaxLen + 1], rank[kMaxLen + 1], code = 0, shorter = 0;
         uint8_t *D = &dec[k * 256], *S = &dec[(rows + k) * 256], *O = &dec[rows * 512 + k * kDecOff];      // lengths, symbols, offsets
         int least = 9;                                              // what the table says for codes of 9 bits or more
+        memset(O, 0, kDecOff);
+        for (int i = 0; i < 4; ++i) lim[k * 4 + i] = 0xffffffffu;
         for (int len = 1; len <= kMaxLen; ++len) {
             kraft += count[len] << (kMaxLen - len);
             next[len] = code;                                       // first code of this length, and its rank
@@ -1291,7 +1283,7 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
             }
             code <<= 1;
         }
-        if (kraft != (1u << kMaxLen)) log.clear();
+        if (kraft != (1u << kMaxLen)) log_b = 0;
         if (kraft > (1u << kMaxLen))
             return set_error(KVTC_E_ARG, "kvtc_entropy_create: table %d, position %d: the lengths are not those of a prefix code", (int)(k / R), (int)(k % R));
         memset(D, least, 256);
@@ -1303,26 +1295,25 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
             if (len <= 8)
                 for (uint32_t i = rev; i < 256u; i += 1u << len) D[i] = (uint8_t)len;
         }
-        if (!log.empty()) {
+        if (log_b != 0) {
             uint8_t* const set = &log[k / R * R * kLogRow];
             const size_t pos = k % R;
             memcpy(set + pos * 256, S, 256);
-            for (int len = 1; len <= kMaxLen; ++len) set[(size_t)R * 256 + pos * kDecOff + 16 - len] = O[len];
+            for (int len = 1; len <= kDecOff; ++len) set[(size_t)R * 256 + pos * kDecOff + 16 - len] = len <= kMaxLen ? O[len] : 0;
             log_lengths(count, set + (size_t)R * (256 + kDecOff) + pos * kLogEntries);
         }
     }
     // one allocation: codes, the decoders' tables and limits, lengths
-    const size_t enc_b = enc.size() * 2, dec_b = dec.size(), lim_b = lim.size() * 4, len_b = rows * 256, least_b = enc_b + dec_b + lim_b + len_b;
+    const size_t least_b = enc_b + dec_b + lim_b + len_b;
     char* blob = nullptr;
-    if (!log.empty() && hipMalloc(reinterpret_cast<void**>(&blob), least_b + log.size()) != hipSuccess) {
+    if (log_b != 0 && hipMalloc(reinterpret_cast<void**>(&blob), least_b + log_b) != hipSuccess) {
         (void)hipGetLastError();
-        log.clear();                                            // no room for the staged decoder's: the other decoder serves these records
+        log_b = 0;                                                  // no room for the staged decoder's: the other decoder serves these records
     }
-    if (log.empty() && hipMalloc(reinterpret_cast<void**>(&blob), least_b) != hipSuccess) {
+    if (log_b == 0 && hipMalloc(reinterpret_cast<void**>(&blob), least_b) != hipSuccess) {
         (void)hipGetLastError();
         return set_error(KVTC_E_NOMEM, "kvtc_entropy_create: hipMalloc of %zu bytes failed", least_b);
     }
-    const size_t log_b = log.size();
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = hipSuccess;
     size_t at = 0;
@@ -1332,11 +1323,11 @@ kvtc_status kvtc_entropy_create(kvtc_entropy** out, int record_bytes, int n_tabl
         at += n;
         return dst;
     };
-    const char* enc_d = put(enc.data(), enc_b);
-    const char* lim_d = put(lim.data(), lim_b);
-    const char* dec_d = put(dec.data(), dec_b);
+    const char* enc_d = put(enc.get(), enc_b);
+    const char* lim_d = put(lim.get(), lim_b);
+    const char* dec_d = put(dec.get(), dec_b);
     const char* len_d = put(code_len_host, len_b);
-    const char* log_d = log_b ? put(log.data(), log_b) : nullptr;
+    const char* log_d = log_b ? put(log.get(), log_b) : nullptr;
     if (e == hipSuccess) e = hipStreamSynchronize(st);           // the host images die with this call
     kvtc_entropy* h = e == hipSuccess ? new (std::nothrow) kvtc_entropy : nullptr;
     if (!h) {
