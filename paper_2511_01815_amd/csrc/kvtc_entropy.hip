@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <memory>
 #include <new>
@@ -37,7 +38,7 @@ using namespace kvtc;
 
 struct kvtc_entropy {
     int record_bytes, n_tables;
-    void* blob;                 // device: the four tables below
+    void* blob;                 // device: the tables below
     const uint16_t* enc_dev;    // [n_tables][R][256] reversed code | length << 12
     const uint8_t* len_dev;     // [n_tables][R][256] length
     const uint8_t* dec_dev;     // the decoder's tables, one behind the other, each [n_tables][R]: lengths, symbols, offsets
@@ -846,9 +847,9 @@ __global__ void __launch_bounds__(1024) entropy_decode_kernel(const EntropyArgs 
 // whole lines, past the caches (they pushed the strings out of the L2s that are read up to four times).  A wave takes four codes from a window of 64 bits, and looks
 // up four symbols meanwhile.  Bound by the LDS, 3.9 reads to a symbol and in use for half of the time, with four waves to a SIMD, as many as the strings leave room
 // for, that wait for each other's lookups.
-// 256 MiB of records of 128 bytes: 264 us by the form above, 162 so (192 with 64-byte pieces of rows and windows of two codes, 171 with stores that the
-// caches keep); 64 tensors of 30000 tokens of 100 bytes 292 and 117; one of 64 tokens 16 and 13, with waves that help to copy the tables 11.  (With a reader behind it that finds 30 to 125 MB of
-// records in the caches, the pair gains nothing by the stores past them, and loses 2 %.)
+// 256 MiB of records of 128 bytes: 264 us by the form above, 162 to 175 so, by the card (192 with 64-byte pieces of rows and windows of two codes); 64 tensors of 30000 tokens of 100
+// bytes 292 and 117; one of 64 tokens 16 and 13, with waves that help to copy the tables 11.  With stores that the caches keep: 256 MiB 196 for 185, 64 MiB 51.2 49.6, 32 MiB 29.5
+// 27.5, 1 MiB 12.1 11.9; and with kvtc_decode_batch behind it, which reads the records again: 1442 1442, 379 348, 167 169, 22.2 22.3 (16 and 128 MiB 88 91, 716 734).
 template <int N> using row_of = std::integral_constant<int, N>;
 __global__ void __launch_bounds__(1024) entropy_decode_staged_kernel(const EntropyArgs a) {
     extern __shared__ uint32_t lds[];
@@ -859,7 +860,7 @@ __global__ void __launch_bounds__(1024) entropy_decode_staged_kernel(const Entro
     const uint32_t R = (uint32_t)a.R, per_row = R / 4u;
     const JobView v = job_view(a, blockIdx.y);
     const int64_t first = (int64_t)blockIdx.x * n_waves * a.chunks_per_wave;
-    if (!v.ok || first >= v.n_chunks || lds_offset(lds) != 0u) return;         // (there is no other LDS: the tables are at 0)
+    if (!v.ok || first >= v.n_chunks) return;
     const uint32_t slot = (uint32_t)log_bytes((int)R) + wave * kLogSlot, slot_bit = slot / 8u, lane4 = lane * 4u;
 
     // the chunk being decoded: its string less a dword, the last dword of the payload from its first on; the slot's first dword
@@ -1160,6 +1161,14 @@ bool small_jobs_wait(const Shape& staged, const Shape& other, int64_t n_chunks, 
     return n_chunks <= 12 && rounds(staged) > rounds(other);
 }
 
+// The staged decoder's tables begin at the LDS's address 0: a build that gave the kernel LDS of its own in front of what a launch asks for must not run it.
+bool staged_lds_at_zero() {
+    static std::atomic<bool> seen{false};
+    hipFuncAttributes attr;
+    if (!seen && hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&entropy_decode_staged_kernel)) == hipSuccess && attr.sharedSizeBytes == 0) seen = true;
+    return seen;
+}
+
 // Records of less than a piece of 16 bytes gain little by the staged decoder, or lose by its larger tables where there are more jobs than compute units.
 // (us, the other and the staged: 4 bytes, a tensor of one token 3.2 and 3.6, 64 of 1000 4.7 and 5.1, of 30000 25.4 and 25.3, 1000 of 1000 14.4 and 19.3; 8 bytes 3.7 and 3.9, 5.1
 // and 5.0, 31.1 and 27.2, 16.9 and 20.8; 12 bytes 4.1 and 4.0, 5.7 and 5.5, 37.5 and 29.2, 19.8 and 22.7; 16 bytes 4.3 and 3.9, 5.9 and 4.8, 40.8 and 27.0, 21.9 and 21.1.)
@@ -1214,7 +1223,7 @@ kvtc_status run_decode(const char* who, const kvtc_entropy* e, const EntropyArgs
     void (*const fn)(EntropyArgs) = !tab_lds                                        ? &entropy_decode_kernel<false, false>
                                     : decode_in_pieces(sh, R, max_chunks, n_jobs) ? &entropy_decode_kernel<true, true>
                                                                                     : &entropy_decode_kernel<true, false>;
-    const Shape staged = a.log && tab_lds && log_pays(R, n_jobs) ? launch_shape(log_bytes(R), kLogSlot, max_chunks, n_jobs) : Shape{};
+    const Shape staged = a.log && tab_lds && log_pays(R, n_jobs) && staged_lds_at_zero() ? launch_shape(log_bytes(R), kLogSlot, max_chunks, n_jobs) : Shape{};
     const kvtc_status rc = staged.waves && !small_jobs_wait(staged, sh, max_chunks, n_jobs) ? launch(who, &entropy_decode_staged_kernel, staged, n_jobs, a, st, true)
                                                                                            : launch(who, fn, sh, n_jobs, a, st);
     if (rc != KVTC_OK) return rc;
