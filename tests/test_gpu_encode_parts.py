@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2511_01815_amd as kv
-from test_gpu_encode_short import bulk_tokens
+from test_gpu_encode_short import bulk_tokens, short_tokens
 from test_gpu_parity import DEV, _gpu_plan, _manual
 
 pytestmark = pytest.mark.gpu
@@ -19,7 +19,7 @@ PLANS = {"odd blocks": [(16, 3), (48, 5), (16, 1), (80, 7), (16, 2), (96, 3)], "
 @pytest.mark.parametrize("name", sorted(PLANS))
 @pytest.mark.parametrize("p,dtype", [(1024, kv.KVTC_BF16), (320, kv.KVTC_F32), (1088, kv.KVTC_BF16), (1152, kv.KVTC_F32)])
 def test_shares_of_groups_are_coded_as_whole_tiles(name, p, dtype):
-    """1152 features in fp32 are more than the LDS holds of 32 tokens: no shares there either."""
+    """1152 features in fp32 are the most of which the LDS holds 32 tokens."""
     groups = PLANS[name]
     if sum(n for n, _ in groups) > p:
         pytest.skip("more coordinates than features")
@@ -124,7 +124,8 @@ def test_small_batches_whose_form_the_jobs_lengths_decide(dtype, jobs_of, lens, 
 @pytest.mark.parametrize("r", [528, 560, 592, 608, 640])
 @pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
 def test_bulk_plans_of_17_to_20_tiles_leave_the_padding_out(r, dtype):
-    """Whole tiles and a half, shared out over four waves as 5 and 4: the short-job kernels' bits, which a call of a tile or two takes."""
+    """Whole tiles and a half, shared out over four waves as 5 and 4: the bits of a call of 130 tokens, which is coded by parts, and of one that is too long for
+    that and not for the short-job kernel."""
     plan = _gpu_plan(_manual(1024, [(16, 8), (r - 144, 3), (128, 2)], r))
     R, n_bulk = plan.record_bytes, bulk_tokens()
     x = torch.randn((130, 1024), generator=torch.Generator(device=DEV).manual_seed(r), device=DEV).to(torch.bfloat16 if dtype == kv.KVTC_BF16 else torch.float32)
@@ -135,4 +136,43 @@ def test_bulk_plans_of_17_to_20_tiles_leave_the_padding_out(r, dtype):
     kv.kvtc_encode(plan.handle, rows, dtype, n_bulk, 1024, got, got.numel())
     torch.cuda.synchronize()
     assert torch.equal(got, want.repeat(n_bulk // 130 + 1, 1)[:n_bulk])
+    n_short = short_tokens() + 33
+    got = torch.zeros((n_short, R), dtype=torch.uint8, device=DEV)
+    kv.kvtc_encode(plan.handle, rows, dtype, n_short, 1024, got, got.numel())
+    torch.cuda.synchronize()
+    assert torch.equal(got, want.repeat(n_short // 130 + 1, 1)[:n_short])
     plan.close()
+
+
+@pytest.mark.parametrize("p,dtype", [(1216, kv.KVTC_F32), (2560, kv.KVTC_BF16)])
+def test_more_features_than_the_lds_holds_of_32_tokens_are_not_shared_out(p, dtype):
+    """Groups that can be shared out, of a plan too wide for it: alone, and in a batch beside a plan that is not (no job of which may be coded by parts then)."""
+    groups = PLANS["wide codes"]
+    narrow = {kv.KVTC_F32: 1152, kv.KVTC_BF16: 1024}[dtype]
+    plans = [_gpu_plan(_manual(p, groups, 6)), _gpu_plan(_manual(narrow, groups, 7))]
+    n_bulk = bulk_tokens()
+    x = torch.randn((100, p), generator=torch.Generator(device=DEV).manual_seed(p), device=DEV).to(torch.bfloat16 if dtype == kv.KVTC_BF16 else torch.float32)
+    rows, bulk = x.repeat(n_bulk // 100 + 1, 1)[:n_bulk].contiguous(), []
+    for plan in plans:
+        out = torch.zeros((n_bulk, plan.record_bytes), dtype=torch.uint8, device=DEV)
+        kv.kvtc_encode(plan.handle, rows, dtype, n_bulk, p, out, out.numel())
+        bulk.append(out[:100])
+    for plan, want in zip(plans, bulk):
+        for n in (1, 32, 97):
+            got = torch.zeros((n, plan.record_bytes), dtype=torch.uint8, device=DEV)
+            kv.kvtc_encode(plan.handle, x, dtype, n, p, got, got.numel())
+            torch.cuda.synchronize()
+            assert torch.equal(got, want[:n]), n
+    batch = kv.Batch(plans)
+    which, ns, row0 = [0, 1, 1, 0], [16, 16, 33, 5], [0, 20, 40, 90]
+    jobs = torch.from_numpy(kv.make_jobs(which, ns, row0).view(np.uint8)).to(DEV)
+    offs = torch.zeros(5, dtype=torch.int64, device=DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=DEV)
+    out = torch.zeros(sum(n * plans[w].record_bytes for n, w in zip(ns, which)), dtype=torch.uint8, device=DEV)
+    kv.kvtc_offsets(batch.handle, jobs, 4, offs)
+    kv.kvtc_encode_batch(batch.handle, jobs, 4, x, dtype, p, offs, out, out.numel(), status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0 and torch.equal(out, torch.cat([bulk[w][a:a + n].reshape(-1) for w, n, a in zip(which, ns, row0)]))
+    batch.close()
+    for plan in plans:
+        plan.close()

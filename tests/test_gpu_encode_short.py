@@ -16,6 +16,13 @@ def bulk_tokens():
     every compute unit, the most that the short-job kernel is given."""
     return 2 * 64 * torch.cuda.get_device_properties(0).multi_processor_count + 200
 
+
+def short_tokens():
+    """Tokens of a tensor that the short-job kernel codes whatever its plan (of up to 640 coordinates) and type, with up to 64 times the compute units less
+    this more: more shares of 32-token tiles than one and a half for every compute unit, the most that are coded by parts, and no more 64-token tiles than compute units."""
+    return 48 * torch.cuda.get_device_properties(0).multi_processor_count + 64
+
+
 WIDE = {64: [(32, 4)], 192: [(16, 8), (64, 4), (16, 2)], 320: [(64, 5), (96, 3)], 448: [(128, 5), (128, 3)], 1024: [(16, 8), (64, 5), (128, 3), (112, 2)],
         1088: [(64, 6), (256, 3), (64, 2)], 1152: [(256, 4), (240, 3)], 2048: [(64, 12), (512, 3), (64, 2)], 832: [(256, 3), (512, 1)]}
 
@@ -23,6 +30,9 @@ WIDE = {64: [(32, 4)], 192: [(16, 8), (64, 4), (16, 2)], 320: [(64, 5), (96, 3)]
 @pytest.mark.parametrize("p", sorted(WIDE))
 @pytest.mark.parametrize("dtype", [kv.KVTC_BF16, kv.KVTC_F32])
 def test_short_jobs_are_coded_as_long_ones(p, dtype):
+    """Single calls of up to 200 tokens and the batch of 16 jobs go by parts where the plan's groups can be shared out and X fits the LDS (not of 2048 features in fp32);
+    the single calls of short_tokens() and more, with last tiles of 1, 31, 32, 33 and 63 tokens, are the short-job kernel's, and so are the batches of more jobs
+    than compute units have places for by parts."""
     plan = _gpu_plan(_manual(p, WIDE[p], 11))
     other = _gpu_plan(_manual(p, [(16, 6)], 12))                 # a narrow plan in the same launch
     R, T = plan.record_bytes, 200
@@ -61,6 +71,17 @@ def test_short_jobs_are_coded_as_long_ones(p, dtype):
         kv.kvtc_encode(plan.handle, x, dtype, n, p, got, got.numel())
         torch.cuda.synchronize()
         assert torch.equal(got, bulk[:n]), (p, n, "single call")
+    for n_jobs in (150, 300):                                    # (300: of plans of up to 256 coordinates)
+        which, ns, at = [j % 2 for j in range(n_jobs)], [lens[j // 2 % 7] for j in range(n_jobs)], [row0[j // 2 % 7] for j in range(n_jobs)]
+        out, offs = coded(which, ns, at)
+        for j in range(0, n_jobs, 2):
+            assert torch.equal(out[offs[j]:offs[j] + ns[j] * R].view(ns[j], R), bulk[at[j]:at[j] + ns[j]]), (p, n_jobs, j)
+    longer = base.repeat((short_tokens() + 63) // T + 1, 1)
+    for n in (short_tokens() + k for k in (1, 31, 32, 33, 63)):
+        got = torch.zeros((n, R), dtype=torch.uint8, device=DEV)
+        kv.kvtc_encode(plan.handle, longer, dtype, n, p, got, got.numel())
+        torch.cuda.synchronize()
+        assert torch.equal(got, bulk.repeat(n // T + 1, 1)[:n]), (p, n, "longer call")
     if p % 64 == 0 and p > 64:
         heads = x.view(T, p // 64, 64).permute(1, 0, 2).contiguous()
         got = torch.zeros((T, R), dtype=torch.uint8, device=DEV)

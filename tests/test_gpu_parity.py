@@ -329,10 +329,11 @@ def _variant_data(T, seed):
 def test_every_kernel_variant_in_every_form(r):
     """Each padded width has a bulk and a short-job encode kernel and a two-tile and a one-tile decode kernel, each
     with its own LDS ring, stage and wait-count constants.  Three forms reach them all:
-      (a) a single call of 50 tokens: the short-job encode variant (where the width has one) and the one-tile decode;
+      (a) a single call of 50 tokens: the encode by parts where the plan's groups can be shared out, else the short-job variant (where the width has
+          one; longer calls for it: test_gpu_encode_short.py), and the one-tile decode;
       (b) a single call too long for the short-job path (more 64-token tiles than workgroup slots): bulk encode
           through the single-tensor arguments, checked on sampled rows and, whole, against form (c);
-      (c) a batch with jobs of 300, 70 and 5 tokens: the short-job encode kernel through a job table (where the width has one),
+      (c) a batch with jobs of 300, 70 and 5 tokens: the same encode kernels through a job table (where the width has one),
           bulk decode.  (Bulk encode in fp32 and beside short jobs: test_gpu_encode_short.py.)"""
     oplan = _variant_plan(r)
     plan = _gpu_plan(oplan)

@@ -7,7 +7,7 @@ import torch
 import kvtc_oracle as ko
 import paper_2511_01815_amd as kv
 import test_gpu_encode_short as es
-from test_gpu_encode_short import bulk_tokens
+from test_gpu_encode_short import bulk_tokens, short_tokens
 from test_gpu_parity import DEV, _gpu_plan
 
 pytestmark = pytest.mark.gpu
@@ -49,7 +49,7 @@ def test_records_of_known_coefficients(groups):
     shift[-1], scale[-1], codes[-1] = np.float16(65504.0), np.float16(-65504.0), 0
     want[-1] = ko.pack(oplan, shift[-1:], scale[-1:], codes[-1:])
     x_dev = torch.from_numpy(x).to(DEV)
-    for tokens in (n, T):                                        # the short-job kernel, the bulk kernel
+    for tokens in (n, short_tokens() + 33, T):                   # by parts, the short-job kernel, the bulk kernel
         for dtype, src in ((kv.KVTC_F32, x_dev), (kv.KVTC_BF16, x_dev.to(torch.bfloat16))):
             src = src.repeat(tokens // n + 1, 1)[:tokens].contiguous()
             out = torch.zeros((tokens, plan.record_bytes), dtype=torch.uint8, device=DEV)
@@ -91,7 +91,8 @@ def test_records_of_known_coefficients_in_every_kernel(p, r, tokens):
     assert saturated[:n].any() and not saturated[n:].any()
     x_dev = torch.from_numpy(x).to(DEV)
     for dtype, src in ((kv.KVTC_BF16, x_dev.to(torch.bfloat16)), (kv.KVTC_F32, x_dev)):
-        for T in (tokens, 3 * n):                                 # the bulk kernel, several tiles to a workgroup; where there is one, the short-job kernel
+        # the bulk kernel, several tiles to a workgroup; where there is one, the short-job kernel; by parts, or the short-job kernel where the groups are too many tiles for that
+        for T in (tokens, short_tokens() + 31, 3 * n):
             rows = src.repeat(T // (3 * n) + 1, 1)[:T].contiguous()
             out = torch.zeros((T, plan.record_bytes), dtype=torch.uint8, device=DEV)
             kv.kvtc_encode(plan.handle, rows, dtype, T, p, out, out.numel())
