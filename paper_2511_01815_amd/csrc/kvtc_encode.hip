@@ -661,7 +661,7 @@ __device__ __forceinline__ void encode_register_tile(const PlanEnc& P, const Til
     auto fetch = [&](int step, int slot) {
         const global_ptr src = (global_ptr)(vg + (uint64_t)(uint32_t)min(step, n_steps - 1) * (uint64_t)(uint32_t)(ntp * 1024));      // a scalar address
 #pragma unroll
-        for (int i = 0; i < NTW; ++i) af[slot][i] = *(global_u4)(src + (uint32_t)(lane * 16) + i * 1024);
+        for (int i = 0; i < NTW; ++i) af[slot][i] = *(global_u4)(src + (uint32_t)(lane * 16) + (NTW <= 2 || BULK ? i : min(i, max(n_ct - 1, 0))) * 1024);      // (two tiles to a wave are whole pairs)
     };
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k) fetch(k, k);
@@ -958,10 +958,10 @@ __device__ __forceinline__ bool short_tile(const KernelArgs& a, uint32_t number,
     }
     return true;
 }
-template <int NTW, typename XT>
+template <int NTW, typename XT, int AHEAD = short_ahead<NTW>()>
 __device__ __forceinline__ void short_tile_code(const PlanEnc& P, const TileRef& tr, const KernelArgs& a, uint4* smem) {
-    if (tr.n_tokens - tr.tile * kEncShortTile <= 32) encode_register_tile<NTW, XT, 1, kEncShortTile, short_ahead<NTW>(), false>(P, tr, a, smem, false);
-    else encode_register_tile<NTW, XT, 2, kEncShortTile, short_ahead<NTW>(), false>(P, tr, a, smem, false);
+    if (tr.n_tokens - tr.tile * kEncShortTile <= 32) encode_register_tile<NTW, XT, 1, kEncShortTile, AHEAD, false>(P, tr, a, smem, false);
+    else encode_register_tile<NTW, XT, 2, kEncShortTile, AHEAD, false>(P, tr, a, smem, false);
 }
 
 // By parts: a.enc_split workgroups to a tile, each a share of its plan's groups.
@@ -981,16 +981,17 @@ __global__ void KVTC_SHORT_BOUNDS(NTW) kvtc_encode_short_kernel(const KernelArgs
     PlanEnc P;
     if (short_tile<NTW, false>(a, blockIdx.x, tr, P)) short_tile_code<NTW, XT>(P, tr, a, smem);
 }
-// EITHER: by parts where the jobs, whose lengths only the device knows, then are one round of workgroups.  (Counting them costs 0.3 us, and the parts have this launch's waves
-// and registers, 16 k-steps ahead: an append step of 64 tensors with room for four 10.5 us, 9.2 in a launch of their own, 12.0 as the short-job kernel.)
-template <int NTW, typename XT, bool EITHER>
-__global__ void KVTC_SHORT_BOUNDS(EITHER && sizeof(XT) == 4 ? 2 : NTW) kvtc_encode_small_batch_kernel(const KernelArgs args) {
+// EITHER: by parts where the jobs, whose lengths only the device knows, then are one round of workgroups.  With the launch's waves and registers, 16 k-steps ahead (1); of plans
+// whose shares are of up to four coordinate tiles, with the four waves and 32 k-steps of the parts, and the short jobs' tiles by two or three to a wave (2).  (An append step of
+// 64 tensors at 16x with room for four: 12.0 us as the short-job kernel, 10.5 (1), 9.3 (2), 9.2 in a launch of its own that does not count; of 32 to 96 tokens 15.3, 15.7, 15.5 and 16.8.)
+template <int NTW, typename XT, int EITHER>
+__global__ void __launch_bounds__(EITHER == 2 ? 256 : kShortThreads) __attribute__((amdgpu_waves_per_eu(EITHER == 2 ? 2 : NTW == 1 && !(EITHER == 1 && sizeof(XT) == 4) ? 4 : 3))) kvtc_encode_small_batch_kernel(const KernelArgs args) {
     extern __shared__ uint4 smem[];
     if (blockIdx.x + 1u == gridDim.x) {
         if (threadIdx.x < 64) report_bad_job(args);
         return;
     }
-    if constexpr (EITHER) {
+    if constexpr (EITHER != 0) {
         uint32_t tiles = 0u;                                         // of the lane's jobs
         for (uint32_t j = threadIdx.x & 63u; j < (uint32_t)args.n_jobs; j += 64u) {
             const int n = args.jobs[j].n_tokens;
@@ -1003,7 +1004,7 @@ __global__ void KVTC_SHORT_BOUNDS(EITHER && sizeof(XT) == 4 ? 2 : NTW) kvtc_enco
             const ShortTable<false, kEncPartTile> t(args);
             TileRef tr;
             PlanEnc P;
-            if (t.find(args, number / split, tr) && short_tile<0, true, kEncPartTile>(args, 0u, tr, P)) part_code<XT, 16>(P, tr, args, (int)(number % split), smem);
+            if (t.find(args, number / split, tr) && short_tile<0, true, kEncPartTile>(args, 0u, tr, P)) part_code<XT, EITHER == 2 ? 32 : 16>(P, tr, args, (int)(number % split), smem);
             return;
         }
     }
@@ -1022,7 +1023,7 @@ __global__ void KVTC_SHORT_BOUNDS(EITHER && sizeof(XT) == 4 ? 2 : NTW) kvtc_enco
         const uint32_t per_xcd = (t.total + 7u) / 8u;
         if (i >= per_xcd || !t.find(a, (blockIdx.x & 7u) * per_xcd + i, tr)) return;
         const bool last = i + (gridDim.x - 1u) / 8u >= per_xcd;       // (seen at the table of the next one it was half a microsecond)
-        if (short_tile<NTW, true>(a, 0u, tr, P)) short_tile_code<NTW, XT>(P, tr, a, smem);
+        if (short_tile<EITHER == 2 ? 0 : NTW, true>(a, 0u, tr, P)) short_tile_code<NTW, XT, EITHER != 2 ? short_ahead<NTW>() : NTW == 2 ? 16 : 8>(P, tr, a, smem);
         if (last) return;
     }
 }
@@ -1090,12 +1091,14 @@ hipError_t launch_encode(const KernelArgs& a, kvtc_dtype dtype, int key, int gri
 // times the jobs; ntw: coordinate tiles per wave (the plans' enc_short).
 hipError_t launch_encode_short(const KernelArgs& a, kvtc_dtype dtype, int ntw, int waves, int grid, size_t lds_bytes, hipStream_t stream) {
     const void* fn = nullptr;
-#define KVTC_X(NTW, XT) (a.enc_table ? reinterpret_cast<const void*>(&kvtc_encode_small_batch_kernel<NTW, XT, false>) : reinterpret_cast<const void*>(&kvtc_encode_short_kernel<NTW, XT>))
-    if (a.enc_part_most != 0 && ntw == 1) fn = dtype == KVTC_BF16 ? reinterpret_cast<const void*>(&kvtc_encode_small_batch_kernel<1, uint16_t, true>) : reinterpret_cast<const void*>(&kvtc_encode_small_batch_kernel<1, float, true>);
-    else if (a.enc_part_most != 0) fn = nullptr;
-    else if (ntw == 1) fn = dtype == KVTC_BF16 ? KVTC_X(1, uint16_t) : KVTC_X(1, float);
-    else if (ntw == 2) fn = dtype == KVTC_BF16 ? KVTC_X(2, uint16_t) : KVTC_X(2, float);
+#define KVTC_X(NTW, XT, EITHER) reinterpret_cast<const void*>(&kvtc_encode_small_batch_kernel<NTW, XT, EITHER>)
+#define KVTC_Y(NTW, XT) (a.enc_table ? KVTC_X(NTW, XT, 0) : reinterpret_cast<const void*>(&kvtc_encode_short_kernel<NTW, XT>))
+    if (a.enc_part_most != 0 && ntw == 1) fn = dtype == KVTC_BF16 ? KVTC_X(1, uint16_t, 1) : KVTC_X(1, float, 1);
+    else if (a.enc_part_most != 0) fn = dtype == KVTC_BF16 && waves == 4 ? (ntw == 2 ? KVTC_X(2, uint16_t, 2) : KVTC_X(3, uint16_t, 2)) : nullptr;
+    else if (ntw == 1) fn = dtype == KVTC_BF16 ? KVTC_Y(1, uint16_t) : KVTC_Y(1, float);
+    else if (ntw == 2) fn = dtype == KVTC_BF16 ? KVTC_Y(2, uint16_t) : KVTC_Y(2, float);
 #undef KVTC_X
+#undef KVTC_Y
     if (!fn || waves < 2 || waves * 64 > kShortThreads) return hipErrorInvalidValue;
     hipError_t e = allow_full_lds(fn);
     if (e != hipSuccess) return e;
