@@ -980,15 +980,16 @@ static kvtc_status launch_encode_jobs(const char* who, const EncodeLaunches& l, 
     // two coordinate tiles to a wave, one workgroup of which a compute unit has room for, are faster by parts in two rounds as well.
     // (us, the short-job launch and by parts with a workgroup for each share.  At once: 64 tensors at 16x, room for 32 tokens each, all of 31 12.6 and 9.8, 48 and 16 in
     // turn 13.1 and 9.7; 256 heads of 16 to 48 6.4 and 5.6.  Not all at once: 128 of 256 features, 100 and 20 in turn, 7.1 and 9.5; 64 at 16x 15.1 and 16.8; in fp32 of 48 and
-    // 16 in turn 17.8 and 18.9; 128 at 40x, one share each, of 64 12.1 and 10.7, of 32 to 96, 312 shares, 12.0 and 13.1; 64 of 512 coordinates, 100 and 20 in turn, 20.2 and 18.7.
+    // 16 in turn 17.8 and 18.9; 128 at 40x, one share each, of 64 12.3 and 11.7, of 32 to 96, 312 shares, 12.0 and 13.1 (counted 12.6); 64 of 512 coordinates, 100 and 20 in turn, 20.2 and 18.7.
     // Counted on the device: 64 at 16x, room for 64 tokens each, 16 coded, 12.0, 9.2 and 9.3, of 32 to 96 15.2, 16.8 and 15.5; in fp32 64 of 16 12.8 12.0 11.7, of 48 and 16 in turn 17.8, 18.9 and 17.3.)
     enum { kNot, kParts, kEither } by = kNot;
     const size_t cus = (size_t)compute_units(), places = (size_t)part_places(l.part.waves, l.part.lds);
     const PartShares ps = l.part.split > 0 ? part_shares(a.cap, l.min_rec_dwords, a.n_jobs, l.part.split) : PartShares{};
     const size_t at_once = l.part.split == 1 && l.max_p > 512 ? cus : places;
-    if (l.part.split > 0 && a.n_jobs <= kShortTableJobs && ps.equal <= (ps.each > kEncPartTile ? at_once : std::min(at_once, cus))) {
-        const bool either = l.part.split > 2 && l.shrt[2].waves == 0 && grid != 0 && (dtype == KVTC_BF16 || places == cus);
-        if ((either ? ps.most : ps.mixed) <= at_once || l.shrt[1].waves == 0) by = kParts;
+    const bool fours = dtype == KVTC_BF16 && l.part.waves == 4;        // (short-job kernels of one tile to a wave have ten of them at most)
+    if (l.part.split > 0 && a.n_jobs <= kShortTableJobs && ps.equal <= (ps.each > kEncPartTile ? places : std::min(at_once, cus))) {
+        const bool either = l.shrt[2].waves == 0 && grid != 0 && (l.part.split > 2 ? dtype == KVTC_BF16 || places == cus : fours && l.max_p > 512);
+        if ((either ? ps.most : std::max(ps.equal, ps.mixed)) <= at_once || l.shrt[1].waves == 0) by = kParts;
         else if (either) by = kEither;
     }
     hipError_t e = hipSuccess;
@@ -1001,10 +1002,9 @@ static kvtc_status launch_encode_jobs(const char* who, const EncodeLaunches& l, 
         a.enc_table = 1;
         a.enc_max_tokens = (int32_t)(a.cap / ((size_t)l.min_rec_dwords * 4));
         const int lds = std::max(l.part.lds, l.shrt[1].lds);
-        const bool fours = dtype == KVTC_BF16 && l.part.waves == 4;        // (short-job kernels of one tile to a wave have ten of them at most)
         const int waves = fours ? 4 : std::max(l.part.waves, l.shrt[1].waves);
-        a.enc_part_most = fours ? part_places(4, lds) : (int)(short_pairs(1, waves, lds) ? cus * 3 / 2 : cus);
-        e = launch_encode_short(a, dtype, !fours ? 1 : l.shrt[1].waves <= 8 ? 2 : 3, waves, std::max(grid, whole_shares((size_t)a.enc_part_most)), (size_t)lds, st);
+        a.enc_part_most = fours ? std::min(part_places(4, lds), (int)at_once) : (int)(short_pairs(1, waves, lds) ? cus * 3 / 2 : cus);
+        e = launch_encode_short(a, dtype, !fours || l.shrt[1].waves <= 4 ? 1 : l.shrt[1].waves <= 8 ? 2 : 3, waves, std::max(grid, whole_shares((size_t)a.enc_part_most)), (size_t)lds, st);
     } else if (grid != 0) {
         // few tokens in all: one round of the short-job kernel
         a.enc_table = 1;

@@ -982,7 +982,7 @@ __global__ void KVTC_SHORT_BOUNDS(NTW) kvtc_encode_short_kernel(const KernelArgs
     if (short_tile<NTW, false>(a, blockIdx.x, tr, P)) short_tile_code<NTW, XT>(P, tr, a, smem);
 }
 // EITHER: by parts where the jobs, whose lengths only the device knows, then are one round of workgroups.  With the launch's waves and registers, 16 k-steps ahead (1); of plans
-// whose shares are of up to four coordinate tiles, with the four waves and 32 k-steps of the parts, and the short jobs' tiles by two or three to a wave (2).  (An append step of
+// whose shares are of up to four coordinate tiles, with the four waves and 32 k-steps of the parts, and the short jobs' tiles by one to three to a wave (2).  (An append step of
 // 64 tensors at 16x with room for four: 12.0 us as the short-job kernel, 10.5 (1), 9.3 (2), 9.2 in a launch of its own that does not count; of 32 to 96 tokens 15.3, 15.7, 15.5 and 16.8.)
 template <int NTW, typename XT, int EITHER>
 __global__ void __launch_bounds__(EITHER == 2 ? 256 : kShortThreads) __attribute__((amdgpu_waves_per_eu(EITHER == 2 ? 2 : NTW == 1 && !(EITHER == 1 && sizeof(XT) == 4) ? 4 : 3))) kvtc_encode_small_batch_kernel(const KernelArgs args) {
@@ -1023,7 +1023,7 @@ __global__ void __launch_bounds__(EITHER == 2 ? 256 : kShortThreads) __attribute
         const uint32_t per_xcd = (t.total + 7u) / 8u;
         if (i >= per_xcd || !t.find(a, (blockIdx.x & 7u) * per_xcd + i, tr)) return;
         const bool last = i + (gridDim.x - 1u) / 8u >= per_xcd;       // (seen at the table of the next one it was half a microsecond)
-        if (short_tile<EITHER == 2 ? 0 : NTW, true>(a, 0u, tr, P)) short_tile_code<NTW, XT, EITHER != 2 ? short_ahead<NTW>() : NTW == 2 ? 16 : 8>(P, tr, a, smem);
+        if (short_tile<EITHER == 2 ? 0 : NTW, true>(a, 0u, tr, P)) short_tile_code<NTW, XT, EITHER != 2 || NTW == 1 ? short_ahead<NTW>() : NTW == 2 ? 16 : 8>(P, tr, a, smem);
         if (last) return;
     }
 }
@@ -1093,8 +1093,8 @@ hipError_t launch_encode_short(const KernelArgs& a, kvtc_dtype dtype, int ntw, i
     const void* fn = nullptr;
 #define KVTC_X(NTW, XT, EITHER) reinterpret_cast<const void*>(&kvtc_encode_small_batch_kernel<NTW, XT, EITHER>)
 #define KVTC_Y(NTW, XT) (a.enc_table ? KVTC_X(NTW, XT, 0) : reinterpret_cast<const void*>(&kvtc_encode_short_kernel<NTW, XT>))
-    if (a.enc_part_most != 0 && ntw == 1) fn = dtype == KVTC_BF16 ? KVTC_X(1, uint16_t, 1) : KVTC_X(1, float, 1);
-    else if (a.enc_part_most != 0) fn = dtype == KVTC_BF16 && waves == 4 ? (ntw == 2 ? KVTC_X(2, uint16_t, 2) : KVTC_X(3, uint16_t, 2)) : nullptr;
+    if (a.enc_part_most != 0 && dtype == KVTC_BF16 && waves == 4) fn = ntw == 1 ? KVTC_X(1, uint16_t, 2) : ntw == 2 ? KVTC_X(2, uint16_t, 2) : KVTC_X(3, uint16_t, 2);
+    else if (a.enc_part_most != 0) fn = ntw != 1 ? nullptr : dtype == KVTC_BF16 ? KVTC_X(1, uint16_t, 1) : KVTC_X(1, float, 1);
     else if (ntw == 1) fn = dtype == KVTC_BF16 ? KVTC_Y(1, uint16_t) : KVTC_Y(1, float);
     else if (ntw == 2) fn = dtype == KVTC_BF16 ? KVTC_Y(2, uint16_t) : KVTC_Y(2, float);
 #undef KVTC_X

@@ -90,13 +90,13 @@ def test_features_on_both_sides_of_what_is_fetched_ahead(p, dtype):
 @pytest.mark.parametrize("dtype,jobs_of,lens,room", [
     (kv.KVTC_BF16, 4, [16], 4), (kv.KVTC_BF16, 4, [17, 0, 33, 5], 4),                     # room for 64 tokens a job: a share for every compute unit, and fewer
     (kv.KVTC_BF16, 4, [48], 1), (kv.KVTC_BF16, 4, [100, 20, 64, 1], 1),                   # no room left: more shares than run at once
-    (kv.KVTC_F32, 16, [40, 7, 64, 1], 4), (kv.KVTC_F32, 16, [97, 129], 1),
+    (kv.KVTC_F32, 16, [40, 7, 64, 1], 4), (kv.KVTC_F32, 16, [97, 129], 1), (kv.KVTC_BF16, 2, [40, 64], 1),      # (the last: of the plan of one share)
 ])
-@pytest.mark.parametrize("groups", [[(16, 8), (16, 6), (80, 4), (64, 3), (64, 2)], [(16, 8), (32, 6), (64, 4), (96, 3), (64, 2)], [(16, 8), (96, 5), (144, 3), (16, 2)]])
+@pytest.mark.parametrize("groups", [[(16, 8), (16, 6), (80, 4), (64, 3), (64, 2)], [(16, 8), (32, 6), (64, 4), (96, 3), (64, 2)], [(16, 8), (96, 5), (144, 3), (16, 2)], [(16, 6), (80, 3)]])
 def test_small_batches_whose_form_the_jobs_lengths_decide(dtype, jobs_of, lens, room, groups):
     """Batches that may be more shares than run at once: the kernel that counts them, on both sides of its line, in a buffer of just their records
     and in a roomy one, and as a job more or fewer for the launches on either side of it; two, three and one coordinate tile to a wave of the short jobs'
-    form (plans of 8 and 10 tiles with shares of up to four, and one with a share of five).  The bulk kernels' bits."""
+    form (plans of 8 and 10 tiles with shares of up to four, one with a share of five, and one of a single share).  The bulk kernels' bits."""
     p = 1024
     plan = _gpu_plan(_manual(p, groups, 9))
     R, n_bulk = plan.record_bytes, bulk_tokens()
